@@ -11,10 +11,17 @@
 // (group stride 0) and the weight-gradient product contracts over the stacked minibatches of all
 // workers, M = d_{l-1}, N = d_l, Kc = N B, updating the average in place.
 //
-// A workgroup is 4 wavefronts (8 on the widest tile); each wavefront owns TM x TN accumulator tiles of 32x32
-// (v_mfma_f32_32x32x16_bf16 or v_mfma_f32_32x32x2_f32).  Operand tiles are staged through LDS in
-// their natural memory orientation with 16-byte global loads; an operand whose contraction
-// index is the strided one is transposed while its MFMA fragments are read out of LDS.
+// Operand tiles go from memory to LDS without passing through registers: every wavefront requests
+// 1024-byte pieces (64 lanes x 16 bytes) that land at consecutive LDS addresses, S tiles deep, and
+// the wait for a tile leaves the requests of the following tiles in flight.  A piece cannot be padded
+// on its way, so bank conflicts are avoided by permuting WHICH 16 bytes a lane requests (below).  A
+// tile is 128 bytes deep along the contraction (64 bf16 or 32 fp32 elements); an operand whose
+// contraction index is the strided one is transposed while its MFMA fragments are read out of LDS.
+// The wavefronts of a workgroup are a WM x WN grid over the output tile times WK shares of the
+// contraction: larger blocks per wavefront read fewer LDS bytes per matrix instruction (the bound of
+// the large bf16 products), and a small output tile still occupies several matrix cores (the bound of
+// the small fp32 products, whose instructions are 8 times as slow).  The shares are added in order
+// when the output tile leaves through LDS.
 #include <atomic>
 #include <type_traits>
 
@@ -26,147 +33,18 @@ enum { OP_CONTIG = 0, OP_TRANS = 1 };
 
 struct TF32 {
   using elem = float;
-  using frag = float;
-  static constexpr int V = 4;        // elements per 16-byte vector
-  static constexpr int KSTEP = 2;    // contraction depth of one MFMA
-  static constexpr int BK = 32;      // contraction depth of one LDS tile
-  static constexpr int PADC = 1;
-  static constexpr int PADT = 0;     // row padding of a transposed tile
   static constexpr bool kBf16 = false;
 };
 struct TBF16 {
   using elem = uint16_t;
-  using frag = bf16x8_t;
-  static constexpr int V = 8;
-  static constexpr int KSTEP = 16;
-#ifndef PRSGD_BF16_BK
-#define PRSGD_BF16_BK 64
-#endif
-  static constexpr int BK = PRSGD_BF16_BK;
-  static constexpr int PADC = 8;
-  // A transpose read (ds_read_b64_tr_b16) is served 32 lanes at a time: 4 consecutive contraction rows
-  // times 16 dwords each.  With a row stride of 16 dwords modulo 32 (32 bf16 modulo 64) they fall on
-  // 64 distinct banks; the earlier padding of 16 lost 17 % (one transposed operand) to 37 % (two) of the
-  // LDS cycles to bank conflicts, this one none (SQ_LDS_BANK_CONFLICT).
-  static constexpr int PADT = 32;
   static constexpr bool kBf16 = true;
 };
+constexpr int kTileBytes = 128;        // depth of a tile along the contraction
+constexpr int kSlices = 4;             // 32-byte slices of it, one fragment step each
 
-template <typename T> __device__ __forceinline__ typename T::elem to_elem(float v);
-template <> __device__ __forceinline__ float to_elem<TF32>(float v) { return v; }
-template <> __device__ __forceinline__ uint16_t to_elem<TBF16>(float v) { return f32_to_bf16_rne(v); }
-template <typename T> __device__ __forceinline__ float from_elem(typename T::elem v);
-template <> __device__ __forceinline__ float from_elem<TF32>(float v) { return v; }
-template <> __device__ __forceinline__ float from_elem<TBF16>(uint16_t v) { return bf16_to_f32(v); }
-
-// LDS footprint (elements) of a ROWS x BK operand tile.
-template <typename T, int ROWS, int KIND> struct TileShape {
-  static constexpr int kStride = (KIND == OP_CONTIG) ? (T::BK + T::PADC) : (ROWS + T::PADT);
-  static constexpr int kElems = (KIND == OP_CONTIG) ? ROWS * kStride : T::BK * kStride;
-};
-
-// Moves a ROWS x BK operand tile from global memory to LDS in two halves so that the global
-// loads of tile k+1 can be in flight while tile k is multiplied: fetch() fills registers with
-// 16-byte vectors (zero outside the operand), stash() writes them to LDS.
-//   OP_CONTIG: element (r, c) at src[r * ld + c]; LDS [ROWS][BK + PADC]
-//   OP_TRANS : element (r, c) at src[c * ld + r]; LDS [BK][ROWS + PADT]
-// Vector loads run along the memory-contiguous index; a vector that starts inside the logical
-// extent may run into the zero padding every buffer carries up to a multiple of 8 elements.
-template <typename T, int ROWS, int KIND, int NTHR = kThreads> struct TileIO {
-  using E = typename T::elem;
-  static constexpr int V = T::V, BK = T::BK;
-  static constexpr int VECS = ROWS * BK / V;
-  static constexpr int NPT = VECS / NTHR;                // vectors per thread
-  static_assert(VECS % NTHR == 0, "tile must split evenly over the workgroup");
-  static constexpr int STRIDE = TileShape<T, ROWS, KIND>::kStride;
-
-  // Returns the validity mask of the NPT vectors (bit q set = inside the operand).
-  __device__ static __forceinline__ uint32_t fetch(uint4 (&reg)[NPT], const E* __restrict__ src, int ld,
-                                                   int row0, int n_rows, int c0, int n_c, int tid) {
-    uint32_t mask = 0;
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-      const int v = q * NTHR + tid;
-      // Branch-free: an out-of-range vector loads element (0, 0) instead and is zeroed when it
-      // is written to LDS, so nothing waits on the load here and the loads stay countable for
-      // the compiler's vmcnt bookkeeping across the pipeline.
-      bool ok;
-      size_t off;
-      if (KIND == OP_CONTIG) {
-        constexpr int VPR = BK / V;
-        const int row = row0 + v / VPR, c = c0 + (v % VPR) * V;
-        ok = row < n_rows && c < n_c;
-        off = (size_t)row * ld + c;
-      } else {
-        constexpr int VPC = ROWS / V;
-        const int cc = c0 + v / VPC, row = row0 + (v % VPC) * V;
-        ok = cc < n_c && row < n_rows;
-        off = (size_t)cc * ld + row;
-      }
-      reg[q] = *reinterpret_cast<const uint4*>(src + (ok ? off : (size_t)0));
-      mask |= (ok ? 1u : 0u) << q;
-    }
-    return mask;
-  }
-
-  __device__ static __forceinline__ void stash(E* __restrict__ lds, const uint4 (&reg_in)[NPT],
-                                               uint32_t mask, int tid) {
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-      const int v = q * NTHR + tid;
-      const uint32_t keep = 0u - ((mask >> q) & 1u);      // all ones inside the operand, else zero
-      uint4 reg[1];
-      reg[0] = make_uint4(reg_in[q].x & keep, reg_in[q].y & keep, reg_in[q].z & keep, reg_in[q].w & keep);
-      if (KIND == OP_CONTIG) {
-        constexpr int VPR = BK / V;
-        E* dst = lds + (v / VPR) * STRIDE + (v % VPR) * V;
-        if (T::kBf16) {
-          *reinterpret_cast<uint4*>(dst) = reg[0];
-        } else {                                   // odd row stride: four 4-byte stores
-          uint32_t* d32 = reinterpret_cast<uint32_t*>(dst);
-          d32[0] = reg[0].x; d32[1] = reg[0].y; d32[2] = reg[0].z; d32[3] = reg[0].w;
-        }
-      } else {
-        constexpr int VPC = ROWS / V;
-        *reinterpret_cast<uint4*>(lds + (v / VPC) * STRIDE + (v % VPC) * V) = reg[0];
-      }
-    }
-  }
-};
-
-// MFMA operand fragment of lane (r = lane % 32, kb = lane / 32) for tile row `row` and the
-// kk-th KSTEP slice.  A and B fragments use the same (kb, e) -> contraction index map, which is
-// all the instruction needs for the product to be the plain sum over c.
-template <int ROWS, int KIND>
-__device__ __forceinline__ float load_frag_f32(const float* __restrict__ lds, int row, int kk, int kb) {
-  if (KIND == OP_CONTIG) return lds[row * TileShape<TF32, ROWS, KIND>::kStride + kk * 2 + kb];
-  return lds[(kk * 2 + kb) * TileShape<TF32, ROWS, KIND>::kStride + row];
-}
-// bf16 fragment: one 16-byte read of a contraction-contiguous tile, the LDS transpose load for a
-// tile stored with the contraction index as its row.
-template <int ROWS, int KIND>
-__device__ __forceinline__ bf16x8_t load_frag_bf16(const uint16_t* __restrict__ lds, int row_block,
-                                                   int kk, int lane) {
-  constexpr int STRIDE = TileShape<TBF16, ROWS, KIND>::kStride;
-  if (KIND == OP_CONTIG) return frag_contig(lds, STRIDE, row_block, kk, lane);
-  return frag_trans(lds, STRIDE, row_block, kk, lane);
-}
-
-__device__ __forceinline__ f32x16_t mfma(float a, float b, f32x16_t c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x16_t mfma(bf16x8_t a, bf16x8_t b, f32x16_t c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-// A-operand fragment of all ones: with it one matrix instruction yields the column sums of the
-// B fragment (every row of the 32 x 32 result holds them).
-template <typename F> __device__ __forceinline__ F ones_frag();
-template <> __device__ __forceinline__ float ones_frag<float>() { return 1.0f; }
-template <> __device__ __forceinline__ bf16x8_t ones_frag<bf16x8_t>() {
-  const u16x8_t u = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
-  return __builtin_bit_cast(bf16x8_t, u);
-}
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float act_fwd(float z, int act) {
   return act == PRSGD_TANH ? tanhf(z) : fmaxf(z, 0.0f);
@@ -175,76 +53,253 @@ __device__ __forceinline__ float act_bwd_from_h(float h, int act) {
   return act == PRSGD_TANH ? (1.0f - h * h) : (h > 0.0f ? 1.0f : 0.0f);
 }
 
-// DEEP: the two-stage, four-register-set pipeline (long contractions); otherwise a single LDS
-// stage with a one-tile prefetch (the per-replica weight-gradient product: one or two tiles).
-template <typename T, int BM, int BN, int WM, int WN, int AKIND, int BKIND,
-          bool DEEP = !(AKIND == OP_TRANS && BKIND == OP_TRANS)>
-__global__ __launch_bounds__(64 * WM * WN) void grouped_gemm_kernel(GemmArgs p) {
+// 64 x 16 bytes from base + per-lane offset to LDS [m0, m0 + 1024), lane order.  Not visible to the
+// compiler's wait counts: the pipeline below waits by itself (wait_tiles), everything the compiler
+// waits for on its own is then waited for at least as long as it needs.  Nothing else in this file
+// uses m0 (a reserved register, which cannot be listed as clobbered).
+__device__ __forceinline__ void load_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
+  // both are the same in every lane; said explicitly, they end up in scalar registers
+  const uint64_t u = (uint64_t)(uintptr_t)base_any;
+  const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)u) |
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32);
+  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+}
+
+// One operand tile of ROWS output rows (or columns) in LDS, and the requests that fill it.
+//   OP_CONTIG: element (r, c) at src[r * ld + c]; LDS [ROWS][128 bytes], the 16-byte chunk q of row r
+//     at chunk q ^ (r & 7): eight consecutive rows then read one chunk each from all banks.
+//   OP_TRANS : element (r, c) at src[c * ld + r]; LDS [depth][ROWS].  bf16: the transpose read takes
+//     32 consecutive elements (64 bytes) of four consecutive contraction rows at a time, so those
+//     64-byte segments are permuted within 256 bytes such that the four fall on different banks.
+// Rows past the operand are requested as copies of the last one (their results are not stored).
+template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
   using E = typename T::elem;
-  constexpr int NTHR = 64 * WM * WN;
-  using IOA = TileIO<T, BM, AKIND, NTHR>;
-  using IOB = TileIO<T, BN, BKIND, NTHR>;
-  constexpr int BK = T::BK;
-  constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
-  constexpr int A_ELEMS = TileShape<T, BM, AKIND>::kElems, B_ELEMS = TileShape<T, BN, BKIND>::kElems;
-  static_assert(WM * WN == 4 || WM * WN == 8, "4 or 8 wavefronts per workgroup");
-  static_assert(TM >= 1 && TN >= 1, "tile too small for the wavefront grid");
-  static_assert((A_ELEMS * sizeof(E)) % 16 == 0 && (B_ELEMS * sizeof(E)) % 16 == 0, "LDS alignment");
+  static constexpr int ES = (int)sizeof(E), BK = kTileBytes / ES, V = 16 / ES;
+  static constexpr int BYTES = ROWS * kTileBytes;
+  static constexpr int NPT = BYTES / 1024 / NWAVE;         // requests per wavefront and tile
+  static_assert(BYTES % (1024 * NWAVE) == 0, "a tile must split evenly over the wavefronts");
+  static constexpr int ROW_BYTES = KIND == OP_CONTIG ? kTileBytes : ROWS * ES;
+  static constexpr int CH = ROW_BYTES / 16;                // 16-byte chunks of an LDS row
 
-  // Workgroup -> (group, tile).  The hardware deals consecutive workgroups round-robin to the
-  // 8 XCDs; when the group count is a multiple of 8 all tiles of a group land on one XCD, so the
-  // group's activations and weight panel stay in that XCD's L2.
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  const int n_splits = p.k_splits > 1 ? p.k_splits : 1;     // contraction ranges per output tile
-  const int tiles = tiles_m * tiles_n * n_splits;
-  int g, tile;
-  if ((p.n_groups & 7) == 0) {
-    const int slot = blockIdx.x >> 3;
-    g = (blockIdx.x & 7) + 8 * (slot / tiles);
-    tile = slot % tiles;
-  } else {
-    g = blockIdx.x / tiles;
-    tile = blockIdx.x % tiles;
+  // permutation of the 64-byte segments of contraction row c (OP_TRANS)
+  __device__ static __forceinline__ int seg_xor(int c) {
+    if (!T::kBf16 || ROW_BYTES <= 64) return 0;
+    return ROW_BYTES == 128 ? (c >> 1) & 1 : c & 3;
   }
-  const int ks = tile % n_splits;
-  tile /= n_splits;
-  if (p.worker_steps != nullptr && p.step >= p.worker_steps[g]) return;
-  const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  // Two LDS stages of each operand tile; the per-replica weight-gradient product (one or two
-  // contraction tiles in all) keeps a single stage so that more workgroups fit on a compute unit.
-  constexpr int kStages = DEEP ? 2 : 1;
-  E* const a_lds0 = reinterpret_cast<E*>(smem);
-  E* const b_lds0 = a_lds0 + kStages * A_ELEMS;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int lr32 = lane & 31, kb = lane >> 5;
-
-  const E* a_src = reinterpret_cast<const E*>(p.a) + (size_t)g * p.a_gs;
-  const E* b_src = reinterpret_cast<const E*>(p.b) + (size_t)g * p.b_gs;
-  // this workgroup's contraction range [k_lo, k_lo + Kc): whole tiles per split
-  int Kc = p.Kc;
-  if (n_splits > 1) {
-    const int per = ((p.Kc + BK - 1) / BK + n_splits - 1) / n_splits * BK;
-    const int k_lo = ks * per;
-    Kc = max(0, min(p.Kc - k_lo, per));
-    if (Kc > 0) {                                  // an empty range keeps valid base addresses
-      a_src += (AKIND == OP_CONTIG) ? (size_t)k_lo : (size_t)k_lo * p.lda;
-      b_src += (BKIND == OP_CONTIG) ? (size_t)k_lo : (size_t)k_lo * p.ldb;
+  // offsets (bytes from the tile's base address) of this lane's requests.  n_rows: rows of the operand
+  // from the tile's first; n_c: contraction elements from the tile's first (clamped like the rows)
+  __device__ static __forceinline__ void offsets(uint32_t (&off)[NPT], int ld, int n_rows, int n_c, int wave,
+                                                 int lane) {
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int chunk = (q * NWAVE + wave) * 64 + lane;    // position in the LDS tile
+      const int lr = chunk / CH, pos = chunk % CH;
+      if (KIND == OP_CONTIG) {
+        const int row = min(lr, n_rows - 1);
+        const int c = min((pos ^ (lr & 7)) * V, (n_c - 1) / V * V);
+        off[q] = (uint32_t)((size_t)row * ld + c) * ES;
+      } else {
+        const int c = min(lr, n_c - 1);
+        const int row = min(((((pos >> 2) ^ seg_xor(lr)) << 2) | (pos & 3)) * V, (n_rows - 1) / V * V);
+        off[q] = (uint32_t)((size_t)c * ld + row) * ES;
+      }
     }
   }
+  __device__ static __forceinline__ void request(const E* tile_base, const uint32_t (&off)[NPT], uint32_t lds_tile,
+                                                 int wave) {
+#pragma unroll
+    for (int q = 0; q < NPT; ++q)
+      load_to_lds(tile_base, off[q], lds_tile + (uint32_t)(q * NWAVE + wave) * 1024u);
+  }
+};
+
+// MFMA operand fragments of a 32-row block for the kk-th 32-byte slice.  Lane (r = lane % 32,
+// kb = lane / 32) holds contraction elements of row r; A and B fragments use the same assignment,
+// which is all the instruction needs for the product to be the plain sum over c.
+//   bf16: the eight elements 16 kk + 8 kb + 0..7 of one v_mfma_f32_32x32x16
+//   fp32: the four elements   8 kk + 4 kb + 0..3 of four v_mfma_f32_32x32x2
+template <typename T> struct Frag;
+template <> struct Frag<TBF16> { bf16x8_t v; };
+template <> struct Frag<TF32> { f32x4_t v; };
+
+template <typename T, int ROWS, int KIND, int NWAVE>
+__device__ __forceinline__ Frag<T> load_frag(const unsigned char* tile, int block, int kk, int lane) {
+  using IO = TileIO<T, ROWS, KIND, NWAVE>;
+  Frag<T> f;
+  const int r = lane & 31, kb = lane >> 5;
+  if constexpr (KIND == OP_CONTIG) {
+    const unsigned char* p = tile + (block * 32 + r) * kTileBytes + (((2 * kk + kb) ^ (r & 7)) << 4);
+    if constexpr (T::kBf16) f.v = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(p));
+    else f.v = *reinterpret_cast<const f32x4_t*>(p);
+  } else if constexpr (T::kBf16) {
+    // transpose read (see frag_trans): lane r of 16 addresses contraction row c0 + r/4, elements
+    // 4 (r%4) .. +3, and receives four consecutive contraction elements of element row r
+    typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
+    typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
+    const int g = lane >> 4, r16 = lane & 15;
+    const int c = kk * 16 + 8 * (g >> 1) + (r16 >> 2);
+    const unsigned char* p = tile + c * IO::ROW_BYTES + ((block ^ IO::seg_xor(r16 >> 2)) << 6) + 32 * (g & 1) +
+                             8 * (r16 & 3);
+    const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
+    const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * IO::ROW_BYTES));
+    f.v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  } else {
+    const unsigned char* p = tile + (8 * kk + 4 * kb) * IO::ROW_BYTES + (block * 32 + r) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f.v[e] = *reinterpret_cast<const float*>(p + e * IO::ROW_BYTES);
+  }
+  return f;
+}
+
+__device__ __forceinline__ f32x16_t mma(const Frag<TBF16>& a, const Frag<TBF16>& b, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t mma(const Frag<TF32>& a, const Frag<TF32>& b, f32x16_t c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e], b.v[e], c, 0, 0, 0);
+  return c;
+}
+// Fragment of all ones: as A operand every row of the 32 x 32 result holds the column sums of B.
+__device__ __forceinline__ void set_ones(Frag<TBF16>& f) {
+  const u16x8_t u = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
+  f.v = __builtin_bit_cast(bf16x8_t, u);
+}
+__device__ __forceinline__ void set_ones(Frag<TF32>& f) { f.v = (f32x4_t){1.0f, 1.0f, 1.0f, 1.0f}; }
+
+// Zeroes the contraction elements at and past n_c (the last tile of a ragged contraction; what was
+// requested there is some other element of the operand).
+__device__ __forceinline__ void mask_frag(Frag<TBF16>& f, int kk, int lane, int n_c) {
+  u32x4_t u = __builtin_bit_cast(u32x4_t, f.v);
+  const int c = 16 * kk + 8 * (lane >> 5);
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    u[e] &= (c + 2 * e < n_c ? 0xFFFFu : 0u) | (c + 2 * e + 1 < n_c ? 0xFFFF0000u : 0u);
+  f.v = __builtin_bit_cast(bf16x8_t, u);
+}
+__device__ __forceinline__ void mask_frag(Frag<TF32>& f, int kk, int lane, int n_c) {
+  const int c = 8 * kk + 4 * (lane >> 5);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) f.v[e] = c + e < n_c ? f.v[e] : 0.0f;
+}
+
+// Waits until all but the newest `ahead` tiles (PER requests each) have landed.
+template <int PER> __device__ __forceinline__ void wait_tiles(int ahead) {
+#define PRSGD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((n) * PER > 63 ? 63 : (n) * PER) : "memory")
+  switch (ahead) {
+    case 0: PRSGD_WAIT(0); break;
+    case 1: PRSGD_WAIT(1); break;
+    case 2: PRSGD_WAIT(2); break;
+    case 3: PRSGD_WAIT(3); break;
+    case 4: PRSGD_WAIT(4); break;
+    case 5: PRSGD_WAIT(5); break;
+    case 6: PRSGD_WAIT(6); break;
+    default: PRSGD_WAIT(7); break;
+  }
+#undef PRSGD_WAIT
+}
+
+template <typename T, int BM, int BN, int WK, int S> constexpr size_t gemm_lds_bytes() {
+  const size_t stages = (size_t)S * (BM + BN) * kTileBytes;
+  const size_t out = sizeof(float) * ((size_t)WK * BM * (BN + 4) + (size_t)WK * BN);
+  return stages > out ? stages : out;
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(GemmArgs p) {
+  using E = typename T::elem;
+  constexpr int NWAVE = WM * WN * WK, NTHR = 64 * NWAVE;
+  using IOA = TileIO<T, BM, AKIND, NWAVE>;
+  using IOB = TileIO<T, BN, BKIND, NWAVE>;
+  constexpr int BK = IOA::BK;
+  constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
+  constexpr int PER = IOA::NPT + IOB::NPT;
+  static_assert(TM >= 1 && TN >= 1, "tile too small for the wavefront grid");
+  static_assert(kSlices % WK == 0, "the slices of a tile must split evenly over the shares");
+  static_assert(S >= 2 && S <= 8 && PER * (S - 1) <= 63, "wait_tiles");
+
+  // Workgroup -> (group, tile).  The hardware deals consecutive workgroups round-robin to the 8
+  // XCDs; each XCD gets a contiguous range of the tiles, so that a group's activations and weight
+  // panel stay in that XCD's L2.  The order is by group; with one weight stream for all groups
+  // (b_gs == 0) by column tile first, and with a single group in 8-high strips of tiles.
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+  const int n_splits = p.k_splits > 1 ? p.k_splits : 1;     // contraction ranges per output tile
+  const int total = tiles_m * tiles_n * n_splits * p.n_groups;
+  const int xcd = blockIdx.x & 7;
+  int idx = xcd * (total >> 3) + min(xcd, total & 7) + (int)(blockIdx.x >> 3);
+  const int ks = idx % n_splits;
+  idx /= n_splits;
+  int g = 0, tm, tn;
+  if (p.n_groups == 1) {
+    const int strip = idx / (8 * tiles_n), in = idx - strip * 8 * tiles_n;
+    const int high = min(8, tiles_m - 8 * strip);
+    tm = 8 * strip + in % high;
+    tn = in / high;
+  } else if (p.b_gs == 0) {
+    tm = idx % tiles_m;
+    idx /= tiles_m;
+    g = idx % p.n_groups;
+    tn = idx / p.n_groups;
+  } else {
+    g = idx / (tiles_m * tiles_n);
+    idx -= g * tiles_m * tiles_n;
+    tm = idx / tiles_n;
+    tn = idx % tiles_n;
+  }
+  if (p.worker_steps != nullptr && p.step >= p.worker_steps[g]) return;
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  constexpr int STAGE = (BM + BN) * kTileBytes;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
+  const int lr32 = lane & 31, kb = lane >> 5;
+
+  // this workgroup's contraction range [k_lo, k_lo + Kc): whole tiles per split
+  int Kc = p.Kc, k_lo = 0;
+  if (n_splits > 1) {
+    const int per = ((p.Kc + BK - 1) / BK + n_splits - 1) / n_splits * BK;
+    k_lo = ks * per;
+    Kc = max(0, min(p.Kc - k_lo, per));
+    if (Kc == 0) k_lo = 0;
+  }
+  const E* a_src = reinterpret_cast<const E*>(p.a) + (size_t)g * p.a_gs +
+                   (AKIND == OP_CONTIG ? (size_t)m0 * p.lda + k_lo : (size_t)k_lo * p.lda + m0);
+  const E* b_src = reinterpret_cast<const E*>(p.b) + (size_t)g * p.b_gs +
+                   (BKIND == OP_CONTIG ? (size_t)n0 * p.ldb + k_lo : (size_t)k_lo * p.ldb + n0);
+  const size_t a_step = AKIND == OP_CONTIG ? (size_t)BK : (size_t)BK * p.lda;
+  const size_t b_step = BKIND == OP_CONTIG ? (size_t)BK : (size_t)BK * p.ldb;
   const size_t pg = (size_t)g * p.p_gs;
   constexpr bool kIsDw = (AKIND == OP_TRANS && BKIND == OP_TRANS);   // weight-gradient product
   const bool fused = kIsDw && (p.epi == EPI_DW_FUSED);
 
+  const int n_k = (Kc + BK - 1) / BK;
+  const int k_tail = Kc - (n_k - 1) * BK;                  // elements of the last tile
+  uint32_t a_off[IOA::NPT], b_off[IOB::NPT];
+  IOA::offsets(a_off, p.lda, p.M - m0, BK, wave, lane);
+  IOB::offsets(b_off, p.ldb, p.N - n0, BK, wave, lane);
+  auto request = [&](int j, int stage) __attribute__((always_inline)) {
+    const uint32_t lds_a = lds0 + (uint32_t)stage * STAGE, lds_b = lds_a + BM * kTileBytes;
+    if (j == n_k - 1 && k_tail < BK) {                     // nothing past the operands is touched
+      uint32_t a_o[IOA::NPT], b_o[IOB::NPT];
+      IOA::offsets(a_o, p.lda, p.M - m0, k_tail, wave, lane);
+      IOB::offsets(b_o, p.ldb, p.N - n0, k_tail, wave, lane);
+      IOA::request(a_src + (size_t)j * a_step, a_o, lds_a, wave);
+      IOB::request(b_src + (size_t)j * b_step, b_o, lds_b, wave);
+    } else {
+      IOA::request(a_src + (size_t)j * a_step, a_off, lds_a, wave);
+      IOB::request(b_src + (size_t)j * b_step, b_off, lds_b, wave);
+    }
+  };
+
   // Weight-update epilogue: the output tile leaves through LDS in row-major order, one 16-byte
-  // vector per lane (EV vectors per thread).  Start streaming the old weights in that layout now,
-  // they are not needed until the products are done.
-  typedef float f32x4_t __attribute__((ext_vector_type(4)));
-  constexpr int SC = BN + 8;                               // LDS row stride of the output tile (floats)
+  // vector per lane (EV vectors per thread).  The old weights are requested in that layout before
+  // the products.
+  constexpr int SC = BN + 4;                               // LDS row stride of the output tile (floats)
   constexpr int VPR_C = BN / 4, ROWS_PER_PASS = NTHR / VPR_C, EV = kIsDw ? BM / ROWS_PER_PASS : 1;
   static_assert(!kIsDw || (NTHR % VPR_C == 0 && BM % ROWS_PER_PASS == 0), "output tile must split evenly");
   const int e_row = tid / VPR_C, e_col = 4 * (tid % VPR_C);
@@ -259,6 +314,11 @@ __global__ __launch_bounds__(64 * WM * WN) void grouped_gemm_kernel(GemmArgs p) 
       w_old[q] = p.streaming ? __builtin_nontemporal_load(wp) : *wp;
     }
   }
+
+  // ... and the old bias, by the workgroups of the first row band (one column per thread)
+  static_assert(!kIsDw || BN <= NTHR, "one bias column per thread");
+  const bool bias_thread = kIsDw && m0 == 0 && tid < BN && n0 + tid < p.N;
+  const float b_old = fused && bias_thread ? p.params[pg + p.b_off + n0 + tid] : 0.0f;
 
   f32x16_t acc[TM][TN];
 #pragma unroll
@@ -277,145 +337,126 @@ __global__ __launch_bounds__(64 * WM * WN) void grouped_gemm_kernel(GemmArgs p) 
 #pragma unroll
     for (int v = 0; v < 16; ++v) accb[j][v] = 0.0f;
 
-  // Software pipeline: two LDS stages and R register sets, so that the global loads of tiles
-  // it+2 .. it+1+R are all in flight while tile `it` is multiplied -- one tile of compute is far
-  // shorter than the HBM latency it has to hide, and a launch has few workgroups per compute unit.
-  // Tile j (j >= 1) travels through register set j % R.  The per-replica weight-gradient product
-  // contracts over the minibatch only (one or two tiles): it keeps a single LDS stage and a
-  // one-tile prefetch and spends its registers on the streamed weights instead.
-  constexpr bool kDeep = DEEP;
-  constexpr int R = kDeep ? 4 : 1;
-  const int n_k = (Kc + BK - 1) / BK;
-  uint4 a_r[R][IOA::NPT], b_r[R][IOB::NPT];
-  uint32_t a_m[R], b_m[R];                           // validity masks of the register sets
+  // Software pipeline over S LDS stages and two fragment sets.  A wavefront reads the fragments of
+  // the next slice while the matrix instructions of the current one run; before it reads the first
+  // slice of the next tile it waits for its own requests of that tile and meets the others: then the
+  // tile has landed for all, and nobody reads the current tile any more (the fragments have arrived,
+  // lgkmcnt(0)), so that its stage takes tile it + S.  The matrix instructions of the last slice
+  // are issued after that meeting and run over the latency of the new fragments.
+  constexpr int KW = kSlices / WK;                         // slices of this wavefront's share of a tile
+  Frag<T> af[2][TM], bf[2][TN];
+  auto load = [&](int stage, int u, int set) __attribute__((always_inline)) {
+    const unsigned char* a_t = smem + stage * STAGE;
+    const unsigned char* b_t = a_t + BM * kTileBytes;
+    const int kk = wk * KW + u;
 #pragma unroll
-  for (int r = 0; r < R; ++r) { a_m[r] = 0; b_m[r] = 0; }
-  a_m[0] = IOA::fetch(a_r[0], a_src, p.lda, m0, p.M, 0, Kc, tid);
-  b_m[0] = IOB::fetch(b_r[0], b_src, p.ldb, n0, p.N, 0, Kc, tid);
-  IOA::stash(a_lds0, a_r[0], a_m[0], tid);
-  IOB::stash(b_lds0, b_r[0], b_m[0], tid);
-  if constexpr (kDeep) {
-    // Unconditional: a tile past the end of the contraction is fetched masked (all vectors read
-    // element (0, 0) and are zeroed on the way to LDS).  Straight-line code keeps the number of
-    // loads in flight the same on every path, which the wait-count bookkeeping needs.
+    for (int i = 0; i < TM; ++i) af[set][i] = load_frag<T, BM, AKIND, NWAVE>(a_t, wm * TM + i, kk, lane);
 #pragma unroll
-    for (int j = 1; j <= R; ++j) {
-      a_m[j % R] = IOA::fetch(a_r[j % R], a_src, p.lda, m0, p.M, j * BK, Kc, tid);
-      b_m[j % R] = IOB::fetch(b_r[j % R], b_src, p.ldb, n0, p.N, j * BK, Kc, tid);
-    }
-  }
-  __syncthreads();
-
-  auto compute = [&](int cur) {
-    const E* a_cur = a_lds0 + cur * A_ELEMS;
-    const E* b_cur = b_lds0 + cur * B_ELEMS;
-    constexpr int KK = BK / T::KSTEP;
-    // fragments of contraction step kk + 1 are read from LDS while the matrix instructions of
-    // step kk run: two register sets, filled alternately (reading further ahead measured no faster)
-    typename T::frag af[2][TM], bf[2][TN];
-    auto load_frags = [&](int kk, int set) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int rb_ = (wm * TM + i) * 32;
-        if constexpr (T::kBf16) af[set][i] = load_frag_bf16<BM, AKIND>(a_cur, rb_, kk, lane);
-        else af[set][i] = load_frag_f32<BM, AKIND>(a_cur, rb_ + lr32, kk, kb);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int rb_ = (wn * TN + j) * 32;
-        if constexpr (T::kBf16) bf[set][j] = load_frag_bf16<BN, BKIND>(b_cur, rb_, kk, lane);
-        else bf[set][j] = load_frag_f32<BN, BKIND>(b_cur, rb_ + lr32, kk, kb);
-      }
-    };
-    load_frags(0, 0);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      if (kk + 1 < KK) load_frags(kk + 1, (kk + 1) & 1);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma(af[kk & 1][i], bf[kk & 1][j], acc[i][j]);
-      if constexpr (kIsDw) {
-        if (bias_wave) {               // rows beyond Kc were zero-filled in LDS
-#pragma unroll
-          for (int j = 0; j < TN; ++j) accb[j] = mfma(ones_frag<typename T::frag>(), bf[kk & 1][j], accb[j]);
-        }
-      }
-    }
+    for (int j = 0; j < TN; ++j) bf[set][j] = load_frag<T, BN, BKIND, NWAVE>(b_t, wn * TN + j, kk, lane);
+    __builtin_amdgcn_sched_barrier(0);                     // ahead of the matrix instructions below
   };
-  if constexpr (kDeep) {
-    // One pipeline step on tile `it` (it % R == U): multiply the LDS stage it & 1, move tile
-    // it+1 from its register set to the other stage, refill that set with tile it+1+R.
-    // Straight-line code without a single conditional load: the hardware counts outstanding
-    // memory operations in issue order, and the compiler can only leave the loads of the other
-    // register sets in flight across a step if their number is the same on every path (a
-    // conditional prologue or drain loop made it wait for ALL of them once per R steps).
-    auto step = [&](int it, auto u_tag) {
-      constexpr int U = decltype(u_tag)::value;
-      constexpr int SET = (U + 1) % R, CUR = U & 1;
-      compute(CUR);
-      IOA::stash(a_lds0 + (CUR ^ 1) * A_ELEMS, a_r[SET], a_m[SET], tid);
-      IOB::stash(b_lds0 + (CUR ^ 1) * B_ELEMS, b_r[SET], b_m[SET], tid);
-      a_m[SET] = IOA::fetch(a_r[SET], a_src, p.lda, m0, p.M, (it + 1 + R) * BK, Kc, tid);
-      b_m[SET] = IOB::fetch(b_r[SET], b_src, p.ldb, n0, p.N, (it + 1 + R) * BK, Kc, tid);
-      __syncthreads();
-    };
-    static_assert(R == 4, "the unrolled pipeline below is written for four register sets");
-    using std::integral_constant;
-    // Every group of R steps runs the straight-line form: tiles past the end arrive as zeros
-    // (masked fetch) and add nothing, at the cost of at most R - 1 empty steps per workgroup.
-    for (int it = 0; it < n_k; it += R) {
-      step(it, integral_constant<int, 0>{});
-      step(it + 1, integral_constant<int, 1>{});
-      step(it + 2, integral_constant<int, 2>{});
-      step(it + 3, integral_constant<int, 3>{});
+  auto multiply = [&](int u, int set, bool ragged) __attribute__((always_inline)) {
+    if (ragged) {
+      const int kk = wk * KW + u;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) mask_frag(af[set][i], kk, lane, k_tail);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) mask_frag(bf[set][j], kk, lane, k_tail);
     }
-  } else {
-    for (int it = 0; it < n_k; ++it) {         // single LDS stage, next tile prefetched in registers
-      const bool more = it + 1 < n_k;
-      if (more) {
-        a_m[0] = IOA::fetch(a_r[0], a_src, p.lda, m0, p.M, (it + 1) * BK, Kc, tid);
-        b_m[0] = IOB::fetch(b_r[0], b_src, p.ldb, n0, p.N, (it + 1) * BK, Kc, tid);
-      }
-      compute(0);
-      if (more) {
-        __syncthreads();
-        IOA::stash(a_lds0, a_r[0], a_m[0], tid);
-        IOB::stash(b_lds0, b_r[0], b_m[0], tid);
-        __syncthreads();
-      }
-    }
-  }
-
-  // ---- epilogue: accumulator element v of lane (lr32, kb) is C[8*(v/4) + 4*kb + v%4][lr32] ----
-  if constexpr (kIsDw) {
-    float* wbase = (fused ? p.params : p.grads) + pg + p.w_off;
-    // accumulators -> LDS (the operand stages are free now) -> row-major 16-byte accesses
-    float* c_lds = reinterpret_cast<float*>(smem);
-    __syncthreads();                                       // every wavefront is done with the last tile
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j) acc[i][j] = mma(af[set][i], bf[set][j], acc[i][j]);
+    if constexpr (kIsDw) {
+      if (bias_wave) {
+        Frag<T> ones;
+        set_ones(ones);
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          c_lds[((wm * TM + i) * 32 + 8 * (v / 4) + 4 * kb + (v % 4)) * SC + (wn * TN + j) * 32 + lr32] =
-              acc[i][j][v];
-    __syncthreads();
+        for (int j = 0; j < TN; ++j) accb[j] = mma(ones, bf[set][j], accb[j]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int it = 0, stage = 0;                                   // tile being multiplied, and its stage
+  // Tile `it`, whose first slice is in fragment set FIRST; ends with the first slice of tile it + 1
+  // in the set after its own last one (past the last tile: stale LDS contents, never multiplied).
+  auto tile_step = [&](auto first_tag) __attribute__((always_inline)) {
+    constexpr int FIRST = decltype(first_tag)::value;
+    const bool ragged = it == n_k - 1 && k_tail < BK;
+#pragma unroll
+    for (int u = 0; u + 1 < KW; ++u) {
+      load(stage, u + 1, (FIRST + u + 1) & 1);
+      multiply(u, (FIRST + u) & 1, ragged);
+    }
+    const int ahead = n_k - 2 - it;                        // tiles requested after tile it + 1
+    if (ahead >= S - 2) wait_tiles<PER>(S - 2); else wait_tiles<PER>(max(ahead, 0));
+    asm volatile("s_barrier" ::: "memory");
+    if (it + S < n_k) request(it + S, stage);
+    stage = stage + 1 == S ? 0 : stage + 1;
+    load(stage, 0, (FIRST + KW) & 1);
+    multiply(KW - 1, (FIRST + KW - 1) & 1, ragged);
+    ++it;
+  };
+  for (int j = 0; j < S && j < n_k; ++j) request(j, j);
+  if (n_k > 0) {
+    wait_tiles<PER>(min(S, n_k) - 1);
+    asm volatile("s_barrier" ::: "memory");
+    load(0, 0, 0);
+    for (;;) {
+      tile_step(std::integral_constant<int, 0>{});
+      if (it == n_k) break;
+      if constexpr ((KW & 1) != 0) {                       // the fragment sets swap roles every tile
+        tile_step(std::integral_constant<int, 1>{});
+        if (it == n_k) break;
+      }
+    }
+  }
+  __syncthreads();                                         // every wavefront is done with the last tile
+
+  // ---- epilogue: accumulator element v of lane (lr32, kb) is C[8*(v/4) + 4*kb + v%4][lr32]; the
+  // tile leaves through LDS (the operand stages are free now) in row-major vectors
+  float* c_lds = reinterpret_cast<float*>(smem);           // [WK][BM][SC]
+  float* cs_lds = c_lds + WK * BM * SC;                    // [WK][BN] column sums
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        c_lds[(wk * BM + (wm * TM + i) * 32 + 8 * (v / 4) + 4 * kb + (v % 4)) * SC + (wn * TN + j) * 32 + lr32] =
+            acc[i][j][v];
+  if constexpr (kIsDw) {
+    if (bias_wave && kb == 0) {       // row 0 of the ones product: lane lr32 holds column lr32
+#pragma unroll
+      for (int j = 0; j < TN; ++j) cs_lds[wk * BN + (wn * TN + j) * 32 + lr32] = accb[j][0];
+    }
+  }
+  __syncthreads();
+  auto c_read = [&](int r, int c) __attribute__((always_inline)) {
+    f32x4_t s = *reinterpret_cast<const f32x4_t*>(c_lds + r * SC + c);
+#pragma unroll
+    for (int w = 1; w < WK; ++w) {
+      const f32x4_t o = *reinterpret_cast<const f32x4_t*>(c_lds + (w * BM + r) * SC + c);
+      s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+    }
+    return s;
+  };
+
+  if constexpr (kIsDw) {
+    float* wbase = (fused ? p.params : p.grads) + pg + p.w_off;
 #pragma unroll
     for (int q = 0; q < EV; ++q) {
       const int r = q * ROWS_PER_PASS + e_row;
       const int m = m0 + r, n = n0 + e_col;
       if (m < p.M && n < p.N) {
-        const f32x4_t g = *reinterpret_cast<const f32x4_t*>(c_lds + r * SC + e_col);
+        const f32x4_t gr = c_read(r, e_col);
         const size_t off = (size_t)m * p.ldw + n;
         if (fused) {
           f32x4_t w = w_old[q];
-          w.x = fmaf(-p.lr, g.x, w.x);
-          w.y = fmaf(-p.lr, g.y, w.y);
-          w.z = fmaf(-p.lr, g.z, w.z);
-          w.w = fmaf(-p.lr, g.w, w.w);
-          typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+          w.x = fmaf(-p.lr, gr.x, w.x);
+          w.y = fmaf(-p.lr, gr.y, w.y);
+          w.z = fmaf(-p.lr, gr.z, w.z);
+          w.w = fmaf(-p.lr, gr.w, w.w);
           const u32x2_t hv = {(uint32_t)f32_to_bf16_rne(w.x) | ((uint32_t)f32_to_bf16_rne(w.y) << 16),
                               (uint32_t)f32_to_bf16_rne(w.z) | ((uint32_t)f32_to_bf16_rne(w.w) << 16)};
           if (p.streaming) {
@@ -427,80 +468,80 @@ __global__ __launch_bounds__(64 * WM * WN) void grouped_gemm_kernel(GemmArgs p) 
             if (p.shadow != nullptr) *reinterpret_cast<u32x2_t*>(p.shadow + pg + p.w_off + off) = hv;
           }
         } else {
-          *reinterpret_cast<f32x4_t*>(wbase + off) = g;
+          *reinterpret_cast<f32x4_t*>(wbase + off) = gr;
         }
       }
     }
-    if (bias_wave && kb == 0) {       // row 0 of the ones product: lane lr32 holds column lr32
+    if (bias_thread) {
+      float colsum = cs_lds[tid];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = n0 + (wn * TN + j) * 32 + lr32;
-        const float colsum = accb[j][0];
-        if (n < p.N) {
-          if (fused) {
-            float* bptr = p.params + pg + p.b_off + n;
-            *bptr = fmaf(-p.lr, colsum, *bptr);
-          } else {
-            p.grads[pg + p.b_off + n] = colsum;
-          }
-        }
-      }
+      for (int w = 1; w < WK; ++w) colsum += cs_lds[w * BN + tid];
+      if (fused) p.params[pg + p.b_off + n0 + tid] = fmaf(-p.lr, colsum, b_old);
+      else p.grads[pg + p.b_off + n0 + tid] = colsum;
     }
     return;
   }
 
+  // eight output columns per thread: 16 bytes of bf16, 32 of fp32.  Padding columns [N, out_cols)
+  // are written as zeros.
   const float* bias = (p.epi == EPI_FWD_HIDDEN || p.epi == EPI_FWD_LOGITS)
                           ? p.bias_src + (size_t)g * p.bias_gs + p.b_off : nullptr;
   const E* aux = reinterpret_cast<const E*>(p.aux) + (size_t)g * p.aux_gs;
+  constexpr int VPR8 = BN / 8;
+  for (int e = tid; e < BM * VPR8; e += NTHR) {
+    const int r = e / VPR8, c = 8 * (e % VPR8);
+    const int m = m0 + r, n = n0 + c;
+    if (m >= p.M || n >= p.out_cols) continue;
+    float z[8];
+    {
+      const f32x4_t lo = c_read(r, c), hi = c_read(r, c + 4);
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+      for (int q = 0; q < 4; ++q) { z[q] = lo[q]; z[4 + q] = hi[q]; }
+    }
+    // partial sums of a split contraction carry no bias: the loss head adds it once
+    if (bias != nullptr && n_splits == 1) {
+      const f32x4_t lo = *reinterpret_cast<const f32x4_t*>(bias + n), hi = *reinterpret_cast<const f32x4_t*>(bias + n + 4);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int n = n0 + (wn * TN + j) * 32 + lr32;
-      const bool n_ok = n < p.out_cols;
-      // partial sums of a split contraction carry no bias: the loss head adds it once
-      const float bn = (bias != nullptr && n_splits == 1) ? bias[n_ok ? n : 0] : 0.0f;
-      // all loads of the tile first (they may not be reordered across the stores below)
-      float h[16];
-      if (p.epi == EPI_DX) {
+      for (int q = 0; q < 4; ++q) { z[q] += lo[q]; z[4 + q] += hi[q]; }
+    }
+    if (p.epi == EPI_FWD_HIDDEN) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int m = m0 + (wm * TM + i) * 32 + 8 * (v / 4) + 4 * kb + (v % 4);
-          const bool ok = n_ok && m < p.M;
-          h[v] = from_elem<T>(aux[ok ? (size_t)m * p.ldaux + n : (size_t)0]);
-        }
-      }
+      for (int q = 0; q < 8; ++q) z[q] = act_fwd(z[q], p.act);
+    } else if (p.epi == EPI_DX) {
+      const E* ap = aux + (size_t)m * p.ldaux + n;
+      if constexpr (T::kBf16) {
+        const u16x8_t h = *reinterpret_cast<const u16x8_t*>(ap);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = m0 + (wm * TM + i) * 32 + 8 * (v / 4) + 4 * kb + (v % 4);
-        if (!n_ok || m >= p.M) continue;
-        const size_t o = (size_t)g * p.out_gs + (size_t)m * p.ldo + n;
-        const float c = acc[i][j][v];
-        if (p.epi == EPI_FWD_HIDDEN) {
-          reinterpret_cast<E*>(p.out)[o] = to_elem<T>(act_fwd(c + bn, p.act));
-        } else if (p.epi == EPI_FWD_LOGITS) {
-          reinterpret_cast<float*>(p.out)[(size_t)ks * p.split_stride + o] = c + bn;
-        } else {  // EPI_DX
-          reinterpret_cast<E*>(p.out)[o] = to_elem<T>(c * act_bwd_from_h(h[v], p.act));
-        }
+        for (int q = 0; q < 8; ++q) z[q] *= act_bwd_from_h(bf16_to_f32(h[q]), p.act);
+      } else {
+        const f32x4_t lo = *reinterpret_cast<const f32x4_t*>(ap), hi = *reinterpret_cast<const f32x4_t*>(ap + 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { z[q] *= act_bwd_from_h(lo[q], p.act); z[4 + q] *= act_bwd_from_h(hi[q], p.act); }
       }
     }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) z[q] = n + q < p.N ? z[q] : 0.0f;
+    const size_t o = (size_t)g * p.out_gs + (size_t)m * p.ldo + n;
+    if (T::kBf16 && p.epi != EPI_FWD_LOGITS) {
+      u16x8_t h;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) h[q] = f32_to_bf16_rne(z[q]);
+      *reinterpret_cast<u16x8_t*>(reinterpret_cast<uint16_t*>(p.out) + o) = h;
+    } else {
+      float* op = reinterpret_cast<float*>(p.out) + (p.epi == EPI_FWD_LOGITS ? (size_t)ks * p.split_stride : 0) + o;
+      *reinterpret_cast<f32x4_t*>(op) = (f32x4_t){z[0], z[1], z[2], z[3]};
+      *reinterpret_cast<f32x4_t*>(op + 4) = (f32x4_t){z[4], z[5], z[6], z[7]};
+    }
+  }
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int AKIND, int BKIND,
-          bool DEEP = !(AKIND == OP_TRANS && BKIND == OP_TRANS)>
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
 static hipError_t launch_one(GemmArgs p, int n_groups, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0 || n_groups <= 0) return hipSuccess;
-  using E = typename T::elem;
-  constexpr size_t kStages = DEEP ? 2 : 1;
-  constexpr bool kIsDw = (AKIND == OP_TRANS && BKIND == OP_TRANS);
-  constexpr size_t kStageBytes =
-      kStages * sizeof(E) * (TileShape<T, BM, AKIND>::kElems + TileShape<T, BN, BKIND>::kElems);
-  // the weight-gradient product parks its fp32 output tile [BM][BN + 8] in the same memory
-  constexpr size_t kOutBytes = kIsDw ? sizeof(float) * BM * (BN + 8) : 0;
-  constexpr size_t kLds = kStageBytes > kOutBytes ? kStageBytes : kOutBytes;
-  auto kernel = grouped_gemm_kernel<T, BM, BN, WM, WN, AKIND, BKIND, DEEP>;
-  // double-buffered tiles can exceed the 64 KB default; setting the limit twice is harmless
+  constexpr size_t kLds = gemm_lds_bytes<T, BM, BN, WK, S>();
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+  auto kernel = grouped_gemm_kernel<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>;
+  // the tiles can exceed the 64 KB default; setting the limit twice is harmless
   static std::atomic<bool> configured{false};
   if (!configured.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -511,53 +552,56 @@ static hipError_t launch_one(GemmArgs p, int n_groups, hipStream_t s) {
   p.n_groups = n_groups;
   if (p.k_splits > 1 && p.epi != EPI_FWD_LOGITS) return hipErrorInvalidValue;
   const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) * (p.k_splits > 1 ? p.k_splits : 1);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * n_groups)), dim3(64 * WM * WN), kLds, s, p);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * n_groups)), dim3(64 * WM * WN * WK), kLds, s, p);
   return hipGetLastError();
 }
 
 constexpr int kComputeUnits = 256;
 
-// Batch-row products (forward, backward-data): the whole minibatch sits in one M tile when
-// B <= 128 so that each weight element is read from HBM exactly once per product.  The wide
-// (128-column) tile halves LDS traffic per flop; it is used when it still yields at least one
-// workgroup per compute unit.
-template <typename T, int AKIND, int BKIND>
-static hipError_t launch_rows(const GemmArgs& p, int n_groups, hipStream_t s) {
-  if (p.M <= 32) return launch_one<T, 32, 128, 1, 4, AKIND, BKIND>(p, n_groups, s);
-  const bool wide = (long)((p.N + 127) / 128) * n_groups * ((p.M + 127) / 128) >= kComputeUnits;
-  if (p.M <= 64) {
-    if (wide) return launch_one<T, 64, 128, 2, 2, AKIND, BKIND>(p, n_groups, s);
-    return launch_one<T, 64, 64, 2, 2, AKIND, BKIND>(p, n_groups, s);
-  }
-  // eight wavefronts on the widest tile: with one wavefront per SIMD nothing covers the LDS
-  // latency between fragment reads and matrix instructions (4096 x 4096, 8 replicas: 74 -> 61 us)
-  if (wide) return launch_one<T, 128, 128, 2, 4, AKIND, BKIND>(p, n_groups, s);
-  // a narrow layer that would leave compute units idle splits the minibatch rows over two
-  // workgroups instead: the second reader of a weight tile finds it in the L2 of the same XCD
-  if ((long)((p.N + 63) / 64) * n_groups < kComputeUnits)
-    return launch_one<T, 64, 64, 2, 2, AKIND, BKIND>(p, n_groups, s);
-  return launch_one<T, 128, 64, 2, 2, AKIND, BKIND>(p, n_groups, s);
+// Batch-row products (forward, backward-data).  What bounds a large launch is the rate at which one
+// compute unit takes in its operand tiles (about 27 GB/s from HBM, 40 GB/s from L2: the number of
+// lines it can have outstanding), so the tile is the widest that still gives every compute unit one:
+// 8 x (128 x 4096) x 4096 with shared weights, 128 x 128 tiles: 57 -> 48 us forward, 47 -> 37 us
+// backward-data against the register-staged tiles this replaces.  A launch that cannot fill the
+// chip with 64 x 64 tiles is bound by the latency of one tile after the other; 32 x 32 tiles put all
+// compute units to work on it (6 x (100 x 500) x 600: 9.6 -> 7.3 us; fp32, 8 x (50 x 784) x 300, where a
+// serial chain of slow matrix instructions is cut in four as well: 27.5 -> 12 us).  bf16 adds the
+// contraction in one ascending chain in every tile: the first layer's backward kernel computes the
+// same product ahead and must give the same bits.
+enum RowsTile { ROWS_32, ROWS_64, ROWS_128 };
+static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
+  auto tiles = [&](int bm, int bn) {
+    return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * n_groups;
+  };
+  if (!bf16) return tiles(64, 64) >= 2 * kComputeUnits ? ROWS_64 : ROWS_32;
+  if (p.M <= 32 || tiles(64, 64) < kComputeUnits) return ROWS_32;
+  return p.M > 64 && tiles(128, 128) >= kComputeUnits ? ROWS_128 : ROWS_64;
 }
+static int rows_edge(RowsTile t) { return t == ROWS_32 ? 32 : t == ROWS_64 ? 64 : 128; }
 
-// Output tiles of the batch-row launch launch_rows() would make for p.
-static long rows_launch_tiles(const GemmArgs& p, int n_groups) {
-  int bm, bn;
-  if (p.M <= 32) { bm = 32; bn = 128; }
-  else {
-    const bool wide = (long)((p.N + 127) / 128) * n_groups * ((p.M + 127) / 128) >= kComputeUnits;
-    const bool narrow = (long)((p.N + 63) / 64) * n_groups < kComputeUnits;
-    bm = (p.M <= 64 || (!wide && narrow)) ? 64 : 128;
-    bn = wide ? 128 : 64;
+template <int AKIND, int BKIND>
+static hipError_t launch_rows_bf16(const GemmArgs& p, int n_groups, hipStream_t s) {
+  switch (rows_tile(p, n_groups, true)) {
+    case ROWS_32: return launch_one<TBF16, 32, 32, 1, 1, 1, 8, AKIND, BKIND>(p, n_groups, s);
+    case ROWS_64: return launch_one<TBF16, 64, 64, 2, 2, 1, 8, AKIND, BKIND>(p, n_groups, s);
+    default: return launch_one<TBF16, 128, 128, 2, 4, 1, 4, AKIND, BKIND>(p, n_groups, s);
   }
-  return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * n_groups;
+}
+template <int AKIND, int BKIND>
+static hipError_t launch_rows_f32(const GemmArgs& p, int n_groups, hipStream_t s) {
+  if (rows_tile(p, n_groups, false) == ROWS_64)
+    return launch_one<TF32, 64, 64, 2, 2, 1, 4, AKIND, BKIND>(p, n_groups, s);
+  return launch_one<TF32, 32, 32, 1, 1, 4, 8, AKIND, BKIND>(p, n_groups, s);
 }
 
 // A logits product that leaves most compute units idle (few classes) cuts its contraction into
 // 2 or 4 ranges of whole tiles, every range non-empty and at least two tiles long.
 int gemm_logit_splits(const GemmArgs& p, int n_groups, bool bf16) {
-  const int bk = bf16 ? TBF16::BK : TF32::BK;
+  const int bk = kTileBytes / (bf16 ? 2 : 4);
   const int n_k = (p.Kc + bk - 1) / bk;
-  const long wgs = rows_launch_tiles(p, n_groups);
+  const RowsTile t = rows_tile(p, n_groups, bf16);
+  const int edge = rows_edge(t);
+  const long wgs = (long)((p.M + edge - 1) / edge) * ((p.N + edge - 1) / edge) * n_groups;
   for (int s = kMaxLogitSplits; s >= 2; s >>= 1) {
     const int per = (n_k + s - 1) / s;
     if (wgs * s <= 2 * kComputeUnits && per >= 2 && (long)per * (s - 1) < n_k) return s;
@@ -566,27 +610,32 @@ int gemm_logit_splits(const GemmArgs& p, int n_groups, bool bf16) {
 }
 
 hipError_t launch_gemm_fwd(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s) {
-  return bf16 ? launch_rows<TBF16, OP_CONTIG, OP_TRANS>(p, n_groups, s)
-              : launch_rows<TF32, OP_CONTIG, OP_TRANS>(p, n_groups, s);
+  return bf16 ? launch_rows_bf16<OP_CONTIG, OP_TRANS>(p, n_groups, s)
+              : launch_rows_f32<OP_CONTIG, OP_TRANS>(p, n_groups, s);
 }
 hipError_t launch_gemm_dx(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s) {
-  return bf16 ? launch_rows<TBF16, OP_CONTIG, OP_CONTIG>(p, n_groups, s)
-              : launch_rows<TF32, OP_CONTIG, OP_CONTIG>(p, n_groups, s);
+  return bf16 ? launch_rows_bf16<OP_CONTIG, OP_CONTIG>(p, n_groups, s)
+              : launch_rows_f32<OP_CONTIG, OP_CONTIG>(p, n_groups, s);
+}
+// Weight-gradient products.  128 x 128 tiles in workgroups of four wavefronts, two of them per compute
+// unit, so that the weight read-modify-write of one runs beside the products of the other: 4096 x 4096
+// with 1024 stacked rows 87 -> 70 us, 8 x (3072 x 1024) with 512 rows 102 -> 79 us.  Launches without two such
+// tiles per compute unit: 64 x 64 tiles.
+template <typename T>
+static hipError_t launch_dw_tiles(const GemmArgs& p, int n_groups, hipStream_t s) {
+  if constexpr (T::kBf16) {
+    if ((long)((p.M + 127) / 128) * ((p.N + 127) / 128) * n_groups >= 2 * kComputeUnits)
+      return launch_one<T, 128, 128, 2, 2, 1, 2, OP_TRANS, OP_TRANS>(p, n_groups, s);
+  }
+  return launch_one<T, 64, 64, 2, 2, 1, 4, OP_TRANS, OP_TRANS>(p, n_groups, s);
 }
 hipError_t launch_gemm_dw(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s) {
-  return bf16 ? launch_one<TBF16, 128, 64, 2, 2, OP_TRANS, OP_TRANS>(p, n_groups, s)
-              : launch_one<TF32, 128, 64, 2, 2, OP_TRANS, OP_TRANS>(p, n_groups, s);
+  return bf16 ? launch_dw_tiles<TBF16>(p, n_groups, s) : launch_dw_tiles<TF32>(p, n_groups, s);
 }
 // The same product with the minibatches of all workers stacked into one contraction (a single
-// group, Kc = N B rows).  Large layers: the deep pipeline on the widest tile.  Layers with few
-// tiles: 64 x 64 tiles on the shallow pipeline, several workgroups per compute unit, so that the
-// weight read-modify-write of one overlaps the products of another (3072 x 1024 with 1024 stacked
-// rows: 22 -> 18 us).
+// group, Kc = N B rows).
 hipError_t launch_gemm_dw_stacked(const GemmArgs& p, hipStream_t s) {
-  const long wide_tiles = (long)((p.M + 127) / 128) * ((p.N + 127) / 128);
-  if (wide_tiles >= kComputeUnits)
-    return launch_one<TBF16, 128, 128, 2, 4, OP_TRANS, OP_TRANS, true>(p, 1, s);
-  return launch_one<TBF16, 64, 64, 2, 2, OP_TRANS, OP_TRANS, false>(p, 1, s);
+  return launch_dw_tiles<TBF16>(p, 1, s);
 }
 
 }  // namespace prsgd

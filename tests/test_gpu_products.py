@@ -1,0 +1,48 @@
+"""The grouped matrix products at the edges of their tiles, against the CPU oracle.
+
+One local step with the update kept apart (every product writes its result) and one with it fused.
+Bounds: fp32 1e-5, the one-step gate.  bf16 1e-4: oracle and kernels round the same operands, so
+one step differs by the fp32 sums (a relative sqrt(K) 2^-24, 5e-6 for the longest contraction here)
+and by an operand whose rounding falls the other way: 2^-9 of one of the B terms of a gradient that
+moves a weight by gamma = 0.05 times its size.  tanh: no kink that could switch a whole term.
+"""
+import numpy as np
+import pytest
+import torch
+
+from helpers import inputs_for, oracle_run, rel_err, small_mlp
+
+pytestmark = pytest.mark.gpu
+
+# dims, batch, workers: contractions of one element, of a whole tile (64 bf16, 32 fp32 elements), one
+# less and one more, of several tiles past the depth of the pipeline, and ragged last tiles; output
+# tiles of 32, 64 and 128 rows and columns, whole and ragged; worker counts that do and do not fill
+# the 8 chiplets evenly
+SHAPES = [
+    ("bf16", (1, 33, 3), 1, 1),
+    ("bf16", (64, 65, 63, 10), 33, 3),
+    ("bf16", (127, 128, 129, 37), 65, 6),
+    ("bf16", (600, 40, 72, 9), 31, 5),
+    ("bf16", (72, 520, 130, 12), 64, 32),            # 64-row tiles
+    ("bf16", (72, 1032, 1000, 12), 160, 16),         # 128-row tiles, ragged contraction and rows
+    ("f32", (1, 33, 3), 1, 1),
+    ("f32", (31, 32, 33, 10), 33, 3),
+    ("f32", (300, 65, 100, 37), 50, 6),
+    ("f32", (40, 520, 72, 9), 130, 20),              # 64-row tiles
+]
+
+
+@pytest.mark.parametrize("dtype,dims,batch,n_workers", SHAPES)
+@pytest.mark.parametrize("fused", [True, False])
+def test_products_at_tile_edges(dtype, dims, batch, n_workers, fused):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=dims, batch=batch, n_workers=n_workers, gemm_dtype=dtype, activation="tanh",
+                  rows_per_worker=256, iterations=1)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0", fused_update=fused)
+    P.prsgd_local_steps(h, 1)
+    want = oracle_run(w, inp, iterations=1)
+    assert rel_err(D.read_all(h), want["x"]) <= (1e-5 if dtype == "f32" else 1e-4)
+    assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-5 if dtype == "f32" else 2e-3, atol=1e-6)
+    P.prsgd_destroy(h)
