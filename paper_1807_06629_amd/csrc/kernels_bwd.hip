@@ -643,6 +643,21 @@ hipError_t launch_bwd_one(const BwdArgs& p, hipStream_t s) {
 
 bool bwd_fused_supported(int batch) { return batch >= 1 && batch <= 128; }
 
+// Ragged layers with fewer 64-row bands than compute units (and no momentum, which the products
+// cannot apply): a band walks its column tiles one after the other at about 2.5 us each behind a
+// 7 us start, while the products of the layer spread over all compute units.  1000-500-300-37, six
+// workers, 100 rows: the three layers' launches 21 + 20 + 10 us, the two backward-data products 5 + 7 us and the
+// weight-gradient products in one launch 14 us.  With a band per compute unit the pass over
+// the weights is the shorter one (16 x (1024 x 10), 64 rows: 9 us against 5 + 6).
+bool bwd_products_apart(const BwdArgs& p) {
+  if (p.vel != nullptr) return false;
+  if (p.dx == nullptr && bwd_first_fwd_shape(p.B, p.K, p.Nn)) return false;   // same bits as that kernel
+  const int mb = p.B <= 32 ? 1 : p.B <= 64 ? 2 : 4;
+  if (bwd_full_applies(p, mb, 2) || bwd_full_applies(p, mb, 2, 32)) return false;
+  if ((p.Nn % BN) != 0 && (p.ldw % BN) == 0 && p.ldw - p.Nn < BN) return false;      // walked padded
+  return (long)((p.K + BMK - 1) / BMK) * p.n_groups < 256;
+}
+
 hipError_t launch_bwd_fused(const BwdArgs& p, hipStream_t s) {
   if (p.K <= 0 || p.Nn <= 0 || p.n_groups <= 0) return hipSuccess;
   if (!bwd_fused_supported(p.B)) return hipErrorInvalidValue;

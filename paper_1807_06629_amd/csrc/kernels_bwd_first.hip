@@ -304,10 +304,15 @@ hipError_t launch_first_mb(const BwdArgs& p, hipStream_t s) {
 
 }  // namespace
 
+// Layer shapes made of whole tiles.
+bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
+  return (batch == 32 || batch == 64 || batch == 128) && d_in >= 4 * BT && (d_in % (2 * BT)) == 0 &&
+         d_out >= BT && (d_out % BT) == 0;
+}
+
 // Whole tiles, every worker active, and the buffers of the next iteration given.
 bool bwd_first_fwd_applies(const BwdArgs& p) {
-  if (p.B != 32 && p.B != 64 && p.B != 128) return false;
-  if (p.K < 4 * BT || (p.K % (2 * BT)) != 0 || p.Nn < BT || (p.Nn % BT) != 0) return false;
+  if (!bwd_first_fwd_shape(p.B, p.K, p.Nn)) return false;
   if (p.worker_steps != nullptr || p.dx != nullptr) return false;
   if (p.x_next == nullptr || p.h_next == nullptr) return false;   // shadow == nullptr: it is left stale
   return (p.ldw % 4) == 0 && (p.ldh % 8) == 0 && (p.ldx % 8) == 0 && (p.ldd % 8) == 0 && (p.w_off % 4) == 0;

@@ -206,8 +206,9 @@ template <typename T, int BM, int BN, int WK, int S> constexpr size_t gemm_lds_b
   return stages > out ? stages : out;
 }
 
+// One output tile of product p: workgroup `block` of the product's.
 template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
-__global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(GemmArgs p) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   using E = typename T::elem;
   constexpr int NWAVE = WM * WN * WK, NTHR = 64 * NWAVE;
   using IOA = TileIO<T, BM, AKIND, NWAVE>;
@@ -226,8 +227,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(Gemm
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   const int n_splits = p.k_splits > 1 ? p.k_splits : 1;     // contraction ranges per output tile
   const int total = tiles_m * tiles_n * n_splits * p.n_groups;
-  const int xcd = blockIdx.x & 7;
-  int idx = xcd * (total >> 3) + min(xcd, total & 7) + (int)(blockIdx.x >> 3);
+  const int xcd = block & 7;
+  int idx = xcd * (total >> 3) + min(xcd, total & 7) + (block >> 3);
   const int ks = idx % n_splits;
   idx /= n_splits;
   int g = 0, tm, tn;
@@ -305,20 +306,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(Gemm
   const int e_row = tid / VPR_C, e_col = 4 * (tid % VPR_C);
   f32x4_t w_old[EV];
   if constexpr (kIsDw) if (fused) {
-    const float* wbase = p.params + pg + p.w_off;
+    const float* wbase = p.src + (size_t)g * p.src_gs + p.w_off;
+    const bool nt_read = p.streaming && p.src_gs != 0;     // a shared source is re-read by every group
 #pragma unroll
     for (int q = 0; q < EV; ++q) {
       const int m = m0 + q * ROWS_PER_PASS + e_row, n = n0 + e_col;
       const bool ok = m < p.M && n < p.N;
       const f32x4_t* wp = reinterpret_cast<const f32x4_t*>(wbase + (ok ? (size_t)m * p.ldw + n : (size_t)0));
-      w_old[q] = p.streaming ? __builtin_nontemporal_load(wp) : *wp;
+      w_old[q] = nt_read ? __builtin_nontemporal_load(wp) : *wp;
     }
   }
 
   // ... and the old bias, by the workgroups of the first row band (one column per thread)
   static_assert(!kIsDw || BN <= NTHR, "one bias column per thread");
   const bool bias_thread = kIsDw && m0 == 0 && tid < BN && n0 + tid < p.N;
-  const float b_old = fused && bias_thread ? p.params[pg + p.b_off + n0 + tid] : 0.0f;
+  const float b_old = fused && bias_thread ? p.src[(size_t)g * p.src_gs + p.b_off + n0 + tid] : 0.0f;
 
   f32x16_t acc[TM][TN];
 #pragma unroll
@@ -485,7 +487,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(Gemm
   // eight output columns per thread: 16 bytes of bf16, 32 of fp32.  Padding columns [N, out_cols)
   // are written as zeros.
   const float* bias = (p.epi == EPI_FWD_HIDDEN || p.epi == EPI_FWD_LOGITS)
-                          ? p.bias_src + (size_t)g * p.bias_gs + p.b_off : nullptr;
+                          ? p.src + (size_t)g * p.src_gs + p.b_off : nullptr;
   const E* aux = reinterpret_cast<const E*>(p.aux) + (size_t)g * p.aux_gs;
   constexpr int VPR8 = BN / 8;
   for (int e = tid; e < BM * VPR8; e += NTHR) {
@@ -536,6 +538,24 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(Gemm
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(GemmArgs p) {
+  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>(p, (int)blockIdx.x);
+}
+
+// Several products in one launch: product i has the workgroups first[i] .. first[i + 1] - 1.
+struct GemmSet {
+  int n;
+  int first[kMaxGemmSet + 1];
+  GemmArgs p[kMaxGemmSet];
+};
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_set_kernel(GemmSet set) {
+  int i = 0;
+  while (i + 1 < set.n && (int)blockIdx.x >= set.first[i + 1]) ++i;
+  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>(set.p[i], (int)blockIdx.x - set.first[i]);
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
 static hipError_t launch_one(GemmArgs p, int n_groups, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0 || n_groups <= 0) return hipSuccess;
   constexpr size_t kLds = gemm_lds_bytes<T, BM, BN, WK, S>();
@@ -558,38 +578,43 @@ static hipError_t launch_one(GemmArgs p, int n_groups, hipStream_t s) {
 
 constexpr int kComputeUnits = 256;
 
-// Batch-row products (forward, backward-data).  What bounds a large launch is the rate at which one
-// compute unit takes in its operand tiles (about 27 GB/s from HBM, 40 GB/s from L2: the number of
-// lines it can have outstanding), so the tile is the widest that still gives every compute unit one:
-// 8 x (128 x 4096) x 4096 with shared weights, 128 x 128 tiles: 57 -> 48 us forward, 47 -> 37 us
-// backward-data against the register-staged tiles this replaces.  A launch that cannot fill the
-// chip with 64 x 64 tiles is bound by the latency of one tile after the other; 32 x 32 tiles put all
-// compute units to work on it (6 x (100 x 500) x 600: 9.6 -> 7.3 us; fp32, 8 x (50 x 784) x 300, where a
-// serial chain of slow matrix instructions is cut in four as well: 27.5 -> 12 us).  bf16 adds the
-// contraction in one ascending chain in every tile: the first layer's backward kernel computes the
-// same product ahead and must give the same bits.
-enum RowsTile { ROWS_32, ROWS_64, ROWS_128 };
+// Batch-row products (forward, backward-data).  What bounds a launch is the rate at which one compute
+// unit takes in its operand tiles (about 27 GB/s from HBM, 40 GB/s from L2: the number of lines it
+// can have outstanding), so a launch takes the tile with which the busiest compute unit requests the
+// fewest bytes: tiles per compute unit, rounded up, times rows + columns of a tile.  8 x (128 x 4096) x
+// 4096 with shared weights, 128 x 128 tiles: 57 -> 48 us forward, 47 -> 37 us backward-data against the
+// register-staged tiles this replaces; 6 x (100 x 300) x 500, 32 x 64 tiles: 9.6 -> 8.3 us; 6 x (128 x 896) x
+// 3776: 26 us with 64 x 64 tiles, 48 us with 32 x 64; 8 x (95 x 3456) x 3760: 133 us with 64 x 64.
+// bf16 adds the contraction in one ascending chain in every tile: the first layer's backward kernel
+// computes the same product ahead and must give the same bits.
+// fp32 is bound by its matrix instructions, 8 times as slow: 32 x 32 tiles whose wavefronts share the
+// contraction (8 x (50 x 784) x 300: 27.5 -> 12 us), until the chip is full either way.
+struct RowsTile { int bm, bn; };
 static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
-  auto tiles = [&](int bm, int bn) {
-    return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * n_groups;
+  auto tiles = [&](RowsTile t) {
+    return (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * n_groups;
   };
-  if (!bf16) return tiles(64, 64) >= 2 * kComputeUnits ? ROWS_64 : ROWS_32;
-  if (p.M <= 32 || tiles(64, 64) < kComputeUnits) return ROWS_32;
-  return p.M > 64 && tiles(128, 128) >= kComputeUnits ? ROWS_128 : ROWS_64;
+  if (!bf16) return tiles({64, 64}) >= 2 * kComputeUnits ? RowsTile{64, 64} : RowsTile{32, 32};
+  RowsTile best = {32, 64};
+  if (p.M <= 32) return best;
+  auto cost = [&](RowsTile t) { return (tiles(t) + kComputeUnits - 1) / kComputeUnits * (t.bm + t.bn); };
+  for (const RowsTile t : {RowsTile{64, 64}, RowsTile{128, 64}, RowsTile{128, 128}})
+    if (cost(t) <= cost(best)) best = t;
+  return best;
 }
-static int rows_edge(RowsTile t) { return t == ROWS_32 ? 32 : t == ROWS_64 ? 64 : 128; }
 
 template <int AKIND, int BKIND>
 static hipError_t launch_rows_bf16(const GemmArgs& p, int n_groups, hipStream_t s) {
-  switch (rows_tile(p, n_groups, true)) {
-    case ROWS_32: return launch_one<TBF16, 32, 32, 1, 1, 1, 8, AKIND, BKIND>(p, n_groups, s);
-    case ROWS_64: return launch_one<TBF16, 64, 64, 2, 2, 1, 8, AKIND, BKIND>(p, n_groups, s);
-    default: return launch_one<TBF16, 128, 128, 2, 4, 1, 4, AKIND, BKIND>(p, n_groups, s);
-  }
+  const RowsTile t = rows_tile(p, n_groups, true);
+  if (t.bm == 32) return launch_one<TBF16, 32, 64, 1, 2, 1, 8, AKIND, BKIND>(p, n_groups, s);
+  if (t.bm == 64) return launch_one<TBF16, 64, 64, 2, 2, 1, 8, AKIND, BKIND>(p, n_groups, s);
+  if (t.bn == 64) return launch_one<TBF16, 128, 64, 4, 2, 1, 6, AKIND, BKIND>(p, n_groups, s);
+  // eight wavefronts: two per SIMD cover the LDS latency of each other
+  return launch_one<TBF16, 128, 128, 2, 4, 1, 4, AKIND, BKIND>(p, n_groups, s);
 }
 template <int AKIND, int BKIND>
 static hipError_t launch_rows_f32(const GemmArgs& p, int n_groups, hipStream_t s) {
-  if (rows_tile(p, n_groups, false) == ROWS_64)
+  if (rows_tile(p, n_groups, false).bm == 64)
     return launch_one<TF32, 64, 64, 2, 2, 1, 4, AKIND, BKIND>(p, n_groups, s);
   return launch_one<TF32, 32, 32, 1, 1, 4, 8, AKIND, BKIND>(p, n_groups, s);
 }
@@ -600,8 +625,7 @@ int gemm_logit_splits(const GemmArgs& p, int n_groups, bool bf16) {
   const int bk = kTileBytes / (bf16 ? 2 : 4);
   const int n_k = (p.Kc + bk - 1) / bk;
   const RowsTile t = rows_tile(p, n_groups, bf16);
-  const int edge = rows_edge(t);
-  const long wgs = (long)((p.M + edge - 1) / edge) * ((p.N + edge - 1) / edge) * n_groups;
+  const long wgs = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * n_groups;
   for (int s = kMaxLogitSplits; s >= 2; s >>= 1) {
     const int per = (n_k + s - 1) / s;
     if (wgs * s <= 2 * kComputeUnits && per >= 2 && (long)per * (s - 1) < n_k) return s;
@@ -621,21 +645,51 @@ hipError_t launch_gemm_dx(const GemmArgs& p, int n_groups, bool bf16, hipStream_
 // unit, so that the weight read-modify-write of one runs beside the products of the other: 4096 x 4096
 // with 1024 stacked rows 87 -> 70 us, 8 x (3072 x 1024) with 512 rows 102 -> 79 us.  Launches without two such
 // tiles per compute unit: 64 x 64 tiles.
-template <typename T>
-static hipError_t launch_dw_tiles(const GemmArgs& p, int n_groups, hipStream_t s) {
-  if constexpr (T::kBf16) {
-    if ((long)((p.M + 127) / 128) * ((p.N + 127) / 128) * n_groups >= 2 * kComputeUnits)
-      return launch_one<T, 128, 128, 2, 2, 1, 2, OP_TRANS, OP_TRANS>(p, n_groups, s);
+static bool dw_large(const GemmArgs& p, int n_groups, bool bf16) {
+  return bf16 && (long)((p.M + 127) / 128) * ((p.N + 127) / 128) * n_groups >= 2 * kComputeUnits;
+}
+// Launches without two such tiles per compute unit are bound by latency, not by what they move
+// (7 us for a single 64 x 64 tile: launch, first operand and weight loads, write-back), so the layers'
+// products, which depend on nothing of each other, share one launch (fp32 784-300-100-10, eight workers:
+// 11.8 + 6.9 + 7.1 us in three launches, 12.7 us in one).
+template <typename T, int S> static hipError_t launch_dw_set(const GemmArgs* ps, int n, int n_groups, hipStream_t s) {
+  constexpr int BM = 64, BN = 64;
+  constexpr size_t kLds = gemm_lds_bytes<T, BM, BN, 1, S>();
+  auto kernel = grouped_gemm_set_kernel<T, BM, BN, 2, 2, 1, S, OP_TRANS, OP_TRANS>;
+  static std::atomic<bool> configured{false};
+  if (!configured.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    if (e != hipSuccess) return e;
+    configured.store(true, std::memory_order_release);
   }
-  return launch_one<T, 64, 64, 2, 2, 1, 4, OP_TRANS, OP_TRANS>(p, n_groups, s);
+  GemmSet set;
+  set.n = 0;
+  set.first[0] = 0;
+  for (int i = 0; i < n; ++i) {
+    if (ps[i].M <= 0 || ps[i].N <= 0) continue;
+    if (ps[i].k_splits > 1) return hipErrorInvalidValue;
+    set.p[set.n] = ps[i];
+    set.p[set.n].n_groups = n_groups;
+    set.first[set.n + 1] = set.first[set.n] + ((ps[i].M + BM - 1) / BM) * ((ps[i].N + BN - 1) / BN) * n_groups;
+    ++set.n;
+  }
+  if (set.n == 0 || n_groups <= 0) return hipSuccess;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)set.first[set.n]), dim3(256), kLds, s, set);
+  return hipGetLastError();
 }
-hipError_t launch_gemm_dw(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s) {
-  return bf16 ? launch_dw_tiles<TBF16>(p, n_groups, s) : launch_dw_tiles<TF32>(p, n_groups, s);
-}
-// The same product with the minibatches of all workers stacked into one contraction (a single
-// group, Kc = N B rows).
-hipError_t launch_gemm_dw_stacked(const GemmArgs& p, hipStream_t s) {
-  return launch_dw_tiles<TBF16>(p, 1, s);
+// One large product, or up to kMaxGemmSet others (gemm_dw_shares_launch).
+bool gemm_dw_shares_launch(const GemmArgs& p, int n_groups, bool bf16) { return !dw_large(p, n_groups, bf16); }
+hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hipStream_t s) {
+  if (n < 0 || n > kMaxGemmSet) return hipErrorInvalidValue;
+  if (n == 1 && dw_large(ps[0], n_groups, bf16))
+    return launch_one<TBF16, 128, 128, 2, 2, 1, 2, OP_TRANS, OP_TRANS>(ps[0], n_groups, s);
+  // contractions of one or two tiles: two stages, and the more workgroups on a compute unit
+  int depth = 0;
+  for (int i = 0; i < n; ++i) depth = depth > ps[i].Kc ? depth : ps[i].Kc;
+  const bool shallow = depth <= 2 * kTileBytes / (bf16 ? 2 : 4);
+  if (bf16) return shallow ? launch_dw_set<TBF16, 2>(ps, n, n_groups, s) : launch_dw_set<TBF16, 4>(ps, n, n_groups, s);
+  return shallow ? launch_dw_set<TF32, 2>(ps, n, n_groups, s) : launch_dw_set<TF32, 4>(ps, n, n_groups, s);
 }
 
 }  // namespace prsgd

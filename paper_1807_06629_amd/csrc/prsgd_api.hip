@@ -290,6 +290,37 @@ int refresh_first_shadow(prsgd_ctx* ctx) {
   return PRSGD_OK;
 }
 
+// Weight-gradient products of one backward pass.  Small ones wait for each other and share a launch: they
+// read H and D of their layers, which stay as they are until the next iteration, and write W_l after
+// the backward-data product that needs its old value.
+struct DwQueue {
+  prsgd_ctx* ctx;
+  GemmArgs ps[kMaxGemmSet];
+  int n = 0, n_groups = 0, kind = 0;
+  explicit DwQueue(prsgd_ctx* c) : ctx(c) {}
+  int flush() {
+    if (n == 0) return PRSGD_OK;
+    const int count = n;
+    n = 0;
+    LAUNCH(ctx, kind, launch_gemm_dw(ps, count, n_groups, ctx->bf16, ctx->stream));
+    return PRSGD_OK;
+  }
+  int add(const GemmArgs& p, int groups, int k) {
+    if (!gemm_dw_shares_launch(p, groups, ctx->bf16)) {
+      LAUNCH(ctx, k, launch_gemm_dw(&p, 1, groups, ctx->bf16, ctx->stream));
+      return PRSGD_OK;
+    }
+    if (n == kMaxGemmSet) {
+      const int rc = flush();
+      if (rc != PRSGD_OK) return rc;
+    }
+    ps[n++] = p;
+    n_groups = groups;
+    kind = k;
+    return PRSGD_OK;
+  }
+};
+
 // One local iteration of every (active) MLP worker: gradient observation + eq. (3).
 // fuse_average: this iteration is followed by a restart, and both are taken together,
 //   (1/N) sum_i (x_i - gamma G_i) = ybar - (gamma / N) sum_i G_i,   ybar = (1/N) sum_i x_i   (eq. 2-3).
@@ -349,8 +380,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
   // The matrix products read weights from the bf16 shadow (bf16 mode) or the fp32 master.
   const void* wsrc = bf16 ? (const void*)(from_mean ? ctx->mean_shadow() : ctx->shadow())
                           : (const void*)ctx->params;
-  base.bias_src = ctx->src();
-  base.bias_gs = ctx->src_stride();
+  base.src = ctx->src();
+  base.src_gs = ctx->src_stride();
 
   // forward.  H_1 may already be there: the previous iteration's first-layer backward kernel computes
   // it from the weights it writes, for this iteration's minibatch
@@ -406,6 +437,30 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
                              lo.ld[L], bf16, worker_steps, step, prefetch ? &next_batch : nullptr, s));
   if (prefetch) ctx->batch_t[bk ^ 1] = t + 1;
 
+  // products of layer l: D_{l-1} = (D_l W_l^T) phi'(H_{l-1}) and dW_l = H_{l-1}^T D_l
+  auto dx_args = [&](int l) {
+    GemmArgs p = base;
+    p.a = ctx->at<void>(cv.delta[l]); p.a_gs = (long)B * lo.ld[l]; p.lda = lo.ld[l];
+    p.b = bf16 ? (const void*)(reinterpret_cast<const uint16_t*>(wsrc) + lo.w_off[l - 1])
+               : (const void*)(reinterpret_cast<const float*>(wsrc) + lo.w_off[l - 1]);
+    p.b_gs = w_gs; p.ldb = lo.ld[l];
+    p.M = B; p.N = lo.d[l - 1]; p.Kc = lo.d[l];
+    p.epi = EPI_DX;
+    p.out = ctx->at<void>(cv.delta[l - 1]); p.out_gs = (long)B * lo.ld[l - 1];
+    p.ldo = lo.ld[l - 1]; p.out_cols = lo.ld[l - 1];
+    p.aux = act_in(l - 1); p.aux_gs = (long)B * lo.ld[l - 1]; p.ldaux = lo.ld[l - 1];
+    return p;
+  };
+  auto dw_args = [&](int l) {
+    GemmArgs p = base;
+    p.a = act_in(l - 1); p.a_gs = (long)B * lo.ld[l - 1]; p.lda = lo.ld[l - 1];
+    p.b = ctx->at<void>(cv.delta[l]); p.b_gs = (long)B * lo.ld[l]; p.ldb = lo.ld[l];
+    p.M = lo.d[l - 1]; p.N = lo.d[l]; p.Kc = B;
+    p.w_off = lo.w_off[l - 1]; p.b_off = lo.b_off[l - 1]; p.ldw = lo.ld[l];
+    return p;
+  };
+  DwQueue dw(ctx);
+
   if (fuse_average) {
     // The workers' points differ (the last iteration of an epoch with I >= 2, or the first
     // iteration of a run): ybar is first taken from the points as they are (the restart kernel),
@@ -417,30 +472,21 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     // weights the forward pass used (the bf16 image of ybar, or of every worker's own point), and
     // when that is ybar it runs before layer l's pass changes it
     for (int l = L; l >= 1; --l) {
-      if (l > 1) {
-        GemmArgs p = base;
-        p.a = ctx->at<void>(cv.delta[l]); p.a_gs = (long)B * lo.ld[l]; p.lda = lo.ld[l];
-        p.b = (const void*)((from_mean ? ctx->mean_shadow() : ctx->shadow()) + lo.w_off[l - 1]);
-        p.b_gs = from_mean ? 0 : lo.m_pad; p.ldb = lo.ld[l];
-        p.M = B; p.N = lo.d[l - 1]; p.Kc = lo.d[l];
-        p.epi = EPI_DX;
-        p.out = ctx->at<void>(cv.delta[l - 1]); p.out_gs = (long)B * lo.ld[l - 1];
-        p.ldo = lo.ld[l - 1]; p.out_cols = lo.ld[l - 1];
-        p.aux = act_in(l - 1); p.aux_gs = (long)B * lo.ld[l - 1]; p.ldaux = lo.ld[l - 1];
-        LAUNCH(ctx, KK_DX, launch_gemm_dx(p, N, true, s));
-      }
+      if (l > 1) LAUNCH(ctx, KK_DX, launch_gemm_dx(dx_args(l), N, true, s));
       // all minibatches stacked: sum_i dW_i = [H_1; ..; H_N]^T [D_1; ..; D_N], one contraction of N B
       // rows, and ybar <- ybar - (gamma / N) sum_i dW_i (likewise the bias from the column sums)
-      GemmArgs p = base;
-      p.a = act_in(l - 1); p.a_gs = 0; p.lda = lo.ld[l - 1];
-      p.b = ctx->at<void>(cv.delta[l]); p.b_gs = 0; p.ldb = lo.ld[l];
-      p.M = lo.d[l - 1]; p.N = lo.d[l]; p.Kc = N * B;
+      GemmArgs p = dw_args(l);
+      p.a_gs = 0; p.b_gs = 0;
+      p.Kc = N * B;
       p.epi = EPI_DW_FUSED;
       p.lr = ctx->lr / (float)N;
       p.params = ctx->mean(); p.shadow = ctx->mean_shadow(); p.p_gs = 0;
-      p.w_off = lo.w_off[l - 1]; p.b_off = lo.b_off[l - 1]; p.ldw = lo.ld[l];
-      LAUNCH(ctx, KK_STEP_MEAN, launch_gemm_dw_stacked(p, s));
+      p.src = ctx->mean(); p.src_gs = 0;
+      const int rc = dw.add(p, 1, KK_STEP_MEAN);
+      if (rc != PRSGD_OK) return rc;
     }
+    const int rc = dw.flush();
+    if (rc != PRSGD_OK) return rc;
     ctx->at_mean = true;             // every worker's point is the new ybar; the replicas are stale
     return PRSGD_OK;
   }
@@ -465,6 +511,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
       q.x_next = reinterpret_cast<const uint16_t*>(ctx->xb(bk ^ 1)); q.x_gs = (long)B * lo.ld[0]; q.ldx = lo.ld[0];
       q.h_next = ctx->at<uint16_t>(cv.h[1]); q.hn_gs = (long)B * lo.ld[1]; q.ldhn = lo.ld[1];
       if (bwd_first_fwd_applies(q)) {
+        const int rc = dw.flush();          // H_1 is rewritten: layer 2's weight gradient still reads it
+        if (rc != PRSGD_OK) return rc;
         q.shadow = nullptr;                 // replica shadows of W_1 have no reader while H_1 comes from here
         LAUNCH(ctx, KK_BWD_FIRST, launch_bwd_first_fwd(q, s));
         ctx->shadow1_stale = true;
@@ -473,30 +521,27 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
         continue;
       }
     }
+    if (bwd_products_apart(q)) {
+      if (l > 1) LAUNCH(ctx, KK_BWD, launch_gemm_dx(dx_args(l), N, true, s));
+      GemmArgs p = dw_args(l);
+      p.epi = EPI_DW_FUSED;
+      const int rc = dw.add(p, N, KK_BWD);
+      if (rc != PRSGD_OK) return rc;
+      continue;
+    }
     LAUNCH(ctx, KK_BWD, launch_bwd_fused(q, s));
   }
   // otherwise: D_{l-1} needs the pre-update W_l, so it runs before layer l's weight kernel
   for (int l = L; !fused_bwd && l >= 1; --l) {
-    if (l > 1) {
-      GemmArgs p = base;
-      p.a = ctx->at<void>(cv.delta[l]); p.a_gs = (long)B * lo.ld[l]; p.lda = lo.ld[l];
-      p.b = bf16 ? (const void*)(reinterpret_cast<const uint16_t*>(wsrc) + lo.w_off[l - 1])
-                 : (const void*)(reinterpret_cast<const float*>(wsrc) + lo.w_off[l - 1]);
-      p.b_gs = lo.m_pad; p.ldb = lo.ld[l];
-      p.M = B; p.N = lo.d[l - 1]; p.Kc = lo.d[l];
-      p.epi = EPI_DX;
-      p.out = ctx->at<void>(cv.delta[l - 1]); p.out_gs = (long)B * lo.ld[l - 1];
-      p.ldo = lo.ld[l - 1]; p.out_cols = lo.ld[l - 1];
-      p.aux = act_in(l - 1); p.aux_gs = (long)B * lo.ld[l - 1]; p.ldaux = lo.ld[l - 1];
-      LAUNCH(ctx, KK_DX, launch_gemm_dx(p, N, bf16, s));
-    }
-    GemmArgs p = base;
-    p.a = act_in(l - 1); p.a_gs = (long)B * lo.ld[l - 1]; p.lda = lo.ld[l - 1];
-    p.b = ctx->at<void>(cv.delta[l]); p.b_gs = (long)B * lo.ld[l]; p.ldb = lo.ld[l];
-    p.M = lo.d[l - 1]; p.N = lo.d[l]; p.Kc = B;
+    if (l > 1) LAUNCH(ctx, KK_DX, launch_gemm_dx(dx_args(l), N, bf16, s));
+    GemmArgs p = dw_args(l);
     p.epi = c.fused_update ? EPI_DW_FUSED : EPI_DW_GRAD;
-    p.w_off = lo.w_off[l - 1]; p.b_off = lo.b_off[l - 1]; p.ldw = lo.ld[l];
-    LAUNCH(ctx, KK_DW, launch_gemm_dw(p, N, bf16, s));
+    const int rc = dw.add(p, N, KK_DW);
+    if (rc != PRSGD_OK) return rc;
+  }
+  {
+    const int rc = dw.flush();
+    if (rc != PRSGD_OK) return rc;
   }
 
   if (!c.fused_update) {

@@ -50,9 +50,10 @@ struct GemmArgs {
   float lr;
   // parameters / gradients (fp32, replica stride m_pad), bf16 shadow of the parameters
   float* params; float* grads; uint16_t* shadow; long p_gs;
-  // where the forward products read the bias from: the replicas, or (right after a restart
-  // whose broadcast was skipped) the shared node average with stride 0
-  const float* bias_src; long bias_gs;
+  // where the old parameters (forward: the bias; update: weights and bias) are read from: the
+  // replicas, or (right after a restart whose broadcast was skipped) the shared node average with
+  // stride 0
+  const float* src; long src_gs;
   long w_off, b_off; int ldw;
   // activation-like output (element type T, or float for logits) and auxiliary input
   void* out; long out_gs; int ldo; int out_cols;
@@ -94,8 +95,11 @@ struct BwdArgs {
   uint16_t* h_next; long hn_gs; int ldhn;
 };
 bool bwd_fused_supported(int batch);
+// The kernel's walk over the columns leaves most of the chip idle: the layer's products apart are faster.
+bool bwd_products_apart(const BwdArgs& p);
 hipError_t launch_bwd_fused(const BwdArgs& p, hipStream_t s);
 // Layer 1: backward step fused with the next iteration's forward product of that layer.
+bool bwd_first_fwd_shape(int batch, int d_in, int d_out);
 bool bwd_first_fwd_applies(const BwdArgs& p);
 hipError_t launch_bwd_first_fwd(const BwdArgs& p, hipStream_t s);
 
@@ -129,8 +133,11 @@ const char* kernel_kind_name(int kind);
 // ---- launchers (each returns the hipError_t of the launch) --------------------------------
 hipError_t launch_gemm_fwd(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s);
 hipError_t launch_gemm_dx(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s);
-hipError_t launch_gemm_dw_stacked(const GemmArgs& p, hipStream_t s);   // bf16 operands, one group
-hipError_t launch_gemm_dw(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s);
+// Weight-gradient products of up to kMaxGemmSet layers: products that may share a launch, or one that
+// may not.
+constexpr int kMaxGemmSet = 4;
+bool gemm_dw_shares_launch(const GemmArgs& p, int n_groups, bool bf16);
+hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hipStream_t s);
 
 // Minibatch draw of iteration t: rows of the workers' shards copied into the batch buffer.
 struct GatherArgs {
