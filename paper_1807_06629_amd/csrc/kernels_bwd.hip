@@ -136,8 +136,8 @@ __global__ __launch_bounds__(kThreads) void grouped_bwd_kernel(BwdArgs p) {
     for (int q = 0; q < 4; ++q) {
       const bool ok = (mask >> q) & 1u;
       uint2 hv;
-      hv.x = ok ? ((uint32_t)f32_to_bf16_rne(reg[q].x) | ((uint32_t)f32_to_bf16_rne(reg[q].y) << 16)) : 0u;
-      hv.y = ok ? ((uint32_t)f32_to_bf16_rne(reg[q].z) | ((uint32_t)f32_to_bf16_rne(reg[q].w) << 16)) : 0u;
+      hv.x = ok ? (f32x2_to_bf16x2_rne(reg[q].x, reg[q].y)) : 0u;
+      hv.y = ok ? (f32x2_to_bf16x2_rne(reg[q].z, reg[q].w)) : 0u;
       *reinterpret_cast<uint2*>(Wl + (q * 16 + (tid >> 4)) * SW + 4 * (tid & 15)) = hv;
     }
   };
@@ -244,8 +244,8 @@ __global__ __launch_bounds__(kThreads) void grouped_bwd_kernel(BwdArgs p) {
         w.z = fmaf(-p.lr, gr.z, w.z);
         w.w = fmaf(-p.lr, gr.w, w.w);
         uint2 hv;
-        hv.x = (uint32_t)f32_to_bf16_rne(w.x) | ((uint32_t)f32_to_bf16_rne(w.y) << 16);
-        hv.y = (uint32_t)f32_to_bf16_rne(w.z) | ((uint32_t)f32_to_bf16_rne(w.w) << 16);
+        hv.x = f32x2_to_bf16x2_rne(w.x, w.y);
+        hv.y = f32x2_to_bf16x2_rne(w.z, w.w);
         typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
         const u32x2_t hv2 = {hv.x, hv.y};
         if (nt) {
@@ -377,8 +377,8 @@ __global__ __launch_bounds__(kThreads) void grouped_bwd_full_kernel(BwdArgs p) {
   auto stash_w = [&](const f32x4_t (&reg)[QW]) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
-      const u32x2_t hv = {(uint32_t)f32_to_bf16_rne(reg[q].x) | ((uint32_t)f32_to_bf16_rne(reg[q].y) << 16),
-                          (uint32_t)f32_to_bf16_rne(reg[q].z) | ((uint32_t)f32_to_bf16_rne(reg[q].w) << 16)};
+      const u32x2_t hv = {f32x2_to_bf16x2_rne(reg[q].x, reg[q].y),
+                          f32x2_to_bf16x2_rne(reg[q].z, reg[q].w)};
       *reinterpret_cast<u32x2_t*>(Wl + (q * 16 + wrow) * SW + wcol) = hv;
     }
   };
@@ -489,8 +489,8 @@ __global__ __launch_bounds__(kThreads) void grouped_bwd_full_kernel(BwdArgs p) {
       w.y = fmaf(-p.lr, gr.y, w.y);
       w.z = fmaf(-p.lr, gr.z, w.z);
       w.w = fmaf(-p.lr, gr.w, w.w);
-      const u32x2_t hv2 = {(uint32_t)f32_to_bf16_rne(w.x) | ((uint32_t)f32_to_bf16_rne(w.y) << 16),
-                           (uint32_t)f32_to_bf16_rne(w.z) | ((uint32_t)f32_to_bf16_rne(w.w) << 16)};
+      const u32x2_t hv2 = {f32x2_to_bf16x2_rne(w.x, w.y),
+                           f32x2_to_bf16x2_rne(w.z, w.w)};
       if (NT) {
         __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(w_g + off));
         __builtin_nontemporal_store(hv2, reinterpret_cast<u32x2_t*>(s_g + off));

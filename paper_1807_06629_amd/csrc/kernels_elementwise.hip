@@ -30,14 +30,14 @@ template <bool NT> __device__ __forceinline__ void st2(u32x2_t* p, u32x2_t v) {
 
 __device__ __forceinline__ uint2 pack_bf16x4(float4 v) {
   uint2 r;
-  r.x = (uint32_t)f32_to_bf16_rne(v.x) | ((uint32_t)f32_to_bf16_rne(v.y) << 16);
-  r.y = (uint32_t)f32_to_bf16_rne(v.z) | ((uint32_t)f32_to_bf16_rne(v.w) << 16);
+  r.x = f32x2_to_bf16x2_rne(v.x, v.y);
+  r.y = f32x2_to_bf16x2_rne(v.z, v.w);
   return r;
 }
 __device__ __forceinline__ u32x2_t pack_bf16x4(f32x4_t v) {
   u32x2_t r;
-  r.x = (uint32_t)f32_to_bf16_rne(v.x) | ((uint32_t)f32_to_bf16_rne(v.y) << 16);
-  r.y = (uint32_t)f32_to_bf16_rne(v.z) | ((uint32_t)f32_to_bf16_rne(v.w) << 16);
+  r.x = f32x2_to_bf16x2_rne(v.x, v.y);
+  r.y = f32x2_to_bf16x2_rne(v.z, v.w);
   return r;
 }
 

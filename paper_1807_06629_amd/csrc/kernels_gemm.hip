@@ -459,8 +459,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
           w.y = fmaf(-p.lr, gr.y, w.y);
           w.z = fmaf(-p.lr, gr.z, w.z);
           w.w = fmaf(-p.lr, gr.w, w.w);
-          const u32x2_t hv = {(uint32_t)f32_to_bf16_rne(w.x) | ((uint32_t)f32_to_bf16_rne(w.y) << 16),
-                              (uint32_t)f32_to_bf16_rne(w.z) | ((uint32_t)f32_to_bf16_rne(w.w) << 16)};
+          const u32x2_t hv = {f32x2_to_bf16x2_rne(w.x, w.y),
+                              f32x2_to_bf16x2_rne(w.z, w.w)};
           if (p.streaming) {
             __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(wbase + off));
             if (p.shadow != nullptr)

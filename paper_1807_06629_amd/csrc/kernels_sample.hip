@@ -33,8 +33,8 @@ __device__ __forceinline__ void gather_row(const GatherArgs& a, int j, int i) {
       const float4 v = src4[c];
       if (BF16) {
         uint2 h;
-        h.x = (uint32_t)f32_to_bf16_rne(v.x) | ((uint32_t)f32_to_bf16_rne(v.y) << 16);
-        h.y = (uint32_t)f32_to_bf16_rne(v.z) | ((uint32_t)f32_to_bf16_rne(v.w) << 16);
+        h.x = f32x2_to_bf16x2_rne(v.x, v.y);
+        h.y = f32x2_to_bf16x2_rne(v.z, v.w);
         reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.xb) + slot * ld0)[c] = h;
       } else {
         reinterpret_cast<float4*>(reinterpret_cast<float*>(a.xb) + slot * ld0)[c] = v;
