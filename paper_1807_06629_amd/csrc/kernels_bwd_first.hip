@@ -11,17 +11,27 @@
 // forward launch and its read of the bf16 shadow are gone).
 //
 // For the contraction of X^{t+1} W_1 over the rows k of W_1 to stay inside one workgroup, the walk is
-// transposed against the other layers' kernel: a workgroup (4 wavefronts) owns 64 COLUMNS n of W_1 of
-// one replica and walks down all rows in tiles of 64.  D_1[:, n-band] stays in LDS and the B x 64
-// accumulators of the next pre-activation stay in registers; per tile it stages X^t[:, k-tile] and
-// X^{t+1}[:, k-tile] (both L2-resident), forms the dW tile, passes it through LDS into the row-major
-// layout of the 16-byte weight loads, writes master and shadow, and multiplies X^{t+1}[:, k-tile] with
-// the new tile.  Every output block accumulates over k in the order of the stand-alone forward
-// product, and the bias is summed as in the other layers' kernel, so H_1^{t+1} and the parameters
-// have the bits the two separate launches give.  Whole tiles only (B = 32 MB, d_0 and d_1 multiples
-// of 64); straight-line memory operations, first and last two steps peeled, as in the whole-tile
-// kernel of the other layers.
+// transposed against the other layers' kernel: a workgroup owns a band of NB columns n of W_1 of one
+// replica and walks down all rows in tiles of 64.  The B x NB accumulators of the next pre-activation
+// and the matrix fragments of D_1[:, n-band] stay in registers; X^t[:, k-tile] and X^{t+1}[:, k-tile] (both
+// L2-resident) are requested straight into LDS.  A wavefront owns a 32 x 32 block of every weight tile:
+// it multiplies the block's gradient, turns it through a piece of LDS of its own into the row-major
+// layout of the 16-byte weight loads, updates, stores, and leaves the new block as bf16 for the next
+// product.  Tile i's gradient and tile i - 1's share of the next pre-activation are independent, so
+// they run in the same phase, and a tile costs ONE workgroup barrier.  Requests go out at the start
+// of a phase, X one tile and W_1 two tiles ahead: the memory pipe returns in order, so that the wait
+// for an X tile also covers the weights requested before it, which have had two phases by then.
+// What bounds it: the weight stream (8 B per element), and per compute unit the X tiles beside it --
+// 128 columns per workgroup of eight wavefronts where that still gives every compute unit one (B = 128:
+// 96 instead of 128 KB pass through the unit per 32 KB of weights), 64 columns and four otherwise.
+// Measured against five barriers per tile and X tiles through registers: 8 x (4096 x 4096), 128 rows 242 ->
+// 208 us (5.2 TB/s of weight bytes); 16 x (3072 x 1024), 64 rows 85 -> 76 us (5.3 TB/s).
+//
+// Every output block accumulates over k in the order of the stand-alone forward product, and the bias
+// is summed as in the other layers' kernel, so H_1^{t+1} and the parameters have the bits the two
+// separate launches give.  Whole tiles only (B = 32 MB, d_0 a multiple of 128, d_1 of 64).
 #include <atomic>
+#include <type_traits>
 
 #include "prsgd_internal.h"
 
@@ -33,12 +43,8 @@ typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 namespace {
 
-constexpr int BT = 64;              // tile edge: weight rows per step, weight columns per workgroup
-constexpr int SD = BT + 16;         // LDS row stride of the D_1 band   [b][n]  (bf16 elements)
-constexpr int SH = BT + 16;         // LDS row stride of the X^t tile   [b][k]
-constexpr int SX = BT + 8;          // LDS row stride of the X^{t+1} tile [b][k] (contraction-contiguous reads)
-constexpr int SW = BT + 32;         // LDS row stride of the new W tile [k][n]  (transpose reads)
-constexpr int SG = BT + 4;          // LDS row stride of the dW tile    [k][n]  (floats)
+constexpr int BT = 64;              // weight rows per step
+constexpr int ST = 36;              // LDS row stride of a wavefront's 32 x 32 transposition piece (floats)
 
 __device__ __forceinline__ f32x16_t mfma_bf16(bf16x8_t a, bf16x8_t b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -47,24 +53,65 @@ __device__ __forceinline__ float act_from_z(float z, int act) {
   return act == PRSGD_TANH ? tanhf(z) : fmaxf(z, 0.0f);
 }
 
-constexpr size_t first_lds_bytes(int mb) {
-  const size_t br = 32 * (size_t)mb;
-  const size_t hk = sizeof(uint16_t) * br * SH, gl = sizeof(float) * BT * SG;
-  return sizeof(uint16_t) * (br * SD + br * SX + BT * SW) + (hk > gl ? hk : gl) + sizeof(float) * 5 * BT;
+// LDS tiles are unpadded (requests land at consecutive addresses) and permuted instead, as in the
+// grouped products: a tile whose row is the contraction index has its 64-byte segments exchanged so
+// that the four rows of a transpose read fall on different banks ...
+template <int ROW_BYTES> __device__ __forceinline__ int seg_xor(int c) {
+  return ROW_BYTES == 128 ? (c >> 1) & 1 : c & 3;
+}
+template <int ROW_BYTES>
+__device__ __forceinline__ bf16x8_t frag_rows(const unsigned char* tile, int block, int kk, int lane) {
+  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
+  typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
+  const int g = lane >> 4, r16 = lane & 15;
+  const int c = kk * 16 + 8 * (g >> 1) + (r16 >> 2);
+  const unsigned char* p = tile + c * ROW_BYTES + ((block ^ seg_xor<ROW_BYTES>(r16 >> 2)) << 6) + 32 * (g & 1) +
+                           8 * (r16 & 3);
+  const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
+  const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * ROW_BYTES));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// ... and a tile with contiguous contraction (128-byte rows) its 16-byte chunks, chunk q of row r at q ^ (r & 7).
+__device__ __forceinline__ bf16x8_t frag_cols(const unsigned char* tile, int block, int kk, int lane) {
+  const int r = lane & 31, kb = lane >> 5;
+  return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(
+      tile + (block * 32 + r) * 128 + (((2 * kk + kb) ^ (r & 7)) << 4)));
+}
+// 64 x 16 bytes from base + per-lane offset to LDS [lds_off, lds_off + 1024).  Invisible to the compiler's
+// wait counts; nothing else here uses m0.
+__device__ __forceinline__ void load_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
+  const uint64_t u = (uint64_t)(uintptr_t)base_any;
+  const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)u) |
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32);
+  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
 }
 
-// MB: 32-row tiles of the minibatch (B = 32 MB).  NT: non-temporal weight traffic.  SHW: also write
-// the bf16 shadow of W_1 (only the stand-alone forward product reads it; the caller may leave it
-// stale while this kernel supplies H_1, and refresh it when that chain breaks).  MOM: momentum form
-// of the local update, v <- mu v + G, x <- x - gamma v, with the velocity tile streamed beside the
-// weights.
-template <int MB, bool NT, bool SHW, bool MOM>
-__global__ __launch_bounds__(kThreads) void bwd_first_fwd_kernel(BwdArgs p) {
-  constexpr int BR = 32 * MB;
-  constexpr int S = 2;                                // weight tiles in flight
-  constexpr int NZ = (2 * MB + 3) / 4;                // next-activation blocks (32 x 32) per wavefront
+// LDS of a workgroup: two X^t tiles, three X^{t+1} tiles, two new weight tiles, the wavefronts'
+// transposition pieces, partial column sums and the new bias.  The D_1 band passes through the X^{t+1}
+// tiles before the walk.
+constexpr size_t first_lds_bytes(int mb, int nb) {
+  const size_t x_tile = 32 * (size_t)mb * 128, waves = (size_t)nb / 16;
+  return 5 * x_tile + 2 * (size_t)BT * nb * 2 + waves * 32 * ST * 4 + 5 * (size_t)nb * 4;
+}
 
-  const int bands = p.Nn / BT;
+// MB: 32-row tiles of the minibatch (B = 32 MB).  NB: band width, 64 or 128.  NT: non-temporal weight
+// traffic.  SHW: also write the bf16 shadow of W_1 (only the stand-alone forward product reads it;
+// the caller may leave it stale while this kernel supplies H_1, and refresh it when that chain
+// breaks).  MOM: momentum form of the local update, v <- mu v + G, x <- x - gamma v, with the velocity
+// tile streamed beside the weights.
+template <int MB, int NB, bool NT, bool SHW, bool MOM>
+__global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdArgs p) {
+  constexpr int BR = 32 * MB;
+  constexpr int NW = NB / 16, NTHR = 64 * NW;         // wavefronts: 2 (rows) x NB / 32 (columns)
+  constexpr int NBLK = MB * (NB / 32);                // next-activation blocks (32 x 32)
+  constexpr int NZ = (NBLK + NW - 1) / NW;            // ... per wavefront
+  constexpr int XT = BR * 128;                        // bytes of an X tile [BR][64]
+  constexpr int WT = BT * NB * 2;                     // bytes of a new weight tile [BT][NB]
+  constexpr int REQ = (XT / 1024 + NW - 1) / NW;      // requests per wavefront and X tile
+
+  const int bands = p.Nn / NB;
   int g, band;
   if ((p.n_groups & 7) == 0) {                        // all bands of a replica on one XCD
     const int slot = blockIdx.x >> 3;
@@ -74,85 +121,96 @@ __global__ __launch_bounds__(kThreads) void bwd_first_fwd_kernel(BwdArgs p) {
     g = blockIdx.x / bands;
     band = blockIdx.x % bands;
   }
-  const int n0 = band * BT;
+  const int n0 = band * NB;
 
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr size_t kHkBytes = sizeof(uint16_t) * BR * SH, kGlBytes = sizeof(float) * BT * SG;
-  uint16_t* Dn = reinterpret_cast<uint16_t*>(smem);                      // [BR][SD]  D_1 band, resident
-  uint16_t* Hk = Dn + BR * SD;                                           // [BR][SH]  X^t tile ...
-  float* Gl = reinterpret_cast<float*>(Hk);                              // ... and, after it, the dW tile [BT][SG]
-  uint16_t* Xk = reinterpret_cast<uint16_t*>(reinterpret_cast<unsigned char*>(Hk) +
-                                             (kHkBytes > kGlBytes ? kHkBytes : kGlBytes));   // [BR][SX]
-  uint16_t* Wl = Xk + BR * SX;                                           // [BT][SW]  new W tile, bf16
-  float* Bs = reinterpret_cast<float*>(Wl + BT * SW);                    // [4][BT] partial column sums
-  float* Bn = Bs + 4 * BT;                                               // [BT]    new bias of the band
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  unsigned char* const Hk = smem;                                        // [2][BR][64]  X^t tiles
+  unsigned char* const Xk = Hk + 2 * XT;                                 // [3][BR][64]  X^{t+1} tiles
+  unsigned char* const Wl = Xk + 3 * XT;                                 // [2][BT][NB]  new W tiles, bf16
+  float* const Tl = reinterpret_cast<float*>(Wl + 2 * WT);               // [NW][32][ST]
+  float* const Bs = Tl + NW * 32 * ST;                                   // [4][NB] partial column sums
+  float* const Bn = Bs + 4 * NB;                                         // [NB]    new bias of the band
+  uint16_t* const Dn = reinterpret_cast<uint16_t*>(Xk);                  // [BR][NB] D_1 band, before the walk
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr32 = lane & 31, kb = lane >> 5;
-  const int wk = wave >> 1, wn = wave & 1;
+  const int wk = wave & 1, wn = wave >> 1;            // this wavefront's block of the weight tile
 
   const uint16_t* h_g = p.h + (size_t)g * p.h_gs;               // X^t      [B][ldh]
   const uint16_t* x_g = p.x_next + (size_t)g * p.x_gs;          // X^{t+1}  [B][ldx]
   const uint16_t* d_g = p.d + (size_t)g * p.d_gs;               // D_1      [B][ldd]
-  float* w_g = p.params + (size_t)g * p.p_gs + p.w_off;
-  uint16_t* s_g = SHW ? p.shadow + (size_t)g * p.p_gs + p.w_off : nullptr;
-  const float* wsrc_g = p.src + (size_t)g * p.src_gs + p.w_off;
-  float* v_g = MOM ? p.vel + (size_t)g * p.p_gs + p.w_off : nullptr;
   const bool nt_read = NT && p.src_gs != 0;           // a shared source is re-read by every replica
 
-  const int prow = tid >> 3, pcol = (tid & 7) * 8;              // panels: row q*32 + prow
-  const int wrow = tid >> 4, wcol = 4 * (tid & 15);             // weights: row q*16 + wrow
-  auto fetch_panel = [&](u32x4_t (&reg)[MB], const uint16_t* src, int ld, int col0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < MB; ++q)
-      reg[q] = *reinterpret_cast<const u32x4_t*>(src + (size_t)(q * 32 + prow) * ld + col0 + pcol);
-  };
-  auto stash_panel = [&](uint16_t* lds, int stride, const u32x4_t (&reg)[MB]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < MB; ++q)
-      *reinterpret_cast<u32x4_t*>(lds + (q * 32 + prow) * stride + pcol) = reg[q];
-  };
-  auto fetch_w = [&](f32x4_t (&reg)[4], int k0) __attribute__((always_inline)) {
+  // the wavefront's block of a weight tile, row-major: vector q at row 8 q + lane / 8, column 4 (lane % 8)
+  const int trow = lane >> 3, tcol = 4 * (lane & 7);
+  const size_t w_first = (size_t)p.w_off + (size_t)(wk * 32 + trow) * p.ldw + n0 + wn * 32 + tcol;
+  float* const w_g = p.params + (size_t)g * p.p_gs + w_first;
+  uint16_t* const s_g = SHW ? p.shadow + (size_t)g * p.p_gs + w_first : nullptr;
+  const float* const wsrc_g = p.src + (size_t)g * p.src_gs + w_first;
+  float* const v_g = MOM ? p.vel + (size_t)g * p.p_gs + w_first : nullptr;
+  const size_t row8 = (size_t)8 * p.ldw;
+  auto fetch = [&](f32x4_t (&reg)[4], const float* base, int it, bool stream) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const f32x4_t* src =
-          reinterpret_cast<const f32x4_t*>(wsrc_g + (size_t)(k0 + q * 16 + wrow) * p.ldw + n0 + wcol);
-      reg[q] = nt_read ? __builtin_nontemporal_load(src) : *src;
-    }
-  };
-  auto fetch_v = [&](f32x4_t (&reg)[4], int k0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4_t* src =
-          reinterpret_cast<const f32x4_t*>(v_g + (size_t)(k0 + q * 16 + wrow) * p.ldw + n0 + wcol);
-      reg[q] = NT ? __builtin_nontemporal_load(src) : *src;
+      const f32x4_t* src = reinterpret_cast<const f32x4_t*>(base + (size_t)it * BT * p.ldw + q * row8);
+      reg[q] = stream ? __builtin_nontemporal_load(src) : *src;
     }
   };
 
-  const int n_t = p.K / BT;                           // steps of the walk down the rows
-  u32x4_t hr[MB], xr[MB];
-  f32x4_t wr[S][4];
-  f32x4_t vr[MOM ? S : 1][4];
-  fetch_panel(hr, d_g, p.ldd, n0);                    // the D_1 band first (through hr)
-  fetch_w(wr[0], 0);
-  if (MOM) fetch_v(vr[0], 0);
-  stash_panel(Dn, SD, hr);
-  fetch_panel(hr, h_g, p.ldh, 0);
-  fetch_panel(xr, x_g, p.ldx, 0);
-  fetch_w(wr[1], BT);
-  if (MOM) fetch_v(vr[1], BT);
-  __syncthreads();
+  // requests of an X tile: this lane's chunk of piece q * NW + wave (8 rows of 128 bytes)
+  uint32_t h_off[REQ], x_off[REQ];
+#pragma unroll
+  for (int q = 0; q < REQ; ++q) {
+    const int r = (q * NW + wave) * 8 + (lane >> 3), pos = lane & 7;
+    const int row = r < BR ? r : BR - 1;
+    h_off[q] = (uint32_t)(((size_t)row * p.ldh + ((((pos >> 2) ^ seg_xor<128>(r)) << 2) | (pos & 3)) * 8) * 2);
+    x_off[q] = (uint32_t)(((size_t)row * p.ldx + ((pos ^ (r & 7)) * 8)) * 2);
+  }
+  auto request_x = [&](int it, int hbuf, int xbuf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < REQ; ++q) {
+      if ((q * NW + wave) * 1024 < XT) {                                 // uniform over the wavefront
+        load_to_lds(h_g + it * BT, h_off[q], lds0 + hbuf * XT + (q * NW + wave) * 1024);
+        load_to_lds(x_g + it * BT, x_off[q], lds0 + (2 + xbuf) * XT + (q * NW + wave) * 1024);
+      }
+    }
+  };
 
-  // b_1 <- b_1 - gamma db_1: four quarter sums over the minibatch rows, added in order
-  {
-    float cs = 0.0f;
-#pragma unroll 8
-    for (int b = wave * (BR / 4); b < (wave + 1) * (BR / 4); ++b) cs += bf16_to_f32(Dn[b * SD + lane]);
-    Bs[wave * BT + lane] = cs;
+  const int n_t = p.K / BT;                           // steps of the walk down the rows (at least 4)
+  f32x4_t wr[3][4];
+  f32x4_t vr[MOM ? 3 : 1][4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    fetch(wr[j], wsrc_g, j, nt_read);
+    if (MOM) fetch(vr[j], v_g, j, NT);
+  }
+
+  // the D_1 band: through LDS for the column sums and into fragments
+  for (int e = tid; e < BR * (NB / 8); e += NTHR) {
+    const int b = e / (NB / 8), c = e % (NB / 8);
+    *reinterpret_cast<u32x4_t*>(reinterpret_cast<unsigned char*>(Dn) + b * (NB * 2) +
+                                ((((c >> 2) ^ seg_xor<NB * 2>(b)) << 6) | ((c & 3) << 4))) =
+        *reinterpret_cast<const u32x4_t*>(d_g + (size_t)b * p.ldd + n0 + 8 * c);
   }
   __syncthreads();
-  if (tid < BT) {
-    float cs = ((Bs[tid] + Bs[BT + tid]) + Bs[2 * BT + tid]) + Bs[3 * BT + tid];
+  bf16x8_t df[BR / 16];
+#pragma unroll
+  for (int kk = 0; kk < BR / 16; ++kk)
+    df[kk] = frag_rows<NB * 2>(reinterpret_cast<const unsigned char*>(Dn), wn, kk, lane);
+  // b_1 <- b_1 - gamma db_1: four quarter sums over the minibatch rows, added in order
+  {
+    const int n = tid % NB, quarter = tid / NB;                          // NTHR = 4 NB
+    float cs = 0.0f;
+#pragma unroll 8
+    for (int b = quarter * (BR / 4); b < (quarter + 1) * (BR / 4); ++b)
+      cs += bf16_to_f32(Dn[b * NB + (((n >> 5) ^ seg_xor<NB * 2>(b)) << 5) + (n & 31)]);
+    Bs[quarter * NB + n] = cs;
+  }
+  __syncthreads();                                    // the band's place is free for the X tiles
+  request_x(0, 0, 0);
+  if (tid < NB) {
+    float cs = ((Bs[tid] + Bs[NB + tid]) + Bs[2 * NB + tid]) + Bs[3 * NB + tid];
     const size_t bo = p.b_off + (size_t)n0 + tid;
     if (MOM) {
       float* vb = p.vel + (size_t)g * p.p_gs + bo;
@@ -169,51 +227,69 @@ __global__ __launch_bounds__(kThreads) void bwd_first_fwd_kernel(BwdArgs p) {
   for (int t = 0; t < NZ; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc_z[t][v] = 0.0f;
+  float* const T = Tl + wave * 32 * ST;
 
-  // One step of the walk: rows k0 .. k0 + 63 of the band.  PF: fetch the weight tile S steps ahead.
-  // NEXT: fetch the next minibatch tiles.  (Both flags are literal at every call site.)
-  auto tile_step = [&](int it, f32x4_t (&wr)[4], f32x4_t (&vr)[4], const bool PF, const bool NEXT) __attribute__((always_inline)) {
-    const int k0 = it * BT;
-    stash_panel(Hk, SH, hr);
-    stash_panel(Xk, SX, xr);
-    __syncthreads();
-    if (NEXT) {
-      fetch_panel(hr, h_g, p.ldh, k0 + BT);
-      fetch_panel(xr, x_g, p.ldx, k0 + BT);
+  // next pre-activation [b][n] += X^{t+1}[:, k-tile] bf16(W_new tile): contraction over the tile's rows
+  auto next_product = [&](int wbuf, int xbuf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NZ; ++t) {
+      const int blk = wave + NW * t;
+      if (NBLK % NW == 0 || blk < NBLK) {
+        const int mb = blk / (NB / 32), nblk = blk % (NB / 32);
+#pragma unroll
+        for (int kk = 0; kk < BT / 16; ++kk)
+          acc_z[t] = mfma_bf16(frag_cols(Xk + xbuf * XT, mb, kk, lane), frag_rows<NB * 2>(Wl + wbuf * WT, nblk, kk, lane),
+                               acc_z[t]);
+      }
     }
-    // dW tile [k][n] = X^t[:, k-tile]^T D_1[:, n-band]: contraction over the minibatch
+  };
+
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  int hbuf = 0, xbuf = 0;                             // buffers of tile it (its new weights: Wl[hbuf])
+  // Phase of tile it (weights in register set SLOT).  FIRST: no previous tile.  The requests past the
+  // last tile repeat it and are not used.
+  auto phase = [&](int it, auto slot_tag, auto first_tag) __attribute__((always_inline)) {
+    constexpr int SLOT = decltype(slot_tag)::value, AHEAD = (SLOT + 2) % 3;
+    constexpr bool FIRST = decltype(first_tag)::value;
+    const int xprev = xbuf == 0 ? 2 : xbuf - 1, xnext = xbuf == 2 ? 0 : xbuf + 1;
+    request_x(min(it + 1, n_t - 1), hbuf ^ 1, xnext);
+    const int ahead = min(it + 2, n_t - 1);
+    fetch(wr[AHEAD], wsrc_g, ahead, nt_read);
+    if (MOM) fetch(vr[AHEAD], v_g, ahead, NT);
+    // gradient block: contraction over the minibatch
     f32x16_t acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
 #pragma unroll
-    for (int kk = 0; kk < BR / 16; ++kk)
-      acc = mfma_bf16(frag_trans(Hk, SH, wk * 32, kk, lane), frag_trans(Dn, SD, wn * 32, kk, lane), acc);
-    __syncthreads();                                  // the dW tile takes the place of the X^t tile
+    for (int kk = 0; kk < BR / 16; ++kk) acc = mfma_bf16(frag_rows<128>(Hk + hbuf * XT, wk, kk, lane), df[kk], acc);
+    if (!FIRST) next_product(hbuf ^ 1, xprev);
+    // accumulator element v of lane (lr32, kb) is C[8 (v/4) + 4 kb + v%4][lr32]
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-      Gl[(wk * 32 + 8 * (v / 4) + 4 * kb + (v % 4)) * SG + wn * 32 + lr32] = acc[v];
-    __syncthreads();
-    // eq. (3) on the tile, in the layout of the weight loads; the new tile also goes to LDS as bf16
+    for (int v = 0; v < 16; ++v) T[(8 * (v / 4) + 4 * kb + (v % 4)) * ST + lr32] = acc[v];
+    __builtin_amdgcn_wave_barrier();                  // the piece is this wavefront's own
+    f32x4_t grad[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) grad[q] = *reinterpret_cast<const f32x4_t*>(T + (8 * q + trow) * ST + tcol);
+    // eq. (3) on the block, in the layout of the weight loads; the new block also goes to LDS as bf16
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int row = q * 16 + wrow;
-      f32x4_t gr = *reinterpret_cast<const f32x4_t*>(Gl + row * SG + wcol);
-      const size_t off = (size_t)(k0 + row) * p.ldw + n0 + wcol;
+      f32x4_t gr = grad[q];
+      const size_t off = (size_t)it * BT * p.ldw + q * row8;
       if (MOM) {
-        gr.x = fmaf(p.mu, vr[q].x, gr.x);
-        gr.y = fmaf(p.mu, vr[q].y, gr.y);
-        gr.z = fmaf(p.mu, vr[q].z, gr.z);
-        gr.w = fmaf(p.mu, vr[q].w, gr.w);
+        gr.x = fmaf(p.mu, vr[SLOT][q].x, gr.x);
+        gr.y = fmaf(p.mu, vr[SLOT][q].y, gr.y);
+        gr.z = fmaf(p.mu, vr[SLOT][q].z, gr.z);
+        gr.w = fmaf(p.mu, vr[SLOT][q].w, gr.w);
         if (NT) __builtin_nontemporal_store(gr, reinterpret_cast<f32x4_t*>(v_g + off));
         else *reinterpret_cast<f32x4_t*>(v_g + off) = gr;
       }
-      f32x4_t w = wr[q];
+      f32x4_t w = wr[SLOT][q];
       w.x = fmaf(-p.lr, gr.x, w.x);
       w.y = fmaf(-p.lr, gr.y, w.y);
       w.z = fmaf(-p.lr, gr.z, w.z);
       w.w = fmaf(-p.lr, gr.w, w.w);
-      const u32x2_t hv2 = {(uint32_t)f32_to_bf16_rne(w.x) | ((uint32_t)f32_to_bf16_rne(w.y) << 16),
-                           (uint32_t)f32_to_bf16_rne(w.z) | ((uint32_t)f32_to_bf16_rne(w.w) << 16)};
+      const u32x2_t hv2 = {f32x2_to_bf16x2_rne(w.x, w.y),
+                           f32x2_to_bf16x2_rne(w.z, w.w)};
       if (NT) {
         __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(w_g + off));
         if (SHW) __builtin_nontemporal_store(hv2, reinterpret_cast<u32x2_t*>(s_g + off));
@@ -221,46 +297,39 @@ __global__ __launch_bounds__(kThreads) void bwd_first_fwd_kernel(BwdArgs p) {
         *reinterpret_cast<f32x4_t*>(w_g + off) = w;
         if (SHW) *reinterpret_cast<u32x2_t*>(s_g + off) = hv2;
       }
-      *reinterpret_cast<u32x2_t*>(Wl + row * SW + wcol) = hv2;
+      const int k = wk * 32 + 8 * q + trow;
+      *reinterpret_cast<u32x2_t*>(Wl + hbuf * WT + k * (NB * 2) + ((wn ^ seg_xor<NB * 2>(k)) << 6) + 2 * tcol) = hv2;
     }
-    __syncthreads();
-    // next pre-activation [b][n] += X^{t+1}[:, k-tile] bf16(W_new tile): contraction over k
-#pragma unroll
-    for (int t = 0; t < NZ; ++t) {
-      const int blk = wave + 4 * t;
-      if (blk < 2 * MB) {
-        const int mb = blk >> 1, nblk = blk & 1;
-#pragma unroll
-        for (int kk = 0; kk < BT / 16; ++kk)
-          acc_z[t] = mfma_bf16(frag_contig(Xk, SX, mb * 32, kk, lane), frag_trans(Wl, SW, nblk * 32, kk, lane),
-                               acc_z[t]);
-      }
-    }
-    if (PF) {
-      fetch_w(wr, k0 + S * BT);
-      if (MOM) fetch_v(vr, k0 + S * BT);
-    }
-    __syncthreads();                                  // the tiles in LDS are rewritten by the next step
+    // The next X tile has landed (younger than its requests: this phase's weight loads and stores), the
+    // new weights are in LDS, and nobody reads this phase's tiles any more.
+    constexpr int YOUNGER = (MOM ? 16 : 8) + (SHW ? 4 : 0);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(YOUNGER) : "memory");
+    hbuf ^= 1;
+    xbuf = xnext;
   };
 
-  int it = 0;
-#pragma unroll
-  for (int st = 0; st < S; ++st) tile_step(st, wr[st], vr[MOM ? st : 0], true, true);
-  for (it = S; it < n_t - S; it += S) {
-#pragma unroll
-    for (int st = 0; st < S; ++st) tile_step(it + st, wr[st], vr[MOM ? st : 0], true, true);
+  const std::integral_constant<int, 0> set0{};
+  const std::integral_constant<int, 1> set1{};
+  const std::integral_constant<int, 2> set2{};
+  phase(0, set0, std::true_type{});
+  for (int it = 1;;) {
+    phase(it, set1, std::false_type{});
+    if (++it == n_t) break;
+    phase(it, set2, std::false_type{});
+    if (++it == n_t) break;
+    phase(it, set0, std::false_type{});
+    if (++it == n_t) break;
   }
-#pragma unroll
-  for (int st = 0; st < S; ++st)                      // the last S tiles: nothing left to prefetch
-    tile_step(it + st, wr[st], vr[MOM ? st : 0], false, st + 1 < S);
+  next_product(hbuf ^ 1, xbuf == 0 ? 2 : xbuf - 1);   // the last tile's share
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no request into LDS outlives the workgroup
 
   // ---- H_1^{t+1} = phi(Z + b_1) for this band ------------------------------------------------------
   uint16_t* hn_g = p.h_next + (size_t)g * p.hn_gs;
 #pragma unroll
   for (int t = 0; t < NZ; ++t) {
-    const int blk = wave + 4 * t;
-    if (blk < 2 * MB) {
-      const int mb = blk >> 1, nblk = blk & 1;
+    const int blk = wave + NW * t;
+    if (NBLK % NW == 0 || blk < NBLK) {
+      const int mb = blk / (NB / 32), nblk = blk % (NB / 32);
       const int n = nblk * 32 + lr32;
       const float bn = Bn[n];
 #pragma unroll
@@ -272,34 +341,38 @@ __global__ __launch_bounds__(kThreads) void bwd_first_fwd_kernel(BwdArgs p) {
   }
 }
 
-template <int MB, bool SHW, bool MOM>
+template <int MB, int NB, bool NT, bool SHW, bool MOM>
 hipError_t launch_first_one(const BwdArgs& p, hipStream_t s) {
-  constexpr size_t kLds = first_lds_bytes(MB);
+  constexpr size_t kLds = first_lds_bytes(MB, NB);
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+  auto kernel = bwd_first_fwd_kernel<MB, NB, NT, SHW, MOM>;
   static std::atomic<bool> configured{false};
   if (!configured.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_first_fwd_kernel<MB, true, SHW, MOM>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_first_fwd_kernel<MB, false, SHW, MOM>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (e != hipSuccess) return e;
     configured.store(true, std::memory_order_release);
   }
-  const int bands = p.Nn / BT;
-  if (p.streaming)
-    hipLaunchKernelGGL((bwd_first_fwd_kernel<MB, true, SHW, MOM>), dim3((unsigned)(bands * p.n_groups)),
-                       dim3(kThreads), kLds, s, p);
-  else
-    hipLaunchKernelGGL((bwd_first_fwd_kernel<MB, false, SHW, MOM>), dim3((unsigned)(bands * p.n_groups)),
-                       dim3(kThreads), kLds, s, p);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(p.Nn / NB * p.n_groups)), dim3(4 * NB), kLds, s, p);
   return hipGetLastError();
 }
 
-template <int MB>
-hipError_t launch_first_mb(const BwdArgs& p, hipStream_t s) {
-  const bool shw = p.shadow != nullptr, mom = p.vel != nullptr;
-  if (mom) return shw ? launch_first_one<MB, true, true>(p, s) : launch_first_one<MB, false, true>(p, s);
-  return shw ? launch_first_one<MB, true, false>(p, s) : launch_first_one<MB, false, false>(p, s);
+template <int MB, int NB, bool NT>
+hipError_t launch_first_nt(const BwdArgs& p, hipStream_t s) {
+  const bool shw = p.shadow != nullptr;
+  if constexpr (NB == 64) {
+    if (p.vel != nullptr)
+      return shw ? launch_first_one<MB, NB, NT, true, true>(p, s) : launch_first_one<MB, NB, NT, false, true>(p, s);
+  }
+  return shw ? launch_first_one<MB, NB, NT, true, false>(p, s) : launch_first_one<MB, NB, NT, false, false>(p, s);
+}
+
+// 128-column bands where they still give every compute unit a workgroup; not with momentum, whose second
+// stream of tiles does not fit the registers of eight wavefronts.
+template <int MB> hipError_t launch_first_mb(const BwdArgs& p, hipStream_t s) {
+  const bool wide = p.vel == nullptr && (p.Nn % 128) == 0 && (long)(p.Nn / 128) * p.n_groups >= 256;
+  if (wide) return p.streaming ? launch_first_nt<MB, 128, true>(p, s) : launch_first_nt<MB, 128, false>(p, s);
+  return p.streaming ? launch_first_nt<MB, 64, true>(p, s) : launch_first_nt<MB, 64, false>(p, s);
 }
 
 }  // namespace
