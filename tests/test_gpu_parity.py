@@ -410,6 +410,31 @@ def test_bf16_heterogeneous_steps_mask_the_fused_backward_kernel(P, D):
     P.prsgd_destroy(h)
 
 
+@pytest.mark.parametrize("dims,batch", [((256, 128, 64, 10), 32), ((100, 72, 40, 10), 24)])
+@pytest.mark.parametrize("steps", [[1, 2, 4], [2, 2, 2], [3, 2, 3], [0, 1, 2]])
+def test_algorithm3_steps_that_every_worker_takes(P, D, dims, batch, steps):
+    """Those steps run unmasked, the first straight from the node average (no broadcast): same bits as
+    from the broadcast replicas, on whole-tile and ragged layers, and the oracle's points."""
+    w = small_mlp(dims=dims, batch=batch, n_workers=3, gemm_dtype="bf16", activation="tanh", rows_per_worker=256)
+    inp = inputs_for(w)
+    outs = []
+    for lazy in (True, False):
+        h = _open(D, w, inp)
+        P.prsgd_set_lazy_restart(h, lazy)
+        D.run_algorithm3(h, steps, 3)
+        P.prsgd_local_steps_hetero(h, steps)
+        outs.append((D.read_all(h), P.prsgd_read_loss(h), P.prsgd_read_indices(h)))
+        P.prsgd_destroy(h)
+    for a, b in zip(outs[0], outs[1]):
+        assert np.array_equal(a, b)
+    h = _open(D, w, inp)
+    D.run_algorithm3(h, steps, 2)
+    want = oracle.run_heterogeneous(**oracle_args(w, inp), lr=w.lr, worker_steps=steps, n_epochs=2)
+    assert P.prsgd_iteration(h) == want["t"]
+    assert rel_err(D.read_all(h), want["x"]) <= 5e-3
+    P.prsgd_destroy(h)
+
+
 @pytest.mark.parametrize("shape", [
     dict(dims=(72, 96, 256, 10), batch=32, n_workers=3),          # layer 2: three 32-row bands
     dict(dims=(64, 160, 384, 12), batch=64, n_workers=2),         # five bands, six column tiles
