@@ -23,6 +23,14 @@ extern "C" {
 int prsgd_copy_bytes(void* dst_dev, const void* src_dev, size_t bytes, void* hip_stream);
 
 /*
+ * The output tile that a forward or backward-data product of n_workers minibatches of `rows` rows and
+ * a layer of `cols` columns is cut into: out[0] tile rows, out[1] tile columns, out[2] bytes of LDS a
+ * workgroup takes.  Host only; tests use it to see which kernels a shape reaches.  PRSGD_EINVAL on
+ * a size below 1, an unknown gemm_dtype or a null `out`.
+ */
+int prsgd_product_tile(int32_t rows, int32_t cols, int32_t n_workers, int32_t gemm_dtype, int32_t* out);
+
+/*
  * Number of polls after which a workgroup of the one-launch epoch kernel stops waiting for its
  * team (see prsgd_status in prsgd.h); the default is 2^22.  Tests set a tiny value to drive the
  * give-up path from the host while every kernel still runs to its end.

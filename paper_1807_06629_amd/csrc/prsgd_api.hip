@@ -1198,6 +1198,19 @@ int prsgd_copy_bytes(void* dst_dev, const void* src_dev, size_t bytes, void* hip
   return PRSGD_OK;
 }
 
+int prsgd_product_tile(int32_t rows, int32_t cols, int32_t n_workers, int32_t gemm_dtype, int32_t* out) {
+  if (rows < 1 || cols < 1 || n_workers < 1 || (gemm_dtype != PRSGD_F32 && gemm_dtype != PRSGD_BF16) ||
+      out == nullptr)
+    return set_err(nullptr, PRSGD_EINVAL, "prsgd_product_tile: bad argument");
+  int tile_rows = 0, tile_cols = 0;
+  size_t lds = 0;
+  gemm_rows_shape(rows, cols, n_workers, gemm_dtype == PRSGD_BF16, &tile_rows, &tile_cols, &lds);
+  out[0] = tile_rows;
+  out[1] = tile_cols;
+  out[2] = (int32_t)lds;
+  return PRSGD_OK;
+}
+
 int prsgd_status(prsgd_ctx* ctx) {
   if (ctx == nullptr) return PRSGD_EINVAL;
   const int arc = check_fused2_abort(ctx);

@@ -133,6 +133,8 @@ const char* kernel_kind_name(int kind);
 // ---- launchers (each returns the hipError_t of the launch) --------------------------------
 hipError_t launch_gemm_fwd(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s);
 hipError_t launch_gemm_dx(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s);
+// Tile and LDS bytes per workgroup of the batch-row product [rows] x [cols] of n_groups workers.
+void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows, int* tile_cols, size_t* lds_bytes);
 // Weight-gradient products of up to kMaxGemmSet layers: products that may share a launch, or one that
 // may not.
 constexpr int kMaxGemmSet = 4;

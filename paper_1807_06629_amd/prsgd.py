@@ -82,6 +82,7 @@ def _load() -> ctypes.CDLL:
         "prsgd_sample_indices": (ctypes.c_int, [ctypes.c_uint64, i32, i32, i64, i64, i32, vp, vp]),
         "prsgd_sgd_update": (ctypes.c_int, [vp, vp, vp, sz, ctypes.c_float, vp]),
         "prsgd_copy_bytes": (ctypes.c_int, [vp, vp, sz, vp]),
+        "prsgd_product_tile": (ctypes.c_int, [i32, i32, i32, i32, vp]),
         "prsgd_time_varying_schedule": (ctypes.c_int, [i32, i32, vp, vp]),
         "prsgd_status": (ctypes.c_int, [vp]),
         "prsgd_set_epoch_wait_limit": (ctypes.c_int, [vp, ctypes.c_uint32]),
@@ -334,6 +335,12 @@ def prsgd_set_restart_fusion(h: Handle, on: bool) -> None:
 
 def prsgd_set_first_layer_fusion(h: Handle, on: bool) -> None:
     _check(_lib.prsgd_set_first_layer_fusion(h.ctx, 1 if on else 0), h.ctx)
+
+
+def prsgd_product_tile(rows: int, cols: int, n_workers: int, gemm_dtype: str):
+    out = (ctypes.c_int32 * 3)()
+    _check(_lib.prsgd_product_tile(rows, cols, n_workers, {"f32": PRSGD_F32, "bf16": PRSGD_BF16}[gemm_dtype], out))
+    return tuple(out)
 
 
 def prsgd_set_lr(h: Handle, lr: float) -> None:

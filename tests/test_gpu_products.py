@@ -23,13 +23,25 @@ SHAPES = [
     ("bf16", (64, 65, 63, 10), 33, 3),
     ("bf16", (127, 128, 129, 37), 65, 6),
     ("bf16", (600, 40, 72, 9), 31, 5),
-    ("bf16", (72, 520, 130, 12), 64, 32),            # 64-row tiles
+    ("bf16", (72, 600, 520, 12), 64, 20),            # 64 x 64 tiles
+    ("bf16", (72, 520, 130, 12), 64, 32),            # several rounds of tiles
+    ("bf16", (72, 1032, 1000, 12), 100, 12),         # 128 x 64 tiles, ragged rows
+    ("bf16", (72, 1032, 1024, 12), 128, 12),         # 128 x 64 tiles, whole rows
     ("bf16", (72, 1032, 1000, 12), 160, 16),         # 128-row tiles, ragged contraction and rows
     ("f32", (1, 33, 3), 1, 1),
     ("f32", (31, 32, 33, 10), 33, 3),
     ("f32", (300, 65, 100, 37), 50, 6),
     ("f32", (40, 520, 72, 9), 130, 20),              # 64-row tiles
 ]
+
+
+def test_every_tile_is_reached():
+    # forward products have the columns of layers 1 and up, backward-data ones those of the hidden layers
+    from paper_1807_06629_amd import prsgd as P
+    for dtype, tiles in (("bf16", {(32, 64), (64, 64), (128, 64), (128, 128)}), ("f32", {(32, 32), (64, 64)})):
+        seen = [{P.prsgd_product_tile(b, d, n, dtype)[:2] for t, dims, b, n in SHAPES if t == dtype for d in dims[1:last]}
+                for last in (None, -1)]
+        assert seen[0] == tiles and seen[1] == tiles, (dtype, seen)
 
 
 @pytest.mark.parametrize("dtype,dims,batch,n_workers", SHAPES)

@@ -1,0 +1,38 @@
+"""Which tile a forward or backward-data product is cut into (host rule, no GPU)."""
+import os
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LDS_BYTES = 160 * 1024                                   # of a compute unit
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not os.path.exists(os.path.join(ROOT, "paper_1807_06629_amd", "libprsgd.so")):
+        from paper_1807_06629_amd.build import build
+        build()
+    from paper_1807_06629_amd import prsgd
+    return prsgd
+
+
+# minibatch rows, layer columns, workers: from one tile to many rounds of them
+SHAPES = [(b, n, w) for b in (1, 8, 31, 32, 33, 64, 65, 100, 128, 129, 300, 512)
+          for n in (10, 100, 256, 300, 1000, 1024, 4096) for w in (1, 8, 12, 16, 64, 200)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_compute_unit_holds_two_workgroups_of_the_smaller_tiles(P, dtype):
+    seen = set()
+    for b, n, w in SHAPES:
+        rows, cols, lds = P.prsgd_product_tile(b, n, w, dtype)
+        seen.add((rows, cols))
+        if (rows, cols) != (128, 128):
+            assert 2 * lds <= LDS_BYTES, (b, n, w, rows, cols, lds)
+    assert seen == ({(32, 64), (64, 64), (128, 64), (128, 128)} if dtype == "bf16" else {(32, 32), (64, 64)})
+
+
+def test_bad_arguments_are_rejected(P):
+    for bad in ((0, 1, 1), (1, 0, 1), (1, 1, 0)):
+        with pytest.raises(P.PrsgdError):
+            P.prsgd_product_tile(*bad, "f32")
