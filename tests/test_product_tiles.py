@@ -32,6 +32,13 @@ def test_a_compute_unit_holds_two_workgroups_of_the_smaller_tiles(P, dtype):
     assert seen == ({(32, 64), (64, 64), (128, 64), (128, 128)} if dtype == "bf16" else {(32, 32), (64, 64)})
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_no_tile_is_taller_than_the_minibatch(P, dtype):
+    for b, n, w in SHAPES:
+        rows, cols, _ = P.prsgd_product_tile(b, n, w, dtype)
+        assert rows <= (32 if b <= 32 else 64 if b <= 64 else 128), (b, n, w, rows, cols)
+
+
 def test_bad_arguments_are_rejected(P):
     for bad in ((0, 1, 1), (1, 0, 1), (1, 1, 0)):
         with pytest.raises(P.PrsgdError):
