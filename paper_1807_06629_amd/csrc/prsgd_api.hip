@@ -501,6 +501,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
 
   // backward.  bf16 operands with the fused update: one kernel per layer does the weight
   // gradient, eq. (3) and the delta of the layer below in a single pass over W_l.
+  bool first_shadow_left = false;
   for (int l = L; fused_bwd && l >= 1; --l) {
     BwdArgs q;
     memset(&q, 0, sizeof(q));
@@ -523,7 +524,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
         if (rc != PRSGD_OK) return rc;
         q.shadow = nullptr;                 // replica shadows of W_1 have no reader while H_1 comes from here
         LAUNCH(ctx, KK_BWD_FIRST, launch_bwd_first_fwd(q, s));
-        ctx->shadow1_stale = true;
+        ctx->shadow1_stale = first_shadow_left = true;
         ctx->h1_t = t + 1;
         ctx->h1_batch = bk ^ 1;
         continue;
@@ -551,6 +552,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     const int rc = dw.flush();
     if (rc != PRSGD_OK) return rc;
   }
+  // every other backward pass of layer 1 writes the shadows of the replicas it steps
+  if (fused_bwd && worker_steps == nullptr && !first_shadow_left) ctx->shadow1_stale = false;
 
   if (!c.fused_update) {
     if (ctx->velocity() != nullptr)

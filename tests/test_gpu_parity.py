@@ -435,6 +435,27 @@ def test_algorithm3_steps_that_every_worker_takes(P, D, dims, batch, steps):
     P.prsgd_destroy(h)
 
 
+@pytest.mark.parametrize("steps", [[2, 3, 4], [3, 4, 3], [4, 4, 4]])
+def test_algorithm3_epochs_refresh_no_shadow(P, D, steps):
+    """The last step that every worker takes writes the whole bf16 shadow of W_1 again, which the steps
+    before it left stale: the masked steps read it as it is, with the bits of separate launches."""
+    w = small_mlp(dims=(256, 128, 10), batch=32, n_workers=3, gemm_dtype="bf16", activation="tanh", rows_per_worker=256)
+    inp = inputs_for(w)
+    outs = []
+    for first_layer in (True, False):
+        h = _open(D, w, inp)
+        P.prsgd_set_first_layer_fusion(h, first_layer)
+        P.prsgd_profile_enable(h, True)
+        D.run_algorithm3(h, steps, 3)
+        launches = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
+        assert bool(launches.get("gemm_bwd_first")) == first_layer
+        assert not launches.get("refresh_shadow")
+        outs.append((D.read_all(h), P.prsgd_read_loss(h)))
+        P.prsgd_destroy(h)
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("shape", [
     dict(dims=(72, 96, 256, 10), batch=32, n_workers=3),          # layer 2: three 32-row bands
     dict(dims=(64, 160, 384, 12), batch=64, n_workers=2),         # five bands, six column tiles
