@@ -31,6 +31,13 @@ int prsgd_copy_bytes(void* dst_dev, const void* src_dev, size_t bytes, void* hip
 int prsgd_product_tile(int32_t rows, int32_t cols, int32_t n_workers, int32_t gemm_dtype, int32_t* out);
 
 /*
+ * Which launches of a configuration mark their weight traffic non-temporal: a sum of the constants
+ * below.  Host only, for tests.  PRSGD_EINVAL on an invalid configuration.
+ */
+enum { PRSGD_STREAM_STEPS = 1, PRSGD_STREAM_STEP_MEAN = 2 };
+int prsgd_streamed_uses(const prsgd_config* cfg);
+
+/*
  * Number of polls after which a workgroup of the one-launch epoch kernel stops waiting for its
  * team (see prsgd_status in prsgd.h); the default is 2^22.  Tests set a tiny value to drive the
  * give-up path from the host while every kernel still runs to its end.

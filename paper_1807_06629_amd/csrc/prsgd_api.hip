@@ -108,6 +108,21 @@ prsgd_config effective_config(const prsgd_config* c) {
 // 16 replicas of 3072-1024-1024-10 (269 MB) 157 -> 155 us per iteration, 274 -> 266 us with momentum.
 constexpr size_t kStreamingBytes = (size_t)192 << 20;
 
+// Which launches of a configuration are streamed.
+struct Streamed {
+  bool steps;         // local steps: they rewrite the replica set
+  bool step_mean;     // a step on the node average: the average is all it rewrites, and the next iteration reads
+                      // it again (16 x (3072-1024-1024-10) at interval 1, an average of 17 MB: 78 us per iteration, 84
+                      // streamed; 2 x (4096-4096-4096-4096-1000), 218 MB: 302 us, 295 streamed)
+};
+Streamed streamed_uses(const prsgd_config& c, const Layout& lo) {
+  const size_t average = (size_t)lo.m_pad * sizeof(float), set = average * (size_t)c.n_workers;
+  Streamed u;
+  u.steps = set >= kStreamingBytes;
+  u.step_mean = average >= kStreamingBytes;
+  return u;
+}
+
 void build_carve(const prsgd_config* c_in, const Layout& lo, Carve* cv) {
   const prsgd_config eff = effective_config(c_in);
   const prsgd_config* c = &eff;
@@ -166,7 +181,7 @@ struct prsgd_ctx {
   bool bf16;
   bool use_fused2;      // one-hidden-layer fp32 MLP: whole epochs in one launch
   Fused2Plan f2;
-  bool streaming;       // replica set >= 192 MiB: weight traffic is marked non-temporal
+  Streamed streamed;    // launches whose weight traffic is marked non-temporal
   bool lazy_restart;    // a restart only writes the node average; the next local iteration
                         // reads it as every worker's starting point (no broadcast)
   bool at_mean;         // the replicas are stale: every worker's current point is the vector `mean`
@@ -369,7 +384,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
   base.shadow = ctx->shadow();
   base.p_gs = lo.m_pad;
   base.worker_steps = worker_steps;
-  base.streaming = ctx->streaming ? 1 : 0;
+  base.streaming = ctx->streamed.steps ? 1 : 0;
   base.step = step;
 
   auto act_in = [&](int l) -> const void* {   // H_l as stored (l = 0: the gathered batch)
@@ -475,7 +490,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     // then moved by the averaged gradient; the points themselves are not rewritten.
     if (!from_mean)
       LAUNCH(ctx, KK_RESTART_MEAN,
-             launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), lo.m_pad, N, ctx->streaming, s));
+             launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), lo.m_pad, N, ctx->streamed.steps, s));
     // eq. (3) and eq. (2) in one pass over ybar, layer by layer from the top: D_{l-1} needs the
     // weights the forward pass used (the bf16 image of ybar, or of every worker's own point), and
     // when that is ybar it runs before layer l's pass changes it
@@ -490,6 +505,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
       p.lr = ctx->lr / (float)N;
       p.params = ctx->mean(); p.shadow = ctx->mean_shadow(); p.p_gs = 0;
       p.src = ctx->mean(); p.src_gs = 0;
+      p.streaming = ctx->streamed.step_mean ? 1 : 0;
       const int rc = dw.add(p, 1, KK_STEP_MEAN);
       if (rc != PRSGD_OK) return rc;
     }
@@ -512,7 +528,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     q.w_off = lo.w_off[l - 1]; q.b_off = lo.b_off[l - 1]; q.ldw = lo.ld[l];
     if (l > 1) { q.dx = ctx->at<uint16_t>(cv.delta[l - 1]); q.dx_gs = (long)B * lo.ld[l - 1]; q.lddx = lo.ld[l - 1]; }
     q.B = B; q.K = lo.d[l - 1]; q.Nn = lo.d[l];
-    q.n_groups = N; q.act = c.activation; q.streaming = ctx->streaming ? 1 : 0;
+    q.n_groups = N; q.act = c.activation; q.streaming = ctx->streamed.steps ? 1 : 0;
     q.lr = ctx->lr;
     q.vel = ctx->velocity(); q.mu = c.momentum;
     q.worker_steps = worker_steps; q.step = step;
@@ -767,7 +783,7 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
   ctx->lo = lo;
   build_carve(cfg, lo, &ctx->cv);
   ctx->bf16 = cfg->model == PRSGD_MLP && cfg->gemm_dtype == PRSGD_BF16;
-  ctx->streaming = (size_t)cfg->n_workers * (size_t)lo.m_pad * sizeof(float) >= kStreamingBytes;
+  ctx->streamed = streamed_uses(*cfg, lo);
   ctx->stream = reinterpret_cast<hipStream_t>(hip_stream);
   ctx->use_fused2 = ctx->cv.part != 0 && ctx->cv.sync != 0 &&
                     fused2_plan(cfg->n_workers, lo.d[0], lo.d[1], lo.d[2], cfg->batch,
@@ -976,7 +992,7 @@ int prsgd_average(prsgd_ctx* ctx) {
     // or start every epoch without momentum
     if (ctx->cfg.momentum_restart == PRSGD_MOM_AVERAGE)
       LAUNCH(ctx, KK_AVERAGE, launch_average(ctx->velocity(), nullptr, ctx->lo.m_pad, ctx->cfg.n_workers,
-                                             ctx->streaming, ctx->stream));
+                                             ctx->streamed.steps, ctx->stream));
     else
       LAUNCH(ctx, KK_UPDATE, launch_fill_zero(ctx->velocity(), (size_t)ctx->cfg.n_workers * ctx->lo.m_pad,
                                               ctx->stream));
@@ -986,12 +1002,12 @@ int prsgd_average(prsgd_ctx* ctx) {
     // every worker's starting point and writes the replicas  x_i = ybar - gamma G_i  itself
     LAUNCH(ctx, KK_RESTART_MEAN,
            launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), ctx->lo.m_pad, ctx->cfg.n_workers,
-                       ctx->streaming, ctx->stream));
+                       ctx->streamed.steps, ctx->stream));
     ctx->at_mean = true;
     return PRSGD_OK;
   }
   LAUNCH(ctx, KK_AVERAGE,
-         launch_average(ctx->params, ctx->shadow(), ctx->lo.m_pad, ctx->cfg.n_workers, ctx->streaming,
+         launch_average(ctx->params, ctx->shadow(), ctx->lo.m_pad, ctx->cfg.n_workers, ctx->streamed.steps,
                         ctx->stream));
   ctx->shadow1_stale = false;               // the averaging kernel rewrites every shadow
   return PRSGD_OK;
@@ -1212,6 +1228,14 @@ int prsgd_product_tile(int32_t rows, int32_t cols, int32_t n_workers, int32_t ge
   out[1] = tile_cols;
   out[2] = (int32_t)lds;
   return PRSGD_OK;
+}
+
+int prsgd_streamed_uses(const prsgd_config* cfg) {
+  Layout lo;
+  char err[128];
+  if (!build_layout(cfg, &lo, err, sizeof(err))) return set_err(nullptr, PRSGD_EINVAL, "%s", err);
+  const Streamed u = streamed_uses(*cfg, lo);
+  return (u.steps ? PRSGD_STREAM_STEPS : 0) | (u.step_mean ? PRSGD_STREAM_STEP_MEAN : 0);
 }
 
 int prsgd_status(prsgd_ctx* ctx) {

@@ -25,6 +25,7 @@ PRSGD_TANH, PRSGD_RELU = 0, 1
 PRSGD_F32, PRSGD_BF16 = 0, 1
 PRSGD_MOM_KEEP, PRSGD_MOM_AVERAGE, PRSGD_MOM_RESET = 0, 1, 2
 PRSGD_MAX_DIMS = 16
+PRSGD_STREAM_STEPS, PRSGD_STREAM_STEP_MEAN = 1, 2
 
 
 class PrsgdError(RuntimeError):
@@ -83,6 +84,7 @@ def _load() -> ctypes.CDLL:
         "prsgd_sgd_update": (ctypes.c_int, [vp, vp, vp, sz, ctypes.c_float, vp]),
         "prsgd_copy_bytes": (ctypes.c_int, [vp, vp, sz, vp]),
         "prsgd_product_tile": (ctypes.c_int, [i32, i32, i32, i32, vp]),
+        "prsgd_streamed_uses": (ctypes.c_int, [cfgp]),
         "prsgd_time_varying_schedule": (ctypes.c_int, [i32, i32, vp, vp]),
         "prsgd_status": (ctypes.c_int, [vp]),
         "prsgd_set_epoch_wait_limit": (ctypes.c_int, [vp, ctypes.c_uint32]),
@@ -341,6 +343,13 @@ def prsgd_product_tile(rows: int, cols: int, n_workers: int, gemm_dtype: str):
     out = (ctypes.c_int32 * 3)()
     _check(_lib.prsgd_product_tile(rows, cols, n_workers, {"f32": PRSGD_F32, "bf16": PRSGD_BF16}[gemm_dtype], out))
     return tuple(out)
+
+
+def prsgd_streamed_uses(cfg: prsgd_config) -> int:
+    rc = _lib.prsgd_streamed_uses(ctypes.byref(cfg))
+    if rc < 0:
+        _check(rc)
+    return rc
 
 
 def prsgd_set_lr(h: Handle, lr: float) -> None:

@@ -83,6 +83,20 @@ def test_invalid_configurations_are_rejected_without_touching_the_gpu(P, kw):
     assert P.prsgd_last_error(None) != ""
 
 
+@pytest.mark.parametrize("dims,n_workers,steps,step_mean", [
+    ((3072, 1024, 1024, 10), 11, False, False),              # 177 MiB of replicas
+    ((3072, 1024, 1024, 10), 16, True, False),               # 257 MiB, the average 16
+    ((4096, 4096, 4096, 10), 8, True, False),                # 1026 MiB, the average 128
+    ((4096, 4096, 4096, 4096, 1000), 1, True, True),         # 208 MiB
+    ((4096, 4096, 4096, 4096, 1000), 8, True, True),
+])
+def test_streamed_launches_go_by_what_they_rewrite(P, dims, n_workers, steps, step_mean):
+    # past the last-level cache: the replica set for local steps, the average for a step on the average
+    uses = P.prsgd_streamed_uses(P.make_config(n_workers, "mlp", dims, 64, 1024, 0.1, 1, "relu", "bf16"))
+    assert bool(uses & P.PRSGD_STREAM_STEPS) == steps
+    assert bool(uses & P.PRSGD_STREAM_STEP_MEAN) == step_mean
+
+
 def test_null_context_calls_return_einval(P):
     assert P._lib.prsgd_local_steps(None, 1) == P.PRSGD_EINVAL
     assert P._lib.prsgd_average(None) == P.PRSGD_EINVAL
