@@ -34,7 +34,7 @@ int prsgd_product_tile(int32_t rows, int32_t cols, int32_t n_workers, int32_t ge
  * Which launches of a configuration mark their weight traffic non-temporal: a sum of the constants
  * below.  Host only, for tests.  PRSGD_EINVAL on an invalid configuration.
  */
-enum { PRSGD_STREAM_STEPS = 1, PRSGD_STREAM_STEP_MEAN = 2 };
+enum { PRSGD_STREAM_STEPS = 1, PRSGD_STREAM_STEP_MEAN = 2, PRSGD_STREAM_MEAN = 4, PRSGD_STREAM_AVERAGE = 8 };
 int prsgd_streamed_uses(const prsgd_config* cfg);
 
 /*

@@ -338,7 +338,7 @@ static void launch_mean_u(const f32x4_t* p4, f32x4_t* o4, u32x2_t* s2, size_t st
 hipError_t launch_average(float* params, uint16_t* shadow, long m_pad, int n_workers, bool streaming,
                           hipStream_t s) {
   const size_t stride4 = (size_t)m_pad / 4;
-  // the non-temporal variants are for replica sets far beyond the 256 MB last-level cache
+  // non-temporal variants: for replica sets past the 256 MB last-level cache (the caller's rule)
   f32x4_t* p4 = reinterpret_cast<f32x4_t*>(params);
   u32x2_t* s2 = reinterpret_cast<u32x2_t*>(shadow);
   if (restart_is_small(stride4, n_workers)) {

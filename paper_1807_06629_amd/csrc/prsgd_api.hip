@@ -114,12 +114,22 @@ struct Streamed {
   bool step_mean;     // a step on the node average: the average is all it rewrites, and the next iteration reads
                       // it again (16 x (3072-1024-1024-10) at interval 1, an average of 17 MB: 78 us per iteration, 84
                       // streamed; 2 x (4096-4096-4096-4096-1000), 218 MB: 302 us, 295 streamed)
+  bool mean;          // the average written apart: with up to four workers it writes 6 bytes for the next iteration
+                      // to every 16 or fewer that it reads, and streamed reads lose (2 x (4096-4096-4096-10), 257 MiB at
+                      // interval 2: 239 us per iteration, 251 streamed; 8 x (2048-2048-2048-10), as large: 167 us, 156
+                      // streamed)
+  bool average;       // the average written to every replica, which the next iteration reads: pays from well past
+                      // the cache on (fp32 at interval 4, 28 x (1024-1024-1024-10), 226 MiB: 191 us, 194 streamed; 2 x
+                      // (4096-4096-4096-10), 257 MiB: 262 and 277 us; 12 x (2048-2048-2048-10), 386 MiB: 341 and 332 us)
 };
+constexpr size_t kStreamingMeanFewBytes = (size_t)1 << 30, kStreamingAverageBytes = (size_t)384 << 20;
 Streamed streamed_uses(const prsgd_config& c, const Layout& lo) {
   const size_t average = (size_t)lo.m_pad * sizeof(float), set = average * (size_t)c.n_workers;
   Streamed u;
   u.steps = set >= kStreamingBytes;
   u.step_mean = average >= kStreamingBytes;
+  u.mean = set >= (c.n_workers > 4 ? kStreamingBytes : kStreamingMeanFewBytes);
+  u.average = set >= kStreamingAverageBytes;
   return u;
 }
 
@@ -490,7 +500,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     // then moved by the averaged gradient; the points themselves are not rewritten.
     if (!from_mean)
       LAUNCH(ctx, KK_RESTART_MEAN,
-             launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), lo.m_pad, N, ctx->streamed.steps, s));
+             launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), lo.m_pad, N, ctx->streamed.mean, s));
     // eq. (3) and eq. (2) in one pass over ybar, layer by layer from the top: D_{l-1} needs the
     // weights the forward pass used (the bf16 image of ybar, or of every worker's own point), and
     // when that is ybar it runs before layer l's pass changes it
@@ -992,7 +1002,7 @@ int prsgd_average(prsgd_ctx* ctx) {
     // or start every epoch without momentum
     if (ctx->cfg.momentum_restart == PRSGD_MOM_AVERAGE)
       LAUNCH(ctx, KK_AVERAGE, launch_average(ctx->velocity(), nullptr, ctx->lo.m_pad, ctx->cfg.n_workers,
-                                             ctx->streamed.steps, ctx->stream));
+                                             ctx->streamed.average, ctx->stream));
     else
       LAUNCH(ctx, KK_UPDATE, launch_fill_zero(ctx->velocity(), (size_t)ctx->cfg.n_workers * ctx->lo.m_pad,
                                               ctx->stream));
@@ -1002,12 +1012,12 @@ int prsgd_average(prsgd_ctx* ctx) {
     // every worker's starting point and writes the replicas  x_i = ybar - gamma G_i  itself
     LAUNCH(ctx, KK_RESTART_MEAN,
            launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), ctx->lo.m_pad, ctx->cfg.n_workers,
-                       ctx->streamed.steps, ctx->stream));
+                       ctx->streamed.mean, ctx->stream));
     ctx->at_mean = true;
     return PRSGD_OK;
   }
   LAUNCH(ctx, KK_AVERAGE,
-         launch_average(ctx->params, ctx->shadow(), ctx->lo.m_pad, ctx->cfg.n_workers, ctx->streamed.steps,
+         launch_average(ctx->params, ctx->shadow(), ctx->lo.m_pad, ctx->cfg.n_workers, ctx->streamed.average,
                         ctx->stream));
   ctx->shadow1_stale = false;               // the averaging kernel rewrites every shadow
   return PRSGD_OK;
@@ -1235,7 +1245,8 @@ int prsgd_streamed_uses(const prsgd_config* cfg) {
   char err[128];
   if (!build_layout(cfg, &lo, err, sizeof(err))) return set_err(nullptr, PRSGD_EINVAL, "%s", err);
   const Streamed u = streamed_uses(*cfg, lo);
-  return (u.steps ? PRSGD_STREAM_STEPS : 0) | (u.step_mean ? PRSGD_STREAM_STEP_MEAN : 0);
+  return (u.steps ? PRSGD_STREAM_STEPS : 0) | (u.step_mean ? PRSGD_STREAM_STEP_MEAN : 0) |
+         (u.mean ? PRSGD_STREAM_MEAN : 0) | (u.average ? PRSGD_STREAM_AVERAGE : 0);
 }
 
 int prsgd_status(prsgd_ctx* ctx) {

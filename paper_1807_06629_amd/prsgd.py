@@ -25,7 +25,7 @@ PRSGD_TANH, PRSGD_RELU = 0, 1
 PRSGD_F32, PRSGD_BF16 = 0, 1
 PRSGD_MOM_KEEP, PRSGD_MOM_AVERAGE, PRSGD_MOM_RESET = 0, 1, 2
 PRSGD_MAX_DIMS = 16
-PRSGD_STREAM_STEPS, PRSGD_STREAM_STEP_MEAN = 1, 2
+PRSGD_STREAM_STEPS, PRSGD_STREAM_STEP_MEAN, PRSGD_STREAM_MEAN, PRSGD_STREAM_AVERAGE = 1, 2, 4, 8
 
 
 class PrsgdError(RuntimeError):

@@ -97,6 +97,20 @@ def test_streamed_launches_go_by_what_they_rewrite(P, dims, n_workers, steps, st
     assert bool(uses & P.PRSGD_STREAM_STEP_MEAN) == step_mean
 
 
+@pytest.mark.parametrize("dims,n_workers,mean,average", [
+    ((3072, 1024, 1024, 10), 11, False, False),              # 177 MiB
+    ((3072, 1024, 1024, 10), 16, True, False),               # 257 MiB
+    ((4096, 4096, 4096, 10), 2, False, False),               # 257 MiB in two replicas
+    ((2048, 2048, 2048, 10), 12, True, True),                # 386 MiB
+    ((4096, 4096, 4096, 4096, 1000), 4, False, True),        # 832 MiB in four
+    ((4096, 4096, 4096, 4096, 1000), 5, True, True),
+])
+def test_streamed_averages_go_by_what_is_read_again(P, dims, n_workers, mean, average):
+    uses = P.prsgd_streamed_uses(P.make_config(n_workers, "mlp", dims, 64, 1024, 0.1, 1, "relu", "bf16"))
+    assert bool(uses & P.PRSGD_STREAM_MEAN) == mean
+    assert bool(uses & P.PRSGD_STREAM_AVERAGE) == average
+
+
 def test_null_context_calls_return_einval(P):
     assert P._lib.prsgd_local_steps(None, 1) == P.PRSGD_EINVAL
     assert P._lib.prsgd_average(None) == P.PRSGD_EINVAL
