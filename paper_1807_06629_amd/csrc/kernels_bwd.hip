@@ -657,6 +657,11 @@ bool bwd_products_apart(const BwdArgs& p) {
   if ((p.Nn % BN) != 0 && (p.ldw % BN) == 0 && p.ldw - p.Nn < BN) return false;      // walked padded
   return (long)((p.K + BMK - 1) / BMK) * p.n_groups < 256;
 }
+// A layer of one column tile has nothing to spread; its weight gradient is only cheaper apart if it rides in the
+// launch of another layer's.  With 784-100-100-10, eight workers, 128 rows: 35.8 us per iteration, 38.6 with the
+// last layer as one kernel.  Such layers alone: 256-128-10, eight workers, 32 rows 22.1 us apart, 18.3 us as one kernel;
+// two of them, 391-34-44-10, eleven workers, 128 rows 36 and 40 us, but 500-60-10, eight workers, 32 rows 22.1 and 21.2 us.
+bool bwd_apart_pays(int n_layers, int widest, int batch) { return widest > BN || (n_layers >= 2 && batch > 64); }
 
 hipError_t launch_bwd_fused(const BwdArgs& p, hipStream_t s) {
   if (p.K <= 0 || p.Nn <= 0 || p.n_groups <= 0) return hipSuccess;

@@ -527,8 +527,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
 
   // backward.  bf16 operands with the fused update: one kernel per layer does the weight
   // gradient, eq. (3) and the delta of the layer below in a single pass over W_l.
-  bool first_shadow_left = false;
-  for (int l = L; fused_bwd && l >= 1; --l) {
+  auto bwd_args = [&](int l) {
     BwdArgs q;
     memset(&q, 0, sizeof(q));
     q.h = reinterpret_cast<const uint16_t*>(act_in(l - 1)); q.h_gs = (long)B * lo.ld[l - 1]; q.ldh = lo.ld[l - 1];
@@ -542,6 +541,18 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     q.lr = ctx->lr;
     q.vel = ctx->velocity(); q.mu = c.momentum;
     q.worker_steps = worker_steps; q.step = step;
+    return q;
+  };
+  int n_apart = 0, widest_apart = 0;
+  for (int l = L; fused_bwd && l >= 1; --l) {
+    if (!bwd_products_apart(bwd_args(l))) continue;
+    ++n_apart;
+    if (lo.d[l] > widest_apart) widest_apart = lo.d[l];
+  }
+  const bool take_apart = bwd_apart_pays(n_apart, widest_apart, B);
+  bool first_shadow_left = false;
+  for (int l = L; fused_bwd && l >= 1; --l) {
+    BwdArgs q = bwd_args(l);
     if (l == 1 && L >= 2 && ctx->first_fusion && prefetch && ctx->batch_t[bk ^ 1] == t + 1) {
       q.x_next = reinterpret_cast<const uint16_t*>(ctx->xb(bk ^ 1)); q.x_gs = (long)B * lo.ld[0]; q.ldx = lo.ld[0];
       q.h_next = ctx->at<uint16_t>(cv.h[1]); q.hn_gs = (long)B * lo.ld[1]; q.ldhn = lo.ld[1];
@@ -556,7 +567,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
         continue;
       }
     }
-    if (bwd_products_apart(q)) {
+    if (take_apart && bwd_products_apart(q)) {
       if (l > 1) LAUNCH(ctx, KK_BWD, launch_gemm_dx(dx_args(l), N, true, s));
       GemmArgs p = dw_args(l);
       p.epi = EPI_DW_FUSED;

@@ -95,8 +95,10 @@ struct BwdArgs {
   uint16_t* h_next; long hn_gs; int ldhn;
 };
 bool bwd_fused_supported(int batch);
-// The kernel's walk over the columns leaves most of the chip idle: the layer's products apart are faster.
+// The kernel's walk over the columns leaves most of the chip idle: the layer's products apart are faster
+// if, over the layers this holds for, their number and the widest of them say so.
 bool bwd_products_apart(const BwdArgs& p);
+bool bwd_apart_pays(int n_layers, int widest, int batch);
 hipError_t launch_bwd_fused(const BwdArgs& p, hipStream_t s);
 // Layer 1: backward step fused with the next iteration's forward product of that layer.
 bool bwd_first_fwd_shape(int batch, int d_in, int d_out);

@@ -435,6 +435,24 @@ def test_algorithm3_steps_that_every_worker_takes(P, D, dims, batch, steps):
     P.prsgd_destroy(h)
 
 
+@pytest.mark.parametrize("dims,batch,launches", [
+    ((200, 10), 33, 1), ((500, 60, 10), 33, 2), ((200, 10), 100, 1),   # one kernel per layer
+    ((40, 30, 20, 10), 100, 3),                                        # apart: two backward-data and a shared launch
+    ((300, 200, 10), 33, 2),                                           # apart: one backward-data and a shared launch
+])
+def test_layers_of_one_column_tile_share_a_backward_launch_or_keep_their_kernel(P, D, dims, batch, launches):
+    w = small_mlp(dims=dims, batch=batch, n_workers=3, gemm_dtype="bf16", activation="tanh", rows_per_worker=256)
+    inp = inputs_for(w)
+    h = _open(D, w, inp)
+    P.prsgd_profile_enable(h, True)
+    P.prsgd_local_steps(h, 2)
+    counts = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
+    assert counts["gemm_bwd"] == 2 * launches and not counts.get("gemm_dw")
+    want = oracle_run(w, inp, iterations=2, interval=100)
+    assert rel_err(D.read_all(h), want["x"]) <= 5e-3
+    P.prsgd_destroy(h)
+
+
 @pytest.mark.parametrize("steps", [[2, 3, 4], [3, 4, 3], [4, 4, 4]])
 def test_algorithm3_epochs_refresh_no_shadow(P, D, steps):
     """The last step that every worker takes writes the whole bf16 shadow of W_1 again, which the steps
