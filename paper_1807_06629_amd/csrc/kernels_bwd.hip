@@ -573,8 +573,18 @@ static bool bwd_full_applies(const BwdArgs& p, int mb, int S, int kb = BMK) {
   return (p.ldw % 4) == 0 && (p.ldh % 8) == 0 && (p.ldd % 8) == 0 && (p.w_off % 4) == 0;
 }
 
-// Fewer than two workgroups of 64-row bands per compute unit on the current device.
-static bool few_bands(const BwdArgs& p) {
+// A layer whose rows are padded to whole column tiles (ld a multiple of 64, less than one tile of
+// padding) is walked over its padded width: the padding columns of W_l, D_l and b_l are zero,
+// their gradient is zero, and the update leaves them zero.
+static bool bwd_padded_applies(const BwdArgs& p, int mb, BwdArgs* padded) {
+  if ((p.Nn % BN) == 0 || (p.ldw % BN) != 0 || p.ldw - p.Nn >= BN || p.ldd != p.ldw) return false;
+  *padded = p;
+  padded->Nn = p.ldw;
+  return bwd_full_applies(*padded, mb, 2);
+}
+
+// Fewer 64-row bands than `eighths` / 8 for every compute unit of the current device.
+static bool fewer_bands(const BwdArgs& p, long eighths) {
   static std::atomic<int> cus{0};
   int n = cus.load(std::memory_order_relaxed);
   if (n == 0) {
@@ -584,7 +594,7 @@ static bool few_bands(const BwdArgs& p) {
       return false;
     cus.store(n, std::memory_order_relaxed);
   }
-  return (long)((p.K + BMK - 1) / BMK) * p.n_groups < 2L * n;
+  return (long)((p.K + BMK - 1) / BMK) * p.n_groups * 8 < eighths * n;
 }
 
 template <int MB, bool DX, bool MOM, int S, int KB>
@@ -648,14 +658,19 @@ bool bwd_fused_supported(int batch) { return batch >= 1 && batch <= 128; }
 // 7 us start, while the products of the layer spread over all compute units.  1000-500-300-37, six
 // workers, 100 rows: the three layers' launches 21 + 20 + 10 us, the two backward-data products 5 + 7 us and the
 // weight-gradient products in one launch 14 us.  With a band per compute unit the pass over
-// the weights is the shorter one (16 x (1024 x 10), 64 rows: 9 us against 5 + 6).
+// the weights is the shorter one (16 x (1024 x 10), 64 rows: 9 us against 5 + 6).  Wide layers whose rows
+// are padded to whole column tiles are walked faster (16-byte accesses throughout): with up to 64 rows they are from 7
+// bands per 8 compute units on (500-600-600-10, per iteration, apart and not: 20 workers, 160 and 200 bands, 8 rows 52.9
+// and 59.4 us; 24 workers, 192 and 240 bands, 64.8 and 61.5 us; with 128 rows 84.4 and 86.6 us).
 bool bwd_products_apart(const BwdArgs& p) {
   if (p.vel != nullptr) return false;
   if (p.dx == nullptr && bwd_first_fwd_shape(p.B, p.K, p.Nn)) return false;   // same bits as that kernel
   const int mb = p.B <= 32 ? 1 : p.B <= 64 ? 2 : 4;
   if (bwd_full_applies(p, mb, 2) || bwd_full_applies(p, mb, 2, 32)) return false;
-  if ((p.Nn % BN) != 0 && (p.ldw % BN) == 0 && p.ldw - p.Nn < BN) return false;      // walked padded
-  return (long)((p.K + BMK - 1) / BMK) * p.n_groups < 256;
+  BwdArgs padded;
+  if (bwd_padded_applies(p, mb, &padded)) return false;
+  const bool padded_rows = (p.Nn % BN) != 0 && (p.ldw % BN) == 0;
+  return fewer_bands(p, padded_rows && p.B <= 64 ? 7 : 8);
 }
 // A layer of one column tile has nothing to spread; its weight gradient is only cheaper apart if it rides in the
 // launch of another layer's.  With 784-100-100-10, eight workers, 128 rows: 35.8 us per iteration, 38.6 with the
@@ -685,18 +700,12 @@ hipError_t launch_bwd_fused(const BwdArgs& p, hipStream_t s) {
   // 283 us inside the real step: not kept.
   // A layer whose 64-row bands leave compute units without a second workgroup to overlap with is
   // walked in 32-row bands instead (twice the workgroups, each with half the rows of a tile).
-  if (few_bands(p) && bwd_full_applies(p, mb, 2, 32)) PRSGD_BWD_PICK(launch_bwd_full2_half);
+  if (fewer_bands(p, 16) && bwd_full_applies(p, mb, 2, 32)) PRSGD_BWD_PICK(launch_bwd_full2_half);
   if (bwd_full_applies(p, mb, 2)) PRSGD_BWD_PICK(launch_bwd_full2);
-  // A layer whose rows are padded to whole column tiles (ld a multiple of 64, less than one tile of
-  // padding) is walked over its padded width: the padding columns of W_l, D_l and b_l are zero,
-  // their gradient is zero, and the update leaves them zero.
-  if ((p.Nn % BN) != 0 && (p.ldw % BN) == 0 && p.ldw - p.Nn < BN && p.ldd == p.ldw) {
-    BwdArgs padded = p;
-    padded.Nn = p.ldw;
-    if (bwd_full_applies(padded, mb, 2)) {
-      const BwdArgs& p = padded;
-      PRSGD_BWD_PICK(launch_bwd_full2);
-    }
+  BwdArgs padded;
+  if (bwd_padded_applies(p, mb, &padded)) {
+    const BwdArgs& p = padded;
+    PRSGD_BWD_PICK(launch_bwd_full2);
   }
   PRSGD_BWD_PICK(launch_bwd_one);
 #undef PRSGD_BWD_PICK

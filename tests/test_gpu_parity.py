@@ -439,8 +439,10 @@ def test_algorithm3_steps_that_every_worker_takes(P, D, dims, batch, steps):
     ((200, 10), 33, 1), ((500, 60, 10), 33, 2), ((200, 10), 100, 1),   # one kernel per layer
     ((40, 30, 20, 10), 100, 3),                                        # apart: two backward-data and a shared launch
     ((300, 200, 10), 33, 2),                                           # apart: one backward-data and a shared launch
+    ((64, 512, 1000), 64, 2),                                          # both walked, the second over its padded width
+    ((256, 600, 1000), 64, 3),                                         # the second apart: 600 rows are no whole bands
 ])
-def test_layers_of_one_column_tile_share_a_backward_launch_or_keep_their_kernel(P, D, dims, batch, launches):
+def test_backward_launches_of_ragged_layers(P, D, dims, batch, launches):
     w = small_mlp(dims=dims, batch=batch, n_workers=3, gemm_dtype="bf16", activation="tanh", rows_per_worker=256)
     inp = inputs_for(w)
     h = _open(D, w, inp)
