@@ -712,6 +712,14 @@ hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hi
   int depth = 0;
   for (int i = 0; i < n; ++i) depth = depth > ps[i].Kc ? depth : ps[i].Kc;
   const bool shallow = depth <= 2 * kTileBytes / (bf16 ? 2 : 4);
+  // one product: a kernel that has its arguments at fixed places is 0.5 us faster (7.0 and 7.5 us for 165 x 10, 32 rows)
+  if (n == 1) {
+    if (bf16)
+      return shallow ? launch_one<TBF16, 64, 64, 2, 2, 1, 2, OP_TRANS, OP_TRANS>(ps[0], n_groups, s)
+                     : launch_one<TBF16, 64, 64, 2, 2, 1, 4, OP_TRANS, OP_TRANS>(ps[0], n_groups, s);
+    return shallow ? launch_one<TF32, 64, 64, 2, 2, 1, 2, OP_TRANS, OP_TRANS>(ps[0], n_groups, s)
+                   : launch_one<TF32, 64, 64, 2, 2, 1, 4, OP_TRANS, OP_TRANS>(ps[0], n_groups, s);
+  }
   if (bf16) return shallow ? launch_dw_set<TBF16, 2>(ps, n, n_groups, s) : launch_dw_set<TBF16, 4>(ps, n, n_groups, s);
   return shallow ? launch_dw_set<TF32, 2>(ps, n, n_groups, s) : launch_dw_set<TF32, 4>(ps, n, n_groups, s);
 }
