@@ -193,8 +193,7 @@ template <int PER> __device__ __forceinline__ void wait_tiles(int ahead) {
     case 0: PRSGD_WAIT(0); break;
     case 1: PRSGD_WAIT(1); break;
     case 2: PRSGD_WAIT(2); break;
-    case 3: PRSGD_WAIT(3); break;
-    default: PRSGD_WAIT(4); break;
+    default: PRSGD_WAIT(3); break;
   }
 #undef PRSGD_WAIT
 }
@@ -217,7 +216,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   constexpr int PER = IOA::NPT + IOB::NPT;
   static_assert(TM >= 1 && TN >= 1, "tile too small for the wavefront grid");
   static_assert(kSlices % WK == 0, "the slices of a tile must split evenly over the shares");
-  static_assert(S >= 2 && S <= 5 && PER * (S - 1) <= 63, "wait_tiles");
+  static_assert(S >= 2 && S <= 4 && PER * (S - 1) <= 63, "wait_tiles");
 
   // Workgroup -> (group, tile).  The hardware deals consecutive workgroups round-robin to the 8
   // XCDs; each XCD gets a contiguous range of the tiles, so that a group's activations and weight
@@ -610,7 +609,8 @@ static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
 // compute units ran in rounds.  With eight and with three tiles: 64 x (8 x 1024) x 1024 in 32 x 64 tiles 36.1
 // and 15.8 us, 128 x (8 x 64) x 1024 25.3 and 10.6 us, alone on its compute unit 4 x (8 x 4096) x 1024 26.6 and
 // 20.6 us; 64 x (64 x 1024) x 256 in 64 x 64 tiles 24.2 and 13.9 us.  Two lose where a compute unit has one
-// workgroup (32.1 us for the third of these products).
+// workgroup (32.1 us for the third of these products).  128 x 128 tiles, five, four and three in flight: 8 x (128 x 4096)
+// x 4096 with shared weights 54.1, 48.7 and 47.0 us, 64 x (128 x 1024) x 1024 38.7, 35.5 and 33.8 us.
 constexpr int kRowStages = 3;
 
 template <int AKIND, int BKIND>
@@ -619,9 +619,8 @@ static hipError_t launch_rows_bf16(const GemmArgs& p, int n_groups, hipStream_t 
   if (t.bm == 32) return launch_one<TBF16, 32, 64, 1, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
   if (t.bm == 64) return launch_one<TBF16, 64, 64, 2, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
   if (t.bn == 64) return launch_one<TBF16, 128, 64, 4, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
-  // eight wavefronts: two per SIMD cover the LDS latency of each other; five tiles in flight take all of
-  // the LDS (4096 x 4096 layers at interval 1: 9.04 ms per 16 iterations with four, 8.87 with five)
-  return launch_one<TBF16, 128, 128, 2, 4, 1, 5, AKIND, BKIND>(p, n_groups, s);
+  // eight wavefronts: two per SIMD cover the LDS latency of each other
+  return launch_one<TBF16, 128, 128, 2, 4, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
 }
 template <int AKIND, int BKIND>
 static hipError_t launch_rows_f32(const GemmArgs& p, int n_groups, hipStream_t s) {
@@ -640,7 +639,7 @@ void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows
   *lds_bytes = !bf16 ? (t.bm == 64 ? gemm_lds_bytes<TF32, 64, 64, 1, 4>() : gemm_lds_bytes<TF32, 32, 32, 4, kRowStages>())
                : t.bm == 32 ? gemm_lds_bytes<TBF16, 32, 64, 1, kRowStages>()
                : t.bm == 64 ? gemm_lds_bytes<TBF16, 64, 64, 1, kRowStages>()
-               : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, 5>();
+               : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, kRowStages>();
 }
 
 // A logits product that leaves most compute units idle (few classes) cuts its contraction into
