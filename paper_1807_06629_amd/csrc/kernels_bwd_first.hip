@@ -97,11 +97,10 @@ constexpr size_t first_lds_bytes(int mb, int nb) {
 }
 
 // MB: 32-row tiles of the minibatch (B = 32 MB).  NB: band width, 64 or 128.  NT: non-temporal weight
-// traffic.  SHW: also write the bf16 shadow of W_1 (only the stand-alone forward product reads it;
-// the caller may leave it stale while this kernel supplies H_1, and refresh it when that chain
-// breaks).  MOM: momentum form of the local update, v <- mu v + G, x <- x - gamma v, with the velocity
-// tile streamed beside the weights.
-template <int MB, int NB, bool NT, bool SHW, bool MOM>
+// traffic.  MOM: momentum form of the local update, v <- mu v + G, x <- x - gamma v, with the velocity
+// tile streamed beside the weights.  The bf16 shadow of W_1 is left as it is: only the stand-alone forward
+// product reads it, and the caller refreshes it when the chain of activations from here breaks.
+template <int MB, int NB, bool NT, bool MOM>
 __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdArgs p) {
   constexpr int BR = 32 * MB;
   constexpr int NW = NB / 16, NTHR = 64 * NW;         // wavefronts: 2 (rows) x NB / 32 (columns)
@@ -146,7 +145,6 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
   const int trow = lane >> 3, tcol = 4 * (lane & 7);
   const size_t w_first = (size_t)p.w_off + (size_t)(wk * 32 + trow) * p.ldw + n0 + wn * 32 + tcol;
   float* const w_g = p.params + (size_t)g * p.p_gs + w_first;
-  uint16_t* const s_g = SHW ? p.shadow + (size_t)g * p.p_gs + w_first : nullptr;
   const float* const wsrc_g = p.src + (size_t)g * p.src_gs + w_first;
   float* const v_g = MOM ? p.vel + (size_t)g * p.p_gs + w_first : nullptr;
   const size_t row8 = (size_t)8 * p.ldw;
@@ -292,17 +290,15 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
                            f32x2_to_bf16x2_rne(w.z, w.w)};
       if (NT) {
         __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(w_g + off));
-        if (SHW) __builtin_nontemporal_store(hv2, reinterpret_cast<u32x2_t*>(s_g + off));
       } else {
         *reinterpret_cast<f32x4_t*>(w_g + off) = w;
-        if (SHW) *reinterpret_cast<u32x2_t*>(s_g + off) = hv2;
       }
       const int k = wk * 32 + 8 * q + trow;
       *reinterpret_cast<u32x2_t*>(Wl + hbuf * WT + k * (NB * 2) + ((wn ^ seg_xor<NB * 2>(k)) << 6) + 2 * tcol) = hv2;
     }
     // The next X tile has landed (younger than its requests: this phase's weight loads and stores), the
     // new weights are in LDS, and nobody reads this phase's tiles any more.
-    constexpr int YOUNGER = (MOM ? 16 : 8) + (SHW ? 4 : 0);
+    constexpr int YOUNGER = MOM ? 16 : 8;
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(YOUNGER) : "memory");
     hbuf ^= 1;
     xbuf = xnext;
@@ -341,11 +337,11 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
   }
 }
 
-template <int MB, int NB, bool NT, bool SHW, bool MOM>
+template <int MB, int NB, bool NT, bool MOM>
 hipError_t launch_first_one(const BwdArgs& p, hipStream_t s) {
   constexpr size_t kLds = first_lds_bytes(MB, NB);
   static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
-  auto kernel = bwd_first_fwd_kernel<MB, NB, NT, SHW, MOM>;
+  auto kernel = bwd_first_fwd_kernel<MB, NB, NT, MOM>;
   static std::atomic<bool> configured{false};
   if (!configured.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -359,12 +355,10 @@ hipError_t launch_first_one(const BwdArgs& p, hipStream_t s) {
 
 template <int MB, int NB, bool NT>
 hipError_t launch_first_nt(const BwdArgs& p, hipStream_t s) {
-  const bool shw = p.shadow != nullptr;
   if constexpr (NB == 64) {
-    if (p.vel != nullptr)
-      return shw ? launch_first_one<MB, NB, NT, true, true>(p, s) : launch_first_one<MB, NB, NT, false, true>(p, s);
+    if (p.vel != nullptr) return launch_first_one<MB, NB, NT, true>(p, s);
   }
-  return shw ? launch_first_one<MB, NB, NT, true, false>(p, s) : launch_first_one<MB, NB, NT, false, false>(p, s);
+  return launch_first_one<MB, NB, NT, false>(p, s);
 }
 
 // 128-column bands where they still give every compute unit a workgroup; not with momentum, whose second
@@ -387,7 +381,7 @@ bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
 bool bwd_first_fwd_applies(const BwdArgs& p) {
   if (!bwd_first_fwd_shape(p.B, p.K, p.Nn)) return false;
   if (p.worker_steps != nullptr || p.dx != nullptr) return false;
-  if (p.x_next == nullptr || p.h_next == nullptr) return false;   // shadow == nullptr: it is left stale
+  if (p.x_next == nullptr || p.h_next == nullptr) return false;
   return (p.ldw % 4) == 0 && (p.ldh % 8) == 0 && (p.ldx % 8) == 0 && (p.ldd % 8) == 0 && (p.w_off % 4) == 0;
 }
 

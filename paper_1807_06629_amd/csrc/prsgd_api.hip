@@ -559,9 +559,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
       if (bwd_first_fwd_applies(q)) {
         const int rc = dw.flush();          // H_1 is rewritten: layer 2's weight gradient still reads it
         if (rc != PRSGD_OK) return rc;
-        q.shadow = nullptr;                 // replica shadows of W_1 have no reader while H_1 comes from here
         LAUNCH(ctx, KK_BWD_FIRST, launch_bwd_first_fwd(q, s));
-        ctx->shadow1_stale = first_shadow_left = true;
+        ctx->shadow1_stale = first_shadow_left = true;   // not written: it has no reader while H_1 comes from here
         ctx->h1_t = t + 1;
         ctx->h1_batch = bk ^ 1;
         continue;
