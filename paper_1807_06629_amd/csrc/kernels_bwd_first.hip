@@ -53,41 +53,6 @@ __device__ __forceinline__ float act_from_z(float z, int act) {
   return act == PRSGD_TANH ? tanhf(z) : fmaxf(z, 0.0f);
 }
 
-// LDS tiles are unpadded (requests land at consecutive addresses) and permuted instead, as in the
-// grouped products: a tile whose row is the contraction index has its 64-byte segments exchanged so
-// that the four rows of a transpose read fall on different banks ...
-template <int ROW_BYTES> __device__ __forceinline__ int seg_xor(int c) {
-  return ROW_BYTES == 128 ? (c >> 1) & 1 : c & 3;
-}
-template <int ROW_BYTES>
-__device__ __forceinline__ bf16x8_t frag_rows(const unsigned char* tile, int block, int kk, int lane) {
-  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
-  typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
-  const int g = lane >> 4, r16 = lane & 15;
-  const int c = kk * 16 + 8 * (g >> 1) + (r16 >> 2);
-  const unsigned char* p = tile + c * ROW_BYTES + ((block ^ seg_xor<ROW_BYTES>(r16 >> 2)) << 6) + 32 * (g & 1) +
-                           8 * (r16 & 3);
-  const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
-  const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * ROW_BYTES));
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-// ... and a tile with contiguous contraction (128-byte rows) its 16-byte chunks, chunk q of row r at q ^ (r & 7).
-__device__ __forceinline__ bf16x8_t frag_cols(const unsigned char* tile, int block, int kk, int lane) {
-  const int r = lane & 31, kb = lane >> 5;
-  return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(
-      tile + (block * 32 + r) * 128 + (((2 * kk + kb) ^ (r & 7)) << 4)));
-}
-// 64 x 16 bytes from base + per-lane offset to LDS [lds_off, lds_off + 1024).  Invisible to the compiler's
-// wait counts; nothing else here uses m0.
-__device__ __forceinline__ void load_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
-  const uint64_t u = (uint64_t)(uintptr_t)base_any;
-  const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)u) |
-                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32);
-  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
-}
-
 // LDS of a workgroup: two X^t tiles, three X^{t+1} tiles, two new weight tiles, the wavefronts'
 // transposition pieces, partial column sums and the new bias.  The D_1 band passes through the X^{t+1}
 // tiles before the walk.
@@ -162,8 +127,8 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
   for (int q = 0; q < REQ; ++q) {
     const int r = (q * NW + wave) * 8 + (lane >> 3), pos = lane & 7;
     const int row = r < BR ? r : BR - 1;
-    h_off[q] = (uint32_t)(((size_t)row * p.ldh + ((((pos >> 2) ^ seg_xor<128>(r)) << 2) | (pos & 3)) * 8) * 2);
-    x_off[q] = (uint32_t)(((size_t)row * p.ldx + ((pos ^ (r & 7)) * 8)) * 2);
+    h_off[q] = (uint32_t)(((size_t)row * p.ldh + ((((pos >> 2) ^ lds_seg_xor<128>(r)) << 2) | (pos & 3)) * 8) * 2);
+    x_off[q] = (uint32_t)(((size_t)row * p.ldx + (lds_chunk(r, pos) * 8)) * 2);
   }
   auto request_x = [&](int it, int hbuf, int xbuf) __attribute__((always_inline)) {
 #pragma unroll
@@ -188,21 +153,21 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
   for (int e = tid; e < BR * (NB / 8); e += NTHR) {
     const int b = e / (NB / 8), c = e % (NB / 8);
     *reinterpret_cast<u32x4_t*>(reinterpret_cast<unsigned char*>(Dn) + b * (NB * 2) +
-                                ((((c >> 2) ^ seg_xor<NB * 2>(b)) << 6) | ((c & 3) << 4))) =
+                                ((((c >> 2) ^ lds_seg_xor<NB * 2>(b)) << 6) | ((c & 3) << 4))) =
         *reinterpret_cast<const u32x4_t*>(d_g + (size_t)b * p.ldd + n0 + 8 * c);
   }
   __syncthreads();
   bf16x8_t df[BR / 16];
 #pragma unroll
   for (int kk = 0; kk < BR / 16; ++kk)
-    df[kk] = frag_rows<NB * 2>(reinterpret_cast<const unsigned char*>(Dn), wn, kk, lane);
+    df[kk] = lds_frag_trans<NB * 2>(reinterpret_cast<const unsigned char*>(Dn), wn, kk, lane);
   // b_1 <- b_1 - gamma db_1: four quarter sums over the minibatch rows, added in order
   {
     const int n = tid % NB, quarter = tid / NB;                          // NTHR = 4 NB
     float cs = 0.0f;
 #pragma unroll 8
     for (int b = quarter * (BR / 4); b < (quarter + 1) * (BR / 4); ++b)
-      cs += bf16_to_f32(Dn[b * NB + (((n >> 5) ^ seg_xor<NB * 2>(b)) << 5) + (n & 31)]);
+      cs += bf16_to_f32(Dn[b * NB + (((n >> 5) ^ lds_seg_xor<NB * 2>(b)) << 5) + (n & 31)]);
     Bs[quarter * NB + n] = cs;
   }
   __syncthreads();                                    // the band's place is free for the X tiles
@@ -236,7 +201,7 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
         const int mb = blk / (NB / 32), nblk = blk % (NB / 32);
 #pragma unroll
         for (int kk = 0; kk < BT / 16; ++kk)
-          acc_z[t] = mfma_bf16(frag_cols(Xk + xbuf * XT, mb, kk, lane), frag_rows<NB * 2>(Wl + wbuf * WT, nblk, kk, lane),
+          acc_z[t] = mfma_bf16(lds_frag_contig(Xk + xbuf * XT, mb, kk, lane), lds_frag_trans<NB * 2>(Wl + wbuf * WT, nblk, kk, lane),
                                acc_z[t]);
       }
     }
@@ -259,7 +224,7 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
 #pragma unroll
-    for (int kk = 0; kk < BR / 16; ++kk) acc = mfma_bf16(frag_rows<128>(Hk + hbuf * XT, wk, kk, lane), df[kk], acc);
+    for (int kk = 0; kk < BR / 16; ++kk) acc = mfma_bf16(lds_frag_trans<128>(Hk + hbuf * XT, wk, kk, lane), df[kk], acc);
     if (!FIRST) next_product(hbuf ^ 1, xprev);
     // accumulator element v of lane (lr32, kb) is C[8 (v/4) + 4 kb + v%4][lr32]
 #pragma unroll
@@ -294,7 +259,7 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
         *reinterpret_cast<f32x4_t*>(w_g + off) = w;
       }
       const int k = wk * 32 + 8 * q + trow;
-      *reinterpret_cast<u32x2_t*>(Wl + hbuf * WT + k * (NB * 2) + ((wn ^ seg_xor<NB * 2>(k)) << 6) + 2 * tcol) = hv2;
+      *reinterpret_cast<u32x2_t*>(Wl + hbuf * WT + k * (NB * 2) + ((wn ^ lds_seg_xor<NB * 2>(k)) << 6) + 2 * tcol) = hv2;
     }
     // The next X tile has landed (younger than its requests: this phase's weight loads and stores), the
     // new weights are in LDS, and nobody reads this phase's tiles any more.

@@ -55,26 +55,9 @@ __device__ __forceinline__ float act_bwd_from_h(float h, int act) {
   return act == PRSGD_TANH ? (1.0f - h * h) : (h > 0.0f ? 1.0f : 0.0f);
 }
 
-// 64 x 16 bytes from base + per-lane offset to LDS [m0, m0 + 1024), lane order.  Not visible to the
-// compiler's wait counts: the pipeline below waits by itself (wait_tiles), everything the compiler
-// waits for on its own is then waited for at least as long as it needs.  Nothing else in this file
-// uses m0 (a reserved register, which cannot be listed as clobbered).
-__device__ __forceinline__ void load_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
-  // both are the same in every lane; said explicitly, they end up in scalar registers
-  const uint64_t u = (uint64_t)(uintptr_t)base_any;
-  const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)u) |
-                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32);
-  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
-}
-
 // One operand tile of ROWS output rows (or columns) in LDS, and the requests that fill it.
-//   OP_CONTIG: element (r, c) at src[r * ld + c]; LDS [ROWS][128 bytes], the 16-byte chunk q of row r
-//     at chunk q ^ (r & 7): eight consecutive rows then read one chunk each from all banks.
-//   OP_TRANS : element (r, c) at src[c * ld + r]; LDS [depth][ROWS].  bf16: the transpose read takes
-//     32 consecutive elements (64 bytes) of four consecutive contraction rows at a time, so those
-//     64-byte segments are permuted within 256 bytes such that the four fall on different banks.
+//   OP_CONTIG: element (r, c) at src[r * ld + c]; LDS [ROWS][128 bytes], chunks at lds_chunk
+//   OP_TRANS : element (r, c) at src[c * ld + r]; LDS [depth][ROWS], bf16 segments at lds_seg_xor
 // Rows past the operand are requested as copies of the last one (their results are not stored).
 template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
   using E = typename T::elem;
@@ -86,10 +69,7 @@ template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
   static constexpr int CH = ROW_BYTES / 16;                // 16-byte chunks of an LDS row
 
   // permutation of the 64-byte segments of contraction row c (OP_TRANS)
-  __device__ static __forceinline__ int seg_xor(int c) {
-    if (!T::kBf16 || ROW_BYTES <= 64) return 0;
-    return ROW_BYTES == 128 ? (c >> 1) & 1 : c & 3;
-  }
+  __device__ static __forceinline__ int seg_xor(int c) { return T::kBf16 ? lds_seg_xor<ROW_BYTES>(c) : 0; }
   // offsets (bytes from the tile's base address) of this lane's requests.  n_rows: rows of the operand
   // from the tile's first; n_c: contraction elements from the tile's first (clamped like the rows)
   __device__ static __forceinline__ void offsets(uint32_t (&off)[NPT], int ld, int n_rows, int n_c, int wave,
@@ -100,7 +80,7 @@ template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
       const int lr = chunk / CH, pos = chunk % CH;
       if (KIND == OP_CONTIG) {
         const int row = min(lr, n_rows - 1);
-        const int c = min((pos ^ (lr & 7)) * V, (n_c - 1) / V * V);
+        const int c = min(lds_chunk(lr, pos) * V, (n_c - 1) / V * V);
         off[q] = (uint32_t)((size_t)row * ld + c) * ES;
       } else {
         const int c = min(lr, n_c - 1);
@@ -131,22 +111,12 @@ __device__ __forceinline__ Frag<T> load_frag(const unsigned char* tile, int bloc
   using IO = TileIO<T, ROWS, KIND, NWAVE>;
   Frag<T> f;
   const int r = lane & 31, kb = lane >> 5;
-  if constexpr (KIND == OP_CONTIG) {
-    const unsigned char* p = tile + (block * 32 + r) * kTileBytes + (((2 * kk + kb) ^ (r & 7)) << 4);
-    if constexpr (T::kBf16) f.v = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(p));
-    else f.v = *reinterpret_cast<const f32x4_t*>(p);
+  if constexpr (KIND == OP_CONTIG && T::kBf16) {
+    f.v = lds_frag_contig(tile, block, kk, lane);
+  } else if constexpr (KIND == OP_CONTIG) {
+    f.v = *reinterpret_cast<const f32x4_t*>(tile + (block * 32 + r) * kTileBytes + (lds_chunk(r, 2 * kk + kb) << 4));
   } else if constexpr (T::kBf16) {
-    // transpose read (see frag_trans): lane r of 16 addresses contraction row c0 + r/4, elements
-    // 4 (r%4) .. +3, and receives four consecutive contraction elements of element row r
-    typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
-    typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
-    const int g = lane >> 4, r16 = lane & 15;
-    const int c = kk * 16 + 8 * (g >> 1) + (r16 >> 2);
-    const unsigned char* p = tile + c * IO::ROW_BYTES + ((block ^ IO::seg_xor(r16 >> 2)) << 6) + 32 * (g & 1) +
-                             8 * (r16 & 3);
-    const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
-    const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * IO::ROW_BYTES));
-    f.v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    f.v = lds_frag_trans<IO::ROW_BYTES>(tile, block, kk, lane);
   } else {
     const unsigned char* p = tile + (8 * kk + 4 * kb) * IO::ROW_BYTES + (block * 32 + r) * 4;
 #pragma unroll

@@ -243,6 +243,50 @@ __device__ __forceinline__ bf16x8_t frag_trans(const uint16_t* lds, int stride, 
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// ---- tiles requested straight into LDS ---------------------------------------------------------
+// 64 x 16 bytes from base + per-lane offset to LDS [lds_any, lds_any + 1024), lane order.  Not visible to the
+// compiler's wait counts: a kernel that uses it waits by itself, and everything the compiler waits for on its
+// own is then waited for at least as long as it needs.  m0 is a reserved register, which cannot be listed as
+// clobbered: nothing else in such a kernel may use it.
+__device__ __forceinline__ void load_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
+  // both are the same in every lane; said explicitly, they end up in scalar registers
+  const uint64_t u = (uint64_t)(uintptr_t)base_any;
+  const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)u) |
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32);
+  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+}
+// Such a tile cannot be padded on its way, so bank conflicts are avoided by permuting WHICH 16 bytes a lane
+// requests.  [c][row], contraction index c the LDS row of ROW_BYTES: the transpose read takes 64 bytes of
+// four consecutive c at a time, so the 64-byte segments of row c are exchanged (segment s at s ^ lds_seg_xor(c))
+// such that the four fall on different banks.
+template <int ROW_BYTES> __device__ __forceinline__ int lds_seg_xor(int c) {
+  if (ROW_BYTES <= 64) return 0;
+  return ROW_BYTES == 128 ? (c >> 1) & 1 : c & 3;
+}
+// bf16 fragment of a 32-row block out of such a tile (the lane addresses of frag_trans).
+template <int ROW_BYTES>
+__device__ __forceinline__ bf16x8_t lds_frag_trans(const unsigned char* tile, int block, int kk, int lane) {
+  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
+  typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
+  const int g = lane >> 4, r = lane & 15;
+  const int c = kk * 16 + 8 * (g >> 1) + (r >> 2);
+  const unsigned char* p = tile + c * ROW_BYTES + ((block ^ lds_seg_xor<ROW_BYTES>(r >> 2)) << 6) + 32 * (g & 1) +
+                           8 * (r & 3);
+  const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
+  const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * ROW_BYTES));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// [row][c] with 128-byte rows: the 16-byte chunk q of row r stands at lds_chunk(r, q), so that eight consecutive
+// rows read one chunk each from all banks.
+__device__ __forceinline__ int lds_chunk(int r, int q) { return q ^ (r & 7); }
+__device__ __forceinline__ bf16x8_t lds_frag_contig(const unsigned char* tile, int block, int kk, int lane) {
+  const int r = lane & 31, kb = lane >> 5;
+  return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(tile + (block * 32 + r) * 128 +
+                                                                       (lds_chunk(r, 2 * kk + kb) << 4)));
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two 32x32->64 multiplies
 // with the key advanced by the Weyl constants between rounds.
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
