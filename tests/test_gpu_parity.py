@@ -562,8 +562,8 @@ def test_bf16_full_size_replicas(P, D, name, iters, interval):
 
 @pytest.mark.parametrize("name", ["c3", "c5"])
 def test_first_layer_pass_at_full_size_matches_the_separate_launches(P, D, name):
-    # the launch shapes the benchmark times (c5: non-temporal weight traffic, 128-row minibatches;
-    # c3: 64-row minibatches, 16 replicas): fused and separate forms agree bit for bit
+    # the launch shapes the benchmark times (c5: 128-column bands, 128-row minibatches; c3: 64-column bands,
+    # 64-row minibatches, 16 replicas; both non-temporal): fused and separate forms agree bit for bit
     w = get_workload(name).scaled(rows_per_worker=256, iterations=5, interval=3)
     inp = make_inputs(w)
     outs = []
@@ -576,6 +576,43 @@ def test_first_layer_pass_at_full_size_matches_the_separate_launches(P, D, name)
         P.prsgd_destroy(h)
     for a, b in zip(outs[0], outs[1]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("dims,n_workers,streamed", [((256, 1024, 10), 32, False), ((1024, 2048, 10), 24, True)])
+@pytest.mark.parametrize("batch", [32, 64, 128])
+def test_first_layer_pass_in_wide_bands_matches_the_separate_launches(P, D, dims, n_workers, streamed, batch):
+    # at least 256 workgroups of 128-column bands, cached and non-temporal, every minibatch height
+    assert dims[1] % 128 == 0 and dims[1] // 128 * n_workers >= 256
+    w = small_mlp(dims=dims, n_workers=n_workers, batch=batch, gemm_dtype="bf16", activation="relu",
+                  rows_per_worker=256, interval=3, iterations=5)
+    uses = P.prsgd_streamed_uses(P.make_config(n_workers, "mlp", dims, batch, 256, w.lr, w.index_seed, "relu", "bf16"))
+    assert bool(uses & P.PRSGD_STREAM_STEPS) == streamed
+    inp = inputs_for(w)
+    outs = []
+    for on in (True, False):
+        h = _open(D, w, inp)
+        P.prsgd_set_first_layer_fusion(h, on)
+        names = _kernel_names(P, h, w.iterations, w.interval)
+        assert ("gemm_bwd_first" in names) == on, names
+        outs.append((D.read_all(h), P.prsgd_read_loss(h)))
+        P.prsgd_destroy(h)
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
+def test_bf16_rounding_of_every_class_of_value(P):
+    """Nearest even in every upper half with every kind of lower half, infinities, denormals and NaN
+    (which stay NaN): the shadow that an update with gradient zero writes."""
+    low = np.array([0, 1, 0x7FFF, 0x8000, 0x8001, 0xFFFF], dtype=np.uint32)
+    u = ((np.arange(1 << 16, dtype=np.uint32) << 16)[:, None] | low[None, :]).ravel()
+    nan = (u & 0x7FFFFFFF) > 0x7F800000
+    want = np.where(nan, (u >> 16) | 0x40, (u + np.where(nan, 0, 0x7FFF + ((u >> 16) & 1)).astype(np.uint32)) >> 16)
+    x = torch.from_numpy(u.view(np.float32).copy()).cuda()
+    shadow = torch.zeros(u.size, dtype=torch.bfloat16, device="cuda")
+    P.prsgd_sgd_update(x, torch.zeros_like(x), 0.0, shadow=shadow)
+    got = shadow.view(torch.int16).cpu().numpy().view(np.uint16)
+    bad = got != want
+    assert not bad.any(), [(hex(a), hex(b), hex(c)) for a, b, c in zip(u[bad][:5], got[bad][:5], want[bad][:5])]
 
 
 # --------------------------------------------------------------------------- restart average
