@@ -43,8 +43,8 @@ KERNEL_SYMBOL = {
     "mlp2_epoch": "mlp2_epoch_kernel",
     "gemm_bwd_first": "bwd_first_fwd_kernel (layer 1: backward step + next forward product)",
     "refresh_shadow": "refresh_shadow_kernel (bf16 image of W_1 when the first-layer chain breaks)",
-    "step_mean": "grouped_gemm_kernel<.., OP_TRANS, OP_TRANS, true> (the minibatches of all workers "
-                 "stacked into one contraction)",
+    "step_mean": "grouped_gemm_kernel<.., OP_TRANS, OP_TRANS> (the minibatches of all workers stacked "
+                 "into one contraction; small layers together: grouped_gemm_set_kernel)",
 }
 
 

@@ -104,8 +104,9 @@ prsgd_config effective_config(const prsgd_config* c) {
 }
 
 // Replica sets from here on are streamed (non-temporal weight loads and stores).  An iteration rewrites the
-// whole set, so that past most of the 256 MB last-level cache a line is gone before it is needed again:
-// 16 replicas of 3072-1024-1024-10 (269 MB) 157 -> 155 us per iteration, 274 -> 266 us with momentum.
+// whole set, so that past most of the 256 MB last-level cache a line is gone before it is needed again.
+// Replicas of 3072-1024-1024-10 at interval 16, per iteration, cached and streamed: 10 (161 MiB) 107 and 110 us, 11 119
+// and 119 us, 12 (193 MiB) 138 and 126 us, 16 149 and 146 us (with momentum 262 and 258 us), 32 288 and 279 us.
 constexpr size_t kStreamingBytes = (size_t)192 << 20;
 
 // Which launches of a configuration are streamed.
