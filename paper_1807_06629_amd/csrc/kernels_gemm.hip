@@ -550,8 +550,8 @@ constexpr int kComputeUnits = 256;
 // unit takes in its operand tiles (the number of lines it can have outstanding), so a launch takes the tile
 // with which the busiest compute unit requests the fewest bytes: tiles per compute unit, rounded up, times
 // rows + columns of a tile.  Workers x (rows x contraction) x columns: 8 x (128 x 4096) x 4096 with shared weights,
-// 128 x 128 tiles 57 -> 49 us forward, 47 -> 40 us backward-data against the register-staged tiles this replaces;
-// 6 x (100 x 500) x 300, 32 x 64 tiles 9.6 -> 6.7 us.  Taken in 32 x 64, 64 x 64, 128 x 64 and 128 x 128 tiles:
+// 128 x 128 tiles 57 -> 49 us forward against the register-staged tiles this replaces (backward-data, two such products
+// and one with a contraction of 1000 on average 47 -> 40 us); 6 x (100 x 500) x 300, 32 x 64 tiles 9.6 -> 6.7 us.  Taken in 32 x 64, 64 x 64, 128 x 64 and 128 x 128 tiles:
 // 6 x (128 x 896) x 3776 25.7, 17.8, 16.6, 16.1 us (128 x 128 by the rule), 8 x (95 x 3456) x 3760 119.7, 100.3, 78.9,
 // 73.5 us (128 x 128), 6 x (100 x 500) x 300 8.7, 9.1, 10.2, 12.5 us (32 x 64); over 292 products the rule's tile is
 // within 3 % of the best one on six in seven, and within 18 % on all.

@@ -28,6 +28,8 @@ SHAPES = [
     ("bf16", (72, 1032, 1000, 12), 100, 12),         # 128 x 64 tiles, ragged rows
     ("bf16", (72, 1032, 1024, 12), 128, 12),         # 128 x 64 tiles, whole rows
     ("bf16", (72, 1032, 1000, 12), 160, 16),         # 128-row tiles, ragged contraction and rows
+    ("bf16", (40, 66, 70, 80, 50, 30, 9), 33, 3),    # more weight gradients than one launch takes
+    ("f32", (40, 66, 70, 80, 50, 30, 9), 33, 3),
     ("bf16", (130, 70), 40, 5),                      # a weight gradient alone in its launch, contraction of one tile
     ("bf16", (130, 70), 200, 3),                     # ... and of several
     ("f32", (130, 70), 40, 5),
