@@ -39,7 +39,7 @@ KERNEL_SYMBOL = {
                "than 262144 floats)",
     "restart_mean": "mean_kernel (restart_small_kernel<.., false> when N >= 8 and a replica has "
                     "fewer than 262144 floats)",
-    "lsq_steps": "lsq_steps_staged_kernel (lsq_steps_kernel for shapes it does not take)",
+    "lsq_steps": "lsq_resident_kernel (lsq_steps_staged_kernel, lsq_steps_kernel for shapes it does not take)",
     "mlp2_epoch": "mlp2_epoch_kernel",
     "gemm_bwd_first": "bwd_first_fwd_kernel (layer 1: backward step + next forward product)",
     "refresh_shadow": "refresh_shadow_kernel (bf16 image of W_1 when the first-layer chain breaks)",

@@ -239,22 +239,25 @@ int64_t prsgd_iteration(const prsgd_ctx* ctx);            /* < 0 on a null conte
 
 /*
  * Synchronises the stream and reports whether every launch so far ran to completion.
- * One-hidden-layer fp32 MLPs run whole epochs in one launch whose workgroups wait for each other
- * inside the kernel; that needs all of them resident at once, which holds on a device that runs
- * nothing else (checked at prsgd_init) -- keep the device otherwise idle while such a context is
- * stepping.  If other work did hold compute units, the kernel's bounded wait gives up instead of
+ * Some launches have workgroups that wait for each other inside the kernel, which needs all of them
+ * resident at once: whole epochs of one-hidden-layer fp32 MLPs, and prsgd_run on small least-squares
+ * problems (N <= 64, d <= 512, B <= 64), whose restarts are exchanges inside the launch.  That holds on a
+ * device that runs nothing else (checked at prsgd_init) -- keep the device otherwise idle while such a
+ * context is stepping; prsgd_run looks after the process's own contexts: restarts are launches of their own where
+ * contexts of other streams could hold the compute units that a launch waits for, and in a stream that is being
+ * captured.  If other work did hold compute units, the kernel's bounded wait gives up instead of
  * hanging: this call (like every prsgd_read_* call) then returns PRSGD_ESTATE, the replicas are
  * inconsistent, and prsgd_local_steps / prsgd_average / prsgd_run keep returning PRSGD_ESTATE
  * until every replica has been rewritten with prsgd_write_params (worker -1, or each worker
- * once).  From then on the context runs its local steps as a chain of per-layer kernels, which
- * needs no co-resident workgroups.
+ * once).  From then on the context runs kernels that need no co-resident workgroups: a chain of per-layer kernels,
+ * or for least squares a launch per epoch.
  */
 int prsgd_status(prsgd_ctx* ctx);
 
 /*
  * Per-kernel timing with HIP events on the context's stream.  While enabled every kernel
  * launch is bracketed by an event pair (this serialises launches; leave it off when timing
- * whole runs).  prsgd_profile_read synchronises, then fills up to `max` records, returns the
+ * whole runs), and prsgd_run gives every restart a launch of its own.  prsgd_profile_read synchronises, then fills up to `max` records, returns the
  * number of kernel kinds (or a negative status) and resets the counters.
  */
 typedef struct {

@@ -32,7 +32,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 thread_local char g_init_error[256] = "";
 
 struct Carve {
-  size_t xb = 0, yb = 0, idx = 0, xb2 = 0, yb2 = 0, idx2 = 0, logits = 0, losses = 0, row_loss = 0, part = 0, sync = 0, shadow = 0, grads = 0, mean = 0, mean_shadow = 0, steps = 0, vel = 0;
+  size_t xb = 0, yb = 0, idx = 0, xb2 = 0, yb2 = 0, idx2 = 0, logits = 0, losses = 0, row_loss = 0, part = 0, sync = 0, shadow = 0, grads = 0, mean = 0, mean_shadow = 0, steps = 0, vel = 0, exchange = 0;
   size_t h[PRSGD_MAX_DIMS] = {0}, delta[PRSGD_MAX_DIMS] = {0};
   size_t total = 0;
 };
@@ -145,8 +145,12 @@ void build_carve(const prsgd_config* c_in, const Layout& lo, Carve* cv) {
   cv->idx = take(n * b * 4);
   cv->losses = take(n * 4);
   cv->steps = take(n * 4);
-  cv->mean = take((size_t)lo.m_pad * 4);
+  cv->mean = take((size_t)lo.m_pad * 4 + (c->model == PRSGD_LSQ ? kAlign : 0));   // least squares: abort flag behind it
   if (c->momentum != 0.0f) cv->vel = take(n * (size_t)lo.m_pad * 4);
+  if (c->model == PRSGD_LSQ && lsq_restarts_in_launch(c->n_workers, lo.d[0], c->batch)) {
+    cv->sync = take(4);
+    cv->exchange = take(lsq_exchange_bytes(c->n_workers, lo.d[0]));
+  }
   if (c->model == PRSGD_MLP) {
     const int L = lo.n_layers;
     cv->yb = take(n * b * 4);
@@ -191,6 +195,8 @@ struct prsgd_ctx {
   Carve cv;
   bool bf16;
   bool use_fused2;      // one-hidden-layer fp32 MLP: whole epochs in one launch
+  bool enlisted;        // in the table of contexts whose workgroups wait for each other
+  bool restarts_in_launch;   // whole runs in one launch: its workgroups exchange the points at a restart
   Fused2Plan f2;
   Streamed streamed;    // launches whose weight traffic is marked non-temporal
   bool lazy_restart;    // a restart only writes the node average; the next local iteration
@@ -228,7 +234,7 @@ struct prsgd_ctx {
   double prof_ms[KK_COUNT];
   int64_t prof_n[KK_COUNT];
   // scratch host buffer for padded <-> dense parameter conversion
-  float* host_pad;                    // [m_pad]
+  float* host_pad;                    // [m_pad + 1]
   std::vector<float> host_pad_heap;   // owns it, unless the context lives in static storage
   int static_slot;                    // >= 0: context, workspace and host_pad are the per-device
                                       // static ones of prsgd_init_static
@@ -248,6 +254,12 @@ struct prsgd_ctx {
   bool can_start_from_mean() const {
     return cfg.model == PRSGD_LSQ || use_fused2 ||
            (bf16 && cfg.fused_update && prsgd::bwd_fused_supported(cfg.batch));
+  }
+  // set by a launch whose workgroups gave up waiting for each other (nullptr: no such launches)
+  unsigned int* abort_flag() const {
+    if (use_fused2) return at<unsigned int>(cv.sync) + (size_t)cfg.n_workers * 32;
+    if (cfg.model == PRSGD_LSQ && restarts_in_launch) return reinterpret_cast<unsigned int*>(mean() + lo.m_pad);
+    return nullptr;
   }
   float* grads() const { return cfg.fused_update ? nullptr : at<float>(cv.grads); }
 };
@@ -642,6 +654,21 @@ Fused2Args fused2_args(prsgd_ctx* ctx, int k, const int* worker_steps) {
   return a;
 }
 
+LsqArgs lsq_args(prsgd_ctx* ctx, int k) {
+  const prsgd_config& c = ctx->cfg;
+  LsqArgs a;
+  memset(&a, 0, sizeof(a));
+  a.features = ctx->features;
+  a.targets = reinterpret_cast<const float*>(ctx->targets);
+  a.src = ctx->src(); a.src_stride = ctx->src_stride();
+  a.params = ctx->params; a.m_pad = ctx->lo.m_pad;
+  a.velocity = ctx->velocity(); a.mu = c.momentum;
+  a.losses = ctx->at<float>(ctx->cv.losses); a.idx = ctx->at<int32_t>(ctx->cv.idx);
+  a.n_workers = c.n_workers; a.d = ctx->lo.d[0]; a.rows = (long)c.rows_per_worker; a.batch = c.batch;
+  a.lr = ctx->lr; a.seed = c.seed; a.t0 = (uint64_t)ctx->t; a.k = k;
+  return a;
+}
+
 constexpr const char* kPoisonedMsg =
     "the epoch kernel gave up waiting for a team member (was other work running on the device?); "
     "the replicas are inconsistent: restore them with prsgd_write_params (and prsgd_set_iteration)";
@@ -655,26 +682,29 @@ int check_poisoned(prsgd_ctx* ctx) {
 // stream is synchronised anyway: reads the flag (4 bytes); if it is set, clears it, marks the
 // context poisoned and switches every later local step to the per-layer kernel chain, which needs
 // no co-resident workgroups.
-int check_fused2_abort(prsgd_ctx* ctx) {
-  if (ctx->poisoned) return set_err(ctx, PRSGD_ESTATE, "%s", kPoisonedMsg);
-  if (!ctx->use_fused2) return PRSGD_OK;
-  unsigned int* flag_dev = ctx->at<unsigned int>(ctx->cv.sync) + (size_t)ctx->cfg.n_workers * 32;
-  unsigned int flag = 0;
-  hipError_t e = hipMemcpyAsync(&flag, flag_dev, sizeof(flag), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  if (e != hipSuccess) return hip_fail(ctx, e, "abort-flag read");
-  if (flag == 0) return PRSGD_OK;
+int workgroups_gave_up(prsgd_ctx* ctx) {
   const unsigned int zero = 0;
-  e = hipMemcpyAsync(flag_dev, &zero, sizeof(zero), hipMemcpyHostToDevice, ctx->stream);
+  hipError_t e = hipMemcpyAsync(ctx->abort_flag(), &zero, sizeof(zero), hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "abort-flag reset");
+  if (ctx->use_fused2 && ctx->cfg.momentum != 0.0f) ctx->cfg.fused_update = 0;   // the chain applies momentum elementwise
   ctx->use_fused2 = false;
-  if (ctx->cfg.momentum != 0.0f) ctx->cfg.fused_update = 0;   // the chain applies momentum elementwise
+  ctx->restarts_in_launch = false;
   ctx->poisoned = true;
   ctx->at_mean = false;
   ctx->n_restored = 0;
   memset(ctx->restored, 0, sizeof(ctx->restored));
   return set_err(ctx, PRSGD_ESTATE, "%s", kPoisonedMsg);
+}
+int check_gave_up(prsgd_ctx* ctx) {
+  if (ctx->poisoned) return set_err(ctx, PRSGD_ESTATE, "%s", kPoisonedMsg);
+  unsigned int* flag_dev = ctx->abort_flag();
+  if (flag_dev == nullptr) return PRSGD_OK;
+  unsigned int flag = 0;
+  hipError_t e = hipMemcpyAsync(&flag, flag_dev, sizeof(flag), hipMemcpyDeviceToHost, ctx->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e != hipSuccess) return hip_fail(ctx, e, "abort-flag read");
+  return flag == 0 ? PRSGD_OK : workgroups_gave_up(ctx);
 }
 
 // Writes the node average into every replica (and the bf16 shadow) if the last restart left the
@@ -761,7 +791,89 @@ StaticSlot g_static[kMaxStaticDevices];
 float g_static_pad[kMaxStaticDevices][kStaticBytes / sizeof(float)];   // host staging, per device
 std::mutex g_static_mutex;
 
+// Contexts whose launches have workgroups that wait for each other, on any device.  A launch that needs its whole grid
+// resident (restarts inside the launch) only goes out while every such grid that could run beside it fits the
+// device with it: contexts of one stream never run together, those of other streams may, and two half-resident
+// grids would wait for each other until they give up.  Otherwise the restarts are launches of their own.
+struct WaitingUse {
+  const prsgd_ctx* ctx;
+  hipStream_t stream;
+  int dev, workgroups, compute_units;
+};
+constexpr int kMaxWaitingUses = 256;
+WaitingUse g_waiting[kMaxWaitingUses];
+int g_n_waiting = 0, g_waiting_unlisted = 0;     // contexts beyond the table: nobody goes out whole
+std::mutex g_waiting_mutex;
+
+// Workgroups that other streams' contexts may have waiting on `dev`: the largest context of each stream.
+int waiting_beside(int dev, hipStream_t stream) {
+  int total = 0;
+  for (int a = 0; a < g_n_waiting; ++a) {
+    const WaitingUse& u = g_waiting[a];
+    if (u.dev != dev || u.stream == stream) continue;
+    bool largest = true;
+    for (int b = 0; b < g_n_waiting && largest; ++b) {
+      const WaitingUse& o = g_waiting[b];
+      if (b != a && o.dev == dev && o.stream == u.stream &&
+          (o.workgroups > u.workgroups || (o.workgroups == u.workgroups && b < a)))
+        largest = false;
+    }
+    if (largest) total += u.workgroups;
+  }
+  return total;
+}
+// With g_waiting_mutex held: may this context's grid be launched as one that waits as a whole?
+bool may_wait_as_whole(const prsgd_ctx* ctx) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;   // a graph may be launched beside anything
+  if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (g_waiting_unlisted != 0) return false;
+  for (int a = 0; a < g_n_waiting; ++a) {
+    const WaitingUse& u = g_waiting[a];
+    if (u.ctx != ctx) continue;
+    const int beside = waiting_beside(u.dev, u.stream);
+    return beside == 0 || beside + u.workgroups <= u.compute_units;
+  }
+  return false;
+}
+// A context that no longer fits beside the others lets their launches under way finish before its own begin.
+hipError_t enlist_waiting(prsgd_ctx* ctx, int workgroups) {
+  WaitingUse u = {ctx, ctx->stream, 0, workgroups, 0};
+  hipError_t e = hipGetDevice(&u.dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&u.compute_units, hipDeviceAttributeMultiprocessorCount, u.dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lock(g_waiting_mutex);
+  if (g_n_waiting < kMaxWaitingUses) g_waiting[g_n_waiting++] = u;
+  else ++g_waiting_unlisted;
+  ctx->enlisted = true;
+  if (waiting_beside(u.dev, u.stream) + workgroups <= u.compute_units && g_waiting_unlisted == 0) return hipSuccess;
+  for (int a = 0; a < g_n_waiting; ++a) {
+    if (g_waiting[a].dev != u.dev || g_waiting[a].stream == u.stream) continue;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(g_waiting[a].stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      continue;
+    }
+    e = hipStreamSynchronize(g_waiting[a].stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+void strike_waiting(const prsgd_ctx* ctx) {
+  if (!ctx->enlisted) return;
+  std::lock_guard<std::mutex> lock(g_waiting_mutex);
+  for (int a = 0; a < g_n_waiting; ++a) {
+    if (g_waiting[a].ctx != ctx) continue;
+    g_waiting[a] = g_waiting[--g_n_waiting];
+    return;
+  }
+  --g_waiting_unlisted;
+}
+
 void release_ctx(prsgd_ctx* ctx) {
+  strike_waiting(ctx);
   if (ctx->static_slot < 0) { delete ctx; return; }
   const int slot = ctx->static_slot;
   ctx->~prsgd_ctx();
@@ -810,6 +922,8 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
                     fused2_plan(cfg->n_workers, lo.d[0], lo.d[1], lo.d[2], cfg->batch,
                                 cfg->momentum != 0.0f, &ctx->f2);
   if (cfg->momentum != 0.0f && !bwd_fused_config(ctx->cfg) && !ctx->use_fused2) ctx->cfg.fused_update = 0;
+  ctx->restarts_in_launch = cfg->model == PRSGD_LSQ && ctx->cv.exchange != 0;
+  ctx->enlisted = false;
   ctx->features = reinterpret_cast<const float*>(features_dev);
   ctx->targets = targets_dev;
   ctx->params = reinterpret_cast<float*>(params_dev);
@@ -835,10 +949,10 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
   memset(ctx->prof_ms, 0, sizeof(ctx->prof_ms));
   memset(ctx->prof_n, 0, sizeof(ctx->prof_n));
   if (static_slot >= 0) {
-    ctx->host_pad = g_static_pad[static_slot];       // m_pad floats fit: the workspace holds as many
+    ctx->host_pad = g_static_pad[static_slot];       // m_pad + 1 floats fit: the workspace holds more
   } else {
     try {
-      ctx->host_pad_heap.resize((size_t)lo.m_pad);
+      ctx->host_pad_heap.resize((size_t)lo.m_pad + 1);
     } catch (...) {
       release_ctx(ctx);
       return set_err(nullptr, PRSGD_ENOMEM, "out of host memory");
@@ -859,6 +973,8 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
     e = launch_broadcast(ctx->at<float>(ctx->cv.mean), ctx->params, ctx->shadow(), lo.m_pad,
                          cfg->n_workers, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e == hipSuccess && (ctx->use_fused2 || ctx->restarts_in_launch))
+    e = enlist_waiting(ctx, ctx->use_fused2 ? cfg->n_workers * ctx->f2.P : cfg->n_workers);
   if (e != hipSuccess) {
     hip_fail(nullptr, e, "prsgd_init");
     release_ctx(ctx);
@@ -924,12 +1040,7 @@ int prsgd_local_steps(prsgd_ctx* ctx, int32_t k) {
   const prsgd_config& c = ctx->cfg;
   if (c.model == PRSGD_LSQ) {
     if (k == 0) return PRSGD_OK;
-    LAUNCH(ctx, KK_LSQ,
-           launch_lsq_steps(ctx->features, reinterpret_cast<const float*>(ctx->targets), ctx->src(),
-                            ctx->src_stride(), ctx->params, ctx->velocity(), c.momentum,
-                            ctx->at<float>(ctx->cv.losses), ctx->at<int32_t>(ctx->cv.idx), c.n_workers,
-                            ctx->lo.d[0], ctx->lo.m_pad, (long)c.rows_per_worker, c.batch, ctx->lr, c.seed,
-                            ctx->t, k, nullptr, ctx->stream));
+    LAUNCH(ctx, KK_LSQ, launch_lsq_steps(lsq_args(ctx, k), ctx->stream));
     ctx->at_mean = false;
     ctx->t += k;
     return PRSGD_OK;
@@ -979,12 +1090,9 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "copy of worker step counts");
   if (c.model == PRSGD_LSQ) {
-    LAUNCH(ctx, KK_LSQ,
-           launch_lsq_steps(ctx->features, reinterpret_cast<const float*>(ctx->targets), ctx->params,
-                            ctx->lo.m_pad, ctx->params, nullptr, 0.0f,
-                            ctx->at<float>(ctx->cv.losses), ctx->at<int32_t>(ctx->cv.idx), c.n_workers,
-                            ctx->lo.d[0], ctx->lo.m_pad, (long)c.rows_per_worker, c.batch, ctx->lr, c.seed,
-                            ctx->t, k_max, steps_dev, ctx->stream));
+    LsqArgs a = lsq_args(ctx, k_max);
+    a.worker_steps = steps_dev;
+    LAUNCH(ctx, KK_LSQ, launch_lsq_steps(a, ctx->stream));
     ctx->t += k_max;
     return PRSGD_OK;
   }
@@ -1048,6 +1156,34 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
   if (ctx == nullptr) return PRSGD_EINVAL;
   if (iterations < 0 || interval < 1) return set_err(ctx, PRSGD_EINVAL, "iterations >= 0, interval >= 1");
   int64_t left = iterations;
+  // Restarts that need no launch of their own: the whole run, up to a restart at its end, is one launch (least squares, 4
+  // workers of 64 floats, 256 iterations with a restart after every eighth: 530 us with two launches per epoch, 205 us).
+  // Per-kernel timing keeps them apart, as launches of their own.
+  while (ctx->restarts_in_launch && ctx->lazy_restart && !ctx->profiling &&
+         (ctx->velocity() == nullptr || ctx->cfg.momentum_restart == PRSGD_MOM_KEEP)) {
+    constexpr int64_t kLongest = 1 << 20;
+    const int k = (int)(left < kLongest ? left : kLongest);
+    if (k <= interval - (ctx->t % interval)) break;
+    if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
+    {
+      std::lock_guard<std::mutex> lock(g_waiting_mutex);
+      if (!may_wait_as_whole(ctx)) break;
+      LsqArgs a = lsq_args(ctx, k);
+      a.interval = interval;
+      a.sync = ctx->at<unsigned int>(ctx->cv.sync);
+      a.abort_flag = ctx->abort_flag();
+      a.exchange = ctx->at<unsigned long long>(ctx->cv.exchange);
+      a.spin_limit = ctx->spin_limit;
+      LAUNCH(ctx, KK_LSQ, launch_lsq_steps(a, ctx->stream));
+    }
+    ctx->at_mean = false;
+    ctx->t += k;
+    left -= k;
+    if (ctx->t % interval == 0) {
+      const int rc = prsgd_average(ctx);
+      if (rc != PRSGD_OK) return rc;
+    }
+  }
   // Plain SGD on bf16 operands with the deferred broadcast: the iteration that completes an epoch
   // and the restart after it are one pass that writes only ybar (with I = 1: every iteration)
   const bool can_fuse = ctx->cfg.model == PRSGD_MLP && ctx->bf16 && ctx->cfg.fused_update &&
@@ -1085,8 +1221,13 @@ int prsgd_read_params(prsgd_ctx* ctx, int32_t worker, float* out_host, size_t m)
   if (out_host == nullptr) return set_err(ctx, PRSGD_EINVAL, "out_host is null");
   if (m != (size_t)ctx->lo.m) return set_err(ctx, PRSGD_EINVAL, "m does not match the parameter count");
   if (worker < -1 || worker >= ctx->cfg.n_workers) return set_err(ctx, PRSGD_EINVAL, "worker out of range");
-  const int arc = check_fused2_abort(ctx);
-  if (arc != PRSGD_OK) return arc;
+  // the average of a least-squares context comes with the abort flag that stands behind it: one copy
+  const bool with_flag = ctx->lo.n_layers == 0 && ctx->abort_flag() != nullptr && !ctx->poisoned &&
+                         (ctx->at_mean || worker < 0);
+  if (!with_flag) {
+    const int arc = check_gave_up(ctx);
+    if (arc != PRSGD_OK) return arc;
+  }
   const float* src;
   if (ctx->at_mean) {
     src = ctx->mean();                      // every worker's point, and their average
@@ -1097,10 +1238,15 @@ int prsgd_read_params(prsgd_ctx* ctx, int32_t worker, float* out_host, size_t m)
   } else {
     src = ctx->params + (size_t)worker * ctx->lo.m_pad;
   }
-  hipError_t e = hipMemcpyAsync(ctx->host_pad, src, sizeof(float) * (size_t)ctx->lo.m_pad,
+  hipError_t e = hipMemcpyAsync(ctx->host_pad, src, sizeof(float) * (size_t)(ctx->lo.m_pad + (with_flag ? 1 : 0)),
                                 hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "prsgd_read_params");
+  if (with_flag) {
+    unsigned int flag = 0;
+    memcpy(&flag, ctx->host_pad + ctx->lo.m_pad, sizeof(flag));
+    if (flag != 0) return workgroups_gave_up(ctx);
+  }
   dense_from_pad(ctx, ctx->host_pad, out_host);
   return PRSGD_OK;
 }
@@ -1152,7 +1298,7 @@ int prsgd_read_velocity(prsgd_ctx* ctx, int32_t worker, float* out_host, size_t 
   if (m != (size_t)ctx->lo.m) return set_err(ctx, PRSGD_EINVAL, "m does not match the parameter count");
   if (worker < 0 || worker >= ctx->cfg.n_workers) return set_err(ctx, PRSGD_EINVAL, "worker out of range");
   if (ctx->velocity() == nullptr) return set_err(ctx, PRSGD_ESTATE, "the context has no momentum buffers");
-  const int arc = check_fused2_abort(ctx);
+  const int arc = check_gave_up(ctx);
   if (arc != PRSGD_OK) return arc;
   hipError_t e = hipMemcpyAsync(ctx->host_pad, ctx->velocity() + (size_t)worker * ctx->lo.m_pad,
                                 sizeof(float) * (size_t)ctx->lo.m_pad, hipMemcpyDeviceToHost, ctx->stream);
@@ -1179,7 +1325,7 @@ int prsgd_write_velocity(prsgd_ctx* ctx, int32_t worker, const float* in_host, s
 int prsgd_read_loss(prsgd_ctx* ctx, float* out_host) {
   if (ctx == nullptr) return PRSGD_EINVAL;
   if (out_host == nullptr) return set_err(ctx, PRSGD_EINVAL, "out_host is null");
-  const int arc = check_fused2_abort(ctx);
+  const int arc = check_gave_up(ctx);
   if (arc != PRSGD_OK) return arc;
   hipError_t e = hipSuccess;
   if (ctx->cfg.model == PRSGD_MLP)
@@ -1196,7 +1342,7 @@ int prsgd_read_loss(prsgd_ctx* ctx, float* out_host) {
 int prsgd_read_indices(prsgd_ctx* ctx, int32_t* out_host) {
   if (ctx == nullptr) return PRSGD_EINVAL;
   if (out_host == nullptr) return set_err(ctx, PRSGD_EINVAL, "out_host is null");
-  const int arc = check_fused2_abort(ctx);
+  const int arc = check_gave_up(ctx);
   if (arc != PRSGD_OK) return arc;
   const size_t bytes = sizeof(int32_t) * (size_t)ctx->cfg.n_workers * ctx->cfg.batch;
   // the layer-wise MLP path alternates between two buffer sets; the others only use the first
@@ -1262,7 +1408,7 @@ int prsgd_streamed_uses(const prsgd_config* cfg) {
 
 int prsgd_status(prsgd_ctx* ctx) {
   if (ctx == nullptr) return PRSGD_EINVAL;
-  const int arc = check_fused2_abort(ctx);
+  const int arc = check_gave_up(ctx);
   if (arc != PRSGD_OK) return arc;
   const hipError_t e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "prsgd_status");

@@ -187,11 +187,26 @@ hipError_t launch_fill_zero(float* x, size_t count, hipStream_t s);
 hipError_t launch_update_masked(float* x, const float* g, uint16_t* shadow, long m_pad, int n_workers,
                                 float lr, const int* worker_steps, int step, hipStream_t s);
 
-hipError_t launch_lsq_steps(const float* features, const float* targets, const float* src,
-                            long src_stride, float* params, float* velocity, float mu, float* losses,
-                            int32_t* idx, int n_workers, int d, long m_pad, long rows, int batch,
-                            float lr, uint64_t seed, int64_t t0, int k, const int* worker_steps,
-                            hipStream_t s);
+// Least squares: k local iterations of every worker (kernels_lsq.hip).
+struct LsqArgs {
+  const float* features; const float* targets;
+  const float* src; long src_stride;     // starting points: the replicas, or the shared node average (stride 0)
+  float* params; float* velocity; float mu; long m_pad;
+  float* losses; int32_t* idx;
+  int n_workers, d; long rows; int log2n; int batch;    // log2n is filled in by the launcher
+  float lr; uint64_t seed, t0; int k;
+  const int* worker_steps;               // Algorithm 3 step counts (nullptr: every worker takes k steps)
+  int interval;                          // > 0: restarts inside the launch (lsq_restarts_in_launch)
+  unsigned long long* exchange;          // [2][N][d] published points with the number of their restart
+  unsigned int* sync;                    // restarts published so far
+  unsigned int* abort_flag;
+  unsigned int spin_limit;               // polls before a workgroup gives up
+};
+constexpr int kLsqMaxTeam = 64;          // workgroups that wait for each other: a quarter of the compute units
+constexpr long kLsqMaxExchange = 32768;  // floats that everybody reads at a restart (64 workers of 512: 6 us)
+bool lsq_restarts_in_launch(int n_workers, int d, int batch);
+size_t lsq_exchange_bytes(int n_workers, int d);
+hipError_t launch_lsq_steps(LsqArgs p, hipStream_t s);
 
 // ---- small device helpers ------------------------------------------------------------------
 // Round to nearest even on the conversion instruction (two values per v_cvt_pk_bf16_f32; a NaN stays a
@@ -257,7 +272,22 @@ __device__ __forceinline__ void load_to_lds(const void* base_any, uint32_t lane_
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
 }
-// Such a tile cannot be padded on its way, so bank conflicts are avoided by permuting WHICH 16 bytes a lane
+// The same with 4 bytes per lane: any alignment of the source, 256 consecutive bytes of LDS.
+__device__ __forceinline__ void load_dword_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
+  const uint64_t u = (uint64_t)(uintptr_t)base_any;
+  const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)u) |
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32);
+  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+}
+// 64 x 16 bytes from an address of every lane's own.
+__device__ __forceinline__ void load_x4_to_lds(uint64_t lane_addr, uint32_t lds_any) {
+  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :: "s"(lds_off), "v"(lane_addr) : "memory");
+}
+// A tile of 16-byte pieces cannot be padded on its way, so bank conflicts are avoided by permuting WHICH 16 bytes a lane
 // requests.  [c][row], contraction index c the LDS row of ROW_BYTES: the transpose read takes 64 bytes of
 // four consecutive c at a time, so the 64-byte segments of row c are exchanged (segment s at s ^ lds_seg_xor(c))
 // such that the four fall on different banks.
