@@ -240,8 +240,8 @@ int64_t prsgd_iteration(const prsgd_ctx* ctx);            /* < 0 on a null conte
 /*
  * Synchronises the stream and reports whether every launch so far ran to completion.
  * Some launches have workgroups that wait for each other inside the kernel, which needs all of them
- * resident at once: whole epochs of one-hidden-layer fp32 MLPs, and prsgd_run on small least-squares
- * problems (N <= 64, d <= 512, B <= 64), whose restarts are exchanges inside the launch.  That holds on a
+ * resident at once: whole epochs of one-hidden-layer fp32 MLPs, and prsgd_run on those and on small
+ * least-squares problems (N <= 64, d <= 512, B <= 64), whose restarts are exchanges inside the launch.  That holds on a
  * device that runs nothing else (checked at prsgd_init) -- keep the device otherwise idle while such a
  * context is stepping; prsgd_run looks after the process's own contexts: restarts are launches of their own where
  * contexts of other streams could hold the compute units that a launch waits for, and in a stream that is being

@@ -1,22 +1,45 @@
-// One launch = a whole epoch of local iterations (Algorithm 1, eq. 3) for small fp32 MLPs with
-// one hidden layer, the latency-bound regime where a chain of per-layer kernels is dominated
+// One launch = a whole epoch of local iterations (Algorithm 1, eq. 3), or a whole run with its restarts, for small
+// fp32 MLPs with one hidden layer, the latency-bound regime where a chain of per-layer kernels is dominated
 // by launch gaps and by re-reading weights that would fit on chip.
 //
 // Workers never exchange anything inside an epoch (paragraph below Algorithm 1), so the only
 // coupling is inside one worker's own forward/backward pass.  Worker i is served by a TEAM of P
-// workgroups; workgroup j of the team owns W = d_1 / P hidden units:
+// workgroups; workgroup j of the team owns the W hidden units from j W on:
 //   - its [d_0][W] slice of W_1 lives in REGISTERS for the whole launch, laid out so that the
 //     MFMA B-operand registers of the forward product are, element for element, the accumulator
 //     registers of the weight-gradient product: eq. (3) for W_1 is a register-to-register fma;
 //   - its slices of b_1 and W_2 (and a private copy of b_2) live in LDS;
-//   - per iteration it computes its slice of the hidden layer on the minibatch held in LDS and
-//     contributes a partial logit block; the next iteration's rows are drawn meanwhile and, for
-//     shapes with registers to spare, gathered (HBM -> registers) meanwhile as well -- otherwise
-//     at the end of the iteration, with loads that write LDS directly.  One team-wide barrier per iteration
-//     (a counter in HBM, bounded spin) lets every member sum the P partials in fixed order;
-//     everything after that (softmax, both delta blocks, dW_2, db, dW_1) is local to the slice.
-// Teams of different workers never synchronise.  Summation orders are fixed, so a run is
-// bit-reproducible.
+//   - a wavefront owns pairs of 16-row blocks of the slice, and with them the 32 columns of the minibatch in
+//     LDS that the forward and the weight-gradient product of those rows read: nobody else touches
+//     them, so the wavefront requests the next minibatch into their place as soon as it has multiplied them, and waits
+//     for nothing but its own requests before the next forward product;
+//   - one exchange per iteration: every member publishes its partial logits, each float with the iteration's number in one
+//     8-byte store, and polls the others' data itself (no arrival counter, no second trip for the data),
+//     summing the P partials in fixed order; everything after that (softmax, both delta blocks, dW_2, db, dW_1)
+//     is local to the slice.  Two sets of slots alternate: a member can only publish iteration t + 2 after
+//     everybody has read iteration t.
+// The last wavefront draws the rows of the iteration after the next while the others wait for the exchange, and touches one
+// word per line of the member's share of them, so that the requests of all members find them in the L2.
+// Teams of different workers meet only at a restart.  Summation orders are fixed, so a run is bit-reproducible.
+//
+// Restarts (`interval` > 0): after every iteration whose number is a multiple of the interval, but the last of
+// the call, every workgroup writes its slice into the replicas, all workgroups of the grid together take the node average (each
+// a range of the parameters, in the order of the restart kernels) and load their slices of it: two grid-wide
+// meetings over one flag per workgroup, each polled by one wavefront.
+//
+// Every wait is bounded; giving up raises the abort flag, which ends every workgroup.
+//
+// What bounds it: latency.  Of the 24,000 cycles of an iteration of 784-256-10 (8 workers, 32 rows) the exchange takes 6,800, the
+// two large products 5,700 each (3,500 at the matrix cores' rate; two wavefronts per SIMD, 7 blocks on the busiest), the requests of
+// the next minibatch 2,500, the small phases 900 to 1,400 each.  Per iteration, against an arrival counter, partials and minibatch as
+// loads of their own and a launch per epoch (widths that are no multiple of 16, or of 4 for the input: against the
+// chain of per-layer launches): 784-256-10 with interval 16 12.3 and 11.3 us, 64 workers of 256-128-10 with
+// 8 rows, interval 8, 7.8 and 7.2 us, 4 workers of 300-100-10, 20 rows, interval 4, 26.6 and 8.9 us, 30 workers of
+// 1023-255-15, 30 rows, 46.7 and 25.6 us.  A restart inside the launch takes 7 us with 0.5 MB of replicas and 14 us
+// with 9 MB (the agent-scope traffic of all workgroups), 3 to 5 us less than the end of a launch, the averaging launch and a new
+// start.
+#include <type_traits>
+
 #include "prsgd_internal.h"
 
 namespace prsgd {
@@ -26,7 +49,11 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTT = 512;                      // threads per team member: two wavefronts per SIMD, so
 constexpr int kTW = kTT / kWave;              // that the latency-bound phases of one overlap the other's
-constexpr int kAgentScope = 16;               // buffer-load cache policy: the sc1 bit (agent scope)
+constexpr int kPollers = kTT - kWave;         // threads that sum the partial logits: all but the drawing wavefront
+// Partial logits of a team from which they are summed in two hops: 16 x 320 floats 9,200 cycles in one, 6,800 in two; with 4 x 80 one
+// takes 3,000, which a second would double.
+constexpr int kTwoHopFloats = 2048;
+constexpr int kAgentScope = 16;               // buffer access cache policy: the sc1 bit (agent scope)
 
 __device__ __forceinline__ f32x4_t mfma16(float a, float b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -55,219 +82,414 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_move<0x141>(v);
   return v + dpp_move<0x140>(v);
 }
+__device__ __forceinline__ float agent_load(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool gave_up(unsigned int* abort_flag, unsigned& polls, unsigned limit) {
+  if (++polls <= limit &&
+      ((polls & 15) != 0 || __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0))
+    return false;
+  __hip_atomic_store(abort_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
 
 // KBI: 16-row blocks of W_1 per wavefront (register budget); NT: 16-column tiles of the hidden
-// slice; MT: 16-row tiles of the minibatch.  MOM: momentum form of the local update
+// slice; MT: 16-row tiles of the minibatch; CT: 16-column tiles of the classes.  MOM: momentum form of the local update
 // (v <- mu v + G, x <- x - gamma v) with the velocity of the slice held next to the slice.
-template <int KBI, int NT, int MT, bool MOM>
+template <int KBI, int NT, int MT, int CT, bool MOM>
 __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
-  constexpr int W = NT * 16, MR = MT * 16;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int W = NT * 16, MR = MT * 16, D2P = CT * 16;
+  constexpr int XB = MR * 32;                              // floats of a pair of 16-column blocks of the minibatch
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int n16 = lane & 15, q4 = lane >> 4;
 
-  // team mapping: consecutive workgroups go round-robin to the 8 XCDs; keep a team on one XCD
-  // (its partial logits then stay in that XCD's L2) when the worker count allows it
-  int i, j;
-  if ((p.n_workers & 7) == 0) {
-    const int slot = blockIdx.x >> 3;
-    i = (blockIdx.x & 7) + 8 * (slot / p.P);
-    j = slot % p.P;
-  } else {
-    i = blockIdx.x / p.P;
-    j = blockIdx.x % p.P;
-  }
+  // team mapping: consecutive workgroups go round-robin to the 8 XCDs; a team stays on one XCD (its
+  // partial logits and the members' minibatch then stay in that XCD's L2).  The grid is filled up to whole rounds.
+  const int slot = blockIdx.x >> 3;
+  const int i = (blockIdx.x & 7) + 8 * (slot / p.P), j = slot % p.P;
+  if (i >= p.n_workers) return;
   const int my_k = p.worker_steps != nullptr ? min(p.worker_steps[i], p.k) : p.k;
   if (my_k <= 0) return;                                   // uniform over the team
-  unsigned int* cnt = p.sync + (size_t)i * 32;             // one 128-byte line per team
+  const int members = p.n_workers * p.P, me = i * p.P + j;
+  unsigned int* base_slot = p.sync + (size_t)i * 32 + 1;   // one 128-byte line per team
   unsigned int* abort_flag = p.sync + (size_t)p.n_workers * 32;
-  unsigned int* base_slot = cnt + 1;
+  unsigned int* restart_base = abort_flag + 1;
+  const int flag_stride = fused2_flag_stride(members);
+  unsigned char* flags = reinterpret_cast<unsigned char*>(p.sync + (size_t)(p.n_workers + 1) * 32);   // [2][8][flag_stride]
   if (__hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-  const unsigned base = *base_slot;                        // arrivals counted before this launch
+  const unsigned base = *base_slot;                        // iterations exchanged before this launch
+  unsigned restarts = p.interval > 0 ? *restart_base : 0;  // ... and restarts
 
-  const int d0 = p.d0, d2 = p.d2, B = p.batch, D2P = p.d2p, ldx = p.ldx;
-  const int KB = (d0 + 15) / 16;
+  const int d0 = p.d0, d1 = p.d1, d2 = p.d2, B = p.batch;
+  const int KB = (d0 + 15) / 16, pairs = (KB + 1) / 2;
+  // row block kbi of this wavefront: blocks come in pairs, 128 bytes of a row of the minibatch
+  auto block = [&](int kbi) __attribute__((always_inline)) { return 2 * (wave + kTW * (kbi >> 1)) + (kbi & 1); };
+  const bool rows_x4 = (d0 & 3) == 0;                      // rows of the shard start 16-byte aligned
 
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  float* X = lds;                                          // [MR][ldx]   gathered rows
-  float* red = X + (size_t)MR * ldx;                       // [kTW][MR][W] per-wavefront partial z_1
-  float* h = red + kTW * MR * W;                           // [MR][W]
+  float* X = lds;                                          // [pairs][MR][32]  gathered rows in pairs of column blocks
+  float* red = X + (size_t)pairs * XB;                     // [shares][MR][W] partial z_1: one per wavefront, or per two
+  const int shares = p.shares;
+  float* h = red + shares * MR * W;                        // [MR][W]
   float* dl1 = h + MR * W;                                 // [MR][W]
-  float* lg = dl1 + MR * W;                                // [MR][D2P]   logits, then delta_2
+  float* lg = dl1 + MR * W;                                // [MR][D2P]   delta_2
   float* w2 = lg + MR * D2P;                               // [W][D2P]
   float* b1 = w2 + W * D2P;                                // [W]
   float* b2 = b1 + W;                                      // [D2P]
-  int* rows = reinterpret_cast<int*>(b2 + D2P);            // [MR] rows of this iteration
-  int* ylab = rows + MR;                                   // [MR] their labels
-  int* rows_ahead = ylab + MR;                             // [2][MR] rows of iteration t at [t & 1], drawn early
-  int* flag = rows_ahead + 2 * MR;                         // [4] abort broadcast
-  float* vw2 = reinterpret_cast<float*>(flag + 4);         // [W][D2P] velocities (MOM only)
+  int* rows = reinterpret_cast<int*>(b2 + D2P);            // [2][MR] rows of iteration t at [t & 1]
+  int* ylab = rows + 2 * MR;                               // [2][MR] their labels
+  int* flag = ylab + 2 * MR;                               // [4] abort broadcast
+  float* dump = reinterpret_cast<float*>(flag + 4);        // [64] what the line-touching loads bring
+  float* vw2 = dump + kWave;                               // [W][D2P] velocities (MOM only)
   float* vb1 = vw2 + W * D2P;                              // [W]
   float* vb2 = vb1 + W;                                    // [D2P]
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)lds;
 
-  float* prm = p.params + (size_t)i * p.m_pad;
-  const float* prm0 = p.src + (size_t)i * p.src_stride;      // this worker's starting point
   const float* feat = p.features + (size_t)i * p.rows * d0;
-  const int32_t* lab = p.labels + (size_t)i * p.rows;
-
-  // Rows of the first iteration first: their features, their labels and the parameter slice are
-  // then requested together, so that the launch pays one memory latency instead of three.
-  int row_first = 0;
-  if (tid < B) {
-    row_first = sample_row(p.seed, (uint32_t)i, p.t0 + 1, (uint32_t)tid, p.log2n);
-    rows[tid] = row_first;
-  }
-  for (int e = tid; e < MR * ldx; e += kTT) X[e] = 0.0f;     // pad rows / columns stay zero
-  if (tid == 0) flag[0] = 0;
-  __syncthreads();
-
+  // Arguments that only the ends of the launch, the restarts and the drawing wavefront need: loaded where they are used, so
+  // that the scalar registers are left to the iterations.
+  auto cold = []() __attribute__((always_inline)) {
+    auto* k = (const __attribute__((address_space(4))) Fused2Args*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return k;
+  };
   const float inv_b = 1.0f / (float)B;
-  const size_t part_team = (size_t)MR * D2P;                      // floats per (team member)
   bool aborted = false;
 
-  // ---- minibatch pipeline ----------------------------------------------------------------------
-  // The index stream is a pure function of (seed, worker, iteration, slot): the rows of iteration
-  // s+1 are drawn at the start of iteration s and their features travel HBM -> registers while
-  // iteration s computes; they are written to LDS once X is no longer read.  A thread owns the
-  // 16-byte column pc of rows rg, rg + ng, rg + 2 ng, ... (a row is at most 256 vectors wide).
-  // Rows B .. MR-1 of X receive a copy of the first drawn row: finite values that only ever meet
-  // zero deltas.
-  // PF vectors per thread make up a minibatch and are requested an iteration early; 0 = no
-  // prefetch, for the shapes whose W_1 slice leaves no registers for it (measured on 784-256-10,
-  // seven row blocks per wavefront: 200 us per 16-iteration launch without, 219 us with)
-  constexpr int PF = (MT > 2 || KBI * NT > 4) ? 0 : 8 * MT;
-  const int v4 = d0 >> 2, total4 = B * v4;
-  int cw_log = 5;                                          // ng <= 16 divides MR
-  while ((1 << cw_log) < v4) ++cw_log;
-  const int pc = tid & ((1 << cw_log) - 1), ng = kTT >> cw_log;
-  const bool pc_ok = pc < v4;
-  int rg = tid >> cw_log;
-  f32x4_t pre[PF > 0 ? PF : 1];
-  auto gather_issue = [&](const int* rws) {
-    // opaque copy: keeps the per-vector addresses and predicates from being hoisted out of the
-    // iteration loop into (spilled) registers
-    asm volatile("" : "+v"(rg));
-    const float* src = feat + (pc_ok ? 4 * pc : 0);
+  // ---- minibatch ----------------------------------------------------------------------------------
+  // Element (row r, column 32 i + c) stands at X[i][r][..] with the eight 4-column chunks of a row exchanged
+  // by r / 2, so that the 16 rows of a forward fragment and the elements of a gradient fragment fall on
+  // different banks.  Columns from d_0 on stay zero.
+  auto x_chunk = [&](int r, int q) { return q ^ ((r >> 1) & 7); };
+  // Requests of the rows in `rws`: where this lane's pieces of a row start (16-byte pieces; rows that are not 16-byte
+  // aligned go by single words), and one pair of blocks of them.  A compute unit has about a hundred lines under way:
+  // 64-byte pieces (single blocks) took twice as long.
+  struct RowStarts { uint64_t at[MT * 2]; const int* rws; };
+  auto row_starts = [&](const int* rws) __attribute__((always_inline)) {
+    RowStarts rs;
+    rs.rws = rws;
 #pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      if (ng * u < B) {                                    // uniform over the workgroup
-        const int r = rg + ng * u;
-        pre[u] = *reinterpret_cast<const f32x4_t*>(src + (size_t)rws[r < B ? r : 0] * d0);
+    for (int g = 0; g < MT * 2; ++g) {
+      const int r = g * 8 + (lane >> 3);
+      rs.at[g] = (uint64_t)(uintptr_t)(feat + (size_t)(uint32_t)rws[min(r, B - 1)] * d0 + 4 * x_chunk(r, lane & 7));
+    }
+    return rs;
+  };
+  auto request_pair = [&](const RowStarts& rs, int pi) __attribute__((always_inline)) {
+    if (rows_x4 && 32 * pi + 32 <= d0) {                   // whole pairs, with copies of the last row behind it (zero deltas)
+#pragma unroll
+      for (int g = 0; g < MT * 2; ++g)
+        load_x4_to_lds(rs.at[g] + (uint32_t)(128 * pi), lds0 + (uint32_t)(pi * XB + g * 256) * 4u);
+    } else if (rows_x4) {
+#pragma unroll 1
+      for (int g = 0; g < MT * 2; ++g) {
+        const int r = g * 8 + (lane >> 3), c = 32 * pi + 4 * x_chunk(r, lane & 7);
+        if (c < d0)
+          load_x4_to_lds((uint64_t)(uintptr_t)(feat + (size_t)(uint32_t)rs.rws[min(r, B - 1)] * d0 + c),
+                         lds0 + (uint32_t)(pi * XB + g * 256) * 4u);
+      }
+    } else {
+#pragma unroll 1
+      for (int g = 0; g < MT * 8; ++g) {
+        const int r = 2 * g + (lane >> 5), c = 32 * pi + 4 * x_chunk(r, (lane >> 2) & 7) + (lane & 3);
+        if (c < d0)
+          load_lane_dword_to_lds((uint64_t)(uintptr_t)(feat + (size_t)(uint32_t)rs.rws[min(r, B - 1)] * d0 + c),
+                                 lds0 + (uint32_t)(pi * XB + g * 64) * 4u);
       }
     }
   };
-  auto gather_store = [&]() {
-    asm volatile("" : "+v"(rg));
-    if (pc_ok) {
-      float* dst = X + (size_t)rg * ldx + 4 * pc;
-      const int step = ng * ldx;
-#pragma unroll
-      for (int u = 0; u < PF; ++u) {
-        if (ng * u < B) *reinterpret_cast<f32x4_t*>(dst) = pre[u];
-        dst += step;
-      }
+  // one word per 128-byte line of this member's share of the rows that the lanes of this wavefront hold
+  const int lines = (d0 * 4 + 127) / 128 + 1;              // a row need not start on a line
+  auto touch_lines = [&](int row_of_lane) __attribute__((always_inline)) {
+    for (int e0 = 0; e0 * p.P < B * lines; e0 += kWave) {
+      const int e = (e0 + lane) * p.P + j;
+      const int r = min(e / lines, B - 1), l = e - (e / lines) * lines;
+      const int row = __shfl(row_of_lane, r);
+      if (e < B * lines)
+        load_lane_dword_to_lds((uint64_t)(uintptr_t)(feat + (size_t)(uint32_t)row * d0 + min(32 * l, d0 - 1)),
+                               lds0 + (uint32_t)((dump - lds) * 4));
     }
-  };
-  // Gather without the register stage (shapes whose minibatch does not fit the register budget):
-  // loads that write LDS directly, one instruction per 64 consecutive 16-byte vectors of a row
-  // (the lanes' data lands at consecutive LDS addresses from a wavefront-uniform base), so the
-  // whole minibatch is in flight at once at no register cost.
-  auto gather_direct = [&]() {
-    typedef const __attribute__((address_space(1))) void* gptr_t;
-    typedef __attribute__((address_space(3))) void* lptr_t;
-    const int cpr = (v4 + 63) >> 6;                        // 64-vector chunks per row
-    for (int t = wave; t < B * cpr; t += kTW) {
-      const int r = t / cpr, ch = t - r * cpr;
-      const int c = 64 * ch + lane;
-      const int lds_off = __builtin_amdgcn_readfirstlane(r * ldx + 256 * ch);
-      if (c < v4)
-        __builtin_amdgcn_global_load_lds((gptr_t)(feat + (size_t)rows[r] * d0 + 4 * c), (lptr_t)(X + lds_off),
-                                         16, 0, 0);
-    }
-  };
-  auto gather_direct_wait = [&]() {                        // the data is in LDS before the next barrier
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   };
 
-  // labels and features of the first iteration, requested before the parameter slice
-  int lab_first = 0;
-  if (tid < B) lab_first = lab[row_first];
-  if constexpr (PF > 0) gather_issue(rows); else gather_direct();
-  // ---- load the slice: W_1 to registers, W_2 / b_1 / b_2 to LDS -------------------------------
+  // ---- the slice: W_1 in registers, W_2 / b_1 / b_2 in LDS ----------------------------------------
   float w1[KBI][NT][4];
+  // Walks the slice of W_1 in register order: f(register, byte offset in a replica, exists).  The lane indices are made opaque,
+  // so that no addresses or masks of the slice are kept in registers through the iterations.
+  auto each_w1 = [&](auto&& f) __attribute__((always_inline)) {
+    const auto* k = cold();
+    int nn = n16, qq = q4;
+    asm volatile("" : "+v"(nn), "+v"(qq));
+    const int ld1 = k->ld1;
+    const uint32_t first = 4u * (uint32_t)(k->w1_off + (long)(32 * wave + 4 * qq) * ld1 + j * W + nn);
 #pragma unroll
-  for (int kbi = 0; kbi < KBI; ++kbi) {
-    const int kb = wave + kTW * kbi;
+    for (int kbi = 0; kbi < KBI; ++kbi)
+      if (block(kbi) < KB) {                               // uniform
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = 16 * kb + 4 * q4 + s;
-        const bool ok = kb < KB && k < d0;
-        const float v = prm0[p.w1_off + (ok ? (size_t)k * p.ld1 + j * W + nt * 16 + n16 : (size_t)0)];
-        w1[kbi][nt][s] = ok ? v : 0.0f;
+          for (int q = 0; q < 4; ++q)
+            f(kbi, nt, q, first + 4u * (uint32_t)((32 * kTW * (kbi >> 1) + 16 * (kbi & 1) + q) * ld1 + nt * 16),
+              16 * block(kbi) + 4 * qq + q < d0 && j * W + nt * 16 + nn < d1);
       }
-  }
-  for (int e = tid; e < W * D2P; e += kTT) {
-    const int n = e / D2P, c = e % D2P;
-    w2[e] = c < d2 ? prm0[p.w2_off + (size_t)(j * W + n) * p.ld2 + c] : 0.0f;
-  }
-  if (tid < W) b1[tid] = prm0[p.b1_off + j * W + tid];
-  if (tid < D2P) b2[tid] = tid < d2 ? prm0[p.b2_off + tid] : 0.0f;
-  // velocity of the slice, same places
-  float* vel = MOM ? p.vel + (size_t)i * p.m_pad : nullptr;
-  float vw1[MOM ? KBI : 1][NT][4];
-  if constexpr (MOM) {
+  };
+  auto at = [](auto* base, uint32_t bytes) __attribute__((always_inline)) {
+    typedef std::remove_pointer_t<decltype(base)> F;
+    typedef std::conditional_t<std::is_const_v<F>, const char, char> C;
+    return reinterpret_cast<F*>(reinterpret_cast<C*>(base) + bytes);
+  };
+  auto zero_w = [&](float (&w)[KBI][NT][4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kbi = 0; kbi < KBI; ++kbi) {
-      const int kb = wave + kTW * kbi;
+    for (int kbi = 0; kbi < KBI; ++kbi)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = 16 * kb + 4 * q4 + q;
-          const bool ok = kb < KB && k < d0;
-          const float v = vel[p.w1_off + (ok ? (size_t)k * p.ld1 + j * W + nt * 16 + n16 : (size_t)0)];
-          vw1[kbi][nt][q] = ok ? v : 0.0f;
-        }
+        for (int q = 0; q < 4; ++q) w[kbi][nt][q] = 0.0f;
+  };
+  // between LDS and a replica: f(LDS element of W_2 / b_1 / b_2, byte offset in a replica, exists)
+  auto each_small = [&](float* lw2, float* lb1, float* lb2, auto&& f) __attribute__((always_inline)) {
+    const auto* k = cold();
+#pragma unroll
+    for (int u = 0; u < (W * D2P + kTT - 1) / kTT; ++u) {
+      const int e = tid + u * kTT, n = e / D2P, c = e % D2P;
+      if ((W * D2P) % kTT == 0 || e < W * D2P)
+        f(lw2[e], (uint32_t)(4 * (k->w2_off + (long)(j * W + n) * k->ld2 + c)), c < d2 && j * W + n < d1);
     }
-    for (int e = tid; e < W * D2P; e += kTT) {
-      const int n = e / D2P, c = e % D2P;
-      vw2[e] = c < d2 ? vel[p.w2_off + (size_t)(j * W + n) * p.ld2 + c] : 0.0f;
-    }
-    if (tid < W) vb1[tid] = vel[p.b1_off + j * W + tid];
-    if (tid < D2P) vb2[tid] = tid < d2 ? vel[p.b2_off + tid] : 0.0f;
+    if (tid < W) f(lb1[tid], (uint32_t)(4 * (k->b1_off + j * W + tid)), j * W + tid < d1);
+    if (tid < D2P) f(lb2[tid], (uint32_t)(4 * (k->b2_off + tid)), tid < d2);
+  };
+  auto draw = [&](int s, int slot_of_batch) __attribute__((always_inline)) {      // row of iteration s of this call
+    const auto* k = cold();
+    return sample_row(k->seed, (uint32_t)i, k->t0 + (uint64_t)s, (uint32_t)min(slot_of_batch, B - 1), k->log2n);
+  };
+  auto label = [&](int row) __attribute__((always_inline)) {
+    const auto* k = cold();
+    return k->labels[(size_t)i * k->rows + row];
+  };
+  // Everything that waits for memory is asked for before the first barrier, the minibatch (whose rows have to be drawn) right
+  // behind it: the launch pays one latency instead of four.
+  zero_w(w1);
+  {
+    const auto* k = cold();
+    const float* src = k->src + (size_t)i * k->src_stride; // this worker's starting point
+    each_w1([&](int kbi, int nt, int q, uint32_t off, bool ok) __attribute__((always_inline)) {
+      if (ok) w1[kbi][nt][q] = *at(src, off);
+    });
+    each_small(w2, b1, b2, [&](float& l, uint32_t off, bool ok) __attribute__((always_inline)) { l = ok ? *at(src, off) : 0.0f; });
   }
-  if (tid < B) ylab[tid] = lab_first;
-  if constexpr (PF > 0) gather_store(); else gather_direct_wait();
-  // rows and labels of the second iteration (the pipeline runs one iteration ahead)
+  float vw1[MOM ? KBI : 1][NT][4];
+  if constexpr (MOM) {
+    const float* vel = cold()->vel + (size_t)i * cold()->m_pad;
+    zero_w(vw1);
+    each_w1([&](int kbi, int nt, int q, uint32_t off, bool ok) __attribute__((always_inline)) {
+      if (ok) vw1[kbi][nt][q] = *at(vel, off);
+    });
+    each_small(vw2, vb1, vb2, [&](float& l, uint32_t off, bool ok) __attribute__((always_inline)) { l = ok ? *at(vel, off) : 0.0f; });
+  }
+  if (tid < B) rows[MR + tid] = draw(1, tid);
+  for (int pi = wave; pi < pairs; pi += kTW)               // this wavefront's blocks
+    for (int e = lane; e < XB / 4; e += kWave)
+      reinterpret_cast<f32x4_t*>(X + (size_t)pi * XB)[e] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  if (tid == 0) flag[0] = 0;
+  lds_barrier();
+  {
+    const RowStarts rs = row_starts(rows + MR);
+    for (int pi = wave; pi < pairs; pi += kTW) request_pair(rs, pi);
+  }
+
+  // Rows of iteration t + 1 and labels of iteration t, by the lanes of the last wavefront: the row at which a label is read is
+  // drawn an iteration before the label is stored.
+  const bool drawer = wave == kTW - 1;
   int lab_next = 0;
-  if (PF > 0 && my_k > 1 && tid < B) {
-    const int r = sample_row(p.seed, (uint32_t)i, p.t0 + 2, (uint32_t)tid, p.log2n);
-    rows_ahead[tid] = r;                                   // iteration 2 of this call: slot 0
-    lab_next = lab[r];
+  if (drawer) {
+    const int r1 = rows[MR + min(lane, B - 1)], r2 = draw(2, lane);
+    if (lane < B) {
+      ylab[MR + lane] = label(r1);
+      rows[lane] = r2;
+      lab_next = label(r2);
+    }
+    touch_lines(r2);
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the blocks of iteration 1 have landed
   __syncthreads();
 
-  // partial-logit exchange: Q 16-byte vectors per member; G groups of members are summed in
-  // parallel (group g = members [g * PG, (g+1) * PG) in order), then the groups in order
-  const int Q = MR * D2P / 4;
-  const int G = Q < kTT ? kTT / Q : 1;
+  // ---- restart: x_i <- (1/N) sum_i x_i --------------------------------------------------------------
+  // Meeting of the whole grid; false: given up.  Everything stored before it is visible to the agent-scope loads after it.
+  // Nobody can be a meeting ahead of those that still look for this one's flags, so a flag is the low byte of the
+  // meeting's number, and a wavefront sees 256 of them in one load.  Every XCD looks at a copy of its own.
+  auto meet = [&](unsigned char* fl, unsigned number) -> bool {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid < 8)
+      __hip_atomic_store(fl + tid * flag_stride + me, (unsigned char)number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wave == 0) {
+      unsigned tries = 0;
+      const unsigned* words = reinterpret_cast<const unsigned*>(fl + (blockIdx.x & 7) * flag_stride);
+      const unsigned want = (number & 255u) * 0x01010101u;
+      for (int w0 = 0; 4 * w0 < members; w0 += kWave) {
+        const int w = w0 + lane, live = min(4, members - 4 * w);           // flags of this lane's word
+        const unsigned mask = live >= 4 ? ~0u : live > 0 ? (1u << (8 * live)) - 1u : 0u;
+        for (;;) {
+          unsigned v = want;
+          if (live > 0) v = __hip_atomic_load(words + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (__all(((v ^ want) & mask) == 0)) break;
+          if (gave_up(abort_flag, tries, p.spin_limit)) { flag[0] = 1; break; }
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+    }
+    __syncthreads();
+    return flag[0] == 0;
+  };
+  // The slices pass through memory in register order (block kb of tile nt: 1 KB), 16 bytes per lane: as single words in the
+  // layout of the replicas the agent-scope stores alone took 8 us with 256 workgroups.
+  const int blocks4 = KB * NT * kWave;                     // 16-byte vectors of a slice of W_1
+  const int small = W * D2P + W + D2P;                     // floats behind them (a multiple of 4)
+  const int slice4 = blocks4 + small / 4;
+  auto restart = [&]() -> bool {
+    const auto* k = cold();
+    const int n = k->n_workers;
+    f32x4_t* const mine = reinterpret_cast<f32x4_t*>(k->exchange) + (size_t)me * slice4;
+    f32x4_t* const means = reinterpret_cast<f32x4_t*>(k->exchange) + (size_t)members * slice4;    // [P][slice4]
+    auto rsrc = [&](f32x4_t* base) __attribute__((always_inline)) {
+      return __builtin_amdgcn_make_buffer_rsrc(base, 0, slice4 * 16, 0x00020000);
+    };
+    {
+      const __amdgpu_buffer_rsrc_t to = rsrc(mine);
+#pragma unroll
+      for (int kbi = 0; kbi < KBI; ++kbi)
+        if (block(kbi) < KB) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) {
+            const f32x4_t v = {w1[kbi][nt][0], w1[kbi][nt][1], w1[kbi][nt][2], w1[kbi][nt][3]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), to,
+                                                   ((block(kbi) * NT + nt) * kWave + lane) * 16, 0, kAgentScope);
+          }
+        }
+      for (int e = tid; e < small / 4; e += kTT)
+        __builtin_amdgcn_raw_buffer_store_b128(reinterpret_cast<const u32x4_t*>(w2)[e], to, (blocks4 + e) * 16, 0, kAgentScope);
+    }
+    ++restarts;
+    if (!meet(flags, restarts)) return false;
+    // this worker's share of the vectors of slice j, in the order of the restart kernels
+    const int per = (slice4 + n - 1) / n, lo = min(slice4, i * per), hi = min(slice4, lo + per);
+    const bool quarters = n >= 8 && k->m_pad / 4 < 65536;
+    const int n_per = quarters ? (n + 3) / 4 : n;
+    const int split = quarters && n > 16 ? 4 : 1;          // wide sums: a quarter per group of threads
+    const int cols = kTT / split;
+    f32x4_t* part = reinterpret_cast<f32x4_t*>(red);       // [4][cols]
+    const __amdgpu_buffer_rsrc_t out = rsrc(means + (size_t)j * slice4);
+    const __amdgpu_buffer_rsrc_t all = __builtin_amdgcn_make_buffer_rsrc(k->exchange, 0, members * slice4 * 16, 0x00020000);
+    const int first = j * slice4 * 16, stride = p.P * slice4 * 16;
+    for (int c0 = lo; c0 < hi; c0 += cols) {
+      const int q = tid / cols, c = c0 + tid - q * cols;
+      const int i0 = split == 4 ? min(n, q * n_per) : 0, i1 = split == 4 ? min(n, i0 + n_per) : n;
+      f32x4_t total = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f}, sum = total;
+      int left = n_per;
+      bool begun = false;
+      if (c < hi) {
+        for (int r0 = i0; r0 < i1; r0 += 16) {
+          u32x4_t v[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            if (r0 + u < i1)
+              v[u] = __builtin_amdgcn_raw_buffer_load_b128(all, first + c * 16 + (r0 + u) * stride, 0, kAgentScope);
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            if (r0 + u < i1) {
+              sum += __builtin_bit_cast(f32x4_t, v[u]);
+              if (--left == 0) {
+                total = begun ? total + sum : sum;
+                begun = true;
+                sum = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+                left = n_per;
+              }
+            }
+        }
+        if (left != n_per) total = begun ? total + sum : sum;
+      }
+      if (split == 4) {
+        part[tid] = total;
+        __syncthreads();
+        if (q == 0) total = ((total + part[cols + tid]) + part[2 * cols + tid]) + part[3 * cols + tid];
+        __syncthreads();
+      }
+      if (q == 0 && c < hi) {
+        const f32x4_t mean = total / (float)n;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, mean), out, c * 16, 0, kAgentScope);
+      }
+    }
+    if (!meet(flags + 8 * flag_stride, restarts)) return false;
+#pragma unroll
+    for (int kbi = 0; kbi < KBI; ++kbi)
+      if (block(kbi) < KB) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const f32x4_t v = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+              out, ((block(kbi) * NT + nt) * kWave + lane) * 16, 0, kAgentScope));
+#pragma unroll
+          for (int q = 0; q < 4; ++q) w1[kbi][nt][q] = v[q];
+        }
+      }
+    for (int e = tid; e < small / 4; e += kTT)
+      reinterpret_cast<u32x4_t*>(w2)[e] = __builtin_amdgcn_raw_buffer_load_b128(out, (blocks4 + e) * 16, 0, kAgentScope);
+    __syncthreads();
+    return true;
+  };
+  int to_restart = p.interval > 0 ? p.interval - (int)(p.t0 % (uint64_t)p.interval) : 0;
+
+  // Partial-logit exchange: E floats per member.  Small teams: every member reads all P partials, G groups of
+  // members in parallel (group g = members [g PG, (g + 1) PG) in order), then the groups in order.  Large ones (kTwoHopFloats)
+  // in two hops: member j adds the P partials of its share of the floats, publishes the sums, and everybody
+  // reads E sums: 2 E floats per member instead of P E.
+  const int E = B * d2;
+  const bool two_hops = p.P * E >= kTwoHopFloats;
+  const int share = (E + p.P - 1) / p.P, share_lo = min(E, j * share), share_hi = min(E, share_lo + share);
+  const int G = two_hops ? 1 : max(1, min(p.P, kPollers / E));
   const int PG = (p.P + G - 1) / G;
+  // this thread's first float, and the members it adds (with several groups a thread has one float at most)
+  const int item_g = G > 1 ? tid / E : 0, item_e = tid - item_g * E;
+  const bool has_item = !drawer && item_g < G;
+  const int j_lo = item_g * PG, j_hi = min(p.P, j_lo + PG);
+  unsigned polls = 0;
+  // sum of what `from[0]`, `from[stride]`, .. (count) hold once they carry `number`
+  auto polled_sum = [&](const unsigned long long* from, int first, int stride, int count, unsigned number)
+      __attribute__((always_inline)) {
+    float sum = 0.0f;
+    for (int u0 = 0; u0 < count; u0 += 8) {
+      unsigned long long v[8];
+      unsigned missing = (1u << min(8, count - u0)) - 1u;
+      const unsigned asked = missing;
+      for (;;) {                                           // only what is still missing is asked for again
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if ((missing >> u) & 1u)
+            v[u] = __hip_atomic_load(at(from, 8u * (uint32_t)(first + (u0 + u) * stride)), __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (((missing >> u) & 1u) && (unsigned)(v[u] >> 32) == number) missing &= ~(1u << u);
+        if (missing == 0) break;
+        if (gave_up(abort_flag, polls, p.spin_limit)) { flag[0] = 1; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if ((asked >> u) & 1u) sum += __uint_as_float((unsigned)v[u]);
+    }
+    return sum;
+  };
 
   for (int s = 1; s <= my_k; ++s) {
     // opaque copies: LDS addresses built from the lane indices are recomputed every iteration
-    // instead of being hoisted out of the loop into dozens of registers.  Measured: a gain for
-    // the shapes with few row blocks per wavefront; with many row blocks the matrix-instruction
-    // loops are issue-bound and run faster on hoisted addresses.
-    if constexpr (KBI <= 4) asm volatile("" : "+v"(n16), "+v"(q4));
-    // (a) start the features of iteration s+1 (rows drawn one iteration ago) towards the
-    // registers: their issue stalls once the memory pipeline is full, and the matrix products
-    // of the forward slice below do not need that pipeline
-    if constexpr (PF > 0) {
-      if (s < my_k) gather_issue(rows_ahead + ((s + 1) & 1) * MR);
-    }
-    // (c) forward slice: contraction index of MFMA step q is k = 16 kb + 4 q4 + q.  Row blocks
-    // past the last one hold zero weights and re-read the last block, so the loop is branch-free.
+    // instead of being hoisted out of the loop into dozens of registers
+    asm volatile("" : "+v"(n16), "+v"(q4));
+    int nb = KB;                                           // opaque: compared again, not kept as a mask per block
+    asm volatile("" : "+s"(nb));
+    const unsigned number = base + (unsigned)s;
+    // (a) forward slice: contraction index of MFMA step q is k = 16 kb + 4 q4 + q
     {
       f32x4_t acc[MT][NT];
 #pragma unroll
@@ -277,163 +499,163 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
       // the A fragments of row block kbi+1 are read from LDS while block kbi is multiplied; the
       // scheduling fence keeps the compiler from hoisting every block's reads (and their
       // registers) to the top
-      auto load_a = [&](int kbi, f32x4_t (&a)[MT]) {
-        const int kb = min(wave + kTW * kbi, KB - 1);
+      auto load_a = [&](int kbi, f32x4_t (&a)[MT]) __attribute__((always_inline)) {
+        const float* xp = X + (size_t)(wave + kTW * (kbi >> 1)) * XB;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          a[mt] = *reinterpret_cast<const f32x4_t*>(X + (size_t)(mt * 16 + n16) * ldx + 16 * kb + 4 * q4);
+        for (int mt = 0; mt < MT; ++mt) {
+          const int r = mt * 16 + n16;
+          a[mt] = *reinterpret_cast<const f32x4_t*>(xp + r * 32 + 4 * x_chunk(r, 4 * (kbi & 1) + q4));
+        }
       };
       f32x4_t a_cur[MT], a_nxt[MT];
-      load_a(0, a_cur);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) a_cur[mt] = a_nxt[mt] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+      if (block(0) < nb) load_a(0, a_cur);
 #pragma unroll
       for (int kbi = 0; kbi < KBI; ++kbi) {
-        if (kbi + 1 < KBI) load_a(kbi + 1, a_nxt);
+        if (block(kbi) < nb) {                       // uniform
+          if (kbi + 1 < KBI && block(kbi + 1) < nb) load_a(kbi + 1, a_nxt);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma16(a_cur[mt][q], w1[kbi][nt][q], acc[mt][nt]);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) a_cur[mt] = a_nxt[mt];
+        }
+      }
+      auto share_out = [&](bool add) __attribute__((always_inline)) {
+        float* to = red + (size_t)(add ? wave - kTW / 2 : wave) * MR * W;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[mt][nt] = mfma16(a_cur[mt][q], w1[kbi][nt][q], acc[mt][nt]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) a_cur[mt] = a_nxt[mt];
+            for (int v = 0; v < 4; ++v) {
+              float* q = to + (mt * 16 + 4 * q4 + v) * W + nt * 16 + n16;
+              *q = add ? *q + acc[mt][nt][v] : acc[mt][nt][v];
+            }
+      };
+      if (shares == kTW || wave < kTW / 2) share_out(false);
+      if (shares != kTW) {                                 // the upper wavefronts add theirs
+        lds_barrier();
+        if (wave >= kTW / 2) share_out(true);
       }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            red[((size_t)wave * MR + mt * 16 + 4 * q4 + v) * W + nt * 16 + n16] = acc[mt][nt][v];
     }
-    __syncthreads();
+    lds_barrier();
     for (int e = tid; e < MR * W; e += kTT) {
       const int b = e / W, n = e % W;
       float z = b1[n];
 #pragma unroll
-      for (int w = 0; w < kTW; ++w) z += red[w * MR * W + e];          // wavefronts in order
+      for (int w = 0; w < kTW / 2; ++w) z += red[w * MR * W + e];      // shares in order
+      if (shares == kTW) {
+#pragma unroll
+        for (int w = kTW / 2; w < kTW; ++w) z += red[w * MR * W + e];
+      }
       h[e] = b < B ? act2_fwd(z, p.act) : 0.0f;
     }
-    __syncthreads();
-    // (d) this slice's contribution to the logits, one 16 x 16 block per wavefront on the matrix
-    // cores: part[b][c] = sum_n h[b][n] W_2[n][c]  (rows b >= B of h are zero)
-    float* my_part = p.part + (((size_t)(s & 1) * p.n_workers + i) * p.P + j) * part_team;
-    {
-      const int ctiles = D2P >> 4;
-      for (int tile = wave; tile < MT * ctiles; tile += kTW) {
-        const int mt = tile / ctiles, ct = tile - mt * ctiles;
-        f32x4_t g = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+    lds_barrier();
+    // (b) this slice's contribution to the logits, one 16 x 16 block per wavefront on the matrix
+    // cores: part[b][c] = sum_n h[b][n] W_2[n][c]
+    unsigned long long* team_part = p.part + (size_t)((number & 1) * p.n_workers + i) * p.P * E;
+    for (int tile = wave; tile < MT * CT; tile += kTW) {
+      const int mt = tile / CT, ct = tile - mt * CT;
+      f32x4_t g = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int u = 0; u < NT * 4; ++u)
-          g = mfma16(h[(mt * 16 + n16) * W + 4 * u + q4], w2[(4 * u + q4) * D2P + ct * 16 + n16], g);
-        // agent-scope stores: visible to the other compute units without flushing whole caches
+      for (int u = 0; u < NT * 4; ++u)
+        g = mfma16(h[(mt * 16 + n16) * W + 4 * u + q4], w2[(4 * u + q4) * D2P + ct * 16 + n16], g);
+      const int b0 = mt * 16 + 4 * q4, c = ct * 16 + n16;
+      unsigned long long* to = team_part + j * E;
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          __hip_atomic_store(my_part + (mt * 16 + 4 * q4 + v) * D2P + ct * 16 + n16, g[v], __ATOMIC_RELAXED,
+      for (int v = 0; v < 4; ++v)
+        if (b0 + v < B && c < d2)
+          __hip_atomic_store(at(to, 8u * (uint32_t)((b0 + v) * d2 + c)),
+                             ((unsigned long long)number << 32) | __float_as_uint(g[v]), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
-      }
     }
-    // (e) team barrier: arrivals are counted in HBM; the wait is bounded.  The partials were
-    // written with agent-scope stores; draining this wavefront's stores before the workgroup
-    // barrier orders them before the arrival count without a cache-wide release fence.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) {
-      __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned target = base + (unsigned)p.P * (unsigned)s;
-      unsigned spins = 0;
-      int bad = 0;
-      while ((int)(__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-        if (++spins > p.spin_limit ||
-            __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-          __hip_atomic_store(abort_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          bad = 1;
-          break;
+    // (c) sum of the P partial blocks, polled until every float carries this iteration's number
+    float* lgp = red;                                      // [G][E] group sums
+    if (!drawer) {
+      polls = 0;
+      if (two_hops) {
+        unsigned long long* sums = p.part + (size_t)2 * members * E + (size_t)((number & 1) * p.n_workers + i) * E;
+        for (int e = share_lo + tid; e < share_hi; e += kPollers) {
+          const float sum = polled_sum(team_part, e, E, p.P, number);
+          __hip_atomic_store(at(sums, 8u * (uint32_t)e), ((unsigned long long)number << 32) | __float_as_uint(sum),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        __builtin_amdgcn_s_sleep(1);
+        for (int e = tid; e < E; e += kPollers) lgp[e] = polled_sum(sums, e, 0, 1, number);
+      } else if (has_item) {
+        for (int e = item_e; e < E; e += kPollers) {       // one pass when E <= 448
+          lgp[item_g * E + e] = polled_sum(team_part, j_lo * E + e, E, j_hi - j_lo, number);
+          if (G > 1) break;
+        }
       }
-      flag[0] = bad;
+    } else if (s < my_k) {
+      // meanwhile: labels of iteration s + 1 and rows of iteration s + 2
+      const int r = draw(s + 2, lane);
+      if (lane < B) {
+        ylab[((s + 1) & 1) * MR + lane] = lab_next;
+        rows[(s & 1) * MR + lane] = r;
+        lab_next = label(r);
+      }
+      touch_lines(r);
     }
-    __syncthreads();
+    lds_barrier();
     if (flag[0] != 0) { aborted = true; break; }
-    // (f) sum the P partial blocks.  The other members wrote them through to the coherence
-    // point; reading them with agent-scope (sc1) 16-byte buffer loads never returns a copy
-    // cached before the arrivals just observed, and needs no cache-wide invalidate.
+    // (d) logits = b_2 + group sums in order; softmax cross-entropy head, 16 lanes per minibatch
+    // row, lane l holding classes l, l + 16, ...
     {
-      const float* team_part = p.part + (((size_t)(s & 1) * p.n_workers + i) * p.P) * part_team;
-      const __amdgpu_buffer_rsrc_t team_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<float*>(team_part), 0, (int)(p.P * part_team * sizeof(float)), 0x00020000);
-      float* lgp = red;                                    // [G][MR * D2P] group sums
-      for (int w0 = tid; w0 < G * Q; w0 += kTT) {          // one pass when Q <= 512
-        const int g = w0 / Q, q = w0 - g * Q;
-        const int j_lo = g * PG, j_hi = min(p.P, j_lo + PG);
-        f32x4_t sum = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-        for (int j0 = j_lo; j0 < j_hi; j0 += 8) {
-          u32x4_t v[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int jj = j0 + u < j_hi ? j0 + u : j_lo;
-            v[u] = __builtin_amdgcn_raw_buffer_load_b128(
-                team_rsrc, (int)((jj * part_team + 4 * q) * sizeof(float)), 0, kAgentScope);
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-            if (j0 + u < j_hi) sum += __builtin_bit_cast(f32x4_t, v[u]);
-        }
-        *reinterpret_cast<f32x4_t*>(lgp + (size_t)g * MR * D2P + 4 * q) = sum;
-      }
-    }
-    __syncthreads();
-    // logits = b_2 + group sums in order; softmax cross-entropy head, 16 lanes per minibatch
-    // row, lane l holding classes l, l + 16, l + 32, l + 48 (d_2 <= 64)
-    {
-      const float* lgp = red;
       const int l16 = tid & 15;
       for (int b = tid >> 4; b < MR; b += kTT / 16) {
         float* row = lg + b * D2P;
         if (b < B) {
-          float z[4];
+          float z[CT];
           float mx = -INFINITY;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          for (int q = 0; q < CT; ++q) {
             const int c = l16 + 16 * q;
             z[q] = -INFINITY;
             if (c < d2) {
               float sum = b2[c];
-              for (int g = 0; g < G; ++g) sum += lgp[(size_t)g * MR * D2P + b * D2P + c];
+              for (int g = 0; g < G; ++g) sum += lgp[(size_t)g * E + b * d2 + c];
               z[q] = sum;
               mx = fmaxf(mx, sum);
             }
           }
           mx = row16_max(mx);
-          float ex[4];
+          float ex[CT];
           float se = 0.0f;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          for (int q = 0; q < CT; ++q) {
             ex[q] = (l16 + 16 * q < d2) ? expf(z[q] - mx) : 0.0f;
             se += ex[q];
           }
           se = row16_sum(se);
           const float inv_se = __builtin_amdgcn_rcpf(se);    // 1 <= se <= 64; one ulp
-          const int y = ylab[b];
+          const int y = ylab[(s & 1) * MR + b];
           const bool y_ok = y >= 0 && y < d2;               // an out-of-range label selects nothing
           if (j == 0 && l16 == (y_ok ? (y & 15) : 0)) {
             const int yq = y_ok ? (y >> 4) : 0;
-            const float zy = !y_ok ? 0.0f : yq == 0 ? z[0] : yq == 1 ? z[1] : yq == 2 ? z[2] : z[3];
+            float zy = 0.0f;
+#pragma unroll
+            for (int q = 0; q < CT; ++q) zy = y_ok && yq == q ? z[q] : zy;
             p.row_loss[(size_t)i * B + b] = (mx + logf(se)) - zy;
           }
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          for (int q = 0; q < CT; ++q) {
             const int c = l16 + 16 * q;
-            if (c < D2P) row[c] = c < d2 ? (ex[q] * inv_se - (c == y ? 1.0f : 0.0f)) * inv_b : 0.0f;
+            row[c] = c < d2 ? (ex[q] * inv_se - (c == y ? 1.0f : 0.0f)) * inv_b : 0.0f;
           }
         } else {
           for (int c = l16; c < D2P; c += 16) row[c] = 0.0f;
         }
       }
     }
-    __syncthreads();
-    // (g) delta_1 slice (needs the pre-update W_2), then the small updates
+    lds_barrier();
+    // (e) delta_1 slice (needs the pre-update W_2)
     for (int e = tid; e < MR * W; e += kTT) {
       const int b = e / W, n = e % W;
       float sum = 0.0f;
@@ -448,11 +670,11 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
     // dW_2 = h^T delta_2 (one 16 x 16 block per wavefront) and db_2 = column sums of delta_2 (a
     // product with a matrix of ones) on the matrix cores, kept in registers until every read of
     // the old W_2 above is done.  Rows b >= B of delta_2 are zero.
-    const int ctiles2 = D2P >> 4;
-    const bool has_w = wave < NT * ctiles2;                       // NT * ctiles2 <= 8 wavefronts
-    const int nt_w = wave / ctiles2, ct_w = wave - nt_w * ctiles2;
+    static_assert(NT * CT <= kTW, "one block of dW_2 per wavefront");
+    const bool has_w = wave < NT * CT;
+    const int nt_w = wave / CT, ct_w = wave - nt_w * CT;
     const int ct_b = kTW - 1 - wave;                              // db_2 blocks go to the last wavefronts
-    const bool has_b2 = ct_b < ctiles2;
+    const bool has_b2 = ct_b < CT;
     f32x4_t gw = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f}, gb2 = gw;
     if (has_w) {
 #pragma unroll
@@ -463,7 +685,61 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
 #pragma unroll
       for (int u = 0; u < MT * 4; ++u) gb2 = mfma16(1.0f, lg[(4 * u + q4) * D2P + ct_b * 16 + n16], gb2);
     }
-    __syncthreads();
+    lds_barrier();
+    // (f) dW_1 slice and eq. (3) in registers: contraction index of MFMA step u is b = 4u + q4.  A block
+    // that has been multiplied takes the next minibatch.
+    {
+      const RowStarts rs = row_starts(rows + ((s + 1) & 1) * MR);
+      float dfr[MT * 4][NT];
+#pragma unroll
+      for (int u = 0; u < MT * 4; ++u)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) dfr[u][nt] = dl1[(4 * u + q4) * W + nt * 16 + n16];
+      auto load_x = [&](int kbi, float (&a)[MT * 4]) __attribute__((always_inline)) {
+        const float* xp = X + (size_t)(wave + kTW * (kbi >> 1)) * XB;
+#pragma unroll
+        for (int u = 0; u < MT * 4; ++u)
+          a[u] = xp[(4 * u + q4) * 32 + 4 * x_chunk(4 * u + q4, 4 * (kbi & 1) + (n16 >> 2)) + (n16 & 3)];
+      };
+      float x_cur[MT * 4], x_nxt[MT * 4];
+#pragma unroll
+      for (int u = 0; u < MT * 4; ++u) x_cur[u] = x_nxt[u] = 0.0f;
+      if (block(0) < nb) load_x(0, x_cur);
+#pragma unroll
+      for (int kbi = 0; kbi < KBI; ++kbi) {
+        if (block(kbi) < nb) {                       // uniform
+          if (kbi + 1 < KBI && block(kbi + 1) < nb) load_x(kbi + 1, x_nxt);
+          f32x4_t g[NT], g2[NT];                           // two chains: rows 4u of even and of odd u
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) g[nt] = g2[nt] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int u = 0; u < MT * 4; u += 2)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              g[nt] = mfma16(x_cur[u], dfr[u][nt], g[nt]);
+              g2[nt] = mfma16(x_cur[u + 1], dfr[u + 1][nt], g2[nt]);
+            }
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) g[nt] += g2[nt];
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              float gv = g[nt][v];
+              if constexpr (MOM) {
+                gv = fmaf(p.mu, vw1[kbi][nt][v], gv);
+                vw1[kbi][nt][v] = gv;
+              }
+              w1[kbi][nt][v] = fmaf(-p.lr, gv, w1[kbi][nt][v]);
+            }
+          __builtin_amdgcn_sched_barrier(0);               // the products above have taken the pair out of LDS
+          if (s < my_k && ((kbi & 1) != 0 || block(kbi) == nb - 1)) request_pair(rs, wave + kTW * (kbi >> 1));
+#pragma unroll
+          for (int u = 0; u < MT * 4; ++u) x_cur[u] = x_nxt[u];
+        }
+      }
+    }
+    // (g) the small updates; their next readers are behind a barrier of the next iteration
     if (has_w) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
@@ -489,190 +765,143 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
         b1[nt_b * 16 + n16] = fmaf(-p.lr, g, b1[nt_b * 16 + n16]);
       }
     }
-    // (h) dW_1 slice and eq. (3) in registers: contraction index of MFMA step u is b = 4u + q4
-    {
-      float dfr[MT * 4][NT];
-#pragma unroll
-      for (int u = 0; u < MT * 4; ++u)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) dfr[u][nt] = dl1[(4 * u + q4) * W + nt * 16 + n16];
-      auto load_x = [&](int kbi, float (&a)[MT * 4]) {
-        const int kb = min(wave + kTW * kbi, KB - 1);
-#pragma unroll
-        for (int u = 0; u < MT * 4; ++u) a[u] = X[(size_t)(4 * u + q4) * ldx + 16 * kb + n16];
-      };
-      float x_cur[MT * 4], x_nxt[MT * 4];
-      load_x(0, x_cur);
-#pragma unroll
-      for (int kbi = 0; kbi < KBI; ++kbi) {
-        if (kbi + 1 < KBI) load_x(kbi + 1, x_nxt);
-        f32x4_t g[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) g[nt] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int u = 0; u < MT * 4; ++u)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) g[nt] = mfma16(x_cur[u], dfr[u][nt], g[nt]);
-        const bool live = wave + kTW * kbi < KB;           // blocks past the end keep zero weights
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            float gv = g[nt][v];
-            if constexpr (MOM) {
-              gv = live ? fmaf(p.mu, vw1[kbi][nt][v], gv) : 0.0f;
-              vw1[kbi][nt][v] = gv;
-            }
-            w1[kbi][nt][v] = live ? fmaf(-p.lr, gv, w1[kbi][nt][v]) : 0.0f;
-          }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < MT * 4; ++u) x_cur[u] = x_nxt[u];
+    if (p.interval > 0 && --to_restart == 0) {
+      to_restart = p.interval;
+      if (s < my_k) {
+        __syncthreads();                                   // the slice is complete
+        if (!restart()) { aborted = true; break; }
       }
     }
-    __syncthreads();                                     // X and the small buffers are free
-    // (i) the next minibatch takes its place
-    if (s < my_k) {
-      if constexpr (PF > 0) {
-        const int* rows_next = rows_ahead + ((s + 1) & 1) * MR;
-        gather_store();
-        if (tid < B) {
-          rows[tid] = rows_next[tid];
-          ylab[tid] = lab_next;
-          if (s + 1 < my_k) {                            // rows and labels of iteration s+2 (other slot)
-            const int r = sample_row(p.seed, (uint32_t)i, p.t0 + (uint64_t)s + 2, (uint32_t)tid, p.log2n);
-            rows_ahead[(s & 1) * MR + tid] = r;
-            lab_next = lab[r];
-          }
-        }
-      } else {
-        if (tid < B) {
-          const int r = sample_row(p.seed, (uint32_t)i, p.t0 + (uint64_t)s + 1, (uint32_t)tid, p.log2n);
-          rows[tid] = r;
-          ylab[tid] = lab[r];
-        }
-        __syncthreads();
-        gather_direct();
-        gather_direct_wait();
-      }
-      __syncthreads();
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wavefront's blocks have landed
   }
 
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // no request into LDS outlives the workgroup
   if (aborted) return;
+  __syncthreads();
   // ---- write the slice back ------------------------------------------------------------------
-#pragma unroll
-  for (int kbi = 0; kbi < KBI; ++kbi) {
-    const int kb = wave + kTW * kbi;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = 16 * kb + 4 * q4 + q;
-        if (kb < KB && k < d0) prm[p.w1_off + (size_t)k * p.ld1 + j * W + nt * 16 + n16] = w1[kbi][nt][q];
-      }
-  }
-  for (int e = tid; e < W * D2P; e += kTT) {
-    const int n = e / D2P, c = e % D2P;
-    if (c < d2) prm[p.w2_off + (size_t)(j * W + n) * p.ld2 + c] = w2[e];
-  }
-  if (tid < W) prm[p.b1_off + j * W + tid] = b1[tid];
-  if constexpr (MOM) {
-#pragma unroll
-    for (int kbi = 0; kbi < KBI; ++kbi) {
-      const int kb = wave + kTW * kbi;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = 16 * kb + 4 * q4 + q;
-          if (kb < KB && k < d0) vel[p.w1_off + (size_t)k * p.ld1 + j * W + nt * 16 + n16] = vw1[kbi][nt][q];
-        }
+  {
+    const auto* k = cold();
+    float* prm = k->params + (size_t)i * k->m_pad;
+    each_w1([&](int kbi, int nt, int q, uint32_t off, bool ok) __attribute__((always_inline)) {
+      if (ok) *at(prm, off) = w1[kbi][nt][q];
+    });
+    // every member holds the same b_2: the first one writes it
+    const long b2_at = 4 * k->b2_off;
+    each_small(w2, b1, b2, [&](float& l, uint32_t off, bool ok) __attribute__((always_inline)) {
+      if (ok && (j == 0 || (long)off < b2_at)) *at(prm, off) = l;
+    });
+    if constexpr (MOM) {
+      float* vel = k->vel + (size_t)i * k->m_pad;
+      each_w1([&](int kbi, int nt, int q, uint32_t off, bool ok) __attribute__((always_inline)) {
+        if (ok) *at(vel, off) = vw1[kbi][nt][q];
+      });
+      each_small(vw2, vb1, vb2, [&](float& l, uint32_t off, bool ok) __attribute__((always_inline)) {
+        if (ok && (j == 0 || (long)off < b2_at)) *at(vel, off) = l;
+      });
     }
-    for (int e = tid; e < W * D2P; e += kTT) {
-      const int n = e / D2P, c = e % D2P;
-      if (c < d2) vel[p.w2_off + (size_t)(j * W + n) * p.ld2 + c] = vw2[e];
-    }
-    if (tid < W) vel[p.b1_off + j * W + tid] = vb1[tid];
-    if (j == 0 && tid < d2) vel[p.b2_off + tid] = vb2[tid];
   }
   if (j == 0) {
-    if (tid < d2) prm[p.b2_off + tid] = b2[tid];
-    if (tid < B) p.idx[(size_t)i * B + tid] = rows[tid];
-    if (tid == 0) *base_slot = base + (unsigned)p.P * (unsigned)my_k;   // all arrivals are in
+    if (tid < B) p.idx[(size_t)i * B + tid] = rows[(my_k & 1) * MR + tid];
+    if (tid == 0) {
+      *base_slot = base + (unsigned)my_k;                  // all members have taken part in the last exchange
+      if (i == 0 && p.interval > 0) *restart_base = restarts;
+    }
   }
 }
 
 // ---- host side --------------------------------------------------------------------------------
 size_t fused2_lds_bytes(const Fused2Plan& pl) {
   const size_t MR = (size_t)pl.MT * 16, W = (size_t)pl.NT * 16;
-  size_t floats = MR * pl.ldx + kTW * MR * W + 2 * MR * W + MR * pl.d2p + W * pl.d2p + W + pl.d2p +
-                  4 * MR + 4;
+  size_t floats = (size_t)((pl.KB + 1) / 2) * MR * 32 + pl.shares * MR * W + 2 * MR * W + MR * pl.d2p + W * pl.d2p + W + pl.d2p +
+                  4 * MR + 4 + kWave;
   if (pl.momentum) floats += W * pl.d2p + W + pl.d2p;
   return floats * sizeof(float);
 }
 
-template <int KBI, int NT, int MT> static const void* fused2_symbol(bool mom) {
-  return mom ? reinterpret_cast<const void*>(mlp2_epoch_kernel<KBI, NT, MT, true>)
-             : reinterpret_cast<const void*>(mlp2_epoch_kernel<KBI, NT, MT, false>);
+template <int KBI, int NT, int MT> static const void* fused2_symbol(int ct, bool mom) {
+  if (ct == 1)
+    return mom ? reinterpret_cast<const void*>(mlp2_epoch_kernel<KBI, NT, MT, 1, true>)
+               : reinterpret_cast<const void*>(mlp2_epoch_kernel<KBI, NT, MT, 1, false>);
+  return mom ? reinterpret_cast<const void*>(mlp2_epoch_kernel<KBI, NT, MT, 4, true>)
+             : reinterpret_cast<const void*>(mlp2_epoch_kernel<KBI, NT, MT, 4, false>);
 }
 
-static const void* fused2_pick(int kbi, int nt, int mt, bool mom) {
-#define PICK(K, N, M) if (kbi == K && nt == N && mt == M) return fused2_symbol<K, N, M>(mom);
-  PICK(2, 1, 1) PICK(2, 1, 2) PICK(2, 1, 4) PICK(2, 2, 1) PICK(2, 2, 2) PICK(2, 2, 4)
-  PICK(4, 1, 1) PICK(4, 1, 2) PICK(4, 1, 4) PICK(4, 2, 1) PICK(4, 2, 2) PICK(4, 2, 4)
-  PICK(7, 1, 1) PICK(7, 1, 2) PICK(7, 1, 4) PICK(7, 2, 1) PICK(7, 2, 2) PICK(7, 2, 4)
-  PICK(8, 1, 1) PICK(8, 1, 2) PICK(8, 1, 4) PICK(8, 2, 1) PICK(8, 2, 2) PICK(8, 2, 4)
+static const void* fused2_pick(int kbi, int nt, int mt, int ct, bool mom) {
+#define PICK(K, N, M) if (kbi == K && nt == N && mt == M) return fused2_symbol<K, N, M>(ct, mom);
+  PICK(2, 1, 1) PICK(2, 1, 2) PICK(2, 1, 3) PICK(2, 1, 4) PICK(2, 2, 1) PICK(2, 2, 2) PICK(2, 2, 3) PICK(2, 2, 4)
+  PICK(4, 1, 1) PICK(4, 1, 2) PICK(4, 1, 3) PICK(4, 1, 4) PICK(4, 2, 1) PICK(4, 2, 2) PICK(4, 2, 3) PICK(4, 2, 4)
+  PICK(8, 1, 1) PICK(8, 1, 2) PICK(8, 1, 3) PICK(8, 1, 4) PICK(8, 2, 1) PICK(8, 2, 2) PICK(8, 2, 3) PICK(8, 2, 4)
 #undef PICK
   return nullptr;
+}
+
+// Shapes the epoch kernel is written for (whether the team fits the device is the plan's question).  Momentum on hidden
+// layers that are not whole tiles stays with the per-layer chain.
+bool fused2_shape(int d0, int d1, int d2, int batch, bool momentum) {
+  if (momentum && ((d0 & 3) != 0 || (d1 & 15) != 0)) return false;
+  return d0 >= 1 && d0 <= 1024 && d1 >= 1 && d1 <= kFused2MaxHidden && d2 <= 64 && batch <= 64;
+}
+
+// Floats that the restarts inside a launch pass through memory: a slice per member, and the averages.  0: no plan can
+// have that many workgroups resident.
+size_t fused2_exchange_floats(int n_workers, int d0, int d1, int d2) {
+  const size_t kb = ((size_t)d0 + 15) / 16, d2p = d2 <= 16 ? 16 : 64;
+  size_t most = 0;
+  for (size_t nt = 1; nt <= 2; ++nt) {
+    const size_t team = (d1 + 16 * nt - 1) / (16 * nt), slice = kb * nt * 256 + nt * 16 * (d2p + 1) + d2p;
+    const size_t floats = ((size_t)n_workers + 1) * team * slice;
+    if ((size_t)n_workers * team <= kFused2MaxMembers && floats * sizeof(float) < ((size_t)1 << 31) && floats > most)
+      most = floats;
+  }
+  return most;
 }
 
 // Decides whether the epoch kernel applies and how the team is shaped.  It needs every
 // workgroup of the grid resident at once (checked against the occupancy the runtime reports).
 bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum, Fused2Plan* pl) {
-  if (d0 < 4 || (d0 & 3) != 0 || d0 > 1024 || (d1 & 15) != 0 || d2 > 64 || batch > 64) return false;
+  if (!fused2_shape(d0, d1, d2, batch, momentum)) return false;
   pl->momentum = momentum ? 1 : 0;
-  pl->MT = batch <= 16 ? 1 : batch <= 32 ? 2 : 4;
-  const int kb = (d0 + 15) / 16, kbi_need = (kb + kTW - 1) / kTW;
-  pl->KBI = kbi_need <= 2 ? 2 : kbi_need <= 4 ? 4 : kbi_need <= 7 ? 7 : 8;
-  pl->d2p = (d2 + 15) / 16 * 16;
-  int ldx = (d0 + 15) / 16 * 16 + 4;                        // (ldx / 4) odd: conflict-free 16-byte rows
-  if (((ldx / 4) & 1) == 0) ldx += 4;
-  pl->ldx = ldx;
+  pl->MT = (batch + 15) / 16;
+  pl->KB = (d0 + 15) / 16;
+  const int kbi_need = 2 * (((pl->KB + 1) / 2 + kTW - 1) / kTW);
+  pl->KBI = kbi_need <= 2 ? 2 : kbi_need <= 4 ? 4 : 8;
+  pl->d2p = d2 <= 16 ? 16 : 64;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
   for (int nt = 1; nt <= 2; ++nt) {
-    if (d1 % (16 * nt) != 0) continue;
     pl->NT = nt;
-    pl->P = d1 / (16 * nt);
+    pl->P = (d1 + 16 * nt - 1) / (16 * nt);
+    // partial pre-activations of two wavefronts in one place, one barrier more, where the minibatch leaves no room
+    pl->shares = kTW;
+    if (fused2_lds_bytes(*pl) > 160 * 1024) pl->shares = kTW / 2;
     const size_t lds_bytes = fused2_lds_bytes(*pl);
     if (lds_bytes > 160 * 1024) continue;
-    const void* sym = fused2_pick(pl->KBI, pl->NT, pl->MT, momentum);
+    const void* sym = fused2_pick(pl->KBI, pl->NT, pl->MT, pl->d2p / 16, momentum);
     if (sym == nullptr) return false;
     if (hipFuncSetAttribute(sym, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
       return false;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sym, kTT, lds_bytes) != hipSuccess)
       return false;
-    if ((long)n_workers * pl->P <= (long)per_cu * cus) return true;
+    // a team stays on one of the eight XCDs
+    if ((long)((n_workers + 7) / 8) * pl->P <= (long)per_cu * (cus / 8)) return true;
   }
   return false;
 }
 
 hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, hipStream_t s) {
-  const void* sym = fused2_pick(pl.KBI, pl.NT, pl.MT, pl.momentum != 0);
+  const void* sym = fused2_pick(pl.KBI, pl.NT, pl.MT, pl.d2p / 16, pl.momentum != 0);
   if (sym == nullptr) return hipErrorInvalidValue;
   if ((pl.momentum != 0) != (args.vel != nullptr)) return hipErrorInvalidValue;
   args.P = pl.P;
-  args.d2p = pl.d2p;
-  args.ldx = pl.ldx;
+  args.shares = pl.shares;
   void* kargs[] = {&args};
   // Plain launch: fused2_plan has checked that the whole grid fits on an otherwise idle device at
   // once, and a team member that never shows up (other work holding compute units) ends in the
   // kernel's bounded wait and the abort flag, not in a hang.
-  return hipLaunchKernel(sym, dim3((unsigned)(args.n_workers * pl.P)), dim3(kTT), kargs,
+  return hipLaunchKernel(sym, dim3((unsigned)((args.n_workers + 7) / 8 * 8 * pl.P)), dim3(kTT), kargs,
                          fused2_lds_bytes(pl), s);
 }
 

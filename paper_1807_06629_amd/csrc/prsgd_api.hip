@@ -95,7 +95,7 @@ bool bwd_fused_config(const prsgd_config& c) {
 // shapes the epoch kernel may take (whether it does is decided at init, on the device)
 bool epoch_candidate(const prsgd_config& c) {
   return c.model == PRSGD_MLP && c.gemm_dtype == PRSGD_F32 && c.n_dims == 3 && c.fused_update &&
-         (c.dims[1] % 16) == 0 && c.dims[2] <= 64 && c.batch <= 64;
+         prsgd::fused2_shape(c.dims[0], c.dims[1], c.dims[2], c.batch, c.momentum != 0.0f);
 }
 prsgd_config effective_config(const prsgd_config* c) {
   prsgd_config e = *c;
@@ -171,12 +171,12 @@ void build_carve(const prsgd_config* c_in, const Layout& lo, Carve* cv) {
       cv->mean_shadow = take((size_t)lo.m_pad * 2);
     }
     if (epoch_candidate(*c)) {
-      // epoch kernel: partial logits for the finest team split, arrival counters, abort flag
-      // batch tiles come in 1, 2 or 4 blocks of 16 rows
-      const size_t mr = c->batch <= 16 ? 16 : c->batch <= 32 ? 32 : 64;
-      const size_t d2p = ((size_t)lo.d[2] + 15) / 16 * 16;
-      cv->part = take(2 * n * (size_t)(lo.d[1] / 16) * mr * d2p * 4);
-      cv->sync = take((n + 1) * 128);
+      // epoch kernel: partial logits for the finest team split, numbers of the exchanges, abort flag, restart flags
+      const size_t members = n * (((size_t)lo.d[1] + 15) / 16);
+      cv->part = take(2 * (members + n) * b * lo.d[2] * 8);
+      cv->sync = take((n + 1) * 128 + 16 * (size_t)fused2_flag_stride((int)(members < 4096 ? members : 4096)));
+      const size_t exchange = fused2_exchange_floats(c->n_workers, lo.d[0], lo.d[1], lo.d[2]);
+      if (exchange != 0) cv->exchange = take(exchange * 4);
     }
     // un-fused update; also the fallback of a momentum run whose epoch kernel does not fit the device
     if (!c->fused_update || (c->momentum != 0.0f && !bwd_fused_config(*c)))
@@ -644,7 +644,8 @@ Fused2Args fused2_args(prsgd_ctx* ctx, int k, const int* worker_steps) {
   a.t0 = (uint64_t)ctx->t;
   a.k = k;
   a.worker_steps = worker_steps;
-  a.part = ctx->at<float>(ctx->cv.part);
+  a.part = ctx->at<unsigned long long>(ctx->cv.part);
+  a.exchange = ctx->at<float>(ctx->cv.exchange);
   a.sync = ctx->at<unsigned int>(ctx->cv.sync);
   a.spin_limit = ctx->spin_limit;
   a.row_loss = ctx->at<float>(ctx->cv.row_loss);
@@ -922,7 +923,7 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
                     fused2_plan(cfg->n_workers, lo.d[0], lo.d[1], lo.d[2], cfg->batch,
                                 cfg->momentum != 0.0f, &ctx->f2);
   if (cfg->momentum != 0.0f && !bwd_fused_config(ctx->cfg) && !ctx->use_fused2) ctx->cfg.fused_update = 0;
-  ctx->restarts_in_launch = cfg->model == PRSGD_LSQ && ctx->cv.exchange != 0;
+  ctx->restarts_in_launch = ctx->cv.exchange != 0 && (cfg->model == PRSGD_LSQ || ctx->use_fused2);
   ctx->enlisted = false;
   ctx->features = reinterpret_cast<const float*>(features_dev);
   ctx->targets = targets_dev;
@@ -1157,7 +1158,7 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
   if (iterations < 0 || interval < 1) return set_err(ctx, PRSGD_EINVAL, "iterations >= 0, interval >= 1");
   int64_t left = iterations;
   // Restarts that need no launch of their own: the whole run, up to a restart at its end, is one launch (least squares, 4
-  // workers of 64 floats, 256 iterations with a restart after every eighth: 530 us with two launches per epoch, 205 us).
+  // workers of 64 floats, 256 iterations with a restart after every eighth: 530 us with two launches per epoch, 200 us).
   // Per-kernel timing keeps them apart, as launches of their own.
   while (ctx->restarts_in_launch && ctx->lazy_restart && !ctx->profiling &&
          (ctx->velocity() == nullptr || ctx->cfg.momentum_restart == PRSGD_MOM_KEEP)) {
@@ -1168,13 +1169,19 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
     {
       std::lock_guard<std::mutex> lock(g_waiting_mutex);
       if (!may_wait_as_whole(ctx)) break;
-      LsqArgs a = lsq_args(ctx, k);
-      a.interval = interval;
-      a.sync = ctx->at<unsigned int>(ctx->cv.sync);
-      a.abort_flag = ctx->abort_flag();
-      a.exchange = ctx->at<unsigned long long>(ctx->cv.exchange);
-      a.spin_limit = ctx->spin_limit;
-      LAUNCH(ctx, KK_LSQ, launch_lsq_steps(a, ctx->stream));
+      if (ctx->use_fused2) {
+        Fused2Args a = fused2_args(ctx, k, nullptr);
+        a.interval = interval;
+        LAUNCH(ctx, KK_FUSED2, launch_fused2(ctx->f2, a, ctx->stream));
+      } else {
+        LsqArgs a = lsq_args(ctx, k);
+        a.interval = interval;
+        a.sync = ctx->at<unsigned int>(ctx->cv.sync);
+        a.abort_flag = ctx->abort_flag();
+        a.exchange = ctx->at<unsigned long long>(ctx->cv.exchange);
+        a.spin_limit = ctx->spin_limit;
+        LAUNCH(ctx, KK_LSQ, launch_lsq_steps(a, ctx->stream));
+      }
     }
     ctx->at_mean = false;
     ctx->t += k;

@@ -109,25 +109,35 @@ hipError_t launch_bwd_first_fwd(const BwdArgs& p, hipStream_t s);
 struct Fused2Plan {
   int KBI, NT, MT;     // template shape: W_1 row blocks per wavefront, hidden tiles, batch tiles
   int P;               // workgroups per worker
-  int d2p, ldx;        // padded class count, LDS row stride of the gathered batch
+  int d2p, KB;         // padded class count, 16-column blocks of the gathered batch
   int momentum;        // 1: the variant that carries velocities
+  int shares;          // places for partial pre-activations in LDS
 };
 struct Fused2Args {
   const float* features; const int32_t* labels;
   float* params; long m_pad; long w1_off, b1_off, w2_off, b2_off; int ld1, ld2;
   const float* src; long src_stride;   // starting point of every worker: its replica, or the shared
                                        // node average (stride 0) right after a restart
-  int n_workers, P, d0, d1, d2, d2p, ldx, batch; long rows; int log2n;
+  int n_workers, P, shares, d0, d1, d2, batch; long rows; int log2n;
   int act; float lr; uint64_t seed; uint64_t t0; int k;
   const int* worker_steps;       // Algorithm 3 step counts (nullptr: every worker takes k steps)
-  float* part;                   // [2][N][P][MT*16][d2p] partial logits
-  unsigned int* sync;            // [N][32] arrival counters (+ launch base), then the abort flag
-  unsigned int spin_limit;       // polls of the team barrier before a member gives up
+  int interval;                  // > 0: restarts inside the launch
+  float* exchange;               // [N][P] slices on their way, then [P] averages (fused2_exchange_floats)
+  unsigned long long* part;      // [2][N][P][B d2] partial logits with the number of their iteration,
+                                 // then [2][N][B d2] their sums
+  unsigned int* sync;            // [N][32]: iterations exchanged so far (word 1); [32]: abort flag, restarts so far;
+                                 // then [2][8] copies of a flag byte per workgroup
+  unsigned int spin_limit;       // polls before a member gives up
   float* row_loss; int32_t* idx;
   float* vel; float mu;          // momentum buffers [N][m_pad] (nullptr = plain SGD)
 };
 constexpr unsigned int kFused2SpinLimit = 1u << 22;   // default bound of the team barrier's wait
 size_t fused2_lds_bytes(const Fused2Plan& pl);
+constexpr int kFused2MaxHidden = 512, kFused2MaxMembers = 1024;
+// bytes between the copies of the flags: a line each, on different memory channels
+__host__ __device__ constexpr int fused2_flag_stride(int members) { return (members + 255) / 256 * 256 + 256; }
+size_t fused2_exchange_floats(int n_workers, int d0, int d1, int d2);
+bool fused2_shape(int d0, int d1, int d2, int batch, bool momentum);
 bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum, Fused2Plan* pl);
 hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, hipStream_t s);
 const char* kernel_kind_name(int kind);
@@ -287,6 +297,14 @@ __device__ __forceinline__ void load_x4_to_lds(uint64_t lane_addr, uint32_t lds_
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                :: "s"(lds_off), "v"(lane_addr) : "memory");
 }
+// ... and 4 bytes from an address of every lane's own.
+__device__ __forceinline__ void load_lane_dword_to_lds(uint64_t lane_addr, uint32_t lds_any) {
+  const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+               :: "s"(lds_off), "v"(lane_addr) : "memory");
+}
+// Workgroup barrier that leaves requests into LDS in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 // A tile of 16-byte pieces cannot be padded on its way, so bank conflicts are avoided by permuting WHICH 16 bytes a lane
 // requests.  [c][row], contraction index c the LDS row of ROW_BYTES: the transpose read takes 64 bytes of
 // four consecutive c at a time, so the 64-byte segments of row c are exchanged (segment s at s ^ lds_seg_xor(c))

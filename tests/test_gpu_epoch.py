@@ -1,0 +1,90 @@
+"""One-hidden-layer fp32 nets in one launch: ragged widths, the forms of the exchange, restarts inside the launch.
+
+The gates against the oracle are those of every fp32 net: 1e-5 after one step, 1e-4 after a short run.  Restarts inside the
+launch add in the order of the restart kernels, so that a run in one launch has the bits of the same run
+with a launch per epoch, which per-kernel timing asks for.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import inputs_for, oracle_run, rel_err, small_mlp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_1807_06629_amd import prsgd
+    return prsgd
+
+
+@pytest.fixture(scope="module")
+def D():
+    from paper_1807_06629_amd import drivers
+    return drivers
+
+
+SHAPES = [
+    dict(dims=(1, 1, 1), batch=1, n_workers=1),
+    dict(dims=(5, 15, 3), batch=16, n_workers=2),                 # rows that are not 16-byte aligned
+    dict(dims=(31, 17, 16), batch=17, n_workers=3),               # last hidden tile of one unit
+    dict(dims=(32, 16, 17), batch=15, n_workers=9),               # one pair of row blocks; two class tiles
+    dict(dims=(33, 33, 64), batch=33, n_workers=7),               # a block of one row; two hops (3 x 2112 floats)
+    dict(dims=(255, 100, 10), batch=48, n_workers=4),             # three batch tiles
+    dict(dims=(260, 40, 10), batch=49, n_workers=8),              # four; 9 pairs
+    dict(dims=(500, 150, 12), batch=50, n_workers=3),             # partial pre-activations of two wavefronts in one place
+    dict(dims=(512, 256, 10), batch=13, n_workers=8),             # two hops just reached (16 x 130 floats)
+    dict(dims=(513, 255, 5), batch=32, n_workers=2),              # 33 row blocks
+    dict(dims=(1023, 48, 10), batch=20, n_workers=2),             # 64 row blocks, single words
+    dict(dims=(1024, 64, 10), batch=30, n_workers=20),            # quarters of the restart sum by groups of threads
+    dict(dims=(96, 64, 10), batch=8, n_workers=33),
+]
+
+
+@pytest.mark.parametrize("interval", [1, 4])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_run_in_one_launch(P, D, shape, interval):
+    activation = "relu" if interval == 1 else "tanh"
+    w = small_mlp(activation=activation, rows_per_worker=128, interval=interval, iterations=11, lr=0.02, **shape)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp)
+    P.prsgd_local_steps(h, 1)
+    assert rel_err(D.read_all(h), oracle_run(w, inp, iterations=1, interval=100)["x"]) <= 1e-5
+    P.prsgd_write_params(h, -1, inp["x0"])
+    P.prsgd_set_iteration(h, 0)
+    P.prsgd_run(h, w.iterations, interval)
+    got, loss = D.read_all(h), P.prsgd_read_loss(h)
+    last = w.n_workers - 1
+    assert np.array_equal(P.prsgd_read_indices(h)[last],
+                          oracle.sample_rows(w.index_seed, last, w.iterations, w.batch, w.rows_per_worker))
+    P.prsgd_destroy(h)
+    h = D.open_workload(w, inp)
+    P.prsgd_profile_enable(h, True)                               # a launch per epoch, a launch per restart
+    P.prsgd_run(h, w.iterations, interval)
+    names = {r["name"] for r in P.prsgd_profile_read(h)}
+    assert names == {"mlp2_epoch", "restart_mean"}, names
+    assert np.array_equal(D.read_all(h), got) and np.array_equal(P.prsgd_read_loss(h), loss)
+    P.prsgd_destroy(h)
+    want = oracle_run(w, inp)
+    assert rel_err(got, want["x"]) <= 1e-4
+    assert np.allclose(loss, want["losses"], rtol=1e-3, atol=1e-6)
+
+
+def test_contexts_of_three_streams_together(P, D):
+    """Three grids of 128 workgroups on three streams: not all of them may wait as a whole at once."""
+    w = small_mlp(dims=(784, 256, 10), batch=32, n_workers=8, rows_per_worker=128, interval=2, iterations=12)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp)
+    P.prsgd_run(h, w.iterations, w.interval)
+    want = D.read_all(h)
+    P.prsgd_destroy(h)
+    handles = [D.open_workload(w, inp, stream=torch.cuda.Stream()) for _ in range(3)]
+    for _ in range(2):
+        for h in handles:
+            P.prsgd_run(h, w.iterations // 2, w.interval)
+    for h in handles:
+        assert np.array_equal(D.read_all(h), want)
+        P.prsgd_destroy(h)
