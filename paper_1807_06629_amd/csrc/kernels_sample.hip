@@ -228,8 +228,30 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_row_kernel(
 
 // Narrow head (at most 16 classes, bf16 operands): the logits product is taken here as well,
 //   z_b = H_{L-1}[b, :] bf16(W_L) + b_L,
-// one wavefront per minibatch row with the contraction spread over its lanes -- a product of a few
-// thousand multiply-adds per row does not pay for a launch of its own (and its split contraction).
+// 16 minibatch rows per workgroup on the matrix cores (v_mfma_f32_16x16x32_bf16), the contraction dealt to the four
+// wavefronts in pieces of kPiece: a wavefront takes its H fragments straight from memory and turns its rows of W_L through
+// LDS of its own; the four partial blocks are added in order.  Then 16 lanes per row, a class each.
+// One wavefront per row with multiply-adds and six exchanges per class had been bound by its instructions: with the
+// row gather beside it HEADFIG.
+constexpr int kHeadRows = 16;
+constexpr int kPiece = 256;                            // contraction elements of a wavefront and step
+
+template <int CTRL> __device__ __forceinline__ float row_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float head_row_max(float v) {                 // over 16 lanes
+  v = fmaxf(v, row_move<0xB1>(v));
+  v = fmaxf(v, row_move<0x4E>(v));
+  v = fmaxf(v, row_move<0x141>(v));
+  return fmaxf(v, row_move<0x140>(v));
+}
+__device__ __forceinline__ float head_row_sum(float v) {
+  v += row_move<0xB1>(v);
+  v += row_move<0x4E>(v);
+  v += row_move<0x141>(v);
+  return v + row_move<0x140>(v);
+}
+
 __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     const uint16_t* __restrict__ h, long h_gs, int ldh, int k_dim, const uint16_t* __restrict__ w_sh,
     long w_gs, const float* __restrict__ bias, long bias_gs, const int32_t* __restrict__ yb,
@@ -241,55 +263,74 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     return;
   }
   if (worker_steps != nullptr && step >= worker_steps[g]) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b = blockIdx.x * (kThreads / kWave) + wave;
-  if (b >= batch) return;
-  const size_t r = (size_t)g * batch + b;
-  const uint16_t* h_r = h + (size_t)g * h_gs + (size_t)b * ldh;
-  const uint16_t* w_g = w_sh + (size_t)g * w_gs;        // [k_dim][ldc], ldc = 8 or 16
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  float acc[16];
+  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
+  typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
+  __shared__ __attribute__((aligned(16))) uint16_t w_lds[kThreads / kWave][kPiece][16];
+  __shared__ float part[kThreads / kWave][kHeadRows][17];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n16 = lane & 15, q4 = lane >> 4;
+  const int b0 = (int)blockIdx.x * kHeadRows;
+  const uint16_t* h_r = h + (size_t)g * h_gs + (size_t)min(b0 + n16, batch - 1) * ldh;   // rows past the end: not stored
+  const uint16_t* w_g = w_sh + (size_t)g * w_gs;        // [k_dim][ldc], ldc = 8 or 16
+  const u32x4_t zero = {0u, 0u, 0u, 0u};
+  f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int k0 = wave * kPiece; k0 < k_dim; k0 += (kThreads / kWave) * kPiece) {
+    u32x4_t a[kPiece / 32], w[kPiece / 32];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) acc[c] = 0.0f;
-#pragma unroll 8
-  for (int k = lane; k < k_dim; k += kWave) {
-    const float hv = bf16_to_f32(h_r[k]);
-    const u32x4_t lo = *reinterpret_cast<const u32x4_t*>(w_g + (size_t)k * ldc);
-    u32x4_t hi = {0u, 0u, 0u, 0u};
-    if (ldc > 8) hi = *reinterpret_cast<const u32x4_t*>(w_g + (size_t)k * ldc + 8);   // uniform
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      acc[2 * j] = fmaf(hv, __uint_as_float(lo[j] << 16), acc[2 * j]);
-      acc[2 * j + 1] = fmaf(hv, __uint_as_float(lo[j] & 0xFFFF0000u), acc[2 * j + 1]);
-      acc[8 + 2 * j] = fmaf(hv, __uint_as_float(hi[j] << 16), acc[8 + 2 * j]);
-      acc[8 + 2 * j + 1] = fmaf(hv, __uint_as_float(hi[j] & 0xFFFF0000u), acc[8 + 2 * j + 1]);
+    for (int u = 0; u < kPiece / 32; ++u) {             // columns [k_dim, ldh) of H are zero
+      const int k = k0 + 32 * u + 8 * q4;
+      a[u] = k < k_dim ? *reinterpret_cast<const u32x4_t*>(h_r + k) : zero;
     }
+    if (ldc > 8) {                                      // uniform: 32 rows of 32 bytes per load
+#pragma unroll
+      for (int u = 0; u < kPiece / 32; ++u) {
+        const int k = k0 + 32 * u + (lane >> 1);
+        w[u] = k < k_dim ? *reinterpret_cast<const u32x4_t*>(w_g + (size_t)k * 16 + 8 * (lane & 1)) : zero;
+      }
+    } else {                                            // lanes of the upper halves write the zeros of classes 8 .. 15
+#pragma unroll
+      for (int u = 0; u < kPiece / 32; ++u) {
+        const int k = k0 + 32 * u + (lane >> 1);
+        w[u] = k < k_dim && (lane & 1) == 0 ? *reinterpret_cast<const u32x4_t*>(w_g + (size_t)k * 8) : zero;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kPiece / 32; ++u)
+      *reinterpret_cast<u32x4_t*>(&w_lds[wave][32 * u + (lane >> 1)][8 * (lane & 1)]) = w[u];
+    __builtin_amdgcn_wave_barrier();                    // the piece is this wavefront's own
+#pragma unroll
+    for (int u = 0; u < kPiece / 32; ++u) {
+      // lane (class n16, q4) takes W[32 u + 8 q4 .. + 7][n16]: two transposed reads of four rows (see frag_trans)
+      const uint16_t* p = &w_lds[wave][32 * u + 8 * q4 + (n16 >> 2)][4 * (n16 & 3)];
+      const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
+      const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * 16));
+      const bf16x8_t wf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u]), wf, acc, 0, 0, 0);
+    }
+    __builtin_amdgcn_wave_barrier();
   }
+  // element v of lane (n16, q4) is row 4 q4 + v, class n16
 #pragma unroll
-  for (int c = 0; c < 16; ++c)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc[c] += __shfl_xor(acc[c], o);
-  // lane c keeps class c
+  for (int v = 0; v < 4; ++v) part[wave][4 * q4 + v][n16] = acc[v];
+  __syncthreads();
+  const int row = tid >> 4, c = tid & 15, b = b0 + row;
+  if (b >= batch) return;                               // whole groups of 16 lanes
+  const size_t r = (size_t)g * batch + b;
   float z = -INFINITY;
-#pragma unroll
-  for (int c = 0; c < 16; ++c)
-    if (lane == c && c < n_classes) z = acc[c] + bias[(size_t)g * bias_gs + c];
-  float mx = z;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  if (c < n_classes)
+    z = (((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c]) + bias[(size_t)g * bias_gs + c];
+  const float mx = head_row_max(z);
   const int label = yb[r];
-  const float e = lane < n_classes ? expf(z - mx) : 0.0f;
-  float se = e, zl = (lane == label && lane < n_classes) ? z : 0.0f;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    se += __shfl_xor(se, o);
-    zl += __shfl_xor(zl, o);
+  const float e = c < n_classes ? expf(z - mx) : 0.0f;
+  const float se = head_row_sum(e);
+  const float zl = head_row_sum(c == label && c < n_classes ? z : 0.0f);   // an out-of-range label selects nothing
+  if (c < ldc) {
+    const float d = c < n_classes ? (e / se - (c == label ? 1.0f : 0.0f)) * (1.0f / (float)batch) : 0.0f;
+    delta[r * ldc + c] = f32_to_bf16_rne(d);
   }
-  if (lane < ldc) {
-    const float d = lane < n_classes ? (e / se - (lane == label ? 1.0f : 0.0f)) * (1.0f / (float)batch) : 0.0f;
-    delta[r * ldc + lane] = f32_to_bf16_rne(d);
-  }
-  if (lane == 0) row_loss[r] = (mx + logf(se)) - zl;    // an out-of-range label selects nothing
+  if (c == 0) row_loss[r] = (mx + logf(se)) - zl;
 }
 
 // Minibatch loss of each worker: mean of its row losses, rows summed in slot order.
@@ -369,8 +410,8 @@ hipError_t launch_softmax_xent_narrow(const uint16_t* h, long h_gs, int ldh, int
                                       uint16_t* delta, float* row_loss, int n_workers, int batch, int n_classes,
                                       int ldc, const int* worker_steps, int step, const GatherArgs* next,
                                       hipStream_t s) {
-  if (!softmax_narrow_applies(n_classes, ldc, true) || (ldh % 2) != 0) return hipErrorInvalidValue;
-  const int head_blocks = (batch + kThreads / kWave - 1) / (kThreads / kWave);
+  if (!softmax_narrow_applies(n_classes, ldc, true) || (ldh % 8) != 0) return hipErrorInvalidValue;
+  const int head_blocks = (batch + kHeadRows - 1) / kHeadRows;
   GatherArgs ga;
   memset(&ga, 0, sizeof(ga));
   if (next != nullptr) ga = *next;
