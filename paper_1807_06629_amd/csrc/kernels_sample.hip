@@ -226,15 +226,18 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_row_kernel(
   if (tid == 0) row_loss[r] = (mx + logf(se)) - zl;     // an out-of-range label selects nothing
 }
 
-// Narrow head (at most 16 classes, bf16 operands): the logits product is taken here as well,
-//   z_b = H_{L-1}[b, :] bf16(W_L) + b_L,
-// 16 minibatch rows per workgroup on the matrix cores (v_mfma_f32_16x16x32_bf16), the contraction dealt to the four
-// wavefronts in pieces of kPiece: a wavefront takes its H fragments straight from memory and turns its rows of W_L through
-// LDS of its own; the four partial blocks are added in order.  Then 16 lanes per row, a class each.
-// One wavefront per row with multiply-adds and six exchanges per class had been bound by its instructions: with the
-// row gather beside it HEADFIG.
+// Head of at most 64 classes: the logits product is taken here as well,
+//   z_b = H_{L-1}[b, :] W_L + b_L        (bf16 operands: bf16(W_L)),
+// 16 minibatch rows per workgroup on the matrix cores, the contraction dealt to the four wavefronts in pieces; the four
+// partial blocks are added in order.  Then 16 lanes per row, CT classes each (classes past the last are zero columns).
+//   bf16: v_mfma_f32_16x16x32; a wavefront takes its H fragments straight from memory and turns its rows of W_L through LDS
+//         of its own
+//   fp32: v_mfma_f32_16x16x4; contraction element 4 q4 + q of every 16 in step q, so that an H fragment is one 16-byte load
+// It saves the launch of a small product: an iteration of 784-300-100-10 in fp32 (8 workers, 50 rows) 49.6 -> 44.5 us, of
+// 1000-500-300-37 in bf16 (6 workers, 100 rows) 50.5 -> 46.3 us; with up to 16 classes in bf16 it replaces a wavefront per row with
+// multiply-adds, which was bound by its instructions (16 workers of 3072-1024-1024-10, 64 rows: 147.5 -> 144.2 us).
 constexpr int kHeadRows = 16;
-constexpr int kPiece = 256;                            // contraction elements of a wavefront and step
+constexpr int kHeadClasses = 64;
 
 template <int CTRL> __device__ __forceinline__ float row_move(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
@@ -252,85 +255,133 @@ __device__ __forceinline__ float head_row_sum(float v) {
   return v + row_move<0x140>(v);
 }
 
+template <bool BF16, int CT>
 __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
-    const uint16_t* __restrict__ h, long h_gs, int ldh, int k_dim, const uint16_t* __restrict__ w_sh,
+    const void* __restrict__ h_any, long h_gs, int ldh, int k_dim, const void* __restrict__ w_any,
     long w_gs, const float* __restrict__ bias, long bias_gs, const int32_t* __restrict__ yb,
-    uint16_t* __restrict__ delta, float* __restrict__ row_loss, int batch, int n_classes, int ldc,
+    void* __restrict__ delta, float* __restrict__ row_loss, int batch, int n_classes, int ldc,
     const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next) {
   const int g = blockIdx.y;
   if ((int)blockIdx.x >= head_blocks) {                 // the minibatch draw of the next iteration
-    gather_row<true>(next, (int)blockIdx.x - head_blocks, g);
+    gather_row<BF16>(next, (int)blockIdx.x - head_blocks, g);
     return;
   }
   if (worker_steps != nullptr && step >= worker_steps[g]) return;
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
-  typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
-  __shared__ __attribute__((aligned(16))) uint16_t w_lds[kThreads / kWave][kPiece][16];
-  __shared__ float part[kThreads / kWave][kHeadRows][17];
+  constexpr int NW = kThreads / kWave;
+  __shared__ float part[NW][kHeadRows][16 * CT + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n16 = lane & 15, q4 = lane >> 4;
   const int b0 = (int)blockIdx.x * kHeadRows;
-  const uint16_t* h_r = h + (size_t)g * h_gs + (size_t)min(b0 + n16, batch - 1) * ldh;   // rows past the end: not stored
-  const uint16_t* w_g = w_sh + (size_t)g * w_gs;        // [k_dim][ldc], ldc = 8 or 16
-  const u32x4_t zero = {0u, 0u, 0u, 0u};
-  f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int k0 = wave * kPiece; k0 < k_dim; k0 += (kThreads / kWave) * kPiece) {
-    u32x4_t a[kPiece / 32], w[kPiece / 32];
+  const size_t h_row = (size_t)g * h_gs + (size_t)min(b0 + n16, batch - 1) * ldh;        // rows past the end: not stored
+  f32x4_t acc[CT];
 #pragma unroll
-    for (int u = 0; u < kPiece / 32; ++u) {             // columns [k_dim, ldh) of H are zero
-      const int k = k0 + 32 * u + 8 * q4;
-      a[u] = k < k_dim ? *reinterpret_cast<const u32x4_t*>(h_r + k) : zero;
-    }
-    if (ldc > 8) {                                      // uniform: 32 rows of 32 bytes per load
+  for (int ct = 0; ct < CT; ++ct) acc[ct] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (BF16) {
+    typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
+    typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
+    constexpr int kPiece = 256 / CT;                    // contraction elements of a wavefront and step
+    constexpr int CPR = 2 * CT, RPL = kWave / CPR;      // 16-byte chunks of a row, rows of a load
+    __shared__ __attribute__((aligned(16))) uint16_t w_lds[NW][kPiece][16 * CT];
+    const uint16_t* h_r = reinterpret_cast<const uint16_t*>(h_any) + h_row;
+    const uint16_t* w_g = reinterpret_cast<const uint16_t*>(w_any) + (size_t)g * w_gs;   // [k_dim][ldc]
+    const u32x4_t zero = {0u, 0u, 0u, 0u};
+    const int wr = lane / CPR, wc = 8 * (lane % CPR);
+    for (int k0 = wave * kPiece; k0 < k_dim; k0 += NW * kPiece) {
+      u32x4_t a[kPiece / 32], w[kPiece / RPL];
 #pragma unroll
-      for (int u = 0; u < kPiece / 32; ++u) {
-        const int k = k0 + 32 * u + (lane >> 1);
-        w[u] = k < k_dim ? *reinterpret_cast<const u32x4_t*>(w_g + (size_t)k * 16 + 8 * (lane & 1)) : zero;
+      for (int u = 0; u < kPiece / 32; ++u) {           // columns [k_dim, ldh) of H are zero
+        const int k = k0 + 32 * u + 8 * q4;
+        a[u] = k < k_dim ? *reinterpret_cast<const u32x4_t*>(h_r + k) : zero;
       }
-    } else {                                            // lanes of the upper halves write the zeros of classes 8 .. 15
 #pragma unroll
-      for (int u = 0; u < kPiece / 32; ++u) {
-        const int k = k0 + 32 * u + (lane >> 1);
-        w[u] = k < k_dim && (lane & 1) == 0 ? *reinterpret_cast<const u32x4_t*>(w_g + (size_t)k * 8) : zero;
+      for (int u = 0; u < kPiece / RPL; ++u) {
+        const int k = k0 + RPL * u + wr;
+        w[u] = k < k_dim && wc < ldc ? *reinterpret_cast<const u32x4_t*>(w_g + (size_t)k * ldc + wc) : zero;
       }
-    }
 #pragma unroll
-    for (int u = 0; u < kPiece / 32; ++u)
-      *reinterpret_cast<u32x4_t*>(&w_lds[wave][32 * u + (lane >> 1)][8 * (lane & 1)]) = w[u];
-    __builtin_amdgcn_wave_barrier();                    // the piece is this wavefront's own
+      for (int u = 0; u < kPiece / RPL; ++u) *reinterpret_cast<u32x4_t*>(&w_lds[wave][RPL * u + wr][wc]) = w[u];
+      __builtin_amdgcn_wave_barrier();                  // the piece is this wavefront's own
 #pragma unroll
-    for (int u = 0; u < kPiece / 32; ++u) {
-      // lane (class n16, q4) takes W[32 u + 8 q4 .. + 7][n16]: two transposed reads of four rows (see frag_trans)
-      const uint16_t* p = &w_lds[wave][32 * u + 8 * q4 + (n16 >> 2)][4 * (n16 & 3)];
-      const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
-      const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * 16));
-      const bf16x8_t wf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u]), wf, acc, 0, 0, 0);
+      for (int u = 0; u < kPiece / 32; ++u)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          // lane (class n16, q4) takes W[32 u + 8 q4 .. + 7][n16]: two transposed reads of four rows (see frag_trans)
+          const uint16_t* p = &w_lds[wave][32 * u + 8 * q4 + (n16 >> 2)][16 * ct + 4 * (n16 & 3)];
+          const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p));
+          const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 4 * 16 * CT));
+          const bf16x8_t wf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u]), wf, acc[ct], 0, 0, 0);
+        }
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
+  } else {
+    const float* h_r = reinterpret_cast<const float*>(h_any) + h_row;
+    const float* w_g = reinterpret_cast<const float*>(w_any) + (size_t)g * w_gs;
+    constexpr int U = CT == 1 ? 4 : 2;                  // 16-deep pieces in flight
+    for (int k0 = wave * 16 * U; k0 < k_dim; k0 += NW * 16 * U) {
+      f32x4_t a[U];
+      float w[U][4][CT];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 16 * u + 4 * q4;
+        a[u] = k < k_dim ? *reinterpret_cast<const f32x4_t*>(h_r + k) : (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            w[u][q][ct] = k + q < k_dim && 16 * ct + n16 < ldc ? w_g[(size_t)(k + q) * ldc + 16 * ct + n16] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][q], w[u][q][ct], acc[ct], 0, 0, 0);
+    }
   }
-  // element v of lane (n16, q4) is row 4 q4 + v, class n16
+  // element v of lane (n16, q4) is row 4 q4 + v, class n16 of the tile
 #pragma unroll
-  for (int v = 0; v < 4; ++v) part[wave][4 * q4 + v][n16] = acc[v];
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[wave][4 * q4 + v][16 * ct + n16] = acc[ct][v];
   __syncthreads();
-  const int row = tid >> 4, c = tid & 15, b = b0 + row;
+  const int row = tid >> 4, l16 = tid & 15, b = b0 + row;
   if (b >= batch) return;                               // whole groups of 16 lanes
   const size_t r = (size_t)g * batch + b;
-  float z = -INFINITY;
-  if (c < n_classes)
-    z = (((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c]) + bias[(size_t)g * bias_gs + c];
-  const float mx = head_row_max(z);
   const int label = yb[r];
-  const float e = c < n_classes ? expf(z - mx) : 0.0f;
-  const float se = head_row_sum(e);
-  const float zl = head_row_sum(c == label && c < n_classes ? z : 0.0f);   // an out-of-range label selects nothing
-  if (c < ldc) {
-    const float d = c < n_classes ? (e / se - (c == label ? 1.0f : 0.0f)) * (1.0f / (float)batch) : 0.0f;
-    delta[r * ldc + c] = f32_to_bf16_rne(d);
+  float z[CT], mx = -INFINITY;
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int c = 16 * ct + l16;
+    z[ct] = -INFINITY;
+    if (c < n_classes)
+      z[ct] = (((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c]) + bias[(size_t)g * bias_gs + c];
+    mx = fmaxf(mx, z[ct]);
   }
-  if (c == 0) row_loss[r] = (mx + logf(se)) - zl;
+  mx = head_row_max(mx);
+  float e[CT], se = 0.0f, zl = 0.0f;
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int c = 16 * ct + l16;
+    if (c == label && c < n_classes) zl = z[ct];        // an out-of-range label selects nothing
+    e[ct] = c < n_classes ? expf(z[ct] - mx) : 0.0f;
+    se += e[ct];
+  }
+  se = head_row_sum(se);
+  zl = head_row_sum(zl);
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int c = 16 * ct + l16;
+    if (c < ldc) {
+      const float d = c < n_classes ? (e[ct] / se - (c == label ? 1.0f : 0.0f)) * (1.0f / (float)batch) : 0.0f;
+      if (BF16) reinterpret_cast<uint16_t*>(delta)[r * ldc + c] = f32_to_bf16_rne(d);
+      else reinterpret_cast<float*>(delta)[r * ldc + c] = d;
+    }
+  }
+  if (l16 == 0) row_loss[r] = (mx + logf(se)) - zl;
 }
 
 // Minibatch loss of each worker: mean of its row losses, rows summed in slot order.
@@ -401,22 +452,28 @@ hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_strid
   return hipGetLastError();
 }
 
-bool softmax_narrow_applies(int n_classes, int ldc, bool bf16) {
-  return bf16 && n_classes >= 1 && n_classes <= 16 && (ldc == 8 || ldc == 16);
+// A workgroup reads all of W_L for its 16 rows: up to kHeadBytes of it the launch saved is worth more (bf16
+// with at most 16 classes, whose product has a split contraction to pay for as well: always).
+constexpr long kHeadBytes = 128 << 10;
+bool softmax_narrow_applies(int n_classes, int ldc, int k_dim, bool bf16) {
+  if (n_classes < 1 || n_classes > kHeadClasses || ldc > kHeadClasses || (ldc & 7) != 0) return false;
+  return (bf16 && n_classes <= 16) || (long)k_dim * ldc * (bf16 ? 2 : 4) <= kHeadBytes;
 }
 
-hipError_t launch_softmax_xent_narrow(const uint16_t* h, long h_gs, int ldh, int k_dim, const uint16_t* w_sh,
+hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_dim, const void* w,
                                       long w_gs, const float* bias, long bias_gs, const int32_t* yb,
-                                      uint16_t* delta, float* row_loss, int n_workers, int batch, int n_classes,
-                                      int ldc, const int* worker_steps, int step, const GatherArgs* next,
+                                      void* delta, float* row_loss, int n_workers, int batch, int n_classes,
+                                      int ldc, bool bf16, const int* worker_steps, int step, const GatherArgs* next,
                                       hipStream_t s) {
-  if (!softmax_narrow_applies(n_classes, ldc, true) || (ldh % 8) != 0) return hipErrorInvalidValue;
+  if (!softmax_narrow_applies(n_classes, ldc, k_dim, bf16) || (ldh % 8) != 0) return hipErrorInvalidValue;
   const int head_blocks = (batch + kHeadRows - 1) / kHeadRows;
   GatherArgs ga;
   memset(&ga, 0, sizeof(ga));
   if (next != nullptr) ga = *next;
   dim3 grid(head_blocks + (next != nullptr ? next->batch : 0), n_workers);
-  hipLaunchKernelGGL(softmax_xent_narrow_kernel, grid, dim3(kThreads), 0, s, h, h_gs, ldh, k_dim, w_sh, w_gs, bias,
+  auto kernel = bf16 ? (ldc <= 16 ? softmax_xent_narrow_kernel<true, 1> : softmax_xent_narrow_kernel<true, 4>)
+                     : (ldc <= 16 ? softmax_xent_narrow_kernel<false, 1> : softmax_xent_narrow_kernel<false, 4>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, h, h_gs, ldh, k_dim, w, w_gs, bias,
                      bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step, head_blocks, ga);
   return hipGetLastError();
 }
