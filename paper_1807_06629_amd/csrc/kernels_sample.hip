@@ -16,35 +16,60 @@ static int ilog2(long n) {
   return l;
 }
 
-// One workgroup per (slot j, worker i): draw the row, copy it into the batch buffer.
+// One workgroup per (slot j, worker i): draw the row, copy it into the batch buffer.  Bound by the latency of the row's
+// loads: all of a round (4 vectors or 8 single words per thread, clamped to the row so that no load is conditional) are
+// issued before the first store, which the compiler cannot move them across, and the label is stored last.  Per iteration,
+// against a load and a store in turn: 8 workers, 512 rows of 3072 215.9 -> 212.8 us, 16 workers, 64 rows 144.3 -> 143.8 us.
 template <bool BF16>
 __device__ __forceinline__ void gather_row(const GatherArgs& a, int j, int i) {
   const int32_t row = sample_row(a.seed, (uint32_t)i, a.t, (uint32_t)j, a.log2n);
   const size_t slot = (size_t)i * a.batch + j;
-  if (threadIdx.x == 0) {
-    a.idx[slot] = row;
-    a.yb[slot] = a.labels[(size_t)i * a.rows + row];
-  }
+  const int32_t label = a.labels[(size_t)i * a.rows + row];
   const int d0 = a.d0, ld0 = a.ld0;
   const float* src = a.features + ((size_t)i * a.rows + row) * d0;
   if ((d0 & 3) == 0) {
-    const float4* src4 = reinterpret_cast<const float4*>(src);
-    for (int c = threadIdx.x; c < d0 / 4; c += kThreads) {
-      const float4 v = src4[c];
-      if (BF16) {
-        uint2 h;
-        h.x = f32x2_to_bf16x2_rne(v.x, v.y);
-        h.y = f32x2_to_bf16x2_rne(v.z, v.w);
-        reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.xb) + slot * ld0)[c] = h;
-      } else {
-        reinterpret_cast<float4*>(reinterpret_cast<float*>(a.xb) + slot * ld0)[c] = v;
+    constexpr int U = 4;
+    const int n4 = d0 / 4;
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));      // arrays of float4 structs end in scratch memory
+    const f32x4_t* src4 = reinterpret_cast<const f32x4_t*>(src);
+    for (int c0 = threadIdx.x; c0 < n4; c0 += U * kThreads) {
+      f32x4_t v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = src4[min(c0 + u * kThreads, n4 - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * kThreads;
+        if (c >= n4) break;
+        if (BF16) {
+          uint2 h;
+          h.x = f32x2_to_bf16x2_rne(v[u].x, v[u].y);
+          h.y = f32x2_to_bf16x2_rne(v[u].z, v[u].w);
+          reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.xb) + slot * ld0)[c] = h;
+        } else {
+          reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(a.xb) + slot * ld0)[c] = v[u];
+        }
       }
     }
   } else {
-    for (int c = threadIdx.x; c < d0; c += kThreads) {
-      if (BF16) reinterpret_cast<uint16_t*>(a.xb)[slot * ld0 + c] = f32_to_bf16_rne(src[c]);
-      else reinterpret_cast<float*>(a.xb)[slot * ld0 + c] = src[c];
+    constexpr int U = 8;
+    for (int c0 = threadIdx.x; c0 < d0; c0 += U * kThreads) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = src[min(c0 + u * kThreads, d0 - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) asm volatile("" : "+v"(v[u]));         // a load is not moved to its conditional store
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * kThreads;
+        if (c >= d0) break;
+        if (BF16) reinterpret_cast<uint16_t*>(a.xb)[slot * ld0 + c] = f32_to_bf16_rne(v[u]);
+        else reinterpret_cast<float*>(a.xb)[slot * ld0 + c] = v[u];
+      }
     }
+  }
+  if (threadIdx.x == 0) {
+    a.idx[slot] = row;
+    a.yb[slot] = label;
   }
 }
 
