@@ -300,9 +300,16 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
   const int n16 = lane & 15, q4 = lane >> 4;
   const int b0 = (int)blockIdx.x * kHeadRows;
   const size_t h_row = (size_t)g * h_gs + (size_t)min(b0 + n16, batch - 1) * ldh;        // rows past the end: not stored
+  // what the softmax part needs from memory is requested before the product: 1000-500-300-37 in bf16 46.1 -> 45.7 us per iteration
+  const int row = tid >> 4, l16 = tid & 15, b = b0 + row;
+  const int label = yb[(size_t)g * batch + min(b, batch - 1)];
+  float bias_c[CT];
   f32x4_t acc[CT];
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) acc[ct] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  for (int ct = 0; ct < CT; ++ct) {
+    bias_c[ct] = bias[(size_t)g * bias_gs + min(16 * ct + l16, n_classes - 1)];
+    acc[ct] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  }
   if constexpr (BF16) {
     typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
     typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
@@ -373,17 +380,15 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
 #pragma unroll
     for (int v = 0; v < 4; ++v) part[wave][4 * q4 + v][16 * ct + n16] = acc[ct][v];
   __syncthreads();
-  const int row = tid >> 4, l16 = tid & 15, b = b0 + row;
   if (b >= batch) return;                               // whole groups of 16 lanes
   const size_t r = (size_t)g * batch + b;
-  const int label = yb[r];
   float z[CT], mx = -INFINITY;
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int c = 16 * ct + l16;
     z[ct] = -INFINITY;
     if (c < n_classes)
-      z[ct] = (((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c]) + bias[(size_t)g * bias_gs + c];
+      z[ct] = (((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c]) + bias_c[ct];
     mx = fmaxf(mx, z[ct]);
   }
   mx = head_row_max(mx);

@@ -1,0 +1,59 @@
+"""The loss head that multiplies a narrow logits layer itself, at the edges of its tiles, against the CPU oracle.
+
+The bounds are those of the grouped products: fp32 1e-5, the one-step gate; bf16 1e-4, since oracle and kernels round
+the same operands and one step differs by its fp32 sums and by an operand whose rounding falls the other way.
+"""
+import numpy as np
+import pytest
+import torch
+
+from helpers import inputs_for, oracle_run, rel_err, small_mlp
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, width in front of the logits, classes, batch, workers, whether the head takes the product): class tiles of 16 and
+# 64, whole and ragged; blocks of 16 rows; contractions of one element, around a piece (bf16 256 and 64, fp32 64 and 32
+# elements per wavefront) and a round of four, and the largest whose weights are 128 KB and one beyond
+SHAPES = [
+    ("bf16", 1, 1, 1, 1, True),
+    ("bf16", 255, 16, 15, 3, True),
+    ("bf16", 257, 7, 16, 2, True),
+    ("bf16", 1032, 10, 17, 2, True),
+    ("bf16", 4097, 16, 33, 2, True),                 # any width up to 16 classes
+    ("bf16", 63, 17, 16, 5, True),
+    ("bf16", 65, 33, 31, 3, True),
+    ("bf16", 263, 64, 129, 2, True),
+    ("bf16", 1024, 64, 20, 2, True),
+    ("bf16", 1025, 64, 20, 2, False),
+    ("bf16", 72, 65, 20, 2, False),
+    ("f32", 1, 1, 1, 1, True),
+    ("f32", 63, 9, 15, 3, True),
+    ("f32", 65, 16, 17, 2, True),
+    ("f32", 259, 3, 130, 2, True),
+    ("f32", 2048, 16, 16, 2, True),
+    ("f32", 2049, 16, 16, 2, False),
+    ("f32", 31, 17, 16, 5, True),
+    ("f32", 33, 41, 33, 3, True),
+    ("f32", 130, 64, 65, 2, True),
+    ("f32", 512, 64, 20, 2, True),
+    ("f32", 513, 64, 20, 2, False),
+]
+
+
+@pytest.mark.parametrize("dtype,width,classes,batch,n_workers,inside", SHAPES)
+def test_logits_inside_the_head(dtype, width, classes, batch, n_workers, inside):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=(24, 40, width, classes), batch=batch, n_workers=n_workers, gemm_dtype=dtype,
+                  rows_per_worker=256, iterations=1)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_local_steps(h, 1)
+    want = oracle_run(w, inp, iterations=1)
+    assert rel_err(D.read_all(h), want["x"]) <= (1e-5 if dtype == "f32" else 1e-4)
+    assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-5 if dtype == "f32" else 2e-3, atol=1e-6)
+    P.prsgd_profile_enable(h, True)
+    P.prsgd_local_steps(h, 1)
+    launches = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
+    assert launches["gemm_fwd"] == (2 if inside else 3), launches
+    P.prsgd_destroy(h)
