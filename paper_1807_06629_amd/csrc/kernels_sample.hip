@@ -94,6 +94,36 @@ __global__ __launch_bounds__(kThreads) void sample_indices_kernel(int32_t* __res
   }
 }
 
+// Logits of classes c0, c0 + STRIDE, ... of one row: the product's output, or (split contraction) the bias plus the partial
+// sums in split order.  All Q (S + 1) loads are in flight together: indices are clamped, no load is conditional.  4096-4096-4096-
+// 4096-1000, 8 workers, 128 rows, interval 16: 1008.0 -> 1005.7 us per iteration against a part after the other.
+template <int Q, int STRIDE, int S>
+__device__ __forceinline__ void fetch_logits_parts(float (&z)[Q], const float* __restrict__ row, long part_stride,
+                                                   const float* __restrict__ bias, int c0, int n_classes) {
+  float v[Q][S], add[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int c = min(c0 + STRIDE * q, n_classes - 1);
+    add[q] = bias != nullptr ? bias[c] : 0.0f;
+#pragma unroll
+    for (int s = 0; s < S; ++s) v[q][s] = row[(size_t)s * part_stride + c];
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    float t = add[q];
+#pragma unroll
+    for (int s = 0; s < S; ++s) t += v[q][s];
+    z[q] = c0 + STRIDE * q < n_classes ? t : -INFINITY;
+  }
+}
+template <int Q, int STRIDE>
+__device__ __forceinline__ void fetch_logits(float (&z)[Q], const float* __restrict__ row, int n_parts, long part_stride,
+                                             const float* __restrict__ bias, int c0, int n_classes) {
+  if (n_parts == kMaxLogitSplits) return fetch_logits_parts<Q, STRIDE, kMaxLogitSplits>(z, row, part_stride, bias, c0, n_classes);
+  if (n_parts == 2) return fetch_logits_parts<Q, STRIDE, 2>(z, row, part_stride, bias, c0, n_classes);
+  fetch_logits_parts<Q, STRIDE, 1>(z, row, part_stride, bias, c0, n_classes);
+}
+
 // Softmax cross-entropy head: one wavefront per minibatch row (4 rows per workgroup).  The same
 // launch can carry the row gather of the next iteration in extra workgroups.
 //   row_loss[b] = -log softmax(z_b)[c_b],   delta = (softmax(z) - onehot(c)) / B
@@ -125,16 +155,13 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     return z;
   };
   const int label = yb[r];
-  constexpr int ZR = 16;                             // classes per lane held in registers
+  constexpr int ZR = 4;                              // classes per lane held in registers
   if (n_classes <= ZR * kWave) {
     float z[ZR];
     float mx = -INFINITY;
+    fetch_logits<ZR, kWave>(z, logits + r * ldc, n_parts, part_stride, bias_g, lane, n_classes);
 #pragma unroll
-    for (int q = 0; q < ZR; ++q) {
-      const int c = lane + kWave * q;
-      z[q] = (kWave * q < n_classes && c < n_classes) ? logit(c) : -INFINITY;
-      mx = fmaxf(mx, z[q]);
-    }
+    for (int q = 0; q < ZR; ++q) mx = fmaxf(mx, z[q]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     float zl = 0.0f, se = 0.0f;                      // the label's logit lives in one lane
@@ -142,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     for (int q = 0; q < ZR; ++q) {
       const int c = lane + kWave * q;
       if (c == label && c < n_classes) zl = z[q];
-      z[q] = (kWave * q < n_classes && c < n_classes) ? expf(z[q] - mx) : 0.0f;
+      z[q] = c < n_classes ? expf(z[q] - mx) : 0.0f;
       se += z[q];
     }
 #pragma unroll
@@ -153,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
 #pragma unroll
     for (int q = 0; q < ZR; ++q) {
       const int c = lane + kWave * q;
-      if (kWave * q < ldc && c < ldc) {
+      if (c < ldc) {
         const float d = c < n_classes ? (z[q] / se - (c == label ? 1.0f : 0.0f)) * inv_b : 0.0f;
         if (BF16) reinterpret_cast<uint16_t*>(delta)[r * ldc + c] = f32_to_bf16_rne(d);
         else reinterpret_cast<float*>(delta)[r * ldc + c] = d;
@@ -206,17 +233,9 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_row_kernel(
   constexpr int ZT = 4;                                 // classes per thread
   float z[ZT];
   float mx = -INFINITY;
+  fetch_logits<ZT, kThreads>(z, logits + r * ldc, n_parts, part_stride, bias_g, tid, n_classes);
 #pragma unroll
-  for (int q = 0; q < ZT; ++q) {
-    const int c = tid + kThreads * q;
-    float v = -INFINITY;
-    if (c < n_classes) {                                // bias plus the partial sums in split order
-      v = bias_g != nullptr ? bias_g[c] : 0.0f;
-      for (int s = 0; s < n_parts; ++s) v += logits[(size_t)s * part_stride + r * ldc + c];
-    }
-    z[q] = v;
-    mx = fmaxf(mx, v);
-  }
+  for (int q = 0; q < ZT; ++q) mx = fmaxf(mx, z[q]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
   if (lane == 0) red[0][wave] = mx;
@@ -456,6 +475,7 @@ hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_strid
                                long bias_gs, const int32_t* yb, void* delta, float* row_loss,
                                int n_workers, int batch, int n_classes, int ldc, bool bf16,
                                const int* worker_steps, int step, const GatherArgs* next, hipStream_t s) {
+  if (n_parts != 1 && n_parts != 2 && n_parts != kMaxLogitSplits) return hipErrorInvalidValue;
   GatherArgs ga;
   memset(&ga, 0, sizeof(ga));
   if (next != nullptr) ga = *next;
