@@ -243,9 +243,10 @@ int64_t prsgd_iteration(const prsgd_ctx* ctx);            /* < 0 on a null conte
  * resident at once: whole epochs of one-hidden-layer fp32 MLPs, and prsgd_run on those and on small
  * least-squares problems (N <= 64, d <= 512, B <= 64), whose restarts are exchanges inside the launch.  That holds on a
  * device that runs nothing else (checked at prsgd_init) -- keep the device otherwise idle while such a
- * context is stepping; prsgd_run looks after the process's own contexts: restarts are launches of their own where
- * contexts of other streams could hold the compute units that a launch waits for, and in a stream that is being
- * captured.  If other work did hold compute units, the kernel's bounded wait gives up instead of
+ * context is stepping.  The process's own contexts are looked after: those of several streams that fit the device together
+ * run together; where they do not, a launch that waits follows launches of other streams (by stream events) until it
+ * does, and restarts are launches of their own.  In a stream that is being captured restarts are launches of their own
+ * too, and keeping the graph's launches apart from other contexts is left to the caller.  If other work did hold compute units, the kernel's bounded wait gives up instead of
  * hanging: this call (like every prsgd_read_* call) then returns PRSGD_ESTATE, the replicas are
  * inconsistent, and prsgd_local_steps / prsgd_average / prsgd_run keep returning PRSGD_ESTATE
  * until every replica has been rewritten with prsgd_write_params (worker -1, or each worker

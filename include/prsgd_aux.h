@@ -38,6 +38,22 @@ enum { PRSGD_STREAM_STEPS = 1, PRSGD_STREAM_STEP_MEAN = 2, PRSGD_STREAM_MEAN = 4
 int prsgd_streamed_uses(const prsgd_config* cfg);
 
 /*
+ * Launches whose workgroups wait for each other, of contexts on n_streams streams of one device (n_workers[k] teams of
+ * team[k] workgroups on stream k; least squares: teams of one): PRSGD_WAIT_ALONE for a single stream,
+ * PRSGD_WAIT_TOGETHER if all of them fit the device at once, XCD by XCD, PRSGD_WAIT_CROWDED if not (then they
+ * follow each other by stream events, and restarts are launches of their own).  Host only, for tests.  PRSGD_EINVAL on a
+ * null array, no stream or fewer than eight compute units.
+ */
+enum { PRSGD_WAIT_ALONE = 0, PRSGD_WAIT_TOGETHER = 1, PRSGD_WAIT_CROWDED = 2 };
+int prsgd_waiting_regime(const int32_t* n_workers, const int32_t* team, int32_t n_streams, int32_t compute_units);
+
+/*
+ * out[0]: launches of this context that had restarts inside; out[1]: how often its stream was made to wait for a launch
+ * of another stream.  PRSGD_EINVAL on a null pointer.
+ */
+int prsgd_waiting_launches(const prsgd_ctx* ctx, int64_t* out);
+
+/*
  * Number of polls after which a workgroup of the one-launch epoch kernel stops waiting for its
  * team (see prsgd_status in prsgd.h); the default is 2^22.  Tests set a tiny value to drive the
  * give-up path from the host while every kernel still runs to its end.

@@ -106,10 +106,13 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int n16 = lane & 15, q4 = lane >> 4;
 
-  // team mapping: consecutive workgroups go round-robin to the 8 XCDs; a team stays on one XCD (its
-  // partial logits and the members' minibatch then stay in that XCD's L2).  The grid is filled up to whole rounds.
-  const int slot = blockIdx.x >> 3;
-  const int i = (blockIdx.x & 7) + 8 * (slot / p.P), j = slot % p.P;
+  // team mapping: consecutive workgroups go round-robin to the 8 XCDs.  Pinned: a team stays on one XCD (its
+  // partial logits and the members' minibatch then stay in that XCD's L2); the grid is filled up to whole rounds.  Spread: the
+  // members of a team follow each other, so that every XCD holds its share of any number of workers.  Per iteration, pinned
+  // and spread: 20 x (256-128-10), 8 rows, 5.7 and 6.3 us; 2 x (784-256-10), 32 rows, 11.1 and 11.5 us.
+  const int slot = p.pinned ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
+  const int team = slot / p.P, j = slot - team * p.P;
+  const int i = p.pinned ? ((int)blockIdx.x & 7) + 8 * team : team;
   if (i >= p.n_workers) return;
   const int my_k = p.worker_steps != nullptr ? min(p.worker_steps[i], p.k) : p.k;
   if (my_k <= 0) return;                                   // uniform over the team
@@ -886,23 +889,25 @@ bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sym, kTT, lds_bytes) != hipSuccess)
       return false;
     // a team stays on one of the eight XCDs
-    if ((long)((n_workers + 7) / 8) * pl->P <= (long)per_cu * (cus / 8)) return true;
+    pl->pinned_fits = xcd_workgroups(n_workers, pl->P, true) <= (long)per_cu * (cus / 8);
+    if (pl->pinned_fits) return true;
   }
   return false;
 }
 
-hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, hipStream_t s) {
+hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, bool pinned, hipStream_t s) {
   const void* sym = fused2_pick(pl.KBI, pl.NT, pl.MT, pl.d2p / 16, pl.momentum != 0);
   if (sym == nullptr) return hipErrorInvalidValue;
   if ((pl.momentum != 0) != (args.vel != nullptr)) return hipErrorInvalidValue;
   args.P = pl.P;
   args.shares = pl.shares;
+  args.pinned = pinned ? 1 : 0;
   void* kargs[] = {&args};
   // Plain launch: fused2_plan has checked that the whole grid fits on an otherwise idle device at
   // once, and a team member that never shows up (other work holding compute units) ends in the
   // kernel's bounded wait and the abort flag, not in a hang.
-  return hipLaunchKernel(sym, dim3((unsigned)((args.n_workers + 7) / 8 * 8 * pl.P)), dim3(kTT), kargs,
-                         fused2_lds_bytes(pl), s);
+  const int teams = pinned ? (args.n_workers + 7) / 8 * 8 : args.n_workers;
+  return hipLaunchKernel(sym, dim3((unsigned)(teams * pl.P)), dim3(kTT), kargs, fused2_lds_bytes(pl), s);
 }
 
 }  // namespace prsgd

@@ -195,7 +195,15 @@ struct prsgd_ctx {
   Carve cv;
   bool bf16;
   bool use_fused2;      // one-hidden-layer fp32 MLP: whole epochs in one launch
-  bool enlisted;        // in the table of contexts whose workgroups wait for each other
+  // contexts whose launches have workgroups that wait for each other: the list of all of them, and what the rules of
+  // launches beside each other need of this one
+  bool enlisted;
+  prsgd_ctx* next_waiting;
+  int wait_dev, wait_team;     // device, workgroups per worker
+  long wait_places;            // workgroups that an XCD of it holds, one per compute unit
+  hipEvent_t wait_event;       // behind its newest launch (nullptr: none recorded), and that launch's place among all
+  uint64_t wait_seq;
+  int64_t n_whole, n_followed; // launches with restarts inside; launches of other streams that this one's stream waited for
   bool restarts_in_launch;   // whole runs in one launch: its workgroups exchange the points at a restart
   Fused2Plan f2;
   Streamed streamed;    // launches whose weight traffic is marked non-temporal
@@ -320,6 +328,7 @@ struct Timed {
   } while (0)
 
 int materialize(prsgd_ctx* ctx);
+void strike_waiting(prsgd_ctx* ctx);
 
 // bf16 shadow of W_1 of every replica from its fp32 master (after first-layer kernels that skipped it)
 int refresh_first_shadow(prsgd_ctx* ctx) {
@@ -691,6 +700,7 @@ int workgroups_gave_up(prsgd_ctx* ctx) {
   if (ctx->use_fused2 && ctx->cfg.momentum != 0.0f) ctx->cfg.fused_update = 0;   // the chain applies momentum elementwise
   ctx->use_fused2 = false;
   ctx->restarts_in_launch = false;
+  strike_waiting(ctx);                      // no launch of it waits any more
   ctx->poisoned = true;
   ctx->at_mean = false;
   ctx->n_restored = 0;
@@ -792,85 +802,167 @@ StaticSlot g_static[kMaxStaticDevices];
 float g_static_pad[kMaxStaticDevices][kStaticBytes / sizeof(float)];   // host staging, per device
 std::mutex g_static_mutex;
 
-// Contexts whose launches have workgroups that wait for each other, on any device.  A launch that needs its whole grid
-// resident (restarts inside the launch) only goes out while every such grid that could run beside it fits the
-// device with it: contexts of one stream never run together, those of other streams may, and two half-resident
-// grids would wait for each other until they give up.  Otherwise the restarts are launches of their own.
-struct WaitingUse {
-  const prsgd_ctx* ctx;
-  hipStream_t stream;
-  int dev, workgroups, compute_units;
-};
-constexpr int kMaxWaitingUses = 256;
-WaitingUse g_waiting[kMaxWaitingUses];
-int g_n_waiting = 0, g_waiting_unlisted = 0;     // contexts beyond the table: nobody goes out whole
+// Contexts whose launches have workgroups that wait for each other, on any device.  Such a launch ends only while all that it
+// waits for can be resident.  Launches of one stream follow each other; those of other streams may run beside them, and
+// several half-resident grids would wait for each other until they give up.  So launches that may be under way together
+// have to fit the device together, XCD by XCD, with a compute unit per workgroup (LDS and registers mostly leave no
+// room for a second one):
+//   - the only stream of its device: nothing runs beside it, any grid that its plan has accepted goes out;
+//   - several streams that fit together: likewise, but teams are spread over the XCDs (pinned, the few workers of several
+//     contexts would meet on the first XCDs: five times 2 x (784-256-10), 160 workgroups, would need 80 places on XCD 0);
+//   - several that do not: a launch follows the oldest launches of other streams until those left fit beside it (stream
+//     events), and restarts are launches of their own, so that a stream holds the device for an epoch at a time.
+// A stream that is being captured takes no part: its launches run when the graph is launched, beside anything.
+prsgd_ctx* g_waiting = nullptr;      // list of such contexts
+uint64_t g_waiting_seq = 0;          // launches recorded so far
 std::mutex g_waiting_mutex;
 
-// Workgroups that other streams' contexts may have waiting on `dev`: the largest context of each stream.
-int waiting_beside(int dev, hipStream_t stream) {
-  int total = 0;
-  for (int a = 0; a < g_n_waiting; ++a) {
-    const WaitingUse& u = g_waiting[a];
-    if (u.dev != dev || u.stream == stream) continue;
-    bool largest = true;
-    for (int b = 0; b < g_n_waiting && largest; ++b) {
-      const WaitingUse& o = g_waiting[b];
-      if (b != a && o.dev == dev && o.stream == u.stream &&
-          (o.workgroups > u.workgroups || (o.workgroups == u.workgroups && b < a)))
-        largest = false;
-    }
-    if (largest) total += u.workgroups;
-  }
-  return total;
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();           // the default stream while another one is being captured
+  return true;
 }
-// With g_waiting_mutex held: may this context's grid be launched as one that waits as a whole?
-bool may_wait_as_whole(const prsgd_ctx* ctx) {
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;   // a graph may be launched beside anything
-  if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
-  if (g_waiting_unlisted != 0) return false;
-  for (int a = 0; a < g_n_waiting; ++a) {
-    const WaitingUse& u = g_waiting[a];
-    if (u.ctx != ctx) continue;
-    const int beside = waiting_beside(u.dev, u.stream);
-    return beside == 0 || beside + u.workgroups <= u.compute_units;
-  }
-  return false;
+// The rules below, with g_waiting_mutex held.  A stream is stood for by the first of its contexts in the list.
+bool stands_for_stream(const prsgd_ctx* c) {
+  for (const prsgd_ctx* o = g_waiting; o != c; o = o->next_waiting)
+    if (o->wait_dev == c->wait_dev && o->stream == c->stream) return false;
+  return true;
 }
-// A context that no longer fits beside the others lets their launches under way finish before its own begin.
-hipError_t enlist_waiting(prsgd_ctx* ctx, int workgroups) {
-  WaitingUse u = {ctx, ctx->stream, 0, workgroups, 0};
-  hipError_t e = hipGetDevice(&u.dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&u.compute_units, hipDeviceAttributeMultiprocessorCount, u.dev);
-  if (e != hipSuccess) return e;
-  std::lock_guard<std::mutex> lock(g_waiting_mutex);
-  if (g_n_waiting < kMaxWaitingUses) g_waiting[g_n_waiting++] = u;
-  else ++g_waiting_unlisted;
-  ctx->enlisted = true;
-  if (waiting_beside(u.dev, u.stream) + workgroups <= u.compute_units && g_waiting_unlisted == 0) return hipSuccess;
-  for (int a = 0; a < g_n_waiting; ++a) {
-    if (g_waiting[a].dev != u.dev || g_waiting[a].stream == u.stream) continue;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(g_waiting[a].stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      continue;
+// Workgroups on the fullest XCD of the largest launch in this context's stream.
+long stream_demand(const prsgd_ctx* c, bool pinned) {
+  long most = 0;
+  for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
+    if (o->wait_dev == c->wait_dev && o->stream == c->stream) {
+      const long need = xcd_workgroups(o->cfg.n_workers, o->wait_team, pinned && o->f2.pinned_fits);
+      if (need > most) most = need;
     }
-    e = hipStreamSynchronize(g_waiting[a].stream);
+  return most;
+}
+// Newest recorded launch of this context's stream (nullptr: none).
+const prsgd_ctx* stream_newest(const prsgd_ctx* c) {
+  const prsgd_ctx* newest = nullptr;
+  for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
+    if (o->wait_dev == c->wait_dev && o->stream == c->stream && o->wait_seq != 0 &&
+        (newest == nullptr || o->wait_seq > newest->wait_seq))
+      newest = o;
+  return newest;
+}
+int waiting_regime(long n_streams, long demand, long xcd_places) {
+  return n_streams <= 1 ? PRSGD_WAIT_ALONE : demand <= xcd_places ? PRSGD_WAIT_TOGETHER : PRSGD_WAIT_CROWDED;
+}
+int waiting_regime_of(const prsgd_ctx* ctx) {
+  long n_streams = 0, demand = 0;
+  for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
+    if (o->wait_dev == ctx->wait_dev && stands_for_stream(o)) {
+      ++n_streams;
+      demand += stream_demand(o, false);
+    }
+  return waiting_regime(n_streams, demand, ctx->wait_places);
+}
+// Everything enqueued so far in the context's stream counts as its newest launch.
+hipError_t record_waiting(prsgd_ctx* ctx) {
+  if (ctx->wait_event == nullptr) {
+    const hipError_t e = hipEventCreateWithFlags(&ctx->wait_event, hipEventDisableTiming);
     if (e != hipSuccess) return e;
+  }
+  ctx->wait_seq = ++g_waiting_seq;
+  return hipEventRecord(ctx->wait_event, ctx->stream);
+}
+// Lets the context's stream wait for the oldest launches of other streams until those left fit beside `demand` workgroups per XCD.
+hipError_t follow_others(prsgd_ctx* ctx, long demand, bool pinned) {
+  long total = demand;
+  for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
+    if (o->wait_dev == ctx->wait_dev && o->stream != ctx->stream && stands_for_stream(o) && stream_newest(o) != nullptr)
+      total += stream_demand(o, pinned);
+  uint64_t followed = 0;
+  while (total > ctx->wait_places) {
+    const prsgd_ctx* oldest = nullptr;
+    for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting) {
+      if (o->wait_dev != ctx->wait_dev || o->stream == ctx->stream || !stands_for_stream(o)) continue;
+      const prsgd_ctx* newest = stream_newest(o);
+      if (newest != nullptr && newest->wait_seq > followed && (oldest == nullptr || newest->wait_seq < oldest->wait_seq))
+        oldest = newest;
+    }
+    if (oldest == nullptr) return hipSuccess;
+    const hipError_t e = hipStreamWaitEvent(ctx->stream, oldest->wait_event, 0);
+    if (e != hipSuccess) return e;
+    followed = oldest->wait_seq;
+    total -= stream_demand(oldest, pinned);
+    ++ctx->n_followed;
   }
   return hipSuccess;
 }
-void strike_waiting(const prsgd_ctx* ctx) {
+
+// Around one launch whose workgroups wait for each other.
+struct WaitingLaunch {
+  prsgd_ctx* ctx;
+  std::lock_guard<std::mutex> lock;
+  int regime;
+  bool capturing;
+  explicit WaitingLaunch(prsgd_ctx* c)
+      : ctx(c), lock(g_waiting_mutex), regime(waiting_regime_of(c)), capturing(is_capturing(c->stream)) {}
+  bool may_wait_as_whole() const { return !capturing && regime != PRSGD_WAIT_CROWDED; }
+  bool pinned() const { return ctx->cfg.n_workers % 8 == 0 || (regime == PRSGD_WAIT_ALONE && !capturing && ctx->f2.pinned_fits); }
+  hipError_t before() {
+    if (capturing || regime != PRSGD_WAIT_CROWDED) return hipSuccess;
+    return follow_others(ctx, xcd_workgroups(ctx->cfg.n_workers, ctx->wait_team, false), false);
+  }
+  hipError_t after() { return capturing || regime != PRSGD_WAIT_CROWDED ? hipSuccess : record_waiting(ctx); }
+};
+
+// A context joins the list.  Launches under way were ordered without it: if they (pinned, where their stream was the only
+// one) leave it no room, its own first launches follow them.
+hipError_t enlist_waiting(prsgd_ctx* ctx, int team) {
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  ctx->wait_dev = dev;
+  ctx->wait_places = cus / 8;
+  ctx->wait_team = team;
+  std::lock_guard<std::mutex> lock(g_waiting_mutex);
+  ctx->next_waiting = g_waiting;
+  g_waiting = ctx;
+  ctx->enlisted = true;
+  if (waiting_regime_of(ctx) == PRSGD_WAIT_ALONE) return hipSuccess;
+  long n_others = 0, pinned_beside = 0;
+  for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
+    if (o->wait_dev == dev && o->stream != ctx->stream && stands_for_stream(o)) {
+      ++n_others;
+      pinned_beside += stream_demand(o, true);
+    }
+  const bool pinned = n_others == 1;
+  const long demand = xcd_workgroups(ctx->cfg.n_workers, team, false);
+  if (waiting_regime_of(ctx) == PRSGD_WAIT_TOGETHER && !(pinned && pinned_beside + demand > ctx->wait_places)) return hipSuccess;
+  for (prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
+    if (o->wait_dev == dev && o->stream != ctx->stream && stands_for_stream(o) && !is_capturing(o->stream)) {
+      e = record_waiting(o);
+      if (e != hipSuccess) return e;
+    }
+  return follow_others(ctx, demand, pinned);
+}
+void strike_waiting(prsgd_ctx* ctx) {
   if (!ctx->enlisted) return;
   std::lock_guard<std::mutex> lock(g_waiting_mutex);
-  for (int a = 0; a < g_n_waiting; ++a) {
-    if (g_waiting[a].ctx != ctx) continue;
-    g_waiting[a] = g_waiting[--g_n_waiting];
-    return;
-  }
-  --g_waiting_unlisted;
+  for (prsgd_ctx** at = &g_waiting; *at != nullptr; at = &(*at)->next_waiting)
+    if (*at == ctx) {
+      *at = ctx->next_waiting;
+      break;
+    }
+  ctx->enlisted = false;
+  if (ctx->wait_event != nullptr) (void)hipEventDestroy(ctx->wait_event);
+  ctx->wait_event = nullptr;
+}
+
+// k iterations of every worker in one launch of the epoch kernel.
+int launch_epoch(prsgd_ctx* ctx, int k, const int* worker_steps) {
+  WaitingLaunch waiting(ctx);
+  hipError_t e = waiting.before();
+  if (e != hipSuccess) return hip_fail(ctx, e, "order of launches that wait");
+  LAUNCH(ctx, KK_FUSED2, launch_fused2(ctx->f2, fused2_args(ctx, k, worker_steps), waiting.pinned(), ctx->stream));
+  e = waiting.after();
+  return e == hipSuccess ? PRSGD_OK : hip_fail(ctx, e, "order of launches that wait");
 }
 
 void release_ctx(prsgd_ctx* ctx) {
@@ -925,6 +1017,10 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
   if (cfg->momentum != 0.0f && !bwd_fused_config(ctx->cfg) && !ctx->use_fused2) ctx->cfg.fused_update = 0;
   ctx->restarts_in_launch = ctx->cv.exchange != 0 && (cfg->model == PRSGD_LSQ || ctx->use_fused2);
   ctx->enlisted = false;
+  ctx->next_waiting = nullptr;
+  ctx->wait_event = nullptr;
+  ctx->wait_seq = 0;
+  ctx->n_whole = ctx->n_followed = 0;
   ctx->features = reinterpret_cast<const float*>(features_dev);
   ctx->targets = targets_dev;
   ctx->params = reinterpret_cast<float*>(params_dev);
@@ -975,7 +1071,7 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
                          cfg->n_workers, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e == hipSuccess && (ctx->use_fused2 || ctx->restarts_in_launch))
-    e = enlist_waiting(ctx, ctx->use_fused2 ? cfg->n_workers * ctx->f2.P : cfg->n_workers);
+    e = enlist_waiting(ctx, ctx->use_fused2 ? ctx->f2.P : 1);
   if (e != hipSuccess) {
     hip_fail(nullptr, e, "prsgd_init");
     release_ctx(ctx);
@@ -1048,7 +1144,8 @@ int prsgd_local_steps(prsgd_ctx* ctx, int32_t k) {
   }
   if (ctx->use_fused2) {
     if (k > 0) {
-      LAUNCH(ctx, KK_FUSED2, launch_fused2(ctx->f2, fused2_args(ctx, k, nullptr), ctx->stream));
+      const int rc = launch_epoch(ctx, k, nullptr);
+      if (rc != PRSGD_OK) return rc;
       ctx->at_mean = false;
     }
     ctx->t += k;
@@ -1098,8 +1195,10 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
     return PRSGD_OK;
   }
   if (ctx->use_fused2) {
-    if (k_max > 0)
-      LAUNCH(ctx, KK_FUSED2, launch_fused2(ctx->f2, fused2_args(ctx, k_max, steps_dev), ctx->stream));
+    if (k_max > 0) {
+      const int rc = launch_epoch(ctx, k_max, steps_dev);
+      if (rc != PRSGD_OK) return rc;
+    }
     ctx->t += k_max;
     return PRSGD_OK;
   }
@@ -1167,12 +1266,12 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
     if (k <= interval - (ctx->t % interval)) break;
     if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
     {
-      std::lock_guard<std::mutex> lock(g_waiting_mutex);
-      if (!may_wait_as_whole(ctx)) break;
+      WaitingLaunch waiting(ctx);
+      if (!waiting.may_wait_as_whole()) break;
       if (ctx->use_fused2) {
         Fused2Args a = fused2_args(ctx, k, nullptr);
         a.interval = interval;
-        LAUNCH(ctx, KK_FUSED2, launch_fused2(ctx->f2, a, ctx->stream));
+        LAUNCH(ctx, KK_FUSED2, launch_fused2(ctx->f2, a, waiting.pinned(), ctx->stream));
       } else {
         LsqArgs a = lsq_args(ctx, k);
         a.interval = interval;
@@ -1182,6 +1281,7 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
         a.spin_limit = ctx->spin_limit;
         LAUNCH(ctx, KK_LSQ, launch_lsq_steps(a, ctx->stream));
       }
+      ++ctx->n_whole;
     }
     ctx->at_mean = false;
     ctx->t += k;
@@ -1411,6 +1511,21 @@ int prsgd_streamed_uses(const prsgd_config* cfg) {
   const Streamed u = streamed_uses(*cfg, lo);
   return (u.steps ? PRSGD_STREAM_STEPS : 0) | (u.step_mean ? PRSGD_STREAM_STEP_MEAN : 0) |
          (u.mean ? PRSGD_STREAM_MEAN : 0) | (u.average ? PRSGD_STREAM_AVERAGE : 0);
+}
+
+int prsgd_waiting_regime(const int32_t* n_workers, const int32_t* team, int32_t n_streams, int32_t compute_units) {
+  if (n_workers == nullptr || team == nullptr || n_streams < 1 || compute_units < 8)
+    return set_err(nullptr, PRSGD_EINVAL, "prsgd_waiting_regime: bad argument");
+  long demand = 0;
+  for (int k = 0; k < n_streams; ++k) demand += xcd_workgroups(n_workers[k], team[k], false);
+  return waiting_regime(n_streams, demand, compute_units / 8);
+}
+
+int prsgd_waiting_launches(const prsgd_ctx* ctx, int64_t* out) {
+  if (ctx == nullptr || out == nullptr) return PRSGD_EINVAL;
+  out[0] = ctx->n_whole;
+  out[1] = ctx->n_followed;
+  return PRSGD_OK;
 }
 
 int prsgd_status(prsgd_ctx* ctx) {

@@ -112,13 +112,14 @@ struct Fused2Plan {
   int d2p, KB;         // padded class count, 16-column blocks of the gathered batch
   int momentum;        // 1: the variant that carries velocities
   int shares;          // places for partial pre-activations in LDS
+  bool pinned_fits;    // all teams resident with each on one XCD
 };
 struct Fused2Args {
   const float* features; const int32_t* labels;
   float* params; long m_pad; long w1_off, b1_off, w2_off, b2_off; int ld1, ld2;
   const float* src; long src_stride;   // starting point of every worker: its replica, or the shared
                                        // node average (stride 0) right after a restart
-  int n_workers, P, shares, d0, d1, d2, batch; long rows; int log2n;
+  int n_workers, P, shares, pinned, d0, d1, d2, batch; long rows; int log2n;
   int act; float lr; uint64_t seed; uint64_t t0; int k;
   const int* worker_steps;       // Algorithm 3 step counts (nullptr: every worker takes k steps)
   int interval;                  // > 0: restarts inside the launch
@@ -139,7 +140,12 @@ __host__ __device__ constexpr int fused2_flag_stride(int members) { return (memb
 size_t fused2_exchange_floats(int n_workers, int d0, int d1, int d2);
 bool fused2_shape(int d0, int d1, int d2, int batch, bool momentum);
 bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum, Fused2Plan* pl);
-hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, hipStream_t s);
+hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, bool pinned, hipStream_t s);
+// Workgroups that n_workers teams put on the fullest of the eight XCDs: pinned, a team stays on XCD i mod 8; spread, the
+// workgroups are dealt to the XCDs in turn.
+constexpr long xcd_workgroups(long n_workers, long team, bool pinned) {
+  return pinned ? (n_workers + 7) / 8 * team : (n_workers * team + 7) / 8;
+}
 const char* kernel_kind_name(int kind);
 
 // ---- launchers (each returns the hipError_t of the launch) --------------------------------

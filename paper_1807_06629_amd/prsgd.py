@@ -25,6 +25,7 @@ PRSGD_TANH, PRSGD_RELU = 0, 1
 PRSGD_F32, PRSGD_BF16 = 0, 1
 PRSGD_MOM_KEEP, PRSGD_MOM_AVERAGE, PRSGD_MOM_RESET = 0, 1, 2
 PRSGD_MAX_DIMS = 16
+PRSGD_WAIT_ALONE, PRSGD_WAIT_TOGETHER, PRSGD_WAIT_CROWDED = 0, 1, 2
 PRSGD_STREAM_STEPS, PRSGD_STREAM_STEP_MEAN, PRSGD_STREAM_MEAN, PRSGD_STREAM_AVERAGE = 1, 2, 4, 8
 
 
@@ -85,6 +86,8 @@ def _load() -> ctypes.CDLL:
         "prsgd_copy_bytes": (ctypes.c_int, [vp, vp, sz, vp]),
         "prsgd_product_tile": (ctypes.c_int, [i32, i32, i32, i32, vp]),
         "prsgd_streamed_uses": (ctypes.c_int, [cfgp]),
+        "prsgd_waiting_regime": (ctypes.c_int, [vp, vp, i32, i32]),
+        "prsgd_waiting_launches": (ctypes.c_int, [vp, vp]),
         "prsgd_time_varying_schedule": (ctypes.c_int, [i32, i32, vp, vp]),
         "prsgd_status": (ctypes.c_int, [vp]),
         "prsgd_set_epoch_wait_limit": (ctypes.c_int, [vp, ctypes.c_uint32]),
@@ -350,6 +353,22 @@ def prsgd_streamed_uses(cfg: prsgd_config) -> int:
     if rc < 0:
         _check(rc)
     return rc
+
+
+def prsgd_waiting_regime(n_workers: Sequence[int], team: Sequence[int], compute_units: int = 256) -> int:
+    n, t = np.ascontiguousarray(n_workers, dtype=np.int32), np.ascontiguousarray(team, dtype=np.int32)
+    if n.shape != t.shape or n.ndim != 1:
+        raise ValueError("one team size per stream")
+    rc = _lib.prsgd_waiting_regime(n.ctypes.data, t.ctypes.data, n.size, int(compute_units))
+    if rc < 0:
+        _check(rc)
+    return rc
+
+
+def prsgd_waiting_launches(h: Handle):
+    out = (ctypes.c_int64 * 2)()
+    _check(_lib.prsgd_waiting_launches(h.ctx, out), h.ctx)
+    return tuple(out)
 
 
 def prsgd_set_lr(h: Handle, lr: float) -> None:

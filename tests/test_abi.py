@@ -111,6 +111,24 @@ def test_streamed_averages_go_by_what_is_read_again(P, dims, n_workers, mean, av
     assert bool(uses & P.PRSGD_STREAM_AVERAGE) == average
 
 
+@pytest.mark.parametrize("streams,regime", [
+    ([(64, 16)], "ALONE"),                                   # whatever its own plan took
+    ([(8, 16), (8, 16)], "TOGETHER"),                        # 16 + 16 of 32 places on every XCD
+    ([(8, 16), (8, 16), (1, 1)], "CROWDED"),
+    ([(2, 16)] * 5, "TOGETHER"),                             # spread: 4 each, where pinned teams would need 80 on XCD 0
+    ([(1, 32), (1, 32)], "TOGETHER"),                        # 4 + 4, where pinned each would take all of XCD 0
+    ([(1, 32)] * 8, "TOGETHER"),
+    ([(1, 32)] * 9, "CROWDED"),
+    ([(9, 16), (7, 16)], "TOGETHER"),                        # 18 + 14
+    ([(9, 16), (7, 16), (1, 1)], "CROWDED"),
+    ([(64, 1)] * 4, "TOGETHER"),                             # least squares: 8 each
+    ([(64, 1)] * 5, "CROWDED"),
+])
+def test_launches_that_wait_are_counted_by_xcd(P, streams, regime):
+    got = P.prsgd_waiting_regime([n for n, _ in streams], [t for _, t in streams], 256)
+    assert got == getattr(P, "PRSGD_WAIT_" + regime)
+
+
 def test_null_context_calls_return_einval(P):
     assert P._lib.prsgd_local_steps(None, 1) == P.PRSGD_EINVAL
     assert P._lib.prsgd_average(None) == P.PRSGD_EINVAL
@@ -118,6 +136,8 @@ def test_null_context_calls_return_einval(P):
     assert P._lib.prsgd_read_params(None, 0, None, 0) == P.PRSGD_EINVAL
     assert P._lib.prsgd_iteration(None) == -1
     assert P._lib.prsgd_destroy(None) == P.PRSGD_EINVAL
+    assert P._lib.prsgd_waiting_regime(None, None, 1, 256) == P.PRSGD_EINVAL
+    assert P._lib.prsgd_waiting_launches(None, None) == P.PRSGD_EINVAL
 
 
 def test_theorem2_schedule_of_the_library(P):

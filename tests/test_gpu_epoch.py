@@ -88,3 +88,64 @@ def test_contexts_of_three_streams_together(P, D):
     for h in handles:
         assert np.array_equal(D.read_all(h), want)
         P.prsgd_destroy(h)
+
+
+def test_small_contexts_of_several_streams_run_together(P, D):
+    """Five contexts of two teams of 16 fit the device together once their teams are spread over the XCDs; the first of them
+    has run alone (teams on XCDs 0 and 1) before the others come."""
+    w = small_mlp(dims=(784, 256, 10), batch=32, n_workers=2, rows_per_worker=128, interval=2, iterations=12)
+    inp = inputs_for(w)
+    assert P.prsgd_waiting_regime([2] * 5, [16] * 5) == P.PRSGD_WAIT_TOGETHER
+    handles = [D.open_workload(w, inp, stream=torch.cuda.Stream())]
+    P.prsgd_run(handles[0], w.iterations, w.interval)
+    want = D.read_all(handles[0])
+    P.prsgd_write_params(handles[0], -1, inp["x0"])
+    P.prsgd_set_iteration(handles[0], 0)
+    handles += [D.open_workload(w, inp, stream=torch.cuda.Stream()) for _ in range(4)]
+    before = [P.prsgd_waiting_launches(h)[0] for h in handles]
+    for _ in range(2):
+        for h in handles:
+            P.prsgd_run(h, w.iterations // 2, w.interval)
+    for h, n in zip(handles, before):
+        assert P.prsgd_waiting_launches(h) == (n + 2, 0)
+        assert np.array_equal(D.read_all(h), want)
+        P.prsgd_destroy(h)
+
+
+def test_contexts_that_do_not_fit_follow_each_other(P, D):
+    """Three grids of 16 workgroups per XCD: two fit, so the launches of a third stream follow one of theirs."""
+    w = small_mlp(dims=(784, 256, 10), batch=32, n_workers=8, rows_per_worker=128, interval=3, iterations=9)
+    inp = inputs_for(w)
+    assert P.prsgd_waiting_regime([8] * 3, [16] * 3) == P.PRSGD_WAIT_CROWDED
+    handles = [D.open_workload(w, inp, stream=torch.cuda.Stream()) for _ in range(3)]
+    for _ in range(3):
+        for h in handles:
+            P.prsgd_local_steps(h, 3)
+            P.prsgd_average(h)
+    got = [D.read_all(h) for h in handles]
+    counts = [P.prsgd_waiting_launches(h) for h in handles]
+    assert all(c[0] == 0 for c in counts) and sum(c[1] for c in counts) >= 7, counts
+    for h in handles[1:]:
+        P.prsgd_destroy(h)
+    P.prsgd_write_params(handles[0], -1, inp["x0"])
+    P.prsgd_set_iteration(handles[0], 0)
+    P.prsgd_run(handles[0], w.iterations, w.interval)             # alone again: in one launch
+    assert P.prsgd_waiting_launches(handles[0])[0] == 1
+    want = D.read_all(handles[0])
+    P.prsgd_destroy(handles[0])
+    for g in got:
+        assert np.array_equal(g, want)
+
+
+def test_a_context_that_comes_during_a_pinned_launch_follows_it(P, D):
+    """Alone, two teams of 32 take XCDs 0 and 1 whole: what is launched on another stream meanwhile goes behind them."""
+    w = small_mlp(dims=(784, 512, 10), batch=32, n_workers=2, rows_per_worker=128, interval=4, iterations=600, lr=0.002)
+    inp = inputs_for(w)
+    a = D.open_workload(w, inp, stream=torch.cuda.Stream())
+    P.prsgd_run(a, w.iterations, w.interval)
+    b = D.open_workload(w, inp, stream=torch.cuda.Stream())
+    P.prsgd_run(b, w.iterations, w.interval)
+    assert P.prsgd_waiting_launches(a) == (1, 0) and P.prsgd_waiting_launches(b) == (1, 1)
+    assert np.array_equal(D.read_all(a), D.read_all(b))
+    P.prsgd_destroy(a)
+    P.prsgd_destroy(b)
