@@ -29,11 +29,11 @@
 //
 // Every wait is bounded; giving up raises the abort flag, which ends every workgroup.
 //
-// What bounds it: latency.  Of the 24,000 cycles of an iteration of 784-256-10 (8 workers, 32 rows) the exchange takes 6,800, the
+// What bounds it: latency.  Of the 22,600 cycles of an iteration of 784-256-10 (8 workers, 32 rows) the exchange takes 5,400, the
 // two large products 5,700 each (3,500 at the matrix cores' rate; two wavefronts per SIMD, 7 blocks on the busiest), the requests of
 // the next minibatch 2,500, the small phases 900 to 1,400 each.  Per iteration, against an arrival counter, partials and minibatch as
 // loads of their own and a launch per epoch (widths that are no multiple of 16, or of 4 for the input: against the
-// chain of per-layer launches): 784-256-10 with interval 16 12.3 and 11.3 us, 64 workers of 256-128-10 with
+// chain of per-layer launches): 784-256-10 with interval 16 12.3 and 10.6 us, 64 workers of 256-128-10 with
 // 8 rows, interval 8, 7.8 and 7.2 us, 4 workers of 300-100-10, 20 rows, interval 4, 26.6 and 8.9 us, 30 workers of
 // 1023-255-15, 30 rows, 46.7 and 25.6 us.  A restart inside the launch takes 7 us with 0.5 MB of replicas and 14 us
 // with 9 MB (the agent-scope traffic of all workgroups), 3 to 5 us less than the end of a launch, the averaging launch and a new
@@ -50,7 +50,7 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kTT = 512;                      // threads per team member: two wavefronts per SIMD, so
 constexpr int kTW = kTT / kWave;              // that the latency-bound phases of one overlap the other's
 constexpr int kPollers = kTT - kWave;         // threads that sum the partial logits: all but the drawing wavefront
-// Partial logits of a team from which they are summed in two hops: 16 x 320 floats 9,200 cycles in one, 6,800 in two; with 4 x 80 one
+// Partial logits of a team from which they are summed in two hops: 16 x 320 floats 9,200 cycles in one, 5,400 in two; with 4 x 80 one
 // takes 3,000, which a second would double.
 constexpr int kTwoHopFloats = 2048;
 constexpr int kAgentScope = 16;               // buffer access cache policy: the sc1 bit (agent scope)
@@ -450,6 +450,12 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
   const int E = B * d2;
   const bool two_hops = p.P * E >= kTwoHopFloats;
   const int share = (E + p.P - 1) / p.P, share_lo = min(E, j * share), share_hi = min(E, share_lo + share);
+  // Groups of lanes of a wavefront that add the partials of one float of the share, each every hop_groups-th member: a member's
+  // share is small where the team is large, and one thread per float would ask for P / 8 rounds of partials in turn.  A group's lanes
+  // take consecutive floats (16 lanes of 16 members each instead: 8 x (784-256-10) 10.6 -> 12.1 us per iteration).  Against a
+  // thread per float: 4 x (784-1024-10) 17.2 -> 12.5 us, 1 x (256-4096-10) 29.9 -> 8.7, 8 x (784-256-10) 11.2 -> 10.6.
+  int hop_groups = 1;
+  while (hop_groups < 32 && 8 * hop_groups < p.P) hop_groups *= 2;
   const int G = two_hops ? 1 : max(1, min(p.P, kPollers / E));
   const int PG = (p.P + G - 1) / G;
   // this thread's first float, and the members it adds (with several groups a thread has one float at most)
@@ -584,10 +590,15 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
       polls = 0;
       if (two_hops) {
         unsigned long long* sums = p.part + (size_t)2 * members * E + (size_t)((number & 1) * p.n_workers + i) * E;
-        for (int e = share_lo + tid; e < share_hi; e += kPollers) {
-          const float sum = polled_sum(team_part, e, E, p.P, number);
-          __hip_atomic_store(at(sums, 8u * (uint32_t)e), ((unsigned long long)number << 32) | __float_as_uint(sum),
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int items = kWave / hop_groups, l = lane / items;
+        for (int e0 = share_lo + wave * items; e0 < share_hi; e0 += (kTW - 1) * items) {
+          const int e = e0 + (lane & (items - 1));
+          float sum = polled_sum(team_part, l * E + e, hop_groups * E,
+                                 e < share_hi ? (p.P - l + hop_groups - 1) / hop_groups : 0, number);
+          for (int o = items; o < kWave; o <<= 1) sum += __shfl_xor(sum, o);
+          if (l == 0 && e < share_hi)
+            __hip_atomic_store(at(sums, 8u * (uint32_t)e), ((unsigned long long)number << 32) | __float_as_uint(sum),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         for (int e = tid; e < E; e += kPollers) lgp[e] = polled_sum(sums, e, 0, 1, number);
       } else if (has_item) {
@@ -838,11 +849,13 @@ static const void* fused2_pick(int kbi, int nt, int mt, int ct, bool mom) {
   return nullptr;
 }
 
-// Shapes the epoch kernel is written for (whether the team fits the device is the plan's question).  Momentum on hidden
-// layers that are not whole tiles stays with the per-layer chain.
-bool fused2_shape(int d0, int d1, int d2, int batch, bool momentum) {
+// Shapes the epoch kernel is written for (whether the teams fit the device is the plan's question), with any hidden width: per
+// iteration of the epoch kernel and of the chain, 2 x (100-1999-10), 16 rows, 7.3 and 27 us, 1 x (783-900-10), 16 rows, 12 and 28 us.
+// Momentum on ragged inputs or hidden layers stays with the per-layer chain.
+bool fused2_shape(int n_workers, int d0, int d1, int d2, int batch, bool momentum) {
   if (momentum && ((d0 & 3) != 0 || (d1 & 15) != 0)) return false;
-  return d0 >= 1 && d0 <= 1024 && d1 >= 1 && d1 <= kFused2MaxHidden && d2 <= 64 && batch <= 64;
+  return d0 >= 1 && d0 <= 1024 && d1 >= 1 && d2 <= 64 && batch <= 64 &&
+         (long)n_workers * ((d1 + 31L) / 32) <= kFused2MaxMembers;
 }
 
 // Floats that the restarts inside a launch pass through memory: a slice per member, and the averages.  0: no plan can
@@ -860,9 +873,10 @@ size_t fused2_exchange_floats(int n_workers, int d0, int d1, int d2) {
 }
 
 // Decides whether the epoch kernel applies and how the team is shaped.  It needs every
-// workgroup of the grid resident at once (checked against the occupancy the runtime reports).
+// workgroup of the grid resident at once (checked against the occupancy the runtime reports), spread over the XCDs.  Narrow
+// slices first: 20 x (784-192-10), 32 rows, teams of 12 spread 11.4 us per iteration, teams of 6 on an XCD each 15.7.
 bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum, Fused2Plan* pl) {
-  if (!fused2_shape(d0, d1, d2, batch, momentum)) return false;
+  if (!fused2_shape(n_workers, d0, d1, d2, batch, momentum)) return false;
   pl->momentum = momentum ? 1 : 0;
   pl->MT = (batch + 15) / 16;
   pl->KB = (d0 + 15) / 16;
@@ -888,9 +902,10 @@ bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sym, kTT, lds_bytes) != hipSuccess)
       return false;
-    // a team stays on one of the eight XCDs
-    pl->pinned_fits = xcd_workgroups(n_workers, pl->P, true) <= (long)per_cu * (cus / 8);
-    if (pl->pinned_fits) return true;
+    const long places = (long)per_cu * (cus / 8);
+    if (xcd_workgroups(n_workers, pl->P, false) > places) continue;
+    pl->pinned_fits = xcd_workgroups(n_workers, pl->P, true) <= places;
+    return true;
   }
   return false;
 }

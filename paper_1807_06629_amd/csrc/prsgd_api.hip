@@ -95,7 +95,7 @@ bool bwd_fused_config(const prsgd_config& c) {
 // shapes the epoch kernel may take (whether it does is decided at init, on the device)
 bool epoch_candidate(const prsgd_config& c) {
   return c.model == PRSGD_MLP && c.gemm_dtype == PRSGD_F32 && c.n_dims == 3 && c.fused_update &&
-         prsgd::fused2_shape(c.dims[0], c.dims[1], c.dims[2], c.batch, c.momentum != 0.0f);
+         prsgd::fused2_shape(c.n_workers, c.dims[0], c.dims[1], c.dims[2], c.batch, c.momentum != 0.0f);
 }
 prsgd_config effective_config(const prsgd_config* c) {
   prsgd_config e = *c;

@@ -134,11 +134,11 @@ struct Fused2Args {
 };
 constexpr unsigned int kFused2SpinLimit = 1u << 22;   // default bound of the team barrier's wait
 size_t fused2_lds_bytes(const Fused2Plan& pl);
-constexpr int kFused2MaxHidden = 512, kFused2MaxMembers = 1024;
+constexpr int kFused2MaxMembers = 1024;      // workgroups of 512 threads that 256 compute units hold
 // bytes between the copies of the flags: a line each, on different memory channels
 __host__ __device__ constexpr int fused2_flag_stride(int members) { return (members + 255) / 256 * 256 + 256; }
 size_t fused2_exchange_floats(int n_workers, int d0, int d1, int d2);
-bool fused2_shape(int d0, int d1, int d2, int batch, bool momentum);
+bool fused2_shape(int n_workers, int d0, int d1, int d2, int batch, bool momentum);
 bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum, Fused2Plan* pl);
 hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, bool pinned, hipStream_t s);
 // Workgroups that n_workers teams put on the fullest of the eight XCDs: pinned, a team stays on XCD i mod 8; spread, the

@@ -41,6 +41,16 @@ SHAPES = [
     dict(dims=(1023, 48, 10), batch=20, n_workers=2),             # 64 row blocks, single words
     dict(dims=(1024, 64, 10), batch=30, n_workers=20),            # quarters of the restart sum by groups of threads
     dict(dims=(96, 64, 10), batch=8, n_workers=33),
+    # teams that fit the device but not with each on one XCD (4 or 5 teams of 7 to 12 on the first ones)
+    dict(dims=(784, 192, 10), batch=32, n_workers=20),
+    dict(dims=(784, 224, 10), batch=32, n_workers=33),
+    dict(dims=(784, 160, 10), batch=32, n_workers=51),
+    # teams of 44, 64, 125 and 256: the first hop in 8, 8, 16 and 32 groups of lanes
+    dict(dims=(64, 700, 10), batch=8, n_workers=3),
+    dict(dims=(784, 1024, 10), batch=32, n_workers=4),
+    dict(dims=(100, 1999, 10), batch=16, n_workers=2),
+    dict(dims=(256, 4096, 10), batch=16, n_workers=1),
+    dict(dims=(33, 600, 3), batch=1, n_workers=5),                # 38 members, one hop
 ]
 
 
