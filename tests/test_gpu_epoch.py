@@ -51,6 +51,10 @@ SHAPES = [
     dict(dims=(100, 1999, 10), batch=16, n_workers=2),
     dict(dims=(256, 4096, 10), batch=16, n_workers=1),
     dict(dims=(33, 600, 3), batch=1, n_workers=5),                # 38 members, one hop
+    # class rows of 64 with their chunks exchanged; sums of the second hop in batches (1300, 3072 and 4096 floats)
+    dict(dims=(100, 48, 26), batch=50, n_workers=3),
+    dict(dims=(256, 128, 48), batch=64, n_workers=2),
+    dict(dims=(128, 50, 64), batch=64, n_workers=2),
 ]
 
 
