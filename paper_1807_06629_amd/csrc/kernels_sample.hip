@@ -502,12 +502,14 @@ hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_strid
   return hipGetLastError();
 }
 
-// A workgroup reads all of W_L for its 16 rows: up to kHeadBytes of it the launch saved is worth more (bf16
-// with at most 16 classes, whose product has a split contraction to pay for as well: always).
+// A workgroup multiplies its 16 rows with all of W_L, in class tiles of 16 or 64: up to kHeadBytes of it in whole tiles the launch
+// saved is worth more (bf16 with at most 16 classes, whose product has a split contraction to pay for as well: always).  By
+// W_L's own bytes, 1024 x 17 in fp32 would be taken too and loses: 4 workers of 128-64-1024-17, 256 rows, 55.2 us per iteration
+// with the product apart and 58.9 here, 16 workers, 64 rows, 51.8 and 55.6.
 constexpr long kHeadBytes = 128 << 10;
 bool softmax_narrow_applies(int n_classes, int ldc, int k_dim, bool bf16) {
   if (n_classes < 1 || n_classes > kHeadClasses || ldc > kHeadClasses || (ldc & 7) != 0) return false;
-  return (bf16 && n_classes <= 16) || (long)k_dim * ldc * (bf16 ? 2 : 4) <= kHeadBytes;
+  return (bf16 && n_classes <= 16) || (long)k_dim * (ldc <= 16 ? 16 : 64) * (bf16 ? 2 : 4) <= kHeadBytes;
 }
 
 hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_dim, const void* w,

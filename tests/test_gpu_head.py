@@ -37,6 +37,8 @@ SHAPES = [
     ("f32", 130, 64, 65, 2, True),
     ("f32", 512, 64, 20, 2, True),
     ("f32", 513, 64, 20, 2, False),
+    ("f32", 512, 20, 20, 2, True),                   # tiles of 64 count, not the classes' own bytes
+    ("f32", 1024, 17, 20, 2, False),
 ]
 
 
