@@ -305,9 +305,10 @@ template <int R> __device__ __forceinline__ void wave_sums(float (&v)[R], int la
 }
 
 // Iterations requested ahead by each of W wavefronts with `floats` floats per lane in each: what 128 KB of LDS hold, at
-// most 63 requests in flight across a wait, and eight (sixteen are no faster).
-constexpr int resident_depth(int floats, int W, bool v4) {
-  int depth = 512 / W / floats;
+// most 63 requests in flight across a wait, and eight (sixteen are no faster).  Many workers: what 32 KB hold, and one at least.
+constexpr int resident_depth(int floats, int W, bool v4, bool many) {
+  int depth = (many ? 128 : 512) / W / floats;
+  if (depth < 1) depth = 1;
   const int in_flight = 1 + 63 / (v4 ? floats / 4 : floats);
   if (depth > in_flight) depth = in_flight;
   return depth > 8 ? 8 : depth;
@@ -333,26 +334,26 @@ constexpr int resident_depth(int floats, int W, bool v4) {
 // can only publish restart e + 2 after everybody has read restart e.  The wait is bounded; on giving up, the abort
 // flag ends every workgroup without writing.  A restart takes 1.4 us with 4 workers of 64 floats and 2 us with 64, against
 // 17 us for ending a launch, the averaging launch and the start of the next.
-template <int CPL, int R, int W, bool V4>
+template <int CPL, int R, int W, bool V4, bool MANY>
 __global__ __launch_bounds__(64 * W) void lsq_resident_kernel(LsqArgs p) {
   static_assert(R == 1 || R == 2 || R == 4 || R == 8, "rows of a wavefront are words of one or two Philox calls");
   constexpr int DC = 64 * CPL;                      // columns held
   static_assert(!V4 || R * CPL >= 4, "a request of 16 bytes per lane is 256 floats");
   constexpr int REQ = V4 ? R * CPL / 4 : R * CPL;   // requests per wavefront and iteration
-  constexpr int D = resident_depth(R * CPL, W, V4);
+  constexpr int D = resident_depth(R * CPL, W, V4, MANY);
   static_assert((D - 1) * REQ <= 63, "requests that a wait can leave in flight");
   constexpr bool kOwnSum = W > 4;                   // a column is added by one thread
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];   // [W][D][R][DC] requested rows
   __shared__ float part[kOwnSum ? 1 : 2][W][DC];
-  __shared__ float xs[DC];
-  __shared__ float quarter[4][DC];                  // sums of a restart
+  __shared__ float xs[kOwnSum ? DC : 1];
+  __shared__ float quarter[4][MANY ? 1 : DC];       // sums of a restart
   __shared__ float resl[W * R];
   __shared__ int bad;
 
   const int i = blockIdx.x;
   const int my_k = p.worker_steps != nullptr ? min(p.worker_steps[i], p.k) : p.k;
   if (my_k <= 0) return;
-  const bool restarts = p.interval > 0;
+  const bool restarts = !MANY && p.interval > 0;
   uint32_t tag = 0;
   if (restarts) {
     if (__hip_atomic_load(p.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
@@ -554,7 +555,9 @@ __global__ __launch_bounds__(64 * W) void lsq_resident_kernel(LsqArgs p) {
   for (int s = 0; s < my_k; ++s) {
     if (((s + D) & 63) == 0) draw((s + D) >> 6);
     if ((s & 63) == 0 && s > 0) take_targets();
-    request(s + D, place);                  // this iteration's rows are in registers
+    // This iteration's rows are in registers.  A wavefront past the minibatch keeps the rows of the first D iterations, which
+    // meet residuals of zero.
+    if (n_rows > 0) request(s + D, place);
     place = place + 1 == D ? 0 : place + 1;
     float res[R];
 #pragma unroll
@@ -653,11 +656,15 @@ __global__ __launch_bounds__(64 * W) void lsq_resident_kernel(LsqArgs p) {
 }
 
 constexpr int kResidentDim = 512, kResidentBatch = 64;
+// From more workers than compute units on, several workgroups have to share one, and each hides the others' latency: rings of a
+// quarter, no restart sums.  Per iteration with a launch after every eighth, rings of 128 KB and of 32 KB: 512 x (64 x 64) 4.4 and
+// 3.1 us, 1024 x (1 x 512) 7.0 and 4.3, 4000 x (32 x 128) 27.7 and 15.8 (staged kernel 5.5, 4.4 and 19.9).
+constexpr int kManyWorkers = 256;
 static bool lsq_resident(int d, int batch) { return d <= kResidentDim && batch <= kResidentBatch; }
 
-template <int CPL, int R, int W, bool V4> static hipError_t launch_resident_v(const LsqArgs& p, hipStream_t s) {
-  constexpr size_t kRing = (size_t)W * resident_depth(R * CPL, W, V4) * R * CPL * 256;
-  auto kernel = lsq_resident_kernel<CPL, R, W, V4>;
+template <int CPL, int R, int W, bool V4, bool MANY> static hipError_t launch_resident_v(const LsqArgs& p, hipStream_t s) {
+  constexpr size_t kRing = (size_t)W * resident_depth(R * CPL, W, V4, MANY) * R * CPL * 256;
+  auto kernel = lsq_resident_kernel<CPL, R, W, V4, MANY>;
   static std::atomic<bool> configured{false};
   if (!configured.load(std::memory_order_acquire)) {      // rows and shares can exceed the 64 KB default
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -669,10 +676,12 @@ template <int CPL, int R, int W, bool V4> static hipError_t launch_resident_v(co
   return hipGetLastError();
 }
 template <int CPL, int R, int W> static hipError_t launch_resident(const LsqArgs& p, hipStream_t s) {
+  const bool many = p.n_workers > kManyWorkers;
   if constexpr (R * CPL >= 4) {
-    if ((p.d & 3) == 0) return launch_resident_v<CPL, R, W, true>(p, s);     // 16-byte aligned rows
+    if ((p.d & 3) == 0)                                                      // 16-byte aligned rows
+      return many ? launch_resident_v<CPL, R, W, true, true>(p, s) : launch_resident_v<CPL, R, W, true, false>(p, s);
   }
-  return launch_resident_v<CPL, R, W, false>(p, s);
+  return many ? launch_resident_v<CPL, R, W, false, true>(p, s) : launch_resident_v<CPL, R, W, false, false>(p, s);
 }
 template <int CPL> static hipError_t launch_resident_rows(const LsqArgs& p, hipStream_t s) {
   if (p.batch <= 4) return launch_resident<CPL, 1, 4>(p, s);

@@ -40,6 +40,8 @@ def _problem(d, batch, n, interval, iterations=70, momentum=0.0):
 @pytest.mark.parametrize("d,batch,n,interval", [
     (1, 1, 2, 1), (63, 4, 3, 3), (64, 5, 7, 1), (65, 8, 8, 2), (100, 3, 4, 5), (128, 9, 9, 7), (129, 16, 13, 64),
     (256, 17, 5, 65), (257, 32, 6, 4), (300, 33, 17, 1), (511, 64, 4, 9), (512, 64, 64, 6), (512, 1, 2, 70), (4, 64, 33, 1),
+    # more workers than compute units: the shorter rings, of one to eight iterations
+    (3, 1, 257, 8), (64, 16, 300, 5), (100, 6, 257, 7), (130, 30, 260, 9), (512, 1, 257, 9), (511, 16, 258, 4), (512, 64, 257, 3),
 ])
 def test_run_in_one_launch(P, D, d, batch, n, interval, momentum):
     w, inp = _problem(d, batch, n, interval, momentum=momentum)
