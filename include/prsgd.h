@@ -110,9 +110,11 @@ int prsgd_init(const prsgd_config* cfg, const float* x0_host, const void* featur
  * array inside the library, PRSGD_STATIC_WORKSPACE_BYTES per device, held by every device the
  * library runs on until the process ends.  The call itself allocates nothing, neither on the
  * device nor on the host (the context and its staging buffer live in static storage too); the
- * caller still passes the shards and the replica buffer.  A configuration whose
- * prsgd_workspace_bytes exceeds the limit is refused with PRSGD_EINVAL (the limit covers the
- * small, latency-bound configurations: c1, c2, c4); device indices 0..7.  All static contexts of a
+ * caller still passes the shards and the replica buffer.  A configuration whose workspace
+ * exceeds the limit is refused with PRSGD_EINVAL (the limit covers the small, latency-bound
+ * configurations: c1, c2, c4); one that only exceeds it by scratch that prsgd_workspace_bytes
+ * includes to keep restarts, or else whole epochs, inside a launch goes without that scratch.
+ * Device indices 0..7.  All static contexts of a
  * device share the one array, so only one may be live per device at a time: a second call before
  * prsgd_destroy returns PRSGD_ESTATE.  The array keeps what the previous context left in it;
  * the call clears what the new one needs.  Everything else (errors, stream, ownership) as

@@ -38,6 +38,14 @@ enum { PRSGD_STREAM_STEPS = 1, PRSGD_STREAM_STEP_MEAN = 2, PRSGD_STREAM_MEAN = 4
 int prsgd_streamed_uses(const prsgd_config* cfg);
 
 /*
+ * What prsgd_init_static leaves a configuration of the scratch that is no part of the method: PRSGD_SCRATCH_RUNS all of
+ * it, PRSGD_SCRATCH_EPOCHS without what keeps restarts inside a launch, PRSGD_SCRATCH_LAYERS without what the one-launch
+ * epoch kernel exchanges.  Host only, for tests.  PRSGD_EINVAL on an invalid configuration and on one that does not fit.
+ */
+enum { PRSGD_SCRATCH_LAYERS = 0, PRSGD_SCRATCH_EPOCHS = 1, PRSGD_SCRATCH_RUNS = 2 };
+int prsgd_static_scratch(const prsgd_config* cfg);
+
+/*
  * Launches whose workgroups wait for each other, of contexts on n_streams streams of one device (n_workers[k] teams of
  * team[k] workgroups on stream k; least squares: teams of one): PRSGD_WAIT_ALONE for a single stream,
  * PRSGD_WAIT_TOGETHER if all of them fit the device at once, XCD by XCD, PRSGD_WAIT_CROWDED if not (then they

@@ -17,7 +17,9 @@
 //     8-byte store, and polls the others' data itself (no arrival counter, no second trip for the data),
 //     summing the P partials in fixed order; everything after that (softmax, both delta blocks, dW_2, db, dW_1)
 //     is local to the slice.  Two sets of slots alternate: a member can only publish iteration t + 2 after
-//     everybody has read iteration t.
+//     everybody has read iteration t.  Where the partials are summed in two hops one set would do: nobody publishes partials of t + 1
+//     before it has all sums of t, which stand for everybody's partials of t read, nor sums before all partials of t + 1.  It is
+//     taken where scratch is short; two are faster (4 x (784-256-10), 32 rows, 9.8 and 10.3 us per iteration).
 // The last wavefront draws the rows of the iteration after the next while the others wait for the exchange, and touches one
 // word per line of the member's share of them, so that the requests of all members find them in the L2.
 // Teams of different workers meet only at a restart.  Summation orders are fixed, so a run is bit-reproducible.
@@ -53,6 +55,7 @@ constexpr int kPollers = kTT - kWave;         // threads that sum the partial lo
 // Partial logits of a team from which they are summed in two hops: 16 x 320 floats 9,200 cycles in one, 5,400 in two; with 4 x 80 one
 // takes 3,000, which a second would double.
 constexpr int kTwoHopFloats = 2048;
+__host__ __device__ constexpr bool two_hop_exchange(int P, int floats) { return (long)P * floats >= kTwoHopFloats; }
 constexpr int kAgentScope = 16;               // buffer access cache policy: the sc1 bit (agent scope)
 
 __device__ __forceinline__ f32x4_t mfma16(float a, float b, f32x4_t c) {
@@ -456,14 +459,11 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
   // in two hops: member j adds the P partials of its share of the floats, publishes the sums, and everybody
   // reads E sums: 2 E floats per member instead of P E.
   const int E = B * d2;
-  const bool two_hops = p.P * E >= kTwoHopFloats;
-  const int share = (E + p.P - 1) / p.P, share_lo = min(E, j * share), share_hi = min(E, share_lo + share);
-  // Groups of lanes of a wavefront that add the partials of one float of the share, each every hop_groups-th member: a member's
-  // share is small where the team is large, and one thread per float would ask for P / 8 rounds of partials in turn.  A group's lanes
-  // take consecutive floats (16 lanes of 16 members each instead: 8 x (784-256-10) 10.6 -> 12.1 us per iteration).  Against a
-  // thread per float: 4 x (784-1024-10) 17.2 -> 12.5 us, 1 x (256-4096-10) 29.9 -> 8.7, 8 x (784-256-10) 11.2 -> 10.6.
-  int hop_groups = 1;
-  while (hop_groups < 32 && 8 * hop_groups < p.P) hop_groups *= 2;
+  const bool two_hops = two_hop_exchange(p.P, E);
+  // The first hop goes by groups of lanes of a wavefront that add the partials of one float of the share, each every hop_groups-th
+  // member: a member's share is small where the team is large, and one thread per float would ask for P / 8 rounds of partials in
+  // turn.  A group's lanes take consecutive floats (16 lanes of 16 members each instead: 8 x (784-256-10) 10.6 -> 12.1 us per iteration).
+  // Against a thread per float: 4 x (784-1024-10) 17.2 -> 12.5 us, 1 x (256-4096-10) 29.9 -> 8.7, 8 x (784-256-10) 11.2 -> 10.6.
   const int G = two_hops ? 1 : max(1, min(p.P, kPollers / E));
   const int PG = (p.P + G - 1) / G;
   // this thread's first float, and the members it adds (with several groups a thread has one float at most)
@@ -471,11 +471,39 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
   const bool has_item = !drawer && item_g < G;
   const int j_lo = item_g * PG, j_hi = min(p.P, j_lo + PG);
   unsigned polls = 0;
-  // what from[first + u stride] (u < count <= 8) hold once they carry `number`
-  auto polled = [&](const unsigned long long* from, int first, int stride, int count, unsigned number,
-                    unsigned long long (&v)[8]) __attribute__((always_inline)) {
+  // sum of what `from[first]`, `from[first + stride]`, .. (count) hold once they carry `number`
+  auto polled_sum = [&](const unsigned long long* from, int first, int stride, int count, unsigned number)
+      __attribute__((always_inline)) {
+    float sum = 0.0f;
+    for (int u0 = 0; u0 < count; u0 += 8) {
+      unsigned long long v[8];
+      unsigned missing = (1u << min(8, count - u0)) - 1u;
+      const unsigned asked = missing;
+      for (;;) {                                           // only what is still missing is asked for again
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if ((missing >> u) & 1u)
+            v[u] = __hip_atomic_load(at(from, 8u * (uint32_t)(first + (u0 + u) * stride)), __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (((missing >> u) & 1u) && (unsigned)(v[u] >> 32) == number) missing &= ~(1u << u);
+        if (missing == 0) break;
+        if (gave_up(abort_flag, polls, p.spin_limit)) { flag[0] = 1; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if ((asked >> u) & 1u) sum += __uint_as_float((unsigned)v[u]);
+    }
+    return sum;
+  };
+  // the same with every float to a place of its own: to[u to_stride] = from[first + u stride]
+  auto polled_copy = [&](float* to, int to_stride, const unsigned long long* from, int first, int stride, int count, unsigned number)
+      __attribute__((always_inline)) {
+    unsigned long long v[8];
     unsigned missing = (1u << count) - 1u;
-    while (missing != 0) {                                 // only what is still missing is asked for again
+    for (;;) {
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if ((missing >> u) & 1u)
@@ -487,19 +515,9 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
       if (gave_up(abort_flag, polls, p.spin_limit)) { flag[0] = 1; break; }
       __builtin_amdgcn_s_sleep(1);
     }
-  };
-  auto polled_sum = [&](const unsigned long long* from, int first, int stride, int count, unsigned number)
-      __attribute__((always_inline)) {
-    float sum = 0.0f;
-    for (int u0 = 0; u0 < count; u0 += 8) {
-      unsigned long long v[8];
-      const int asked = min(8, count - u0);
-      polled(from, first + u0 * stride, stride, asked, number, v);
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (u < asked) sum += __uint_as_float((unsigned)v[u]);
-    }
-    return sum;
+    for (int u = 0; u < 8; ++u)
+      if (u < count) to[u * to_stride] = __uint_as_float((unsigned)v[u]);
   };
 
   for (int s = 1; s <= my_k; ++s) {
@@ -579,7 +597,8 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
     lds_barrier();
     // (b) this slice's contribution to the logits, one 16 x 16 block per wavefront on the matrix
     // cores: part[b][c] = sum_n h[b][n] W_2[n][c]
-    unsigned long long* team_part = p.part + (size_t)((number & 1) * p.n_workers + i) * p.P * E;
+    unsigned long long* const set = p.part + ((number & 1) != 0 ? p.part_odd : 0u);
+    unsigned long long* team_part = set + (size_t)i * p.P * E;
     for (int tile = wave; tile < MT * CT; tile += kTW) {
       const int mt = tile / CT, ct = tile - mt * CT;
       f32x4_t g = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
@@ -599,8 +618,17 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
     float* lgp = red;                                      // [G][E] group sums
     if (!drawer) {
       polls = 0;
-      if (two_hops) {
-        unsigned long long* sums = p.part + (size_t)2 * members * E + (size_t)((number & 1) * p.n_workers + i) * E;
+      if (!two_hops) {
+        if (has_item) {
+          for (int e = item_e; e < E; e += kPollers) {       // one pass when E <= 448
+            lgp[item_g * E + e] = polled_sum(team_part, j_lo * E + e, E, j_hi - j_lo, number);
+            if (G > 1) break;
+          }
+        }
+      } else {
+        const auto* k = cold();
+        const int share_lo = min(E, j * k->share), share_hi = min(E, share_lo + k->share), hop_groups = k->hop_groups;
+        unsigned long long* sums = set + (size_t)(members + i) * E;
         const int items = kWave / hop_groups, l = lane / items;
         for (int e0 = share_lo + wave * items; e0 < share_hi; e0 += (kTW - 1) * items) {
           const int e = e0 + (lane & (items - 1));
@@ -615,18 +643,9 @@ __global__ __launch_bounds__(kTT) void mlp2_epoch_kernel(Fused2Args p) {
         // per iteration; fewer floats lose more by the registers (8 x (256-128-20), 32 rows, 8.0 -> 8.5 us).
         if constexpr (CT == 1 || MT < 3) {
           for (int e = tid; e < E; e += kPollers) lgp[e] = polled_sum(sums, e, 0, 1, number);
-        } else for (int e0 = tid; e0 < E; e0 += 8 * kPollers) {
-          unsigned long long v[8];
-          const int asked = min(8, (E - e0 + kPollers - 1) / kPollers);
-          polled(sums, e0, kPollers, asked, number, v);
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-            if (u < asked) lgp[e0 + u * kPollers] = __uint_as_float((unsigned)v[u]);
-        }
-      } else if (has_item) {
-        for (int e = item_e; e < E; e += kPollers) {       // one pass when E <= 448
-          lgp[item_g * E + e] = polled_sum(team_part, j_lo * E + e, E, j_hi - j_lo, number);
-          if (G > 1) break;
+        } else {
+          for (int e0 = tid; e0 < E; e0 += 8 * kPollers)
+            polled_copy(lgp + e0, kPollers, sums, e0, kPollers, min(8, (E - e0 + kPollers - 1) / kPollers), number);
         }
       }
     } else if (s < my_k) {
@@ -879,6 +898,14 @@ bool fused2_shape(int n_workers, int d0, int d1, int d2, int batch, bool momentu
          (long)n_workers * ((d1 + 31L) / 32) <= kFused2MaxMembers;
 }
 
+// Slots of the partial-logit exchange for the finest split, in two sets, or (`spare`) in one where two hops allow it.  Half as
+// many members that take one hop, in two sets, need no more.
+size_t fused2_part_slots(int n_workers, int d1, int d2, int batch, bool spare) {
+  const size_t team = ((size_t)d1 + 15) / 16, floats = (size_t)batch * d2;
+  if (!two_hop_exchange((int)team, (int)floats)) return (size_t)n_workers * floats * 2 * team;
+  return (size_t)n_workers * floats * (team + 1) * (spare ? 1 : 2);
+}
+
 // Floats that the restarts inside a launch pass through memory: a slice per member, and the averages.  0: no plan can
 // have that many workgroups resident.
 size_t fused2_exchange_floats(int n_workers, int d0, int d1, int d2) {
@@ -938,6 +965,12 @@ hipError_t launch_fused2(const Fused2Plan& pl, Fused2Args args, bool pinned, hip
   args.P = pl.P;
   args.shares = pl.shares;
   args.pinned = pinned ? 1 : 0;
+  const unsigned floats = (unsigned)(args.batch * args.d2);
+  const bool two_hops = two_hop_exchange(pl.P, (int)floats);
+  args.part_odd = args.spare_part && two_hops ? 0 : (unsigned)args.n_workers * (pl.P + (two_hops ? 1 : 0)) * floats;
+  args.share = (args.batch * args.d2 + pl.P - 1) / pl.P;
+  args.hop_groups = 1;
+  while (args.hop_groups < 32 && 8 * args.hop_groups < pl.P) args.hop_groups *= 2;
   void* kargs[] = {&args};
   // Plain launch: fused2_plan has checked that the whole grid fits on an otherwise idle device at
   // once, and a team member that never shows up (other work holding compute units) ends in the

@@ -35,6 +35,7 @@ struct Carve {
   size_t xb = 0, yb = 0, idx = 0, xb2 = 0, yb2 = 0, idx2 = 0, logits = 0, losses = 0, row_loss = 0, part = 0, sync = 0, shadow = 0, grads = 0, mean = 0, mean_shadow = 0, steps = 0, vel = 0, exchange = 0;
   size_t h[PRSGD_MAX_DIMS] = {0}, delta[PRSGD_MAX_DIMS] = {0};
   size_t total = 0;
+  bool spare_part = false;    // the exchange of the epoch kernel keeps one set of partial logits where that is enough
 };
 
 bool build_layout(const prsgd_config* c, Layout* lo, char* err, size_t errn) {
@@ -134,7 +135,9 @@ Streamed streamed_uses(const prsgd_config& c, const Layout& lo) {
   return u;
 }
 
-void build_carve(const prsgd_config* c_in, const Layout& lo, Carve* cv) {
+// `scratch`: PRSGD_SCRATCH_RUNS, or without what a configuration can do without: what keeps restarts inside a launch (they are
+// launches of their own then), and what the epoch kernel exchanges (local steps are the chain of per-layer launches then).
+void build_carve(const prsgd_config* c_in, const Layout& lo, int scratch, Carve* cv) {
   const prsgd_config eff = effective_config(c_in);
   const prsgd_config* c = &eff;
   size_t off = 0;
@@ -147,7 +150,7 @@ void build_carve(const prsgd_config* c_in, const Layout& lo, Carve* cv) {
   cv->steps = take(n * 4);
   cv->mean = take((size_t)lo.m_pad * 4 + (c->model == PRSGD_LSQ ? kAlign : 0));   // least squares: abort flag behind it
   if (c->momentum != 0.0f) cv->vel = take(n * (size_t)lo.m_pad * 4);
-  if (c->model == PRSGD_LSQ && lsq_restarts_in_launch(c->n_workers, lo.d[0], c->batch)) {
+  if (scratch >= PRSGD_SCRATCH_RUNS && c->model == PRSGD_LSQ && lsq_restarts_in_launch(c->n_workers, lo.d[0], c->batch)) {
     cv->sync = take(4);
     cv->exchange = take(lsq_exchange_bytes(c->n_workers, lo.d[0]));
   }
@@ -170,12 +173,15 @@ void build_carve(const prsgd_config* c_in, const Layout& lo, Carve* cv) {
       cv->shadow = take(n * (size_t)lo.m_pad * 2);
       cv->mean_shadow = take((size_t)lo.m_pad * 2);
     }
-    if (epoch_candidate(*c)) {
-      // epoch kernel: partial logits for the finest team split, numbers of the exchanges, abort flag, restart flags
+    if (scratch >= PRSGD_SCRATCH_EPOCHS && epoch_candidate(*c)) {
+      // epoch kernel: partial logits, numbers of the exchanges, abort flag; for restarts inside a launch flags behind
+      // them, and the slices on their way
       const size_t members = n * (((size_t)lo.d[1] + 15) / 16);
-      cv->part = take(2 * (members + n) * b * lo.d[2] * 8);
-      cv->sync = take((n + 1) * 128 + 16 * (size_t)fused2_flag_stride((int)(members < 4096 ? members : 4096)));
-      const size_t exchange = fused2_exchange_floats(c->n_workers, lo.d[0], lo.d[1], lo.d[2]);
+      const size_t exchange = scratch < PRSGD_SCRATCH_RUNS ? 0 : fused2_exchange_floats(c->n_workers, lo.d[0], lo.d[1], lo.d[2]);
+      const size_t flags = exchange == 0 ? 0 : 16 * (size_t)fused2_flag_stride((int)(members < 4096 ? members : 4096));
+      cv->part = take(fused2_part_slots(c->n_workers, lo.d[1], lo.d[2], c->batch, scratch < PRSGD_SCRATCH_RUNS) * 8);
+      cv->spare_part = scratch < PRSGD_SCRATCH_RUNS;
+      cv->sync = take((n + 1) * 128 + flags);
       if (exchange != 0) cv->exchange = take(exchange * 4);
     }
     // un-fused update; also the fallback of a momentum run whose epoch kernel does not fit the device
@@ -183,6 +189,14 @@ void build_carve(const prsgd_config* c_in, const Layout& lo, Carve* cv) {
       cv->grads = take(n * (size_t)lo.m_pad * 4);
   }
   cv->total = off;
+}
+// The most scratch that prsgd_init_static has room for (PRSGD_SCRATCH_LAYERS also where even that is too much).
+int static_scratch(const prsgd_config* cfg, const Layout& lo, Carve* cv) {
+  for (int scratch = PRSGD_SCRATCH_RUNS;; --scratch) {
+    *cv = Carve();
+    build_carve(cfg, lo, scratch, cv);
+    if (cv->total <= PRSGD_STATIC_WORKSPACE_BYTES || scratch == PRSGD_SCRATCH_LAYERS) return scratch;
+  }
 }
 
 struct EventPair { hipEvent_t a, b; int kind; };
@@ -654,6 +668,7 @@ Fused2Args fused2_args(prsgd_ctx* ctx, int k, const int* worker_steps) {
   a.k = k;
   a.worker_steps = worker_steps;
   a.part = ctx->at<unsigned long long>(ctx->cv.part);
+  a.spare_part = ctx->cv.spare_part;
   a.exchange = ctx->at<float>(ctx->cv.exchange);
   a.sync = ctx->at<unsigned int>(ctx->cv.sync);
   a.spin_limit = ctx->spin_limit;
@@ -778,7 +793,7 @@ size_t prsgd_workspace_bytes(const prsgd_config* cfg) {
   char err[128];
   if (!build_layout(cfg, &lo, err, sizeof(err))) return 0;
   Carve cv;
-  build_carve(cfg, lo, &cv);
+  build_carve(cfg, lo, PRSGD_SCRATCH_RUNS, &cv);
   return cv.total;
 }
 
@@ -1007,7 +1022,8 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
   ctx->static_slot = static_slot;
   ctx->cfg = effective_config(cfg);
   ctx->lo = lo;
-  build_carve(cfg, lo, &ctx->cv);
+  if (static_slot >= 0) (void)static_scratch(cfg, lo, &ctx->cv);
+  else build_carve(cfg, lo, PRSGD_SCRATCH_RUNS, &ctx->cv);
   ctx->bf16 = cfg->model == PRSGD_MLP && cfg->gemm_dtype == PRSGD_BF16;
   ctx->streamed = streamed_uses(*cfg, lo);
   ctx->stream = reinterpret_cast<hipStream_t>(hip_stream);
@@ -1102,7 +1118,7 @@ int prsgd_init_static(const prsgd_config* cfg, const float* x0_host, const void*
   char err[128];
   if (!build_layout(cfg, &lo, err, sizeof(err))) return set_err(nullptr, PRSGD_EINVAL, "%s", err);
   Carve cv;
-  build_carve(cfg, lo, &cv);
+  (void)static_scratch(cfg, lo, &cv);
   if (cv.total > kStaticBytes) {
     char msg[200];
     snprintf(msg, sizeof(msg), "prsgd_init_static: this configuration needs %zu bytes of workspace, the "
@@ -1511,6 +1527,15 @@ int prsgd_streamed_uses(const prsgd_config* cfg) {
   const Streamed u = streamed_uses(*cfg, lo);
   return (u.steps ? PRSGD_STREAM_STEPS : 0) | (u.step_mean ? PRSGD_STREAM_STEP_MEAN : 0) |
          (u.mean ? PRSGD_STREAM_MEAN : 0) | (u.average ? PRSGD_STREAM_AVERAGE : 0);
+}
+
+int prsgd_static_scratch(const prsgd_config* cfg) {
+  Layout lo;
+  char err[128];
+  if (!build_layout(cfg, &lo, err, sizeof(err))) return set_err(nullptr, PRSGD_EINVAL, "%s", err);
+  Carve cv;
+  const int scratch = static_scratch(cfg, lo, &cv);
+  return cv.total <= kStaticBytes ? scratch : set_err(nullptr, PRSGD_EINVAL, "beyond the static workspace");
 }
 
 int prsgd_waiting_regime(const int32_t* n_workers, const int32_t* team, int32_t n_streams, int32_t compute_units) {

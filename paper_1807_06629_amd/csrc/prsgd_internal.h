@@ -124,10 +124,12 @@ struct Fused2Args {
   const int* worker_steps;       // Algorithm 3 step counts (nullptr: every worker takes k steps)
   int interval;                  // > 0: restarts inside the launch
   float* exchange;               // [N][P] slices on their way, then [P] averages (fused2_exchange_floats)
-  unsigned long long* part;      // [2][N][P][B d2] partial logits with the number of their iteration,
-                                 // then [2][N][B d2] their sums
+  unsigned long long* part;      // [N][P][B d2] partial logits with the number of their iteration, in two hops with [N][B d2]
+                                 // sums behind them; two such sets, or one where scratch is short and two hops allow it
+  bool spare_part; unsigned part_odd;   // ... and the slots from a set to that of odd iterations, 0 for a single one
+  int share, hop_groups;         // two hops: floats that a member sums, lanes for each (these three set by launch_fused2)
   unsigned int* sync;            // [N][32]: iterations exchanged so far (word 1); [32]: abort flag, restarts so far;
-                                 // then [2][8] copies of a flag byte per workgroup
+                                 // with restarts inside the launch also [2][8] copies of a flag byte per workgroup
   unsigned int spin_limit;       // polls before a member gives up
   float* row_loss; int32_t* idx;
   float* vel; float mu;          // momentum buffers [N][m_pad] (nullptr = plain SGD)
@@ -137,6 +139,7 @@ size_t fused2_lds_bytes(const Fused2Plan& pl);
 constexpr int kFused2MaxMembers = 1024;      // workgroups of 512 threads that 256 compute units hold
 // bytes between the copies of the flags: a line each, on different memory channels
 __host__ __device__ constexpr int fused2_flag_stride(int members) { return (members + 255) / 256 * 256 + 256; }
+size_t fused2_part_slots(int n_workers, int d1, int d2, int batch, bool spare);
 size_t fused2_exchange_floats(int n_workers, int d0, int d1, int d2);
 bool fused2_shape(int n_workers, int d0, int d1, int d2, int batch, bool momentum);
 bool fused2_plan(int n_workers, int d0, int d1, int d2, int batch, bool momentum, Fused2Plan* pl);

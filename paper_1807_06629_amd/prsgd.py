@@ -25,6 +25,7 @@ PRSGD_TANH, PRSGD_RELU = 0, 1
 PRSGD_F32, PRSGD_BF16 = 0, 1
 PRSGD_MOM_KEEP, PRSGD_MOM_AVERAGE, PRSGD_MOM_RESET = 0, 1, 2
 PRSGD_MAX_DIMS = 16
+PRSGD_SCRATCH_LAYERS, PRSGD_SCRATCH_EPOCHS, PRSGD_SCRATCH_RUNS = 0, 1, 2
 PRSGD_WAIT_ALONE, PRSGD_WAIT_TOGETHER, PRSGD_WAIT_CROWDED = 0, 1, 2
 PRSGD_STREAM_STEPS, PRSGD_STREAM_STEP_MEAN, PRSGD_STREAM_MEAN, PRSGD_STREAM_AVERAGE = 1, 2, 4, 8
 
@@ -86,6 +87,7 @@ def _load() -> ctypes.CDLL:
         "prsgd_copy_bytes": (ctypes.c_int, [vp, vp, sz, vp]),
         "prsgd_product_tile": (ctypes.c_int, [i32, i32, i32, i32, vp]),
         "prsgd_streamed_uses": (ctypes.c_int, [cfgp]),
+        "prsgd_static_scratch": (ctypes.c_int, [cfgp]),
         "prsgd_waiting_regime": (ctypes.c_int, [vp, vp, i32, i32]),
         "prsgd_waiting_launches": (ctypes.c_int, [vp, vp]),
         "prsgd_time_varying_schedule": (ctypes.c_int, [i32, i32, vp, vp]),
@@ -350,6 +352,13 @@ def prsgd_product_tile(rows: int, cols: int, n_workers: int, gemm_dtype: str):
 
 def prsgd_streamed_uses(cfg: prsgd_config) -> int:
     rc = _lib.prsgd_streamed_uses(ctypes.byref(cfg))
+    if rc < 0:
+        _check(rc)
+    return rc
+
+
+def prsgd_static_scratch(cfg: prsgd_config) -> int:
+    rc = _lib.prsgd_static_scratch(ctypes.byref(cfg))
     if rc < 0:
         _check(rc)
     return rc

@@ -129,6 +129,27 @@ def test_launches_that_wait_are_counted_by_xcd(P, streams, regime):
     assert got == getattr(P, "PRSGD_WAIT_" + regime)
 
 
+@pytest.mark.parametrize("n_workers,dims,batch,momentum,scratch", [
+    (8, (784, 256, 10), 32, 0.0, "RUNS"),
+    # what the replicas' restarts pass through memory is as large as the replicas
+    (64, (512, 128, 10), 8, 0.0, "EPOCHS"), (16, (784, 256, 10), 32, 0.0, "EPOCHS"), (100, (256, 128, 10), 8, 0.0, "EPOCHS"),
+    (20, (784, 192, 10), 16, 0.0, "EPOCHS"), (12, (784, 512, 10), 16, 0.0, "EPOCHS"),
+    # partial logits without padding, in one set
+    (16, (100, 256, 64), 64, 0.0, "EPOCHS"),
+    (196, (292, 32, 57), 16, 0.0, "LAYERS"),
+])
+def test_static_contexts_leave_out_scratch_before_they_are_refused(P, n_workers, dims, batch, momentum, scratch):
+    cfg = P.make_config(n_workers, "mlp", dims, batch, 256, 0.1, 1, "relu", momentum=momentum)
+    assert P.prsgd_static_scratch(cfg) == getattr(P, "PRSGD_SCRATCH_" + scratch)
+
+
+def test_static_contexts_beyond_the_limit_are_refused(P):
+    cfg = P.make_config(16, "mlp", (3072, 1024, 1024, 10), 64, 256, 0.1, 1, "relu", "bf16")
+    with pytest.raises(P.PrsgdError) as err:
+        P.prsgd_static_scratch(cfg)
+    assert err.value.code == P.PRSGD_EINVAL
+
+
 def test_null_context_calls_return_einval(P):
     assert P._lib.prsgd_local_steps(None, 1) == P.PRSGD_EINVAL
     assert P._lib.prsgd_average(None) == P.PRSGD_EINVAL

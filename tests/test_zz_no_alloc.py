@@ -55,6 +55,24 @@ def test_static_workspace_contexts_match_allocated_ones_twice_in_a_row():
         assert rel_err(got[0], want["x"]) <= tol
 
 
+def test_static_workspace_without_all_of_the_scratch():
+    """Restarts as launches of their own give the bits of the allocated context, whose restarts are inside the launch; so
+    does not the chain of per-layer launches, which is held to the oracle."""
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    for kw, scratch in [(dict(dims=(512, 128, 10), batch=8, n_workers=64, iterations=11), P.PRSGD_SCRATCH_EPOCHS),
+                        # partial logits of one set, in two hops
+                        (dict(dims=(100, 256, 64), batch=64, n_workers=16, iterations=11), P.PRSGD_SCRATCH_EPOCHS),
+                        (dict(dims=(292, 32, 57), batch=16, n_workers=196, iterations=5), P.PRSGD_SCRATCH_LAYERS)]:
+        w = small_mlp(rows_per_worker=64, interval=4, activation="relu", lr=0.02, **kw)
+        cfg = P.make_config(w.n_workers, w.model, w.dims, w.batch, w.rows_per_worker, w.lr, w.index_seed, activation="relu")
+        assert P.prsgd_static_scratch(cfg) == scratch
+        inp = make_inputs(w)
+        ref, got = _run(P, D, w, inp, static=False), _run(P, D, w, inp, static=True)
+        for a, b in zip(ref, got):
+            assert np.array_equal(a, b) or scratch == P.PRSGD_SCRATCH_LAYERS
+        assert rel_err(got[0], oracle_run(w, inp)["x"]) <= 1e-4
+
+
 def test_static_workspace_limits_and_single_live_context():
     from paper_1807_06629_amd import prsgd as P
     # a configuration beyond the limit is refused with a message that names it
