@@ -9,7 +9,8 @@ import pytest
 import torch
 
 import oracle
-from helpers import inputs_for, oracle_run, rel_err, small_mlp
+from helpers import inputs_for, oracle_args, oracle_run, rel_err, small_mlp
+from workloads import get_workload, make_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -70,6 +71,7 @@ def test_run_in_one_launch(P, D, shape, interval):
     P.prsgd_write_params(h, -1, inp["x0"])
     P.prsgd_set_iteration(h, 0)
     P.prsgd_run(h, w.iterations, interval)
+    assert P.prsgd_waiting_launches(h)[0] == 1                    # the restarts were inside
     got, loss = D.read_all(h), P.prsgd_read_loss(h)
     last = w.n_workers - 1
     assert np.array_equal(P.prsgd_read_indices(h)[last],
@@ -85,6 +87,83 @@ def test_run_in_one_launch(P, D, shape, interval):
     want = oracle_run(w, inp)
     assert rel_err(got, want["x"]) <= 1e-4
     assert np.allclose(loss, want["losses"], rtol=1e-3, atol=1e-6)
+
+
+@pytest.mark.parametrize("shape", [
+    dict(dims=(64, 32, 10), batch=8, n_workers=3),
+    dict(dims=(100, 48, 33), batch=20, n_workers=8),              # class rows with their chunks exchanged
+    dict(dims=(784, 256, 10), batch=32, n_workers=8),             # two hops
+    dict(dims=(900, 64, 64), batch=20, n_workers=9),              # 57 row blocks, four class tiles
+    dict(dims=(128, 64, 64), batch=64, n_workers=2),              # four batch and class tiles
+    dict(dims=(36, 640, 10), batch=16, n_workers=2),              # teams of 40
+])
+def test_velocities_kept_over_restarts_in_one_launch(P, D, shape):
+    w = small_mlp(activation="tanh", rows_per_worker=128, interval=3, iterations=10, lr=0.005, **shape).scaled(momentum=0.9)
+    inp = inputs_for(w)
+    out = []
+    for apart in (False, True):
+        h = D.open_workload(w, inp)
+        P.prsgd_profile_enable(h, apart)                          # a launch per epoch, a launch per restart
+        P.prsgd_run(h, w.iterations, w.interval)
+        assert P.prsgd_waiting_launches(h)[0] == (0 if apart else 1)
+        out.append((D.read_all(h), np.stack([P.prsgd_read_velocity(h, i) for i in range(w.n_workers)]), P.prsgd_read_loss(h)))
+        P.prsgd_destroy(h)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    want = oracle_run(w, inp, momentum=0.9)
+    assert rel_err(out[0][0], want["x"]) <= 1e-4 and rel_err(out[0][1], want["v"]) <= 1e-4
+
+
+@pytest.mark.parametrize("shape", [
+    dict(dims=(50, 21, 5), batch=7, n_workers=4),
+    dict(dims=(301, 100, 20), batch=33, n_workers=3),
+    dict(dims=(785, 530, 10), batch=20, n_workers=2),             # teams of 34, two hops
+])
+def test_epochs_of_unlike_lengths_on_ragged_widths(P, D, shape):
+    w = small_mlp(rows_per_worker=128, lr=0.02, **shape)
+    inp = inputs_for(w)
+    steps = [5, 0, 3, 1][:w.n_workers]
+    h = D.open_workload(w, inp)
+    P.prsgd_profile_enable(h, True)
+    D.run_algorithm3(h, steps, 3)
+    names = {r["name"] for r in P.prsgd_profile_read(h)}
+    assert "mlp2_epoch" in names and "gemm_fwd" not in names, names
+    args = oracle_args(w, inp)
+    args.pop("bf16")
+    want = oracle.run_heterogeneous(**args, lr=w.lr, worker_steps=steps, n_epochs=3)
+    assert P.prsgd_iteration(h) == want["t"]
+    assert rel_err(D.read_all(h), want["x"]) <= 1e-4
+    P.prsgd_destroy(h)
+
+
+@pytest.mark.parametrize("model", ["lsq", "mlp"])
+def test_run_in_a_captured_stream(P, D, model):
+    """A run recorded in a graph has a launch per epoch.  Every replay, with eager work and synchronisations between
+    them, takes the iterations of the recording from the points as they are."""
+    if model == "lsq":
+        w = get_workload("c1").scaled(dims=(64,), batch=16, rows_per_worker=128, n_workers=5, interval=4, iterations=8)
+    else:
+        w = small_mlp(dims=(784, 200, 10), batch=32, n_workers=5, rows_per_worker=128, interval=4, iterations=8, lr=0.02)
+    inp = make_inputs(w)
+    stream = torch.cuda.Stream()
+    a, b = D.open_workload(w, inp, stream=stream), D.open_workload(w, inp, stream=stream)
+    with torch.cuda.stream(stream):
+        P.prsgd_local_steps(a, 1)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            P.prsgd_run(a, 8, 4)                                  # from one step into an epoch: ends on a bare step
+        assert P.prsgd_waiting_launches(a)[0] == 0
+        P.prsgd_local_steps(b, 1)
+        for _ in range(4):
+            graph.replay()
+            P.prsgd_set_iteration(b, 1)
+            P.prsgd_run(b, 8, 4)
+            assert np.array_equal(D.read_all(a), D.read_all(b))
+            assert np.array_equal(P.prsgd_read_loss(a), P.prsgd_read_loss(b))
+        assert P.prsgd_waiting_launches(b)[0] == 4
+    P.prsgd_destroy(a)
+    P.prsgd_destroy(b)
 
 
 def test_contexts_of_three_streams_together(P, D):

@@ -47,6 +47,7 @@ def test_run_in_one_launch(P, D, d, batch, n, interval, momentum):
     w, inp = _problem(d, batch, n, interval, momentum=momentum)
     h = D.open_workload(w, inp)
     P.prsgd_run(h, w.iterations, interval)
+    assert P.prsgd_waiting_launches(h)[0] == (1 if n <= 64 and interval < w.iterations else 0)
     got, loss = D.read_all(h), P.prsgd_read_loss(h)
     assert P.prsgd_iteration(h) == w.iterations
     assert np.array_equal(P.prsgd_read_indices(h)[n - 1],

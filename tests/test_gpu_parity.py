@@ -148,10 +148,10 @@ def test_c1_least_squares_full_run(P, D):
     P.prsgd_destroy(h)
 
 
-# the shapes with d % 4 == 0 and at most 8192 minibatch floats take the LDS-staged kernel in each
-# of its four (vectors per thread, prefetch depth) variants; the others the plain kernel
+# d <= 512 with at most 64 rows: the register-resident kernel; of the others those with d % 4 == 0 and at most 8192 minibatch
+# floats the LDS-staged one, in each of its four (vectors per thread, prefetch depth) variants; the rest the plain one
 @pytest.mark.parametrize("d,batch", [(1, 1), (7, 3), (300, 70), (1000, 9), (4, 1), (32, 40), (128, 20),
-                                     (64, 100), (8, 300), (2048, 4), (16, 512),
+                                     (64, 100), (8, 300), (2048, 4), (16, 512), (4, 100), (1024, 2), (516, 3),
                                      (8192, 2), (8192, 600)])   # largest d: > 64 KiB of LDS in the plain kernel
 def test_least_squares_ragged_shapes(P, D, d, batch):
     w = get_workload("c1").scaled(dims=(d,), batch=batch, rows_per_worker=128, n_workers=3,
@@ -226,13 +226,13 @@ def test_c4_shape_interval_sweep_reduced_horizon(P, D):
 # --------------------------------------------------------------------------- epoch kernel (one hidden layer, fp32)
 EPOCH_SHAPES = [
     dict(dims=(64, 32, 10), batch=8, n_workers=3),                 # P=2 teams, N not a multiple of 8
-    dict(dims=(100, 48, 7), batch=20, n_workers=8),                # ragged d0 (7 row blocks), two batch tiles
+    dict(dims=(100, 48, 7), batch=20, n_workers=8),                # ragged d0 (7 row blocks in all), two batch tiles
     dict(dims=(256, 128, 10), batch=8, n_workers=16),              # C4's shape
     dict(dims=(784, 256, 10), batch=32, n_workers=8),              # C2's shape
     dict(dims=(784, 256, 10), batch=32, n_workers=16),             # one workgroup on every compute unit
     dict(dims=(600, 48, 7), batch=20, n_workers=3),                # ragged last row block of 38
     dict(dims=(900, 32, 33), batch=30, n_workers=2),               # 57 row blocks: eight per wavefront; 33 classes
-    dict(dims=(128, 64, 33), batch=50, n_workers=2),               # 33 classes (padded to 48), four batch tiles
+    dict(dims=(128, 64, 33), batch=50, n_workers=2),               # 33 classes (rows of 64), four batch tiles
     dict(dims=(1024, 16, 3), batch=1, n_workers=1),                # widest input, B = 1, single-member team
 ]
 
@@ -280,7 +280,7 @@ def test_epoch_kernel_matches_layerwise_kernels(P, D):
     assert rel_err(outs[0], outs[1]) <= 1e-5
 
 
-@pytest.mark.parametrize("dims", [(64, 32, 10), (640, 32, 10)])     # with and without minibatch prefetch
+@pytest.mark.parametrize("dims", [(64, 32, 10), (640, 32, 10)])     # two and six row blocks on the busiest wavefront
 def test_epoch_kernel_heterogeneous_steps(P, D, dims):
     w = small_mlp(dims=dims, batch=8, n_workers=4, rows_per_worker=128)
     inp = inputs_for(w)
@@ -685,7 +685,7 @@ def test_eager_average_at_full_replica_sets(P, D, name):
 LAZY_CASES = [
     ("lsq", dict()),
     ("epoch", dict(dims=(64, 32, 10), batch=8, n_workers=3)),
-    ("epoch-wide", dict(dims=(784, 32, 10), batch=16, n_workers=3)),     # seven row blocks per wavefront
+    ("epoch-wide", dict(dims=(784, 32, 10), batch=16, n_workers=3)),     # eight row blocks on the busiest wavefront
     ("bf16", dict(dims=(100, 72, 40, 10), batch=24, n_workers=4, gemm_dtype="bf16", activation="relu")),
     ("fp32-layers", dict(dims=(40, 24, 16, 6), batch=6, n_workers=3)),   # no deferred broadcast: falls back
 ]
@@ -889,8 +889,8 @@ def test_algorithm3_heterogeneous_steps(P, D, model, fused):
 # --------------------------------------------------------------------------- momentum local steps
 MOMENTUM_CASES = [
     ("lsq", dict()),
-    ("one-hidden", dict(dims=(64, 32, 10), batch=8, n_workers=3)),          # epoch kernel, prefetching variant
-    ("one-hidden-wide", dict(dims=(784, 64, 10), batch=32, n_workers=2, activation="tanh")),  # no prefetch
+    ("one-hidden", dict(dims=(64, 32, 10), batch=8, n_workers=3)),          # epoch kernel
+    ("one-hidden-wide", dict(dims=(784, 64, 10), batch=32, n_workers=2, activation="tanh")),  # ... with eight row blocks per wavefront
     ("one-hidden-unfit", dict(dims=(64, 40, 10), batch=8, n_workers=3)),    # d_1 % 16 != 0: per-layer chain
     ("fp32-layers", dict(dims=(40, 24, 16, 6), batch=6, n_workers=3)),
     ("bf16", dict(dims=(100, 72, 40, 10), batch=24, n_workers=4, gemm_dtype="bf16", activation="relu")),
