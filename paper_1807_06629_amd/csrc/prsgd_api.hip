@@ -217,6 +217,7 @@ struct prsgd_ctx {
   long wait_places;            // workgroups that an XCD of it holds, one per compute unit
   hipEvent_t wait_event;       // behind its newest launch (nullptr: none recorded), and that launch's place among all
   uint64_t wait_seq;
+  bool ran_pinned;             // launches of it, maybe still under way, had teams pinned because its stream was the only one
   int64_t n_whole, n_followed; // launches with restarts inside; launches of other streams that this one's stream waited for
   bool restarts_in_launch;   // whole runs in one launch: its workgroups exchange the points at a restart
   Fused2Plan f2;
@@ -844,12 +845,12 @@ bool stands_for_stream(const prsgd_ctx* c) {
     if (o->wait_dev == c->wait_dev && o->stream == c->stream) return false;
   return true;
 }
-// Workgroups on the fullest XCD of the largest launch in this context's stream.
-long stream_demand(const prsgd_ctx* c, bool pinned) {
+// Workgroups on the fullest XCD of the largest launch in this context's stream: from now on, or (`past`) so far.
+long stream_demand(const prsgd_ctx* c, bool past) {
   long most = 0;
   for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
     if (o->wait_dev == c->wait_dev && o->stream == c->stream) {
-      const long need = xcd_workgroups(o->cfg.n_workers, o->wait_team, pinned && o->f2.pinned_fits);
+      const long need = xcd_workgroups(o->cfg.n_workers, o->wait_team, past && o->ran_pinned);
       if (need > most) most = need;
     }
   return most;
@@ -884,12 +885,16 @@ hipError_t record_waiting(prsgd_ctx* ctx) {
   ctx->wait_seq = ++g_waiting_seq;
   return hipEventRecord(ctx->wait_event, ctx->stream);
 }
-// Lets the context's stream wait for the oldest launches of other streams until those left fit beside `demand` workgroups per XCD.
-hipError_t follow_others(prsgd_ctx* ctx, long demand, bool pinned) {
-  long total = demand;
+hipError_t follow(prsgd_ctx* ctx, const prsgd_ctx* newest) {
+  ++ctx->n_followed;
+  return hipStreamWaitEvent(ctx->stream, newest->wait_event, 0);
+}
+// Lets the context's stream wait for the oldest launches of other streams until those left fit beside its own.
+hipError_t follow_others(prsgd_ctx* ctx) {
+  long total = xcd_workgroups(ctx->cfg.n_workers, ctx->wait_team, false);
   for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
     if (o->wait_dev == ctx->wait_dev && o->stream != ctx->stream && stands_for_stream(o) && stream_newest(o) != nullptr)
-      total += stream_demand(o, pinned);
+      total += stream_demand(o, false);
   uint64_t followed = 0;
   while (total > ctx->wait_places) {
     const prsgd_ctx* oldest = nullptr;
@@ -900,11 +905,10 @@ hipError_t follow_others(prsgd_ctx* ctx, long demand, bool pinned) {
         oldest = newest;
     }
     if (oldest == nullptr) return hipSuccess;
-    const hipError_t e = hipStreamWaitEvent(ctx->stream, oldest->wait_event, 0);
+    const hipError_t e = follow(ctx, oldest);
     if (e != hipSuccess) return e;
     followed = oldest->wait_seq;
-    total -= stream_demand(oldest, pinned);
-    ++ctx->n_followed;
+    total -= stream_demand(oldest, false);
   }
   return hipSuccess;
 }
@@ -918,16 +922,21 @@ struct WaitingLaunch {
   explicit WaitingLaunch(prsgd_ctx* c)
       : ctx(c), lock(g_waiting_mutex), regime(waiting_regime_of(c)), capturing(is_capturing(c->stream)) {}
   bool may_wait_as_whole() const { return !capturing && regime != PRSGD_WAIT_CROWDED; }
-  bool pinned() const { return ctx->cfg.n_workers % 8 == 0 || (regime == PRSGD_WAIT_ALONE && !capturing && ctx->f2.pinned_fits); }
+  bool pinned() const {
+    if (ctx->cfg.n_workers % 8 == 0) return true;          // as many workgroups per XCD as spread
+    if (regime != PRSGD_WAIT_ALONE || capturing || !ctx->f2.pinned_fits) return false;
+    return ctx->ran_pinned = true;
+  }
   hipError_t before() {
     if (capturing || regime != PRSGD_WAIT_CROWDED) return hipSuccess;
-    return follow_others(ctx, xcd_workgroups(ctx->cfg.n_workers, ctx->wait_team, false), false);
+    return follow_others(ctx);
   }
   hipError_t after() { return capturing || regime != PRSGD_WAIT_CROWDED ? hipSuccess : record_waiting(ctx); }
 };
 
-// A context joins the list.  Launches under way were ordered without it: if they (pinned, where their stream was the only
-// one) leave it no room, its own first launches follow them.
+// A context joins the list.  Launches under way were ordered without it.  Its own follow those of a stream that had its teams
+// pinned, unless all that has been launched so far leaves them room; if the streams do not fit together any more, they follow
+// others until those left do.
 hipError_t enlist_waiting(prsgd_ctx* ctx, int team) {
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -941,21 +950,25 @@ hipError_t enlist_waiting(prsgd_ctx* ctx, int team) {
   g_waiting = ctx;
   ctx->enlisted = true;
   if (waiting_regime_of(ctx) == PRSGD_WAIT_ALONE) return hipSuccess;
-  long n_others = 0, pinned_beside = 0;
-  for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
-    if (o->wait_dev == dev && o->stream != ctx->stream && stands_for_stream(o)) {
-      ++n_others;
-      pinned_beside += stream_demand(o, true);
-    }
-  const bool pinned = n_others == 1;
-  const long demand = xcd_workgroups(ctx->cfg.n_workers, team, false);
-  if (waiting_regime_of(ctx) == PRSGD_WAIT_TOGETHER && !(pinned && pinned_beside + demand > ctx->wait_places)) return hipSuccess;
-  for (prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting)
-    if (o->wait_dev == dev && o->stream != ctx->stream && stands_for_stream(o) && !is_capturing(o->stream)) {
-      e = record_waiting(o);
-      if (e != hipSuccess) return e;
-    }
-  return follow_others(ctx, demand, pinned);
+  long total = xcd_workgroups(ctx->cfg.n_workers, team, false);
+  bool past_pinned = false;
+  for (const prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting) {
+    if (o->wait_dev != dev || o->stream == ctx->stream) continue;
+    past_pinned |= o->ran_pinned;
+    if (stands_for_stream(o)) total += stream_demand(o, true);
+  }
+  const bool crowded = waiting_regime_of(ctx) == PRSGD_WAIT_CROWDED;
+  past_pinned &= total > ctx->wait_places;
+  if (!crowded && !past_pinned) return hipSuccess;
+  for (prsgd_ctx* o = g_waiting; o != nullptr; o = o->next_waiting) {
+    if (o->wait_dev != dev || o->stream == ctx->stream || is_capturing(o->stream)) continue;
+    const bool pinned = past_pinned && o->ran_pinned;
+    if (!pinned && !(crowded && stands_for_stream(o))) continue;
+    e = record_waiting(o);
+    if (e == hipSuccess && pinned) e = follow(ctx, o);
+    if (e != hipSuccess) return e;
+  }
+  return crowded ? follow_others(ctx) : hipSuccess;
 }
 void strike_waiting(prsgd_ctx* ctx) {
   if (!ctx->enlisted) return;
@@ -1036,6 +1049,7 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
   ctx->next_waiting = nullptr;
   ctx->wait_event = nullptr;
   ctx->wait_seq = 0;
+  ctx->ran_pinned = false;
   ctx->n_whole = ctx->n_followed = 0;
   ctx->features = reinterpret_cast<const float*>(features_dev);
   ctx->targets = targets_dev;

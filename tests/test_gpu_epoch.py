@@ -242,3 +242,19 @@ def test_a_context_that_comes_during_a_pinned_launch_follows_it(P, D):
     assert np.array_equal(D.read_all(a), D.read_all(b))
     P.prsgd_destroy(a)
     P.prsgd_destroy(b)
+
+
+def test_every_context_that_comes_during_a_pinned_launch_follows_it(P, D):
+    """The second one to come is ordered behind the pinned launch like the first, though the three fit together spread."""
+    w = small_mlp(dims=(784, 512, 10), batch=32, n_workers=2, rows_per_worker=128, interval=4, iterations=600, lr=0.002)
+    inp = inputs_for(w)
+    assert P.prsgd_waiting_regime([2] * 3, [32] * 3) == P.PRSGD_WAIT_TOGETHER
+    handles = []
+    for _ in range(3):
+        handles.append(D.open_workload(w, inp, stream=torch.cuda.Stream()))
+        P.prsgd_run(handles[-1], w.iterations, w.interval)
+    assert [P.prsgd_waiting_launches(h) for h in handles] == [(1, 0), (1, 1), (1, 1)]
+    out = [D.read_all(h) for h in handles]
+    for h, x in zip(handles, out):
+        assert np.array_equal(x, out[0])
+        P.prsgd_destroy(h)
