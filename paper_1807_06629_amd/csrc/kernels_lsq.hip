@@ -485,6 +485,8 @@ __global__ __launch_bounds__(64 * W) void lsq_resident_kernel(LsqArgs p) {
 #pragma unroll
   for (int u = 0; u < D; ++u) request(u, u);
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"((D - 1) * REQ) : "memory");
+  // a wavefront past the minibatch requests nothing more, so that no later wait would be for these
+  if (n_rows == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   take(0);
   __syncthreads();
 

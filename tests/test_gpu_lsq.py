@@ -74,6 +74,22 @@ def test_run_in_one_launch(P, D, d, batch, n, interval, momentum):
     assert rel_err(got, want["x"]) <= 1e-4
 
 
+@pytest.mark.parametrize("d,batch,n", [(512, 1, 3), (100, 6, 4), (64, 33, 5), (512, 33, 4), (3, 1, 257), (512, 1, 257)])
+def test_wavefronts_past_the_minibatch_meet_no_earlier_contents_of_lds(P, D, d, batch, n):
+    """Workgroups on every compute unit leave NaN in the places of all rows; the run behind them reads its own rows only."""
+    other, inp = _problem(d, batch, 256, 8, iterations=8)
+    inp["features"] = np.full_like(inp["features"], np.nan)
+    w, clean = _problem(d, batch, n, 8, iterations=24)
+    h, dirty = D.open_workload(w, clean), D.open_workload(other, inp)
+    for _ in range(3):
+        P.prsgd_local_steps(dirty, 8)
+        P.prsgd_local_steps(h, 8)
+        P.prsgd_average(h)
+    assert rel_err(D.read_all(h), oracle_run(w, clean)["x"]) <= 1e-4
+    P.prsgd_destroy(dirty)
+    P.prsgd_destroy(h)
+
+
 def test_contexts_of_several_streams_together(P, D):
     """Five contexts of 64 workgroups on five streams could not all wait on the device at once: the runs are the
     same, whichever of them goes out in one launch."""
