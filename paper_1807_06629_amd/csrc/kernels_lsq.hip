@@ -485,8 +485,8 @@ __global__ __launch_bounds__(64 * W) void lsq_resident_kernel(LsqArgs p) {
 #pragma unroll
   for (int u = 0; u < D; ++u) request(u, u);
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"((D - 1) * REQ) : "memory");
-  // a wavefront past the minibatch requests nothing more, so that no later wait would be for these
-  if (n_rows == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // a wavefront past the minibatch that requests nothing more: no later wait would be for these
+  if (MANY && n_rows == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   take(0);
   __syncthreads();
 
@@ -557,9 +557,10 @@ __global__ __launch_bounds__(64 * W) void lsq_resident_kernel(LsqArgs p) {
   for (int s = 0; s < my_k; ++s) {
     if (((s + D) & 63) == 0) draw((s + D) >> 6);
     if ((s & 63) == 0 && s > 0) take_targets();
-    // This iteration's rows are in registers.  A wavefront past the minibatch keeps the rows of the first D iterations, which
-    // meet residuals of zero.
-    if (n_rows > 0) request(s + D, place);
+    // This iteration's rows are in registers.  With many workers a wavefront past the minibatch keeps the rows of the first D
+    // iterations, which meet residuals of zero.  With one workgroup per compute unit the branch costs more than the requests: 38 x
+    // (58 x 205) 3.57 and 3.74 us per iteration, 7 x (16 x 19) 0.73 and 0.76 (but 3 x (19 x 360) 1.98 and 1.77).
+    if (!MANY || n_rows > 0) request(s + D, place);
     place = place + 1 == D ? 0 : place + 1;
     float res[R];
 #pragma unroll
