@@ -95,8 +95,7 @@ __global__ __launch_bounds__(kThreads) void sample_indices_kernel(int32_t* __res
 }
 
 // Logits of classes c0, c0 + STRIDE, ... of one row: the product's output, or (split contraction) the bias plus the partial
-// sums in split order.  All Q (S + 1) loads are in flight together: indices are clamped, no load is conditional.  4096-4096-4096-
-// 4096-1000, 8 workers, 128 rows, interval 16: 1008.0 -> 1005.7 us per iteration against a part after the other.
+// sums in split order.  All Q (S + 1) loads are in flight together: indices are clamped, no load is conditional.
 template <int Q, int STRIDE, int S>
 __device__ __forceinline__ void fetch_logits_parts(float (&z)[Q], const float* __restrict__ row, long part_stride,
                                                    const float* __restrict__ bias, int c0, int n_classes) {

@@ -1088,7 +1088,7 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
   }
 
   // Zero the workspace once: padding columns of every activation buffer must read as zero, and
-  // the epoch kernel's arrival counters and abort flag start at zero (the static workspace keeps
+  // the numbers of the epoch kernel's exchanges and its abort flag start at zero (the static workspace keeps
   // what the previous context left in it).
   hipError_t e = hipMemsetAsync(ctx->ws, 0, ctx->cv.total, ctx->stream);
   if (e == hipSuccess) {

@@ -3,7 +3,7 @@
 Each case runs the same seeded problem through prsgd_init (caller-allocated workspace) and through
 prsgd_init_static and demands bit-identical replicas, losses and indices; the run is also held to
 the oracle at the usual tolerance.  Two static contexts are used in a row, the second smaller, so
-that what the first left in the shared array (partial logits, arrival counters, activations) must
+that what the first left in the shared array (partial logits, numbers of exchanges, activations) must
 not leak into the second.
 """
 import ctypes
@@ -35,7 +35,7 @@ def _run(P, D, w, inp, static):
 def test_static_workspace_contexts_match_allocated_ones_twice_in_a_row():
     from paper_1807_06629_amd import drivers as D, prsgd as P
     cases = [
-        # epoch kernel: partial logits and arrival counters live in the workspace
+        # epoch kernel: partial logits and the numbers of exchanges live in the workspace
         small_mlp(dims=(256, 128, 10), batch=8, n_workers=16, rows_per_worker=256, interval=4,
                   iterations=13, activation="relu", lr=0.02),
         # smaller, other kernels: per-layer chain with bf16 shadow, activations and the mean vector
