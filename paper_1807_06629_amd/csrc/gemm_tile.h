@@ -1,0 +1,326 @@
+// What the grouped products share: operand tiles requested into LDS, MFMA fragments, the workgroup's place, and the
+// epilogue of the batch-row products (gfx950 only).
+#pragma once
+
+#include <atomic>
+#include <type_traits>
+
+#include "prsgd_internal.h"
+
+namespace prsgd {
+
+enum { OP_CONTIG = 0, OP_TRANS = 1 };
+
+struct TF32 {
+  using elem = float;
+  static constexpr bool kBf16 = false;
+};
+struct TBF16 {
+  using elem = uint16_t;
+  static constexpr bool kBf16 = true;
+};
+constexpr int kTileBytes = 128;        // depth of a tile along the contraction
+constexpr int kSlices = 4;             // 32-byte slices of it, one fragment step each
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ float act_fwd(float z, int act) {
+  return act == PRSGD_TANH ? tanhf(z) : fmaxf(z, 0.0f);
+}
+__device__ __forceinline__ float act_bwd_from_h(float h, int act) {
+  return act == PRSGD_TANH ? (1.0f - h * h) : (h > 0.0f ? 1.0f : 0.0f);
+}
+
+// One operand tile of ROWS output rows (or columns) in LDS, and the requests that fill it.
+//   OP_CONTIG: element (r, c) at src[r * ld + c]; LDS [ROWS][128 bytes], chunks at lds_chunk
+//   OP_TRANS : element (r, c) at src[c * ld + r]; LDS [depth][ROWS], bf16 segments at lds_seg_xor
+// Rows past the operand are requested as copies of the last one (their results are not stored).
+template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
+  using E = typename T::elem;
+  static constexpr int ES = (int)sizeof(E), BK = kTileBytes / ES, V = 16 / ES;
+  static constexpr int BYTES = ROWS * kTileBytes;
+  static constexpr int NPT = BYTES / 1024 / NWAVE;         // requests per wavefront and tile
+  static_assert(BYTES % (1024 * NWAVE) == 0, "a tile must split evenly over the wavefronts");
+  static constexpr int ROW_BYTES = KIND == OP_CONTIG ? kTileBytes : ROWS * ES;
+  static constexpr int CH = ROW_BYTES / 16;                // 16-byte chunks of an LDS row
+
+  // permutation of the 64-byte segments of contraction row c (OP_TRANS)
+  __device__ static __forceinline__ int seg_xor(int c) { return T::kBf16 ? lds_seg_xor<ROW_BYTES>(c) : 0; }
+  // offsets (bytes from the tile's base address) of this lane's requests.  n_rows: rows of the operand
+  // from the tile's first; n_c: contraction elements from the tile's first (clamped like the rows)
+  __device__ static __forceinline__ void offsets(uint32_t (&off)[NPT], int ld, int n_rows, int n_c, int wave,
+                                                 int lane) {
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int chunk = (q * NWAVE + wave) * 64 + lane;    // position in the LDS tile
+      const int lr = chunk / CH, pos = chunk % CH;
+      if (KIND == OP_CONTIG) {
+        const int row = min(lr, n_rows - 1);
+        const int c = min(lds_chunk(lr, pos) * V, (n_c - 1) / V * V);
+        off[q] = (uint32_t)((size_t)row * ld + c) * ES;
+      } else {
+        const int c = min(lr, n_c - 1);
+        const int row = min(((((pos >> 2) ^ seg_xor(lr)) << 2) | (pos & 3)) * V, (n_rows - 1) / V * V);
+        off[q] = (uint32_t)((size_t)c * ld + row) * ES;
+      }
+    }
+  }
+  __device__ static __forceinline__ void request(const E* tile_base, const uint32_t (&off)[NPT], uint32_t lds_tile,
+                                                 int wave) {
+#pragma unroll
+    for (int q = 0; q < NPT; ++q)
+      load_to_lds(tile_base, off[q], lds_tile + (uint32_t)(q * NWAVE + wave) * 1024u);
+  }
+};
+
+// MFMA operand fragments of a 32-row block for the kk-th 32-byte slice.  Lane (r = lane % 32,
+// kb = lane / 32) holds contraction elements of row r; A and B fragments use the same assignment,
+// which is all the instruction needs for the product to be the plain sum over c.
+//   bf16: the eight elements 16 kk + 8 kb + 0..7 of one v_mfma_f32_32x32x16
+//   fp32: the four elements   8 kk + 4 kb + 0..3 of four v_mfma_f32_32x32x2
+template <typename T> struct Frag;
+template <> struct Frag<TBF16> { bf16x8_t v; };
+template <> struct Frag<TF32> { f32x4_t v; };
+
+template <typename T, int ROWS, int KIND, int NWAVE>
+__device__ __forceinline__ Frag<T> load_frag(const unsigned char* tile, int block, int kk, int lane) {
+  using IO = TileIO<T, ROWS, KIND, NWAVE>;
+  Frag<T> f;
+  const int r = lane & 31, kb = lane >> 5;
+  if constexpr (KIND == OP_CONTIG && T::kBf16) {
+    f.v = lds_frag_contig(tile, block, kk, lane);
+  } else if constexpr (KIND == OP_CONTIG) {
+    f.v = *reinterpret_cast<const f32x4_t*>(tile + (block * 32 + r) * kTileBytes + (lds_chunk(r, 2 * kk + kb) << 4));
+  } else if constexpr (T::kBf16) {
+    f.v = lds_frag_trans<IO::ROW_BYTES>(tile, block, kk, lane);
+  } else {
+    const unsigned char* p = tile + (8 * kk + 4 * kb) * IO::ROW_BYTES + (block * 32 + r) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f.v[e] = *reinterpret_cast<const float*>(p + e * IO::ROW_BYTES);
+  }
+  return f;
+}
+
+__device__ __forceinline__ f32x16_t mma(const Frag<TBF16>& a, const Frag<TBF16>& b, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t mma(const Frag<TF32>& a, const Frag<TF32>& b, f32x16_t c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e], b.v[e], c, 0, 0, 0);
+  return c;
+}
+// Fragment of all ones: as A operand every row of the 32 x 32 result holds the column sums of B.
+__device__ __forceinline__ void set_ones(Frag<TBF16>& f) {
+  const u16x8_t u = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
+  f.v = __builtin_bit_cast(bf16x8_t, u);
+}
+__device__ __forceinline__ void set_ones(Frag<TF32>& f) { f.v = (f32x4_t){1.0f, 1.0f, 1.0f, 1.0f}; }
+
+// Zeroes the contraction elements at and past n_c (the last tile of a ragged contraction; what was
+// requested there is some other element of the operand).
+__device__ __forceinline__ void mask_frag(Frag<TBF16>& f, int kk, int lane, int n_c) {
+  u32x4_t u = __builtin_bit_cast(u32x4_t, f.v);
+  const int c = 16 * kk + 8 * (lane >> 5);
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    u[e] &= (c + 2 * e < n_c ? 0xFFFFu : 0u) | (c + 2 * e + 1 < n_c ? 0xFFFF0000u : 0u);
+  f.v = __builtin_bit_cast(bf16x8_t, u);
+}
+__device__ __forceinline__ void mask_frag(Frag<TF32>& f, int kk, int lane, int n_c) {
+  const int c = 8 * kk + 4 * (lane >> 5);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) f.v[e] = c + e < n_c ? f.v[e] : 0.0f;
+}
+
+// Waits until all but the newest `ahead` tiles (PER requests each) have landed.
+template <int PER> __device__ __forceinline__ void wait_tiles(int ahead) {
+#define PRSGD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((n) * PER > 63 ? 63 : (n) * PER) : "memory")
+  switch (ahead) {
+    case 0: PRSGD_WAIT(0); break;
+    case 1: PRSGD_WAIT(1); break;
+    case 2: PRSGD_WAIT(2); break;
+    default: PRSGD_WAIT(3); break;
+  }
+#undef PRSGD_WAIT
+}
+
+template <typename T, int BM, int BN, int WK, int S> constexpr size_t gemm_lds_bytes() {
+  const size_t stages = (size_t)S * (BM + BN) * kTileBytes;
+  const size_t out = sizeof(float) * ((size_t)WK * BM * (BN + 4) + (size_t)WK * BN);
+  return stages > out ? stages : out;
+}
+
+// Workgroup -> (group, tile).  The hardware deals consecutive workgroups round-robin to the 8
+// XCDs; each XCD gets a contiguous range of the tiles, so that a group's activations and weight
+// panel stay in that XCD's L2.  The order is by group; with one weight stream for all groups
+// (b_gs == 0) by column tile first, and with a single group in 8-high strips of tiles.
+struct TileAt { int g, m0, n0, split, n_splits; };         // split: contraction range of n_splits
+template <int BM, int BN> __device__ __forceinline__ TileAt tile_at(const GemmArgs& p, int block) {
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+  TileAt t;
+  t.n_splits = p.k_splits > 1 ? p.k_splits : 1;
+  const int total = tiles_m * tiles_n * t.n_splits * p.n_groups;
+  const int xcd = block & 7;
+  int idx = xcd * (total >> 3) + min(xcd, total & 7) + (block >> 3);
+  t.split = idx % t.n_splits;
+  idx /= t.n_splits;
+  t.g = 0;
+  int tm, tn;
+  if (p.n_groups == 1) {
+    const int strip = idx / (8 * tiles_n), in = idx - strip * 8 * tiles_n;
+    const int high = min(8, tiles_m - 8 * strip);
+    tm = 8 * strip + in % high;
+    tn = in / high;
+  } else if (p.b_gs == 0) {
+    tm = idx % tiles_m;
+    idx /= tiles_m;
+    t.g = idx % p.n_groups;
+    tn = idx / p.n_groups;
+  } else {
+    t.g = idx / (tiles_m * tiles_n);
+    idx -= t.g * tiles_m * tiles_n;
+    tm = idx / tiles_n;
+    tn = idx % tiles_n;
+  }
+  t.m0 = tm * BM;
+  t.n0 = tn * BN;
+  return t;
+}
+// Its contraction range [k_lo, k_lo + Kc): whole tiles per split.
+template <int BK> __device__ __forceinline__ void contraction_range(const GemmArgs& p, const TileAt& t, int* k_lo, int* Kc) {
+  *Kc = p.Kc;
+  *k_lo = 0;
+  if (t.n_splits > 1) {
+    const int per = ((p.Kc + BK - 1) / BK + t.n_splits - 1) / t.n_splits * BK;
+    *k_lo = t.split * per;
+    *Kc = max(0, min(p.Kc - *k_lo, per));
+    if (*Kc == 0) *k_lo = 0;
+  }
+}
+
+// Epilogue of a batch-row product (DX: backward-data, otherwise forward): eight output columns per thread (16 bytes of bf16,
+// 32 of fp32), the same ones in every pass over the rows.  Bias and phi' operand are requested before the output tile is
+// collected in LDS, so that a workgroup ends on one memory latency instead of one per pass (16 iterations of six workers of
+// 1000-500-300-37 728 -> 716 us; of eight of 4096-4096-4096-4096-1000 at interval 1 8766 -> 8681 us).
+// The instruction cache is shared by the launches of an iteration, and what a launch runs has to be fetched again when they exceed
+// it (0.6 to 1 us per launch): a kernel holds one of the two epilogues, and tanh, 8 of which are 3 KB, once and not per pass.
+template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
+  using E = typename T::elem;
+  static constexpr int VPR = BN / 8, ROWS = NTHR / VPR, NV = (BM + ROWS - 1) / ROWS;
+  using Aux = std::conditional_t<T::kBf16, u16x8_t, f32x4_t>;
+  static constexpr int NH = DX ? NV : 1;
+  int r0, c, m0, n;                                        // first row and column in the tile; tile's first row; column
+  f32x4_t b_lo, b_hi;                                      // bias
+  Aux h_lo[NH], h_hi[T::kBf16 ? 1 : NH];                   // phi' operand
+
+  __device__ __forceinline__ RowsEpilogue(int m0_, int n0, int tid)
+      : r0(tid / VPR), c(8 * (tid % VPR)), m0(m0_), n(n0 + 8 * (tid % VPR)) {}
+  __device__ __forceinline__ void request(const GemmArgs& p, int g) {
+    const int nc = min(n, (p.out_cols - 1) / 8 * 8);       // copies past the operands, never stored
+    if constexpr (DX) {
+      const E* aux = reinterpret_cast<const E*>(p.aux) + (size_t)g * p.aux_gs + nc;
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        const E* ap = aux + (size_t)min(m0 + q * ROWS + r0, p.M - 1) * p.ldaux;
+        h_lo[q] = *reinterpret_cast<const Aux*>(ap);
+        if constexpr (!T::kBf16) h_hi[q] = *reinterpret_cast<const f32x4_t*>(ap + 4);
+      }
+    } else if (biased(p)) {
+      const float* bias = p.src + (size_t)g * p.src_gs + p.b_off + nc;
+      b_lo = *reinterpret_cast<const f32x4_t*>(bias);
+      b_hi = *reinterpret_cast<const f32x4_t*>(bias + 4);
+    }
+  }
+  // partial sums of a split contraction carry no bias: the loss head adds it once
+  __device__ static __forceinline__ bool biased(const GemmArgs& p) { return p.k_splits <= 1; }
+  // c_read(r, c): four floats of the output tile.  Padding columns [N, out_cols) are written as zeros.
+  template <typename F> __device__ __forceinline__ void store(const GemmArgs& p, int g, int split, F&& c_read) const {
+    if constexpr (DX) {
+      if (p.act == PRSGD_TANH) passes(p, g, split, c_read, [&](float (&z)[8], int q) __attribute__((always_inline)) { times_slope(z, q, PRSGD_TANH); });
+      else passes(p, g, split, c_read, [&](float (&z)[8], int q) __attribute__((always_inline)) { times_slope(z, q, PRSGD_RELU); });
+    } else if (p.epi == EPI_FWD_HIDDEN && p.act == PRSGD_TANH) {
+#pragma unroll 1
+      for (int q = 0; q < NV; ++q)
+        pass(p, g, split, q, c_read, [&](float (&z)[8], int) __attribute__((always_inline)) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) z[e] = tanhf(z[e]);
+        });
+    } else {
+      passes(p, g, split, c_read, [&](float (&z)[8], int) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z[e] = p.epi == EPI_FWD_HIDDEN ? act_fwd(z[e], PRSGD_RELU) : z[e];
+      });
+    }
+  }
+
+ private:
+  __device__ __forceinline__ void times_slope(float (&z)[8], int q, int act) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (T::kBf16) z[e] *= act_bwd_from_h(bf16_to_f32(h_lo[q][e]), act);
+      else z[e] *= act_bwd_from_h(e < 4 ? h_lo[q][e & 3] : h_hi[q][e & 3], act);
+    }
+  }
+  template <typename F, typename A>
+  __device__ __forceinline__ void passes(const GemmArgs& p, int g, int split, F&& c_read, A&& apply) const {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) pass(p, g, split, q, c_read, apply);
+  }
+  template <typename F, typename A>
+  __device__ __forceinline__ void pass(const GemmArgs& p, int g, int split, int q, F&& c_read, A&& apply) const {
+    const int r = q * ROWS + r0, m = m0 + r;
+    if (r >= BM || m >= p.M || n >= p.out_cols) return;
+    const f32x4_t lo = c_read(r, c), hi = c_read(r, c + 4);
+    float z[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { z[e] = lo[e]; z[4 + e] = hi[e]; }
+    if (!DX && biased(p)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { z[e] += b_lo[e]; z[4 + e] += b_hi[e]; }
+    }
+    apply(z, q);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) z[e] = n + e < p.N ? z[e] : 0.0f;
+    const size_t o = (size_t)g * p.out_gs + (size_t)m * p.ldo + n;
+    if (T::kBf16 && (DX || p.epi != EPI_FWD_LOGITS)) {
+      u16x8_t v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16_rne(z[e]);
+      *reinterpret_cast<u16x8_t*>(reinterpret_cast<uint16_t*>(p.out) + o) = v;
+    } else {
+      float* op = reinterpret_cast<float*>(p.out) + (!DX && p.epi == EPI_FWD_LOGITS ? (size_t)split * p.split_stride : 0) + o;
+      *reinterpret_cast<f32x4_t*>(op) = (f32x4_t){z[0], z[1], z[2], z[3]};
+      *reinterpret_cast<f32x4_t*>(op + 4) = (f32x4_t){z[4], z[5], z[6], z[7]};
+    }
+  }
+};
+
+// Tiles in flight of the products in 128 x 128 tiles, and those products (kernels_gemm_rows.hip).
+constexpr int kFedStages = 3;
+hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, hipStream_t s);
+hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, hipStream_t s);
+
+// Launches KERNEL (WAVES wavefronts per workgroup) with one workgroup per tile of BM x BN.
+template <typename T, int BM, int BN, int WK, int S, int WAVES, void (*KERNEL)(GemmArgs)>
+static hipError_t launch_tiles(GemmArgs p, int n_groups, hipStream_t s) {
+  if (p.M <= 0 || p.N <= 0 || n_groups <= 0) return hipSuccess;
+  constexpr size_t kLds = gemm_lds_bytes<T, BM, BN, WK, S>();
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+  // the tiles can exceed the 64 KB default; setting the limit twice is harmless
+  static std::atomic<bool> configured{false};
+  if (!configured.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    if (e != hipSuccess) return e;
+    configured.store(true, std::memory_order_release);
+  }
+  p.n_groups = n_groups;
+  if (p.k_splits > 1 && p.epi != EPI_FWD_LOGITS) return hipErrorInvalidValue;
+  const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) * (p.k_splits > 1 ? p.k_splits : 1);
+  hipLaunchKernelGGL(KERNEL, dim3((unsigned)(tiles * n_groups)), dim3(64 * WAVES), kLds, s, p);
+  return hipGetLastError();
+}
+
+}  // namespace prsgd

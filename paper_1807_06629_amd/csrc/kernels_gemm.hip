@@ -24,228 +24,9 @@
 // when the output tile leaves through LDS.
 #include <string.h>
 
-#include <atomic>
-#include <type_traits>
-
-#include "prsgd_internal.h"
+#include "gemm_tile.h"
 
 namespace prsgd {
-
-enum { OP_CONTIG = 0, OP_TRANS = 1 };
-
-struct TF32 {
-  using elem = float;
-  static constexpr bool kBf16 = false;
-};
-struct TBF16 {
-  using elem = uint16_t;
-  static constexpr bool kBf16 = true;
-};
-constexpr int kTileBytes = 128;        // depth of a tile along the contraction
-constexpr int kSlices = 4;             // 32-byte slices of it, one fragment step each
-
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ float act_fwd(float z, int act) {
-  return act == PRSGD_TANH ? tanhf(z) : fmaxf(z, 0.0f);
-}
-__device__ __forceinline__ float act_bwd_from_h(float h, int act) {
-  return act == PRSGD_TANH ? (1.0f - h * h) : (h > 0.0f ? 1.0f : 0.0f);
-}
-
-// One operand tile of ROWS output rows (or columns) in LDS, and the requests that fill it.
-//   OP_CONTIG: element (r, c) at src[r * ld + c]; LDS [ROWS][128 bytes], chunks at lds_chunk
-//   OP_TRANS : element (r, c) at src[c * ld + r]; LDS [depth][ROWS], bf16 segments at lds_seg_xor
-// Rows past the operand are requested as copies of the last one (their results are not stored).
-template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
-  using E = typename T::elem;
-  static constexpr int ES = (int)sizeof(E), BK = kTileBytes / ES, V = 16 / ES;
-  static constexpr int BYTES = ROWS * kTileBytes;
-  static constexpr int NPT = BYTES / 1024 / NWAVE;         // requests per wavefront and tile
-  static_assert(BYTES % (1024 * NWAVE) == 0, "a tile must split evenly over the wavefronts");
-  static constexpr int ROW_BYTES = KIND == OP_CONTIG ? kTileBytes : ROWS * ES;
-  static constexpr int CH = ROW_BYTES / 16;                // 16-byte chunks of an LDS row
-
-  // permutation of the 64-byte segments of contraction row c (OP_TRANS)
-  __device__ static __forceinline__ int seg_xor(int c) { return T::kBf16 ? lds_seg_xor<ROW_BYTES>(c) : 0; }
-  // offsets (bytes from the tile's base address) of this lane's requests.  n_rows: rows of the operand
-  // from the tile's first; n_c: contraction elements from the tile's first (clamped like the rows)
-  __device__ static __forceinline__ void offsets(uint32_t (&off)[NPT], int ld, int n_rows, int n_c, int wave,
-                                                 int lane) {
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-      const int chunk = (q * NWAVE + wave) * 64 + lane;    // position in the LDS tile
-      const int lr = chunk / CH, pos = chunk % CH;
-      if (KIND == OP_CONTIG) {
-        const int row = min(lr, n_rows - 1);
-        const int c = min(lds_chunk(lr, pos) * V, (n_c - 1) / V * V);
-        off[q] = (uint32_t)((size_t)row * ld + c) * ES;
-      } else {
-        const int c = min(lr, n_c - 1);
-        const int row = min(((((pos >> 2) ^ seg_xor(lr)) << 2) | (pos & 3)) * V, (n_rows - 1) / V * V);
-        off[q] = (uint32_t)((size_t)c * ld + row) * ES;
-      }
-    }
-  }
-  __device__ static __forceinline__ void request(const E* tile_base, const uint32_t (&off)[NPT], uint32_t lds_tile,
-                                                 int wave) {
-#pragma unroll
-    for (int q = 0; q < NPT; ++q)
-      load_to_lds(tile_base, off[q], lds_tile + (uint32_t)(q * NWAVE + wave) * 1024u);
-  }
-};
-
-// MFMA operand fragments of a 32-row block for the kk-th 32-byte slice.  Lane (r = lane % 32,
-// kb = lane / 32) holds contraction elements of row r; A and B fragments use the same assignment,
-// which is all the instruction needs for the product to be the plain sum over c.
-//   bf16: the eight elements 16 kk + 8 kb + 0..7 of one v_mfma_f32_32x32x16
-//   fp32: the four elements   8 kk + 4 kb + 0..3 of four v_mfma_f32_32x32x2
-template <typename T> struct Frag;
-template <> struct Frag<TBF16> { bf16x8_t v; };
-template <> struct Frag<TF32> { f32x4_t v; };
-
-template <typename T, int ROWS, int KIND, int NWAVE>
-__device__ __forceinline__ Frag<T> load_frag(const unsigned char* tile, int block, int kk, int lane) {
-  using IO = TileIO<T, ROWS, KIND, NWAVE>;
-  Frag<T> f;
-  const int r = lane & 31, kb = lane >> 5;
-  if constexpr (KIND == OP_CONTIG && T::kBf16) {
-    f.v = lds_frag_contig(tile, block, kk, lane);
-  } else if constexpr (KIND == OP_CONTIG) {
-    f.v = *reinterpret_cast<const f32x4_t*>(tile + (block * 32 + r) * kTileBytes + (lds_chunk(r, 2 * kk + kb) << 4));
-  } else if constexpr (T::kBf16) {
-    f.v = lds_frag_trans<IO::ROW_BYTES>(tile, block, kk, lane);
-  } else {
-    const unsigned char* p = tile + (8 * kk + 4 * kb) * IO::ROW_BYTES + (block * 32 + r) * 4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) f.v[e] = *reinterpret_cast<const float*>(p + e * IO::ROW_BYTES);
-  }
-  return f;
-}
-
-__device__ __forceinline__ f32x16_t mma(const Frag<TBF16>& a, const Frag<TBF16>& b, f32x16_t c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x16_t mma(const Frag<TF32>& a, const Frag<TF32>& b, f32x16_t c) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e], b.v[e], c, 0, 0, 0);
-  return c;
-}
-// Fragment of all ones: as A operand every row of the 32 x 32 result holds the column sums of B.
-__device__ __forceinline__ void set_ones(Frag<TBF16>& f) {
-  const u16x8_t u = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
-  f.v = __builtin_bit_cast(bf16x8_t, u);
-}
-__device__ __forceinline__ void set_ones(Frag<TF32>& f) { f.v = (f32x4_t){1.0f, 1.0f, 1.0f, 1.0f}; }
-
-// Zeroes the contraction elements at and past n_c (the last tile of a ragged contraction; what was
-// requested there is some other element of the operand).
-__device__ __forceinline__ void mask_frag(Frag<TBF16>& f, int kk, int lane, int n_c) {
-  u32x4_t u = __builtin_bit_cast(u32x4_t, f.v);
-  const int c = 16 * kk + 8 * (lane >> 5);
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    u[e] &= (c + 2 * e < n_c ? 0xFFFFu : 0u) | (c + 2 * e + 1 < n_c ? 0xFFFF0000u : 0u);
-  f.v = __builtin_bit_cast(bf16x8_t, u);
-}
-__device__ __forceinline__ void mask_frag(Frag<TF32>& f, int kk, int lane, int n_c) {
-  const int c = 8 * kk + 4 * (lane >> 5);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) f.v[e] = c + e < n_c ? f.v[e] : 0.0f;
-}
-
-// Waits until all but the newest `ahead` tiles (PER requests each) have landed.
-template <int PER> __device__ __forceinline__ void wait_tiles(int ahead) {
-#define PRSGD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((n) * PER > 63 ? 63 : (n) * PER) : "memory")
-  switch (ahead) {
-    case 0: PRSGD_WAIT(0); break;
-    case 1: PRSGD_WAIT(1); break;
-    case 2: PRSGD_WAIT(2); break;
-    default: PRSGD_WAIT(3); break;
-  }
-#undef PRSGD_WAIT
-}
-
-template <typename T, int BM, int BN, int WK, int S> constexpr size_t gemm_lds_bytes() {
-  const size_t stages = (size_t)S * (BM + BN) * kTileBytes;
-  const size_t out = sizeof(float) * ((size_t)WK * BM * (BN + 4) + (size_t)WK * BN);
-  return stages > out ? stages : out;
-}
-
-// Epilogue of a batch-row product: eight output columns per thread (16 bytes of bf16, 32 of fp32), the same ones in every
-// pass over the rows.  Bias and phi' operand are requested before the output tile is collected in LDS, so that a workgroup
-// ends on one memory latency instead of one per pass (16 iterations of six workers of 1000-500-300-37 728 -> 716 us; of eight of
-// 4096-4096-4096-4096-1000 at interval 1 8766 -> 8681 us).
-template <typename T, int BM, int BN, int NTHR> struct RowsEpilogue {
-  using E = typename T::elem;
-  static constexpr int VPR = BN / 8, ROWS = NTHR / VPR, NV = (BM + ROWS - 1) / ROWS;
-  int r0, c, m0, n;                                        // first row and column in the tile; tile's first row; column
-  f32x4_t b_lo, b_hi;
-  using Aux = std::conditional_t<T::kBf16, u16x8_t, f32x4_t>;
-  Aux h_lo[NV], h_hi[T::kBf16 ? 1 : NV];                   // phi' operand
-
-  __device__ __forceinline__ RowsEpilogue(int m0_, int n0, int tid)
-      : r0(tid / VPR), c(8 * (tid % VPR)), m0(m0_), n(n0 + 8 * (tid % VPR)) {}
-  __device__ __forceinline__ void request(const GemmArgs& p, int g) {
-    const int nc = min(n, (p.out_cols - 1) / 8 * 8);       // copies past the operands, never stored
-    if (p.epi == EPI_DX) {
-      const E* aux = reinterpret_cast<const E*>(p.aux) + (size_t)g * p.aux_gs + nc;
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        const E* ap = aux + (size_t)min(m0 + q * ROWS + r0, p.M - 1) * p.ldaux;
-        h_lo[q] = *reinterpret_cast<const Aux*>(ap);
-        if constexpr (!T::kBf16) h_hi[q] = *reinterpret_cast<const f32x4_t*>(ap + 4);
-      }
-    } else if (biased(p)) {
-      const float* bias = p.src + (size_t)g * p.src_gs + p.b_off + nc;
-      b_lo = *reinterpret_cast<const f32x4_t*>(bias);
-      b_hi = *reinterpret_cast<const f32x4_t*>(bias + 4);
-    }
-  }
-  // partial sums of a split contraction carry no bias: the loss head adds it once
-  __device__ static __forceinline__ bool biased(const GemmArgs& p) { return p.epi != EPI_DX && p.k_splits <= 1; }
-  // c_read(r, c): four floats of the output tile.  Padding columns [N, out_cols) are written as zeros.
-  template <typename F> __device__ __forceinline__ void store(const GemmArgs& p, int g, int split, F&& c_read) const {
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      const int r = q * ROWS + r0, m = m0 + r;
-      if (r >= BM || m >= p.M || n >= p.out_cols) continue;
-      const f32x4_t lo = c_read(r, c), hi = c_read(r, c + 4);
-      float z[8];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { z[e] = lo[e]; z[4 + e] = hi[e]; }
-      if (biased(p)) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { z[e] += b_lo[e]; z[4 + e] += b_hi[e]; }
-      }
-      if (p.epi == EPI_FWD_HIDDEN) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = act_fwd(z[e], p.act);
-      } else if (p.epi == EPI_DX) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if constexpr (T::kBf16) z[e] *= act_bwd_from_h(bf16_to_f32(h_lo[q][e]), p.act);
-          else z[e] *= act_bwd_from_h(e < 4 ? h_lo[q][e & 3] : h_hi[q][e & 3], p.act);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) z[e] = n + e < p.N ? z[e] : 0.0f;
-      const size_t o = (size_t)g * p.out_gs + (size_t)m * p.ldo + n;
-      if (T::kBf16 && p.epi != EPI_FWD_LOGITS) {
-        u16x8_t v;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16_rne(z[e]);
-        *reinterpret_cast<u16x8_t*>(reinterpret_cast<uint16_t*>(p.out) + o) = v;
-      } else {
-        float* op = reinterpret_cast<float*>(p.out) + (p.epi == EPI_FWD_LOGITS ? (size_t)split * p.split_stride : 0) + o;
-        *reinterpret_cast<f32x4_t*>(op) = (f32x4_t){z[0], z[1], z[2], z[3]};
-        *reinterpret_cast<f32x4_t*>(op + 4) = (f32x4_t){z[4], z[5], z[6], z[7]};
-      }
-    }
-  }
-};
 
 // One output tile of product p: workgroup `block` of the product's.
 template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
@@ -261,36 +42,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   static_assert(kSlices % WK == 0, "the slices of a tile must split evenly over the shares");
   static_assert(S >= 2 && S <= 4 && PER * (S - 1) <= 63, "wait_tiles");
 
-  // Workgroup -> (group, tile).  The hardware deals consecutive workgroups round-robin to the 8
-  // XCDs; each XCD gets a contiguous range of the tiles, so that a group's activations and weight
-  // panel stay in that XCD's L2.  The order is by group; with one weight stream for all groups
-  // (b_gs == 0) by column tile first, and with a single group in 8-high strips of tiles.
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  const int n_splits = p.k_splits > 1 ? p.k_splits : 1;     // contraction ranges per output tile
-  const int total = tiles_m * tiles_n * n_splits * p.n_groups;
-  const int xcd = block & 7;
-  int idx = xcd * (total >> 3) + min(xcd, total & 7) + (block >> 3);
-  const int ks = idx % n_splits;
-  idx /= n_splits;
-  int g = 0, tm, tn;
-  if (p.n_groups == 1) {
-    const int strip = idx / (8 * tiles_n), in = idx - strip * 8 * tiles_n;
-    const int high = min(8, tiles_m - 8 * strip);
-    tm = 8 * strip + in % high;
-    tn = in / high;
-  } else if (p.b_gs == 0) {
-    tm = idx % tiles_m;
-    idx /= tiles_m;
-    g = idx % p.n_groups;
-    tn = idx / p.n_groups;
-  } else {
-    g = idx / (tiles_m * tiles_n);
-    idx -= g * tiles_m * tiles_n;
-    tm = idx / tiles_n;
-    tn = idx % tiles_n;
-  }
+  const TileAt at = tile_at<BM, BN>(p, block);
+  const int g = at.g, m0 = at.m0, n0 = at.n0, ks = at.split, n_splits = at.n_splits;
   if (p.worker_steps != nullptr && p.step >= p.worker_steps[g]) return;
-  const int m0 = tm * BM, n0 = tn * BN;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int STAGE = (BM + BN) * kTileBytes;
@@ -301,14 +55,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   const int wk = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
   const int lr32 = lane & 31, kb = lane >> 5;
 
-  // this workgroup's contraction range [k_lo, k_lo + Kc): whole tiles per split
-  int Kc = p.Kc, k_lo = 0;
-  if (n_splits > 1) {
-    const int per = ((p.Kc + BK - 1) / BK + n_splits - 1) / n_splits * BK;
-    k_lo = ks * per;
-    Kc = max(0, min(p.Kc - k_lo, per));
-    if (Kc == 0) k_lo = 0;
-  }
+  int Kc, k_lo;
+  contraction_range<BK>(p, at, &k_lo, &Kc);
   const E* a_src = reinterpret_cast<const E*>(p.a) + (size_t)g * p.a_gs +
                    (AKIND == OP_CONTIG ? (size_t)m0 * p.lda + k_lo : (size_t)k_lo * p.lda + m0);
   const E* b_src = reinterpret_cast<const E*>(p.b) + (size_t)g * p.b_gs +
@@ -454,7 +202,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
       }
     }
   }
-  RowsEpilogue<T, BM, BN, NTHR> out(m0, n0, tid);
+  RowsEpilogue<T, BM, BN, NTHR, BKIND == OP_CONTIG> out(m0, n0, tid);
   if constexpr (!kIsDw) out.request(p, g);
   __syncthreads();                                         // every wavefront is done with the last tile
 
@@ -547,26 +295,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_set_kernel(
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
-static hipError_t launch_one(GemmArgs p, int n_groups, hipStream_t s) {
-  if (p.M <= 0 || p.N <= 0 || n_groups <= 0) return hipSuccess;
-  constexpr size_t kLds = gemm_lds_bytes<T, BM, BN, WK, S>();
-  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
-  auto kernel = grouped_gemm_kernel<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>;
-  // the tiles can exceed the 64 KB default; setting the limit twice is harmless
-  static std::atomic<bool> configured{false};
-  if (!configured.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-    if (e != hipSuccess) return e;
-    configured.store(true, std::memory_order_release);
-  }
-  p.n_groups = n_groups;
-  if (p.k_splits > 1 && p.epi != EPI_FWD_LOGITS) return hipErrorInvalidValue;
-  const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) * (p.k_splits > 1 ? p.k_splits : 1);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * n_groups)), dim3(64 * WM * WN * WK), kLds, s, p);
-  return hipGetLastError();
+static hipError_t launch_one(const GemmArgs& p, int n_groups, hipStream_t s) {
+  return launch_tiles<T, BM, BN, WK, S, WM * WN * WK, grouped_gemm_kernel<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>>(
+      p, n_groups, s);
 }
-
 constexpr int kComputeUnits = 256;
 
 // Batch-row products (forward, backward-data).  What bounds a launch is the rate at which one compute
@@ -614,8 +346,7 @@ static hipError_t launch_rows_bf16(const GemmArgs& p, int n_groups, hipStream_t 
   if (t.bm == 32) return launch_one<TBF16, 32, 64, 1, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
   if (t.bm == 64) return launch_one<TBF16, 64, 64, 2, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
   if (t.bn == 64) return launch_one<TBF16, 128, 64, 4, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
-  // eight wavefronts: two per SIMD cover the LDS latency of each other
-  return launch_one<TBF16, 128, 128, 2, 4, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
+  return BKIND == OP_CONTIG ? launch_gemm_dx_fed(p, n_groups, s) : launch_gemm_fwd_fed(p, n_groups, s);
 }
 template <int AKIND, int BKIND>
 static hipError_t launch_rows_f32(const GemmArgs& p, int n_groups, hipStream_t s) {
@@ -634,7 +365,7 @@ void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows
   *lds_bytes = !bf16 ? (t.bm == 64 ? gemm_lds_bytes<TF32, 64, 64, 1, 4>() : gemm_lds_bytes<TF32, 32, 32, 4, kRowStages>())
                : t.bm == 32 ? gemm_lds_bytes<TBF16, 32, 64, 1, kRowStages>()
                : t.bm == 64 ? gemm_lds_bytes<TBF16, 64, 64, 1, kRowStages>()
-               : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, kRowStages>();
+               : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, kFedStages>();
 }
 
 // A logits product that leaves most compute units idle (few classes) cuts its contraction into
