@@ -48,22 +48,25 @@ template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
 
   // permutation of the 64-byte segments of contraction row c (OP_TRANS)
   __device__ static __forceinline__ int seg_xor(int c) { return T::kBf16 ? lds_seg_xor<ROW_BYTES>(c) : 0; }
-  // offsets (bytes from the tile's base address) of this lane's requests.  n_rows: rows of the operand
-  // from the tile's first; n_c: contraction elements from the tile's first (clamped like the rows)
+  // offsets (bytes from the tile's base address, 32 bits: a tile is at most 128 rows of 2^20 elements) of this lane's requests.
+  // n_rows: rows of the operand from the tile's first; n_c (RAGGED): contraction elements from the tile's first, clamped like
+  // the rows
+  template <bool RAGGED>
   __device__ static __forceinline__ void offsets(uint32_t (&off)[NPT], int ld, int n_rows, int n_c, int wave,
                                                  int lane) {
 #pragma unroll
     for (int q = 0; q < NPT; ++q) {
-      const int chunk = (q * NWAVE + wave) * 64 + lane;    // position in the LDS tile
-      const int lr = chunk / CH, pos = chunk % CH;
+      const uint32_t chunk = (uint32_t)(q * NWAVE + wave) * 64 + (uint32_t)lane;       // position in the LDS tile
+      const int lr = (int)(chunk / CH), pos = (int)(chunk % CH);
       if (KIND == OP_CONTIG) {
         const int row = min(lr, n_rows - 1);
-        const int c = min(lds_chunk(lr, pos) * V, (n_c - 1) / V * V);
-        off[q] = (uint32_t)((size_t)row * ld + c) * ES;
+        int c = lds_chunk(lr, pos) * V;
+        if (RAGGED) c = min(c, (n_c - 1) & ~(V - 1));
+        off[q] = (__umul24((uint32_t)row, (uint32_t)ld) + (uint32_t)c) * ES;
       } else {
-        const int c = min(lr, n_c - 1);
-        const int row = min(((((pos >> 2) ^ seg_xor(lr)) << 2) | (pos & 3)) * V, (n_rows - 1) / V * V);
-        off[q] = (uint32_t)((size_t)c * ld + row) * ES;
+        const int c = RAGGED ? min(lr, n_c - 1) : lr;
+        const int row = min(((((pos >> 2) ^ seg_xor(lr)) << 2) | (pos & 3)) * V, (n_rows - 1) & ~(V - 1));
+        off[q] = (__umul24((uint32_t)c, (uint32_t)ld) + (uint32_t)row) * ES;
       }
     }
   }
@@ -156,44 +159,91 @@ template <typename T, int BM, int BN, int WK, int S> constexpr size_t gemm_lds_b
 // XCDs; each XCD gets a contiguous range of the tiles, so that a group's activations and weight
 // panel stay in that XCD's L2.  The order is by group; with one weight stream for all groups
 // (b_gs == 0) by column tile first, and with a single group in 8-high strips of tiles.
+// What the divisions need is worked out on the host (place_tiles): eight of them by values that the compiler does not know
+// were half of the 430 to 570 instructions, at 5 cycles each and more, in front of a workgroup's first request (16 iterations of
+// 784-300-100-10 in fp32, eight workers, 691 -> 655 us; of 1000-500-300-37, six workers, 702 -> 665 us).
+// n / d = (mulhi(mul, n) + n) >> shift for n < 2^31 (Granlund and Montgomery, "Division by invariant integers using
+// multiplication", 1994)
+constexpr TileDivisor tile_divisor(uint32_t d) {
+  uint32_t shift = 0;
+  while ((1ull << shift) < d) ++shift;
+  return TileDivisor{(uint32_t)((((1ull << shift) - d) << 32) / d + 1), shift, d};
+}
+constexpr bool divides(uint32_t d) {                       // at both ends of the first and the last quotients
+  const TileDivisor v = tile_divisor(d);
+  for (uint32_t i = 0; i < 16; ++i) {
+    const uint32_t q = i < 8 ? i : 0x7FFFFFFFu / d - (i - 8), lo = q * d, hi = 0x7FFFFFFFu - lo < d ? 0x7FFFFFFFu : lo + d - 1;
+    if ((i >= 8 && 0x7FFFFFFFu / d < 16) || lo > 0x7FFFFFFFu) continue;
+    for (const uint32_t n : {lo, hi})
+      if ((uint32_t)((((uint64_t)v.mul * n) >> 32) + n) >> v.shift != n / d) return false;
+  }
+  return true;
+}
+constexpr bool divides_up_to(uint32_t d) { return d == 0 || (divides(d) && divides_up_to(d - 1)); }
+static_assert(divides_up_to(400) && divides(641) && divides(4096) && divides(65537) && divides(1000003), "tile_divisor");
+__device__ __forceinline__ int quotient(const TileDivisor& v, int n) {
+  return (int)((__umulhi(v.mul, (uint32_t)n) + (uint32_t)n) >> v.shift);
+}
+// Fills in the placement of p's tiles of bm x bn; returns the workgroups of the product.
+inline int place_tiles(GemmArgs* p, int bm, int bn, int n_groups) {
+  const int tiles_m = (p->M + bm - 1) / bm, tiles_n = (p->N + bn - 1) / bn;
+  const int n_splits = p->k_splits > 1 ? p->k_splits : 1;  // 1, 2 or 4
+  const int total = tiles_m * tiles_n * n_splits * n_groups;
+  TilePlace& t = p->place;
+  t.xcd_tiles = total >> 3;
+  t.xcd_extra = total & 7;
+  t.split_shift = n_splits == 4 ? 2 : n_splits == 2 ? 1 : 0;
+  t.order = n_groups == 1 ? 2 : p->b_gs == 0 ? 1 : 0;
+  t.first = tile_divisor(t.order == 2 ? 8 * tiles_n : t.order == 1 ? tiles_m : tiles_m * tiles_n);
+  t.second = tile_divisor(t.order == 2 ? 8 : t.order == 1 ? n_groups : tiles_n);
+  t.whole_strips = tiles_m >> 3;
+  t.last_strip = tile_divisor((tiles_m & 7) != 0 ? tiles_m & 7 : 1);
+  return total;
+}
+// Asks for every line of a product's arguments at once, and for what the first request of an operand tile needs, and waits for them.
+// Left alone, each is asked for where it is first used, in four to six waits behind each other, and the lines are in no cache
+// when a launch begins: 16 iterations of 784-300-100-10 in fp32, eight workers, 655 -> 631 us, of 1000-500-300-37, six
+// workers, 665 -> 636 us.
+__device__ __forceinline__ void fetch_args(const GemmArgs& p) {
+  static_assert(sizeof(GemmArgs) <= 5 * 64, "a word of every 64 bytes");
+  const int* w = reinterpret_cast<const int*>(&p);
+  asm volatile("" :: "s"(w[0]), "s"(w[16]), "s"(w[32]), "s"(w[48]), "s"(w[sizeof(GemmArgs) / 4 - 1]),
+               "s"(p.a), "s"(p.a_gs), "s"(p.lda), "s"(p.b), "s"(p.b_gs), "s"(p.ldb), "s"(p.M), "s"(p.N), "s"(p.Kc),
+               "s"(p.place.first.mul), "s"(p.place.second.mul), "s"(p.place.order), "s"(p.worker_steps));
+}
 struct TileAt { int g, m0, n0, split, n_splits; };         // split: contraction range of n_splits
 template <int BM, int BN> __device__ __forceinline__ TileAt tile_at(const GemmArgs& p, int block) {
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  TileAt t;
-  t.n_splits = p.k_splits > 1 ? p.k_splits : 1;
-  const int total = tiles_m * tiles_n * t.n_splits * p.n_groups;
+  const TilePlace& t = p.place;
+  TileAt r;
   const int xcd = block & 7;
-  int idx = xcd * (total >> 3) + min(xcd, total & 7) + (block >> 3);
-  t.split = idx % t.n_splits;
-  idx /= t.n_splits;
-  t.g = 0;
+  int idx = xcd * t.xcd_tiles + min(xcd, t.xcd_extra) + (block >> 3);
+  r.n_splits = 1 << t.split_shift;
+  r.split = idx & (r.n_splits - 1);
+  idx >>= t.split_shift;
+  const int q = quotient(t.first, idx), in = idx - q * (int)t.first.d;
   int tm, tn;
-  if (p.n_groups == 1) {
-    const int strip = idx / (8 * tiles_n), in = idx - strip * 8 * tiles_n;
-    const int high = min(8, tiles_m - 8 * strip);
-    tm = 8 * strip + in % high;
-    tn = in / high;
-  } else if (p.b_gs == 0) {
-    tm = idx % tiles_m;
-    idx /= tiles_m;
-    t.g = idx % p.n_groups;
-    tn = idx / p.n_groups;
+  if (t.order == 2) {                                      // strip q, `high` tiles high
+    TileDivisor high = t.second;
+    if (q == t.whole_strips) high = t.last_strip;
+    tn = quotient(high, in);
+    tm = 8 * q + in - tn * (int)high.d;
+    r.g = 0;
   } else {
-    t.g = idx / (tiles_m * tiles_n);
-    idx -= t.g * tiles_m * tiles_n;
-    tm = idx / tiles_n;
-    tn = idx % tiles_n;
+    const int of = t.order == 1 ? q : in, u = quotient(t.second, of), v = of - u * (int)t.second.d;
+    tm = t.order == 1 ? in : u;
+    tn = t.order == 1 ? u : v;
+    r.g = t.order == 1 ? v : q;
   }
-  t.m0 = tm * BM;
-  t.n0 = tn * BN;
-  return t;
+  r.m0 = tm * BM;
+  r.n0 = tn * BN;
+  return r;
 }
 // Its contraction range [k_lo, k_lo + Kc): whole tiles per split.
 template <int BK> __device__ __forceinline__ void contraction_range(const GemmArgs& p, const TileAt& t, int* k_lo, int* Kc) {
   *Kc = p.Kc;
   *k_lo = 0;
   if (t.n_splits > 1) {
-    const int per = ((p.Kc + BK - 1) / BK + t.n_splits - 1) / t.n_splits * BK;
+    const int per = (((p.Kc + BK - 1) / BK + t.n_splits - 1) >> p.place.split_shift) * BK;
     *k_lo = t.split * per;
     *Kc = max(0, min(p.Kc - *k_lo, per));
     if (*Kc == 0) *k_lo = 0;
@@ -220,10 +270,10 @@ template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
   __device__ __forceinline__ void request(const GemmArgs& p, int g) {
     const int nc = min(n, (p.out_cols - 1) / 8 * 8);       // copies past the operands, never stored
     if constexpr (DX) {
-      const E* aux = reinterpret_cast<const E*>(p.aux) + (size_t)g * p.aux_gs + nc;
+      const E* aux = reinterpret_cast<const E*>(p.aux) + (size_t)g * p.aux_gs + (size_t)m0 * p.ldaux;
 #pragma unroll
       for (int q = 0; q < NV; ++q) {
-        const E* ap = aux + (size_t)min(m0 + q * ROWS + r0, p.M - 1) * p.ldaux;
+        const E* ap = aux + (__umul24((uint32_t)min(q * ROWS + r0, p.M - 1 - m0), (uint32_t)p.ldaux) + (uint32_t)nc);
         h_lo[q] = *reinterpret_cast<const Aux*>(ap);
         if constexpr (!T::kBf16) h_hi[q] = *reinterpret_cast<const f32x4_t*>(ap + 4);
       }
@@ -283,14 +333,15 @@ template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
     apply(z, q);
 #pragma unroll
     for (int e = 0; e < 8; ++e) z[e] = n + e < p.N ? z[e] : 0.0f;
-    const size_t o = (size_t)g * p.out_gs + (size_t)m * p.ldo + n;
+    const size_t base = (size_t)g * p.out_gs + (size_t)m0 * p.ldo;
+    const uint32_t o = __umul24((uint32_t)r, (uint32_t)p.ldo) + (uint32_t)n;
     if (T::kBf16 && (DX || p.epi != EPI_FWD_LOGITS)) {
       u16x8_t v;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16_rne(z[e]);
-      *reinterpret_cast<u16x8_t*>(reinterpret_cast<uint16_t*>(p.out) + o) = v;
+      *reinterpret_cast<u16x8_t*>(reinterpret_cast<uint16_t*>(p.out) + base + o) = v;
     } else {
-      float* op = reinterpret_cast<float*>(p.out) + (!DX && p.epi == EPI_FWD_LOGITS ? (size_t)split * p.split_stride : 0) + o;
+      float* op = reinterpret_cast<float*>(p.out) + base + (!DX && p.epi == EPI_FWD_LOGITS ? (size_t)split * p.split_stride : 0) + o;
       *reinterpret_cast<f32x4_t*>(op) = (f32x4_t){z[0], z[1], z[2], z[3]};
       *reinterpret_cast<f32x4_t*>(op + 4) = (f32x4_t){z[4], z[5], z[6], z[7]};
     }
@@ -316,10 +367,9 @@ static hipError_t launch_tiles(GemmArgs p, int n_groups, hipStream_t s) {
     if (e != hipSuccess) return e;
     configured.store(true, std::memory_order_release);
   }
-  p.n_groups = n_groups;
   if (p.k_splits > 1 && p.epi != EPI_FWD_LOGITS) return hipErrorInvalidValue;
-  const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) * (p.k_splits > 1 ? p.k_splits : 1);
-  hipLaunchKernelGGL(KERNEL, dim3((unsigned)(tiles * n_groups)), dim3(64 * WAVES), kLds, s, p);
+  const int tiles = place_tiles(&p, BM, BN, n_groups);
+  hipLaunchKernelGGL(KERNEL, dim3((unsigned)tiles), dim3(64 * WAVES), kLds, s, p);
   return hipGetLastError();
 }
 

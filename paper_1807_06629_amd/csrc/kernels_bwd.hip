@@ -51,6 +51,7 @@ __device__ __forceinline__ float dact_from_h(float h, int act) {
 // update, v <- mu v + G, x <- x - gamma v, with the velocity tile streamed beside the weights.
 template <int MB, bool DX, int S, bool MOM>
 __global__ __launch_bounds__(kThreads) void grouped_bwd_kernel(BwdArgs p) {
+  fetch_kernel_args<sizeof(BwdArgs)>();
   constexpr int BR = 32 * MB;
   constexpr int NTD = DX ? (2 * MB + 3) / 4 : 1;     // D_{l-1} accumulator tiles per wavefront
 
@@ -316,6 +317,7 @@ constexpr int kMaxBiasTiles = 4;   // column tiles whose bias a workgroup may ow
 
 template <int MB, bool DX, int S, bool MOM, bool NT, int KB>
 __global__ __launch_bounds__(kThreads) void grouped_bwd_full_kernel(BwdArgs p) {
+  fetch_kernel_args<sizeof(BwdArgs)>();
   constexpr int BR = 32 * MB;
   constexpr int KH = KB / 32;                          // 32-row halves of the band
   constexpr int QW = KB / 16;                          // 16-byte vectors of a weight tile per thread

@@ -67,6 +67,7 @@ constexpr size_t first_lds_bytes(int mb, int nb) {
 // product reads it, and the caller refreshes it when the chain of activations from here breaks.
 template <int MB, int NB, bool NT, bool MOM>
 __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdArgs p) {
+  fetch_kernel_args<sizeof(BwdArgs)>();
   constexpr int BR = 32 * MB;
   constexpr int NW = NB / 16, NTHR = 64 * NW;         // wavefronts: 2 (rows) x NB / 32 (columns)
   constexpr int NBLK = MB * (NB / 32);                // next-activation blocks (32 x 32)

@@ -42,6 +42,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   static_assert(kSlices % WK == 0, "the slices of a tile must split evenly over the shares");
   static_assert(S >= 2 && S <= 4 && PER * (S - 1) <= 63, "wait_tiles");
 
+  fetch_args(p);
   const TileAt at = tile_at<BM, BN>(p, block);
   const int g = at.g, m0 = at.m0, n0 = at.n0, ks = at.split, n_splits = at.n_splits;
   if (p.worker_steps != nullptr && p.step >= p.worker_steps[g]) return;
@@ -70,14 +71,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   const int n_k = (Kc + BK - 1) / BK;
   const int k_tail = Kc - (n_k - 1) * BK;                  // elements of the last tile
   uint32_t a_off[IOA::NPT], b_off[IOB::NPT];
-  IOA::offsets(a_off, p.lda, p.M - m0, BK, wave, lane);
-  IOB::offsets(b_off, p.ldb, p.N - n0, BK, wave, lane);
+  IOA::template offsets<false>(a_off, p.lda, p.M - m0, BK, wave, lane);
+  IOB::template offsets<false>(b_off, p.ldb, p.N - n0, BK, wave, lane);
   auto request = [&](int j, int stage) __attribute__((always_inline)) {
     const uint32_t lds_a = lds0 + (uint32_t)stage * STAGE, lds_b = lds_a + BM * kTileBytes;
     if (j == n_k - 1 && k_tail < BK) {                     // nothing past the operands is touched
       uint32_t a_o[IOA::NPT], b_o[IOB::NPT];
-      IOA::offsets(a_o, p.lda, p.M - m0, k_tail, wave, lane);
-      IOB::offsets(b_o, p.ldb, p.N - n0, k_tail, wave, lane);
+      IOA::template offsets<true>(a_o, p.lda, p.M - m0, k_tail, wave, lane);
+      IOB::template offsets<true>(b_o, p.ldb, p.N - n0, k_tail, wave, lane);
       IOA::request(a_src + (size_t)j * a_step, a_o, lds_a, wave);
       IOB::request(b_src + (size_t)j * b_step, b_o, lds_b, wave);
     } else {
@@ -95,13 +96,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   const int e_row = tid / VPR_C, e_col = 4 * (tid % VPR_C);
   f32x4_t w_old[EV];
   if constexpr (kIsDw) if (fused) {
-    const float* wbase = p.src + (size_t)g * p.src_gs + p.w_off;
+    const float* wtile = p.src + (size_t)g * p.src_gs + p.w_off + (size_t)m0 * p.ldw + n0;
     const bool nt_read = p.streaming && p.src_gs != 0;     // a shared source is re-read by every group
 #pragma unroll
     for (int q = 0; q < EV; ++q) {
-      const int m = m0 + q * ROWS_PER_PASS + e_row, n = n0 + e_col;
-      const bool ok = m < p.M && n < p.N;
-      const f32x4_t* wp = reinterpret_cast<const f32x4_t*>(wbase + (ok ? (size_t)m * p.ldw + n : (size_t)0));
+      const int r = q * ROWS_PER_PASS + e_row;
+      const bool ok = m0 + r < p.M && n0 + e_col < p.N;
+      const f32x4_t* wp = reinterpret_cast<const f32x4_t*>(
+          wtile + (ok ? __umul24((uint32_t)r, (uint32_t)p.ldw) + (uint32_t)e_col : 0u));
       w_old[q] = nt_read ? __builtin_nontemporal_load(wp) : *wp;
     }
   }
@@ -188,7 +190,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
     multiply(KW - 1, (FIRST + KW - 1) & 1, ragged);
     ++it;
   };
-  for (int j = 0; j < S && j < n_k; ++j) request(j, j);
+#pragma unroll 1                                           // one copy of a request, and one in the loop
+  for (int j = 0; j < min(S, n_k); ++j) request(j, j);
   if (n_k > 0) {
     wait_tiles<PER>(min(S, n_k) - 1);
     asm volatile("s_barrier" ::: "memory");
@@ -236,14 +239,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   };
 
   if constexpr (kIsDw) {
-    float* wbase = (fused ? p.params : p.grads) + pg + p.w_off;
+    const size_t tile = pg + p.w_off + (size_t)m0 * p.ldw + n0;
+    float* wtile = (fused ? p.params : p.grads) + tile;
+    uint16_t* stile = p.shadow + tile;
 #pragma unroll
     for (int q = 0; q < EV; ++q) {
       const int r = q * ROWS_PER_PASS + e_row;
-      const int m = m0 + r, n = n0 + e_col;
-      if (m < p.M && n < p.N) {
+      if (m0 + r < p.M && n0 + e_col < p.N) {
         const f32x4_t gr = c_read(r, e_col);
-        const size_t off = (size_t)m * p.ldw + n;
+        const uint32_t off = __umul24((uint32_t)r, (uint32_t)p.ldw) + (uint32_t)e_col;
         if (fused) {
           f32x4_t w = w_old[q];
           w.x = fmaf(-p.lr, gr.x, w.x);
@@ -253,15 +257,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
           const u32x2_t hv = {f32x2_to_bf16x2_rne(w.x, w.y),
                               f32x2_to_bf16x2_rne(w.z, w.w)};
           if (p.streaming) {
-            __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(wbase + off));
+            __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(wtile + off));
             if (p.shadow != nullptr)
-              __builtin_nontemporal_store(hv, reinterpret_cast<u32x2_t*>(p.shadow + pg + p.w_off + off));
+              __builtin_nontemporal_store(hv, reinterpret_cast<u32x2_t*>(stile + off));
           } else {
-            *reinterpret_cast<f32x4_t*>(wbase + off) = w;
-            if (p.shadow != nullptr) *reinterpret_cast<u32x2_t*>(p.shadow + pg + p.w_off + off) = hv;
+            *reinterpret_cast<f32x4_t*>(wtile + off) = w;
+            if (p.shadow != nullptr) *reinterpret_cast<u32x2_t*>(stile + off) = hv;
           }
         } else {
-          *reinterpret_cast<f32x4_t*>(wbase + off) = gr;
+          *reinterpret_cast<f32x4_t*>(wtile + off) = gr;
         }
       }
     }
@@ -281,17 +285,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(Gemm
   gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>(p, (int)blockIdx.x);
 }
 
-// Several products in one launch: product i has the workgroups first[i] .. first[i + 1] - 1.
+// Several products in one launch: product i has the workgroups first[i] .. first[i + 1] - 1 (past the last product: none).
 struct GemmSet {
-  int n;
-  int first[kMaxGemmSet + 1];
+  int first[kMaxGemmSet];
   GemmArgs p[kMaxGemmSet];
 };
 template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
 __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_set_kernel(GemmSet set) {
-  int i = 0;
-  while (i + 1 < set.n && (int)blockIdx.x >= set.first[i + 1]) ++i;
-  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>(set.p[i], (int)blockIdx.x - set.first[i]);
+  int i = 0, first = 0;
+#pragma unroll
+  for (int k = 1; k < kMaxGemmSet; ++k)
+    if ((int)blockIdx.x >= set.first[k]) { i = k; first = set.first[k]; }
+  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>(set.p[i], (int)blockIdx.x - first);
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
@@ -413,18 +418,19 @@ template <typename T, int S> static hipError_t launch_dw_set(const GemmArgs* ps,
     configured.store(true, std::memory_order_release);
   }
   GemmSet set;
-  set.n = 0;
-  set.first[0] = 0;
+  memset(&set, 0, sizeof(set));
+  int used = 0, total = 0;
   for (int i = 0; i < n; ++i) {
-    if (ps[i].M <= 0 || ps[i].N <= 0) continue;
+    if (ps[i].M <= 0 || ps[i].N <= 0 || n_groups <= 0) continue;
     if (ps[i].k_splits > 1) return hipErrorInvalidValue;
-    set.p[set.n] = ps[i];
-    set.p[set.n].n_groups = n_groups;
-    set.first[set.n + 1] = set.first[set.n] + ((ps[i].M + BM - 1) / BM) * ((ps[i].N + BN - 1) / BN) * n_groups;
-    ++set.n;
+    set.first[used] = total;
+    set.p[used] = ps[i];
+    total += place_tiles(&set.p[used], BM, BN, n_groups);
+    ++used;
   }
-  if (set.n == 0 || n_groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)set.first[set.n]), dim3(256), kLds, s, set);
+  if (used == 0) return hipSuccess;
+  for (int i = used; i < kMaxGemmSet; ++i) set.first[i] = total;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(256), kLds, s, set);
   return hipGetLastError();
 }
 // One large product, or up to kMaxGemmSet others (gemm_dw_shares_launch).

@@ -23,6 +23,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
   static_assert(TM >= 1 && TN >= 1, "tile too small for the wavefront grid");
   static_assert(S >= 2 && S <= 4 && PER * (S - 1) <= 63, "wait_tiles");
 
+  fetch_args(p);
   const TileAt at = tile_at<BM, BN>(p, block);
   const int g = at.g, m0 = at.m0, n0 = at.n0;
   if (p.worker_steps != nullptr && p.step >= p.worker_steps[g]) return;
@@ -49,18 +50,19 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
     const size_t a_step = AKIND == OP_CONTIG ? (size_t)BK : (size_t)BK * p.lda;
     const size_t b_step = BKIND == OP_CONTIG ? (size_t)BK : (size_t)BK * p.ldb;
     uint32_t a_off[IOA::NPT], b_off[IOB::NPT];
-    IOA::offsets(a_off, p.lda, p.M - m0, BK, w, lane);
-    IOB::offsets(b_off, p.ldb, p.N - n0, BK, w, lane);
+    IOA::template offsets<false>(a_off, p.lda, p.M - m0, BK, w, lane);
+    IOB::template offsets<false>(b_off, p.ldb, p.N - n0, BK, w, lane);
     auto request = [&](int j, int stage) __attribute__((always_inline)) {
       const uint32_t lds_a = lds0 + (uint32_t)stage * STAGE, lds_b = lds_a + BM * kTileBytes;
       if (j == n_k - 1 && k_tail < BK) {                   // nothing past the operands is touched
-        IOA::offsets(a_off, p.lda, p.M - m0, k_tail, w, lane);
-        IOB::offsets(b_off, p.ldb, p.N - n0, k_tail, w, lane);
+        IOA::template offsets<true>(a_off, p.lda, p.M - m0, k_tail, w, lane);
+        IOB::template offsets<true>(b_off, p.ldb, p.N - n0, k_tail, w, lane);
       }
       IOA::request(a_src + (size_t)j * a_step, a_off, lds_a, w);
       IOB::request(b_src + (size_t)j * b_step, b_off, lds_b, w);
     };
-    for (int j = 0; j < S && j < n_k; ++j) request(j, j);
+  #pragma unroll 1                                           // one copy of a request, and one in the loop
+  for (int j = 0; j < min(S, n_k); ++j) request(j, j);
     int stage = S - 1;                                     // of tile t - 1
     for (int t = 0; t < n_k; ++t) {
       const int ahead = min(n_k - 1 - t, t == 0 ? S - 1 : S - 2);      // tiles requested after tile t

@@ -123,6 +123,8 @@ __device__ __forceinline__ void fetch_logits(float (&z)[Q], const float* __restr
   fetch_logits_parts<Q, STRIDE, 1>(z, row, part_stride, bias, c0, n_classes);
 }
 
+// Bytes of arguments that the loss heads have at least (what they have in front of the gather's, and the gather's).
+constexpr size_t kHeadArgBytes = 88 + sizeof(GatherArgs);
 // Softmax cross-entropy head: one wavefront per minibatch row (4 rows per workgroup).  The same
 // launch can carry the row gather of the next iteration in extra workgroups.
 //   row_loss[b] = -log softmax(z_b)[c_b],   delta = (softmax(z) - onehot(c)) / B
@@ -132,6 +134,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     long bias_gs, const int32_t* __restrict__ yb, void* __restrict__ delta,
     float* __restrict__ row_loss, int batch, int n_classes, int ldc,
     const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next) {
+  fetch_kernel_args<kHeadArgBytes>();
   const int g = blockIdx.y;
   // workgroups beyond the loss head's own: the minibatch draw of the NEXT iteration, which depends
   // on nothing this iteration computes (zeta_i^t is a function of seed, i, t and the slot alone)
@@ -217,6 +220,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_row_kernel(
     long bias_gs, const int32_t* __restrict__ yb, void* __restrict__ delta,
     float* __restrict__ row_loss, int batch, int n_classes, int ldc,
     const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next) {
+  fetch_kernel_args<kHeadArgBytes>();
   const int g = blockIdx.y;
   if ((int)blockIdx.x >= head_blocks) {                 // the minibatch draw of the next iteration
     gather_row<BF16>(next, (int)blockIdx.x - head_blocks, g);
@@ -304,6 +308,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     long w_gs, const float* __restrict__ bias, long bias_gs, const int32_t* __restrict__ yb,
     void* __restrict__ delta, float* __restrict__ row_loss, int batch, int n_classes, int ldc,
     const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next) {
+  fetch_kernel_args<kHeadArgBytes>();
   const int g = blockIdx.y;
   if ((int)blockIdx.x >= head_blocks) {                 // the minibatch draw of the next iteration
     gather_row<BF16>(next, (int)blockIdx.x - head_blocks, g);

@@ -35,6 +35,15 @@ enum GemmEpilogue {
   EPI_DW_GRAD = 4,      // G_W = acc, G_b = column sums
 };
 
+// Where the tiles of a product stand among its workgroups (gemm_tile.h); filled in by the launcher.
+struct TileDivisor { uint32_t mul, shift, d; };
+struct TilePlace {
+  int xcd_tiles, xcd_extra;           // tiles of every XCD, XCDs with one more
+  int split_shift, order;             // contraction ranges (their logarithm); 0 by group, 1 by column tile, 2 in strips
+  TileDivisor first, second, last_strip;
+  int whole_strips;
+};
+
 // One grouped matrix product: for every group (replica) g
 //   C_g[m][n] = sum_c A_g(m, c) * B_g(n, c),   m < M, n < N, c < Kc
 // followed by an epilogue.  Operand element (r, c) sits at base + g*gs + r*ld + c when the
@@ -43,7 +52,7 @@ struct GemmArgs {
   const void* a; long a_gs; int lda;
   const void* b; long b_gs; int ldb;
   int M, N, Kc;
-  int n_groups;                       // filled in by the launcher
+  TilePlace place;
   int epi;
   int streaming;                      // weights far exceed the caches: non-temporal accesses
   int act;                            // PRSGD_TANH | PRSGD_RELU
@@ -228,6 +237,14 @@ size_t lsq_exchange_bytes(int n_workers, int d);
 hipError_t launch_lsq_steps(LsqArgs p, hipStream_t s);
 
 // ---- small device helpers ------------------------------------------------------------------
+// Asks for every 64-byte line of the first BYTES of a kernel's arguments at once and waits for them.  They are in no cache when a
+// launch begins, and left alone each line is asked for where it is first used, one wait behind the other.
+template <size_t BYTES> __device__ __forceinline__ void fetch_kernel_args() {
+  constexpr int L = (int)(BYTES / 4) - 1;                  // last word
+  static_assert(L / 16 < 5, "a word of every line");
+  const auto* w = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" :: "s"(w[0]), "s"(w[L < 16 ? L : 16]), "s"(w[L < 32 ? L : 32]), "s"(w[L < 48 ? L : 48]), "s"(w[L]));
+}
 // Round to nearest even on the conversion instruction (two values per v_cvt_pk_bf16_f32; a NaN stays a
 // NaN, infinities and denormals are kept).  Written out in integer operations, with the NaN case apart,
 // the compiler made a divergent branch of every element: 11 instructions each, 176 of the 390 of one
