@@ -250,37 +250,38 @@ template <int BK> __device__ __forceinline__ void contraction_range(const GemmAr
   }
 }
 
-// Epilogue of a batch-row product (DX: backward-data, otherwise forward): eight output columns per thread (16 bytes of bf16,
-// 32 of fp32), the same ones in every pass over the rows.  Bias and phi' operand are requested before the output tile is
+// Epilogue of a batch-row product (DX: backward-data, otherwise forward): 16 bytes of output per thread, the same columns in
+// every pass over the rows.  Bias and phi' operand are requested before the output tile is
 // collected in LDS, so that a workgroup ends on one memory latency instead of one per pass (16 iterations of six workers of
 // 1000-500-300-37 728 -> 716 us; of eight of 4096-4096-4096-4096-1000 at interval 1 8766 -> 8681 us).
 // The instruction cache is shared by the launches of an iteration, and what a launch runs has to be fetched again when they exceed
 // it (0.6 to 1 us per launch): a kernel holds one of the two epilogues, and tanh, 8 of which are 3 KB, once and not per pass.
+// In fp32 16 bytes are four columns, so that all threads of a 32 x 32 tile have some: with eight, half of them were idle beside
+// tanh (16 iterations of eight workers of 784-300-100-10 631 -> 605 us).
 template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
   using E = typename T::elem;
-  static constexpr int VPR = BN / 8, ROWS = NTHR / VPR, NV = (BM + ROWS - 1) / ROWS;
+  static constexpr int C = T::kBf16 ? 8 : 4;               // columns per thread
+  static constexpr int VPR = BN / C, ROWS = NTHR / VPR, NV = (BM + ROWS - 1) / ROWS;
   using Aux = std::conditional_t<T::kBf16, u16x8_t, f32x4_t>;
   static constexpr int NH = DX ? NV : 1;
   int r0, c, m0, n;                                        // first row and column in the tile; tile's first row; column
-  f32x4_t b_lo, b_hi;                                      // bias
-  Aux h_lo[NH], h_hi[T::kBf16 ? 1 : NH];                   // phi' operand
+  f32x4_t b[C / 4];                                        // bias
+  Aux h[NH];                                               // phi' operand
 
   __device__ __forceinline__ RowsEpilogue(int m0_, int n0, int tid)
-      : r0(tid / VPR), c(8 * (tid % VPR)), m0(m0_), n(n0 + 8 * (tid % VPR)) {}
+      : r0(tid / VPR), c(C * (tid % VPR)), m0(m0_), n(n0 + C * (tid % VPR)) {}
   __device__ __forceinline__ void request(const GemmArgs& p, int g) {
-    const int nc = min(n, (p.out_cols - 1) / 8 * 8);       // copies past the operands, never stored
+    const int nc = min(n, (p.out_cols - 1) & ~(C - 1));       // copies past the operands, never stored
     if constexpr (DX) {
       const E* aux = reinterpret_cast<const E*>(p.aux) + (size_t)g * p.aux_gs + (size_t)m0 * p.ldaux;
 #pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        const E* ap = aux + (__umul24((uint32_t)min(q * ROWS + r0, p.M - 1 - m0), (uint32_t)p.ldaux) + (uint32_t)nc);
-        h_lo[q] = *reinterpret_cast<const Aux*>(ap);
-        if constexpr (!T::kBf16) h_hi[q] = *reinterpret_cast<const f32x4_t*>(ap + 4);
-      }
+      for (int q = 0; q < NV; ++q)
+        h[q] = *reinterpret_cast<const Aux*>(aux + (__umul24((uint32_t)min(q * ROWS + r0, p.M - 1 - m0), (uint32_t)p.ldaux) +
+                                                    (uint32_t)nc));
     } else if (biased(p)) {
       const float* bias = p.src + (size_t)g * p.src_gs + p.b_off + nc;
-      b_lo = *reinterpret_cast<const f32x4_t*>(bias);
-      b_hi = *reinterpret_cast<const f32x4_t*>(bias + 4);
+#pragma unroll
+      for (int e = 0; e < C / 4; ++e) b[e] = *reinterpret_cast<const f32x4_t*>(bias + 4 * e);
     }
   }
   // partial sums of a split contraction carry no bias: the loss head adds it once
@@ -288,29 +289,29 @@ template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
   // c_read(r, c): four floats of the output tile.  Padding columns [N, out_cols) are written as zeros.
   template <typename F> __device__ __forceinline__ void store(const GemmArgs& p, int g, int split, F&& c_read) const {
     if constexpr (DX) {
-      if (p.act == PRSGD_TANH) passes(p, g, split, c_read, [&](float (&z)[8], int q) __attribute__((always_inline)) { times_slope(z, q, PRSGD_TANH); });
-      else passes(p, g, split, c_read, [&](float (&z)[8], int q) __attribute__((always_inline)) { times_slope(z, q, PRSGD_RELU); });
+      if (p.act == PRSGD_TANH) passes(p, g, split, c_read, [&](float (&z)[C], int q) __attribute__((always_inline)) { times_slope(z, q, PRSGD_TANH); });
+      else passes(p, g, split, c_read, [&](float (&z)[C], int q) __attribute__((always_inline)) { times_slope(z, q, PRSGD_RELU); });
     } else if (p.epi == EPI_FWD_HIDDEN && p.act == PRSGD_TANH) {
 #pragma unroll 1
       for (int q = 0; q < NV; ++q)
-        pass(p, g, split, q, c_read, [&](float (&z)[8], int) __attribute__((always_inline)) {
+        pass(p, g, split, q, c_read, [&](float (&z)[C], int) __attribute__((always_inline)) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) z[e] = tanhf(z[e]);
+          for (int e = 0; e < C; ++e) z[e] = tanhf(z[e]);
         });
     } else {
-      passes(p, g, split, c_read, [&](float (&z)[8], int) __attribute__((always_inline)) {
+      passes(p, g, split, c_read, [&](float (&z)[C], int) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = p.epi == EPI_FWD_HIDDEN ? act_fwd(z[e], PRSGD_RELU) : z[e];
+        for (int e = 0; e < C; ++e) z[e] = p.epi == EPI_FWD_HIDDEN ? act_fwd(z[e], PRSGD_RELU) : z[e];
       });
     }
   }
 
  private:
-  __device__ __forceinline__ void times_slope(float (&z)[8], int q, int act) const {
+  __device__ __forceinline__ void times_slope(float (&z)[C], int q, int act) const {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if constexpr (T::kBf16) z[e] *= act_bwd_from_h(bf16_to_f32(h_lo[q][e]), act);
-      else z[e] *= act_bwd_from_h(e < 4 ? h_lo[q][e & 3] : h_hi[q][e & 3], act);
+    for (int e = 0; e < C; ++e) {
+      if constexpr (T::kBf16) z[e] *= act_bwd_from_h(bf16_to_f32(h[q][e]), act);
+      else z[e] *= act_bwd_from_h(h[q][e], act);
     }
   }
   template <typename F, typename A>
@@ -322,28 +323,31 @@ template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
   __device__ __forceinline__ void pass(const GemmArgs& p, int g, int split, int q, F&& c_read, A&& apply) const {
     const int r = q * ROWS + r0, m = m0 + r;
     if (r >= BM || m >= p.M || n >= p.out_cols) return;
-    const f32x4_t lo = c_read(r, c), hi = c_read(r, c + 4);
-    float z[8];
+    float z[C];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { z[e] = lo[e]; z[4 + e] = hi[e]; }
+    for (int e = 0; e < C; e += 4) {
+      const f32x4_t v = c_read(r, c + e);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) z[e + x] = v[x];
+    }
     if (!DX && biased(p)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { z[e] += b_lo[e]; z[4 + e] += b_hi[e]; }
+      for (int e = 0; e < C; ++e) z[e] += b[e / 4][e % 4];
     }
     apply(z, q);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) z[e] = n + e < p.N ? z[e] : 0.0f;
+    for (int e = 0; e < C; ++e) z[e] = n + e < p.N ? z[e] : 0.0f;
     const size_t base = (size_t)g * p.out_gs + (size_t)m0 * p.ldo;
     const uint32_t o = __umul24((uint32_t)r, (uint32_t)p.ldo) + (uint32_t)n;
     if (T::kBf16 && (DX || p.epi != EPI_FWD_LOGITS)) {
-      u16x8_t v;
+      Aux v;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16_rne(z[e]);
-      *reinterpret_cast<u16x8_t*>(reinterpret_cast<uint16_t*>(p.out) + base + o) = v;
+      for (int e = 0; e < C; ++e) v[e] = f32_to_bf16_rne(z[e]);
+      *reinterpret_cast<Aux*>(reinterpret_cast<uint16_t*>(p.out) + base + o) = v;
     } else {
       float* op = reinterpret_cast<float*>(p.out) + base + (!DX && p.epi == EPI_FWD_LOGITS ? (size_t)split * p.split_stride : 0) + o;
-      *reinterpret_cast<f32x4_t*>(op) = (f32x4_t){z[0], z[1], z[2], z[3]};
-      *reinterpret_cast<f32x4_t*>(op + 4) = (f32x4_t){z[4], z[5], z[6], z[7]};
+#pragma unroll
+      for (int e = 0; e < C; e += 4) *reinterpret_cast<f32x4_t*>(op + e) = (f32x4_t){z[e], z[e + 1], z[e + 2], z[e + 3]};
     }
   }
 };
