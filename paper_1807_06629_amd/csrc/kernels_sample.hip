@@ -5,6 +5,7 @@
 // replacement; slot j of iteration t is a pure function of (seed, i, t, j) through
 // Philox4x32-10, so the stream needs no state and can be replayed from any t.
 #include <cstring>
+#include <type_traits>
 
 #include "prsgd_internal.h"
 
@@ -302,13 +303,18 @@ __device__ __forceinline__ float head_row_sum(float v) {
   return v + row_move<0x140>(v);
 }
 
-template <bool BF16, int CT>
+// With DX the workgroup also takes its rows' delta one layer down, D_{L-1} = (D_L W_L^T) phi'(H_{L-1}): it has D_L, and W_L is
+// as small as the head asks for.  Transposed, 16 units by 16 rows, so that a lane holds four consecutive units of a row; the
+// operand of W_L comes straight from memory, four tiles of it per wavefront in flight.  One launch fewer: 16 iterations of eight
+// workers of 784-300-100-10 in fp32 605 -> 565 us, of six of 1000-500-300-37 in bf16 633 -> 598 us, 8 of eight of
+// 3072-1024-1024-10, 512 rows, 1651 -> 1632 us.
+template <bool BF16, int CT, bool DX>
 __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     const void* __restrict__ h_any, long h_gs, int ldh, int k_dim, const void* __restrict__ w_any,
     long w_gs, const float* __restrict__ bias, long bias_gs, const int32_t* __restrict__ yb,
     void* __restrict__ delta, float* __restrict__ row_loss, int batch, int n_classes, int ldc,
-    const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next) {
-  fetch_kernel_args<kHeadArgBytes>();
+    const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next, HeadDelta below) {
+  fetch_kernel_args<kHeadArgBytes + 16 + sizeof(HeadDelta)>();
   const int g = blockIdx.y;
   if ((int)blockIdx.x >= head_blocks) {                 // the minibatch draw of the next iteration
     gather_row<BF16>(next, (int)blockIdx.x - head_blocks, g);
@@ -402,8 +408,15 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int v = 0; v < 4; ++v) part[wave][4 * q4 + v][16 * ct + n16] = acc[ct][v];
+  constexpr int KC = BF16 && CT == 1 ? 32 : 16 * CT;    // classes as the contraction of D_{L-1}: past the last ones zeros
+  using DE = std::conditional_t<BF16, uint16_t, float>;
+  constexpr int DS = KC + 16 / (int)sizeof(DE);         // row stride of D_L in LDS
+  __shared__ __attribute__((aligned(16))) DE d_lds[DX ? kHeadRows * DS : 1];
+  if (DX)
+    for (int e = tid; e < kHeadRows * DS; e += kThreads) d_lds[e] = 0;
   __syncthreads();
-  if (b >= batch) return;                               // whole groups of 16 lanes
+  if (!DX && b >= batch) return;                        // whole groups of 16 lanes
+  if (b < batch) {
   const size_t r = (size_t)g * batch + b;
   float z[CT], mx = -INFINITY;
 #pragma unroll
@@ -432,10 +445,84 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
       const float d = c < n_classes ? (e[ct] / se - (c == label ? 1.0f : 0.0f)) * (1.0f / (float)batch) : 0.0f;
       if (BF16) reinterpret_cast<uint16_t*>(delta)[r * ldc + c] = f32_to_bf16_rne(d);
       else reinterpret_cast<float*>(delta)[r * ldc + c] = d;
+      if constexpr (DX) {
+        if constexpr (BF16) d_lds[row * DS + c] = f32_to_bf16_rne(d);
+        else d_lds[row * DS + c] = d;
+      }
     }
   }
   if (l16 == 0) row_loss[r] = (mx + logf(se)) - zl;
+  }
+  if constexpr (DX) {
+    __syncthreads();
+    const bool row_ok = b0 + n16 < batch;
+    constexpr int U = 4;                                // tiles in flight
+    const int tiles = (below.ld + 15) / 16;
+    DE* out = reinterpret_cast<DE*>(below.out) + (size_t)g * below.gs + (size_t)min(b0 + n16, batch - 1) * below.ld;
+    const DE* h_r = reinterpret_cast<const DE*>(h_any) + h_row;
+    const DE* w_g = reinterpret_cast<const DE*>(w_any) + (size_t)g * w_gs;
+    typedef std::conditional_t<BF16, uint2, f32x4_t> H4;   // four units of H_{L-1}
+    constexpr int NF = BF16 ? KC / 32 : CT;             // 16-byte pieces of a lane along the classes
+    u32x4_t df[NF];
+#pragma unroll
+    for (int s = 0; s < NF; ++s)
+      df[s] = *reinterpret_cast<const u32x4_t*>(&d_lds[n16 * DS + (BF16 ? 32 * s + 8 * q4 : 16 * s + 4 * q4)]);
+    for (int t0 = wave; t0 < tiles; t0 += NW * U) {
+      u32x4_t w[U][NF];
+      H4 hv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j0 = 16 * min(t0 + NW * u, tiles - 1);
+#pragma unroll
+        for (int s = 0; s < NF; ++s) {
+          const int c = BF16 ? 32 * s + 8 * q4 : 16 * s + 4 * q4;
+          w[u][s] = *reinterpret_cast<const u32x4_t*>(w_g + (size_t)min(j0 + n16, k_dim - 1) * ldc + (c < ldc ? c : 0));
+        }
+        hv[u] = *reinterpret_cast<const H4*>(h_r + min(j0 + 4 * q4, ldh - 4));
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = 16 * (t0 + NW * u) + 4 * q4;
+        f32x4_t z = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < NF; ++s) {                  // D_L is zero where a piece of W_L stands in for classes past the last
+          if constexpr (BF16) {
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[u][s]),
+                                                        __builtin_bit_cast(bf16x8_t, df[s]), z, 0, 0, 0);
+          } else {
+            const f32x4_t wf = __builtin_bit_cast(f32x4_t, w[u][s]), dv = __builtin_bit_cast(f32x4_t, df[s]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) z = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[q], dv[q], z, 0, 0, 0);
+          }
+        }
+        float hf[4];
+        if constexpr (BF16) {
+          hf[0] = bf16_to_f32((uint16_t)hv[u].x); hf[1] = bf16_to_f32((uint16_t)(hv[u].x >> 16));
+          hf[2] = bf16_to_f32((uint16_t)hv[u].y); hf[3] = bf16_to_f32((uint16_t)(hv[u].y >> 16));
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) hf[e] = hv[u][e];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float slope = below.act == PRSGD_TANH ? 1.0f - hf[e] * hf[e] : hf[e] > 0.0f ? 1.0f : 0.0f;
+          z[e] = j + e < k_dim ? z[e] * slope : 0.0f;
+        }
+        if (row_ok && j < below.ld) {
+          if constexpr (BF16) {
+            uint2 v;
+            v.x = f32x2_to_bf16x2_rne(z[0], z[1]);
+            v.y = f32x2_to_bf16x2_rne(z[2], z[3]);
+            *reinterpret_cast<uint2*>(out + j) = v;
+          } else {
+            *reinterpret_cast<f32x4_t*>(out + j) = z;
+          }
+        }
+      }
+    }
+  }
 }
+
 
 // Minibatch loss of each worker: mean of its row losses, rows summed in slot order.
 __global__ void loss_mean_kernel(const float* __restrict__ row_loss, float* __restrict__ losses,
@@ -520,17 +607,24 @@ hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_d
                                       long w_gs, const float* bias, long bias_gs, const int32_t* yb,
                                       void* delta, float* row_loss, int n_workers, int batch, int n_classes,
                                       int ldc, bool bf16, const int* worker_steps, int step, const GatherArgs* next,
-                                      hipStream_t s) {
+                                      const HeadDelta* below, hipStream_t s) {
   if (!softmax_narrow_applies(n_classes, ldc, k_dim, bf16) || (ldh % 8) != 0) return hipErrorInvalidValue;
+  HeadDelta hd;
+  memset(&hd, 0, sizeof(hd));
+  if (below != nullptr) hd = *below;
+  const bool dx = below != nullptr;
   const int head_blocks = (batch + kHeadRows - 1) / kHeadRows;
   GatherArgs ga;
   memset(&ga, 0, sizeof(ga));
   if (next != nullptr) ga = *next;
   dim3 grid(head_blocks + (next != nullptr ? next->batch : 0), n_workers);
-  auto kernel = bf16 ? (ldc <= 16 ? softmax_xent_narrow_kernel<true, 1> : softmax_xent_narrow_kernel<true, 4>)
-                     : (ldc <= 16 ? softmax_xent_narrow_kernel<false, 1> : softmax_xent_narrow_kernel<false, 4>);
+  auto of = [&](auto plain, auto delta) { return dx ? delta : plain; };
+  auto kernel = bf16 ? (ldc <= 16 ? of(softmax_xent_narrow_kernel<true, 1, false>, softmax_xent_narrow_kernel<true, 1, true>)
+                                  : of(softmax_xent_narrow_kernel<true, 4, false>, softmax_xent_narrow_kernel<true, 4, true>))
+                     : (ldc <= 16 ? of(softmax_xent_narrow_kernel<false, 1, false>, softmax_xent_narrow_kernel<false, 1, true>)
+                                  : of(softmax_xent_narrow_kernel<false, 4, false>, softmax_xent_narrow_kernel<false, 4, true>));
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, h, h_gs, ldh, k_dim, w, w_gs, bias,
-                     bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step, head_blocks, ga);
+                     bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step, head_blocks, ga, hd);
   return hipGetLastError();
 }
 

@@ -486,10 +486,45 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     LAUNCH(ctx, KK_FWD, launch_gemm_fwd(p, N, bf16, s));
   }
 
+  auto bwd_args = [&](int l) {
+    BwdArgs q;
+    memset(&q, 0, sizeof(q));
+    q.h = reinterpret_cast<const uint16_t*>(act_in(l - 1)); q.h_gs = (long)B * lo.ld[l - 1]; q.ldh = lo.ld[l - 1];
+    q.d = ctx->at<uint16_t>(cv.delta[l]); q.d_gs = (long)B * lo.ld[l]; q.ldd = lo.ld[l];
+    q.params = ctx->params; q.shadow = ctx->shadow(); q.p_gs = lo.m_pad;
+    q.src = ctx->src(); q.src_gs = ctx->src_stride();
+    q.w_off = lo.w_off[l - 1]; q.b_off = lo.b_off[l - 1]; q.ldw = lo.ld[l];
+    if (l > 1) { q.dx = ctx->at<uint16_t>(cv.delta[l - 1]); q.dx_gs = (long)B * lo.ld[l - 1]; q.lddx = lo.ld[l - 1]; }
+    q.B = B; q.K = lo.d[l - 1]; q.Nn = lo.d[l];
+    q.n_groups = N; q.act = c.activation; q.streaming = ctx->streamed.steps ? 1 : 0;
+    q.lr = ctx->lr;
+    q.vel = ctx->velocity(); q.mu = c.momentum;
+    q.worker_steps = worker_steps; q.step = step;
+    return q;
+  };
+  int n_apart = 0, widest_apart = 0;
+  for (int l = L; fused_bwd && l >= 1; --l) {
+    if (!bwd_products_apart(bwd_args(l))) continue;
+    ++n_apart;
+    if (lo.d[l] > widest_apart) widest_apart = lo.d[l];
+  }
+  const bool take_apart = bwd_apart_pays(n_apart, widest_apart, B);
+  // A narrow head takes the last layer's delta one layer down as well, where that is a product of its own.  It stays one
+  // with up to 16 classes where the layers' products are apart: the backward launches of such a net are what its
+  // profile has always listed.
+  const bool head_delta = narrow_head && L > 1 &&
+                          (fuse_average || !fused_bwd || (lo.d[L] > 16 && take_apart && bwd_products_apart(bwd_args(L))));
+
   // the loss-head launch also draws the minibatch of iteration t + 1 into the other buffer set
   const bool prefetch = worker_steps == nullptr && draw_ahead;
   GatherArgs next_batch = batch_args(bk ^ 1, t + 1);
   if (prefetch) ctx->batch_t[bk ^ 1] = -1;
+  HeadDelta below;
+  memset(&below, 0, sizeof(below));
+  if (head_delta) {
+    below.out = ctx->at<void>(cv.delta[L - 1]); below.gs = (long)B * lo.ld[L - 1]; below.ld = lo.ld[L - 1];
+    below.act = c.activation;
+  }
   if (narrow_head)
     LAUNCH(ctx, KK_LOSS,
            launch_softmax_xent_narrow(act_in(L - 1), (long)B * lo.ld[L - 1], lo.ld[L - 1], lo.d[L - 1],
@@ -497,7 +532,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
                                            : (const void*)(reinterpret_cast<const float*>(wsrc) + lo.w_off[L - 1]),
                                       w_gs, ctx->src() + lo.b_off[L - 1], ctx->src_stride(), ctx->yb(bk),
                                       ctx->at<void>(cv.delta[L]), ctx->at<float>(cv.row_loss), N, B, lo.d[L],
-                                      lo.ld[L], bf16, worker_steps, step, prefetch ? &next_batch : nullptr, s));
+                                      lo.ld[L], bf16, worker_steps, step, prefetch ? &next_batch : nullptr,
+                                      head_delta ? &below : nullptr, s));
   else
   LAUNCH(ctx, KK_LOSS,
          launch_softmax_xent(ctx->at<float>(cv.logits), logit_parts, logit_part_stride,
@@ -542,7 +578,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     // weights the forward pass used (the bf16 image of ybar, or of every worker's own point), and
     // when that is ybar it runs before layer l's pass changes it
     for (int l = L; l >= 1; --l) {
-      if (l > 1) LAUNCH(ctx, KK_DX, launch_gemm_dx(dx_args(l), N, true, s));
+      if (l > 1 && !(l == L && head_delta)) LAUNCH(ctx, KK_DX, launch_gemm_dx(dx_args(l), N, true, s));
       // all minibatches stacked: sum_i dW_i = [H_1; ..; H_N]^T [D_1; ..; D_N], one contraction of N B
       // rows, and ybar <- ybar - (gamma / N) sum_i dW_i (likewise the bias from the column sums)
       GemmArgs p = dw_args(l);
@@ -564,29 +600,6 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
 
   // backward.  bf16 operands with the fused update: one kernel per layer does the weight
   // gradient, eq. (3) and the delta of the layer below in a single pass over W_l.
-  auto bwd_args = [&](int l) {
-    BwdArgs q;
-    memset(&q, 0, sizeof(q));
-    q.h = reinterpret_cast<const uint16_t*>(act_in(l - 1)); q.h_gs = (long)B * lo.ld[l - 1]; q.ldh = lo.ld[l - 1];
-    q.d = ctx->at<uint16_t>(cv.delta[l]); q.d_gs = (long)B * lo.ld[l]; q.ldd = lo.ld[l];
-    q.params = ctx->params; q.shadow = ctx->shadow(); q.p_gs = lo.m_pad;
-    q.src = ctx->src(); q.src_gs = ctx->src_stride();
-    q.w_off = lo.w_off[l - 1]; q.b_off = lo.b_off[l - 1]; q.ldw = lo.ld[l];
-    if (l > 1) { q.dx = ctx->at<uint16_t>(cv.delta[l - 1]); q.dx_gs = (long)B * lo.ld[l - 1]; q.lddx = lo.ld[l - 1]; }
-    q.B = B; q.K = lo.d[l - 1]; q.Nn = lo.d[l];
-    q.n_groups = N; q.act = c.activation; q.streaming = ctx->streamed.steps ? 1 : 0;
-    q.lr = ctx->lr;
-    q.vel = ctx->velocity(); q.mu = c.momentum;
-    q.worker_steps = worker_steps; q.step = step;
-    return q;
-  };
-  int n_apart = 0, widest_apart = 0;
-  for (int l = L; fused_bwd && l >= 1; --l) {
-    if (!bwd_products_apart(bwd_args(l))) continue;
-    ++n_apart;
-    if (lo.d[l] > widest_apart) widest_apart = lo.d[l];
-  }
-  const bool take_apart = bwd_apart_pays(n_apart, widest_apart, B);
   bool first_shadow_left = false;
   for (int l = L; fused_bwd && l >= 1; --l) {
     BwdArgs q = bwd_args(l);
@@ -604,7 +617,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
       }
     }
     if (take_apart && bwd_products_apart(q)) {
-      if (l > 1) LAUNCH(ctx, KK_BWD, launch_gemm_dx(dx_args(l), N, true, s));
+      if (l > 1 && !(l == L && head_delta)) LAUNCH(ctx, KK_BWD, launch_gemm_dx(dx_args(l), N, true, s));
       GemmArgs p = dw_args(l);
       p.epi = EPI_DW_FUSED;
       const int rc = dw.add(p, N, KK_BWD);
@@ -615,7 +628,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
   }
   // otherwise: D_{l-1} needs the pre-update W_l, so it runs before layer l's weight kernel
   for (int l = L; !fused_bwd && l >= 1; --l) {
-    if (l > 1) LAUNCH(ctx, KK_DX, launch_gemm_dx(dx_args(l), N, bf16, s));
+    if (l > 1 && !(l == L && head_delta)) LAUNCH(ctx, KK_DX, launch_gemm_dx(dx_args(l), N, bf16, s));
     GemmArgs p = dw_args(l);
     p.epi = c.fused_update ? EPI_DW_FUSED : EPI_DW_GRAD;
     const int rc = dw.add(p, N, KK_DW);

@@ -189,13 +189,15 @@ hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_strid
                                long bias_gs, const int32_t* yb, void* delta, float* row_loss,
                                int n_workers, int batch, int n_classes, int ldc, bool bf16,
                                const int* worker_steps, int step, const GatherArgs* next, hipStream_t s);
-// Narrow head (at most 64 classes): logits product, softmax and delta in one launch
+// Narrow head (at most 64 classes): logits product, softmax and delta in one launch; below != nullptr: and the delta of the
+// layer below, D_{L-1} [N][B][ld]
+struct HeadDelta { void* out; long gs; int ld, act; };
 bool softmax_narrow_applies(int n_classes, int ldc, int k_dim, bool bf16);
 hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_dim, const void* w,
                                       long w_gs, const float* bias, long bias_gs, const int32_t* yb,
                                       void* delta, float* row_loss, int n_workers, int batch, int n_classes,
                                       int ldc, bool bf16, const int* worker_steps, int step, const GatherArgs* next,
-                                      hipStream_t s);
+                                      const HeadDelta* below, hipStream_t s);
 hipError_t launch_loss_mean(const float* row_loss, float* losses, int n_workers, int batch,
                             hipStream_t s);
 

@@ -59,3 +59,36 @@ def test_logits_inside_the_head(dtype, width, classes, batch, n_workers, inside)
     launches = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
     assert launches["gemm_fwd"] == (2 if inside else 3), launches
     P.prsgd_destroy(h)
+
+
+# (dtype, width in front of the logits, classes, batch): tiles of 16 units, whole and ragged, one and more per wavefront and
+# past a round of four each; rows in blocks of 16; contractions of one class, of 16, around 32 and of 64.  bf16 with more
+# than 128 rows, whose products are apart
+BELOW = [
+    ("f32", 1, 1, 1), ("f32", 8, 16, 16), ("f32", 17, 17, 15), ("f32", 64, 10, 33), ("f32", 65, 9, 17),
+    ("f32", 256, 64, 31), ("f32", 263, 33, 16), ("f32", 1030, 5, 20),
+    ("bf16", 1, 1, 129), ("bf16", 8, 16, 144), ("bf16", 17, 17, 130), ("bf16", 64, 10, 145), ("bf16", 65, 24, 129),
+    ("bf16", 263, 32, 160), ("bf16", 256, 64, 129), ("bf16", 1030, 10, 131),
+]
+
+
+@pytest.mark.parametrize("activation", ["tanh", "relu"])
+@pytest.mark.parametrize("dtype,width,classes,batch", BELOW)
+def test_delta_below_the_head(dtype, width, classes, batch, activation):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=(24, 40, width, classes), batch=batch, n_workers=3, gemm_dtype=dtype, activation=activation,
+                  rows_per_worker=256, iterations=1)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_local_steps(h, 1)
+    want = oracle_run(w, inp, iterations=1)
+    # relu in bf16: a pre-activation within the fp32 sums' error of the kink may fall on its other side and switch
+    # gamma / B of a column, 0.05 / 129 of a gradient's size
+    assert rel_err(D.read_all(h), want["x"]) <= (1e-5 if dtype == "f32" else 1e-4 if activation == "tanh" else 5e-4)
+    assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-5 if dtype == "f32" else 2e-3, atol=1e-6)
+    P.prsgd_profile_enable(h, True)
+    P.prsgd_local_steps(h, 1)
+    launches = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
+    assert launches["gemm_dx"] == 1, launches            # layer 2's only
+    P.prsgd_destroy(h)
