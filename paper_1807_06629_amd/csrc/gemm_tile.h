@@ -137,15 +137,13 @@ __device__ __forceinline__ void mask_frag(Frag<TF32>& f, int kk, int lane, int n
   for (int e = 0; e < 4; ++e) f.v[e] = c + e < n_c ? f.v[e] : 0.0f;
 }
 
-// Waits until all but the newest `ahead` tiles (PER requests each) have landed.
-template <int PER> __device__ __forceinline__ void wait_tiles(int ahead) {
+// Waits until all but the newest `ahead` tiles (PER requests each, `ahead` at most MOST) have landed.
+template <int PER, int MOST> __device__ __forceinline__ void wait_tiles(int ahead) {
 #define PRSGD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((n) * PER > 63 ? 63 : (n) * PER) : "memory")
-  switch (ahead) {
-    case 0: PRSGD_WAIT(0); break;
-    case 1: PRSGD_WAIT(1); break;
-    case 2: PRSGD_WAIT(2); break;
-    default: PRSGD_WAIT(3); break;
-  }
+  if (MOST >= 3 && ahead >= 3) PRSGD_WAIT(3);
+  else if (MOST >= 2 && ahead >= 2) PRSGD_WAIT(2);
+  else if (MOST >= 1 && ahead >= 1) PRSGD_WAIT(1);
+  else PRSGD_WAIT(0);
 #undef PRSGD_WAIT
 }
 
@@ -352,10 +350,12 @@ template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
   }
 };
 
-// Tiles in flight of the products in 128 x 128 tiles, and those products (kernels_gemm_rows.hip).
-constexpr int kFedStages = 3;
-hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, hipStream_t s);
-hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, hipStream_t s);
+// Products whose workgroups have requesting wavefronts (kernels_gemm_rows.hip), and their tiles in flight: 128 x 128, the smaller ones.
+// Four of these cover the latency of a workgroup that has its compute unit to itself (per iteration, 5 workers of
+// 640-1024-448-960-29, 18 rows: three 53.8 us, four 51.1, five or six 51.0; 6 of 1000-500-300-37, 100 rows: 36.2, 35.3, 35.6).
+constexpr int kFedStages = 3, kFedSmallStages = 4;
+hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s);
+hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s);
 
 // Launches KERNEL (WAVES wavefronts per workgroup) with one workgroup per tile of BM x BN.
 template <typename T, int BM, int BN, int WK, int S, int WAVES, void (*KERNEL)(GemmArgs)>

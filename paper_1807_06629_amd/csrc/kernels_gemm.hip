@@ -182,7 +182,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
       multiply(u, (FIRST + u) & 1, ragged);
     }
     const int ahead = n_k - 2 - it;                        // tiles requested after tile it + 1
-    if (ahead >= S - 2) wait_tiles<PER>(S - 2); else wait_tiles<PER>(max(ahead, 0));
+    if (ahead >= S - 2) wait_tiles<PER, S - 1>(S - 2); else wait_tiles<PER, S - 1>(max(ahead, 0));
     asm volatile("s_barrier" ::: "memory");
     if (it + S < n_k) request(it + S, stage);
     stage = stage + 1 == S ? 0 : stage + 1;
@@ -193,7 +193,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
 #pragma unroll 1                                           // one copy of a request, and one in the loop
   for (int j = 0; j < min(S, n_k); ++j) request(j, j);
   if (n_k > 0) {
-    wait_tiles<PER>(min(S, n_k) - 1);
+    wait_tiles<PER, S - 1>(min(S, n_k) - 1);
     asm volatile("s_barrier" ::: "memory");
     load(0, 0, 0);
     for (;;) {
@@ -345,13 +345,28 @@ static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
 // x 4096 with shared weights 54.1, 48.7 and 47.0 us, 64 x (128 x 1024) x 1024 38.7, 35.5 and 33.8 us.
 constexpr int kRowStages = 3;
 
+// Workgroups with requesting wavefronts (kernels_gemm_rows.hip) take the 128 x 128 tiles, and the smaller ones up to two workgroups per
+// compute unit: from then on several workgroups of the plain kernel share a unit and hide each other's requests.  Per iteration, plain
+// and with requesting wavefronts: 6 workers of 1000-500-300-37, 100 rows, 37.7 and 35.3 us; 5 of 640-1024-448-960-29, 18 rows, 56.8
+// and 51.1; 16 of 600-300-100, 40 rows, 29.0 and 27.3; 24 of 520-520-520-520-30, 64 rows (216 tiles of 64 x 64), 89.4 and 86.6; 40 with
+// 32 rows (360 of 32 x 64) 101.9 and 101.0; 32 of 1000-1000-1000-50, 32 and 64 rows (512), 167.7 and 168.1, 183.0 and 182.6; 64 with 32 rows
+// (1024) 347.4 and 349.2.
+constexpr long kFedTiles = 2 * kComputeUnits;
+static long rows_tiles(RowsTile t, int rows, int cols, int splits, int n_groups) {
+  return (long)((rows + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1) * n_groups;
+}
+static bool rows_fed(RowsTile t, const GemmArgs& p, int n_groups) {
+  return t.bn == 128 || (t.bm <= 64 && rows_tiles(t, p.M, p.N, p.k_splits, n_groups) <= kFedTiles);
+}
+
 template <int AKIND, int BKIND>
 static hipError_t launch_rows_bf16(const GemmArgs& p, int n_groups, hipStream_t s) {
   const RowsTile t = rows_tile(p, n_groups, true);
+  if (rows_fed(t, p, n_groups))
+    return BKIND == OP_CONTIG ? launch_gemm_dx_fed(p, n_groups, t.bm, s) : launch_gemm_fwd_fed(p, n_groups, t.bm, s);
   if (t.bm == 32) return launch_one<TBF16, 32, 64, 1, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
   if (t.bm == 64) return launch_one<TBF16, 64, 64, 2, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
-  if (t.bn == 64) return launch_one<TBF16, 128, 64, 4, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
-  return BKIND == OP_CONTIG ? launch_gemm_dx_fed(p, n_groups, s) : launch_gemm_fwd_fed(p, n_groups, s);
+  return launch_one<TBF16, 128, 64, 4, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
 }
 template <int AKIND, int BKIND>
 static hipError_t launch_rows_f32(const GemmArgs& p, int n_groups, hipStream_t s) {
@@ -365,11 +380,12 @@ void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows
   memset(&p, 0, sizeof(p));
   p.M = rows; p.N = cols;
   const RowsTile t = rows_tile(p, n_groups, bf16);
+  const bool fed = rows_fed(t, p, n_groups);
   *tile_rows = t.bm;
   *tile_cols = t.bn;
   *lds_bytes = !bf16 ? (t.bm == 64 ? gemm_lds_bytes<TF32, 64, 64, 1, 4>() : gemm_lds_bytes<TF32, 32, 32, 4, kRowStages>())
-               : t.bm == 32 ? gemm_lds_bytes<TBF16, 32, 64, 1, kRowStages>()
-               : t.bm == 64 ? gemm_lds_bytes<TBF16, 64, 64, 1, kRowStages>()
+               : t.bm == 32 ? (fed ? gemm_lds_bytes<TBF16, 32, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 32, 64, 1, kRowStages>())
+               : t.bm == 64 ? (fed ? gemm_lds_bytes<TBF16, 64, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 64, 64, 1, kRowStages>())
                : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, kFedStages>();
 }
 

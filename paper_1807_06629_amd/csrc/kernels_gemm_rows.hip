@@ -1,5 +1,5 @@
-// Batch-row products (forward, backward-data; kernels_gemm.hip says which) of bf16 operands in 128 x 128 tiles, whose workgroups
-// divide the work by kind of instruction.
+// Batch-row products (forward, backward-data) of bf16 operands whose workgroups divide the work by kind of instruction: those in
+// 128 x 128 tiles, and launches of few smaller ones (kernels_gemm.hip says which).
 #include "gemm_tile.h"
 
 namespace prsgd {
@@ -9,7 +9,9 @@ namespace prsgd {
 // a 128 x 128 tile), and then its matrix instructions wait with it; a SIMD has one wavefront of each kind.  The multiplying
 // wavefronts hold the fragments of a whole tile and read the next tile's behind the matrix instructions, so that they meet the
 // others once per tile, and with 64 x 64 outputs each they read 64 KB of LDS per 128 x 128 tile where eight of 64 x 32 read 96.
-// Same order of the contraction, same bits as gemm_tile.
+// Same order of the contraction, same bits as gemm_tile.  Workers x (rows x contraction) x columns, against eight wavefronts that do
+// both: 8 x (128 x 4096) x 4096 with shared weights 46 -> 36 us forward, 44 -> 35 us backward-data, launched by itself; in an iteration
+// at interval 1, with the weights in HBM and clocks at the power limit, 50 -> 46 and 40 -> 33 us.
 template <int BM, int BN, int CM, int CN, int S, int AKIND, int BKIND>
 __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
   using T = TBF16;
@@ -19,7 +21,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
   using IOB = TileIO<T, BN, BKIND, NREQ>;
   constexpr int BK = IOA::BK, PER = IOA::NPT + IOB::NPT;
   constexpr int TM = BM / (32 * CM), TN = BN / (32 * CN);
-  static_assert(CM * CN == 4, "a multiplying and a requesting wavefront per SIMD");
+  static_assert(CM * CN <= 4, "at most a multiplying and a requesting wavefront per SIMD");
   static_assert(TM >= 1 && TN >= 1, "tile too small for the wavefront grid");
   static_assert(S >= 2 && S <= 4 && PER * (S - 1) <= 63, "wait_tiles");
 
@@ -66,7 +68,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
     int stage = S - 1;                                     // of tile t - 1
     for (int t = 0; t < n_k; ++t) {
       const int ahead = min(n_k - 1 - t, t == 0 ? S - 1 : S - 2);      // tiles requested after tile t
-      if (ahead == S - 2) wait_tiles<PER>(S - 2); else wait_tiles<PER>(ahead);
+      if (ahead == S - 2) wait_tiles<PER, S - 1>(S - 2); else wait_tiles<PER, S - 1>(ahead);
       asm volatile("s_barrier" ::: "memory");
       if (t > 0 && t - 1 + S < n_k) request(t - 1 + S, stage);
       stage = stage + 1 == S ? 0 : stage + 1;
@@ -154,19 +156,23 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
 }
 
 template <int BM, int BN, int CM, int CN, int S, int AKIND, int BKIND>
-__global__ __launch_bounds__(512, 2) void grouped_rows_kernel(GemmArgs p) {
+__global__ __launch_bounds__(64 * (4 + CM * CN), 2) void grouped_rows_kernel(GemmArgs p) {
   gemm_rows_fed<BM, BN, CM, CN, S, AKIND, BKIND>(p, (int)blockIdx.x);
 }
 
-template <int AKIND, int BKIND> static hipError_t launch_fed(const GemmArgs& p, int n_groups, hipStream_t s) {
-  constexpr int S = kFedStages;
+template <int AKIND, int BKIND> static hipError_t launch_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s) {
+  constexpr int S = kFedStages, T = kFedSmallStages;
+  if (bm == 32)
+    return launch_tiles<TBF16, 32, 64, 1, T, 6, grouped_rows_kernel<32, 64, 1, 2, T, AKIND, BKIND>>(p, n_groups, s);
+  if (bm == 64)
+    return launch_tiles<TBF16, 64, 64, 1, T, 8, grouped_rows_kernel<64, 64, 2, 2, T, AKIND, BKIND>>(p, n_groups, s);
   return launch_tiles<TBF16, 128, 128, 1, S, 8, grouped_rows_kernel<128, 128, 2, 2, S, AKIND, BKIND>>(p, n_groups, s);
 }
-hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, hipStream_t s) {
-  return launch_fed<OP_CONTIG, OP_TRANS>(p, n_groups, s);
+hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s) {
+  return launch_fed<OP_CONTIG, OP_TRANS>(p, n_groups, bm, s);
 }
-hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, hipStream_t s) {
-  return launch_fed<OP_CONTIG, OP_CONTIG>(p, n_groups, s);
+hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s) {
+  return launch_fed<OP_CONTIG, OP_CONTIG>(p, n_groups, bm, s);
 }
 
 }  // namespace prsgd

@@ -83,3 +83,27 @@ def test_contractions_of_the_largest_tiles(hidden):
     assert rel_err(D.read_all(h), want["x"]) <= 1e-4
     assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-3, atol=1e-6)
     P.prsgd_destroy(h)
+
+
+# launches of more than two small tiles per compute unit, whose workgroups have no requesting wavefronts: ragged rows, columns
+# and contractions of one to four tiles
+@pytest.mark.parametrize("dims,batch,n_workers", [
+    ((40, 200, 193, 9), 31, 136),                    # 32 x 64 tiles
+    ((70, 200, 256, 9), 32, 136),
+    ((40, 520, 65, 9), 33, 64),                      # 64 x 64 tiles
+    ((130, 513, 520, 9), 64, 64),
+])
+def test_many_small_tiles(dims, batch, n_workers):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    rows, cols, _ = P.prsgd_product_tile(batch, dims[1], n_workers, "bf16")
+    assert rows == (32 if batch <= 32 else 64) and -(-dims[1] // cols) * n_workers > 512
+    w = small_mlp(dims=dims, batch=batch, n_workers=n_workers, gemm_dtype="bf16", activation="tanh", rows_per_worker=64,
+                  iterations=1)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_local_steps(h, 1)
+    want = oracle_run(w, inp, iterations=1)
+    assert rel_err(D.read_all(h), want["x"]) <= 1e-4
+    assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-3, atol=1e-6)
+    P.prsgd_destroy(h)
