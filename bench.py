@@ -29,8 +29,8 @@ MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
 
 # rocprofv3 kernel symbol behind each timing label of the library
 KERNEL_SYMBOL = {
-    "gather": "gather_kernel", "gemm_fwd": "grouped_gemm_kernel<.., OP_CONTIG, OP_TRANS>",
-    "gemm_dx": "grouped_gemm_kernel<.., OP_CONTIG, OP_CONTIG>",
+    "gather": "gather_kernel", "gemm_fwd": "grouped_rows_kernel / grouped_gemm_kernel<.., OP_CONTIG, OP_TRANS>",
+    "gemm_dx": "grouped_rows_kernel / grouped_gemm_kernel<.., OP_CONTIG, OP_CONTIG>",
     "gemm_dw": "grouped_gemm_kernel<.., OP_TRANS, OP_TRANS>",
     "gemm_bwd": "grouped_bwd_full_kernel (grouped_bwd_kernel for layers with partial tiles)",
     "softmax_xent": "softmax_xent_kernel (loss head + row gather of the next iteration)",

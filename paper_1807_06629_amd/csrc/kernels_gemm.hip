@@ -17,6 +17,7 @@
 // on its way, so bank conflicts are avoided by permuting WHICH 16 bytes a lane requests (below).  A
 // tile is 128 bytes deep along the contraction (64 bf16 or 32 fp32 elements); an operand whose
 // contraction index is the strided one is transposed while its MFMA fragments are read out of LDS.
+// (Tiles, fragments, placement and epilogue: gemm_tile.h.  kernels_gemm_rows.hip has the workgroups with requesting wavefronts.)
 // The wavefronts of a workgroup are a WM x WN grid over the output tile times WK shares of the
 // contraction: larger blocks per wavefront read fewer LDS bytes per matrix instruction (the bound of
 // the large bf16 products), and a small output tile still occupies several matrix cores (the bound of
@@ -336,13 +337,12 @@ static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
   return best;
 }
 
-// Tiles in flight per workgroup.  Three cover the latency of one workgroup; with six or eight (74 to 147 KB
+// Tiles in flight per workgroup whose wavefronts all multiply.  Three cover the latency of one workgroup; with six or eight (74 to 147 KB
 // of LDS) a compute unit held one workgroup of two to eight wavefronts, and a launch of more tiles than
 // compute units ran in rounds.  With eight and with three tiles: 64 x (8 x 1024) x 1024 in 32 x 64 tiles 36.1
 // and 15.8 us, 128 x (8 x 64) x 1024 25.3 and 10.6 us, alone on its compute unit 4 x (8 x 4096) x 1024 26.6 and
 // 20.6 us; 64 x (64 x 1024) x 256 in 64 x 64 tiles 24.2 and 13.9 us.  Two lose where a compute unit has one
-// workgroup (32.1 us for the third of these products).  128 x 128 tiles, five, four and three in flight: 8 x (128 x 4096)
-// x 4096 with shared weights 54.1, 48.7 and 47.0 us, 64 x (128 x 1024) x 1024 38.7, 35.5 and 33.8 us.
+// workgroup (32.1 us for the third of these products).
 constexpr int kRowStages = 3;
 
 // Workgroups with requesting wavefronts (kernels_gemm_rows.hip) take the 128 x 128 tiles, and the smaller ones up to two workgroups per
