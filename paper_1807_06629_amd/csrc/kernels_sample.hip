@@ -476,7 +476,8 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
 #pragma unroll
         for (int s = 0; s < NF; ++s) {
           const int c = BF16 ? 32 * s + 8 * q4 : 16 * s + 4 * q4;
-          w[u][s] = *reinterpret_cast<const u32x4_t*>(w_g + (size_t)min(j0 + n16, k_dim - 1) * ldc + (c < ldc ? c : 0));
+          w[u][s] = c < ldc ? *reinterpret_cast<const u32x4_t*>(w_g + (size_t)min(j0 + n16, k_dim - 1) * ldc + c)
+                            : (u32x4_t){0u, 0u, 0u, 0u};      // and not some other class: zero times infinity is a NaN
         }
         hv[u] = *reinterpret_cast<const H4*>(h_r + min(j0 + 4 * q4, ldh - 4));
       }
@@ -485,7 +486,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
         const int j = 16 * (t0 + NW * u) + 4 * q4;
         f32x4_t z = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int s = 0; s < NF; ++s) {                  // D_L is zero where a piece of W_L stands in for classes past the last
+        for (int s = 0; s < NF; ++s) {                  // both are zero past the last class
           if constexpr (BF16) {
             z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[u][s]),
                                                         __builtin_bit_cast(bf16x8_t, df[s]), z, 0, 0, 0);

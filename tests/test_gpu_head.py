@@ -92,3 +92,25 @@ def test_delta_below_the_head(dtype, width, classes, batch, activation):
     launches = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
     assert launches["gemm_dx"] == 1, launches            # layer 2's only
     P.prsgd_destroy(h)
+
+
+# Class counts whose contraction of D_{L-1} goes past the last column of W_L: that part of it is zero times zero
+@pytest.mark.parametrize("dtype,classes,batch", [("f32", 5, 20), ("f32", 20, 20), ("bf16", 10, 144), ("bf16", 40, 144)])
+def test_infinite_weight_below_the_head(dtype, classes, batch):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    dims, unit = (24, 40, 64, classes), 5
+    w = small_mlp(dims=dims, batch=batch, n_workers=2, gemm_dtype=dtype, activation="relu", rows_per_worker=256,
+                  iterations=1)
+    inp = inputs_for(w)
+    b2 = 24 * 40 + 40 + 40 * 64
+    inp["targets"][:] = 0                                # every row's own class is the one that cannot be reached:
+    inp["x0"][b2 + unit] = 50.0                          # the unit is active, its logit -inf, D = -1 / B there
+    inp["x0"][b2 + 64 + unit * classes] = -np.inf
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_local_steps(h, 1)
+    bias = D.read_all(h)[:, b2:b2 + 64]
+    assert np.all(np.isneginf(bias[:, unit])), bias[:, unit]
+    assert np.isfinite(np.delete(bias, unit, axis=1)).all()
+    assert np.all(np.isposinf(P.prsgd_read_loss(h)))
+    P.prsgd_destroy(h)
