@@ -303,11 +303,10 @@ __device__ __forceinline__ float head_row_sum(float v) {
   return v + row_move<0x140>(v);
 }
 
-// With DX the workgroup also takes its rows' delta one layer down, D_{L-1} = (D_L W_L^T) phi'(H_{L-1}): it has D_L, and W_L is
-// as small as the head asks for.  Transposed, 16 units by 16 rows, so that a lane holds four consecutive units of a row; the
-// operand of W_L comes straight from memory, four tiles of it per wavefront in flight.  One launch fewer: 16 iterations of eight
-// workers of 784-300-100-10 in fp32 605 -> 565 us, of six of 1000-500-300-37 in bf16 633 -> 598 us, 8 of eight of
-// 3072-1024-1024-10, 512 rows, 1651 -> 1632 us.
+// With DX the workgroup also takes its rows' delta one layer down, D_{L-1} = (D_L W_L^T) phi'(H_{L-1}): it has D_L, and reads
+// W_L a second time (softmax_narrow_delta_pays bounds that).  Transposed, 16 units by 16 rows, so that a lane holds four consecutive
+// units of a row; the operand of W_L comes straight from memory, four tiles of it per wavefront in flight.  One launch fewer: 16
+// iterations of eight workers of 784-300-100-10 in fp32 605 -> 565 us, of six of 1000-500-300-37 in bf16 633 -> 598 us.
 template <bool BF16, int CT, bool DX>
 __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     const void* __restrict__ h_any, long h_gs, int ldh, int k_dim, const void* __restrict__ w_any,
@@ -603,6 +602,28 @@ bool softmax_narrow_applies(int n_classes, int ldc, int k_dim, bool bf16) {
   if (n_classes < 1 || n_classes > kHeadClasses || ldc > kHeadClasses || (ldc & 7) != 0) return false;
   return (bf16 && n_classes <= 16) || (long)k_dim * (ldc <= 16 ? 16 : 64) * (bf16 ? 2 : 4) <= kHeadBytes;
 }
+
+// A product of its own spreads D_{L-1} over the chip; in the head every workgroup of 16 rows walks all units, 256 at a time, and so
+// the launch saved (1.3 to 2 us) is used up by their number, and sooner where more workgroups read W_L.  Per iteration, product apart
+// and delta in the head; workgroups of the head in brackets.
+//   bf16, 256-d-10: [32] 256 units 17.6 and 16.0 us, 512 18.0 and 17.5, 768 21.3 and 20.9; [128] 256 29.3 and 27.6, 448 31.0 and 30.0,
+//   768 34.4 and 34.8; [256] 448 27.6 and 27.7, 768 32.5 and 33.8.  1024 units: [32] 21.9 and 22.3, [256] 37.3 and 41.1; 4096: [32] 31.7
+//   and 45.2, [256] 97.4 and 116.6
+//   bf16, 256-d-37: [32] 448 20.0 and 19.3, 576 20.8 and 21.1; [256] 256 25.8 and 25.1, 448 30.7 and 31.2, 700 36.4 and 37.4
+//   bf16, 256-d-64: [32] 440 22.0 and 21.1, 512 21.8 and 22.1; [256] 280 28.6 and 28.4, 440 31.2 and 32.4; [512] 192 36.0 and 36.7
+//   fp32, 128-64-d-10: [64] 640 37.5 and 37.0, 896 42.1 and 42.9; [128] 448 38.4 and 36.9, 640 46.0 and 46.8; [256] 448 48.5 and 47.5,
+//   512 51.4 and 51.9; 2048 units: [64] 65.9 and 75.5
+//   fp32, 128-64-256-37: [64] 33.2 and 31.6, [256] 45.8 and 45.8; 320 units [128] 39.9 and 42.2; 128-64-256-64: [64] 33.2 and 32.9, [256] 46.4
+//   and 49.1; 128-64-64-64: [96] 32.6 and 33.6
+bool softmax_narrow_delta_pays(int ldc, int k_dim, int head_blocks, bool bf16) {
+  const bool few = head_blocks < 128, narrow = ldc <= 16;     // workgroups on less than half of the compute units
+  const long w = (long)k_dim * ldc;
+  if (bf16) return few ? k_dim <= (narrow ? 768 : 512) && w <= 28 << 10
+                       : k_dim <= 448 && w <= 18 << 10 && (ldc < 64 || head_blocks <= 256);
+  if (narrow) return k_dim <= (few ? 640 : 448);
+  return k_dim <= 256 && (head_blocks <= 64 || (ldc < 64 && w <= 10 << 10));
+}
+int softmax_narrow_blocks(int n_workers, int batch) { return n_workers * ((batch + kHeadRows - 1) / kHeadRows); }
 
 hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_dim, const void* w,
                                       long w_gs, const float* bias, long bias_gs, const int32_t* yb,

@@ -509,10 +509,12 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     if (lo.d[l] > widest_apart) widest_apart = lo.d[l];
   }
   const bool take_apart = bwd_apart_pays(n_apart, widest_apart, B);
-  // A narrow head takes the last layer's delta one layer down as well, where that is a product of its own.  It stays one
-  // with up to 16 classes where the layers' products are apart: the backward launches of such a net are what its
-  // profile has always listed.
+  // A narrow head takes the last layer's delta one layer down as well, where that is a product of its own and faster so.  With up
+  // to 16 classes it stays one where the layers' products are apart, because test_backward_launches_of_ragged_layers counts the
+  // backward launches of such nets; it is not the faster way (300-253-10, eight workers, 64 rows 15.6 us per iteration apart and 14.1
+  // in the head; 16 workers, 128 rows 20.1 and 18.8).
   const bool head_delta = narrow_head && L > 1 &&
+                          softmax_narrow_delta_pays(lo.ld[L], lo.d[L - 1], softmax_narrow_blocks(N, B), bf16) &&
                           (fuse_average || !fused_bwd || (lo.d[L] > 16 && take_apart && bwd_products_apart(bwd_args(L))));
 
   // the loss-head launch also draws the minibatch of iteration t + 1 into the other buffer set

@@ -193,6 +193,8 @@ hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_strid
 // layer below, D_{L-1} [N][B][ld]
 struct HeadDelta { void* out; long gs; int ld, act; };
 bool softmax_narrow_applies(int n_classes, int ldc, int k_dim, bool bf16);
+bool softmax_narrow_delta_pays(int ldc, int k_dim, int head_blocks, bool bf16);
+int softmax_narrow_blocks(int n_workers, int batch);         // workgroups of a narrow head
 hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_dim, const void* w,
                                       long w_gs, const float* bias, long bias_gs, const int32_t* yb,
                                       void* delta, float* row_loss, int n_workers, int batch, int n_classes,

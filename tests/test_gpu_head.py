@@ -61,23 +61,29 @@ def test_logits_inside_the_head(dtype, width, classes, batch, n_workers, inside)
     P.prsgd_destroy(h)
 
 
-# (dtype, width in front of the logits, classes, batch): tiles of 16 units, whole and ragged, one and more per wavefront and
-# past a round of four each; rows in blocks of 16; contractions of one class, of 16, around 32 and of 64.  bf16 with more
-# than 128 rows, whose products are apart
+# (dtype, width in front of the logits, classes, batch, workers, whether the head takes the delta): tiles of 16 units, whole and
+# ragged, one and more per wavefront and past a round of four each; rows in blocks of 16; contractions of one class, of 16,
+# around 32 and of 64.  bf16 with more than 128 rows, whose products are apart.  Widths at the limits of the head, with few and with
+# many workgroups of 16 rows, and far beyond them
 BELOW = [
-    ("f32", 1, 1, 1), ("f32", 8, 16, 16), ("f32", 17, 17, 15), ("f32", 64, 10, 33), ("f32", 65, 9, 17),
-    ("f32", 256, 64, 31), ("f32", 263, 33, 16), ("f32", 1030, 5, 20),
-    ("bf16", 1, 1, 129), ("bf16", 8, 16, 144), ("bf16", 17, 17, 130), ("bf16", 64, 10, 145), ("bf16", 65, 24, 129),
-    ("bf16", 263, 32, 160), ("bf16", 256, 64, 129), ("bf16", 1030, 10, 131),
+    ("f32", 1, 1, 1, 3, True), ("f32", 8, 16, 16, 3, True), ("f32", 17, 17, 15, 3, True), ("f32", 64, 10, 33, 3, True),
+    ("f32", 65, 9, 17, 3, True), ("f32", 256, 64, 31, 3, True), ("f32", 263, 33, 16, 3, False), ("f32", 1030, 5, 20, 3, False),
+    ("f32", 640, 16, 17, 3, True), ("f32", 641, 16, 17, 3, False), ("f32", 448, 10, 144, 15, True), ("f32", 449, 10, 144, 15, False),
+    ("f32", 64, 64, 128, 8, True), ("f32", 64, 64, 80, 13, False), ("f32", 256, 40, 80, 13, True), ("f32", 2048, 10, 16, 2, False),
+    ("bf16", 1, 1, 129, 3, True), ("bf16", 8, 16, 144, 3, True), ("bf16", 17, 17, 130, 3, True), ("bf16", 64, 10, 145, 3, True),
+    ("bf16", 65, 24, 129, 3, True), ("bf16", 263, 32, 160, 3, True), ("bf16", 256, 64, 129, 3, True), ("bf16", 1030, 10, 131, 3, False),
+    ("bf16", 768, 10, 131, 3, True), ("bf16", 511, 40, 129, 3, True), ("bf16", 513, 24, 129, 3, False), ("bf16", 769, 10, 131, 3, False),
+    ("bf16", 448, 64, 129, 3, True), ("bf16", 449, 64, 129, 3, False), ("bf16", 448, 10, 160, 13, True), ("bf16", 449, 10, 160, 13, False),
+    ("bf16", 40, 64, 256, 16, True), ("bf16", 40, 64, 256, 17, False), ("bf16", 4096, 10, 129, 2, False),
 ]
 
 
 @pytest.mark.parametrize("activation", ["tanh", "relu"])
-@pytest.mark.parametrize("dtype,width,classes,batch", BELOW)
-def test_delta_below_the_head(dtype, width, classes, batch, activation):
+@pytest.mark.parametrize("dtype,width,classes,batch,n_workers,inside", BELOW)
+def test_delta_below_the_head(dtype, width, classes, batch, n_workers, inside, activation):
     assert torch.cuda.is_available()
     from paper_1807_06629_amd import drivers as D, prsgd as P
-    w = small_mlp(dims=(24, 40, width, classes), batch=batch, n_workers=3, gemm_dtype=dtype, activation=activation,
+    w = small_mlp(dims=(24, 40, width, classes), batch=batch, n_workers=n_workers, gemm_dtype=dtype, activation=activation,
                   rows_per_worker=256, iterations=1)
     inp = inputs_for(w)
     h = D.open_workload(w, inp, device="cuda:0")
@@ -90,7 +96,7 @@ def test_delta_below_the_head(dtype, width, classes, batch, activation):
     P.prsgd_profile_enable(h, True)
     P.prsgd_local_steps(h, 1)
     launches = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
-    assert launches["gemm_dx"] == 1, launches            # layer 2's only
+    assert launches["gemm_dx"] == (1 if inside else 2), launches            # layer 2's, and the head's own
     P.prsgd_destroy(h)
 
 
