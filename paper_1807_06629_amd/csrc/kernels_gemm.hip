@@ -345,18 +345,23 @@ static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
 // workgroup (32.1 us for the third of these products).
 constexpr int kRowStages = 3;
 
-// Workgroups with requesting wavefronts (kernels_gemm_rows.hip) take the 128 x 128 tiles, and the smaller ones up to two workgroups per
-// compute unit: from then on several workgroups of the plain kernel share a unit and hide each other's requests.  Per iteration, plain
-// and with requesting wavefronts: 6 workers of 1000-500-300-37, 100 rows, 37.7 and 35.3 us; 5 of 640-1024-448-960-29, 18 rows, 56.8
-// and 51.1; 16 of 600-300-100, 40 rows, 29.0 and 27.3; 24 of 520-520-520-520-30, 64 rows (216 tiles of 64 x 64), 89.4 and 86.6; 40 with
-// 32 rows (360 of 32 x 64) 101.9 and 101.0; 32 of 1000-1000-1000-50, 32 and 64 rows (512), 167.7 and 168.1, 183.0 and 182.6; 64 with 32 rows
-// (1024) 347.4 and 349.2.
+// Workgroups with requesting wavefronts (kernels_gemm_rows.hip) take the 128 x 128 tiles, and launches of fewer than two smaller tiles per
+// compute unit: from then on several workgroups of the plain kernel share a unit and hide each other's requests (its 48 KB of LDS
+// allow three, four tiles in flight two).  Per iteration, plain and with requesting wavefronts: 6 workers of 1000-500-300-37, 100 rows,
+// 37.7 and 35.3 us; 5 of 640-1024-448-960-29, 18 rows, 56.8 and 51.1; 16 of 600-300-100, 40 rows, 29.0 and 27.3; 24 of 520-520-520-520-30, 64
+// rows (216 tiles of 64 x 64), 89.4 and 86.6; 48 of 700-400-400-120 (336) 87.6 and 86.6; 50 of 800-500-500-500-100, 50 rows (400) 194.6 and
+// 193.4; 60 of it, 30 rows (480 of 32 x 64) 213.6 and 211.4.  At 512 it is one way with weights of every worker's own or a contraction
+// in ranges (the logits product of 8 of 4096-4096-4096-4096-1000, 128 rows, interval 1, 24.2 and 25.7 us, an iteration 522.1 and 524.6; 32 of
+// 1000-1000-1000-50, 32 and 64 rows, 195.6 and 196.4, 206.6 and 207.1) and the other way with shared ones (64 of 1024-512-512-512-40, 64 rows,
+// interval 1, 104.0 and 102.7).  64 of 1000-1000-1000-50, 32 rows (1024), 347.4 and 349.2.
 constexpr long kFedTiles = 2 * kComputeUnits;
 static long rows_tiles(RowsTile t, int rows, int cols, int splits, int n_groups) {
   return (long)((rows + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1) * n_groups;
 }
 static bool rows_fed(RowsTile t, const GemmArgs& p, int n_groups) {
-  return t.bn == 128 || (t.bm <= 64 && rows_tiles(t, p.M, p.N, p.k_splits, n_groups) <= kFedTiles);
+  if (t.bn == 128 || t.bm > 64) return t.bn == 128;
+  const long tiles = rows_tiles(t, p.M, p.N, p.k_splits, n_groups);
+  return tiles < kFedTiles || (tiles == kFedTiles && p.b_gs == 0 && p.k_splits <= 1);
 }
 
 template <int AKIND, int BKIND>
@@ -379,6 +384,7 @@ void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows
   GemmArgs p;
   memset(&p, 0, sizeof(p));
   p.M = rows; p.N = cols;
+  p.b_gs = 1;                                              // every worker has weights of its own
   const RowsTile t = rows_tile(p, n_groups, bf16);
   const bool fed = rows_fed(t, p, n_groups);
   *tile_rows = t.bm;

@@ -41,6 +41,14 @@ def test_no_tile_is_taller_than_the_minibatch(P, dtype):
         assert rows <= (32 if b <= 32 else 64 if b <= 64 else 128), (b, n, w, rows, cols)
 
 
+# (rows, columns of a layer, tile): four tiles in flight are the launches with requesting wavefronts, three the others
+@pytest.mark.parametrize("batch,cols,tile", [(64, 1024, (64, 64)), (64, 1000, (64, 64)), (32, 1024, (32, 64)), (31, 1001, (32, 64))])
+def test_two_small_tiles_per_compute_unit_have_no_requesting_wavefronts(P, batch, cols, tile):
+    stage = sum(tile) * 128
+    assert P.prsgd_product_tile(batch, cols, 31, "bf16") == (*tile, 4 * stage)      # 496 tiles
+    assert P.prsgd_product_tile(batch, cols, 32, "bf16") == (*tile, 3 * stage)      # 512
+
+
 def test_bad_arguments_are_rejected(P):
     for bad in ((0, 1, 1), (1, 0, 1), (1, 1, 0)):
         with pytest.raises(P.PrsgdError):
