@@ -33,7 +33,9 @@ KERNEL_SYMBOL = {
     "gemm_dx": "grouped_rows_kernel / grouped_gemm_kernel<.., OP_CONTIG, OP_CONTIG>",
     "gemm_dw": "grouped_gemm_kernel<.., OP_TRANS, OP_TRANS>",
     "gemm_bwd": "grouped_bwd_full_kernel (grouped_bwd_kernel for layers with partial tiles)",
-    "softmax_xent": "softmax_xent_kernel (loss head + row gather of the next iteration)",
+    "softmax_xent": "softmax_xent_kernel / softmax_xent_row_kernel (257 to 1024 classes) / softmax_xent_narrow_kernel (few "
+                    "classes: with the logits product, and the delta below where that pays); loss head + row gather of the "
+                    "next iteration",
     "sgd_update": "update_kernel",
     "average": "average_kernel (restart_small_kernel<.., true> when N >= 8 and a replica has fewer "
                "than 262144 floats)",
@@ -48,13 +50,15 @@ KERNEL_SYMBOL = {
 }
 
 
-def algorithmic_work(w, shared_weights=False, first_fused=False):
+def algorithmic_work(w, shared_weights=False, first_fused=False, head_logits=False, head_delta=False):
     """Algorithmic HBM bytes and flops of ONE iteration, per kernel label (all launches of
     that label in the iteration summed), plus those of one restart average.  shared_weights:
     every iteration starts from the node average (I = 1, one-pass form), so the forward and
     backward-data products read one weight matrix per layer instead of one per worker.
     first_fused: the first layer's backward kernel also runs the next forward product of that
-    layer (label gemm_bwd_first), so gemm_fwd and gemm_bwd cover the layers above it."""
+    layer (label gemm_bwd_first), so gemm_fwd and gemm_bwd cover the layers above it.
+    head_logits, head_delta: the loss head takes the logits product, and the delta of the layer
+    below, along (label softmax_xent), so gemm_fwd and gemm_dx cover the layers below the last."""
     n, b = w.n_workers, w.batch
     nw = 1 if shared_weights else n
     out = {}
@@ -94,18 +98,27 @@ def algorithmic_work(w, shared_weights=False, first_fused=False):
         l1_fwd_b = nw * d0 * d1 * es + n * (b * d0 * es + b * d1 * es)
         out["gemm_bwd"] = {"bytes": bwd_b - l1_bwd_b, "flops": dw_f + dx_f - 2 * n * b * d0 * d1}
         fwd_b, fwd_f = fwd_b - l1_fwd_b, fwd_f - 2 * n * b * d0 * d1
+    # fused epoch kernel (one launch = `interval` iterations): per iteration the gathered rows and
+    # all three products; the weights cross HBM once per launch (read + write), amortised here
+    out["mlp2_epoch"] = {"bytes": n * b * (dims[0] + 1) * 4 + (8.0 + mom) * n * m / max(1, w.interval),
+                         "flops": fwd_f + dx_f + dw_f}
+    # logits read (or, inside the head, W_L and H_{L-1}), D_L written; with the delta D_{L-1} written
+    k, c = layers[-1]
+    head_b, head_f = n * b * c * (4 + es), 0
+    if head_logits:
+        head_b, head_f = nw * k * c * es + n * b * (k + c) * es, 2 * n * b * k * c
+        fwd_b, fwd_f = fwd_b - (nw * k * c * es + n * b * (k + c) * es), fwd_f - 2 * n * b * k * c
+    if head_delta:
+        head_b, head_f = head_b + n * b * k * es, head_f + 2 * n * b * k * c
+        dx_b, dx_f = dx_b - (nw * k * c * es + n * b * (c + 2 * k) * es), dx_f - 2 * n * b * k * c
     out["gather"] = {"bytes": n * b * dims[0] * (4 + es), "flops": 0}
     out["gemm_fwd"] = {"bytes": fwd_b, "flops": fwd_f}
     out["gemm_dx"] = {"bytes": dx_b, "flops": dx_f}
     out["gemm_dw"] = {"bytes": dw_b, "flops": dw_f}
     # the loss-head launch also gathers the next iteration's minibatch (the stand-alone gather only
     # runs when no draw is waiting: the first iteration of a run)
-    out["softmax_xent"] = {"bytes": n * b * dims[-1] * (4 + es) + out["gather"]["bytes"], "flops": 0}
+    out["softmax_xent"] = {"bytes": head_b + out["gather"]["bytes"], "flops": head_f}
     out["sgd_update"] = {"bytes": n * m * (12 + mom + shadow), "flops": (2 + (2 if mom else 0)) * n * m}
-    # fused epoch kernel (one launch = `interval` iterations): per iteration the gathered rows and
-    # all three products; the weights cross HBM once per launch (read + write), amortised here
-    out["mlp2_epoch"] = {"bytes": n * b * (dims[0] + 1) * 4 + (8.0 + mom) * n * m / max(1, w.interval),
-                         "flops": fwd_f + dx_f + dw_f}
     out["average"] = {"bytes": n * m * 8 + n * pw * shadow, "flops": n * m}
     # restart with the broadcast deferred: every replica read once, the node average (and its
     # bf16 image) written once
@@ -115,6 +128,40 @@ def algorithmic_work(w, shared_weights=False, first_fused=False):
     out["step_mean"] = {"bytes": m * 8 + pw * shadow + sum(n * b * (di + do) * 2 for di, do in layers),
                         "flops": dw_f}
     return out
+
+
+def head_products(w, launches, closing_passes):
+    """Whether the loss head took (the logits product, the delta of the layer below) along: from the launches
+    per label of a stretch of iterations, `closing_passes` of which may have ended an epoch in one pass with
+    the restart.  H_1 is a forward product or comes from the first layer's backward kernel; separate
+    backward-data products run in every iteration with gemm_dw launches, or in the closing passes."""
+    if w.model != "mlp" or not launches.get("softmax_xent"):
+        return False, False
+    n_layers, iterations = len(w.dims) - 1, launches["softmax_xent"]
+    forward = launches.get("gemm_fwd", 0) + launches.get("gemm_bwd_first", 0)
+    passes = iterations if launches.get("gemm_dw") else closing_passes if launches.get("step_mean") else 0
+    return (forward < iterations * (n_layers - 0.5),
+            passes > 0 and launches.get("gemm_dx", 0) < passes * (n_layers - 1.5))
+
+
+def priced_iterations(w, name, launches, iterations, first_fused, head_logits, head_delta):
+    """How many times the work of one iteration (algorithmic_work) the launches of a label did.  Kernels launched
+    once per layer are priced per launch: they do not run in every iteration (the pass that closes an epoch
+    replaces the per-replica backward kernels by backward-data products and the stacked weight-gradient
+    product).  Weight gradients may share a launch, and are priced per pass."""
+    if w.model == "mlp":
+        n_layers = len(w.dims) - 1
+        per_iteration = {"gemm_fwd": n_layers - first_fused - head_logits, "gemm_bwd": n_layers - first_fused,
+                         "gemm_dx": n_layers - 1 - head_delta}
+        if name in per_iteration:
+            return launches[name] / max(1, per_iteration[name])
+        if name == "gemm_dw":
+            return launches["softmax_xent"]
+    if name == "step_mean":
+        return max(1, iterations // w.interval)
+    if name in ("average", "restart_mean", "gather", "gemm_bwd_first", "softmax_xent", "sgd_update"):
+        return launches[name]                         # one launch per restart, or iteration in which they run
+    return iterations                                 # one launch covers several iterations, or each has its own
 
 
 def kernel_source_digest():
@@ -359,25 +406,14 @@ def main() -> int:
     one_pass = (w.interval == 1 and w.model == "mlp" and w.gemm_dtype == "bf16" and not args.unfused
                 and not args.eager_restart and w.momentum == 0.0 and w.batch <= 128)
     first_fused = any(s["name"] == "gemm_bwd_first" for s in stats)
-    work = algorithmic_work(w, shared_weights=one_pass, first_fused=first_fused)
+    launches = {s["name"]: s["launches"] for s in stats}
+    head_logits, head_delta = head_products(w, launches, prof_steps // w.interval)
+    work = algorithmic_work(w, shared_weights=one_pass, first_fused=first_fused, head_logits=head_logits, head_delta=head_delta)
     prof_key = w.name + ("_I1" if one_pass else "")      # counter readings are kept per launch pattern
     kernels = {}
-    # the work table is per iteration; kernels launched once per layer are priced per launch (they do
-    # not run in every iteration: the pass that closes an epoch replaces the per-replica backward
-    # kernels by backward-data products and the stacked weight-gradient product)
-    n_layers = len(w.dims) - 1
-    per_iteration_launches = {"gemm_fwd": n_layers - (1 if first_fused else 0),
-                              "gemm_bwd": n_layers - (1 if first_fused else 0),
-                              "gemm_dx": n_layers - 1, "gemm_dw": n_layers, "step_mean": n_layers}
     for s in stats:
         per_iter = work.get(s["name"], {"bytes": 0, "flops": 0})
-        calls = prof_steps if s["name"] not in ("average", "restart_mean") else max(1, prof_steps // w.interval)
-        if s["name"] in ("lsq_steps", "mlp2_epoch"):
-            calls = prof_steps                        # one launch covers several iterations
-        if s["name"] in ("gather", "gemm_bwd_first", "softmax_xent", "sgd_update"):
-            calls = s["launches"]                     # one launch per iteration in which they run
-        if s["name"] in per_iteration_launches and w.model == "mlp":
-            calls = s["launches"] / max(1, per_iteration_launches[s["name"]])
+        calls = priced_iterations(w, s["name"], launches, prof_steps, first_fused, head_logits, head_delta)
         tot_bytes, tot_flops = per_iter["bytes"] * calls, per_iter["flops"] * calls
         sec = s["total_ms"] * 1e-3
         kernels[s["name"]] = {

@@ -102,3 +102,64 @@ def test_stacked_product_of_the_epoch_closing_pass():
     assert work["step_mean"]["flops"] == 2 * n * b * _pw(w.dims)
     # shared weights: the forward products read one weight matrix per layer, not one per worker
     assert bench.algorithmic_work(w)["gemm_fwd"]["bytes"] - work["gemm_fwd"]["bytes"] == 2 * (n - 1) * _pw(w.dims)
+
+
+def test_products_that_the_loss_head_takes_along_are_priced_there():
+    w = get_workload("c3")
+    n, b, k, c = w.n_workers, w.batch, w.dims[-2], w.dims[-1]
+    plain = bench.algorithmic_work(w)
+    logits = bench.algorithmic_work(w, head_logits=True)
+    both = bench.algorithmic_work(w, head_logits=True, head_delta=True)
+    product = 2 * n * b * k * c
+    gather = plain["gather"]["bytes"]
+    for work in (logits, both):                          # nothing is lost or counted twice
+        assert sum(work[x]["flops"] for x in ("gemm_fwd", "gemm_dx", "softmax_xent")) == \
+            sum(plain[x]["flops"] for x in ("gemm_fwd", "gemm_dx"))
+        assert plain["gemm_fwd"]["flops"] - work["gemm_fwd"]["flops"] == product
+        assert plain["gemm_fwd"]["bytes"] - work["gemm_fwd"]["bytes"] == 2 * n * (k * c + b * (k + c))
+        assert work["gemm_dw"] == plain["gemm_dw"] and work["mlp2_epoch"] == plain["mlp2_epoch"]
+    # W_L and H_{L-1} read, D_L written; no logits in memory
+    assert logits["softmax_xent"]["bytes"] == 2 * n * (k * c + b * k + b * c) + gather
+    assert logits["gemm_dx"] == plain["gemm_dx"]
+    # D_{L-1} written
+    assert both["softmax_xent"]["bytes"] == logits["softmax_xent"]["bytes"] + 2 * n * b * k
+    assert plain["gemm_dx"]["bytes"] - both["gemm_dx"]["bytes"] == 2 * n * (k * c + b * (c + 2 * k))
+
+
+def test_what_the_loss_head_took_along_shows_in_the_launches():
+    three, four = get_workload("c3"), get_workload("c5")         # layers
+    # interval 32, two epochs: H_1 comes from the backward kernel in 62 of 64 iterations; two passes close an epoch
+    assert bench.head_products(three, {"softmax_xent": 64, "gemm_fwd": 66, "gemm_bwd_first": 62, "gemm_bwd": 124,
+                                       "gemm_dx": 4, "step_mean": 2}, 2) == (True, False)
+    assert bench.head_products(three, {"softmax_xent": 64, "gemm_fwd": 66, "gemm_bwd_first": 62, "gemm_bwd": 124,
+                                       "gemm_dx": 2, "step_mean": 2}, 2) == (True, True)
+    # interval 1, logits product of its own
+    assert bench.head_products(four, {"softmax_xent": 32, "gemm_fwd": 128, "gemm_dx": 96, "step_mean": 128}, 32) == (False, False)
+    # separate products in every iteration
+    assert bench.head_products(three, {"softmax_xent": 64, "gemm_fwd": 128, "gemm_dx": 64, "gemm_dw": 64}, 2) == (True, True)
+    assert bench.head_products(three, {"softmax_xent": 64, "gemm_fwd": 128, "gemm_dx": 128, "gemm_dw": 64}, 2) == (True, False)
+    # two layers: no product is left when the head takes the delta
+    two = three.scaled(dims=(256, 128, 10))
+    assert bench.head_products(two, {"softmax_xent": 64, "gemm_fwd": 64, "gemm_dw": 64}, 2) == (True, True)
+    assert bench.head_products(two, {"mlp2_epoch": 4}, 2) == (False, False)
+    # momentum: no pass of separate products
+    assert bench.head_products(three, {"softmax_xent": 64, "gemm_fwd": 66, "gemm_bwd_first": 63, "gemm_bwd": 128}, 2) == (True, False)
+
+
+def test_launches_are_priced_by_the_passes_they_belong_to():
+    w = get_workload("c3").scaled(interval=1)
+    # logits inside the head, delta apart: two forward and two backward-data products, all weight gradients in one launch
+    launches = {"softmax_xent": 32, "gemm_fwd": 64, "gemm_dx": 64, "step_mean": 32, "gather": 1, "restart_mean": 1}
+    took = bench.head_products(w, launches, 32)
+    assert took == (True, False)
+    for name in ("softmax_xent", "gemm_fwd", "gemm_dx", "step_mean"):
+        assert bench.priced_iterations(w, name, launches, 32, False, *took) == 32, name
+    for name in ("gather", "restart_mean"):
+        assert bench.priced_iterations(w, name, launches, 32, False, *took) == 1
+    # the head took the delta as well: one backward-data product an iteration
+    launches["gemm_dx"] = 32
+    took = bench.head_products(w, launches, 32)
+    assert took == (True, True) and bench.priced_iterations(w, "gemm_dx", launches, 32, False, *took) == 32
+    # weight gradients of all layers in one launch or in two
+    for count in (64, 128):
+        assert bench.priced_iterations(w, "gemm_dw", {"softmax_xent": 64, "gemm_dw": count}, 64, False, True, True) == 64
