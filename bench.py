@@ -50,7 +50,7 @@ KERNEL_SYMBOL = {
 }
 
 
-def algorithmic_work(w, shared_weights=False, first_fused=False, head_logits=False, head_delta=False):
+def algorithmic_work(w, shared_weights=False, first_fused=False, head_logits=False, head_delta=False, fused_update=True):
     """Algorithmic HBM bytes and flops of ONE iteration, per kernel label (all launches of
     that label in the iteration summed), plus those of one restart average.  shared_weights:
     every iteration starts from the node average (I = 1, one-pass form), so the forward and
@@ -58,7 +58,8 @@ def algorithmic_work(w, shared_weights=False, first_fused=False, head_logits=Fal
     first_fused: the first layer's backward kernel also runs the next forward product of that
     layer (label gemm_bwd_first), so gemm_fwd and gemm_bwd cover the layers above it.
     head_logits, head_delta: the loss head takes the logits product, and the delta of the layer
-    below, along (label softmax_xent), so gemm_fwd and gemm_dx cover the layers below the last."""
+    below, along (label softmax_xent), so gemm_fwd and gemm_dx cover the layers below the last.
+    fused_update: the weight-gradient products update the weights; otherwise they write G."""
     n, b = w.n_workers, w.batch
     nw = 1 if shared_weights else n
     out = {}
@@ -78,7 +79,7 @@ def algorithmic_work(w, shared_weights=False, first_fused=False, head_logits=Fal
     fwd_f = sum(2 * n * b * di * do for di, do in layers)
     dx_b = sum(nw * di * do * es + n * (b * do * es + 2 * b * di * es) for di, do in layers[1:])
     dx_f = sum(2 * n * b * di * do for di, do in layers[1:])
-    dw_b = sum(n * (di * do * (8 + shadow) + b * (di + do) * es) for di, do in layers)
+    dw_b = sum(n * (di * do * (8 + shadow if fused_update else 4) + b * (di + do) * es) for di, do in layers)
     dw_f = fwd_f
     # fused backward kernel (bf16 operands): master read + write, shadow write, the activation and
     # delta panels, and the delta of the layer below; both products
@@ -408,7 +409,8 @@ def main() -> int:
     first_fused = any(s["name"] == "gemm_bwd_first" for s in stats)
     launches = {s["name"]: s["launches"] for s in stats}
     head_logits, head_delta = head_products(w, launches, prof_steps // w.interval)
-    work = algorithmic_work(w, shared_weights=one_pass, first_fused=first_fused, head_logits=head_logits, head_delta=head_delta)
+    work = algorithmic_work(w, shared_weights=one_pass, first_fused=first_fused, head_logits=head_logits,
+                            head_delta=head_delta, fused_update=not args.unfused)
     prof_key = w.name + ("_I1" if one_pass else "")      # counter readings are kept per launch pattern
     kernels = {}
     for s in stats:

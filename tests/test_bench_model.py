@@ -163,3 +163,11 @@ def test_launches_are_priced_by_the_passes_they_belong_to():
     # weight gradients of all layers in one launch or in two
     for count in (64, 128):
         assert bench.priced_iterations(w, "gemm_dw", {"softmax_xent": 64, "gemm_dw": count}, 64, False, True, True) == 64
+
+
+def test_separate_weight_gradients_write_four_bytes_per_weight_element():
+    for name, es, update in (("c2", 4, 8), ("c3", 2, 10)):
+        w = get_workload(name)
+        panels = sum(w.n_workers * w.batch * (di + do) * es for di, do in zip(w.dims[:-1], w.dims[1:]))
+        assert bench.algorithmic_work(w)["gemm_dw"]["bytes"] == update * w.n_workers * _pw(w.dims) + panels
+        assert bench.algorithmic_work(w, fused_update=False)["gemm_dw"]["bytes"] == 4 * w.n_workers * _pw(w.dims) + panels
