@@ -100,6 +100,56 @@ def test_delta_below_the_head(dtype, width, classes, batch, n_workers, inside, a
     P.prsgd_destroy(h)
 
 
+# Ragged nets whose layers' products are apart with at most 128 rows: one launch for all weight gradients, one for each delta that
+# the head does not take
+@pytest.mark.parametrize("dims,batch,n_workers,launches", [
+    ((40, 30, 20, 37), 100, 3, 2),
+    ((300, 200, 24), 33, 8, 1),
+    ((40, 70, 300, 64), 128, 3, 2),
+    ((40, 70, 513, 17), 100, 3, 3),                      # beyond the head's units
+    ((40, 30, 449, 64), 100, 3, 3),                      # ... and its weights
+])
+def test_delta_below_the_head_of_ragged_nets(dims, batch, n_workers, launches):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=dims, batch=batch, n_workers=n_workers, gemm_dtype="bf16", activation="tanh", rows_per_worker=256,
+                  iterations=1)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_local_steps(h, 1)
+    want = oracle_run(w, inp, iterations=1)
+    assert rel_err(D.read_all(h), want["x"]) <= 1e-4
+    assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-3, atol=1e-6)
+    P.prsgd_profile_enable(h, True)
+    P.prsgd_local_steps(h, 1)
+    counts = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
+    assert counts["gemm_bwd"] == launches, counts
+    P.prsgd_destroy(h)
+
+
+# The pass that steps and restarts at once, whose head reads weights shared by all workers; the bounds are those of the other
+# interval-one runs
+@pytest.mark.parametrize("dims,batch,n_workers", [
+    ((100, 72, 40, 37), 24, 4), ((64, 130, 256, 64), 128, 2), ((72, 96, 300, 24), 33, 5), ((80, 64, 640, 10), 64, 8),
+])
+@pytest.mark.parametrize("activation", ["relu", "tanh"])
+def test_delta_below_the_head_at_interval_one(dims, batch, n_workers, activation):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=dims, batch=batch, n_workers=n_workers, gemm_dtype="bf16", activation=activation, rows_per_worker=256,
+                  interval=1, iterations=5)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_profile_enable(h, True)
+    P.prsgd_run(h, w.iterations, 1)
+    counts = {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
+    assert counts["gemm_dx"] == w.iterations, counts     # layer 2's only
+    want = oracle_run(w, inp)
+    assert np.all(np.abs(P.prsgd_read_loss(h) - want["losses"]) <= 2e-2 * np.abs(want["losses"]) + 2.0 ** -20)
+    assert rel_err(D.read_all(h), want["x"]) <= 5e-3
+    P.prsgd_destroy(h)
+
+
 # Class counts whose contraction of D_{L-1} goes past the last column of W_L: that part of it is zero times zero
 @pytest.mark.parametrize("dtype,classes,batch", [("f32", 5, 20), ("f32", 20, 20), ("bf16", 10, 144), ("bf16", 40, 144)])
 def test_infinite_weight_below_the_head(dtype, classes, batch):
