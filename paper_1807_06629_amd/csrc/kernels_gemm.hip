@@ -307,20 +307,20 @@ static hipError_t launch_one(const GemmArgs& p, int n_groups, hipStream_t s) {
 }
 constexpr int kComputeUnits = 256;
 
-// Batch-row products (forward, backward-data).  What bounds a launch is the rate at which one compute
-// unit takes in its operand tiles (the number of lines it can have outstanding), so a launch takes the tile
-// with which the busiest compute unit requests the fewest bytes: tiles per compute unit, rounded up, times
-// rows + columns of a tile.  Workers x (rows x contraction) x columns: 8 x (128 x 4096) x 4096 with shared weights,
-// 128 x 128 tiles 57 -> 49 us forward against the register-staged tiles this replaces (backward-data, two such products
-// and one with a contraction of 1000 on average 47 -> 40 us); 6 x (100 x 500) x 300, 32 x 64 tiles 9.6 -> 6.7 us.  Taken in 32 x 64, 64 x 64, 128 x 64 and 128 x 128 tiles:
-// 6 x (128 x 896) x 3776 25.7, 17.8, 16.6, 16.1 us (128 x 128 by the rule), 8 x (95 x 3456) x 3760 119.7, 100.3, 78.9,
-// 73.5 us (128 x 128), 6 x (100 x 500) x 300 8.7, 9.1, 10.2, 12.5 us (32 x 64); over 292 products the rule's tile is
-// within 3 % of the best one on six in seven, and within 18 % on all.
+// Batch-row products (forward, backward-data).  A launch takes the tile with which the busiest compute unit requests the fewest bytes:
+// tiles per compute unit, rounded up, times rows + columns of a tile.  Not all are bound by that intake (128 x 128 tiles and small
+// launches divide requests and products between wavefronts, kernels_gemm_rows.hip), but it orders the tiles well: over 600 products of
+// 8 to 512 rows, 1 to 64 workers and 64 to 4096 columns and contraction elements the rule's tile is within 3 % of the best one on 88 %,
+// within 10 % on 94 %.  The worst have contractions of one or two tiles behind the epilogue of 128 x 128 (31 x (128 x 128) x 2088 15.4 us, in
+// 128 x 64 10.4).  Launched by itself in 32 x 64, 64 x 64, 128 x 64 and 128 x 128 tiles, the rule's in brackets: 8 x (128 x 4096) x 4096 with shared
+// weights 72.5, 53.2, 45.2, [34.4] us, backward-data 71.3, 55.1, 46.9, [34.3]; 6 x (128 x 896) x 3776 22.0, 14.8, 13.3, [11.7]; 8 x (95 x
+// 3456) x 3760 74.7, 57.8, 47.4, [33.0]; 64 x (128 x 1024) x 1024 43.5, 33.3, 30.9, [30.5]; 6 x (100 x 500) x 300 [4.4], 4.9, 6.6, 7.8.
+// 128 x 64 tiles run in the plain kernel only: they are taken for launches of many of them, where workgroups share a unit.
 // bf16 adds the contraction in one ascending chain in every tile: the first layer's backward kernel
 // computes the same product ahead and must give the same bits.
-// No tile is taller than the minibatch: half of a 128-row tile of 64 rows was copies of the last row, multiplied
-// and thrown away (128 x (64 x 256) x 1024: 30.6 -> 21.0 us in 64 x 64 tiles; fp32 16 x (8 x 2048) x 2048: 47.7 -> 32.3 us
-// forward, 43.6 -> 26.1 us backward-data in 32- instead of 64-row tiles).
+// No tile is taller than the minibatch: half of a 128-row tile of 64 rows is copies of the last row, multiplied
+// and thrown away (measured on an earlier kernel, 128 x (64 x 256) x 1024: 30.6 -> 21.0 us in 64 x 64 tiles; fp32 16 x (8 x 2048) x 2048:
+// 47.7 -> 32.3 us forward, 43.6 -> 26.1 us backward-data in 32- instead of 64-row tiles).
 // fp32 is bound by its matrix instructions, 8 times as slow: 32 x 32 tiles whose wavefronts share the
 // contraction (8 x (50 x 784) x 300: 27.5 -> 12 us), until the chip is full either way.
 struct RowsTile { int bm, bn; };
@@ -337,12 +337,11 @@ static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
   return best;
 }
 
-// Tiles in flight per workgroup whose wavefronts all multiply.  Three cover the latency of one workgroup; with six or eight (74 to 147 KB
-// of LDS) a compute unit held one workgroup of two to eight wavefronts, and a launch of more tiles than
+// Tiles in flight per workgroup of the plain kernel, whose wavefronts all multiply.  Three cover the latency of one workgroup; with six or
+// eight (74 to 147 KB of LDS) a compute unit held one workgroup of two to eight wavefronts, and a launch of more tiles than
 // compute units ran in rounds.  With eight and with three tiles: 64 x (8 x 1024) x 1024 in 32 x 64 tiles 36.1
-// and 15.8 us, 128 x (8 x 64) x 1024 25.3 and 10.6 us, alone on its compute unit 4 x (8 x 4096) x 1024 26.6 and
-// 20.6 us; 64 x (64 x 1024) x 256 in 64 x 64 tiles 24.2 and 13.9 us.  Two lose where a compute unit has one
-// workgroup (32.1 us for the third of these products).
+// and 15.8 us, 128 x (8 x 64) x 1024 25.3 and 10.6 us; 64 x (64 x 1024) x 256 in 64 x 64 tiles 24.2 and 13.9 us.  Two lose where a compute
+// unit has one workgroup (4 x (8 x 4096) x 1024 three 20.6, two 32.1 us), which is where the requesting kernel stands now (11.4).
 constexpr int kRowStages = 3;
 
 // Workgroups with requesting wavefronts (kernels_gemm_rows.hip) take the 128 x 128 tiles, and launches of fewer than two smaller tiles per

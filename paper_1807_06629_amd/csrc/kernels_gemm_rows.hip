@@ -63,8 +63,8 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
       IOA::request(a_src + (size_t)j * a_step, a_off, lds_a, w);
       IOB::request(b_src + (size_t)j * b_step, b_off, lds_b, w);
     };
-  #pragma unroll 1                                           // one copy of a request, and one in the loop
-  for (int j = 0; j < min(S, n_k); ++j) request(j, j);
+#pragma unroll 1                                           // one copy of a request, and one in the loop
+    for (int j = 0; j < min(S, n_k); ++j) request(j, j);
     int stage = S - 1;                                     // of tile t - 1
     for (int t = 0; t < n_k; ++t) {
       const int ahead = min(n_k - 1 - t, t == 0 ? S - 1 : S - 2);      // tiles requested after tile t

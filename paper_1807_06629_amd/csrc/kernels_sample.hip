@@ -416,41 +416,41 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
   __syncthreads();
   if (!DX && b >= batch) return;                        // whole groups of 16 lanes
   if (b < batch) {
-  const size_t r = (size_t)g * batch + b;
-  float z[CT], mx = -INFINITY;
+    const size_t r = (size_t)g * batch + b;
+    float z[CT], mx = -INFINITY;
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int c = 16 * ct + l16;
-    z[ct] = -INFINITY;
-    if (c < n_classes)
-      z[ct] = (((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c]) + bias_c[ct];
-    mx = fmaxf(mx, z[ct]);
-  }
-  mx = head_row_max(mx);
-  float e[CT], se = 0.0f, zl = 0.0f;
+    for (int ct = 0; ct < CT; ++ct) {
+      const int c = 16 * ct + l16;
+      z[ct] = -INFINITY;
+      if (c < n_classes)
+        z[ct] = (((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c]) + bias_c[ct];
+      mx = fmaxf(mx, z[ct]);
+    }
+    mx = head_row_max(mx);
+    float e[CT], se = 0.0f, zl = 0.0f;
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int c = 16 * ct + l16;
-    if (c == label && c < n_classes) zl = z[ct];        // an out-of-range label selects nothing
-    e[ct] = c < n_classes ? expf(z[ct] - mx) : 0.0f;
-    se += e[ct];
-  }
-  se = head_row_sum(se);
-  zl = head_row_sum(zl);
+    for (int ct = 0; ct < CT; ++ct) {
+      const int c = 16 * ct + l16;
+      if (c == label && c < n_classes) zl = z[ct];        // an out-of-range label selects nothing
+      e[ct] = c < n_classes ? expf(z[ct] - mx) : 0.0f;
+      se += e[ct];
+    }
+    se = head_row_sum(se);
+    zl = head_row_sum(zl);
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int c = 16 * ct + l16;
-    if (c < ldc) {
-      const float d = c < n_classes ? (e[ct] / se - (c == label ? 1.0f : 0.0f)) * (1.0f / (float)batch) : 0.0f;
-      if (BF16) reinterpret_cast<uint16_t*>(delta)[r * ldc + c] = f32_to_bf16_rne(d);
-      else reinterpret_cast<float*>(delta)[r * ldc + c] = d;
-      if constexpr (DX) {
-        if constexpr (BF16) d_lds[row * DS + c] = f32_to_bf16_rne(d);
-        else d_lds[row * DS + c] = d;
+    for (int ct = 0; ct < CT; ++ct) {
+      const int c = 16 * ct + l16;
+      if (c < ldc) {
+        const float d = c < n_classes ? (e[ct] / se - (c == label ? 1.0f : 0.0f)) * (1.0f / (float)batch) : 0.0f;
+        if (BF16) reinterpret_cast<uint16_t*>(delta)[r * ldc + c] = f32_to_bf16_rne(d);
+        else reinterpret_cast<float*>(delta)[r * ldc + c] = d;
+        if constexpr (DX) {
+          if constexpr (BF16) d_lds[row * DS + c] = f32_to_bf16_rne(d);
+          else d_lds[row * DS + c] = d;
+        }
       }
     }
-  }
-  if (l16 == 0) row_loss[r] = (mx + logf(se)) - zl;
+    if (l16 == 0) row_loss[r] = (mx + logf(se)) - zl;
   }
   if constexpr (DX) {
     __syncthreads();
@@ -522,7 +522,6 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     }
   }
 }
-
 
 // Minibatch loss of each worker: mean of its row losses, rows summed in slot order.
 __global__ void loss_mean_kernel(const float* __restrict__ row_loss, float* __restrict__ losses,

@@ -27,7 +27,7 @@ def test_a_compute_unit_holds_two_workgroups_of_the_smaller_tiles(P, dtype):
     for b, n, w in SHAPES:
         rows, cols, lds = P.prsgd_product_tile(b, n, w, dtype)
         seen.add((rows, cols))
-        # an operand tile is 128 bytes deep; more than three in flight were slower on every tile
+        # an operand tile is 128 bytes deep; three in flight, or four in half of the LDS (small launches with requesting wavefronts, fp32)
         assert lds <= max(3 * (rows + cols) * 128, LDS_BYTES // 2), (b, n, w, rows, cols, lds)
         if (rows, cols) != (128, 128):
             assert 2 * lds <= LDS_BYTES, (b, n, w, rows, cols, lds)
