@@ -343,9 +343,24 @@ bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
          d_out >= BT && (d_out % BT) == 0;
 }
 
+// A band walks its d_0 / 64 row tiles one after the other, at 0.8 us each behind the two launches that it replaces (0.4 us more than
+// their own share of a tile with up to 64 minibatch rows, 0.9 with 128), while those spread the layer over the chip; their backward
+// pass walks d_1 / 64 column tiles at 0.75 us.  So a tall layer is taken apart until its bands are so many that its bytes count.
+// Per iteration, fused less apart, bands in brackets: 64 rows, 2560 x 256 [8] +13 us, [64] +8.6; 4096 x 1024 [32] +19.1, [64] +4.6, [80]
+// -2.8, [128] -19.2; 2048 x 1024 [16] +3.2, [80] -3.1; 1536 x 1024 [16] -2.0; 768 x 2048 [32] -16; 512 x 256 [4] -1.4.  128 rows:
+// 2560 x 1024 [16] +21, [96] +7.9, [128] -1.6; 1280 x 1024 [16] +4.1, [128] -1.9.  (4 workers of 2560-256-40, 64 rows: 41.8 and 27.7 us.)
+// With momentum 128 rows, 2048 x 1024 [64] +12.8, [80] -0.2, [96] -3.6.  Up to eight row tiles there is next to nothing in it.  An odd
+// number of column tiles apart is the general backward kernel's (3 workers of 1408-1216-303, 128 rows: 45.4 us, 55 apart).
+static bool bwd_first_fwd_pays(const BwdArgs& p) {
+  const int rows = p.K / BT, cols = p.Nn / BT;
+  if (rows <= 8 || (cols & 1) != 0) return true;
+  if (cols * p.n_groups >= (p.B <= 64 ? 80 : p.vel != nullptr ? 96 : 128)) return true;
+  return p.B <= 64 ? 5 * rows <= 8 * cols + 20 : 20 * rows <= 17 * cols + 60;
+}
+
 // Whole tiles, every worker active, and the buffers of the next iteration given.
 bool bwd_first_fwd_applies(const BwdArgs& p) {
-  if (!bwd_first_fwd_shape(p.B, p.K, p.Nn)) return false;
+  if (!bwd_first_fwd_shape(p.B, p.K, p.Nn) || !bwd_first_fwd_pays(p)) return false;
   if (p.worker_steps != nullptr || p.dx != nullptr) return false;
   if (p.x_next == nullptr || p.h_next == nullptr) return false;
   return (p.ldw % 4) == 0 && (p.ldh % 8) == 0 && (p.ldx % 8) == 0 && (p.ldd % 8) == 0 && (p.w_off % 4) == 0;
