@@ -207,9 +207,9 @@ __device__ __forceinline__ void fetch_args(const GemmArgs& p) {
   const int* w = reinterpret_cast<const int*>(&p);
   asm volatile("" :: "s"(w[0]), "s"(w[16]), "s"(w[32]), "s"(w[48]), "s"(w[sizeof(GemmArgs) / 4 - 1]),
                "s"(p.a), "s"(p.a_gs), "s"(p.lda), "s"(p.b), "s"(p.b_gs), "s"(p.ldb), "s"(p.M), "s"(p.N), "s"(p.Kc),
-               "s"(p.place.first.mul), "s"(p.place.second.mul), "s"(p.place.order), "s"(p.worker_steps));
+               "s"(p.place.first.mul), "s"(p.place.second.mul), "s"(p.place.order), "s"(p.order));
 }
-struct TileAt { int g, m0, n0, split, n_splits; };         // split: contraction range of n_splits
+struct TileAt { int g, m0, n0, split, n_splits; };         // worker; split: contraction range of n_splits
 template <int BM, int BN> __device__ __forceinline__ TileAt tile_at(const GemmArgs& p, int block) {
   const TilePlace& t = p.place;
   TileAt r;
@@ -232,6 +232,7 @@ template <int BM, int BN> __device__ __forceinline__ TileAt tile_at(const GemmAr
     tn = t.order == 1 ? u : v;
     r.g = t.order == 1 ? v : q;
   }
+  if (p.order != nullptr) r.g = p.order[r.g];
   r.m0 = tm * BM;
   r.n0 = tn * BN;
   return r;

@@ -86,6 +86,7 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
     g = blockIdx.x / bands;
     band = blockIdx.x % bands;
   }
+  if (p.order != nullptr) g = p.order[g];
   const int n0 = band * NB;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -358,10 +359,10 @@ static bool bwd_first_fwd_pays(const BwdArgs& p) {
   return p.B <= 64 ? 5 * rows <= 8 * cols + 20 : 20 * rows <= 17 * cols + 60;
 }
 
-// Whole tiles, every worker active, and the buffers of the next iteration given.
+// Whole tiles, and the buffers of the next iteration given.
 bool bwd_first_fwd_applies(const BwdArgs& p) {
   if (!bwd_first_fwd_shape(p.B, p.K, p.Nn) || !bwd_first_fwd_pays(p)) return false;
-  if (p.worker_steps != nullptr || p.dx != nullptr) return false;
+  if (p.dx != nullptr) return false;
   if (p.x_next == nullptr || p.h_next == nullptr) return false;
   return (p.ldw % 4) == 0 && (p.ldh % 8) == 0 && (p.ldx % 8) == 0 && (p.ldd % 8) == 0 && (p.w_off % 4) == 0;
 }

@@ -7,6 +7,8 @@
 // run-to-run deterministic summation order) and writes the mean back N times.  Every global
 // access is a fully coalesced 16-byte vector, so the kernels need neither LDS nor cross-lane
 // traffic and are limited by HBM alone.
+#include <string.h>
+
 #include "prsgd_internal.h"
 
 namespace prsgd {
@@ -245,14 +247,12 @@ __global__ __launch_bounds__(kThreads) void fill_zero_kernel(f32x4_t* __restrict
 }
 
 // Same update over [N][m_pad] with finished workers (Algorithm 3) left untouched.
-__global__ __launch_bounds__(kThreads) void update_masked_kernel(float4* __restrict__ x,
-                                                                 const float4* __restrict__ g,
-                                                                 uint2* __restrict__ shadow,
-                                                                 size_t stride4, float lr,
-                                                                 const int* __restrict__ worker_steps,
-                                                                 int step) {
-  const int i = blockIdx.y;
-  if (worker_steps != nullptr && step >= worker_steps[i]) return;
+__global__ __launch_bounds__(kThreads) void update_workers_kernel(float4* __restrict__ x,
+                                                                  const float4* __restrict__ g,
+                                                                  uint2* __restrict__ shadow,
+                                                                  size_t stride4, float lr,
+                                                                  const int* __restrict__ order) {
+  const int i = order[blockIdx.y];
   for (size_t col = (size_t)blockIdx.x * kThreads + threadIdx.x; col < stride4;
        col += (size_t)gridDim.x * kThreads) {
     const size_t k = (size_t)i * stride4 + col;
@@ -265,6 +265,14 @@ __global__ __launch_bounds__(kThreads) void update_masked_kernel(float4* __restr
     x[k] = xv;
     if (shadow != nullptr) shadow[k] = pack_bf16x4(xv);
   }
+}
+
+struct IntBlock {
+  static constexpr int kCount = 256;
+  int v[kCount];
+};
+__global__ __launch_bounds__(IntBlock::kCount) void store_ints_kernel(int* __restrict__ dst, int n, IntBlock b) {
+  if ((int)threadIdx.x < n) dst[threadIdx.x] = b.v[threadIdx.x];
 }
 
 // Plain streaming copy with exactly known traffic (bandwidth / counter calibration).
@@ -450,14 +458,57 @@ hipError_t launch_fill_zero(float* x, size_t count, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_update_masked(float* x, const float* g, uint16_t* shadow, long m_pad, int n_workers,
-                                float lr, const int* worker_steps, int step, hipStream_t s) {
+hipError_t launch_update_workers(float* x, const float* g, uint16_t* shadow, long m_pad, const int* order,
+                                 int n_workers, float lr, hipStream_t s) {
   const size_t stride4 = (size_t)m_pad / 4;
   int gx = grid_for(stride4, kStreamBlocks / (n_workers < 8 ? n_workers : 8));
-  hipLaunchKernelGGL(update_masked_kernel, dim3(gx, n_workers), dim3(kThreads), 0, s,
+  hipLaunchKernelGGL(update_workers_kernel, dim3(gx, n_workers), dim3(kThreads), 0, s,
                      reinterpret_cast<float4*>(x), reinterpret_cast<const float4*>(g),
-                     reinterpret_cast<uint2*>(shadow), stride4, lr, worker_steps, step);
+                     reinterpret_cast<uint2*>(shadow), stride4, lr, order);
   return hipGetLastError();
+}
+
+// A few integers from the host, as arguments of a launch: stream order like any other launch, and the caller's array is free again
+// on return.  A copy from pageable memory has to be waited for instead, which leaves the device idle until the host has caught up.
+struct IntStore {
+  int* dst;
+  hipStream_t s;
+  int n = 0;
+  hipError_t e = hipSuccess;
+  IntBlock b = {};
+  void add(int v) {
+    b.v[n++] = v;
+    if (n == IntBlock::kCount) flush();
+  }
+  hipError_t flush() {
+    if (n > 0 && e == hipSuccess) {
+      hipLaunchKernelGGL(store_ints_kernel, dim3(1), dim3(IntBlock::kCount), 0, s, dst, n, b);
+      e = hipGetLastError();
+    }
+    dst += n;
+    n = 0;
+    return e;
+  }
+};
+hipError_t launch_store_ints(int* dst, const int* src_host, int count, hipStream_t s) {
+  IntStore to{dst, s};
+  for (int i = 0; i < count; ++i) to.add(src_host[i]);
+  return to.flush();
+}
+// The indices of steps_host by falling values, equal ones in their order.
+hipError_t launch_store_order(int* dst, const int* steps_host, int count, hipStream_t s) {
+  IntStore to{dst, s};
+  int value = -1;
+  for (int i = 0; i < count; ++i) value = steps_host[i] > value ? steps_host[i] : value;
+  for (int left = count; left > 0;) {
+    int lower = -1;
+    for (int i = 0; i < count; ++i) {
+      if (steps_host[i] == value) { to.add(i); --left; }
+      if (steps_host[i] < value && steps_host[i] > lower) lower = steps_host[i];
+    }
+    value = lower;
+  }
+  return to.flush();
 }
 
 }  // namespace prsgd

@@ -46,7 +46,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   fetch_args(p);
   const TileAt at = tile_at<BM, BN>(p, block);
   const int g = at.g, m0 = at.m0, n0 = at.n0, ks = at.split, n_splits = at.n_splits;
-  if (p.worker_steps != nullptr && p.step >= p.worker_steps[g]) return;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int STAGE = (BM + BN) * kTileBytes;

@@ -28,7 +28,6 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
   fetch_args(p);
   const TileAt at = tile_at<BM, BN>(p, block);
   const int g = at.g, m0 = at.m0, n0 = at.n0;
-  if (p.worker_steps != nullptr && p.step >= p.worker_steps[g]) return;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int STAGE = (BM + BN) * kTileBytes;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -74,12 +74,16 @@ __device__ __forceinline__ void gather_row(const GatherArgs& a, int j, int i) {
   }
 }
 
+// ... of the i-th of the workers that draw; nothing for an i past them.
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void gather_kernel(GatherArgs a, const int* __restrict__ worker_steps,
-                                                          int step) {
-  const int j = blockIdx.x, i = blockIdx.y;
-  if (worker_steps != nullptr && step >= worker_steps[i]) return;
-  gather_row<BF16>(a, j, i);
+__device__ __forceinline__ void gather_group(const GatherArgs& a, int j, int i) {
+  if (i >= a.workers) return;
+  gather_row<BF16>(a, j, a.order != nullptr ? a.order[i] : i);
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kThreads) void gather_kernel(GatherArgs a) {
+  gather_group<BF16>(a, blockIdx.x, blockIdx.y);
 }
 
 __global__ __launch_bounds__(kThreads) void sample_indices_kernel(int32_t* __restrict__ out,
@@ -134,16 +138,16 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     const float* __restrict__ logits, int n_parts, long part_stride, const float* __restrict__ bias,
     long bias_gs, const int32_t* __restrict__ yb, void* __restrict__ delta,
     float* __restrict__ row_loss, int batch, int n_classes, int ldc,
-    const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next) {
+    const int* __restrict__ order, int head_blocks, GatherArgs next) {
   fetch_kernel_args<kHeadArgBytes>();
-  const int g = blockIdx.y;
+  int g = blockIdx.y;
   // workgroups beyond the loss head's own: the minibatch draw of the NEXT iteration, which depends
   // on nothing this iteration computes (zeta_i^t is a function of seed, i, t and the slot alone)
   if ((int)blockIdx.x >= head_blocks) {
-    gather_row<BF16>(next, (int)blockIdx.x - head_blocks, g);
+    gather_group<BF16>(next, (int)blockIdx.x - head_blocks, g);
     return;
   }
-  if (worker_steps != nullptr && step >= worker_steps[g]) return;
+  if (order != nullptr) g = order[g];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.x * (kThreads / kWave) + wave;
   if (b >= batch) return;
@@ -220,14 +224,14 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_row_kernel(
     const float* __restrict__ logits, int n_parts, long part_stride, const float* __restrict__ bias,
     long bias_gs, const int32_t* __restrict__ yb, void* __restrict__ delta,
     float* __restrict__ row_loss, int batch, int n_classes, int ldc,
-    const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next) {
+    const int* __restrict__ order, int head_blocks, GatherArgs next) {
   fetch_kernel_args<kHeadArgBytes>();
-  const int g = blockIdx.y;
+  int g = blockIdx.y;
   if ((int)blockIdx.x >= head_blocks) {                 // the minibatch draw of the next iteration
-    gather_row<BF16>(next, (int)blockIdx.x - head_blocks, g);
+    gather_group<BF16>(next, (int)blockIdx.x - head_blocks, g);
     return;
   }
-  if (worker_steps != nullptr && step >= worker_steps[g]) return;
+  if (order != nullptr) g = order[g];
   __shared__ float red[3][kThreads / kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const size_t r = (size_t)g * batch + blockIdx.x;
@@ -312,14 +316,14 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     const void* __restrict__ h_any, long h_gs, int ldh, int k_dim, const void* __restrict__ w_any,
     long w_gs, const float* __restrict__ bias, long bias_gs, const int32_t* __restrict__ yb,
     void* __restrict__ delta, float* __restrict__ row_loss, int batch, int n_classes, int ldc,
-    const int* __restrict__ worker_steps, int step, int head_blocks, GatherArgs next, HeadDelta below) {
+    const int* __restrict__ order, int head_blocks, GatherArgs next, HeadDelta below) {
   fetch_kernel_args<kHeadArgBytes + 16 + sizeof(HeadDelta)>();
-  const int g = blockIdx.y;
+  int g = blockIdx.y;
   if ((int)blockIdx.x >= head_blocks) {                 // the minibatch draw of the next iteration
-    gather_row<BF16>(next, (int)blockIdx.x - head_blocks, g);
+    gather_group<BF16>(next, (int)blockIdx.x - head_blocks, g);
     return;
   }
-  if (worker_steps != nullptr && step >= worker_steps[g]) return;
+  if (order != nullptr) g = order[g];
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
   constexpr int NW = kThreads / kWave;
@@ -533,20 +537,20 @@ __global__ void loss_mean_kernel(const float* __restrict__ row_loss, float* __re
   losses[g] = s / (float)batch;
 }
 
-hipError_t launch_gather(const GatherArgs& a, int n_workers, bool bf16, const int* worker_steps, int step,
-                         hipStream_t s) {
-  dim3 grid(a.batch, n_workers);
-  if (bf16) hipLaunchKernelGGL(gather_kernel<true>, grid, dim3(kThreads), 0, s, a, worker_steps, step);
-  else hipLaunchKernelGGL(gather_kernel<false>, grid, dim3(kThreads), 0, s, a, worker_steps, step);
+hipError_t launch_gather(const GatherArgs& a, bool bf16, hipStream_t s) {
+  dim3 grid(a.batch, a.workers);
+  if (bf16) hipLaunchKernelGGL(gather_kernel<true>, grid, dim3(kThreads), 0, s, a);
+  else hipLaunchKernelGGL(gather_kernel<false>, grid, dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
 GatherArgs gather_args(const float* features, const int32_t* labels, void* xb, int32_t* yb, int32_t* idx,
-                       int batch, int d0, int ld0, long rows, uint64_t seed, int64_t t) {
+                       int batch, int d0, int ld0, long rows, uint64_t seed, int64_t t, const int* order, int workers) {
   GatherArgs a;
   a.features = features; a.labels = labels; a.xb = xb; a.yb = yb; a.idx = idx;
   a.batch = batch; a.d0 = d0; a.ld0 = ld0; a.rows = rows; a.log2n = ilog2(rows);
   a.seed = seed; a.t = (uint64_t)t;
+  a.order = order; a.workers = workers;
   return a;
 }
 
@@ -564,7 +568,7 @@ hipError_t launch_sample_indices(uint64_t seed, int n_workers, int batch, long r
 hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_stride, const float* bias,
                                long bias_gs, const int32_t* yb, void* delta, float* row_loss,
                                int n_workers, int batch, int n_classes, int ldc, bool bf16,
-                               const int* worker_steps, int step, const GatherArgs* next, hipStream_t s) {
+                               const int* order, const GatherArgs* next, hipStream_t s) {
   if (n_parts != 1 && n_parts != 2 && n_parts != kMaxLogitSplits) return hipErrorInvalidValue;
   GatherArgs ga;
   memset(&ga, 0, sizeof(ga));
@@ -573,21 +577,21 @@ hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_strid
     dim3 grid(batch + (next != nullptr ? next->batch : 0), n_workers);
     if (bf16)
       hipLaunchKernelGGL(softmax_xent_row_kernel<true>, grid, dim3(kThreads), 0, s, logits, n_parts, part_stride,
-                         bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step, batch, ga);
+                         bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, order, batch, ga);
     else
       hipLaunchKernelGGL(softmax_xent_row_kernel<false>, grid, dim3(kThreads), 0, s, logits, n_parts, part_stride,
-                         bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step, batch, ga);
+                         bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, order, batch, ga);
     return hipGetLastError();
   }
   const int head_blocks = (batch + kThreads / kWave - 1) / (kThreads / kWave);
   dim3 grid(head_blocks + (next != nullptr ? next->batch : 0), n_workers);
   if (bf16)
     hipLaunchKernelGGL(softmax_xent_kernel<true>, grid, dim3(kThreads), 0, s, logits, n_parts, part_stride,
-                       bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step,
+                       bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, order,
                        head_blocks, ga);
   else
     hipLaunchKernelGGL(softmax_xent_kernel<false>, grid, dim3(kThreads), 0, s, logits, n_parts, part_stride,
-                       bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step,
+                       bias, bias_gs, yb, delta, row_loss, batch, n_classes, ldc, order,
                        head_blocks, ga);
   return hipGetLastError();
 }
@@ -627,7 +631,7 @@ int softmax_narrow_blocks(int n_workers, int batch) { return n_workers * ((batch
 hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_dim, const void* w,
                                       long w_gs, const float* bias, long bias_gs, const int32_t* yb,
                                       void* delta, float* row_loss, int n_workers, int batch, int n_classes,
-                                      int ldc, bool bf16, const int* worker_steps, int step, const GatherArgs* next,
+                                      int ldc, bool bf16, const int* order, const GatherArgs* next,
                                       const HeadDelta* below, hipStream_t s) {
   if (!softmax_narrow_applies(n_classes, ldc, k_dim, bf16) || (ldh % 8) != 0) return hipErrorInvalidValue;
   HeadDelta hd;
@@ -645,7 +649,7 @@ hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_d
                      : (ldc <= 16 ? of(softmax_xent_narrow_kernel<false, 1, false>, softmax_xent_narrow_kernel<false, 1, true>)
                                   : of(softmax_xent_narrow_kernel<false, 4, false>, softmax_xent_narrow_kernel<false, 4, true>));
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, h, h_gs, ldh, k_dim, w, w_gs, bias,
-                     bias_gs, yb, delta, row_loss, batch, n_classes, ldc, worker_steps, step, head_blocks, ga, hd);
+                     bias_gs, yb, delta, row_loss, batch, n_classes, ldc, order, head_blocks, ga, hd);
   return hipGetLastError();
 }
 

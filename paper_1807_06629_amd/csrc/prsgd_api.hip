@@ -388,6 +388,19 @@ struct DwQueue {
   }
 };
 
+// Workers that take an iteration (Algorithm 3), and those for which it may prepare the next one.  By falling step counts, the
+// workers that go on are the first of those that take the present step, so that a launch has workgroups for them only.  With a
+// workgroup of every worker that ended at once for the others, workers of unlike speed also left XCDs idle: one to four steps of
+// worker i after i mod 4 had their last step on two of eight (two epochs of 16 workers of
+// 3072-1024-1024-10, 64 rows: 1250 -> 1010 us, with the first layer fused for those that go on).
+struct Active {
+  const int* order = nullptr;   // device: workers by falling step counts (nullptr: every worker, in its own place)
+  int now = 0;                  // order[0 .. now) take this iteration
+  const int* next_order = nullptr;
+  int next = 0;                 // next_order[0 .. next) also take the following one, whose minibatch is drawn ahead
+  int idx_set = -1;             // batch set whose row numbers a masked draw writes: the last ones of every worker stand together
+};
+
 // One local iteration of every (active) MLP worker: gradient observation + eq. (3).
 // fuse_average: this iteration is followed by a restart, and both are taken together,
 //   (1/N) sum_i (x_i - gamma G_i) = ybar - (gamma / N) sum_i G_i,   ybar = (1/N) sum_i x_i   (eq. 2-3).
@@ -395,30 +408,29 @@ struct DwQueue {
 // ybar; the replicas are not rewritten and the context ends "at the mean".  With every worker
 // already at ybar (I = 1) it is one mini-batch SGD step with the N B samples of all workers (first
 // footnote of Section 1).
-// draw_ahead: the next iteration is an unmasked one as well, whose minibatch (and first activation) this one
-// may prepare.
-int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool fuse_average = false,
-             bool draw_ahead = true) {
+// A next iteration that every worker takes also has its first activation prepared.
+int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average = false) {
   const prsgd_config& c = ctx->cfg;
   const Layout& lo = ctx->lo;
   const Carve& cv = ctx->cv;
-  const int N = c.n_workers, B = c.batch, L = lo.n_layers;
+  const int* order = active.order;
+  const int N = active.now, B = c.batch, L = lo.n_layers;
   const bool bf16 = ctx->bf16;
   hipStream_t s = ctx->stream;
 
   // The minibatch of iteration t: already there when the previous iteration's loss-head launch
-  // drew it (below); otherwise gathered now.  A masked draw (Algorithm 3) is never reused.
-  auto batch_args = [&](int k, int64_t tt) {
+  // drew it (below); otherwise gathered now.  prsgd_local_steps_hetero forgets masked draws at the end of an epoch.
+  auto batch_args = [&](int k, int64_t tt, const int* workers, int n) {
     return gather_args(ctx->features, reinterpret_cast<const int32_t*>(ctx->targets), ctx->xb(k), ctx->yb(k),
-                       ctx->idx(k), B, lo.d[0], lo.ld[0], (long)c.rows_per_worker, c.seed, tt);
+                       ctx->idx(workers != nullptr && active.idx_set >= 0 ? active.idx_set : k), B, lo.d[0], lo.ld[0],
+                       (long)c.rows_per_worker, c.seed, tt, workers, n);
   };
-  int bk = -1;
-  if (worker_steps == nullptr) bk = ctx->batch_t[0] == t ? 0 : ctx->batch_t[1] == t ? 1 : -1;
+  int bk = ctx->batch_t[0] == t ? 0 : ctx->batch_t[1] == t ? 1 : -1;
   if (bk < 0) {
     bk = ctx->batch_cur;
     ctx->batch_t[bk] = -1;
-    LAUNCH(ctx, KK_GATHER, launch_gather(batch_args(bk, t), N, bf16, worker_steps, step, s));
-    if (worker_steps == nullptr) ctx->batch_t[bk] = t;
+    LAUNCH(ctx, KK_GATHER, launch_gather(batch_args(bk, t, order, N), bf16, s));
+    ctx->batch_t[bk] = t;
   }
   ctx->batch_cur = bk;
 
@@ -430,9 +442,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
   base.grads = ctx->grads();
   base.shadow = ctx->shadow();
   base.p_gs = lo.m_pad;
-  base.worker_steps = worker_steps;
+  base.order = order;
   base.streaming = ctx->streamed.steps ? 1 : 0;
-  base.step = step;
 
   auto act_in = [&](int l) -> const void* {   // H_l as stored (l = 0: the gathered batch)
     return l == 0 ? ctx->xb(bk) : ctx->at<void>(cv.h[l]);
@@ -441,7 +452,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
   // Right after a restart every worker starts from the shared node average (stride 0); only
   // the fused backward kernel writes complete replicas from it, so every other path first
   // broadcasts the average.  A masked worker (Algorithm 3) would keep a stale replica.
-  if (ctx->at_mean && (!fused_bwd || worker_steps != nullptr)) {
+  if (ctx->at_mean && (!fused_bwd || order != nullptr)) {
     const int rc = materialize(ctx);
     if (rc != PRSGD_OK) return rc;
   }
@@ -455,15 +466,14 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
 
   // forward.  H_1 may already be there: the previous iteration's first-layer backward kernel computes
   // it from the weights it writes, for this iteration's minibatch
-  const bool h1_ready = fused_bwd && !from_mean && worker_steps == nullptr && L >= 2 &&
-                        ctx->h1_t == t && ctx->h1_batch == bk;
+  const bool h1_ready = fused_bwd && !from_mean && L >= 2 && ctx->h1_t == t && ctx->h1_batch == bk;
   ctx->h1_t = -1;
   if (!h1_ready && ctx->shadow1_stale && !from_mean) {
     const int rc = refresh_first_shadow(ctx);
     if (rc != PRSGD_OK) return rc;
   }
   int logit_parts = 1;
-  const long logit_part_stride = (long)N * B * lo.ld[L];
+  const long logit_part_stride = (long)c.n_workers * B * lo.ld[L];
   // a narrow logits layer is multiplied inside the loss-head launch
   const bool narrow_head = softmax_narrow_applies(lo.d[L], lo.ld[L], lo.d[L - 1], bf16);
   for (int l = 1; l <= L; ++l) {
@@ -499,7 +509,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     q.n_groups = N; q.act = c.activation; q.streaming = ctx->streamed.steps ? 1 : 0;
     q.lr = ctx->lr;
     q.vel = ctx->velocity(); q.mu = c.momentum;
-    q.worker_steps = worker_steps; q.step = step;
+    q.order = order;
     return q;
   };
   int n_apart = 0, widest_apart = 0;
@@ -518,8 +528,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
                           (fuse_average || !fused_bwd || (lo.d[L] > 16 && take_apart && bwd_products_apart(bwd_args(L))));
 
   // the loss-head launch also draws the minibatch of iteration t + 1 into the other buffer set
-  const bool prefetch = worker_steps == nullptr && draw_ahead;
-  GatherArgs next_batch = batch_args(bk ^ 1, t + 1);
+  const bool prefetch = active.next > 0;
+  GatherArgs next_batch = batch_args(bk ^ 1, t + 1, active.next_order, active.next);
   if (prefetch) ctx->batch_t[bk ^ 1] = -1;
   HeadDelta below;
   memset(&below, 0, sizeof(below));
@@ -534,7 +544,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
                                            : (const void*)(reinterpret_cast<const float*>(wsrc) + lo.w_off[L - 1]),
                                       w_gs, ctx->src() + lo.b_off[L - 1], ctx->src_stride(), ctx->yb(bk),
                                       ctx->at<void>(cv.delta[L]), ctx->at<float>(cv.row_loss), N, B, lo.d[L],
-                                      lo.ld[L], bf16, worker_steps, step, prefetch ? &next_batch : nullptr,
+                                      lo.ld[L], bf16, order, prefetch ? &next_batch : nullptr,
                                       head_delta ? &below : nullptr, s));
   else
   LAUNCH(ctx, KK_LOSS,
@@ -542,7 +552,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
                              logit_parts > 1 ? ctx->src() + lo.b_off[L - 1] : nullptr, ctx->src_stride(),
                              ctx->yb(bk),
                              ctx->at<void>(cv.delta[L]), ctx->at<float>(cv.row_loss), N, B, lo.d[L],
-                             lo.ld[L], bf16, worker_steps, step, prefetch ? &next_batch : nullptr, s));
+                             lo.ld[L], bf16, order, prefetch ? &next_batch : nullptr, s));
   if (prefetch) ctx->batch_t[bk ^ 1] = t + 1;
 
   // products of layer l: D_{l-1} = (D_l W_l^T) phi'(H_{l-1}) and dW_l = H_{l-1}^T D_l
@@ -608,6 +618,8 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     if (l == 1 && L >= 2 && ctx->first_fusion && prefetch && ctx->batch_t[bk ^ 1] == t + 1) {
       q.x_next = reinterpret_cast<const uint16_t*>(ctx->xb(bk ^ 1)); q.x_gs = (long)B * lo.ld[0]; q.ldx = lo.ld[0];
       q.h_next = ctx->at<uint16_t>(cv.h[1]); q.hn_gs = (long)B * lo.ld[1]; q.ldhn = lo.ld[1];
+      q.order = active.next_order;
+      q.n_groups = active.next;
       if (bwd_first_fwd_applies(q)) {
         const int rc = dw.flush();          // H_1 is rewritten: layer 2's weight gradient still reads it
         if (rc != PRSGD_OK) return rc;
@@ -615,8 +627,13 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
         ctx->shadow1_stale = first_shadow_left = true;   // not written: it has no reader while H_1 comes from here
         ctx->h1_t = t + 1;
         ctx->h1_batch = bk ^ 1;
+        if (N == active.next) continue;
+        q.order = active.next_order + active.next;       // the workers that are done
+        q.n_groups = N - active.next;
+        LAUNCH(ctx, KK_BWD, launch_bwd_fused(q, s));
         continue;
       }
+      q = bwd_args(l);
     }
     if (take_apart && bwd_products_apart(q)) {
       if (l > 1 && !(l == L && head_delta)) LAUNCH(ctx, KK_BWD, launch_gemm_dx(dx_args(l), N, true, s));
@@ -640,22 +657,29 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const int* worker_steps, int step, bool 
     const int rc = dw.flush();
     if (rc != PRSGD_OK) return rc;
   }
-  // every other backward pass of layer 1 writes the shadows of the replicas it steps
-  if (fused_bwd && worker_steps == nullptr && !first_shadow_left) ctx->shadow1_stale = false;
+  // every other backward pass of layer 1 writes the shadows of the replicas it steps: those of all workers, or of those
+  // whose first activation was there, which had been left
+  if (fused_bwd && (order == nullptr || h1_ready) && !first_shadow_left) ctx->shadow1_stale = false;
 
   if (!c.fused_update) {
     if (ctx->velocity() != nullptr)
       LAUNCH(ctx, KK_UPDATE, launch_momentum_update(ctx->params, ctx->velocity(), ctx->grads(), ctx->shadow(),
                                                     (size_t)N * lo.m_pad, ctx->lr, c.momentum, s));
-    else if (worker_steps == nullptr)
+    else if (order == nullptr)
       LAUNCH(ctx, KK_UPDATE, launch_update(ctx->params, ctx->grads(), ctx->shadow(),
                                            (size_t)N * lo.m_pad, ctx->lr, s));
     else
-      LAUNCH(ctx, KK_UPDATE, launch_update_masked(ctx->params, ctx->grads(), ctx->shadow(), lo.m_pad,
-                                                  N, ctx->lr, worker_steps, step, s));
+      LAUNCH(ctx, KK_UPDATE, launch_update_workers(ctx->params, ctx->grads(), ctx->shadow(), lo.m_pad, order, N, ctx->lr, s));
   }
   ctx->at_mean = false;            // every parameter of every replica has been rewritten
   return PRSGD_OK;
+}
+
+// An iteration of every worker, and one behind it.
+Active every_worker(const prsgd_ctx* ctx) {
+  Active a;
+  a.now = a.next = ctx->cfg.n_workers;
+  return a;
 }
 
 Fused2Args fused2_args(prsgd_ctx* ctx, int k, const int* worker_steps) {
@@ -1197,7 +1221,7 @@ int prsgd_local_steps(prsgd_ctx* ctx, int32_t k) {
     return PRSGD_OK;
   }
   for (int32_t s = 0; s < k; ++s) {
-    const int rc = mlp_step(ctx, ctx->t + 1, nullptr, 0);
+    const int rc = mlp_step(ctx, ctx->t + 1, every_worker(ctx));
     if (rc != PRSGD_OK) return rc;
     ctx->t += 1;
   }
@@ -1226,12 +1250,11 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
     const int mrc = materialize(ctx);
     if (mrc != PRSGD_OK) return mrc;
   }
+  // the step counts, or (layer by layer) the workers by falling step counts
   int* steps_dev = ctx->at<int>(ctx->cv.steps);
-  // The pageable source may be reused by the caller right after return: wait for the copy.
-  hipError_t e = hipMemcpyAsync(steps_dev, steps_host, sizeof(int32_t) * c.n_workers,
-                                hipMemcpyHostToDevice, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  if (e != hipSuccess) return hip_fail(ctx, e, "copy of worker step counts");
+  const hipError_t e = layers ? launch_store_order(steps_dev, steps_host, c.n_workers, ctx->stream)
+                              : launch_store_ints(steps_dev, steps_host, c.n_workers, ctx->stream);
+  if (e != hipSuccess) return hip_fail(ctx, e, "worker step counts");
   if (c.model == PRSGD_LSQ) {
     LsqArgs a = lsq_args(ctx, k_max);
     a.worker_steps = steps_dev;
@@ -1247,13 +1270,34 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
     ctx->t += k_max;
     return PRSGD_OK;
   }
-  for (int32_t s = 0; s < k_max; ++s) {
-    const bool all = s < k_min;
-    const int rc = mlp_step(ctx, ctx->t + 1, all ? nullptr : steps_dev, s, false, s + 1 < k_min || k_min == k_max);
-    if (rc != PRSGD_OK) return rc;
-    ctx->t += 1;
+  auto workers_at = [&](int32_t s) {              // that take step s (from 0)
+    int n = 0;
+    for (int i = 0; i < c.n_workers; ++i) n += steps_host[i] > s ? 1 : 0;
+    return n;
+  };
+  int rc = PRSGD_OK, idx_set = -1;
+  if (k_min == 0 && k_max > 0) ctx->batch_t[0] = ctx->batch_t[1] = -1;   // drawn for workers that take no step as well
+  for (int32_t s = 0; s < k_max && rc == PRSGD_OK; ++s) {
+    Active a = every_worker(ctx);
+    if (s >= k_min) {
+      a.order = steps_dev;
+      a.now = workers_at(s);
+    }
+    if (s + 1 >= k_min && k_min != k_max) {
+      a.next_order = steps_dev;
+      a.next = workers_at(s + 1);
+      // masked draws write the row numbers beside those that the workers that are done drew last
+      if (idx_set < 0) idx_set = ctx->batch_t[0] == ctx->t + 1 ? 0 : ctx->batch_t[1] == ctx->t + 1 ? 1 : ctx->batch_cur;
+      a.idx_set = idx_set;
+    }
+    rc = mlp_step(ctx, ctx->t + 1, a);
+    if (rc == PRSGD_OK) ctx->t += 1;
   }
-  return PRSGD_OK;
+  if (k_min != k_max) {                           // a masked draw is not reused
+    ctx->batch_t[0] = ctx->batch_t[1] = -1;
+    if (idx_set >= 0) ctx->batch_cur = idx_set;
+  }
+  return rc;
 }
 
 int prsgd_average(prsgd_ctx* ctx) {
@@ -1349,7 +1393,7 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
         if (rc != PRSGD_OK) return rc;
       }
       if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
-      const int rc = mlp_step(ctx, ctx->t + 1, nullptr, 0, true);
+      const int rc = mlp_step(ctx, ctx->t + 1, every_worker(ctx), true);
       if (rc != PRSGD_OK) return rc;
       ctx->t += 1;
       left -= k_epoch;

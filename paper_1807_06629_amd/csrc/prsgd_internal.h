@@ -67,8 +67,7 @@ struct GemmArgs {
   // activation-like output (element type T, or float for logits) and auxiliary input
   void* out; long out_gs; int ldo; int out_cols;
   const void* aux; long aux_gs; int ldaux;
-  // Algorithm 3: group g is skipped once step >= worker_steps[g] (nullptr = all active)
-  const int* worker_steps; int step;
+  const int* order;                   // Algorithm 3: group g is worker order[g] (nullptr: worker g)
   // logits product of a narrow last layer: the contraction is cut into k_splits ranges, split s
   // writes its partial sums (no bias) at out + s * split_stride; the loss head adds them up
   int k_splits; long split_stride;
@@ -97,7 +96,7 @@ struct BwdArgs {
   int n_groups, act, streaming;
   float lr;
   float* vel; float mu;                         // momentum buffers [N][p_gs] (nullptr = plain SGD)
-  const int* worker_steps; int step;            // Algorithm 3 mask (nullptr = all active)
+  const int* order;                             // Algorithm 3: group g is worker order[g] (nullptr: worker g)
   // first layer only (kernels_bwd_first.hip): minibatch of the next iteration [N][B][ldx] and
   // where its first hidden activation goes [N][B][ldhn]
   const uint16_t* x_next; long x_gs; int ldx;
@@ -177,18 +176,19 @@ struct GatherArgs {
   void* xb; int32_t* yb; int32_t* idx;        // batch rows [N][B][ld0], labels and row indices [N][B]
   int batch, d0, ld0; long rows; int log2n;
   uint64_t seed, t;
+  const int* order; int workers;              // Algorithm 3: the workers order[0 .. workers) draw (nullptr: 0 .. workers)
 };
 GatherArgs gather_args(const float* features, const int32_t* labels, void* xb, int32_t* yb, int32_t* idx,
-                       int batch, int d0, int ld0, long rows, uint64_t seed, int64_t t);
-hipError_t launch_gather(const GatherArgs& a, int n_workers, bool bf16, const int* worker_steps, int step,
-                         hipStream_t s);
+                       int batch, int d0, int ld0, long rows, uint64_t seed, int64_t t, const int* order, int workers);
+hipError_t launch_gather(const GatherArgs& a, bool bf16, hipStream_t s);
 hipError_t launch_sample_indices(uint64_t seed, int n_workers, int batch, long rows, int64_t t_first,
                                  int n_steps, int32_t* out, hipStream_t s);
-// next != nullptr: the launch also gathers that minibatch (all workers, no step mask)
+// Of the n_workers workers order[0 .. n_workers) (nullptr: 0 .. n_workers).  next != nullptr: the launch also gathers that
+// minibatch, of as many workers at most
 hipError_t launch_softmax_xent(const float* logits, int n_parts, long part_stride, const float* bias,
                                long bias_gs, const int32_t* yb, void* delta, float* row_loss,
                                int n_workers, int batch, int n_classes, int ldc, bool bf16,
-                               const int* worker_steps, int step, const GatherArgs* next, hipStream_t s);
+                               const int* order, const GatherArgs* next, hipStream_t s);
 // Narrow head (at most 64 classes): logits product, softmax and delta in one launch; below != nullptr: and the delta of the
 // layer below, D_{L-1} [N][B][ld]
 struct HeadDelta { void* out; long gs; int ld, act; };
@@ -198,7 +198,7 @@ int softmax_narrow_blocks(int n_workers, int batch);         // workgroups of a 
 hipError_t launch_softmax_xent_narrow(const void* h, long h_gs, int ldh, int k_dim, const void* w,
                                       long w_gs, const float* bias, long bias_gs, const int32_t* yb,
                                       void* delta, float* row_loss, int n_workers, int batch, int n_classes,
-                                      int ldc, bool bf16, const int* worker_steps, int step, const GatherArgs* next,
+                                      int ldc, bool bf16, const int* order, const GatherArgs* next,
                                       const HeadDelta* below, hipStream_t s);
 hipError_t launch_loss_mean(const float* row_loss, float* losses, int n_workers, int batch,
                             hipStream_t s);
@@ -216,8 +216,10 @@ hipError_t launch_update(float* x, const float* g, uint16_t* shadow, size_t coun
 hipError_t launch_momentum_update(float* x, float* v, const float* g, uint16_t* shadow, size_t count,
                                   float lr, float mu, hipStream_t s);
 hipError_t launch_fill_zero(float* x, size_t count, hipStream_t s);
-hipError_t launch_update_masked(float* x, const float* g, uint16_t* shadow, long m_pad, int n_workers,
-                                float lr, const int* worker_steps, int step, hipStream_t s);
+hipError_t launch_update_workers(float* x, const float* g, uint16_t* shadow, long m_pad, const int* order,
+                                 int n_workers, float lr, hipStream_t s);
+hipError_t launch_store_ints(int* dst, const int* src_host, int count, hipStream_t s);
+hipError_t launch_store_order(int* dst, const int* steps_host, int count, hipStream_t s);
 
 // Least squares: k local iterations of every worker (kernels_lsq.hip).
 struct LsqArgs {
