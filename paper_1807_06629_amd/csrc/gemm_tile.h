@@ -355,8 +355,8 @@ template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
 // Four of these cover the latency of a workgroup that has its compute unit to itself (per iteration, 5 workers of
 // 640-1024-448-960-29, 18 rows: three 53.8 us, four 51.1, five or six 51.0; 6 of 1000-500-300-37, 100 rows: 36.2, 35.3, 35.6).
 constexpr int kFedStages = 3, kFedSmallStages = 4;
-hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s);
-hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s);
+hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s);
+hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s);
 
 // Launches KERNEL (WAVES wavefronts per workgroup) with one workgroup per tile of BM x BN.
 template <typename T, int BM, int BN, int WK, int S, int WAVES, void (*KERNEL)(GemmArgs)>

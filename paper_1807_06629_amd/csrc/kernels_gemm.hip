@@ -314,7 +314,6 @@ constexpr int kComputeUnits = 256;
 // 128 x 64 10.4).  Launched by itself in 32 x 64, 64 x 64, 128 x 64 and 128 x 128 tiles, the rule's in brackets: 8 x (128 x 4096) x 4096 with shared
 // weights 72.5, 53.2, 45.2, [34.4] us, backward-data 71.3, 55.1, 46.9, [34.3]; 6 x (128 x 896) x 3776 22.0, 14.8, 13.3, [11.7]; 8 x (95 x
 // 3456) x 3760 74.7, 57.8, 47.4, [33.0]; 64 x (128 x 1024) x 1024 43.5, 33.3, 30.9, [30.5]; 6 x (100 x 500) x 300 [4.4], 4.9, 6.6, 7.8.
-// 128 x 64 tiles run in the plain kernel only: they are taken for launches of many of them, where workgroups share a unit.
 // bf16 adds the contraction in one ascending chain in every tile: the first layer's backward kernel
 // computes the same product ahead and must give the same bits.
 // No tile is taller than the minibatch: half of a 128-row tile of 64 rows is copies of the last row, multiplied
@@ -351,13 +350,15 @@ constexpr int kRowStages = 3;
 // 193.4; 60 of it, 30 rows (480 of 32 x 64) 213.6 and 211.4.  At 512 it is one way with weights of every worker's own or a contraction
 // in ranges (the logits product of 8 of 4096-4096-4096-4096-1000, 128 rows, interval 1, 24.2 and 25.7 us, an iteration 522.1 and 524.6; 32 of
 // 1000-1000-1000-50, 32 and 64 rows, 195.6 and 196.4, 206.6 and 207.1) and the other way with shared ones (64 of 1024-512-512-512-40, 64 rows,
-// interval 1, 104.0 and 102.7).  64 of 1000-1000-1000-50, 32 rows (1024), 347.4 and 349.2.
+// interval 1, 104.0 and 102.7).  64 of 1000-1000-1000-50, 32 rows (1024), 347.4 and 349.2.  128 x 64 tiles, the launch alone, forward and
+// backward-data: 5 x (101 x 2688) x 4005 48.9 and 49.6 us, 5 x (101 x 2362) x 2688 26.7 and 24.4, 20.8 and 17.6; 6 x (128 x 2624) x 2880
+// 26.5 and 23.6; 10 x (128 x 832) x 1472 12.2 and 10.2; 10 x (128 x 1472) x 832 10.1 and 8.4; 13 x (128 x 640) x 708 9.2 and 8.3.
 constexpr long kFedTiles = 2 * kComputeUnits;
 static long rows_tiles(RowsTile t, int rows, int cols, int splits, int n_groups) {
   return (long)((rows + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1) * n_groups;
 }
 static bool rows_fed(RowsTile t, const GemmArgs& p, int n_groups) {
-  if (t.bn == 128 || t.bm > 64) return t.bn == 128;
+  if (t.bn == 128) return true;
   const long tiles = rows_tiles(t, p.M, p.N, p.k_splits, n_groups);
   return tiles < kFedTiles || (tiles == kFedTiles && p.b_gs == 0 && p.k_splits <= 1);
 }
@@ -366,7 +367,7 @@ template <int AKIND, int BKIND>
 static hipError_t launch_rows_bf16(const GemmArgs& p, int n_groups, hipStream_t s) {
   const RowsTile t = rows_tile(p, n_groups, true);
   if (rows_fed(t, p, n_groups))
-    return BKIND == OP_CONTIG ? launch_gemm_dx_fed(p, n_groups, t.bm, s) : launch_gemm_fwd_fed(p, n_groups, t.bm, s);
+    return BKIND == OP_CONTIG ? launch_gemm_dx_fed(p, n_groups, t.bm, t.bn, s) : launch_gemm_fwd_fed(p, n_groups, t.bm, t.bn, s);
   if (t.bm == 32) return launch_one<TBF16, 32, 64, 1, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
   if (t.bm == 64) return launch_one<TBF16, 64, 64, 2, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
   return launch_one<TBF16, 128, 64, 4, 2, 1, kRowStages, AKIND, BKIND>(p, n_groups, s);
@@ -390,7 +391,7 @@ void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows
   *lds_bytes = !bf16 ? (t.bm == 64 ? gemm_lds_bytes<TF32, 64, 64, 1, 4>() : gemm_lds_bytes<TF32, 32, 32, 4, kRowStages>())
                : t.bm == 32 ? (fed ? gemm_lds_bytes<TBF16, 32, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 32, 64, 1, kRowStages>())
                : t.bm == 64 ? (fed ? gemm_lds_bytes<TBF16, 64, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 64, 64, 1, kRowStages>())
-               : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, kFedStages>();
+               : t.bn == 64 ? (fed ? gemm_lds_bytes<TBF16, 128, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>()) : gemm_lds_bytes<TBF16, 128, 128, 1, kFedStages>();
 }
 
 // A logits product that leaves most compute units idle (few classes) cuts its contraction into

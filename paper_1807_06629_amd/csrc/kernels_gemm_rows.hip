@@ -159,19 +159,21 @@ __global__ __launch_bounds__(64 * (4 + CM * CN), 2) void grouped_rows_kernel(Gem
   gemm_rows_fed<BM, BN, CM, CN, S, AKIND, BKIND>(p, (int)blockIdx.x);
 }
 
-template <int AKIND, int BKIND> static hipError_t launch_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s) {
+template <int AKIND, int BKIND> static hipError_t launch_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s) {
   constexpr int S = kFedStages, T = kFedSmallStages;
   if (bm == 32)
     return launch_tiles<TBF16, 32, 64, 1, T, 6, grouped_rows_kernel<32, 64, 1, 2, T, AKIND, BKIND>>(p, n_groups, s);
   if (bm == 64)
     return launch_tiles<TBF16, 64, 64, 1, T, 8, grouped_rows_kernel<64, 64, 2, 2, T, AKIND, BKIND>>(p, n_groups, s);
+  if (bn == 64)
+    return launch_tiles<TBF16, 128, 64, 1, T, 8, grouped_rows_kernel<128, 64, 2, 2, T, AKIND, BKIND>>(p, n_groups, s);
   return launch_tiles<TBF16, 128, 128, 1, S, 8, grouped_rows_kernel<128, 128, 2, 2, S, AKIND, BKIND>>(p, n_groups, s);
 }
-hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s) {
-  return launch_fed<OP_CONTIG, OP_TRANS>(p, n_groups, bm, s);
+hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s) {
+  return launch_fed<OP_CONTIG, OP_TRANS>(p, n_groups, bm, bn, s);
 }
-hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, int bm, hipStream_t s) {
-  return launch_fed<OP_CONTIG, OP_CONTIG>(p, n_groups, bm, s);
+hipError_t launch_gemm_dx_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s) {
+  return launch_fed<OP_CONTIG, OP_CONTIG>(p, n_groups, bm, bn, s);
 }
 
 }  // namespace prsgd

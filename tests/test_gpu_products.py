@@ -107,3 +107,22 @@ def test_many_small_tiles(dims, batch, n_workers):
     assert rel_err(D.read_all(h), want["x"]) <= 1e-4
     assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-3, atol=1e-6)
     P.prsgd_destroy(h)
+
+
+# 128 x 64 tiles with requesting wavefronts: contractions of one to five tiles of 64, whole and ragged, rows and columns past the last
+# whole tile
+@pytest.mark.parametrize("hidden", [8, 64, 65, 128, 190, 300])
+def test_contractions_of_tall_narrow_tiles(hidden):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    dims, batch, n_workers = (40, hidden, 456, hidden, 12), 100, 20
+    assert P.prsgd_product_tile(batch, 456, n_workers, "bf16")[:2] == (128, 64)
+    w = small_mlp(dims=dims, batch=batch, n_workers=n_workers, gemm_dtype="bf16", activation="tanh", rows_per_worker=256,
+                  iterations=1)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_local_steps(h, 1)
+    want = oracle_run(w, inp, iterations=1)
+    assert rel_err(D.read_all(h), want["x"]) <= 1e-4
+    assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-3, atol=1e-6)
+    P.prsgd_destroy(h)
