@@ -29,7 +29,9 @@
 //
 // Every output block accumulates over k in the order of the stand-alone forward product, and the bias
 // is summed as in the other layers' kernel, so H_1^{t+1} and the parameters have the bits the two
-// separate launches give.  Whole tiles only (B = 32 MB, d_0 a multiple of 128, d_1 of 64).
+// separate launches give.  Whole tiles (B = 32 MB, d_0 a multiple of 128, d_1 of 64), and from 512 rows of W_1 on any minibatch and
+// any rows with columns that the layout pads to whole tiles: 5 workers of 4005-2688-100, 64 rows, 177 -> 104 us per iteration, 12 of
+// 3001-1472-333-20 208 -> 146; with momentum 282 -> 180 and 321 -> 258.
 #include <atomic>
 #include <type_traits>
 
@@ -65,7 +67,10 @@ constexpr size_t first_lds_bytes(int mb, int nb) {
 // traffic.  MOM: momentum form of the local update, v <- mu v + G, x <- x - gamma v, with the velocity
 // tile streamed beside the weights.  The bf16 shadow of W_1 is left as it is: only the stand-alone forward
 // product reads it, and the caller refreshes it when the chain of activations from here breaks.
-template <int MB, int NB, bool NT, bool MOM>
+// RAG: any number of rows of W_1 (p.Nn: its columns with the padding, whole bands) and of the minibatch.  Weights are read and written
+// with range-checked accesses, so that a row past the last one reads as zeros and is written nowhere, and every phase issues as
+// many accesses as the waits count.
+template <int MB, int NB, bool NT, bool MOM, bool RAG>
 __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdArgs p) {
   fetch_kernel_args<sizeof(BwdArgs)>();
   constexpr int BR = 32 * MB;
@@ -115,9 +120,25 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
   const float* const wsrc_g = p.src + (size_t)g * p.src_gs + w_first;
   float* const v_g = MOM ? p.vel + (size_t)g * p.p_gs + w_first : nullptr;
   const size_t row8 = (size_t)8 * p.ldw;
-  auto fetch = [&](f32x4_t (&reg)[4], const float* base, int it, bool stream) __attribute__((always_inline)) {
+  constexpr int kStream = NT ? 2 : 0;                 // buffer access cache policy: the nt bit
+  const uint32_t lane_first = 4u * ((uint32_t)(wk * 32 + trow) * (uint32_t)p.ldw + (uint32_t)(n0 + wn * 32 + tcol));
+  auto rsrc = [&](const float* base, size_t first) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + first), 0, (int)((uint32_t)p.K * (uint32_t)p.ldw * 4u), 0x00020000);
+  };
+  auto at = [&](int it, int q) __attribute__((always_inline)) {
+    return (int)(lane_first + 4u * (uint32_t)(it * BT + 8 * q) * (uint32_t)p.ldw);
+  };
+  const __amdgpu_buffer_rsrc_t w_src = rsrc(p.src, (size_t)g * p.src_gs + p.w_off);
+  const __amdgpu_buffer_rsrc_t w_dst = rsrc(p.params, (size_t)g * p.p_gs + p.w_off);
+  const __amdgpu_buffer_rsrc_t v_all = rsrc(MOM ? p.vel : p.params, (size_t)g * p.p_gs + p.w_off);
+  auto fetch = [&](f32x4_t (&reg)[4], const float* base, const __amdgpu_buffer_rsrc_t& all, int it, bool stream) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+      if constexpr (RAG) {
+        reg[q] = __builtin_bit_cast(f32x4_t, stream ? __builtin_amdgcn_raw_buffer_load_b128(all, at(it, q), 0, 2)
+                                                    : __builtin_amdgcn_raw_buffer_load_b128(all, at(it, q), 0, 0));
+        continue;
+      }
       const f32x4_t* src = reinterpret_cast<const f32x4_t*>(base + (size_t)it * BT * p.ldw + q * row8);
       reg[q] = stream ? __builtin_nontemporal_load(src) : *src;
     }
@@ -125,14 +146,22 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
 
   // requests of an X tile: this lane's chunk of piece q * NW + wave (8 rows of 128 bytes)
   uint32_t h_off[REQ], x_off[REQ];
+  auto offsets = [&](uint32_t (&h_o)[REQ], uint32_t (&x_o)[REQ], int cols) __attribute__((always_inline)) {
 #pragma unroll
-  for (int q = 0; q < REQ; ++q) {
-    const int r = (q * NW + wave) * 8 + (lane >> 3), pos = lane & 7;
-    const int row = r < BR ? r : BR - 1;
-    h_off[q] = (uint32_t)(((size_t)row * p.ldh + ((((pos >> 2) ^ lds_seg_xor<128>(r)) << 2) | (pos & 3)) * 8) * 2);
-    x_off[q] = (uint32_t)(((size_t)row * p.ldx + (lds_chunk(r, pos) * 8)) * 2);
-  }
+    for (int q = 0; q < REQ; ++q) {
+      const int r = (q * NW + wave) * 8 + (lane >> 3), pos = lane & 7;
+      const int row = RAG ? min(r, p.B - 1) : r < BR ? r : BR - 1;
+      int hc = ((((pos >> 2) ^ lds_seg_xor<128>(r)) << 2) | (pos & 3)) * 8, xc = lds_chunk(r, pos) * 8;
+      if (RAG) { hc = min(hc, (cols - 1) & ~7); xc = min(xc, (cols - 1) & ~7); }
+      h_o[q] = (uint32_t)(((size_t)row * p.ldh + hc) * 2);
+      x_o[q] = (uint32_t)(((size_t)row * p.ldx + xc) * 2);
+    }
+  };
+  offsets(h_off, x_off, BT);
+  const int n_t = RAG ? (p.K + BT - 1) / BT : p.K / BT;          // steps of the walk down the rows (at least 4)
+  const int tail = RAG ? p.K - (n_t - 1) * BT : BT;              // rows of the last one
   auto request_x = [&](int it, int hbuf, int xbuf) __attribute__((always_inline)) {
+    if (RAG && it == n_t - 1 && tail < BT) offsets(h_off, x_off, tail);        // copies of the last columns past them
 #pragma unroll
     for (int q = 0; q < REQ; ++q) {
       if ((q * NW + wave) * 1024 < XT) {                                 // uniform over the wavefront
@@ -142,13 +171,12 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
     }
   };
 
-  const int n_t = p.K / BT;                           // steps of the walk down the rows (at least 4)
   f32x4_t wr[3][4];
   f32x4_t vr[MOM ? 3 : 1][4];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    fetch(wr[j], wsrc_g, j, nt_read);
-    if (MOM) fetch(vr[j], v_g, j, NT);
+    fetch(wr[j], wsrc_g, w_src, j, nt_read);
+    if (MOM) fetch(vr[j], v_g, v_all, j, NT);
   }
 
   // the D_1 band: through LDS for the column sums and into fragments
@@ -156,7 +184,7 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
     const int b = e / (NB / 8), c = e % (NB / 8);
     *reinterpret_cast<u32x4_t*>(reinterpret_cast<unsigned char*>(Dn) + b * (NB * 2) +
                                 ((((c >> 2) ^ lds_seg_xor<NB * 2>(b)) << 6) | ((c & 3) << 4))) =
-        *reinterpret_cast<const u32x4_t*>(d_g + (size_t)b * p.ldd + n0 + 8 * c);
+        RAG && b >= p.B ? (u32x4_t){0u, 0u, 0u, 0u} : *reinterpret_cast<const u32x4_t*>(d_g + (size_t)b * p.ldd + n0 + 8 * c);
   }
   __syncthreads();
   bf16x8_t df[BR / 16];
@@ -195,16 +223,26 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
   float* const T = Tl + wave * 32 * ST;
 
   // next pre-activation [b][n] += X^{t+1}[:, k-tile] bf16(W_new tile): contraction over the tile's rows
-  auto next_product = [&](int wbuf, int xbuf) __attribute__((always_inline)) {
+  // (past `rows` of them zeros; the new weights of such rows are zeros as well)
+  auto next_product = [&](int wbuf, int xbuf, int rows) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < NZ; ++t) {
       const int blk = wave + NW * t;
       if (NBLK % NW == 0 || blk < NBLK) {
         const int mb = blk / (NB / 32), nblk = blk % (NB / 32);
 #pragma unroll
-        for (int kk = 0; kk < BT / 16; ++kk)
-          acc_z[t] = mfma_bf16(lds_frag_contig(Xk + xbuf * XT, mb, kk, lane), lds_frag_trans<NB * 2>(Wl + wbuf * WT, nblk, kk, lane),
-                               acc_z[t]);
+        for (int kk = 0; kk < BT / 16; ++kk) {
+          bf16x8_t xf = lds_frag_contig(Xk + xbuf * XT, mb, kk, lane);
+          if (RAG && rows < BT) {
+            u32x4_t u = __builtin_bit_cast(u32x4_t, xf);
+            const int c = 16 * kk + 8 * kb;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              u[e] &= (c + 2 * e < rows ? 0xFFFFu : 0u) | (c + 2 * e + 1 < rows ? 0xFFFF0000u : 0u);
+            xf = __builtin_bit_cast(bf16x8_t, u);
+          }
+          acc_z[t] = mfma_bf16(xf, lds_frag_trans<NB * 2>(Wl + wbuf * WT, nblk, kk, lane), acc_z[t]);
+        }
       }
     }
   };
@@ -219,15 +257,15 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
     const int xprev = xbuf == 0 ? 2 : xbuf - 1, xnext = xbuf == 2 ? 0 : xbuf + 1;
     request_x(min(it + 1, n_t - 1), hbuf ^ 1, xnext);
     const int ahead = min(it + 2, n_t - 1);
-    fetch(wr[AHEAD], wsrc_g, ahead, nt_read);
-    if (MOM) fetch(vr[AHEAD], v_g, ahead, NT);
+    fetch(wr[AHEAD], wsrc_g, w_src, ahead, nt_read);
+    if (MOM) fetch(vr[AHEAD], v_g, v_all, ahead, NT);
     // gradient block: contraction over the minibatch
     f32x16_t acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
 #pragma unroll
     for (int kk = 0; kk < BR / 16; ++kk) acc = mfma_bf16(lds_frag_trans<128>(Hk + hbuf * XT, wk, kk, lane), df[kk], acc);
-    if (!FIRST) next_product(hbuf ^ 1, xprev);
+    if (!FIRST) next_product(hbuf ^ 1, xprev, BT);
     // accumulator element v of lane (lr32, kb) is C[8 (v/4) + 4 kb + v%4][lr32]
 #pragma unroll
     for (int v = 0; v < 16; ++v) T[(8 * (v / 4) + 4 * kb + (v % 4)) * ST + lr32] = acc[v];
@@ -245,7 +283,8 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
         gr.y = fmaf(p.mu, vr[SLOT][q].y, gr.y);
         gr.z = fmaf(p.mu, vr[SLOT][q].z, gr.z);
         gr.w = fmaf(p.mu, vr[SLOT][q].w, gr.w);
-        if (NT) __builtin_nontemporal_store(gr, reinterpret_cast<f32x4_t*>(v_g + off));
+        if (RAG) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, gr), v_all, at(it, q), 0, kStream);
+        else if (NT) __builtin_nontemporal_store(gr, reinterpret_cast<f32x4_t*>(v_g + off));
         else *reinterpret_cast<f32x4_t*>(v_g + off) = gr;
       }
       f32x4_t w = wr[SLOT][q];
@@ -253,9 +292,12 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
       w.y = fmaf(-p.lr, gr.y, w.y);
       w.z = fmaf(-p.lr, gr.z, w.z);
       w.w = fmaf(-p.lr, gr.w, w.w);
-      const u32x2_t hv2 = {f32x2_to_bf16x2_rne(w.x, w.y),
-                           f32x2_to_bf16x2_rne(w.z, w.w)};
-      if (NT) {
+      u32x2_t hv2 = {f32x2_to_bf16x2_rne(w.x, w.y),
+                     f32x2_to_bf16x2_rne(w.z, w.w)};
+      if (RAG) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, w), w_dst, at(it, q), 0, kStream);
+        if (it * BT + wk * 32 + 8 * q + trow >= p.K) hv2 = (u32x2_t){0u, 0u};
+      } else if (NT) {
         __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(w_g + off));
       } else {
         *reinterpret_cast<f32x4_t*>(w_g + off) = w;
@@ -283,7 +325,7 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
     phase(it, set0, std::false_type{});
     if (++it == n_t) break;
   }
-  next_product(hbuf ^ 1, xbuf == 0 ? 2 : xbuf - 1);   // the last tile's share
+  next_product(hbuf ^ 1, xbuf == 0 ? 2 : xbuf - 1, tail);        // the last tile's share
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no request into LDS outlives the workgroup
 
   // ---- H_1^{t+1} = phi(Z + b_1) for this band ------------------------------------------------------
@@ -298,17 +340,17 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int b = mb * 32 + 8 * (v / 4) + 4 * kb + (v % 4);
-        hn_g[(size_t)b * p.ldhn + n0 + n] = f32_to_bf16_rne(act_from_z(acc_z[t][v] + bn, p.act));
+        if (!RAG || b < p.B) hn_g[(size_t)b * p.ldhn + n0 + n] = f32_to_bf16_rne(act_from_z(acc_z[t][v] + bn, p.act));
       }
     }
   }
 }
 
-template <int MB, int NB, bool NT, bool MOM>
+template <int MB, int NB, bool NT, bool MOM, bool RAG>
 hipError_t launch_first_one(const BwdArgs& p, hipStream_t s) {
   constexpr size_t kLds = first_lds_bytes(MB, NB);
   static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
-  auto kernel = bwd_first_fwd_kernel<MB, NB, NT, MOM>;
+  auto kernel = bwd_first_fwd_kernel<MB, NB, NT, MOM, RAG>;
   static std::atomic<bool> configured{false};
   if (!configured.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -320,20 +362,25 @@ hipError_t launch_first_one(const BwdArgs& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int MB, int NB, bool NT>
+template <int MB, int NB, bool NT, bool RAG>
 hipError_t launch_first_nt(const BwdArgs& p, hipStream_t s) {
   if constexpr (NB == 64) {
-    if (p.vel != nullptr) return launch_first_one<MB, NB, NT, true>(p, s);
+    if (p.vel != nullptr) return launch_first_one<MB, NB, NT, true, RAG>(p, s);
   }
-  return launch_first_one<MB, NB, NT, false>(p, s);
+  return launch_first_one<MB, NB, NT, false, RAG>(p, s);
 }
 
 // 128-column bands where they still give every compute unit a workgroup; not with momentum, whose second
 // stream of tiles does not fit the registers of eight wavefronts.
-template <int MB> hipError_t launch_first_mb(const BwdArgs& p, hipStream_t s) {
+template <int MB, bool RAG> hipError_t launch_first_mb(const BwdArgs& p, hipStream_t s) {
   const bool wide = p.vel == nullptr && (p.Nn % 128) == 0 && (long)(p.Nn / 128) * p.n_groups >= 256;
-  if (wide) return p.streaming ? launch_first_nt<MB, 128, true>(p, s) : launch_first_nt<MB, 128, false>(p, s);
-  return p.streaming ? launch_first_nt<MB, 64, true>(p, s) : launch_first_nt<MB, 64, false>(p, s);
+  if (wide) return p.streaming ? launch_first_nt<MB, 128, true, RAG>(p, s) : launch_first_nt<MB, 128, false, RAG>(p, s);
+  return p.streaming ? launch_first_nt<MB, 64, true, RAG>(p, s) : launch_first_nt<MB, 64, false, RAG>(p, s);
+}
+template <bool RAG> hipError_t launch_first_rag(const BwdArgs& p, hipStream_t s) {
+  if (p.B <= 32) return launch_first_mb<1, RAG>(p, s);
+  if (p.B <= 64) return launch_first_mb<2, RAG>(p, s);
+  return launch_first_mb<4, RAG>(p, s);
 }
 
 }  // namespace
@@ -352,16 +399,38 @@ bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
 // 2560 x 1024 [16] +21, [96] +7.9, [128] -1.6; 1280 x 1024 [16] +4.1, [128] -1.9.  (4 workers of 2560-256-40, 64 rows: 41.8 and 27.7 us.)
 // With momentum 128 rows, 2048 x 1024 [64] +12.8, [80] -0.2, [96] -3.6.  Up to eight row tiles there is next to nothing in it.  An odd
 // number of column tiles apart is the general backward kernel's (3 workers of 1408-1216-303, 128 rows: 45.4 us, 55 apart).
-static bool bwd_first_fwd_pays(const BwdArgs& p) {
-  const int rows = p.K / BT, cols = p.Nn / BT;
-  if (rows <= 8 || (cols & 1) != 0) return true;
-  if (cols * p.n_groups >= (p.B <= 64 ? 80 : p.vel != nullptr ? 96 : 128)) return true;
+// Ragged layers apart are products that spread over the chip however few the bands (kernels_bwd.hip), or with momentum the general
+// backward kernel.  32 rows: 2001 x 1100 [54] +7.3, [90] -3.5, 700 x 1300 [105] +0.2, [168] -5.6; 64 rows: 2001 x 1100 [90] +0.9, [144] -9.3,
+// 3001 x 1472 [115] -9.0, 1000 x 555 [108] +4.2; 128 rows: 2001 x 1100 [144] +1.6, [216] -23.2, 4005 x 2688 [126] +15.9, [210] -84 (208
+// apart).  With momentum 64 rows: 700 x 1300 [21] -20, 2001 x 600 [50] +9.3, [120] -6.7, 4005 x 2688 [42] -8.3, [210] -103.
+// With momentum and more than the last-level cache holds, half of the compute units do not draw what memory gives: 4005 x 600 [120]
+// +40 us, 4096 x 1024 [128] +7, but 3001 x 1472 [115] -30.
+static bool bwd_first_fwd_pays(const BwdArgs& p, bool ragged) {
+  const int rows = (p.K + BT - 1) / BT, cols = p.Nn / BT;
+  const long bands = (long)cols * p.n_groups;
+  if (ragged && p.vel == nullptr) return bands >= (p.B <= 32 ? 96 : p.B <= 64 ? 112 : 152);
+  if (p.vel != nullptr && bands < 192 && (double)p.n_groups * p.K * p.ldw * 8.0 > 220e6) return false;
+  if (!ragged && (rows <= 8 || (cols & 1) != 0)) return true;
+  if (bands >= (p.B <= 64 ? 80 : p.vel != nullptr ? 96 : 128)) return true;
   return p.B <= 64 ? 5 * rows <= 8 * cols + 20 : 20 * rows <= 17 * cols + 60;
 }
 
-// Whole tiles, and the buffers of the next iteration given.
-bool bwd_first_fwd_applies(const BwdArgs& p) {
-  if (!bwd_first_fwd_shape(p.B, p.K, p.Nn) || !bwd_first_fwd_pays(p)) return false;
+// The layer as the kernel walks it: over its padded columns where those are whole tiles (zeros, whose gradient is zero).
+static BwdArgs bwd_first_padded(const BwdArgs& p) {
+  BwdArgs q = p;
+  if ((p.Nn % BT) != 0 && (p.ldw % BT) == 0 && p.ldw - p.Nn < BT) q.Nn = p.ldw;
+  return q;
+}
+static bool bwd_first_ragged_shape(const BwdArgs& p) {
+  return p.B >= 1 && p.B <= 128 && p.K >= 512 && p.Nn >= BT && (p.Nn % BT) == 0 && p.ldd >= p.Nn && p.ldhn >= p.Nn &&
+         (size_t)(p.K + BT) * p.ldw * 4 < ((size_t)1 << 32);
+}
+
+// Whole tiles or such columns, and the buffers of the next iteration given.
+bool bwd_first_fwd_applies(const BwdArgs& p_in) {
+  const BwdArgs p = bwd_first_padded(p_in);
+  const bool whole = bwd_first_fwd_shape(p_in.B, p_in.K, p_in.Nn);
+  if ((!whole && !bwd_first_ragged_shape(p)) || !bwd_first_fwd_pays(p, !whole)) return false;
   if (p.dx != nullptr) return false;
   if (p.x_next == nullptr || p.h_next == nullptr) return false;
   return (p.ldw % 4) == 0 && (p.ldh % 8) == 0 && (p.ldx % 8) == 0 && (p.ldd % 8) == 0 && (p.w_off % 4) == 0;
@@ -369,9 +438,8 @@ bool bwd_first_fwd_applies(const BwdArgs& p) {
 
 hipError_t launch_bwd_first_fwd(const BwdArgs& p, hipStream_t s) {
   if (!bwd_first_fwd_applies(p) || p.n_groups <= 0) return hipErrorInvalidValue;
-  if (p.B == 32) return launch_first_mb<1>(p, s);
-  if (p.B == 64) return launch_first_mb<2>(p, s);
-  return launch_first_mb<4>(p, s);
+  const BwdArgs q = bwd_first_padded(p);
+  return bwd_first_fwd_shape(q.B, q.K, q.Nn) ? launch_first_rag<false>(q, s) : launch_first_rag<true>(q, s);
 }
 
 }  // namespace prsgd
