@@ -351,7 +351,7 @@ template <typename T, int BM, int BN, int NTHR, bool DX> struct RowsEpilogue {
   }
 };
 
-// Products whose workgroups have requesting wavefronts (kernels_gemm_rows.hip), and their tiles in flight: 128 x 128, the smaller ones.
+// Products whose workgroups have requesting wavefronts (kernels_gemm_rows.hip), and their tiles in flight: 128-row tiles, the smaller ones.
 // Four of these cover the latency of a workgroup that has its compute unit to itself (per iteration, 5 workers of
 // 640-1024-448-960-29, 18 rows: three 53.8 us, four 51.1, five or six 51.0; 6 of 1000-500-300-37, 100 rows: 36.2, 35.3, 35.6).
 constexpr int kFedStages = 3, kFedSmallStages = 4;

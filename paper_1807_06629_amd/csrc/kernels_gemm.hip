@@ -341,6 +341,7 @@ static RowsTile rows_tile(const GemmArgs& p, int n_groups, bool bf16) {
 // and 15.8 us, 128 x (8 x 64) x 1024 25.3 and 10.6 us; 64 x (64 x 1024) x 256 in 64 x 64 tiles 24.2 and 13.9 us.  Two lose where a compute
 // unit has one workgroup (4 x (8 x 4096) x 1024 three 20.6, two 32.1 us), which is where the requesting kernel stands now (11.4).
 constexpr int kRowStages = 3;
+static_assert(kRowStages == kFedStages, "128 x 64 tiles of either kernel");
 
 // Workgroups with requesting wavefronts (kernels_gemm_rows.hip) take the 128 x 128 tiles, and launches of fewer than two smaller tiles per
 // compute unit: from then on several workgroups of the plain kernel share a unit and hide each other's requests (its 48 KB of LDS
@@ -391,7 +392,7 @@ void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows
   *lds_bytes = !bf16 ? (t.bm == 64 ? gemm_lds_bytes<TF32, 64, 64, 1, 4>() : gemm_lds_bytes<TF32, 32, 32, 4, kRowStages>())
                : t.bm == 32 ? (fed ? gemm_lds_bytes<TBF16, 32, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 32, 64, 1, kRowStages>())
                : t.bm == 64 ? (fed ? gemm_lds_bytes<TBF16, 64, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 64, 64, 1, kRowStages>())
-               : t.bn == 64 ? (fed ? gemm_lds_bytes<TBF16, 128, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>()) : gemm_lds_bytes<TBF16, 128, 128, 1, kFedStages>();
+               : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, kFedStages>();
 }
 
 // A logits product that leaves most compute units idle (few classes) cuts its contraction into

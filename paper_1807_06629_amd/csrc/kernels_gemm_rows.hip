@@ -166,7 +166,7 @@ template <int AKIND, int BKIND> static hipError_t launch_fed(const GemmArgs& p, 
   if (bm == 64)
     return launch_tiles<TBF16, 64, 64, 1, T, 8, grouped_rows_kernel<64, 64, 2, 2, T, AKIND, BKIND>>(p, n_groups, s);
   if (bn == 64)
-    return launch_tiles<TBF16, 128, 64, 1, T, 8, grouped_rows_kernel<128, 64, 2, 2, T, AKIND, BKIND>>(p, n_groups, s);
+    return launch_tiles<TBF16, 128, 64, 1, S, 8, grouped_rows_kernel<128, 64, 2, 2, S, AKIND, BKIND>>(p, n_groups, s);
   return launch_tiles<TBF16, 128, 128, 1, S, 8, grouped_rows_kernel<128, 128, 2, 2, S, AKIND, BKIND>>(p, n_groups, s);
 }
 hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s) {
