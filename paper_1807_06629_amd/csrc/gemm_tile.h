@@ -232,7 +232,7 @@ template <int BM, int BN> __device__ __forceinline__ TileAt tile_at(const GemmAr
     tn = t.order == 1 ? u : v;
     r.g = t.order == 1 ? v : q;
   }
-  if (p.order != nullptr) r.g = p.order[r.g];
+  r.g = worker_of(p.order, r.g);
   r.m0 = tm * BM;
   r.n0 = tn * BN;
   return r;

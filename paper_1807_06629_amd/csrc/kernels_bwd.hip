@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kThreads) void grouped_bwd_kernel(BwdArgs p) {
     g = blockIdx.x / tiles;
     tile = blockIdx.x % tiles;
   }
-  if (p.order != nullptr) g = p.order[g];
+  g = worker_of(p.order, g);
   const int k0 = tile * BMK;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kThreads) void grouped_bwd_full_kernel(BwdArgs p) {
     g = blockIdx.x / tiles;
     tile = blockIdx.x % tiles;
   }
-  if (p.order != nullptr) g = p.order[g];
+  g = worker_of(p.order, g);
   const int k0 = tile * KB;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];

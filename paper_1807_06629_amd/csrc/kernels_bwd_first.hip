@@ -91,7 +91,7 @@ __global__ __launch_bounds__(4 * NB, MOM ? 1 : 2) void bwd_first_fwd_kernel(BwdA
     g = blockIdx.x / bands;
     band = blockIdx.x % bands;
   }
-  if (p.order != nullptr) g = p.order[g];
+  g = worker_of(p.order, g);
   const int n0 = band * NB;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];

@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kThreads) void update_workers_kernel(float4* __rest
                                                                   uint2* __restrict__ shadow,
                                                                   size_t stride4, float lr,
                                                                   const int* __restrict__ order) {
-  const int i = order[blockIdx.y];
+  const int i = worker_of(order, blockIdx.y);
   for (size_t col = (size_t)blockIdx.x * kThreads + threadIdx.x; col < stride4;
        col += (size_t)gridDim.x * kThreads) {
     const size_t k = (size_t)i * stride4 + col;

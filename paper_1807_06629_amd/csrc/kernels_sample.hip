@@ -78,7 +78,7 @@ __device__ __forceinline__ void gather_row(const GatherArgs& a, int j, int i) {
 template <bool BF16>
 __device__ __forceinline__ void gather_group(const GatherArgs& a, int j, int i) {
   if (i >= a.workers) return;
-  gather_row<BF16>(a, j, a.order != nullptr ? a.order[i] : i);
+  gather_row<BF16>(a, j, worker_of(a.order, i));
 }
 
 template <bool BF16>
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     gather_group<BF16>(next, (int)blockIdx.x - head_blocks, g);
     return;
   }
-  if (order != nullptr) g = order[g];
+  g = worker_of(order, g);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.x * (kThreads / kWave) + wave;
   if (b >= batch) return;
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_row_kernel(
     gather_group<BF16>(next, (int)blockIdx.x - head_blocks, g);
     return;
   }
-  if (order != nullptr) g = order[g];
+  g = worker_of(order, g);
   __shared__ float red[3][kThreads / kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const size_t r = (size_t)g * batch + blockIdx.x;
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_narrow_kernel(
     gather_group<BF16>(next, (int)blockIdx.x - head_blocks, g);
     return;
   }
-  if (order != nullptr) g = order[g];
+  g = worker_of(order, g);
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
   constexpr int NW = kThreads / kWave;

@@ -251,6 +251,11 @@ template <size_t BYTES> __device__ __forceinline__ void fetch_kernel_args() {
   const auto* w = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" :: "s"(w[0]), "s"(w[L < 16 ? L : 16]), "s"(w[L < 32 ? L : 32]), "s"(w[L < 48 ? L : 48]), "s"(w[L]));
 }
+// Worker of group g (Algorithm 3: order[g]), by a scalar load.  As a vector load it put the worker and every address behind it into vector
+// registers, also where order is null: 6 workers of 3456-704-665-384-67, 128 rows, first layer 58 -> 66 us.
+__device__ __forceinline__ int worker_of(const int* order, int g) {
+  return order == nullptr ? g : ((const __attribute__((address_space(4))) int*)order)[g];
+}
 // Round to nearest even on the conversion instruction (two values per v_cvt_pk_bf16_f32; a NaN stays a
 // NaN, infinities and denormals are kept).  Written out in integer operations, with the NaN case apart,
 // the compiler made a divergent branch of every element: 11 instructions each, 176 of the 390 of one
