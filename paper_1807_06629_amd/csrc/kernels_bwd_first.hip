@@ -385,10 +385,11 @@ template <bool RAG> hipError_t launch_first_rag(const BwdArgs& p, hipStream_t s)
 
 }  // namespace
 
-// Layer shapes made of whole tiles.
+// Layer shapes made of whole tiles, whose two forms have the same bits.  An odd number of column tiles is nothing that the other layers'
+// whole-tile kernel takes: such a layer counts as ragged, unless it is so short that it is fused in any case.
 bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
   return (batch == 32 || batch == 64 || batch == 128) && d_in >= 4 * BT && (d_in % (2 * BT)) == 0 &&
-         d_out >= BT && (d_out % BT) == 0;
+         d_out >= BT && (d_out % BT) == 0 && (d_in <= 8 * BT || (d_out / BT) % 2 == 0);
 }
 
 // A band walks its d_0 / 64 row tiles one after the other, at 0.8 us each behind the two launches that it replaces (0.4 us more than
@@ -397,8 +398,7 @@ bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
 // Per iteration, fused less apart, bands in brackets: 64 rows, 2560 x 256 [8] +13 us, [64] +8.6; 4096 x 1024 [32] +19.1, [64] +4.6, [80]
 // -2.8, [128] -19.2; 2048 x 1024 [16] +3.2, [80] -3.1; 1536 x 1024 [16] -2.0; 768 x 2048 [32] -16; 512 x 256 [4] -1.4.  128 rows:
 // 2560 x 1024 [16] +21, [96] +7.9, [128] -1.6; 1280 x 1024 [16] +4.1, [128] -1.9.  (4 workers of 2560-256-40, 64 rows: 41.8 and 27.7 us.)
-// With momentum 128 rows, 2048 x 1024 [64] +12.8, [80] -0.2, [96] -3.6.  Up to eight row tiles there is next to nothing in it.  An odd
-// number of column tiles apart is the general backward kernel's (3 workers of 1408-1216-303, 128 rows: 45.4 us, 55 apart).
+// With momentum 128 rows, 2048 x 1024 [64] +12.8, [80] -0.2, [96] -3.6.  Up to eight row tiles there is next to nothing in it.
 // Ragged layers apart are products that spread over the chip however few the bands (kernels_bwd.hip), or with momentum the general
 // backward kernel.  32 rows: 2001 x 1100 [54] +7.3, [90] -3.5, 700 x 1300 [105] +0.2, [168] -5.6; 64 rows: 2001 x 1100 [90] +0.9, [144] -9.3,
 // 3001 x 1472 [115] -9.0, 1000 x 555 [108] +4.2; 128 rows: 2001 x 1100 [144] +1.6, [216] -23.2, 4005 x 2688 [126] +15.9, [210] -84 (208
@@ -410,7 +410,7 @@ static bool bwd_first_fwd_pays(const BwdArgs& p, bool ragged) {
   const long bands = (long)cols * p.n_groups;
   if (ragged && p.vel == nullptr) return bands >= (p.B <= 32 ? 96 : p.B <= 64 ? 112 : 152);
   if (p.vel != nullptr && bands < 192 && (double)p.n_groups * p.K * p.ldw * 8.0 > 220e6) return false;
-  if (!ragged && (rows <= 8 || (cols & 1) != 0)) return true;
+  if (!ragged && rows <= 8) return true;
   if (bands >= (p.B <= 64 ? 80 : p.vel != nullptr ? 96 : 128)) return true;
   return p.B <= 64 ? 5 * rows <= 8 * cols + 20 : 20 * rows <= 17 * cols + 60;
 }
