@@ -664,11 +664,22 @@ bool bwd_fused_supported(int batch) { return batch >= 1 && batch <= 128; }
 // are padded to whole column tiles are walked faster (16-byte accesses throughout): with up to 64 rows they are from 7
 // bands per 8 compute units on (500-600-600-10, per iteration, apart and not: 20 workers, 160 and 200 bands, 8 rows 52.9
 // and 59.4 us; 24 workers, 192 and 240 bands, 64.8 and 61.5 us; with 128 rows 84.4 and 86.6 us).
+// Layers of whole tiles are walked at 0.6 to 1.1 us per column tile (32 to 128 rows), which few and long bands do not repay either.  Per
+// iteration, walked and apart, 64-row bands of the second layer in brackets: 640-1152-1152-20, 32 rows, 3 workers [54] 45.7 and 44.2 us, 4 [72]
+// 45.7 and 46.1; 64 rows, 4 [72] 49.4 and 47.9, 6 [108] 50.7 and 51.9; 128 rows, 6 [108] 63.3 and 60.8, 8 [144] 71.1 and 76.0.  First
+// layers: 2560-1280-43, 64 rows, 2 workers [80] 41.1 and 34.9, 3 [120] 42.1 and 43.9; 128 rows, 4 [160] 57.6 and 53.8.  Short walks stay:
+// 1024-512-512-10, 32 rows, 1 worker 33.3 and 34.9 us.  (1 worker of 4096-2048-2048-512, 64 rows, 89.8 and 67.5.)
+static bool walk_too_long(const BwdArgs& p) {
+  const int n_t = p.Nn / BN, height = p.B <= 32 ? 0 : p.B <= 64 ? 1 : 2;
+  const long bands = (long)((p.K + BMK - 1) / BMK) * p.n_groups;
+  static constexpr int kTiles[3] = {14, 12, 8}, kBands[3] = {60, 80, 112}, kFirstBands[3] = {100, 110, 256};
+  return p.dx != nullptr ? n_t >= kTiles[height] && bands < kBands[height] : n_t >= 8 && bands < kFirstBands[height];
+}
 bool bwd_products_apart(const BwdArgs& p) {
   if (p.vel != nullptr) return false;
-  if (p.dx == nullptr && bwd_first_fwd_shape(p.B, p.K, p.Nn)) return false;   // same bits as that kernel
+  if (p.dx == nullptr && bwd_first_fwd_same_bits(p)) return false;
   const int mb = p.B <= 32 ? 1 : p.B <= 64 ? 2 : 4;
-  if (bwd_full_applies(p, mb, 2) || bwd_full_applies(p, mb, 2, 32)) return false;
+  if (bwd_full_applies(p, mb, 2) || bwd_full_applies(p, mb, 2, 32)) return walk_too_long(p);
   BwdArgs padded;
   if (bwd_padded_applies(p, mb, &padded)) return false;
   const bool padded_rows = (p.Nn % BN) != 0 && (p.ldw % BN) == 0;

@@ -387,7 +387,7 @@ template <bool RAG> hipError_t launch_first_rag(const BwdArgs& p, hipStream_t s)
 
 // Layer shapes made of whole tiles, whose two forms have the same bits.  An odd number of column tiles is nothing that the other layers'
 // whole-tile kernel takes: such a layer counts as ragged, unless it is so short that it is fused in any case.
-bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
+static bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
   return (batch == 32 || batch == 64 || batch == 128) && d_in >= 4 * BT && (d_in % (2 * BT)) == 0 &&
          d_out >= BT && (d_out % BT) == 0 && (d_in <= 8 * BT || (d_out / BT) % 2 == 0);
 }
@@ -425,6 +425,8 @@ static bool bwd_first_ragged_shape(const BwdArgs& p) {
   return p.B >= 1 && p.B <= 128 && p.K >= 512 && p.Nn >= BT && (p.Nn % BT) == 0 && p.ldd >= p.Nn && p.ldhn >= p.Nn &&
          (size_t)(p.K + BT) * p.ldw * 4 < ((size_t)1 << 32);
 }
+
+bool bwd_first_fwd_same_bits(const BwdArgs& p) { return bwd_first_fwd_shape(p.B, p.K, p.Nn) && bwd_first_fwd_pays(p, false); }
 
 // Whole tiles or such columns, and the buffers of the next iteration given.
 bool bwd_first_fwd_applies(const BwdArgs& p_in) {

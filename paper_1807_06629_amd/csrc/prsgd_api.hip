@@ -512,8 +512,19 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
     q.order = order;
     return q;
   };
+  // the first layer's pass that also runs the next forward product, for the workers that go on
+  const bool prefetch = active.next > 0;
+  auto first_args = [&]() {
+    BwdArgs q = bwd_args(1);
+    q.x_next = reinterpret_cast<const uint16_t*>(ctx->xb(bk ^ 1)); q.x_gs = (long)B * lo.ld[0]; q.ldx = lo.ld[0];
+    q.h_next = ctx->at<uint16_t>(cv.h[1]); q.hn_gs = (long)B * lo.ld[1]; q.ldhn = lo.ld[1];
+    q.order = active.next_order;
+    q.n_groups = active.next;
+    return q;
+  };
+  const bool first_fused = fused_bwd && !fuse_average && L >= 2 && ctx->first_fusion && prefetch && bwd_first_fwd_applies(first_args());
   int n_apart = 0, widest_apart = 0;
-  for (int l = L; fused_bwd && l >= 1; --l) {
+  for (int l = L; fused_bwd && l >= (first_fused ? 2 : 1); --l) {
     if (!bwd_products_apart(bwd_args(l))) continue;
     ++n_apart;
     if (lo.d[l] > widest_apart) widest_apart = lo.d[l];
@@ -528,7 +539,6 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
                           (fuse_average || !fused_bwd || (lo.d[L] > 16 && take_apart && bwd_products_apart(bwd_args(L))));
 
   // the loss-head launch also draws the minibatch of iteration t + 1 into the other buffer set
-  const bool prefetch = active.next > 0;
   GatherArgs next_batch = batch_args(bk ^ 1, t + 1, active.next_order, active.next);
   if (prefetch) ctx->batch_t[bk ^ 1] = -1;
   HeadDelta below;
@@ -614,27 +624,21 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
   // gradient, eq. (3) and the delta of the layer below in a single pass over W_l.
   bool first_shadow_left = false;
   for (int l = L; fused_bwd && l >= 1; --l) {
-    BwdArgs q = bwd_args(l);
-    if (l == 1 && L >= 2 && ctx->first_fusion && prefetch && ctx->batch_t[bk ^ 1] == t + 1) {
-      q.x_next = reinterpret_cast<const uint16_t*>(ctx->xb(bk ^ 1)); q.x_gs = (long)B * lo.ld[0]; q.ldx = lo.ld[0];
-      q.h_next = ctx->at<uint16_t>(cv.h[1]); q.hn_gs = (long)B * lo.ld[1]; q.ldhn = lo.ld[1];
-      q.order = active.next_order;
-      q.n_groups = active.next;
-      if (bwd_first_fwd_applies(q)) {
-        const int rc = dw.flush();          // H_1 is rewritten: layer 2's weight gradient still reads it
-        if (rc != PRSGD_OK) return rc;
-        LAUNCH(ctx, KK_BWD_FIRST, launch_bwd_first_fwd(q, s));
-        ctx->shadow1_stale = first_shadow_left = true;   // not written: it has no reader while H_1 comes from here
-        ctx->h1_t = t + 1;
-        ctx->h1_batch = bk ^ 1;
-        if (N == active.next) continue;
-        q.order = active.next_order + active.next;       // the workers that are done
-        q.n_groups = N - active.next;
-        LAUNCH(ctx, KK_BWD, launch_bwd_fused(q, s));
-        continue;
-      }
-      q = bwd_args(l);
+    if (l == 1 && first_fused) {
+      const int rc = dw.flush();            // H_1 is rewritten: layer 2's weight gradient still reads it
+      if (rc != PRSGD_OK) return rc;
+      LAUNCH(ctx, KK_BWD_FIRST, launch_bwd_first_fwd(first_args(), s));
+      ctx->shadow1_stale = first_shadow_left = true;     // not written: it has no reader while H_1 comes from here
+      ctx->h1_t = t + 1;
+      ctx->h1_batch = bk ^ 1;
+      if (N == active.next) continue;
+      BwdArgs q = bwd_args(1);
+      q.order = active.next_order + active.next;         // the workers that are done
+      q.n_groups = N - active.next;
+      LAUNCH(ctx, KK_BWD, launch_bwd_fused(q, s));
+      continue;
     }
+    const BwdArgs q = bwd_args(l);
     if (take_apart && bwd_products_apart(q)) {
       if (l > 1 && !(l == L && head_delta)) LAUNCH(ctx, KK_BWD, launch_gemm_dx(dx_args(l), N, true, s));
       GemmArgs p = dw_args(l);

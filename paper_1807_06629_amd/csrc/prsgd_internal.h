@@ -109,7 +109,7 @@ bool bwd_products_apart(const BwdArgs& p);
 bool bwd_apart_pays(int n_layers, int widest, int batch);
 hipError_t launch_bwd_fused(const BwdArgs& p, hipStream_t s);
 // Layer 1: backward step fused with the next iteration's forward product of that layer.
-bool bwd_first_fwd_shape(int batch, int d_in, int d_out);
+bool bwd_first_fwd_same_bits(const BwdArgs& p);     // layers that it takes with the bits of the walk over the weights
 bool bwd_first_fwd_applies(const BwdArgs& p);
 hipError_t launch_bwd_first_fwd(const BwdArgs& p, hipStream_t s);
 

@@ -1,0 +1,44 @@
+"""Layers of whole tiles whose walk over the weights few workers do not repay: products of their own, around the lines of that rule.
+
+Bounds: 1e-4 after one step (tests/test_gpu_products.py), 5e-3 and 2e-2 of the other short bf16 runs behind it.
+"""
+import numpy as np
+import pytest
+import torch
+
+from helpers import inputs_for, oracle_run, rel_err, small_mlp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dims,batch,n", [
+    ((128, 256, 896, 10), 32, 2),                    # 14 column tiles: the second layer apart (its bands: 8)
+    ((128, 256, 832, 10), 32, 2),                 # 13: walked
+    ((128, 768, 768, 10), 64, 6),                 # 72 bands of the second layer: apart
+    ((128, 768, 768, 10), 64, 7),                 # 84: walked
+    ((128, 256, 512, 10), 128, 2),                # 8 column tiles
+    ((128, 256, 448, 10), 128, 2),                # 7: an odd number, no whole-tile walk
+    ((640, 512, 10), 128, 3),                     # a first layer apart: 30 bands of 8 column tiles
+])
+def test_layers_apart_and_walked(dims, batch, n):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=dims, batch=batch, n_workers=n, gemm_dtype="bf16", activation="tanh", rows_per_worker=64, lr=0.01, interval=3,
+                  iterations=7)
+    inp = inputs_for(w)
+    outs = []
+    for first in (True, False):
+        h = D.open_workload(w, inp)
+        P.prsgd_set_first_layer_fusion(h, first)
+        P.prsgd_local_steps(h, 1)
+        assert rel_err(D.read_all(h), oracle_run(w, inp, iterations=1)["x"]) <= 1e-4
+        P.prsgd_destroy(h)
+        h = D.open_workload(w, inp)
+        P.prsgd_set_first_layer_fusion(h, first)
+        P.prsgd_run(h, w.iterations, w.interval)
+        outs.append((D.read_all(h), P.prsgd_read_loss(h)))
+        P.prsgd_destroy(h)
+    want = oracle_run(w, inp)
+    for x, loss in outs:
+        assert rel_err(x, want["x"]) <= 5e-3
+        assert np.allclose(loss, want["losses"], rtol=2e-2, atol=2.0 ** -20)
