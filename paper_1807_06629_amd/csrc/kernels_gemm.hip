@@ -364,6 +364,13 @@ static bool rows_fed(RowsTile t, const GemmArgs& p, int n_groups) {
   return tiles < kFedTiles || (tiles == kFedTiles && p.b_gs == 0 && p.k_splits <= 1);
 }
 
+// fp32 tiles of 32 x 32: a step of the plain kernel is 256 cycles of matrix instructions and 130 in which the same wavefronts are held up
+// in their requests.  Launch alone, plain and with requesting wavefronts: 8 x (50 x 300) x 784 10.1 and 8.2 us, 4 x (16 x 66) x 997 12.4 and
+// 8.9, 6 x (43 x 66) x 771 10.4 and 7.5, 5 x (73 x 383) x 457 8.7 and 6.6, 3 x (10 x 75) x 320 5.4 and 5.0.  Per iteration, tiles of the first
+// layer in brackets: 512-1024-512-10, 8 rows, [256] 48.2 and 42.5 us, [512] 61.7 and 57.6, [1024] 96.8 and 94.9, [4096] 407 and 408;
+// 256-256-256-10, 50 rows, [512] 41.5 and 41.7, [2048] 96.2 and 98.6.
+static bool f32_fed(const GemmArgs& p, int n_groups) { return rows_tiles({32, 32}, p.M, p.N, p.k_splits, n_groups) <= kFedTiles; }
+
 template <int AKIND, int BKIND>
 static hipError_t launch_rows_bf16(const GemmArgs& p, int n_groups, hipStream_t s) {
   const RowsTile t = rows_tile(p, n_groups, true);
@@ -377,6 +384,8 @@ template <int AKIND, int BKIND>
 static hipError_t launch_rows_f32(const GemmArgs& p, int n_groups, hipStream_t s) {
   if (rows_tile(p, n_groups, false).bm == 64)
     return launch_one<TF32, 64, 64, 2, 2, 1, 4, AKIND, BKIND>(p, n_groups, s);
+  if (f32_fed(p, n_groups))
+    return BKIND == OP_CONTIG ? launch_gemm_dx_fed(p, n_groups, 32, 32, s) : launch_gemm_fwd_fed(p, n_groups, 32, 32, s);
   return launch_one<TF32, 32, 32, 1, 1, 4, kRowStages, AKIND, BKIND>(p, n_groups, s);
 }
 
@@ -389,7 +398,9 @@ void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows
   const bool fed = rows_fed(t, p, n_groups);
   *tile_rows = t.bm;
   *tile_cols = t.bn;
-  *lds_bytes = !bf16 ? (t.bm == 64 ? gemm_lds_bytes<TF32, 64, 64, 1, 4>() : gemm_lds_bytes<TF32, 32, 32, 4, kRowStages>())
+  *lds_bytes = !bf16 ? (t.bm == 64 ? gemm_lds_bytes<TF32, 64, 64, 1, 4>()
+                        : f32_fed(p, n_groups) ? gemm_lds_bytes<TF32, 32, 32, 4, kFedSmallStages>()
+                                               : gemm_lds_bytes<TF32, 32, 32, 4, kRowStages>())
                : t.bm == 32 ? (fed ? gemm_lds_bytes<TBF16, 32, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 32, 64, 1, kRowStages>())
                : t.bm == 64 ? (fed ? gemm_lds_bytes<TBF16, 64, 64, 1, kFedSmallStages>() : gemm_lds_bytes<TBF16, 64, 64, 1, kRowStages>())
                : t.bn == 64 ? gemm_lds_bytes<TBF16, 128, 64, 1, kRowStages>() : gemm_lds_bytes<TBF16, 128, 128, 1, kFedStages>();

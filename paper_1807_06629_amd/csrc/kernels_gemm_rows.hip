@@ -1,10 +1,10 @@
-// Batch-row products (forward, backward-data) of bf16 operands whose workgroups divide the work by kind of instruction: those in
-// 128 x 128 tiles, and launches of few smaller ones (kernels_gemm.hip says which).
+// Batch-row products (forward, backward-data) whose workgroups divide the work by kind of instruction: those in 128 x 128 tiles, and
+// launches of few smaller ones (kernels_gemm.hip says which).
 #include "gemm_tile.h"
 
 namespace prsgd {
 
-// The same tile of a bf16 batch-row product in a workgroup whose wavefronts share the work by kind: four multiply, CM x CN over the
+// The same tile of a batch-row product in a workgroup whose wavefronts share the work by kind: four multiply, CM x CN over the
 // output tile, four request.  A wavefront that requests is held up until its requests are taken (65 cycles each per SIMD, 32 of them for
 // a 128 x 128 tile), and then its matrix instructions wait with it; a SIMD has one wavefront of each kind.  The multiplying
 // wavefronts hold the fragments of a whole tile and read the next tile's behind the matrix instructions, so that they meet the
@@ -12,16 +12,17 @@ namespace prsgd {
 // Same order of the contraction, same bits as gemm_tile.  Workers x (rows x contraction) x columns, against eight wavefronts that do
 // both: 8 x (128 x 4096) x 4096 with shared weights 46 -> 36 us forward, 44 -> 35 us backward-data, launched by itself; in an iteration
 // at interval 1, with the weights in HBM and clocks at the power limit, 50 -> 46 and 40 -> 33 us.
-template <int BM, int BN, int CM, int CN, int S, int AKIND, int BKIND>
+// fp32, whose tiles are 32 x 32: the multiplying wavefronts share the contraction (WK), and the shares are added in order.
+template <typename T, int BM, int BN, int CM, int CN, int WK, int S, int AKIND, int BKIND>
 __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
-  using T = TBF16;
-  using E = T::elem;
-  constexpr int NREQ = 4, NTHR = 64 * (NREQ + CM * CN);    // requesting wavefronts; threads
+  using E = typename T::elem;
+  constexpr int NREQ = 4, NMUL = CM * CN * WK, NTHR = 64 * (NREQ + NMUL);          // requesting, multiplying wavefronts; threads
+  constexpr int KW = kSlices / WK;                         // slices of a multiplying wavefront
   using IOA = TileIO<T, BM, AKIND, NREQ>;
   using IOB = TileIO<T, BN, BKIND, NREQ>;
   constexpr int BK = IOA::BK, PER = IOA::NPT + IOB::NPT;
   constexpr int TM = BM / (32 * CM), TN = BN / (32 * CN);
-  static_assert(CM * CN <= 4, "at most a multiplying and a requesting wavefront per SIMD");
+  static_assert(NMUL <= 4 && kSlices % WK == 0, "at most a multiplying and a requesting wavefront per SIMD");
   static_assert(TM >= 1 && TN >= 1, "tile too small for the wavefront grid");
   static_assert(S >= 2 && S <= 4 && PER * (S - 1) <= 63, "wait_tiles");
 
@@ -31,8 +32,8 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int STAGE = (BM + BN) * kTileBytes;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool multiplies = wave < CM * CN;
-  const int wm = wave / CN, wn = wave % CN;
+  const bool multiplies = wave < NMUL;
+  const int wk = wave / (CM * CN), wm = (wave / CN) % CM, wn = wave % CN;
   int Kc, k_lo;
   contraction_range<BK>(p, at, &k_lo, &Kc);
   const int n_k = (Kc + BK - 1) / BK;
@@ -43,7 +44,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
   f32x16_t acc[TM][TN];
   if (!multiplies) {
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-    const int w = wave - CM * CN;
+    const int w = wave - NMUL;
     const E* a_src = reinterpret_cast<const E*>(p.a) + (size_t)g * p.a_gs +
                      (AKIND == OP_CONTIG ? (size_t)m0 * p.lda + k_lo : (size_t)k_lo * p.lda + m0);
     const E* b_src = reinterpret_cast<const E*>(p.b) + (size_t)g * p.b_gs +
@@ -79,14 +80,14 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    Frag<T> af[2][kSlices][TM], bf[2][kSlices][TN];
+    Frag<T> af[2][KW][TM], bf[2][KW][TN];
     auto load = [&](int stage, int u, int set) __attribute__((always_inline)) {
       const unsigned char* a_t = smem + stage * STAGE;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[set][u][i] = load_frag<T, BM, AKIND, NREQ>(a_t, wm * TM + i, u, lane);
+      for (int i = 0; i < TM; ++i) af[set][u][i] = load_frag<T, BM, AKIND, NREQ>(a_t, wm * TM + i, wk * KW + u, lane);
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        bf[set][u][j] = load_frag<T, BN, BKIND, NREQ>(a_t + BM * kTileBytes, wn * TN + j, u, lane);
+        bf[set][u][j] = load_frag<T, BN, BKIND, NREQ>(a_t + BM * kTileBytes, wn * TN + j, wk * KW + u, lane);
     };
     int stage = 0;
     // multiplies the tile in set SET; not the last one: reads the next tile into the other set
@@ -98,13 +99,13 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       }
 #pragma unroll
-      for (int u = 0; u < kSlices; ++u) {
+      for (int u = 0; u < KW; ++u) {
         if constexpr (!LAST) load(stage, u, SET ^ 1);
         if (LAST && k_tail < BK) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) mask_frag(af[SET][u][i], u, lane, k_tail);
+          for (int i = 0; i < TM; ++i) mask_frag(af[SET][u][i], wk * KW + u, lane, k_tail);
 #pragma unroll
-          for (int j = 0; j < TN; ++j) mask_frag(bf[SET][u][j], u, lane, k_tail);
+          for (int j = 0; j < TN; ++j) mask_frag(bf[SET][u][j], wk * KW + u, lane, k_tail);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -119,7 +120,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
     if (n_k > 0) {
       asm volatile("s_barrier" ::: "memory");
 #pragma unroll
-      for (int u = 0; u < kSlices; ++u) load(0, u, 0);
+      for (int u = 0; u < KW; ++u) load(0, u, 0);
       int t = 0;
       for (; t + 2 < n_k; t += 2) {                        // one way out: the accumulators stay where they are
         step(Set0{}, std::false_type{});
@@ -137,7 +138,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
   out.request(p, g);
   __syncthreads();                                         // every wavefront is done with the last tile
   constexpr int SC = BN + 4;
-  float* c_lds = reinterpret_cast<float*>(smem);           // [BM][SC]
+  float* c_lds = reinterpret_cast<float*>(smem);           // [WK][BM][SC]
   if (multiplies) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -145,29 +146,37 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-          c_lds[((wm * TM + i) * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4)) * SC + (wn * TN + j) * 32 + (lane & 31)] =
+          c_lds[(wk * BM + (wm * TM + i) * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4)) * SC + (wn * TN + j) * 32 + (lane & 31)] =
               acc[i][j][v];
   }
   __syncthreads();
   out.store(p, g, at.split, [&](int r, int c) __attribute__((always_inline)) {
-    return *reinterpret_cast<const f32x4_t*>(c_lds + r * SC + c);
+    f32x4_t s = *reinterpret_cast<const f32x4_t*>(c_lds + r * SC + c);
+#pragma unroll
+    for (int w = 1; w < WK; ++w) {
+      const f32x4_t o = *reinterpret_cast<const f32x4_t*>(c_lds + (w * BM + r) * SC + c);
+      s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+    }
+    return s;
   });
 }
 
-template <int BM, int BN, int CM, int CN, int S, int AKIND, int BKIND>
-__global__ __launch_bounds__(64 * (4 + CM * CN), 2) void grouped_rows_kernel(GemmArgs p) {
-  gemm_rows_fed<BM, BN, CM, CN, S, AKIND, BKIND>(p, (int)blockIdx.x);
+template <typename T, int BM, int BN, int CM, int CN, int WK, int S, int AKIND, int BKIND>
+__global__ __launch_bounds__(64 * (4 + CM * CN * WK), 2) void grouped_rows_kernel(GemmArgs p) {
+  gemm_rows_fed<T, BM, BN, CM, CN, WK, S, AKIND, BKIND>(p, (int)blockIdx.x);
+}
+template <typename T, int BM, int BN, int CM, int CN, int WK, int S, int AKIND, int BKIND>
+static hipError_t launch_fed_tiles(const GemmArgs& p, int n_groups, hipStream_t s) {
+  return launch_tiles<T, BM, BN, WK, S, 4 + CM * CN * WK, grouped_rows_kernel<T, BM, BN, CM, CN, WK, S, AKIND, BKIND>>(p, n_groups, s);
 }
 
 template <int AKIND, int BKIND> static hipError_t launch_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s) {
   constexpr int S = kFedStages, T = kFedSmallStages;
-  if (bm == 32)
-    return launch_tiles<TBF16, 32, 64, 1, T, 6, grouped_rows_kernel<32, 64, 1, 2, T, AKIND, BKIND>>(p, n_groups, s);
-  if (bm == 64)
-    return launch_tiles<TBF16, 64, 64, 1, T, 8, grouped_rows_kernel<64, 64, 2, 2, T, AKIND, BKIND>>(p, n_groups, s);
-  if (bn == 64)
-    return launch_tiles<TBF16, 128, 64, 1, S, 8, grouped_rows_kernel<128, 64, 2, 2, S, AKIND, BKIND>>(p, n_groups, s);
-  return launch_tiles<TBF16, 128, 128, 1, S, 8, grouped_rows_kernel<128, 128, 2, 2, S, AKIND, BKIND>>(p, n_groups, s);
+  if (bn == 32) return launch_fed_tiles<TF32, 32, 32, 1, 1, 4, T, AKIND, BKIND>(p, n_groups, s);
+  if (bm == 32) return launch_fed_tiles<TBF16, 32, 64, 1, 2, 1, T, AKIND, BKIND>(p, n_groups, s);
+  if (bm == 64) return launch_fed_tiles<TBF16, 64, 64, 2, 2, 1, T, AKIND, BKIND>(p, n_groups, s);
+  if (bn == 64) return launch_fed_tiles<TBF16, 128, 64, 2, 2, 1, S, AKIND, BKIND>(p, n_groups, s);
+  return launch_fed_tiles<TBF16, 128, 128, 2, 2, 1, S, AKIND, BKIND>(p, n_groups, s);
 }
 hipError_t launch_gemm_fwd_fed(const GemmArgs& p, int n_groups, int bm, int bn, hipStream_t s) {
   return launch_fed<OP_CONTIG, OP_TRANS>(p, n_groups, bm, bn, s);

@@ -126,3 +126,22 @@ def test_contractions_of_tall_narrow_tiles(hidden):
     assert rel_err(D.read_all(h), want["x"]) <= 1e-4
     assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-3, atol=1e-6)
     P.prsgd_destroy(h)
+
+
+# fp32 tiles of 32 x 32 with and without requesting wavefronts (up to two workgroups per compute unit, and more): contractions of one
+# element to five tiles of 32, whole and ragged
+@pytest.mark.parametrize("n_workers", [2, 68])
+@pytest.mark.parametrize("hidden", [1, 32, 33, 63, 96, 131, 160])
+def test_fp32_contractions_of_small_tiles(hidden, n_workers):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    dims, batch = (40, hidden, 250, hidden, 12), 31
+    assert P.prsgd_product_tile(batch, 250, n_workers, "f32")[:2] == (32, 32) and (8 * n_workers > 512) == (n_workers == 68)
+    w = small_mlp(dims=dims, batch=batch, n_workers=n_workers, gemm_dtype="f32", activation="tanh", rows_per_worker=64, iterations=1)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp, device="cuda:0")
+    P.prsgd_local_steps(h, 1)
+    want = oracle_run(w, inp, iterations=1)
+    assert rel_err(D.read_all(h), want["x"]) <= 1e-5
+    assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-5, atol=1e-6)
+    P.prsgd_destroy(h)
