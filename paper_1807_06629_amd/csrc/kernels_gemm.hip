@@ -151,6 +151,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   auto multiply = [&](int u, int set, bool ragged) __attribute__((always_inline)) {
     if (ragged) {
       const int kk = wk * KW + u;
+      if (kk * (BK / kSlices) >= k_tail) return;           // nothing but zeros
 #pragma unroll
       for (int i = 0; i < TM; ++i) mask_frag(af[set][i], kk, lane, k_tail);
 #pragma unroll

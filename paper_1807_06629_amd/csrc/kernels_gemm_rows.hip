@@ -101,6 +101,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
 #pragma unroll
       for (int u = 0; u < KW; ++u) {
         if constexpr (!LAST) load(stage, u, SET ^ 1);
+        if (LAST && (wk * KW + u) * (BK / kSlices) >= k_tail) continue;          // nothing but zeros
         if (LAST && k_tail < BK) {
 #pragma unroll
           for (int i = 0; i < TM; ++i) mask_frag(af[SET][u][i], wk * KW + u, lane, k_tail);
