@@ -432,7 +432,11 @@ hipError_t launch_gemm_dx(const GemmArgs& p, int n_groups, bool bf16, hipStream_
 // Weight-gradient products.  128 x 128 tiles in workgroups of four wavefronts, two of them per compute
 // unit, so that the weight read-modify-write of one runs beside the products of the other: 4096 x 4096
 // with 1024 stacked rows 87 -> 70 us, 8 x (3072 x 1024) with 512 rows 102 -> 79 us.  Launches without two such
-// tiles per compute unit: 64 x 64 tiles.
+// tiles per compute unit: 64 x 64 tiles.  Layers that share a launch take the large tiles if one of them does: the old weights of
+// one workgroup then run beside the products of others that have come out of step, where launches of two rounds move and multiply in
+// turn, and small layers cost no rounds of their own.  Kernels of an iteration, launches apart and one: 8 x 4096-4096-4096-4096-1000 at
+// interval 1 225 and 213 us; 8 x 3072-1024-1024-10 with 512 rows 111 and 105; 4 x 2112-2944-2880-2472-465, 128 rows, interval 1, all
+// launches 228 and 192; 10 x 2116-576-576-28, 194 rows, 98 and 89.
 static bool dw_large(const GemmArgs& p, int n_groups, bool bf16) {
   return bf16 && (long)((p.M + 127) / 128) * ((p.N + 127) / 128) * n_groups >= 2 * kComputeUnits;
 }
@@ -440,8 +444,7 @@ static bool dw_large(const GemmArgs& p, int n_groups, bool bf16) {
 // (7 us for a single 64 x 64 tile: launch, first operand and weight loads, write-back), so the layers'
 // products, which depend on nothing of each other, share one launch (fp32 784-300-100-10, eight workers:
 // 11.8 + 6.9 + 7.1 us in three launches, 12.7 us in one).
-template <typename T, int S> static hipError_t launch_dw_set(const GemmArgs* ps, int n, int n_groups, hipStream_t s) {
-  constexpr int BM = 64, BN = 64;
+template <typename T, int BM, int BN, int S> static hipError_t launch_dw_set(const GemmArgs* ps, int n, int n_groups, hipStream_t s) {
   constexpr size_t kLds = gemm_lds_bytes<T, BM, BN, 1, S>();
   auto kernel = grouped_gemm_set_kernel<T, BM, BN, 2, 2, 1, S, OP_TRANS, OP_TRANS>;
   static std::atomic<bool> configured{false};
@@ -467,8 +470,6 @@ template <typename T, int S> static hipError_t launch_dw_set(const GemmArgs* ps,
   hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(256), kLds, s, set);
   return hipGetLastError();
 }
-// One large product, or up to kMaxGemmSet others (gemm_dw_shares_launch).
-bool gemm_dw_shares_launch(const GemmArgs& p, int n_groups, bool bf16) { return !dw_large(p, n_groups, bf16); }
 hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hipStream_t s) {
   if (n < 0 || n > kMaxGemmSet) return hipErrorInvalidValue;
   if (n == 1 && dw_large(ps[0], n_groups, bf16))
@@ -485,8 +486,10 @@ hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hi
     return shallow ? launch_one<TF32, 64, 64, 2, 2, 1, 2, OP_TRANS, OP_TRANS>(ps[0], n_groups, s)
                    : launch_one<TF32, 64, 64, 2, 2, 1, 4, OP_TRANS, OP_TRANS>(ps[0], n_groups, s);
   }
-  if (bf16) return shallow ? launch_dw_set<TBF16, 2>(ps, n, n_groups, s) : launch_dw_set<TBF16, 4>(ps, n, n_groups, s);
-  return shallow ? launch_dw_set<TF32, 2>(ps, n, n_groups, s) : launch_dw_set<TF32, 4>(ps, n, n_groups, s);
+  for (int i = 0; i < n; ++i)
+    if (dw_large(ps[i], n_groups, bf16)) return launch_dw_set<TBF16, 128, 128, 2>(ps, n, n_groups, s);
+  if (bf16) return shallow ? launch_dw_set<TBF16, 64, 64, 2>(ps, n, n_groups, s) : launch_dw_set<TBF16, 64, 64, 4>(ps, n, n_groups, s);
+  return shallow ? launch_dw_set<TF32, 64, 64, 2>(ps, n, n_groups, s) : launch_dw_set<TF32, 64, 64, 4>(ps, n, n_groups, s);
 }
 
 }  // namespace prsgd

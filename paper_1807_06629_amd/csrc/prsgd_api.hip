@@ -357,7 +357,7 @@ int refresh_first_shadow(prsgd_ctx* ctx) {
   return PRSGD_OK;
 }
 
-// Weight-gradient products of one backward pass.  Small ones wait for each other and share a launch: they
+// Weight-gradient products of one backward pass.  They wait for each other and share a launch: they
 // read H and D of their layers, which stay as they are until the next iteration, and write W_l after
 // the backward-data product that needs its old value.
 struct DwQueue {
@@ -373,10 +373,6 @@ struct DwQueue {
     return PRSGD_OK;
   }
   int add(const GemmArgs& p, int groups, int k) {
-    if (!gemm_dw_shares_launch(p, groups, ctx->bf16)) {
-      LAUNCH(ctx, k, launch_gemm_dw(&p, 1, groups, ctx->bf16, ctx->stream));
-      return PRSGD_OK;
-    }
     if (n == kMaxGemmSet) {
       const int rc = flush();
       if (rc != PRSGD_OK) return rc;

@@ -164,10 +164,8 @@ hipError_t launch_gemm_fwd(const GemmArgs& p, int n_groups, bool bf16, hipStream
 hipError_t launch_gemm_dx(const GemmArgs& p, int n_groups, bool bf16, hipStream_t s);
 // Tile and LDS bytes per workgroup of the batch-row product [rows] x [cols] of n_groups workers.
 void gemm_rows_shape(int rows, int cols, int n_groups, bool bf16, int* tile_rows, int* tile_cols, size_t* lds_bytes);
-// Weight-gradient products of up to kMaxGemmSet layers: products that may share a launch, or one that
-// may not.
+// Weight-gradient products of up to kMaxGemmSet layers in one launch.
 constexpr int kMaxGemmSet = 4;
-bool gemm_dw_shares_launch(const GemmArgs& p, int n_groups, bool bf16);
 hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hipStream_t s);
 
 // Minibatch draw of iteration t: rows of the workers' shards copied into the batch buffer.
