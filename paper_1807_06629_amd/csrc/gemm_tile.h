@@ -71,10 +71,16 @@ template <typename T, int ROWS, int KIND, int NWAVE> struct TileIO {
     }
   }
   __device__ static __forceinline__ void request(const E* tile_base, const uint32_t (&off)[NPT], uint32_t lds_tile,
-                                                 int wave) {
+                                                 int wave, bool once = false) {
+    if (once) {
 #pragma unroll
-    for (int q = 0; q < NPT; ++q)
-      load_to_lds(tile_base, off[q], lds_tile + (uint32_t)(q * NWAVE + wave) * 1024u);
+      for (int q = 0; q < NPT; ++q)
+        load_to_lds<true>(tile_base, off[q], lds_tile + (uint32_t)(q * NWAVE + wave) * 1024u);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q)
+        load_to_lds(tile_base, off[q], lds_tile + (uint32_t)(q * NWAVE + wave) * 1024u);
+    }
   }
 };
 
@@ -373,6 +379,11 @@ static hipError_t launch_tiles(GemmArgs p, int n_groups, hipStream_t s) {
     configured.store(true, std::memory_order_release);
   }
   if (p.k_splits > 1 && p.epi != EPI_FWD_LOGITS) return hipErrorInvalidValue;
+  // Weights of a worker's own that one row of tiles covers are read once and not kept: read into the last-level cache, they made it write
+  // back what the backward kernels had left there.  8 x 4096-4096-4096-4096-1000, 128 rows: forward launches of the second and third layer 91
+  // and 68 us, 58 and 57 so, of which the backward kernels lose 6 each; 16 iterations 16043 -> 15850 us.  16 x 3072-1024-1024-10, 64 rows, second
+  // layer 15.2 -> 11.3.  Weights that several rows of tiles or all workers read again stay: 8 x (512 x 3072) x 1024 31 us, 38 non-temporal.
+  p.b_once = p.streaming && p.b_gs != 0 && p.M <= BM ? 1 : 0;
   const int tiles = place_tiles(&p, BM, BN, n_groups);
   hipLaunchKernelGGL(KERNEL, dim3((unsigned)tiles), dim3(64 * WAVES), kLds, s, p);
   return hipGetLastError();

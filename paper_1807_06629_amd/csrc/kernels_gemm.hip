@@ -80,10 +80,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
       IOA::template offsets<true>(a_o, p.lda, p.M - m0, k_tail, wave, lane);
       IOB::template offsets<true>(b_o, p.ldb, p.N - n0, k_tail, wave, lane);
       IOA::request(a_src + (size_t)j * a_step, a_o, lds_a, wave);
-      IOB::request(b_src + (size_t)j * b_step, b_o, lds_b, wave);
+      IOB::request(b_src + (size_t)j * b_step, b_o, lds_b, wave, !kIsDw && p.b_once);
     } else {
       IOA::request(a_src + (size_t)j * a_step, a_off, lds_a, wave);
-      IOB::request(b_src + (size_t)j * b_step, b_off, lds_b, wave);
+      IOB::request(b_src + (size_t)j * b_step, b_off, lds_b, wave, !kIsDw && p.b_once);
     }
   };
 
@@ -97,7 +97,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   f32x4_t w_old[EV];
   if constexpr (kIsDw) if (fused) {
     const float* wtile = p.src + (size_t)g * p.src_gs + p.w_off + (size_t)m0 * p.ldw + n0;
-    const bool nt_read = p.streaming && p.src_gs != 0;     // a shared source is re-read by every group
+    const bool nt_read = p.streaming && (p.src_gs != 0 || p.p_gs == 0);          // a source that several groups share is read again
 #pragma unroll
     for (int q = 0; q < EV; ++q) {
       const int r = q * ROWS_PER_PASS + e_row;

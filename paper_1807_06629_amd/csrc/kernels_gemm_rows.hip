@@ -61,7 +61,7 @@ __device__ __forceinline__ void gemm_rows_fed(const GemmArgs& p, int block) {
         IOB::template offsets<true>(b_off, p.ldb, p.N - n0, k_tail, w, lane);
       }
       IOA::request(a_src + (size_t)j * a_step, a_off, lds_a, w);
-      IOB::request(b_src + (size_t)j * b_step, b_off, lds_b, w);
+      IOB::request(b_src + (size_t)j * b_step, b_off, lds_b, w, p.b_once != 0);
     };
 #pragma unroll 1                                           // one copy of a request, and one in the loop
     for (int j = 0; j < min(S, n_k); ++j) request(j, j);

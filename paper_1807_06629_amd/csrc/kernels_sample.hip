@@ -36,7 +36,10 @@ __device__ __forceinline__ void gather_row(const GatherArgs& a, int j, int i) {
     for (int c0 = threadIdx.x; c0 < n4; c0 += U * kThreads) {
       f32x4_t v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = src4[min(c0 + u * kThreads, n4 - 1)];
+      for (int u = 0; u < U; ++u) {
+        const f32x4_t* at = src4 + min(c0 + u * kThreads, n4 - 1);
+        v[u] = a.once ? __builtin_nontemporal_load(at) : *at;
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int c = c0 + u * kThreads;
@@ -56,7 +59,10 @@ __device__ __forceinline__ void gather_row(const GatherArgs& a, int j, int i) {
     for (int c0 = threadIdx.x; c0 < d0; c0 += U * kThreads) {
       float v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = src[min(c0 + u * kThreads, d0 - 1)];
+      for (int u = 0; u < U; ++u) {
+        const float* at = src + min(c0 + u * kThreads, d0 - 1);
+        v[u] = a.once ? __builtin_nontemporal_load(at) : *at;
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) asm volatile("" : "+v"(v[u]));         // a load is not moved to its conditional store
 #pragma unroll
@@ -551,6 +557,7 @@ GatherArgs gather_args(const float* features, const int32_t* labels, void* xb, i
   a.batch = batch; a.d0 = d0; a.ld0 = ld0; a.rows = rows; a.log2n = ilog2(rows);
   a.seed = seed; a.t = (uint64_t)t;
   a.order = order; a.workers = workers;
+  a.once = 0;
   return a;
 }
 

@@ -112,6 +112,7 @@ constexpr size_t kStreamingBytes = (size_t)192 << 20;
 
 // Which launches of a configuration are streamed.
 struct Streamed {
+  bool rows;          // drawn rows of the shards
   bool steps;         // local steps: they rewrite the replica set
   bool step_mean;     // a step on the node average: the average is all it rewrites, and the next iteration reads
                       // it again (16 x (3072-1024-1024-10) at interval 1, an average of 17 MB: 78 us per iteration, 84
@@ -124,6 +125,9 @@ struct Streamed {
                       // the cache on (fp32 at interval 4, 28 x (1024-1024-1024-10), 226 MiB: 191 us, 194 streamed; 2 x
                       // (4096-4096-4096-10), 257 MiB: 262 and 277 us; 12 x (2048-2048-2048-10), 386 MiB: 341 and 332 us)
 };
+// Shards from here on: a drawn row is gone from the last-level cache before it is drawn again, and in passing made room there (8 workers of
+// 4096-4096-4096-4096-1000, shards of 1 GB, 15850 -> 15805 us per 16 iterations, 16 of 3072-1024-1024-10 4470 -> 4410 per 32).
+constexpr size_t kStreamingRowBytes = (size_t)256 << 20;
 constexpr size_t kStreamingMeanFewBytes = (size_t)1 << 30, kStreamingAverageBytes = (size_t)384 << 20;
 Streamed streamed_uses(const prsgd_config& c, const Layout& lo) {
   const size_t average = (size_t)lo.m_pad * sizeof(float), set = average * (size_t)c.n_workers;
@@ -132,6 +136,7 @@ Streamed streamed_uses(const prsgd_config& c, const Layout& lo) {
   u.step_mean = average >= kStreamingBytes;
   u.mean = set >= (c.n_workers > 4 ? kStreamingBytes : kStreamingMeanFewBytes);
   u.average = set >= kStreamingAverageBytes;
+  u.rows = u.steps && (size_t)c.n_workers * (size_t)c.rows_per_worker * (size_t)lo.d[0] * sizeof(float) >= kStreamingRowBytes;
   return u;
 }
 
@@ -417,9 +422,11 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
   // The minibatch of iteration t: already there when the previous iteration's loss-head launch
   // drew it (below); otherwise gathered now.  prsgd_local_steps_hetero forgets masked draws at the end of an epoch.
   auto batch_args = [&](int k, int64_t tt, const int* workers, int n) {
-    return gather_args(ctx->features, reinterpret_cast<const int32_t*>(ctx->targets), ctx->xb(k), ctx->yb(k),
-                       ctx->idx(workers != nullptr && active.idx_set >= 0 ? active.idx_set : k), B, lo.d[0], lo.ld[0],
-                       (long)c.rows_per_worker, c.seed, tt, workers, n);
+    GatherArgs a = gather_args(ctx->features, reinterpret_cast<const int32_t*>(ctx->targets), ctx->xb(k), ctx->yb(k),
+                               ctx->idx(workers != nullptr && active.idx_set >= 0 ? active.idx_set : k), B, lo.d[0], lo.ld[0],
+                               (long)c.rows_per_worker, c.seed, tt, workers, n);
+    a.once = ctx->streamed.rows ? 1 : 0;
+    return a;
   };
   int bk = ctx->batch_t[0] == t ? 0 : ctx->batch_t[1] == t ? 1 : -1;
   if (bk < 0) {

@@ -55,6 +55,7 @@ struct GemmArgs {
   TilePlace place;
   int epi;
   int streaming;                      // weights far exceed the caches: non-temporal accesses
+  int b_once;                         // ... and every element of B is read by one workgroup only (filled in by the launcher)
   int act;                            // PRSGD_TANH | PRSGD_RELU
   float lr;
   // parameters / gradients (fp32, replica stride m_pad), bf16 shadow of the parameters
@@ -175,6 +176,7 @@ struct GatherArgs {
   int batch, d0, ld0; long rows; int log2n;
   uint64_t seed, t;
   const int* order; int workers;              // Algorithm 3: the workers order[0 .. workers) draw (nullptr: 0 .. workers)
+  int once;                                   // the shards exceed the caches: their rows are read non-temporally
 };
 GatherArgs gather_args(const float* features, const int32_t* labels, void* xb, int32_t* yb, int32_t* idx,
                        int batch, int d0, int ld0, long rows, uint64_t seed, int64_t t, const int* order, int workers);
@@ -308,14 +310,20 @@ __device__ __forceinline__ bf16x8_t frag_trans(const uint16_t* lds, int stride, 
 // compiler's wait counts: a kernel that uses it waits by itself, and everything the compiler waits for on its
 // own is then waited for at least as long as it needs.  m0 is a reserved register, which cannot be listed as
 // clobbered: nothing else in such a kernel may use it.
+// NT: non-temporal, for what is read once and should leave the caches to the rest.
+template <bool NT = false>
 __device__ __forceinline__ void load_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
   // both are the same in every lane; said explicitly, they end up in scalar registers
   const uint64_t u = (uint64_t)(uintptr_t)base_any;
   const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)u) |
                         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32);
   const uint32_t lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_any);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds_off), "v"(lane_off), "s"(base) : "memory");
 }
 // The same with 4 bytes per lane: any alignment of the source, 256 consecutive bytes of LDS.
 __device__ __forceinline__ void load_dword_to_lds(const void* base_any, uint32_t lane_off, uint32_t lds_any) {
