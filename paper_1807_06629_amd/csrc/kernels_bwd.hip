@@ -655,8 +655,7 @@ hipError_t launch_bwd_one(const BwdArgs& p, hipStream_t s) {
 
 bool bwd_fused_supported(int batch) { return batch >= 1 && batch <= 128; }
 
-// Ragged layers with fewer 64-row bands than compute units (and no momentum, which the products
-// cannot apply): a band walks its column tiles one after the other at about 2.5 us each behind a
+// Ragged layers with fewer 64-row bands than compute units: a band walks its column tiles one after the other at about 2.5 us each behind a
 // 7 us start, while the products of the layer spread over all compute units.  1000-500-300-37, six
 // workers, 100 rows: the three layers' launches 21 + 20 + 10 us, the two backward-data products 5 + 7 us and the
 // weight-gradient products in one launch 14 us.  With a band per compute unit the pass over
@@ -668,15 +667,17 @@ bool bwd_fused_supported(int batch) { return batch >= 1 && batch <= 128; }
 // iteration, walked and apart, 64-row bands of the second layer in brackets: 640-1152-1152-20, 32 rows, 3 workers [54] 45.7 and 44.2 us, 4 [72]
 // 45.7 and 46.1; 64 rows, 4 [72] 49.4 and 47.9, 6 [108] 50.7 and 51.9; 128 rows, 6 [108] 63.3 and 60.8, 8 [144] 71.1 and 76.0.  First
 // layers: 2560-1280-43, 64 rows, 2 workers [80] 41.1 and 34.9, 3 [120] 42.1 and 43.9; 128 rows, 4 [160] 57.6 and 53.8.  Short walks stay:
-// 1024-512-512-10, 32 rows, 1 worker 33.3 and 34.9 us.  (1 worker of 4096-2048-2048-512, 64 rows, 89.8 and 67.5.)
+// 1024-512-512-10, 32 rows, 1 worker 33.3 and 34.9 us.  (1 worker of 4096-2048-2048-512, 64 rows, 89.8 and 67.5.)  With momentum a
+// tile of the walk moves 18 bytes per weight: 3072-1024-1024-10, 64 rows, 1 worker 84.6 and 42.9 us, 4 [64] 88.5 and 83.2.
 static bool walk_too_long(const BwdArgs& p) {
   const int n_t = p.Nn / BN, height = p.B <= 32 ? 0 : p.B <= 64 ? 1 : 2;
   const long bands = (long)((p.K + BMK - 1) / BMK) * p.n_groups;
-  static constexpr int kTiles[3] = {14, 12, 8}, kBands[3] = {60, 80, 112}, kFirstBands[3] = {100, 110, 256};
-  return p.dx != nullptr ? n_t >= kTiles[height] && bands < kBands[height] : n_t >= 8 && bands < kFirstBands[height];
+  static constexpr int kTiles[3] = {14, 12, 8}, kBands[3] = {60, 80, 112};
+  static constexpr int kFirstTiles[3] = {14, 14, 8}, kFirstBands[3] = {100, 110, 256};
+  if (p.dx != nullptr) return n_t >= kTiles[height] && bands < kBands[height];
+  return n_t >= kFirstTiles[height] && bands < (p.vel != nullptr ? 256 : kFirstBands[height]);
 }
 bool bwd_products_apart(const BwdArgs& p) {
-  if (p.vel != nullptr) return false;
   if (p.dx == nullptr && bwd_first_fwd_same_bits(p)) return false;
   const int mb = p.B <= 32 ? 1 : p.B <= 64 ? 2 : 4;
   if (bwd_full_applies(p, mb, 2) || bwd_full_applies(p, mb, 2, 32)) return walk_too_long(p);

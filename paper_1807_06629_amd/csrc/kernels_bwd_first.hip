@@ -31,7 +31,7 @@
 // is summed as in the other layers' kernel, so H_1^{t+1} and the parameters have the bits the two
 // separate launches give.  Whole tiles (B = 32 MB, d_0 a multiple of 128, d_1 of 64), and from 512 rows of W_1 on any minibatch and
 // any rows with columns that the layout pads to whole tiles: 5 workers of 4005-2688-100, 64 rows, 177 -> 104 us per iteration, 12 of
-// 3001-1472-333-20 208 -> 146; with momentum 282 -> 180 and 321 -> 258.
+// 3001-1472-333-20 208 -> 146; with momentum 282 -> 179 and 316 -> 257.
 #include <atomic>
 #include <type_traits>
 
@@ -398,20 +398,20 @@ static bool bwd_first_fwd_shape(int batch, int d_in, int d_out) {
 // Per iteration, fused less apart, bands in brackets: 64 rows, 2560 x 256 [8] +13 us, [64] +8.6; 4096 x 1024 [32] +19.1, [64] +4.6, [80]
 // -2.8, [128] -19.2; 2048 x 1024 [16] +3.2, [80] -3.1; 1536 x 1024 [16] -2.0; 768 x 2048 [32] -16; 512 x 256 [4] -1.4.  128 rows:
 // 2560 x 1024 [16] +21, [96] +7.9, [128] -1.6; 1280 x 1024 [16] +4.1, [128] -1.9.  (4 workers of 2560-256-40, 64 rows: 41.8 and 27.7 us.)
-// With momentum 128 rows, 2048 x 1024 [64] +12.8, [80] -0.2, [96] -3.6.  Up to eight row tiles there is next to nothing in it.
-// Ragged layers apart are products that spread over the chip however few the bands (kernels_bwd.hip), or with momentum the general
-// backward kernel.  32 rows: 2001 x 1100 [54] +7.3, [90] -3.5, 700 x 1300 [105] +0.2, [168] -5.6; 64 rows: 2001 x 1100 [90] +0.9, [144] -9.3,
+// With momentum 4096 x 2048 [64] 32 rows -26, 64 rows -5; 128 rows, 2048 x 1024 [64] +12.8, [80] -0.2, [96] -3.6.  Up to eight row tiles
+// there is next to nothing in it.
+// Ragged layers apart are products that spread over the chip however few the bands (kernels_bwd.hip).  32 rows: 2001 x 1100 [54] +7.3, [90]
+// -3.5, 700 x 1300 [105] +0.2, [168] -5.6; 64 rows: 2001 x 1100 [90] +0.9, [144] -9.3,
 // 3001 x 1472 [115] -9.0, 1000 x 555 [108] +4.2; 128 rows: 2001 x 1100 [144] +1.6, [216] -23.2, 4005 x 2688 [126] +15.9, [210] -84 (208
-// apart).  With momentum 64 rows: 700 x 1300 [21] -20, 2001 x 600 [50] +9.3, [120] -6.7, 4005 x 2688 [42] -8.3, [210] -103.
-// With momentum and more than the last-level cache holds, half of the compute units do not draw what memory gives: 4005 x 600 [120]
-// +40 us, 4096 x 1024 [128] +7, but 3001 x 1472 [115] -30.
+// apart).  With momentum 32 rows: 2001 x 1100 [90] -1.0, [144] -10.8, 4005 x 600 [120] -1.3; 64 rows: 3001 x 1472 [115] -1.5, 4005 x 2688
+// [126] +2.3, 2001 x 1100 [144] -13.9; 128 rows: 4005 x 600 [120] +40, 4005 x 2688 [126] +18.6, 2001 x 1100 [144] -11.2.
 static bool bwd_first_fwd_pays(const BwdArgs& p, bool ragged) {
   const int rows = (p.K + BT - 1) / BT, cols = p.Nn / BT;
   const long bands = (long)cols * p.n_groups;
   if (ragged && p.vel == nullptr) return bands >= (p.B <= 32 ? 96 : p.B <= 64 ? 112 : 152);
-  if (p.vel != nullptr && bands < 192 && (double)p.n_groups * p.K * p.ldw * 8.0 > 220e6) return false;
-  if (!ragged && rows <= 8) return true;
-  if (bands >= (p.B <= 64 ? 80 : p.vel != nullptr ? 96 : 128)) return true;
+  if (ragged) return bands >= (p.B <= 32 ? 100 : p.B <= 64 ? 132 : 144);
+  if (rows <= 8) return true;
+  if (bands >= (p.vel != nullptr ? (p.B <= 64 ? 64 : 96) : p.B <= 64 ? 80 : 128)) return true;
   return p.B <= 64 ? 5 * rows <= 8 * cols + 20 : 20 * rows <= 17 * cols + 60;
 }
 

@@ -29,8 +29,8 @@
 
 namespace prsgd {
 
-// One output tile of product p: workgroup `block` of the product's.
-template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
+// One output tile of product p: workgroup `block` of the product's.  MOM: momentum form of the update, v <- mu v + G, W <- W - gamma v.
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND, bool MOM>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   using E = typename T::elem;
   constexpr int NWAVE = WM * WN * WK, NTHR = 64 * NWAVE;
@@ -94,7 +94,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   constexpr int VPR_C = BN / 4, ROWS_PER_PASS = NTHR / VPR_C, EV = kIsDw ? BM / ROWS_PER_PASS : 1;
   static_assert(!kIsDw || (NTHR % VPR_C == 0 && BM % ROWS_PER_PASS == 0), "output tile must split evenly");
   const int e_row = tid / VPR_C, e_col = 4 * (tid % VPR_C);
-  f32x4_t w_old[EV];
+  f32x4_t w_old[EV], v_old[MOM ? EV : 1];
   if constexpr (kIsDw) if (fused) {
     const float* wtile = p.src + (size_t)g * p.src_gs + p.w_off + (size_t)m0 * p.ldw + n0;
     const bool nt_read = p.streaming && (p.src_gs != 0 || p.p_gs == 0);          // a source that several groups share is read again
@@ -105,6 +105,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
       const f32x4_t* wp = reinterpret_cast<const f32x4_t*>(
           wtile + (ok ? __umul24((uint32_t)r, (uint32_t)p.ldw) + (uint32_t)e_col : 0u));
       w_old[q] = nt_read ? __builtin_nontemporal_load(wp) : *wp;
+      if constexpr (MOM) {
+        const f32x4_t* vp = reinterpret_cast<const f32x4_t*>(p.vel + pg + p.w_off + (size_t)m0 * p.ldw + n0 +
+                                                             (ok ? __umul24((uint32_t)r, (uint32_t)p.ldw) + (uint32_t)e_col : 0u));
+        v_old[q] = p.streaming ? __builtin_nontemporal_load(vp) : *vp;
+      }
     }
   }
 
@@ -112,6 +117,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   static_assert(!kIsDw || BN <= NTHR, "one bias column per thread");
   const bool bias_thread = kIsDw && m0 == 0 && tid < BN && n0 + tid < p.N;
   const float b_old = fused && bias_thread ? p.src[(size_t)g * p.src_gs + p.b_off + n0 + tid] : 0.0f;
+  const float vb_old = MOM && bias_thread ? p.vel[pg + p.b_off + n0 + tid] : 0.0f;
 
   f32x16_t acc[TM][TN];
 #pragma unroll
@@ -247,9 +253,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
     for (int q = 0; q < EV; ++q) {
       const int r = q * ROWS_PER_PASS + e_row;
       if (m0 + r < p.M && n0 + e_col < p.N) {
-        const f32x4_t gr = c_read(r, e_col);
+        f32x4_t gr = c_read(r, e_col);
         const uint32_t off = __umul24((uint32_t)r, (uint32_t)p.ldw) + (uint32_t)e_col;
         if (fused) {
+          if constexpr (MOM) {
+            gr.x = fmaf(p.mu, v_old[q].x, gr.x);
+            gr.y = fmaf(p.mu, v_old[q].y, gr.y);
+            gr.z = fmaf(p.mu, v_old[q].z, gr.z);
+            gr.w = fmaf(p.mu, v_old[q].w, gr.w);
+            f32x4_t* vp = reinterpret_cast<f32x4_t*>(p.vel + tile + off);
+            if (p.streaming) __builtin_nontemporal_store(gr, vp);
+            else *vp = gr;
+          }
           f32x4_t w = w_old[q];
           w.x = fmaf(-p.lr, gr.x, w.x);
           w.y = fmaf(-p.lr, gr.y, w.y);
@@ -274,6 +289,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
       float colsum = cs_lds[tid];
 #pragma unroll
       for (int w = 1; w < WK; ++w) colsum += cs_lds[w * BN + tid];
+      if constexpr (MOM) {
+        colsum = fmaf(p.mu, vb_old, colsum);
+        p.vel[pg + p.b_off + n0 + tid] = colsum;
+      }
       if (fused) p.params[pg + p.b_off + n0 + tid] = fmaf(-p.lr, colsum, b_old);
       else p.grads[pg + p.b_off + n0 + tid] = colsum;
     }
@@ -281,9 +300,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   if constexpr (!kIsDw) out.store(p, g, ks, c_read);
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND, bool MOM>
 __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(GemmArgs p) {
-  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>(p, (int)blockIdx.x);
+  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND, MOM>(p, (int)blockIdx.x);
 }
 
 // Several products in one launch: product i has the workgroups first[i] .. first[i + 1] - 1 (past the last product: none).
@@ -291,18 +310,18 @@ struct GemmSet {
   int first[kMaxGemmSet];
   GemmArgs p[kMaxGemmSet];
 };
-template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND, bool MOM>
 __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_set_kernel(GemmSet set) {
   int i = 0, first = 0;
 #pragma unroll
   for (int k = 1; k < kMaxGemmSet; ++k)
     if ((int)blockIdx.x >= set.first[k]) { i = k; first = set.first[k]; }
-  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>(set.p[i], (int)blockIdx.x - first);
+  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND, MOM>(set.p[i], (int)blockIdx.x - first);
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND, bool MOM = false>
 static hipError_t launch_one(const GemmArgs& p, int n_groups, hipStream_t s) {
-  return launch_tiles<T, BM, BN, WK, S, WM * WN * WK, grouped_gemm_kernel<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>>(
+  return launch_tiles<T, BM, BN, WK, S, WM * WN * WK, grouped_gemm_kernel<T, BM, BN, WM, WN, WK, S, AKIND, BKIND, MOM>>(
       p, n_groups, s);
 }
 constexpr int kComputeUnits = 256;
@@ -444,9 +463,9 @@ static bool dw_large(const GemmArgs& p, int n_groups, bool bf16) {
 // (7 us for a single 64 x 64 tile: launch, first operand and weight loads, write-back), so the layers'
 // products, which depend on nothing of each other, share one launch (fp32 784-300-100-10, eight workers:
 // 11.8 + 6.9 + 7.1 us in three launches, 12.7 us in one).
-template <typename T, int BM, int BN, int S> static hipError_t launch_dw_set(const GemmArgs* ps, int n, int n_groups, hipStream_t s) {
+template <typename T, int BM, int BN, int WM, int S, bool MOM = false> static hipError_t launch_dw_set(const GemmArgs* ps, int n, int n_groups, hipStream_t s) {
   constexpr size_t kLds = gemm_lds_bytes<T, BM, BN, 1, S>();
-  auto kernel = grouped_gemm_set_kernel<T, BM, BN, 2, 2, 1, S, OP_TRANS, OP_TRANS>;
+  auto kernel = grouped_gemm_set_kernel<T, BM, BN, WM, 2, 1, S, OP_TRANS, OP_TRANS, MOM>;
   static std::atomic<bool> configured{false};
   if (!configured.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -467,11 +486,22 @@ template <typename T, int BM, int BN, int S> static hipError_t launch_dw_set(con
   }
   if (used == 0) return hipSuccess;
   for (int i = used; i < kMaxGemmSet; ++i) set.first[i] = total;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(256), kLds, s, set);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(128 * WM), kLds, s, set);
   return hipGetLastError();
+}
+// With momentum, bf16 layers of up to 128 rows: large tiles in eight wavefronts, since old weights and velocities of four do not fit
+// their registers.
+static hipError_t launch_dw_momentum(const GemmArgs* ps, int n, int n_groups, bool bf16, hipStream_t s) {
+  if (!bf16) return hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i)
+    if (ps[i].epi != EPI_DW_FUSED || ps[i].vel == nullptr || ps[i].Kc > 128) return hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i)
+    if (dw_large(ps[i], n_groups, bf16)) return launch_dw_set<TBF16, 128, 128, 4, 2, true>(ps, n, n_groups, s);
+  return launch_dw_set<TBF16, 64, 64, 2, 2, true>(ps, n, n_groups, s);
 }
 hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hipStream_t s) {
   if (n < 0 || n > kMaxGemmSet) return hipErrorInvalidValue;
+  if (n > 0 && ps[0].vel != nullptr) return launch_dw_momentum(ps, n, n_groups, bf16, s);
   if (n == 1 && dw_large(ps[0], n_groups, bf16))
     return launch_one<TBF16, 128, 128, 2, 2, 1, 2, OP_TRANS, OP_TRANS>(ps[0], n_groups, s);
   // contractions of one or two tiles: two stages, and the more workgroups on a compute unit
@@ -487,9 +517,9 @@ hipError_t launch_gemm_dw(const GemmArgs* ps, int n, int n_groups, bool bf16, hi
                    : launch_one<TF32, 64, 64, 2, 2, 1, 4, OP_TRANS, OP_TRANS>(ps[0], n_groups, s);
   }
   for (int i = 0; i < n; ++i)
-    if (dw_large(ps[i], n_groups, bf16)) return launch_dw_set<TBF16, 128, 128, 2>(ps, n, n_groups, s);
-  if (bf16) return shallow ? launch_dw_set<TBF16, 64, 64, 2>(ps, n, n_groups, s) : launch_dw_set<TBF16, 64, 64, 4>(ps, n, n_groups, s);
-  return shallow ? launch_dw_set<TF32, 64, 64, 2>(ps, n, n_groups, s) : launch_dw_set<TF32, 64, 64, 4>(ps, n, n_groups, s);
+    if (dw_large(ps[i], n_groups, bf16)) return launch_dw_set<TBF16, 128, 128, 2, 2>(ps, n, n_groups, s);
+  if (bf16) return shallow ? launch_dw_set<TBF16, 64, 64, 2, 2>(ps, n, n_groups, s) : launch_dw_set<TBF16, 64, 64, 2, 4>(ps, n, n_groups, s);
+  return shallow ? launch_dw_set<TF32, 64, 64, 2, 2>(ps, n, n_groups, s) : launch_dw_set<TF32, 64, 64, 2, 4>(ps, n, n_groups, s);
 }
 
 }  // namespace prsgd

@@ -646,6 +646,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
       if (l > 1 && !(l == L && head_delta)) LAUNCH(ctx, KK_BWD, launch_gemm_dx(dx_args(l), N, true, s));
       GemmArgs p = dw_args(l);
       p.epi = EPI_DW_FUSED;
+      p.vel = ctx->velocity(); p.mu = c.momentum;
       const int rc = dw.add(p, N, KK_BWD);
       if (rc != PRSGD_OK) return rc;
       continue;

@@ -58,6 +58,7 @@ struct GemmArgs {
   int b_once;                         // ... and every element of B is read by one workgroup only (filled in by the launcher)
   int act;                            // PRSGD_TANH | PRSGD_RELU
   float lr;
+  float* vel; float mu;               // update with momentum: velocities, replica stride m_pad (nullptr: without)
   // parameters / gradients (fp32, replica stride m_pad), bf16 shadow of the parameters
   float* params; float* grads; uint16_t* shadow; long p_gs;
   // where the old parameters (forward: the bias; update: weights and bias) are read from: the

@@ -42,3 +42,28 @@ def test_layers_apart_and_walked(dims, batch, n):
     for x, loss in outs:
         assert rel_err(x, want["x"]) <= 5e-3
         assert np.allclose(loss, want["losses"], rtol=2e-2, atol=2.0 ** -20)
+
+
+# momentum in the weight gradients' launch: few and many bands, one layer and several of ragged widths, tiles of 64 and of 128, whole layers
+# whose walk is too long, one row and 128, and a replica set that is streamed
+@pytest.mark.parametrize("dims,batch,n", [
+    ((130, 70), 40, 5), ((300, 200, 10), 33, 3), ((40, 66, 70, 80, 50, 30, 9), 33, 3), ((65, 129, 64, 30), 1, 2),
+    ((1000, 1030, 20), 100, 8), ((1024, 1024, 1024, 10), 128, 2), ((2000, 1300, 10), 24, 20),
+])
+@pytest.mark.parametrize("restart", ["keep", "average", "reset"])
+def test_momentum_of_layers_apart(dims, batch, n, restart):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=dims, batch=batch, n_workers=n, gemm_dtype="bf16", activation="tanh", rows_per_worker=64, lr=0.002, interval=2,
+                  iterations=5).scaled(momentum=0.9, momentum_restart=restart)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp)
+    P.prsgd_profile_enable(h, True)
+    P.prsgd_run(h, w.iterations, w.interval)
+    names = {r["name"] for r in P.prsgd_profile_read(h)}
+    assert "gemm_bwd" in names and (restart == "reset" or "sgd_update" not in names)
+    want = oracle_run(w, inp, momentum=0.9, momentum_restart=restart)
+    assert rel_err(D.read_all(h), want["x"]) <= 5e-3
+    v = np.stack([P.prsgd_read_velocity(h, i) for i in range(n)])
+    assert rel_err(v, want["v"]) <= 2e-2                  # the bounds of the other momentum runs with bf16 operands
+    P.prsgd_destroy(h)

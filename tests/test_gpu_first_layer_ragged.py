@@ -13,11 +13,11 @@ pytestmark = pytest.mark.gpu
 
 # rows of W_1: whole tiles, one element past them, one short of them, nothing of a last request but its first element; columns that the
 # layout pads, by one and by 63; minibatches of one row, around a block of 32 and below 128; bands
-# of 64 and of 128 columns
+# of 64 and of 128 columns; workers enough that the layer is fused with momentum and without
 @pytest.mark.parametrize("momentum", [0.0, 0.9])
 @pytest.mark.parametrize("dims,batch,n", [
-    ((576, 512, 10), 32, 13), ((577, 513, 10), 32, 11), ((575, 575, 40, 10), 31, 11), ((520, 576, 10), 1, 11),
-    ((513, 640, 10), 33, 12), ((641, 700, 33), 63, 11), ((639, 512, 10), 65, 19), ((704, 1025, 10), 96, 9), ((1001, 520, 10), 127, 17),
+    ((576, 512, 10), 32, 13), ((577, 513, 10), 32, 12), ((575, 575, 40, 10), 31, 12), ((520, 576, 10), 1, 12),
+    ((513, 640, 10), 33, 14), ((641, 700, 33), 63, 12), ((639, 512, 10), 65, 19), ((704, 1025, 10), 96, 9), ((1001, 520, 10), 127, 17),
     ((768, 600, 10), 128, 16), ((515, 1020, 10), 20, 32),
     ((2101, 1190, 10), 8, 20),                       # a replica set that is streamed
 ])
