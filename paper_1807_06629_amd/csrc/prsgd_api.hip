@@ -249,6 +249,7 @@ struct prsgd_ctx {
   // iteration h1_t on batch set h1_batch while the replicas are untouched (-1: none)
   int64_t h1_t;
   int h1_batch;
+  bool recorded;      // steps were recorded into a graph, whose replays move the points unseen by h1_t and shadow1_stale
   bool restart_fusion;  // prsgd_run: take an epoch's last iteration and the restart as one pass
   bool first_fusion;    // let the first layer's backward kernel run the next forward product
   bool shadow1_stale;   // that kernel skipped the bf16 shadow of W_1 (nothing reads it while the
@@ -349,6 +350,7 @@ struct Timed {
 
 int materialize(prsgd_ctx* ctx);
 void strike_waiting(prsgd_ctx* ctx);
+bool is_capturing(hipStream_t stream);
 
 // bf16 shadow of W_1 of every replica from its fp32 master (after first-layer kernels that skipped it)
 int refresh_first_shadow(prsgd_ctx* ctx) {
@@ -469,7 +471,12 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
 
   // forward.  H_1 may already be there: the previous iteration's first-layer backward kernel computes
   // it from the weights it writes, for this iteration's minibatch
-  const bool h1_ready = fused_bwd && !from_mean && L >= 2 && ctx->h1_t == t && ctx->h1_batch == bk;
+  // A graph of single steps reads H_1 and the shadow of W_1 as they are when it is replayed: ragged layers leave both as
+  // every pass by itself does, from the first recording on.  (Layers of whole tiles are recorded with what is there.)
+  const bool whole_first = (B == 32 || B == 64 || B == 128) && lo.d[0] % 128 == 0 && lo.d[1] % 64 == 0;
+  if (!whole_first && !ctx->recorded) ctx->recorded = is_capturing(s);
+  const bool ahead = whole_first || !ctx->recorded;
+  const bool h1_ready = ahead && fused_bwd && !from_mean && L >= 2 && ctx->h1_t == t && ctx->h1_batch == bk;
   ctx->h1_t = -1;
   if (!h1_ready && ctx->shadow1_stale && !from_mean) {
     const int rc = refresh_first_shadow(ctx);
@@ -525,7 +532,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
     q.n_groups = active.next;
     return q;
   };
-  const bool first_fused = fused_bwd && !fuse_average && L >= 2 && ctx->first_fusion && prefetch && bwd_first_fwd_applies(first_args());
+  const bool first_fused = fused_bwd && !fuse_average && L >= 2 && ctx->first_fusion && ahead && prefetch && bwd_first_fwd_applies(first_args());
   int n_apart = 0, widest_apart = 0;
   for (int l = L; fused_bwd && l >= (first_fused ? 2 : 1); --l) {
     if (!bwd_products_apart(bwd_args(l))) continue;
@@ -1107,6 +1114,7 @@ int init_common(const prsgd_config* cfg, const float* x0_host, const void* featu
   ctx->batch_cur = 0;
   ctx->h1_t = -1;
   ctx->h1_batch = 0;
+  ctx->recorded = false;
   ctx->first_fusion = true;
   ctx->restart_fusion = true;
   ctx->shadow1_stale = false;
@@ -1249,6 +1257,8 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
     if (steps_host[i] > k_max) k_max = steps_host[i];
     if (steps_host[i] < k_min) k_min = steps_host[i];
   }
+  // a graph takes whole epochs of every worker only: its replays would keep the step counts of the recording
+  if (is_capturing(ctx->stream)) return hip_fail(ctx, hipErrorStreamCaptureUnsupported, "worker step counts");
   // a worker that takes no step must still hold the restart point: broadcast it first.  Layer by layer the
   // steps that every worker takes run unmasked, and the first of them starts from the average itself
   // (16 workers of 3072-1024-1024-10, one to four steps: broadcast 67 us, first step 72 + 22 us for layer 1

@@ -43,3 +43,34 @@ def test_ragged_first_layers(dims, batch, n, momentum):
         assert np.allclose(loss, want["losses"], rtol=2e-2, atol=2.0 ** -20)
     # the two forms differ by the order of the bias sums, if at all
     assert rel_err(outs[0][0], outs[1][0]) <= 1e-3
+
+
+# a recorded step reads no activation and no shadow that an eager step left or left stale, also where the layer is fused outside of the graph
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_recorded_steps_of_a_ragged_first_layer(momentum):
+    assert torch.cuda.is_available()
+    from paper_1807_06629_amd import drivers as D, prsgd as P
+    w = small_mlp(dims=(577, 513, 10), batch=32, n_workers=12, gemm_dtype="bf16", activation="tanh", rows_per_worker=64, lr=0.005,
+                  interval=50).scaled(momentum=momentum)
+    inp = inputs_for(w)
+    stream = torch.cuda.Stream()
+    a, b = D.open_workload(w, inp, stream=stream), D.open_workload(w, inp, stream=stream)
+    with torch.cuda.stream(stream):
+        P.prsgd_local_steps(a, 2)
+        P.prsgd_local_steps(b, 2)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            P.prsgd_local_steps(a, 1)
+        P.prsgd_set_first_layer_fusion(b, False)          # the two forms of a ragged layer do not agree in every bit
+        for _ in range(3):
+            graph.replay()
+            stream.synchronize()
+            P.prsgd_set_iteration(b, 2)
+            P.prsgd_local_steps(b, 1)
+            assert np.array_equal(D.read_all(a), D.read_all(b))
+        P.prsgd_local_steps(a, 2)                          # eager again, from the points that the replays left
+        P.prsgd_local_steps(b, 2)
+        assert np.array_equal(D.read_all(a), D.read_all(b))
+    P.prsgd_destroy(a)
+    P.prsgd_destroy(b)

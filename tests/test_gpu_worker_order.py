@@ -86,3 +86,32 @@ def test_first_layer_of_the_workers_that_go_on(P, D, steps, steps_before):
         P.prsgd_destroy(h)
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+def test_an_epoch_is_not_captured(P, D):
+    """Refused before anything is launched; what the graph holds beside it still replays."""
+    w = small_mlp(dims=(100, 72, 40, 10), batch=24, n_workers=3, gemm_dtype="bf16", activation="tanh", rows_per_worker=64, lr=0.02)
+    inp = inputs_for(w)
+    stream = torch.cuda.Stream()
+    a, b = D.open_workload(w, inp, stream=stream), D.open_workload(w, inp, stream=stream)
+    with torch.cuda.stream(stream):
+        P.prsgd_local_steps(a, 1)
+        P.prsgd_local_steps(b, 1)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            with pytest.raises(RuntimeError, match="worker step counts"):
+                P.prsgd_local_steps_hetero(a, [1, 2, 0])
+            P.prsgd_local_steps(a, 1)
+        assert P.prsgd_iteration(a) == 2
+        for _ in range(3):
+            graph.replay()
+            P.prsgd_set_iteration(b, 1)
+            P.prsgd_local_steps(b, 1)
+            assert np.array_equal(D.read_all(a), D.read_all(b))
+        P.prsgd_local_steps_hetero(a, [1, 2, 0])
+        P.prsgd_set_iteration(b, 2)
+        P.prsgd_local_steps_hetero(b, [1, 2, 0])
+        assert np.array_equal(D.read_all(a), D.read_all(b))
+    P.prsgd_destroy(a)
+    P.prsgd_destroy(b)
