@@ -32,7 +32,8 @@ KERNEL_SYMBOL = {
     "gather": "gather_kernel", "gemm_fwd": "grouped_rows_kernel / grouped_gemm_kernel<.., OP_CONTIG, OP_TRANS>",
     "gemm_dx": "grouped_rows_kernel / grouped_gemm_kernel<.., OP_CONTIG, OP_CONTIG>",
     "gemm_dw": "grouped_gemm_kernel<.., OP_TRANS, OP_TRANS>",
-    "gemm_bwd": "grouped_bwd_full_kernel (grouped_bwd_kernel for layers with partial tiles)",
+    "gemm_bwd": "grouped_bwd_full_kernel (grouped_bwd_kernel for layers with partial tiles; layers of few bands as "
+                "separate products)",
     "softmax_xent": "softmax_xent_kernel / softmax_xent_row_kernel (257 to 1024 classes) / softmax_xent_narrow_kernel (few "
                     "classes: with the logits product, and the delta below where that pays); loss head + row gather of the "
                     "next iteration",
@@ -45,8 +46,8 @@ KERNEL_SYMBOL = {
     "mlp2_epoch": "mlp2_epoch_kernel",
     "gemm_bwd_first": "bwd_first_fwd_kernel (layer 1: backward step + next forward product)",
     "refresh_shadow": "refresh_shadow_kernel (bf16 image of W_1 when the first-layer chain breaks)",
-    "step_mean": "grouped_gemm_kernel<.., OP_TRANS, OP_TRANS> (the minibatches of all workers stacked "
-                 "into one contraction; small layers together: grouped_gemm_set_kernel)",
+    "step_mean": "grouped_gemm_set_kernel<.., OP_TRANS, OP_TRANS> (the minibatches of all workers stacked "
+                 "into one contraction, all layers in one launch)",
 }
 
 
