@@ -26,6 +26,13 @@
  *     stream given to prsgd_init.  Calls are asynchronous with respect to the host except
  *     the prsgd_read_* / prsgd_write_* calls, which synchronise that stream.
  *   - A context is not thread-safe; use it from one host thread at a time.
+ *   - prsgd_local_steps, prsgd_average and prsgd_run may be recorded into a HIP graph (stream capture).  A recording counts as
+ *     taken (the iteration counter moves on, so replay it before the next call), and every replay takes the recorded iteration
+ *     numbers again, from the points as they are, between whatever other calls and replays.  A first recording that finds the
+ *     workers at a deferred average (prsgd_average) starts every replay from the average that the library wrote last instead:
+ *     record behind local steps, or with prsgd_set_lazy_restart(ctx, 0), where that is not meant.  From its first recording on a
+ *     context prepares nothing from one call to the next and ends no call at a deferred average, so that calls of many
+ *     iterations pay best.
  */
 #ifndef PRSGD_H
 #define PRSGD_H

@@ -249,7 +249,7 @@ struct prsgd_ctx {
   // iteration h1_t on batch set h1_batch while the replicas are untouched (-1: none)
   int64_t h1_t;
   int h1_batch;
-  bool recorded;      // steps were recorded into a graph, whose replays move the points unseen by h1_t and shadow1_stale
+  bool recorded;      // calls were recorded into a graph, whose replays move the points and rewrite the minibatch sets unseen by the host
   bool restart_fusion;  // prsgd_run: take an epoch's last iteration and the restart as one pass
   bool first_fusion;    // let the first layer's backward kernel run the next forward product
   bool shadow1_stale;   // that kernel skipped the bf16 shadow of W_1 (nothing reads it while the
@@ -284,6 +284,8 @@ struct prsgd_ctx {
     return cfg.model == PRSGD_LSQ || use_fused2 ||
            (bf16 && cfg.fused_update && prsgd::bwd_fused_supported(cfg.batch));
   }
+  // local steps are launches of single layers
+  bool layered() const { return cfg.model == PRSGD_MLP && !use_fused2; }
   // set by a launch whose workgroups gave up waiting for each other (nullptr: no such launches)
   unsigned int* abort_flag() const {
     if (use_fused2) return at<unsigned int>(cv.sync) + (size_t)cfg.n_workers * 32;
@@ -350,7 +352,7 @@ struct Timed {
 
 int materialize(prsgd_ctx* ctx);
 void strike_waiting(prsgd_ctx* ctx);
-bool is_capturing(hipStream_t stream);
+bool is_capturing(hipStream_t stream, bool unknown = true);
 
 // bf16 shadow of W_1 of every replica from its fp32 master (after first-layer kernels that skipped it)
 int refresh_first_shadow(prsgd_ctx* ctx) {
@@ -411,7 +413,7 @@ struct Active {
 // ybar; the replicas are not rewritten and the context ends "at the mean".  With every worker
 // already at ybar (I = 1) it is one mini-batch SGD step with the N B samples of all workers (first
 // footnote of Section 1).
-// A next iteration that every worker takes also has its first activation prepared.
+// The workers that go on have the minibatch of the next iteration drawn, and its first activation computed where that pays.
 int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average = false) {
   const prsgd_config& c = ctx->cfg;
   const Layout& lo = ctx->lo;
@@ -471,12 +473,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
 
   // forward.  H_1 may already be there: the previous iteration's first-layer backward kernel computes
   // it from the weights it writes, for this iteration's minibatch
-  // A graph of single steps reads H_1 and the shadow of W_1 as they are when it is replayed: ragged layers leave both as
-  // every pass by itself does, from the first recording on.  (Layers of whole tiles are recorded with what is there.)
-  const bool whole_first = (B == 32 || B == 64 || B == 128) && lo.d[0] % 128 == 0 && lo.d[1] % 64 == 0;
-  if (!whole_first && !ctx->recorded) ctx->recorded = is_capturing(s);
-  const bool ahead = whole_first || !ctx->recorded;
-  const bool h1_ready = ahead && fused_bwd && !from_mean && L >= 2 && ctx->h1_t == t && ctx->h1_batch == bk;
+  const bool h1_ready = fused_bwd && !from_mean && L >= 2 && ctx->h1_t == t && ctx->h1_batch == bk;
   ctx->h1_t = -1;
   if (!h1_ready && ctx->shadow1_stale && !from_mean) {
     const int rc = refresh_first_shadow(ctx);
@@ -532,7 +529,7 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
     q.n_groups = active.next;
     return q;
   };
-  const bool first_fused = fused_bwd && !fuse_average && L >= 2 && ctx->first_fusion && ahead && prefetch && bwd_first_fwd_applies(first_args());
+  const bool first_fused = fused_bwd && !fuse_average && L >= 2 && ctx->first_fusion && prefetch && bwd_first_fwd_applies(first_args());
   int n_apart = 0, widest_apart = 0;
   for (int l = L; fused_bwd && l >= (first_fused ? 2 : 1); --l) {
     if (!bwd_products_apart(bwd_args(l))) continue;
@@ -690,12 +687,28 @@ int mlp_step(prsgd_ctx* ctx, int64_t t, const Active& active, bool fuse_average 
   return PRSGD_OK;
 }
 
-// An iteration of every worker, and one behind it.
-Active every_worker(const prsgd_ctx* ctx) {
+// An iteration of every worker, and one behind it.  `last` one of a call: nothing is prepared behind it if the context has been recorded.
+Active every_worker(const prsgd_ctx* ctx, bool last) {
   Active a;
-  a.now = a.next = ctx->cfg.n_workers;
+  a.now = ctx->cfg.n_workers;
+  a.next = last && ctx->recorded ? 0 : a.now;
   return a;
 }
+
+// Around every call that enqueues steps or restarts.  A graph that holds such calls takes the recorded launches again, with their buffers
+// and iteration numbers, as often as it is replayed and between whatever calls, and the host learns nothing of it.  So from its first
+// recording on a context hands no more than the points from one call to the next, in the replicas and with their shadows: a call's
+// first step draws its own minibatch and computes its own first activation, its last one prepares nothing, and a restart at its end is
+// broadcast.  (Without this a replayed step multiplied what the steps after the recording had drawn and computed ahead.)
+// `steps`: up to the one whose row numbers stay the newest; they end in set 0, as those of every replay do.
+void begin_call(prsgd_ctx* ctx, int64_t steps) {
+  if (!ctx->recorded) ctx->recorded = is_capturing(ctx->stream, false);
+  if (!ctx->recorded) return;
+  ctx->batch_t[0] = ctx->batch_t[1] = -1;
+  ctx->h1_t = -1;
+  if (steps > 0 && ctx->layered()) ctx->batch_cur = (int)((steps - 1) & 1);
+}
+int end_call(prsgd_ctx* ctx) { return ctx->recorded ? materialize(ctx) : PRSGD_OK; }
 
 Fused2Args fused2_args(prsgd_ctx* ctx, int k, const int* worker_steps) {
   const prsgd_config& c = ctx->cfg;
@@ -887,11 +900,11 @@ prsgd_ctx* g_waiting = nullptr;      // list of such contexts
 uint64_t g_waiting_seq = 0;          // launches recorded so far
 std::mutex g_waiting_mutex;
 
-bool is_capturing(hipStream_t stream) {
+bool is_capturing(hipStream_t stream, bool unknown) {
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
   (void)hipGetLastError();           // the default stream while another one is being captured
-  return true;
+  return unknown;
 }
 // The rules below, with g_waiting_mutex held.  A stream is stood for by the first of its contexts in the list.
 bool stands_for_stream(const prsgd_ctx* c) {
@@ -1215,9 +1228,12 @@ int prsgd_init_static(const prsgd_config* cfg, const float* x0_host, const void*
   return init_common(cfg, x0_host, features_dev, targets_dev, params_dev, ws, hip_stream, dev, out_ctx);
 }
 
-int prsgd_local_steps(prsgd_ctx* ctx, int32_t k) {
-  if (ctx == nullptr) return PRSGD_EINVAL;
-  if (k < 0) return set_err(ctx, PRSGD_EINVAL, "k must be >= 0");
+}  // extern "C"
+
+namespace {
+
+// k local steps; `last`: nothing of the call comes behind them
+int local_steps(prsgd_ctx* ctx, int32_t k, bool last) {
   if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
   const prsgd_config& c = ctx->cfg;
   if (c.model == PRSGD_LSQ) {
@@ -1237,11 +1253,53 @@ int prsgd_local_steps(prsgd_ctx* ctx, int32_t k) {
     return PRSGD_OK;
   }
   for (int32_t s = 0; s < k; ++s) {
-    const int rc = mlp_step(ctx, ctx->t + 1, every_worker(ctx));
+    const int rc = mlp_step(ctx, ctx->t + 1, every_worker(ctx, last && s + 1 == k));
     if (rc != PRSGD_OK) return rc;
     ctx->t += 1;
   }
   return PRSGD_OK;
+}
+
+int average(prsgd_ctx* ctx) {
+  if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
+  if (ctx->at_mean) return PRSGD_OK;        // all workers already sit at their node average
+  ctx->h1_t = -1;                           // an activation computed ahead belongs to the old points
+  if (ctx->velocity() != nullptr && ctx->cfg.momentum_restart != PRSGD_MOM_KEEP) {
+    // the paper leaves the momentum buffers at a restart open: average them like the points,
+    // or start every epoch without momentum
+    if (ctx->cfg.momentum_restart == PRSGD_MOM_AVERAGE)
+      LAUNCH(ctx, KK_AVERAGE, launch_average(ctx->velocity(), nullptr, ctx->lo.m_pad, ctx->cfg.n_workers,
+                                             ctx->streamed.average, ctx->stream));
+    else
+      LAUNCH(ctx, KK_UPDATE, launch_fill_zero(ctx->velocity(), (size_t)ctx->cfg.n_workers * ctx->lo.m_pad,
+                                              ctx->stream));
+  }
+  if (ctx->lazy_restart && ctx->can_start_from_mean()) {
+    // eq. (2) without the broadcast: ybar is written once; the next local iteration reads it as
+    // every worker's starting point and writes the replicas  x_i = ybar - gamma G_i  itself
+    LAUNCH(ctx, KK_RESTART_MEAN,
+           launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), ctx->lo.m_pad, ctx->cfg.n_workers,
+                       ctx->streamed.mean, ctx->stream));
+    ctx->at_mean = true;
+    return PRSGD_OK;
+  }
+  LAUNCH(ctx, KK_AVERAGE,
+         launch_average(ctx->params, ctx->shadow(), ctx->lo.m_pad, ctx->cfg.n_workers, ctx->streamed.average,
+                        ctx->stream));
+  ctx->shadow1_stale = false;               // the averaging kernel rewrites every shadow
+  return PRSGD_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int prsgd_local_steps(prsgd_ctx* ctx, int32_t k) {
+  if (ctx == nullptr) return PRSGD_EINVAL;
+  if (k < 0) return set_err(ctx, PRSGD_EINVAL, "k must be >= 0");
+  begin_call(ctx, k);
+  const int rc = local_steps(ctx, k, true);
+  return rc != PRSGD_OK ? rc : end_call(ctx);
 }
 
 int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
@@ -1263,7 +1321,8 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
   // steps that every worker takes run unmasked, and the first of them starts from the average itself
   // (16 workers of 3072-1024-1024-10, one to four steps: broadcast 67 us, first step 72 + 22 us for layer 1
   // with private weights; 1594 -> 1338 us for two epochs).
-  const bool layers = c.model == PRSGD_MLP && !ctx->use_fused2;
+  const bool layers = ctx->layered();
+  begin_call(ctx, k_min > 1 ? k_min : 1);         // masked steps leave their rows beside those of the last step of all workers
   if (!layers || k_min == 0) {
     const int mrc = materialize(ctx);
     if (mrc != PRSGD_OK) return mrc;
@@ -1296,7 +1355,7 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
   int rc = PRSGD_OK, idx_set = -1;
   if (k_min == 0 && k_max > 0) ctx->batch_t[0] = ctx->batch_t[1] = -1;   // drawn for workers that take no step as well
   for (int32_t s = 0; s < k_max && rc == PRSGD_OK; ++s) {
-    Active a = every_worker(ctx);
+    Active a = every_worker(ctx, s + 1 == k_max);
     if (s >= k_min) {
       a.order = steps_dev;
       a.now = workers_at(s);
@@ -1320,38 +1379,15 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
 
 int prsgd_average(prsgd_ctx* ctx) {
   if (ctx == nullptr) return PRSGD_EINVAL;
-  if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
-  if (ctx->at_mean) return PRSGD_OK;        // all workers already sit at their node average
-  ctx->h1_t = -1;                           // an activation computed ahead belongs to the old points
-  if (ctx->velocity() != nullptr && ctx->cfg.momentum_restart != PRSGD_MOM_KEEP) {
-    // the paper leaves the momentum buffers at a restart open: average them like the points,
-    // or start every epoch without momentum
-    if (ctx->cfg.momentum_restart == PRSGD_MOM_AVERAGE)
-      LAUNCH(ctx, KK_AVERAGE, launch_average(ctx->velocity(), nullptr, ctx->lo.m_pad, ctx->cfg.n_workers,
-                                             ctx->streamed.average, ctx->stream));
-    else
-      LAUNCH(ctx, KK_UPDATE, launch_fill_zero(ctx->velocity(), (size_t)ctx->cfg.n_workers * ctx->lo.m_pad,
-                                              ctx->stream));
-  }
-  if (ctx->lazy_restart && ctx->can_start_from_mean()) {
-    // eq. (2) without the broadcast: ybar is written once; the next local iteration reads it as
-    // every worker's starting point and writes the replicas  x_i = ybar - gamma G_i  itself
-    LAUNCH(ctx, KK_RESTART_MEAN,
-           launch_mean(ctx->params, ctx->mean(), ctx->mean_shadow(), ctx->lo.m_pad, ctx->cfg.n_workers,
-                       ctx->streamed.mean, ctx->stream));
-    ctx->at_mean = true;
-    return PRSGD_OK;
-  }
-  LAUNCH(ctx, KK_AVERAGE,
-         launch_average(ctx->params, ctx->shadow(), ctx->lo.m_pad, ctx->cfg.n_workers, ctx->streamed.average,
-                        ctx->stream));
-  ctx->shadow1_stale = false;               // the averaging kernel rewrites every shadow
-  return PRSGD_OK;
+  begin_call(ctx, 0);
+  const int rc = average(ctx);
+  return rc != PRSGD_OK ? rc : end_call(ctx);
 }
 
 int prsgd_set_lazy_restart(prsgd_ctx* ctx, int32_t on) {
   if (ctx == nullptr) return PRSGD_EINVAL;
   if (!on) {
+    begin_call(ctx, 0);
     const int rc = materialize(ctx);
     if (rc != PRSGD_OK) return rc;
   }
@@ -1363,6 +1399,7 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
   if (ctx == nullptr) return PRSGD_EINVAL;
   if (iterations < 0 || interval < 1) return set_err(ctx, PRSGD_EINVAL, "iterations >= 0, interval >= 1");
   int64_t left = iterations;
+  begin_call(ctx, iterations);
   // Restarts that need no launch of their own: the whole run, up to a restart at its end, is one launch (least squares, 4
   // workers of 64 floats, 256 iterations with a restart after every eighth: 530 us with two launches per epoch, 200 us).
   // Per-kernel timing keeps them apart, as launches of their own.
@@ -1394,7 +1431,7 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
     ctx->t += k;
     left -= k;
     if (ctx->t % interval == 0) {
-      const int rc = prsgd_average(ctx);
+      const int rc = average(ctx);
       if (rc != PRSGD_OK) return rc;
     }
   }
@@ -1407,11 +1444,11 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
     if (can_fuse && interval - (ctx->t % interval) <= left) {
       const int64_t k_epoch = interval - (ctx->t % interval);
       if (k_epoch > 1) {
-        const int rc = prsgd_local_steps(ctx, (int32_t)(k_epoch - 1));
+        const int rc = local_steps(ctx, (int32_t)(k_epoch - 1), false);
         if (rc != PRSGD_OK) return rc;
       }
       if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
-      const int rc = mlp_step(ctx, ctx->t + 1, every_worker(ctx), true);
+      const int rc = mlp_step(ctx, ctx->t + 1, every_worker(ctx, k_epoch == left), true);
       if (rc != PRSGD_OK) return rc;
       ctx->t += 1;
       left -= k_epoch;
@@ -1419,15 +1456,15 @@ int prsgd_run(prsgd_ctx* ctx, int64_t iterations, int32_t interval) {
     }
     int64_t k = interval - (ctx->t % interval);      // steps until the next multiple of I
     if (k > left) k = left;
-    int rc = prsgd_local_steps(ctx, (int32_t)k);
+    int rc = local_steps(ctx, (int32_t)k, k == left);
     if (rc != PRSGD_OK) return rc;
     left -= k;
     if (ctx->t % interval == 0) {
-      rc = prsgd_average(ctx);
+      rc = average(ctx);
       if (rc != PRSGD_OK) return rc;
     }
   }
-  return PRSGD_OK;
+  return end_call(ctx);
 }
 
 int prsgd_read_params(prsgd_ctx* ctx, int32_t worker, float* out_host, size_t m) {

@@ -69,6 +69,7 @@ def test_recorded_steps_of_a_ragged_first_layer(momentum):
             P.prsgd_set_iteration(b, 2)
             P.prsgd_local_steps(b, 1)
             assert np.array_equal(D.read_all(a), D.read_all(b))
+        P.prsgd_set_first_layer_fusion(a, False)           # the steps of one call are fused again behind a recording
         P.prsgd_local_steps(a, 2)                          # eager again, from the points that the replays left
         P.prsgd_local_steps(b, 2)
         assert np.array_equal(D.read_all(a), D.read_all(b))
