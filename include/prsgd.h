@@ -146,6 +146,7 @@ int prsgd_local_steps(prsgd_ctx* ctx, int32_t k);
  * local iterations; a worker that has finished keeps its point (the paper's imagined
  * zero-gradient steps).  The iteration counter advances by max_i steps_host[i].
  * Not defined with momentum (a zero-gradient step would still move the point): PRSGD_EINVAL.
+ * Not recorded: PRSGD_EHIP while the stream is being captured, since a replay would keep the step counts; the capture goes on.
  */
 int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host /* [N] */);
 

@@ -72,7 +72,10 @@ int prsgd_set_epoch_wait_limit(prsgd_ctx* ctx, uint32_t polls);
  * on = 1 (default): on MLPs with bf16 operands the backward kernel of the first layer also runs the
  * first forward product of the next local iteration on the weights it writes (the minibatch of
  * iteration t + 1 is drawn during iteration t), so W_1 crosses HBM once per iteration.  on = 0: two
- * separate launches.  The results are identical bit for bit; tests compare the two.
+ * separate launches.  Which layers are taken is a rule on their size.  The results of layers of whole tiles (32, 64 or 128
+ * minibatch rows, d_0 a multiple of 128 from 256 on, d_1 one of 64, and of 128 where d_0 exceeds 512) are identical bit for bit;
+ * those of the other layers (d_0 from 512 on, up to 128 rows, d_1 from 512 on or padded to a multiple of 64) up to the order in
+ * which the bias gradients are summed in fp32.  Tests compare the two.
  */
 int prsgd_set_first_layer_fusion(prsgd_ctx* ctx, int32_t on);
 

@@ -27,11 +27,12 @@
 // Measured against five barriers per tile and X tiles through registers: 8 x (4096 x 4096), 128 rows 242 ->
 // 208 us (5.2 TB/s of weight bytes); 16 x (3072 x 1024), 64 rows 85 -> 76 us (5.3 TB/s).
 //
-// Every output block accumulates over k in the order of the stand-alone forward product, and the bias
-// is summed as in the other layers' kernel, so H_1^{t+1} and the parameters have the bits the two
-// separate launches give.  Whole tiles (B = 32 MB, d_0 a multiple of 128, d_1 of 64), and from 512 rows of W_1 on any minibatch and
-// any rows with columns that the layout pads to whole tiles: 5 workers of 4005-2688-100, 64 rows, 177 -> 104 us per iteration, 12 of
-// 3001-1472-333-20 208 -> 146; with momentum 282 -> 179 and 316 -> 257.
+// Every output block accumulates over k in the order of the stand-alone forward product.  Layers of whole tiles (bwd_first_fwd_shape)
+// sum the bias as the other layers' whole-tile kernel does, so H_1^{t+1} and the parameters have the bits the two separate launches
+// give.  From 512 rows of W_1 on any minibatch and any rows are taken too, with columns that the layout pads to whole tiles; apart, such
+// layers run in kernels that sum the bias in another order, and the two forms agree up to its rounding (asserted: 1e-3 of the points after
+// seven steps).  5 workers of 4005-2688-100, 64 rows, 177 -> 104 us per iteration, 12 of 3001-1472-333-20 208 -> 146; with momentum
+// 282 -> 179 and 316 -> 257.
 #include <atomic>
 #include <type_traits>
 

@@ -457,8 +457,9 @@ def test_backward_launches_of_ragged_layers(P, D, dims, batch, launches):
 
 @pytest.mark.parametrize("steps", [[2, 3, 4], [3, 4, 3], [4, 4, 4]])
 def test_algorithm3_epochs_refresh_no_shadow(P, D, steps):
-    """The last step that every worker takes writes the whole bf16 shadow of W_1 again, which the steps
-    before it left stale: the masked steps read it as it is, with the bits of separate launches."""
+    """Steps whose first layer is fused leave the bf16 shadow of W_1 stale.  It is never written by a launch of its own: the workers that
+    go on have their activation from the fused pass, and those that are done have their shadow from the plain one, with the bits of
+    separate launches."""
     w = small_mlp(dims=(256, 128, 10), batch=32, n_workers=3, gemm_dtype="bf16", activation="tanh", rows_per_worker=256)
     inp = inputs_for(w)
     outs = []
