@@ -6,8 +6,10 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <memory>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "prsgd_aux.h"
@@ -1232,6 +1234,23 @@ int prsgd_init_static(const prsgd_config* cfg, const float* x0_host, const void*
 
 namespace {
 
+// The workers by falling step counts, equal ones in their order: a counting sort over the bytes in which the counts differ.  Two arrays of
+// n, the result in the first.
+void order_by_steps(const int32_t* steps, int n, int32_t k_min, int32_t k_max, int32_t* order, int32_t* spare) {
+  const uint32_t spread = (uint32_t)(k_max - k_min);
+  int32_t *from = order, *to = spare;
+  for (int i = 0; i < n; ++i) from[i] = i;
+  for (int shift = 0; shift < 32 && (spread >> shift) != 0; shift += 8) {
+    int place[257] = {};
+    auto digit = [&](int32_t i) { return ((uint32_t)(k_max - steps[i]) >> shift) & 255u; };
+    for (int i = 0; i < n; ++i) ++place[digit(from[i]) + 1];
+    for (int d = 0; d < 256; ++d) place[d + 1] += place[d];
+    for (int i = 0; i < n; ++i) to[place[digit(from[i])]++] = from[i];
+    std::swap(from, to);
+  }
+  if (from != order) memcpy(order, from, (size_t)n * sizeof(*order));
+}
+
 // k local steps; `last`: nothing of the call comes behind them
 int local_steps(prsgd_ctx* ctx, int32_t k, bool last) {
   if (check_poisoned(ctx) != PRSGD_OK) return PRSGD_ESTATE;
@@ -1329,8 +1348,14 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
   }
   // the step counts, or (layer by layer) the workers by falling step counts
   int* steps_dev = ctx->at<int>(ctx->cv.steps);
-  const hipError_t e = layers ? launch_store_order(steps_dev, steps_host, c.n_workers, ctx->stream)
-                              : launch_store_ints(steps_dev, steps_host, c.n_workers, ctx->stream);
+  std::unique_ptr<int32_t[]> order;
+  if (layers) {
+    order.reset(new (std::nothrow) int32_t[2 * (size_t)c.n_workers]);
+    if (order == nullptr) return set_err(ctx, PRSGD_ENOMEM, "out of host memory");
+    order_by_steps(steps_host, c.n_workers, k_min, k_max, order.get(), order.get() + c.n_workers);
+  }
+  const hipError_t e = launch_store_ints(steps_dev, layers ? order.get() : steps_host, c.n_workers, layers ? c.n_workers - 1 : k_max,
+                                         ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "worker step counts");
   if (c.model == PRSGD_LSQ) {
     LsqArgs a = lsq_args(ctx, k_max);
@@ -1347,10 +1372,10 @@ int prsgd_local_steps_hetero(prsgd_ctx* ctx, const int32_t* steps_host) {
     ctx->t += k_max;
     return PRSGD_OK;
   }
-  auto workers_at = [&](int32_t s) {              // that take step s (from 0)
-    int n = 0;
-    for (int i = 0; i < c.n_workers; ++i) n += steps_host[i] > s ? 1 : 0;
-    return n;
+  int taking = c.n_workers;
+  auto workers_at = [&](int32_t s) {              // that take step s (from 0); s never falls
+    while (taking > 0 && steps_host[order[taking - 1]] <= s) --taking;
+    return taking;
   };
   int rc = PRSGD_OK, idx_set = -1;
   if (k_min == 0 && k_max > 0) ctx->batch_t[0] = ctx->batch_t[1] = -1;   // drawn for workers that take no step as well

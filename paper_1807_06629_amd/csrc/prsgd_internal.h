@@ -219,8 +219,7 @@ hipError_t launch_momentum_update(float* x, float* v, const float* g, uint16_t* 
 hipError_t launch_fill_zero(float* x, size_t count, hipStream_t s);
 hipError_t launch_update_workers(float* x, const float* g, uint16_t* shadow, long m_pad, const int* order,
                                  int n_workers, float lr, hipStream_t s);
-hipError_t launch_store_ints(int* dst, const int* src_host, int count, hipStream_t s);
-hipError_t launch_store_order(int* dst, const int* steps_host, int count, hipStream_t s);
+hipError_t launch_store_ints(int* dst, const int* src_host, int count, int largest, hipStream_t s);
 
 // Least squares: k local iterations of every worker (kernels_lsq.hip).
 struct LsqArgs {

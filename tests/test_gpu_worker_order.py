@@ -115,3 +115,40 @@ def test_an_epoch_is_not_captured(P, D):
         assert np.array_equal(D.read_all(a), D.read_all(b))
     P.prsgd_destroy(a)
     P.prsgd_destroy(b)
+
+
+# numbers of one byte, of two and of four, as many as travel with a launch and one more; step counts further apart than a byte
+@pytest.mark.parametrize("n,last", [(256, 5), (257, 300), (1920, 255), (1921, 256)])
+def test_many_workers_of_unlike_speed(P, D, n, last):
+    steps = [(7 * i) % 5 for i in range(n - 1)] + [last]
+    w = small_mlp(dims=(12, 9, 8, 5), batch=4, n_workers=n, gemm_dtype="f32", activation="tanh", rows_per_worker=8, lr=0.02)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp)
+    D.run_algorithm3(h, steps, 1)
+    want = oracle.run_heterogeneous(**oracle_args(w, inp), lr=w.lr, worker_steps=steps, n_epochs=1)
+    assert rel_err(D.read_all(h), want["x"]) <= 1e-4
+    rows = P.prsgd_read_indices(h)
+    for i in range(n):
+        if steps[i] > 0:
+            assert np.array_equal(rows[i], oracle.sample_rows(w.index_seed, i, steps[i], 4, 8)), i
+    P.prsgd_destroy(h)
+
+
+@pytest.mark.parametrize("n,last", [(3840, 255), (3841, 3), (1921, 256), (961, 65536)])
+def test_many_least_squares_workers_of_unlike_speed(P, D, n, last):
+    """Where a launch takes the step counts themselves."""
+    steps = [(7 * i) % 5 for i in range(n - 1)] + [last]
+    w = small_mlp(model="lsq", dims=(8,), activation="none", batch=4, n_workers=n, n_classes=0, rows_per_worker=8, lr=0.02)
+    inp = inputs_for(w)
+    h = D.open_workload(w, inp)
+    P.prsgd_local_steps_hetero(h, steps)
+    got = D.read_all(h)
+    few = steps[:-1] + [min(last, 300)]
+    want = oracle.run_heterogeneous(**oracle_args(w, inp), lr=w.lr, worker_steps=few, n_epochs=1)["x"]
+    assert rel_err(got[:-1], want[:-1]) <= 1e-4
+    if last <= 300:
+        assert rel_err(got[-1], want[-1]) <= 1e-4
+    else:
+        assert P.prsgd_iteration(h) == last
+        assert np.array_equal(P.prsgd_read_indices(h)[-1], oracle.sample_rows(w.index_seed, n - 1, last, 4, 8))
+    P.prsgd_destroy(h)
