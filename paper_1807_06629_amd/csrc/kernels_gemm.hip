@@ -300,9 +300,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, int block) {
   if constexpr (!kIsDw) out.store(p, g, ks, c_read);
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND, bool MOM>
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
 __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_kernel(GemmArgs p) {
-  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND, MOM>(p, (int)blockIdx.x);
+  gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND, false>(p, (int)blockIdx.x);
 }
 
 // Several products in one launch: product i has the workgroups first[i] .. first[i + 1] - 1 (past the last product: none).
@@ -319,9 +319,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void grouped_gemm_set_kernel(
   gemm_tile<T, BM, BN, WM, WN, WK, S, AKIND, BKIND, MOM>(set.p[i], (int)blockIdx.x - first);
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND, bool MOM = false>
+template <typename T, int BM, int BN, int WM, int WN, int WK, int S, int AKIND, int BKIND>
 static hipError_t launch_one(const GemmArgs& p, int n_groups, hipStream_t s) {
-  return launch_tiles<T, BM, BN, WK, S, WM * WN * WK, grouped_gemm_kernel<T, BM, BN, WM, WN, WK, S, AKIND, BKIND, MOM>>(
+  return launch_tiles<T, BM, BN, WK, S, WM * WN * WK, grouped_gemm_kernel<T, BM, BN, WM, WN, WK, S, AKIND, BKIND>>(
       p, n_groups, s);
 }
 constexpr int kComputeUnits = 256;
