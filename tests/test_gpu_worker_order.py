@@ -88,6 +88,55 @@ def test_first_layer_of_the_workers_that_go_on(P, D, steps, steps_before):
         assert np.array_equal(a, b)
 
 
+def launches_of(P, h):
+    return {r["name"]: r["launches"] for r in P.prsgd_profile_read(h)}
+
+
+@pytest.mark.parametrize("steps_before", [0, 2])
+def test_first_layer_fused_until_too_few_workers_go_on(P, D, steps_before):
+    """24, 21, 8, 3 workers and the first layer fused for 20 and more: the second step multiplies activations that are there, and
+    writes the shadows of its 21 workers alone, which the third step reads of eight of them.  Same bits as with every product apart."""
+    steps = [4 if i % 8 == 3 else 3 if i % 8 in (1, 6) and i < 20 else 1 if i % 8 == 5 else 2 for i in range(24)]
+    assert [sum(s > k for s in steps) for k in range(4)] == [24, 21, 8, 3]
+    w = small_mlp(dims=(1024, 256, 10), batch=32, n_workers=24, gemm_dtype="bf16", activation="relu", rows_per_worker=64)
+    inp = inputs_for(w)
+    outs = []
+    for on in (True, False):
+        h = D.open_workload(w, inp)
+        P.prsgd_set_first_layer_fusion(h, on)
+        P.prsgd_local_steps(h, steps_before)
+        P.prsgd_profile_enable(h, True)
+        P.prsgd_local_steps_hetero(h, steps)
+        assert launches_of(P, h).get("gemm_bwd_first", 0) == (1 if on else 0)
+        P.prsgd_local_steps_hetero(h, steps)              # from points that differ
+        P.prsgd_average(h)
+        P.prsgd_local_steps_hetero(h, steps)              # from the average
+        assert launches_of(P, h).get("gemm_bwd_first", 0) == (2 if on else 0)      # since then
+        P.prsgd_local_steps(h, 2)
+        outs.append((D.read_all(h), P.prsgd_read_loss(h), P.prsgd_read_indices(h)))
+        P.prsgd_destroy(h)
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
+def test_ragged_first_layer_of_the_workers_that_go_on(P, D):
+    """14, 12, 5 workers and a ragged first layer, fused for eleven and more: in each epoch once, for twelve of fourteen."""
+    steps = [3, 2, 1, 2, 3, 2, 2, 3, 1, 2, 3, 2, 3, 2]
+    assert [sum(s > k for s in steps) for k in range(3)] == [14, 12, 5]
+    w = small_mlp(dims=(577, 513, 10), batch=32, n_workers=14, gemm_dtype="bf16", activation="tanh", rows_per_worker=64, lr=0.02)
+    inp = inputs_for(w)
+    want = oracle.run_heterogeneous(**oracle_args(w, inp), lr=w.lr, worker_steps=steps, n_epochs=2)
+    for on in (True, False):
+        h = D.open_workload(w, inp)
+        P.prsgd_set_first_layer_fusion(h, on)
+        P.prsgd_profile_enable(h, True)
+        D.run_algorithm3(h, steps, 2)
+        assert launches_of(P, h).get("gemm_bwd_first", 0) == (2 if on else 0)
+        assert rel_err(D.read_all(h), want["x"]) <= 5e-3
+        assert np.allclose(P.prsgd_read_loss(h), want["losses"], rtol=2e-2, atol=1e-6)
+        P.prsgd_destroy(h)
+
+
 def test_an_epoch_is_not_captured(P, D):
     """Refused before anything is launched; what the graph holds beside it still replays."""
     w = small_mlp(dims=(100, 72, 40, 10), batch=24, n_workers=3, gemm_dtype="bf16", activation="tanh", rows_per_worker=64, lr=0.02)
