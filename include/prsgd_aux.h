@@ -31,10 +31,11 @@ int prsgd_copy_bytes(void* dst_dev, const void* src_dev, size_t bytes, void* hip
 int prsgd_product_tile(int32_t rows, int32_t cols, int32_t n_workers, int32_t gemm_dtype, int32_t* out);
 
 /*
- * Which launches of a configuration mark their weight traffic non-temporal: a sum of the constants
+ * Which launches of a configuration mark their weight traffic (ROWS: the drawn rows) non-temporal: a sum of the constants
  * below.  Host only, for tests.  PRSGD_EINVAL on an invalid configuration.
  */
-enum { PRSGD_STREAM_STEPS = 1, PRSGD_STREAM_STEP_MEAN = 2, PRSGD_STREAM_MEAN = 4, PRSGD_STREAM_AVERAGE = 8 };
+enum { PRSGD_STREAM_STEPS = 1, PRSGD_STREAM_STEP_MEAN = 2, PRSGD_STREAM_MEAN = 4, PRSGD_STREAM_AVERAGE = 8,
+       PRSGD_STREAM_ROWS = 16 };
 int prsgd_streamed_uses(const prsgd_config* cfg);
 
 /*

@@ -1679,7 +1679,7 @@ int prsgd_streamed_uses(const prsgd_config* cfg) {
   if (!build_layout(cfg, &lo, err, sizeof(err))) return set_err(nullptr, PRSGD_EINVAL, "%s", err);
   const Streamed u = streamed_uses(*cfg, lo);
   return (u.steps ? PRSGD_STREAM_STEPS : 0) | (u.step_mean ? PRSGD_STREAM_STEP_MEAN : 0) |
-         (u.mean ? PRSGD_STREAM_MEAN : 0) | (u.average ? PRSGD_STREAM_AVERAGE : 0);
+         (u.mean ? PRSGD_STREAM_MEAN : 0) | (u.average ? PRSGD_STREAM_AVERAGE : 0) | (u.rows ? PRSGD_STREAM_ROWS : 0);
 }
 
 int prsgd_static_scratch(const prsgd_config* cfg) {

@@ -27,7 +27,7 @@ PRSGD_MOM_KEEP, PRSGD_MOM_AVERAGE, PRSGD_MOM_RESET = 0, 1, 2
 PRSGD_MAX_DIMS = 16
 PRSGD_SCRATCH_LAYERS, PRSGD_SCRATCH_EPOCHS, PRSGD_SCRATCH_RUNS = 0, 1, 2
 PRSGD_WAIT_ALONE, PRSGD_WAIT_TOGETHER, PRSGD_WAIT_CROWDED = 0, 1, 2
-PRSGD_STREAM_STEPS, PRSGD_STREAM_STEP_MEAN, PRSGD_STREAM_MEAN, PRSGD_STREAM_AVERAGE = 1, 2, 4, 8
+PRSGD_STREAM_STEPS, PRSGD_STREAM_STEP_MEAN, PRSGD_STREAM_MEAN, PRSGD_STREAM_AVERAGE, PRSGD_STREAM_ROWS = 1, 2, 4, 8, 16
 
 
 class PrsgdError(RuntimeError):

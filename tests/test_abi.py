@@ -97,6 +97,18 @@ def test_streamed_launches_go_by_what_they_rewrite(P, dims, n_workers, steps, st
     assert bool(uses & P.PRSGD_STREAM_STEP_MEAN) == step_mean
 
 
+@pytest.mark.parametrize("dims,n_workers,rows,streamed", [
+    ((3072, 1024, 1024, 10), 16, 1024, False),               # replicas past the last-level cache, shards of 192 MiB
+    ((3072, 1024, 1024, 10), 16, 2048, True),                # ... of 384
+    ((4096, 4096, 4096, 10), 8, 2048, True),                 # ... of exactly 256
+    ((3072, 1024, 1024, 10), 11, 4096, False),               # shards of 528 MiB, but replicas that the cache holds
+    ((256, 128, 10), 64, 8192, False),
+])
+def test_drawn_rows_are_streamed_beside_streamed_steps(P, dims, n_workers, rows, streamed):
+    uses = P.prsgd_streamed_uses(P.make_config(n_workers, "mlp", dims, 64, rows, 0.1, 1, "relu", "bf16"))
+    assert bool(uses & P.PRSGD_STREAM_ROWS) == streamed
+
+
 @pytest.mark.parametrize("dims,n_workers,mean,average", [
     ((3072, 1024, 1024, 10), 11, False, False),              # 177 MiB
     ((3072, 1024, 1024, 10), 16, True, False),               # 257 MiB
