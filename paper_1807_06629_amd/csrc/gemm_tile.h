@@ -381,7 +381,9 @@ static hipError_t launch_tiles(GemmArgs p, int n_groups, hipStream_t s) {
   if (p.k_splits > 1 && p.epi != EPI_FWD_LOGITS) return hipErrorInvalidValue;
   // Weights of a worker's own that one row of tiles covers are read once and not kept: read into the last-level cache, they made it write
   // back what the backward kernels had left there.  8 x 4096-4096-4096-4096-1000, 128 rows: forward launches of the second and third layer 91
-  // and 68 us, 58 and 57 so, of which the backward kernels lose 6 each; 16 iterations 16043 -> 15850 us.  16 x 3072-1024-1024-10, 64 rows, second
+  // and 68 us, 58 and 57 so.  Most of that goes to the launches that still read through the cache, which now find the lines to be written
+  // back: backward kernels of the layers behind the first 200 -> 208 us on average, the logits product (two rows of tiles) 28 -> 35, the loss
+  // head with its draw 9 -> 12; 16 iterations 16043 -> 15850 us.  16 x 3072-1024-1024-10, 64 rows, second
   // layer 15.2 -> 11.3.  Weights that several rows of tiles or all workers read again stay: 8 x (512 x 3072) x 1024 31 us, 38 non-temporal.
   p.b_once = p.streaming && p.b_gs != 0 && p.M <= BM ? 1 : 0;
   const int tiles = place_tiles(&p, BM, BN, n_groups);

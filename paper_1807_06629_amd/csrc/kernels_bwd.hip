@@ -668,7 +668,12 @@ bool bwd_fused_supported(int batch) { return batch >= 1 && batch <= 128; }
 // 45.7 and 46.1; 64 rows, 4 [72] 49.4 and 47.9, 6 [108] 50.7 and 51.9; 128 rows, 6 [108] 63.3 and 60.8, 8 [144] 71.1 and 76.0.  First
 // layers: 2560-1280-43, 64 rows, 2 workers [80] 41.1 and 34.9, 3 [120] 42.1 and 43.9; 128 rows, 4 [160] 57.6 and 53.8.  Short walks stay:
 // 1024-512-512-10, 32 rows, 1 worker 33.3 and 34.9 us.  (1 worker of 4096-2048-2048-512, 64 rows, 89.8 and 67.5.)  With momentum a
-// tile of the walk moves 18 bytes per weight: 3072-1024-1024-10, 64 rows, 1 worker 84.6 and 42.9 us, 4 [64] 88.5 and 83.2.
+// tile of the walk moves 18 bytes per weight: 3072-1024-1024-10, 64 rows, 1 worker 84.6 and 42.9 us, 4 [64] 88.5 and 83.2.  The lines of the
+// other layers are those of plain steps, which hold with momentum too.  Whole tiles, d x d behind 384 inputs, walked and apart: 32 rows, d = 1024,
+// [48] 46.0 and 43.4, [64] 47.0 and 47.8, d = 1536, [48] 54.0 and 51.4, [72] 55.6 and 56.9; 64 rows, 768, [72] 45.6 and 44.4, [84] 46.7 and
+// 47.7, 1024, [64] 50.1 and 49.5, [80] 51.4 and 52.3; 128 rows, 1024, [80] 61.9 and 57.6, [112] 71.3 and 65.6, 1536, [72] 72.2 and 65.6,
+// [96] 78.2 and 80.0.  Ragged ones would repay it further on: 700 x 400, 24 rows, [198] 61.6 and 40.0, [253] 64.3 and 51.0, [297] 70.8 and
+// 57.2; 500 x 1100, 50 rows, [200] 93.6 and 84.6, [256] 106.6 and 101.3; 500 x 600, 50 rows, [200] 70.3 and 51.8, [224] 73.7 and 64.7.
 static bool walk_too_long(const BwdArgs& p) {
   const int n_t = p.Nn / BN, height = p.B <= 32 ? 0 : p.B <= 64 ? 1 : 2;
   const long bands = (long)((p.K + BMK - 1) / BMK) * p.n_groups;
